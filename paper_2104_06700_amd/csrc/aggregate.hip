@@ -756,6 +756,9 @@ template <typename T>
 __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__restrict__ rows, int64_t n_rows,
                                                            const uint32_t *__restrict__ rowbase,
                                                            const float *__restrict__ partial, int64_t n_pieces, int n_slices,
+                                                           const uint32_t *__restrict__ part_base, int64_t n_parts,
+                                                           const float *__restrict__ tile_partial, int n_groups,
+                                                           int64_t tile_group_stride,
                                                            const void *indptr, int ip64, int dst_mode, T *__restrict__ Y,
                                                            int64_t ldy, int fw, int store_vec, int self_mode,
                                                            const OwnRowSrc own,
@@ -794,6 +797,19 @@ __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__rest
                 sum[4 * q] += v[q].x; sum[4 * q + 1] += v[q].y; sum[4 * q + 2] += v[q].z; sum[4 * q + 3] += v[q].w;
             }
         };
+        if (tile_partial) {  // first the partial lines of the row's parts gathered from staged tiles, one per group of tiles
+            const int64_t v0 = part_base[i], n_lines = int64_t(part_base[i + 1] - v0) * n_groups;
+            const float *__restrict__ ts = tile_partial + (int64_t(slice) * n_parts + v0) * LINE + c * VEC;
+            for (int64_t p = g; p < n_lines; p += 8) {
+                const int64_t part = p / n_groups;
+                const float *__restrict__ q = ts + (p - part * n_groups) * tile_group_stride + part * LINE;
+#pragma unroll
+                for (int k = 0; k < VEC; k += 4) {
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(q + k);
+                    sum[k] += v.x; sum[k + 1] += v.y; sum[k + 2] += v.z; sum[k + 3] += v.w;
+                }
+            }
+        }
         for (int64_t p = p0 + g; p < p1; p += 32) {  // four lines per group in flight
             f32x4 v0[VEC / 4], v1[VEC / 4], v2[VEC / 4], v3[VEC / 4];
             load_line(p, v0); load_line(p + 8, v1); load_line(p + 16, v2); load_line(p + 24, v3);
@@ -1282,6 +1298,22 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             if (rc != GNN_OK) return rc;
         }
     }
+    // The densest source blocks are gathered from tiles staged in LDS (tiles.hip), all column slices in one
+    // launch; the pieces of the other blocks follow.
+    const gnn_tiles *tl = nullptr;
+    const float *tile_coefs = nullptr;
+    if (bl.active) {
+        int rc = gnn_plan_tiles(plan, 8, esz == 2, stream, &tl);
+        if (rc != GNN_OK) return rc;
+        if (tl) {
+            if (coef) {
+                rc = gnn_plan_tile_coefs(plan, tl, w, edge_scale, src_mode, w && w == plan->bound_w, stream, &tile_coefs);
+                if (rc != GNN_OK) return rc;
+            }
+            rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), int(line_elems));
+            if (rc != GNN_OK) return rc;
+        }
+    }
     // Own-row term of the finalisation kernels: from the caller's matrix, or from the plan's layout when a
     // producer wrote the matrix there (then already multiplied by the factor the rows carry).
     const int fin_self_mode = (prepacked && factor_in_tables && orig_self_mode == kSelfInvPlus1) ? int(kSelfPlain) : orig_self_mode;
@@ -1332,6 +1364,13 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         side = nullptr;
         return ok;
     };
+
+    const int tile_groups = tl ? gnn_tile_groups(tl, int(layout.main_lines)) : 0;
+    if (tl) {
+        const int rc = gnn_launch_tiles(tl, o.dtype == GNN_BF16, gathered, layout.table_stride * esz, int(layout.main_lines),
+                                        tile_coefs, static_cast<float *>(plan->tile_partial), stream);
+        if (rc != GNN_OK) { finish_overlap(); return rc; }
+    }
 
     for (int gi = 0; gi < n_segs; ++gi) {
         const int64_t f0 = segs[gi].f0, fw = segs[gi].fw;
@@ -1393,12 +1432,12 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             int rc = gnn_plan_blocked_partial(plan, 1 << log2_s, line_floats);
             if (rc != GNN_OK) { finish_overlap(); return rc; }
             PieceArgs pa{};
-            pa.pieces = bl.pieces;
-            pa.n_pieces = bl.n_pieces;
+            pa.pieces = tl ? tl->left.pieces : bl.pieces;
+            pa.n_pieces = tl ? tl->left.n_pieces : bl.n_pieces;
             pa.idx = bl.indices;
             pa.epos = bl.epos;
             pa.idx16 = bl.idx16;
-            pa.piece_block = bl.piece_block;
+            pa.piece_block = tl ? tl->left.piece_block : bl.piece_block;
             pa.n_blocks = bl.n_blocks;
             pa.hot_lines = bl.hot_lines;
             pa.block_lines = bl.block_lines;
@@ -1409,24 +1448,31 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             pa.slice_stride = layout.table_stride;
             pa.partial = static_cast<float *>(plan->blk_partial);
             pa.log2_slices = log2_s;
-            const int64_t pblocks = ((bl.n_pieces + 8 * kWavesPerBlock - 1) / (8 * kWavesPerBlock)) << log2_s;
+            const int64_t pblocks = ((pa.n_pieces + 8 * kWavesPerBlock - 1) / (8 * kWavesPerBlock)) << log2_s;
             if (pblocks > INT32_MAX) { finish_overlap(); return GNN_ERR_UNSUPPORTED; }
             const int n_sl = 1 << log2_s;
             const dim3 pgrid(static_cast<unsigned>(pblocks)), fgrid(static_cast<unsigned>((bl.n_hot * n_sl * 8 + 255) / 256));
             const int32_t *hot_rows = plan->row_perm + bl.hot_begin;
             const OwnRowSrc own = own_row_src(f0);
+            const float *tile_partial = tl ? static_cast<const float *>(plan->tile_partial) + f0 / line_elems * tl->n_parts * line_floats : nullptr;
+            const int64_t tile_group_stride = tl ? layout.main_lines * tl->n_parts * line_floats : 0;
+            const uint32_t *rowbase = tl ? tl->left.rowbase : bl.rowbase, *part_base = tl ? tl->part_base : nullptr;
             if (o.dtype == GNN_F32) {
-                if (coef) piece_kernel<float, true><<<pgrid, kBlockThreads, 0, stream>>>(pa);
+                if (pa.n_pieces == 0) {}
+                else if (coef) piece_kernel<float, true><<<pgrid, kBlockThreads, 0, stream>>>(pa);
                 else piece_kernel<float, false><<<pgrid, kBlockThreads, 0, stream>>>(pa);
                 blk_finalize_kernel<float><<<fgrid, 256, 0, stream>>>(
-                    hot_rows, bl.n_hot, bl.rowbase, pa.partial, bl.n_pieces, n_sl, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
+                    hot_rows, bl.n_hot, rowbase, pa.partial, pa.n_pieces, n_sl, part_base, tl ? tl->n_parts : 0, tile_partial, tile_groups,
+                    tile_group_stride, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
                     static_cast<float *>(out) + f0, ldy, int(fw), store_vec, fin_self_mode, own,
                     plan->col_counts, bias ? bias + f0 : nullptr, relu);
             } else {
-                if (coef) piece_kernel<bf16_t, true><<<pgrid, kBlockThreads, 0, stream>>>(pa);
+                if (pa.n_pieces == 0) {}
+                else if (coef) piece_kernel<bf16_t, true><<<pgrid, kBlockThreads, 0, stream>>>(pa);
                 else piece_kernel<bf16_t, false><<<pgrid, kBlockThreads, 0, stream>>>(pa);
                 blk_finalize_kernel<bf16_t><<<fgrid, 256, 0, stream>>>(
-                    hot_rows, bl.n_hot, bl.rowbase, pa.partial, bl.n_pieces, n_sl, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
+                    hot_rows, bl.n_hot, rowbase, pa.partial, pa.n_pieces, n_sl, part_base, tl ? tl->n_parts : 0, tile_partial, tile_groups,
+                    tile_group_stride, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
                     static_cast<bf16_t *>(out) + f0, ldy, int(fw), store_vec, fin_self_mode, own,
                     plan->col_counts, bias ? bias + f0 : nullptr, relu);
             }

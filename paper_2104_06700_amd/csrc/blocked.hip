@@ -184,6 +184,46 @@ bool dev_alloc(T **p, int64_t n) { return hipMalloc(p, sizeof(T) * size_t(n > 0 
 
 }  // namespace
 
+// Piece descriptors from a table of edge counts and piece counts per (block, row): cell_pieces is overwritten with its prefix
+// sums, `sums` is scan scratch.  Synchronous; on failure nothing is left allocated.
+int gnn_build_pieces(int64_t n_hot, int n_blocks, int64_t max_piece, const uint32_t *cell_count, const uint32_t *edge_off,
+                     uint32_t *cell_pieces, uint32_t *sums, bool want_block, hipStream_t stream, gnn_piece_list *out) {
+    *out = gnn_piece_list{};
+    const int64_t n_cells = int64_t(n_blocks) * n_hot;
+    gnn_piece_list L{};
+    uint32_t *row_prefix = nullptr;
+    auto fail = [&](int s) {
+        (void)hipStreamSynchronize(stream);
+        (void)hipFree(row_prefix); (void)hipFree(L.pieces); (void)hipFree(L.piece_block); (void)hipFree(L.rowbase);
+        return s;
+    };
+    if (!dev_alloc(&row_prefix, n_cells) || !dev_alloc(&L.rowbase, n_hot + 1)) return fail(GNN_ERR_ALLOC);
+    (void)hipGetLastError();
+    blk_row_prefix_kernel<<<grid_for(n_hot, 256, INT32_MAX), 256, 0, stream>>>(n_hot, n_blocks, cell_pieces, row_prefix, L.rowbase);
+    if (hipGetLastError() != hipSuccess) return fail(GNN_ERR_LAUNCH);
+    // block-major offsets of the cells' pieces; partial slots of the rows
+    uint32_t last_cell_pieces = 0, last_piece_off = 0, last_row = 0, last_rowbase = 0;
+    int rc = GNN_OK;
+    if (hipMemcpyAsync(&last_cell_pieces, cell_pieces + n_cells - 1, 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
+    if (hipMemcpyAsync(&last_row, L.rowbase + n_hot - 1, 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
+    if ((rc = gnn_scan_exclusive_u32(cell_pieces, n_cells, sums, stream)) != GNN_OK) return fail(rc);
+    if ((rc = gnn_scan_exclusive_u32(L.rowbase, n_hot, sums, stream)) != GNN_OK) return fail(rc);
+    if (hipMemcpyAsync(&last_piece_off, cell_pieces + n_cells - 1, 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
+    if (hipMemcpyAsync(&last_rowbase, L.rowbase + n_hot - 1, 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
+    if (hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
+    L.n_pieces = int64_t(last_piece_off) + last_cell_pieces;
+    const uint32_t total_slots = last_rowbase + last_row;
+    if (int64_t(total_slots) != L.n_pieces || L.n_pieces >= int64_t(INT32_MAX)) return fail(GNN_ERR_LAUNCH);
+    if (hipMemcpyAsync(L.rowbase + n_hot, &total_slots, 4, hipMemcpyHostToDevice, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
+    if (!dev_alloc(&L.pieces, 4 * L.n_pieces) || (want_block && !dev_alloc(&L.piece_block, L.n_pieces))) return fail(GNN_ERR_ALLOC);
+    blk_fill_pieces_kernel<<<grid_for(n_cells, 256), 256, 0, stream>>>(n_hot, n_blocks, max_piece, cell_count, edge_off, cell_pieces,
+                                                                      row_prefix, L.rowbase, L.pieces, L.piece_block);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
+    (void)hipFree(row_prefix);
+    *out = L;
+    return GNN_OK;
+}
+
 extern "C" GNN_API int gnn_plan_set_blocking(gnn_plan *plan, const gnn_blocking_params *params) {
     if (!plan) return GNN_ERR_INVALID_ARG;
     if (plan->blk_decided) return GNN_ERR_UNSUPPORTED;
@@ -285,9 +325,14 @@ extern "C" GNN_API int gnn_plan_bind_edge_weights(gnn_plan *plan, const float *e
     if (!plan) return GNN_ERR_INVALID_ARG;
     plan->bound_w = edge_w;
     plan->bound_w_stale = true;
+    ++plan->bound_w_version;
     if (edge_w && plan->blk_decided && plan->blk_n_pieces > 0) {
         const float *unused = nullptr;
-        return gnn_plan_blocked_bound_weights(plan, static_cast<hipStream_t>(stream), &unused);
+        int rc = gnn_plan_blocked_bound_weights(plan, static_cast<hipStream_t>(stream), &unused);
+        for (const gnn_tiles &t : plan->tiles)
+            if (rc == GNN_OK && t.active && t.bound_w)
+                rc = gnn_plan_tile_coefs(plan, &t, edge_w, nullptr, 0, true, static_cast<hipStream_t>(stream), &unused);
+        return rc;
     }
     return GNN_OK;
 }
@@ -347,22 +392,22 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             (void)hipGetLastError();
             const int64_t n_cells = int64_t(m.n_blocks) * n_hot;
             uint32_t *h_of = nullptr, *buf_k[2] = {nullptr, nullptr}, *buf_v[2] = {nullptr, nullptr}, *table = nullptr, *sums = nullptr;
-            uint32_t *cell_start = nullptr, *cell_count = nullptr, *cell_pieces = nullptr, *edge_off = nullptr, *row_prefix = nullptr;
-            uint32_t *rowbase = nullptr, *blk_epos = nullptr;
-            int32_t *blk_indices = nullptr, *pieces = nullptr;
+            uint32_t *cell_start = nullptr, *cell_count = nullptr, *cell_pieces = nullptr, *edge_off = nullptr;
+            uint32_t *blk_epos = nullptr;
+            int32_t *blk_indices = nullptr;
             uint16_t *blk_idx16 = nullptr;
-            uint16_t *piece_block = nullptr;
+            gnn_piece_list list{};
             const bool narrow = m.hot <= 65536 && m.block <= 65536;
             auto cleanup_tmp = [&]() {
                 (void)hipFree(h_of); (void)hipFree(buf_k[0]); (void)hipFree(buf_k[1]); (void)hipFree(buf_v[0]); (void)hipFree(buf_v[1]);
                 (void)hipFree(table); (void)hipFree(sums); (void)hipFree(cell_start); (void)hipFree(cell_count);
-                (void)hipFree(cell_pieces); (void)hipFree(edge_off); (void)hipFree(row_prefix);
+                (void)hipFree(cell_pieces);
             };
             auto fail = [&](int s) {
                 (void)hipStreamSynchronize(stream);
                 cleanup_tmp();
-                (void)hipFree(rowbase); (void)hipFree(blk_epos); (void)hipFree(blk_indices); (void)hipFree(pieces);
-                (void)hipFree(blk_idx16); (void)hipFree(piece_block);
+                (void)hipFree(list.rowbase); (void)hipFree(blk_epos); (void)hipFree(blk_indices); (void)hipFree(list.pieces);
+                (void)hipFree(blk_idx16); (void)hipFree(list.piece_block); (void)hipFree(edge_off);
                 return s;
             };
             const int64_t scan_n = n_cells > n_hot + 1 ? n_cells : n_hot + 1;
@@ -371,7 +416,7 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
                       dev_alloc(&buf_v[0], n_edges) && dev_alloc(&buf_v[1], n_edges) &&
                       dev_alloc(&table, gnn_sort_table_elems(n_edges)) && dev_alloc(&sums, sums_n) &&
                       dev_alloc(&cell_start, n_cells) && dev_alloc(&cell_count, n_cells) && dev_alloc(&cell_pieces, n_cells + 1) &&
-                      dev_alloc(&edge_off, n_cells + 1) && dev_alloc(&row_prefix, n_cells) && dev_alloc(&rowbase, n_hot + 1) &&
+                      dev_alloc(&edge_off, n_cells + 1) &&
                       dev_alloc(&blk_indices, n_edges + kStreamPad) && dev_alloc(&blk_epos, n_edges + kStreamPad);
             if (ok && narrow) ok = dev_alloc(&blk_idx16, n_edges + kStreamPad);
             if (!ok) return fail(GNN_ERR_ALLOC);
@@ -393,27 +438,14 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
                 reinterpret_cast<const uint32_t *>(plan->rank_indices + p0), sorted_pos, n_edges, 0x7FFFFFFFu, sorted_r);
             blk_cells_kernel<<<grid_for(n_cells, 256), 256, 0, stream>>>(plan->p_indptr, hot_begin, n_hot, p0, sorted_r, m,
                                                                         prm.max_piece, cell_start, cell_count, cell_pieces);
-            blk_row_prefix_kernel<<<grid_for(n_hot, 256, INT32_MAX), 256, 0, stream>>>(n_hot, m.n_blocks, cell_pieces, row_prefix, rowbase);
             if (hipGetLastError() != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            // block-major offsets of the cells' edges and pieces; partial slots of the rows
+            // block-major offsets of the cells' edges
             if ((hipMemcpyAsync(edge_off, cell_count, sizeof(uint32_t) * n_cells, hipMemcpyDeviceToDevice, stream)) != hipSuccess) return fail(GNN_ERR_LAUNCH);
             if ((rc = gnn_scan_exclusive_u32(edge_off, n_cells, sums, stream)) != GNN_OK) return fail(rc);
-            uint32_t last_cell_pieces = 0, last_piece_off = 0, last_row = 0, last_rowbase = 0;
-            if ((hipMemcpyAsync(&last_cell_pieces, cell_pieces + n_cells - 1, 4, hipMemcpyDeviceToHost, stream)) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            if ((hipMemcpyAsync(&last_row, rowbase + n_hot - 1, 4, hipMemcpyDeviceToHost, stream)) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            if ((rc = gnn_scan_exclusive_u32(cell_pieces, n_cells, sums, stream)) != GNN_OK) return fail(rc);
-            if ((rc = gnn_scan_exclusive_u32(rowbase, n_hot, sums, stream)) != GNN_OK) return fail(rc);
-            if ((hipMemcpyAsync(&last_piece_off, cell_pieces + n_cells - 1, 4, hipMemcpyDeviceToHost, stream)) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            if ((hipMemcpyAsync(&last_rowbase, rowbase + n_hot - 1, 4, hipMemcpyDeviceToHost, stream)) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            if (hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            const int64_t n_pieces = int64_t(last_piece_off) + last_cell_pieces;
-            const uint32_t total_slots = last_rowbase + last_row;
-            if (int64_t(total_slots) != n_pieces || n_pieces <= 0 || n_pieces >= int64_t(INT32_MAX)) return fail(GNN_ERR_LAUNCH);
-            if ((hipMemcpyAsync(rowbase + n_hot, &total_slots, 4, hipMemcpyHostToDevice, stream)) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            if (!dev_alloc(&pieces, 4 * n_pieces)) return fail(GNN_ERR_ALLOC);
-            if (narrow && !dev_alloc(&piece_block, n_pieces)) return fail(GNN_ERR_ALLOC);
-            blk_fill_pieces_kernel<<<grid_for(n_cells, 256), 256, 0, stream>>>(n_hot, m.n_blocks, prm.max_piece, cell_count, edge_off,
-                                                                              cell_pieces, row_prefix, rowbase, pieces, piece_block);
+            const uint32_t all_edges = uint32_t(n_edges);
+            if ((hipMemcpyAsync(edge_off + n_cells, &all_edges, 4, hipMemcpyHostToDevice, stream)) != hipSuccess) return fail(GNN_ERR_LAUNCH);
+            if ((rc = gnn_build_pieces(n_hot, m.n_blocks, prm.max_piece, cell_count, edge_off, cell_pieces, sums, narrow, stream, &list)) != GNN_OK) return fail(rc);
+            if (list.n_pieces <= 0) return fail(GNN_ERR_LAUNCH);
             blk_scatter_edges_kernel<<<grid_for(n_edges, 256), 256, 0, stream>>>(n_edges, h_of, sorted_r, sorted_pos, plan->p_indptr,
                                                                                 hot_begin, n_hot, p0, plan->row_perm, indptr,
                                                                                 plan->indptr_is_64, m, cell_start, edge_off,
@@ -425,16 +457,19 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             plan->blk_hot_begin = hot_begin;
             plan->blk_n_hot = n_hot;
             plan->blk_n_edges = n_edges;
-            plan->blk_n_pieces = n_pieces;
+            plan->blk_n_pieces = list.n_pieces;
             plan->blk_n_blocks = m.n_blocks;
             plan->blk_indices = blk_indices;
             plan->blk_epos = blk_epos;
             plan->blk_idx16 = blk_idx16;
-            plan->blk_piece_block = piece_block;
+            plan->blk_piece_block = list.piece_block;
             plan->blk_hot_lines = m.hot;
             plan->blk_block_lines = m.block;
-            plan->blk_pieces = pieces;
-            plan->blk_rowbase = rowbase;
+            plan->blk_rest_begin = m.rest_begin;
+            plan->blk_max_piece = int32_t(prm.max_piece);
+            plan->blk_cell_off = edge_off;
+            plan->blk_pieces = list.pieces;
+            plan->blk_rowbase = list.rowbase;
         }
         plan->blk_decided = 1;
     }

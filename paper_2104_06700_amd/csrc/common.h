@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "gnnagg.h"
 
 #define GNN_HIP_TRY(expr)                                  \
@@ -13,6 +15,36 @@
     } while (0)
 
 #define GNN_MAX_BINS (GNN_MAX_THRESHOLDS + 1)
+
+// Source tiles in LDS (tiles.hip): the edges of the long rows into the source blocks where they are dense, as one
+// stream per wavefront of the gather, and the piece list of the rest.  One layout per line width (lanes of 16 bytes
+// per row); built on first use.
+constexpr int GNN_TILE_MAX_GROUPS = 16;
+struct gnn_piece_list {
+    int32_t *pieces = nullptr;        // [n_pieces * 4] (begin, length, partial slot, row)
+    uint16_t *piece_block = nullptr;  // [n_pieces]
+    uint32_t *rowbase = nullptr;      // [n_hot + 1] first partial slot of every row
+    int64_t n_pieces = 0;
+};
+struct gnn_tiles {
+    bool decided = false, active = false;
+    int32_t lanes = 0, rr = 0, n_tiles = 0;  // rr: bundles of rows a wavefront owns at most
+    int64_t n_row_blocks = 0, n_waves = 0, n_iters = 0;
+    int64_t n_parts = 0;                 // rows, long ones cut into parts: each has a partial line per launch and group
+    uint32_t *part_base = nullptr;       // [n_hot + 1] first part of every row
+    uint32_t *order = nullptr;           // [n_parts] parts by size
+    void *tiles = nullptr;               // [n_tiles] (first rank, ranks, block)
+    void *seg = nullptr;                 // [n_tiles][n_parts] edge range of the part at a position of `order`
+    uint16_t *stream = nullptr;
+    uint8_t *counts = nullptr;           // [n_waves][n_tiles][16]
+    uint32_t *wave_off = nullptr;        // [n_waves][n_tiles]
+    std::vector<int64_t> tile_work;      // iterations per tile (host)
+    gnn_piece_list left;                 // the cells that are not staged
+    float *scale[3] = {nullptr, nullptr, nullptr};  // the plan's per-edge factors in stream order
+    float *bound_w = nullptr;            // bound edge weights in stream order, as of binding number bound_version
+    int64_t bound_version = -1;
+    float *tmp_w = nullptr;              // other coefficients, refilled by every call
+};
 
 // One plan = one graph orientation.  All pointers are device memory owned by
 // the plan unless marked host.
@@ -83,7 +115,8 @@ struct gnn_plan {
     // when a block spans more than 65,536 ranks.  blk_piece_block[p] = block of piece p.
     uint16_t *blk_idx16 = nullptr;
     uint16_t *blk_piece_block = nullptr;
-    int32_t blk_hot_lines = 0, blk_block_lines = 0;
+    int32_t blk_hot_lines = 0, blk_block_lines = 0, blk_rest_begin = 0, blk_max_piece = 0;
+    uint32_t *blk_cell_off = nullptr; // [blk_n_blocks * blk_n_hot + 1] first edge of every (block, hot row)
     int32_t *blk_pieces = nullptr;    // [blk_n_pieces * 4] (begin, length, partial slot, row index in the hot range)
     uint32_t *blk_rowbase = nullptr;  // [blk_n_hot + 1] first partial slot of each hot row
     float *blk_edge_scale[3] = {nullptr, nullptr, nullptr};  // edge_scale[m] at blk_epos, i.e. in the order of blk_indices
@@ -93,8 +126,12 @@ struct gnn_plan {
     const float *bound_w = nullptr;
     float *blk_bound_w = nullptr;
     bool bound_w_stale = false;       // the copy is older than the last binding
+    int64_t bound_w_version = 0;      // number of the last binding
     void *blk_partial = nullptr;      // fp32 partial sums of one launch: [slices][blk_n_pieces][floats per line]
     int64_t blk_partial_bytes = 0;
+    gnn_tiles tiles[6];               // for lines of 128, 64 and 32 bytes of fp32, then of bf16
+    void *tile_partial = nullptr;     // their partial lines: [groups][slices][hot rows][floats per line]
+    int64_t tile_partial_bytes = 0;
 };
 
 // Source blocking (the GPU reading of Section 4.2's blocks of source vertices, applied to the long
@@ -130,6 +167,21 @@ int gnn_plan_blocked_edge_scale(gnn_plan *plan, int mode, hipStream_t stream, co
 // The bound edge weights in piece order: refreshed on `stream` when a binding is newer than the copy
 // (allocates on first use).  Needs the layout and a binding.
 int gnn_plan_blocked_bound_weights(gnn_plan *plan, hipStream_t stream, const float **out);
+
+// The tile layout for lines of lanes * 16 bytes (null: the graph has no block dense enough); needs the blocked layout.
+int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, hipStream_t stream, const gnn_tiles **out);
+void gnn_tiles_free(gnn_tiles &t);
+// Coefficients w[e] * scale[e] (either may be null; CSR order) in stream order.
+int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles, const float *w, const float *scale, int scale_mode, bool bound,
+                        hipStream_t stream, const float **out);
+// Groups a launch over n_slices column slices splits the tiles into, each with a partial line of its own per row.
+int gnn_tile_groups(const gnn_tiles *t, int n_slices);
+// Makes plan->tile_partial large enough for such a launch.
+int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats);
+int gnn_build_pieces(int64_t n_hot, int n_blocks, int64_t max_piece, const uint32_t *cell_count, const uint32_t *edge_off,
+                     uint32_t *cell_pieces, uint32_t *sums, bool want_block, hipStream_t stream, gnn_piece_list *out);
+int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,
+                     const float *coefs, float *partial, hipStream_t stream);
 
 // Stable LSD radix sort of 32-bit (key, value) pairs on the low `bits` bits (graph.hip).  buf_k[0] /
 // buf_v[0] hold the input (first_keys, if given, replaces buf_k[0] as read-only input of the first

@@ -498,9 +498,17 @@ extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, 
                     while (slices < 8 && slices * 2 <= layout.main_lines) slices *= 2;
                     rc = gnn_plan_blocked_partial(plan, slices, 128 / esz);
                     if (rc != GNN_OK) return rc;
+                    const gnn_tiles *tl = nullptr;  // and the part of them that is staged in LDS
+                    rc = gnn_plan_tiles(plan, 8, esz == 2, static_cast<hipStream_t>(stream), &tl);
+                    if (rc != GNN_OK) return rc;
+                    if (tl) {
+                        rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), 128 / esz);
+                        if (rc != GNN_OK) return rc;
+                    }
                     if (plan->bound_w) {
                         const float *unused_w = nullptr;
                         rc = gnn_plan_blocked_bound_weights(plan, static_cast<hipStream_t>(stream), &unused_w);
+                        if (rc == GNN_OK && tl) rc = gnn_plan_tile_coefs(plan, tl, plan->bound_w, nullptr, 0, true, static_cast<hipStream_t>(stream), &unused_w);
                         if (rc != GNN_OK) return rc;
                     }
                 }
@@ -518,6 +526,9 @@ extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, 
         // ... and in the order of the source-blocked pieces, for the calls that read it there
         if (rc == GNN_OK && plan->blk_decided && plan->blk_n_pieces > 0 && plan->n_edges > 0)
             rc = gnn_plan_blocked_edge_scale(plan, mode, static_cast<hipStream_t>(stream), &unused);
+        for (const gnn_tiles &t : plan->tiles)
+            if (rc == GNN_OK && t.active && plan->n_edges > 0)
+                rc = gnn_plan_tile_coefs(plan, &t, nullptr, plan->edge_scale[mode - 1], mode, false, static_cast<hipStream_t>(stream), &unused);
     }
     return rc;
 }
@@ -541,6 +552,9 @@ extern "C" GNN_API void gnn_plan_destroy(gnn_plan *plan) {
     (void)hipFree(plan->blk_pieces);
     (void)hipFree(plan->blk_rowbase);
     (void)hipFree(plan->blk_partial);
+    (void)hipFree(plan->blk_cell_off);
+    for (gnn_tiles &t : plan->tiles) gnn_tiles_free(t);
+    (void)hipFree(plan->tile_partial);
     for (int i = 0; i < 3; ++i) (void)hipFree(plan->blk_edge_scale[i]);
     (void)hipFree(plan->blk_bound_w);
     (void)hipFree(plan->row_perm);

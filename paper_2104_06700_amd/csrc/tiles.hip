@@ -1,0 +1,785 @@
+// Gather of the long rows from source tiles staged in LDS.
+//
+// The pieces of blocked.hip gather a block of sources from an L2, one 128-byte request per edge, and the
+// request rate of the L2s (about 160 G lines/s over the chip, 20 TB/s) bounds them.  Where the long rows have
+// many edges into a block, a second level of blocking pays: a workgroup copies a tile of the block's sources
+// (124 KB: 991 lines of 128 bytes, or more shorter ones) into LDS once, and all the rows it owns gather their
+// edges into that tile from there; then the next tile.  The sums stay in registers from the first tile to the
+// last, so a row writes one partial line per launch and not one per piece.
+//
+// A workgroup is 16 wavefronts; L lanes (16 bytes each: L = 8, 4 or 2 for lines of 128, 64 or 32 bytes) own a
+// row, so a wavefront works on a bundle of 64 / L rows at a time, and it owns up to ten bundles.  The lists are
+// stored the way they are read, one stream per wavefront: for every tile, for every bundle of the wavefront, units
+// of four edges per row as 16-bit offsets into the tile; the shorter rows of a bundle are filled up with the
+// offset of a line of zeros behind the tile.  Rows are bundled by similar number of edges, a row much longer
+// than the mean is cut into parts (else it alone would set the time of its workgroup: worst workgroup 4.1 x the
+// mean without, 1.02 x with), and the bundles are dealt to the wavefronts like cards.
+//
+// What bounds it: LDS reads, 128 bytes per clock and compute unit (two halves of a line never share a bank, so
+// 128-byte lines are read without conflicts), 66 clocks per eight edges of a wavefront's rows, against 47
+// clocks of vector instructions (one multiply-add per LDS address, one add per element).  Measured on the 233
+// K-vertex graph (95.6 M of 114.6 M edges staged, 85 % of the slots filled): F=602, 19 lines, 4.45 ms = 52
+// TB/s of lines wanted, 61 TB/s read, where the same edges as pieces took 9.5 ms; the call 11.45 -> 7.8 ms.
+// The 2.45 M-vertex graph (56 of 124 M edges): F=256 1.4 ms for 2.8; the call, which the short rows bound, 9.15 -> 8.4 ms.
+#include <type_traits>
+#include <vector>
+
+#include "common.h"
+
+namespace {
+
+constexpr int kTileThreads = 1024;
+constexpr int kTileWaves = kTileThreads / 64;
+constexpr int kCounts = 16;        // bytes of counts per wavefront and tile (bundles it owns at most)
+// Bundles of rows a wavefront owns at most: as many sums as four wavefronts per SIMD leave registers for.
+constexpr int kBundlesF32 = 10, kBundlesBf16 = 8;
+constexpr int kUnit = 4;          // edges per row in a unit of the streams
+
+constexpr int64_t kFewBundles = 5;      // bundles per wavefront before rows are dealt to more workgroups
+constexpr int64_t kRowBlocks = 64;     // workgroups the rows are dealt to at least (per column slice)
+constexpr int64_t kComputeUnits = 256;
+// A row is staged in a block where it has this many edges per tile (a staged line costs about a third of a gathered
+// one, but a row's list is filled up to whole units and to the longest of its bundle: 5 and 7 measure alike, 4 no better) ...
+constexpr int64_t kMinRowEdges = 5;
+// ... and a block where those rows have this many edges per tile and workgroup of rows: what copying the tile costs
+// (2.45 M vertices: 2,800 and 5,000 within 1 %, 8,000 slower; weighted graph of 133 K vertices F=64 2.89 ms with 2,800, 2.79 with 5,000).
+constexpr int64_t kMinTileEdges = 5000;
+constexpr int kStreamAhead = 64;  // units of padding behind a stream (the loads run up to 2 KB ahead)
+
+int grid_for(int64_t n, int block, int64_t cap = (int64_t(1) << 16)) {
+    int64_t g = (n + block - 1) / block;
+    if (g < 1) g = 1;
+    if (g > cap) g = cap;
+    return static_cast<int>(g);
+}
+
+struct TileDesc { int32_t begin, size, block, pad; };
+
+// Number of bundle r of wavefront w in a list sorted by size, or -1: dealt from the largest down, forwards, then
+// backwards, so that wavefronts get equal loads; neighbours in the list go to different workgroups.
+__host__ __device__ __forceinline__ int64_t dealt_bundle(int64_t w, int r, int64_t n_waves, int64_t n_bundles) {
+    const int64_t at = (w % kTileWaves) * (n_waves / kTileWaves) + w / kTileWaves;
+    const int64_t k = int64_t(r) * n_waves + ((r & 1) ? n_waves - 1 - at : at);
+    return n_bundles - 1 - k;
+}
+
+// The cells (block, row) that are worth staging: block_min[k] = edges a row needs in block k for that (0: none).
+struct DenseRule {
+    const uint32_t *cell_off;
+    const uint32_t *block_min;
+    int64_t n_hot;
+    __device__ __forceinline__ uint32_t edges(int k, int64_t h) const {
+        const int64_t c = int64_t(k) * n_hot + h;
+        const uint32_t n = cell_off[c + 1] - cell_off[c];
+        const uint32_t least = block_min[k];
+        return least && n >= least ? n : 0u;
+    }
+};
+
+// sums[k] += edges of the dense cells of block k (blockIdx.y)
+__global__ void __launch_bounds__(256) tile_block_edges_kernel(DenseRule rule, unsigned long long *__restrict__ sums) {
+    __shared__ unsigned long long part[256];
+    const int k = blockIdx.y;
+    unsigned long long s = 0;
+    for (int64_t h = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; h < rule.n_hot; h += int64_t(gridDim.x) * blockDim.x) s += rule.edges(k, h);
+    part[threadIdx.x] = s;
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+        if (int(threadIdx.x) < off) part[threadIdx.x] += part[threadIdx.x + off];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && part[0]) atomicAdd(&sums[k], part[0]);
+}
+
+// staged[h] = edges of hot row h in its dense cells; n_staged += rows that have any
+__global__ void __launch_bounds__(256) tile_row_edges_kernel(DenseRule rule, int n_blocks, uint32_t *__restrict__ staged,
+                                                             uint32_t *__restrict__ n_staged) {
+    const int64_t h = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    uint32_t s = 0;
+    if (h < rule.n_hot) {
+        for (int k = 0; k < n_blocks; ++k) s += rule.edges(k, h);
+        staged[h] = s;
+    }
+    const unsigned long long m = __ballot(s != 0);
+    if ((threadIdx.x & 63) == 0 && m) atomicAdd(n_staged, uint32_t(__popcll(m)));
+}
+
+// parts[h] = parts that row h is cut into (a row much longer than the others would keep its workgroup waiting)
+__global__ void __launch_bounds__(256) tile_row_parts_kernel(const uint32_t *__restrict__ staged, int64_t n_hot, uint32_t cap,
+                                                             uint32_t *__restrict__ parts) {
+    const int64_t h = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (h < n_hot) parts[h] = (staged[h] + cap - 1) / cap;
+}
+
+// The parts of every row: row, number within the row, parts of the row; and what they are sorted by.
+struct RowPart { uint32_t row, part, parts; };
+__global__ void __launch_bounds__(256) tile_parts_kernel(const uint32_t *__restrict__ staged, const uint32_t *__restrict__ part_base,
+                                                         int64_t n_hot, uint32_t cap, RowPart *__restrict__ out,
+                                                         uint32_t *__restrict__ keys, uint32_t *__restrict__ ids) {
+    const int64_t h = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (h >= n_hot) return;
+    const uint32_t n = (staged[h] + cap - 1) / cap;
+    for (uint32_t j = 0; j < n; ++j) {
+        const uint32_t v = part_base[h] + j;
+        out[v] = RowPart{uint32_t(h), j, n};
+        keys[v] = staged[h] / n;
+        ids[v] = v;
+    }
+}
+
+// Piece counts of the cells that stay pieces (0 where a cell is staged), and the edge counts they are cut from.
+__global__ void __launch_bounds__(256) tile_left_cells_kernel(DenseRule rule, int n_blocks, uint32_t max_piece,
+                                                              uint32_t *__restrict__ cell_count, uint32_t *__restrict__ cell_pieces) {
+    const int64_t n_cells = int64_t(n_blocks) * rule.n_hot;
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t c = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; c < n_cells; c += stride) {
+        const int k = int(c / rule.n_hot);
+        const uint32_t n = rule.edges(k, c - int64_t(k) * rule.n_hot) ? 0u : rule.cell_off[c + 1] - rule.cell_off[c];
+        cell_count[c] = n;
+        cell_pieces[c] = (n + max_piece - 1) / max_piece;
+    }
+}
+
+// first position in [lo, hi) of the ascending list r whose rank is >= bound
+__device__ __forceinline__ uint32_t lower_bound_in(const int32_t *__restrict__ r, uint32_t lo, uint32_t hi, int32_t bound) {
+    while (lo < hi) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if (r[mid] < bound) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// seg[t * n_parts + i] = (begin, end) in the block-major edge list of the edges of row part order[i] into tile t
+__global__ void __launch_bounds__(256) tile_segments_kernel(const TileDesc *__restrict__ tiles, int n_tiles, DenseRule rule,
+                                                            const uint32_t *__restrict__ order, const RowPart *__restrict__ parts,
+                                                            int64_t n_parts, const int32_t *__restrict__ blk_indices,
+                                                            uint2 *__restrict__ seg) {
+    const int64_t total = int64_t(n_tiles) * n_parts;
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < total; x += stride) {
+        const int t = int(x / n_parts);
+        const RowPart p = parts[order[x - int64_t(t) * n_parts]];
+        const TileDesc d = tiles[t];
+        uint2 s = make_uint2(0u, 0u);
+        if (rule.edges(d.block, p.row)) {
+            const int64_t c = int64_t(d.block) * rule.n_hot + p.row;
+            const uint32_t lo = rule.cell_off[c], hi = rule.cell_off[c + 1];
+            const uint32_t b = lower_bound_in(blk_indices, lo, hi, d.begin);
+            const uint64_t len = lower_bound_in(blk_indices, b, hi, d.begin + d.size) - b;
+            s.x = b + uint32_t(len * p.part / p.parts);
+            s.y = b + uint32_t(len * (p.part + 1) / p.parts);
+        }
+        seg[x] = s;
+    }
+}
+
+// One thread per (wavefront, tile): iterations of each of its bundles there, and their sum.
+__global__ void __launch_bounds__(256) tile_counts_kernel(const uint2 *__restrict__ seg, int64_t n_parts, int n_tiles, int64_t n_waves,
+                                                          int rr, int rows_per_bundle, uint8_t *__restrict__ counts,
+                                                          uint32_t *__restrict__ wave_tile_iters, uint32_t *__restrict__ too_long) {
+    const int64_t n_bundles = (n_parts + rows_per_bundle - 1) / rows_per_bundle;
+    const int64_t total = n_waves * n_tiles;
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < total; x += stride) {
+        const int64_t w = x / n_tiles;
+        const int t = int(x - w * n_tiles);
+        uint32_t sum = 0;
+        for (int r = 0; r < rr; ++r) {
+            const int64_t i0 = dealt_bundle(w, r, n_waves, n_bundles) * rows_per_bundle;
+            uint32_t most = 0;
+            for (int g = 0; g < rows_per_bundle; ++g) {
+                if (i0 < 0 || i0 + g >= n_parts) break;
+                const uint2 s = seg[int64_t(t) * n_parts + i0 + g];
+                const uint32_t n = (s.y - s.x + kUnit - 1) / kUnit;
+                most = n > most ? n : most;
+            }
+            if (most > 255u) { *too_long = 1u; most = 255u; }
+            counts[x * kCounts + r] = uint8_t(most);
+            sum += most;
+        }
+        wave_tile_iters[x] = sum;
+    }
+}
+
+// One wavefront per (wavefront of the gather, tile): its stretch of the stream.  W: also (or only) the coefficients,
+// w[epos] * scale[epos] of every edge and 0 where a row is filled up.
+template <bool INDICES, bool W>
+__global__ void __launch_bounds__(256) tile_fill_kernel(const TileDesc *__restrict__ tiles, int n_tiles, int64_t n_waves, int rr,
+                                                        int rows_per_bundle, const uint2 *__restrict__ seg, int64_t n_parts,
+                                                        const uint8_t *__restrict__ counts, const uint32_t *__restrict__ wave_off,
+                                                        const int32_t *__restrict__ blk_indices, const uint32_t *__restrict__ blk_epos,
+                                                        const float *__restrict__ w, const float *__restrict__ scale,
+                                                        int zero_index, uint16_t *__restrict__ stream, float *__restrict__ wstream) {
+    const int lane = threadIdx.x & 63;
+    const int slots = rows_per_bundle * kUnit;  // of one unit
+    const int64_t n_bundles = (n_parts + rows_per_bundle - 1) / rows_per_bundle;
+    const int64_t total = n_waves * n_tiles;
+    const int64_t n_workers = int64_t(gridDim.x) * (blockDim.x >> 6);
+    for (int64_t x = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6); x < total; x += n_workers) {
+        const int64_t wv = x / n_tiles;
+        const int t = int(x - wv * n_tiles);
+        const int32_t tile_begin = tiles[t].begin;
+        int64_t out = int64_t(wave_off[x]) * slots;
+        for (int r = 0; r < rr; ++r) {
+            const int n_it = counts[x * kCounts + r];
+            const int64_t i0 = dealt_bundle(wv, r, n_waves, n_bundles) * rows_per_bundle;
+            const int64_t n_slots = int64_t(n_it) * slots;
+            for (int64_t s = lane; s < n_slots; s += 64) {
+                const int64_t it = s / slots;
+                const int in = int(s - it * slots);
+                const int64_t i = i0 + in / kUnit;
+                int idx = zero_index;
+                float cf = 0.0f;
+                if (i < n_parts) {
+                    const uint2 sg = seg[int64_t(t) * n_parts + i];
+                    const uint64_t e = uint64_t(sg.x) + uint64_t(it) * kUnit + (in % kUnit);
+                    if (e < sg.y) {
+                        if (INDICES) idx = blk_indices[e] - tile_begin;
+                        if (W) {
+                            const uint32_t p = blk_epos[e];
+                            cf = w ? w[p] : 1.0f;
+                            if (scale) cf *= scale[p];
+                        }
+                    }
+                }
+                if (INDICES) stream[out + s] = uint16_t(idx);
+                if (W) wstream[out + s] = cf;
+            }
+            out += n_slots;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- the gather
+struct TileArgs {
+    const TileDesc *tiles;
+    int32_t n_tiles, n_slices, n_groups;
+    int32_t group_begin[GNN_TILE_MAX_GROUPS + 1];  // tiles of the workgroups' groups
+    int64_t n_waves, n_parts;
+    const uint16_t *stream;
+    const float *wstream;
+    const uint32_t *wave_off;   // [n_waves * n_tiles] in iterations
+    const uint8_t *counts;      // [n_waves * n_tiles * kCounts]
+    const uint32_t *order;
+    const void *X;              // first slice table, rows of 16 * L bytes
+    int64_t slice_stride;       // bytes
+    float *partial;             // [n_groups][n_slices][n_parts][floats per line]
+};
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <bool BF16>
+__device__ __forceinline__ void add_line(const u32x4 v, float (&acc)[BF16 ? 8 : 4]) {
+    if constexpr (BF16) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            acc[2 * i] += __uint_as_float(v[i] << 16);
+            acc[2 * i + 1] += __uint_as_float(v[i] & 0xFFFF0000u);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += __uint_as_float(v[i]);
+    }
+}
+template <bool BF16>
+__device__ __forceinline__ void fma_line(const u32x4 v, float cf, float (&acc)[BF16 ? 8 : 4]) {
+    if constexpr (BF16) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            acc[2 * i] = fmaf(cf, __uint_as_float(v[i] << 16), acc[2 * i]);
+            acc[2 * i + 1] = fmaf(cf, __uint_as_float(v[i] & 0xFFFF0000u), acc[2 * i + 1]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = fmaf(cf, __uint_as_float(v[i]), acc[i]);
+    }
+}
+
+// 16 bytes at lds0 + LINE_BYTES * (high or low half of `two`): one multiply-add forms the address.
+template <int LINE_BYTES, bool HIGH>
+__device__ __forceinline__ u32x4 lds_line(uint32_t two, uint32_t lds0) {
+    uint32_t addr;
+    if constexpr (HIGH) asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(addr) : "v"(two), "s"(LINE_BYTES), "v"(lds0));
+    else asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(addr) : "v"(two), "s"(LINE_BYTES), "v"(lds0));
+    return *reinterpret_cast<__attribute__((address_space(3))) const u32x4 *>(static_cast<uintptr_t>(addr));
+}
+
+// Bytes of LDS the tile of lines of L * 16 bytes takes, the line of zeros included: what the streams leave of 160 KB.
+__host__ __device__ constexpr int tile_bytes(int L) { return (L == 8 ? 124 : (L == 4 ? 120 : 112)) << 10; }
+
+// Value of lane J of each quad (PAIR: lane J of each pair of lanes) in all of its lanes.
+template <int J, bool PAIR>
+__device__ __forceinline__ uint32_t spread(uint32_t v) {
+    constexpr int ctrl = PAIR ? (J == 0 ? 0xA0 : 0xF5) : J * 0x55;
+    return uint32_t(__builtin_amdgcn_mov_dpp(int(v), ctrl, 0xF, 0xF, true));
+}
+
+template <bool BF16, int L, bool COEF, int RR>
+__global__ void __launch_bounds__(kTileThreads) tile_kernel(const TileArgs a) {
+    constexpr int VEC = BF16 ? 8 : 4;             // elements per lane
+    constexpr int LOG2L = L == 8 ? 3 : (L == 4 ? 2 : 1);
+    constexpr int ROWS = 64 / L;                  // rows of a bundle
+    constexpr int TS = tile_bytes(L) / (16 * L);  // lines of the tile, the last one zeros
+    constexpr int CHUNKS = (TS * L + kTileThreads - 1) / kTileThreads;
+    constexpr int AHEAD = 128 / ROWS;             // units that 1 KB of the offsets lasts
+    constexpr int W_AHEAD = AHEAD / 2;            // ... and of the coefficients
+    // The streams pass through LDS, 1 KB per wavefront at a time; the next KB waits in registers meanwhile, so
+    // that a load has a KB's time to arrive.  Slot 0 takes the last unit of a KB that a step of two units did not fit.
+    __shared__ uint2 ring[kTileWaves][(AHEAD + 1) * ROWS];
+    __shared__ f32x4 w_ring[COEF ? kTileWaves : 1][(W_AHEAD + 1) * ROWS];
+    __shared__ u32x4 tile[TS * L];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int g = lane >> LOG2L, c = lane & (L - 1);
+    const int slice = int(blockIdx.x % uint32_t(a.n_slices));
+    const int rest = int(blockIdx.x / uint32_t(a.n_slices));
+    const int group = rest % a.n_groups;
+    const int64_t wv = int64_t(rest / a.n_groups) * kTileWaves + wave;
+    const int t0 = a.group_begin[group], t1 = a.group_begin[group + 1];
+
+    float acc[RR][VEC];
+#pragma unroll
+    for (int r = 0; r < RR; ++r)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[r][i] = 0.0f;
+
+    const int64_t first = int64_t(a.wave_off[wv * a.n_tiles + t0]) * ROWS;  // in units of one row
+    const u32x4 *sp = reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint2 *>(a.stream) + first) + lane;
+    const f32x4 *wp = COEF ? reinterpret_cast<const f32x4 *>(a.wstream) + first + lane : nullptr;
+    u32x4 nxt = sp[0];
+    f32x4 w_nxt;
+    if (COEF) w_nxt = wp[0];
+    int pos = AHEAD + 1, w_pos = W_AHEAD + 1;  // next unit in the rings
+    static_assert(RR <= kCounts, "the counts of a tile are one 16-byte load");
+    const u32x4 *cnt = reinterpret_cast<const u32x4 *>(a.counts) + wv * a.n_tiles + t0;
+    const char *Xs = static_cast<const char *>(a.X) + int64_t(slice) * a.slice_stride;
+    // byte address of this lane's part of line 0; the lines of the tile follow each other
+    const uint32_t lds0 = uint32_t(uintptr_t((__attribute__((address_space(3))) const u32x4 *)tile)) + 16u * uint32_t(c);
+    // A unit of a row is two words of offsets; the four lanes of a quad (the two of a pair) read one (two) words of two
+    // units each and spread them.
+    constexpr bool PAIR = L == 2;
+    const uint32_t *ring_lane = reinterpret_cast<const uint32_t *>(ring[wave]) +
+                                (PAIR ? (c * ROWS + g) * 2 : (((lane >> 1) & 1) * ROWS + g) * 2 + (lane & 1));
+    const float *w_lane = reinterpret_cast<const float *>(w_ring[COEF ? wave : 0]) + g * 4 + (PAIR ? 2 * c : lane & 3);
+    constexpr int BATCH = BF16 ? 4 : 8;  // lines in flight per row: the registers beside 8 sums allow no more
+
+    // one or two units (four edges of every row of the bundle each)
+    auto step = [&](auto units, float (&sum)[VEC]) {
+        constexpr int EDGES = decltype(units)::value * kUnit;
+        if (pos >= AHEAD) {
+            if (pos == AHEAD && lane < ROWS) ring[wave][lane] = ring[wave][AHEAD * ROWS + lane];
+            *reinterpret_cast<u32x4 *>(&ring[wave][ROWS + 2 * lane]) = nxt;
+            sp += 64;
+            nxt = *sp;
+            pos -= AHEAD;
+        }
+        uint32_t q[PAIR ? 2 : 1];
+        q[0] = ring_lane[pos * (2 * ROWS)];
+        if constexpr (PAIR) q[1] = ring_lane[pos * (2 * ROWS) + 1];
+        pos += decltype(units)::value;
+        float w[2][2];
+        if (COEF) {
+            if (w_pos >= W_AHEAD) {
+                if (w_pos == W_AHEAD && lane < ROWS) w_ring[wave][lane] = w_ring[wave][W_AHEAD * ROWS + lane];
+                w_ring[wave][ROWS + lane] = w_nxt;
+                wp += 64;
+                w_nxt = *wp;
+                w_pos -= W_AHEAD;
+            }
+#pragma unroll
+            for (int i = 0; i < EDGES / 4; ++i) {
+                w[i][0] = w_lane[(w_pos + i) * (4 * ROWS)];
+                if constexpr (PAIR) w[i][1] = w_lane[(w_pos + i) * (4 * ROWS) + 1];
+            }
+            w_pos += decltype(units)::value;
+        }
+        uint32_t two[4] = {0u, 0u, 0u, 0u};
+        if constexpr (PAIR) {
+            two[0] = spread<0, true>(q[0]); two[1] = spread<0, true>(q[1]);
+            if (EDGES > 4) { two[2] = spread<1, true>(q[0]); two[3] = spread<1, true>(q[1]); }
+        } else {
+            two[0] = spread<0, false>(q[0]); two[1] = spread<1, false>(q[0]);
+            if (EDGES > 4) { two[2] = spread<2, false>(q[0]); two[3] = spread<3, false>(q[0]); }
+        }
+        constexpr int B = EDGES < BATCH ? EDGES : BATCH;
+#pragma unroll
+        for (int h = 0; h < EDGES / B; ++h) {
+            u32x4 x[B];
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                const uint32_t t = two[(h * B + k) >> 1];
+                x[k] = (k & 1) ? lds_line<16 * L, true>(t, lds0) : lds_line<16 * L, false>(t, lds0);
+            }
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                if constexpr (COEF) {
+                    const int e = h * B + k;
+                    const uint32_t wv0 = __float_as_uint(w[e >> 2][PAIR ? e & 1 : 0]);
+                    const uint32_t cf = PAIR ? ((e & 2) ? spread<1, true>(wv0) : spread<0, true>(wv0))
+                                             : ((e & 3) == 0 ? spread<0, false>(wv0) : (e & 3) == 1 ? spread<1, false>(wv0)
+                                                : (e & 3) == 2 ? spread<2, false>(wv0) : spread<3, false>(wv0));
+                    fma_line<BF16>(x[k], __uint_as_float(cf), sum);
+                } else {
+                    add_line<BF16>(x[k], sum);
+                }
+            }
+        }
+    };
+
+    TileDesc d = a.tiles[t0];
+    for (int t = t0; t < t1; ++t) {
+        const u32x4 n_units = *cnt++;
+        const u32x4 *src = reinterpret_cast<const u32x4 *>(Xs) + int64_t(d.begin) * L;
+        const int n_chunks = d.size * L;
+        if (t + 1 < t1) d = a.tiles[t + 1];
+        __syncthreads();  // everyone is done with the tile before
+#pragma unroll
+        for (int h = 0; h < CHUNKS; h += 4) {
+            u32x4 v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int x = int(threadIdx.x) + (h + i) * kTileThreads;
+                v[i] = src[x < n_chunks ? x : n_chunks - 1];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int x = int(threadIdx.x) + (h + i) * kTileThreads;
+                // a tile has at most TS - 1 lines: the last one, and what is behind a shorter tile, are zeros
+                if (x < TS * L) tile[x] = x < n_chunks ? v[i] : u32x4{0u, 0u, 0u, 0u};
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < RR; ++r) {
+            int n = int((__builtin_amdgcn_readfirstlane(n_units[r >> 2]) >> (8 * (r & 3))) & 0xFFu);
+            for (; n >= 2; n -= 2) step(std::integral_constant<int, 2>(), acc[r]);
+            if (n) step(std::integral_constant<int, 1>(), acc[r]);
+        }
+    }
+
+    float *out = a.partial + (int64_t(group) * a.n_slices + slice) * a.n_parts * (L * VEC) + c * VEC;
+#pragma unroll
+    for (int r = 0; r < RR; ++r) {
+        const int64_t i = dealt_bundle(wv, r, a.n_waves, (a.n_parts + ROWS - 1) / ROWS) * ROWS + g;
+        if (i >= 0 && i < a.n_parts) {
+            float *q = out + int64_t(a.order[i]) * (L * VEC);
+#pragma unroll
+            for (int k = 0; k < VEC; k += 4)
+                *reinterpret_cast<f32x4 *>(q + k) = f32x4{acc[r][k], acc[r][k + 1], acc[r][k + 2], acc[r][k + 3]};
+        }
+    }
+}
+
+template <typename T>
+bool dev_alloc(T **p, int64_t n) { return hipMalloc(p, sizeof(T) * size_t(n > 0 ? n : 1)) == hipSuccess; }
+
+// number of the layout for L lanes per row
+int level_of(int lanes, bool bf16) { return (lanes == 8 ? 0 : (lanes == 4 ? 1 : 2)) + (bf16 ? 3 : 0); }
+
+}  // namespace
+
+void gnn_tiles_free(gnn_tiles &t) {
+    (void)hipFree(t.part_base); (void)hipFree(t.order); (void)hipFree(t.tiles); (void)hipFree(t.seg); (void)hipFree(t.stream);
+    (void)hipFree(t.counts); (void)hipFree(t.wave_off); (void)hipFree(t.left.pieces); (void)hipFree(t.left.piece_block);
+    (void)hipFree(t.left.rowbase); (void)hipFree(t.bound_w); (void)hipFree(t.tmp_w);
+    for (int i = 0; i < 3; ++i) (void)hipFree(t.scale[i]);
+    t = gnn_tiles{};
+}
+
+namespace {
+
+// Device memory that lives as long as this object.
+struct Scratch {
+    std::vector<void *> all;
+    hipStream_t stream;
+    explicit Scratch(hipStream_t s) : stream(s) {}
+    ~Scratch() {
+        if (!all.empty()) (void)hipStreamSynchronize(stream);
+        for (void *p : all) (void)hipFree(p);
+    }
+    template <typename T>
+    bool get(T **p, int64_t n) {
+        if (!dev_alloc(p, n)) { *p = nullptr; return false; }
+        all.push_back(*p);
+        return true;
+    }
+};
+
+// Workgroups (per column slice and group of tiles) that so many bundles are dealt to: up to kRowBlocks with kFewBundles or
+// more per wavefront, so that copying a tile is shared by many rows; beyond that as many as the registers ask for.
+int64_t row_blocks_for(int64_t n_bundles, int rr) {
+    int64_t few = n_bundles / (kTileWaves * kFewBundles);
+    if (few > kRowBlocks) few = kRowBlocks;
+    const int64_t least = (n_bundles + kTileWaves * rr - 1) / (kTileWaves * rr);
+    return few > least ? few : (least > 0 ? least : 1);
+}
+
+// Builds B (the caller frees what it holds when this fails).  B.active stays false where nothing is dense enough.
+int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn_tiles &B) {
+    const int64_t n_hot = plan->blk_n_hot;
+    const int n_blocks = plan->blk_n_blocks;
+    const int tile_lines = tile_bytes(lanes) / (16 * lanes) - 1;  // and the line of zeros
+    const int rows = 64 / lanes;
+    (void)hipGetLastError();
+    Scratch tmp(stream);
+
+    // Which cells, and which blocks: a row is staged in a block where it has at least kMinRowEdges edges per tile, the
+    // block where those rows have enough edges to pay for copying its tiles into LDS.
+    auto block_range = [&](int k, int64_t *lo, int64_t *hi) {
+        *lo = k == 0 ? 0 : (k == n_blocks - 1 ? int64_t(plan->blk_rest_begin) : int64_t(plan->blk_hot_lines) + int64_t(k - 1) * plan->blk_block_lines);
+        *hi = k == n_blocks - 1 ? plan->n_rows : (k == 0 ? int64_t(plan->blk_hot_lines) : *lo + plan->blk_block_lines);
+        if (k < n_blocks - 1 && *hi > plan->blk_rest_begin) *hi = plan->blk_rest_begin;
+    };
+    std::vector<int64_t> n_block_tiles(size_t(n_blocks), 0);
+    std::vector<uint32_t> block_min(size_t(n_blocks), 0);
+    for (int k = 0; k < n_blocks; ++k) {
+        int64_t lo, hi;
+        block_range(k, &lo, &hi);
+        n_block_tiles[size_t(k)] = hi > lo ? (hi - lo + tile_lines - 1) / tile_lines : 0;
+        block_min[size_t(k)] = uint32_t(n_block_tiles[size_t(k)] * kMinRowEdges);
+    }
+    uint32_t *d_min = nullptr;
+    unsigned long long *d_sums = nullptr;
+    std::vector<unsigned long long> sums_of_block(size_t(n_blocks), 0);
+    if (!tmp.get(&d_min, n_blocks) || !tmp.get(&d_sums, n_blocks + 1)) return GNN_ERR_ALLOC;
+    const DenseRule rule{plan->blk_cell_off, d_min, n_hot};
+    GNN_HIP_TRY(hipMemcpyAsync(d_min, block_min.data(), sizeof(uint32_t) * size_t(n_blocks), hipMemcpyHostToDevice, stream));
+    GNN_HIP_TRY(hipMemsetAsync(d_sums, 0, sizeof(unsigned long long) * size_t(n_blocks + 1), stream));
+    tile_block_edges_kernel<<<dim3(static_cast<unsigned>(grid_for(n_hot, 256, 64)), static_cast<unsigned>(n_blocks)), 256, 0, stream>>>(rule, d_sums);
+    GNN_HIP_TRY(hipGetLastError());
+    GNN_HIP_TRY(hipMemcpyAsync(sums_of_block.data(), d_sums, sizeof(unsigned long long) * size_t(n_blocks), hipMemcpyDeviceToHost, stream));
+    GNN_HIP_TRY(hipStreamSynchronize(stream));
+    std::vector<TileDesc> tiles;
+    int64_t staged_edges = 0;
+    const int64_t est_row_blocks = row_blocks_for((n_hot + rows - 1) / rows, rr);
+    for (int k = 0; k < n_blocks; ++k) {
+        const int64_t nt = n_block_tiles[size_t(k)];
+        if (nt == 0 || int64_t(sums_of_block[size_t(k)]) < kMinTileEdges * est_row_blocks * nt || int64_t(tiles.size()) + nt > 4096) { block_min[size_t(k)] = 0; continue; }
+        int64_t lo, hi;
+        block_range(k, &lo, &hi);
+        for (int64_t i = 0; i < nt; ++i) {  // tiles of equal size
+            const int64_t b = lo + (hi - lo) * i / nt, e = lo + (hi - lo) * (i + 1) / nt;
+            tiles.push_back(TileDesc{int32_t(b), int32_t(e - b), k, 0});
+        }
+        staged_edges += int64_t(sums_of_block[size_t(k)]);
+    }
+    const int n_tiles = int(tiles.size());
+    if (n_tiles == 0) return GNN_OK;
+
+    // the rows' staged edges, and their parts
+    uint32_t *staged = nullptr, *part_base = nullptr, *scan = nullptr, *n_staged = reinterpret_cast<uint32_t *>(d_sums + n_blocks);
+    const int64_t n_cells = int64_t(n_blocks) * n_hot;
+    if (!tmp.get(&staged, n_hot) || !tmp.get(&scan, gnn_scan_sums_elems(n_cells > n_hot + 1 ? n_cells : n_hot + 1))) return GNN_ERR_ALLOC;
+    if (!dev_alloc(&B.part_base, n_hot + 1)) return GNN_ERR_ALLOC;
+    part_base = B.part_base;
+    GNN_HIP_TRY(hipMemcpyAsync(d_min, block_min.data(), sizeof(uint32_t) * size_t(n_blocks), hipMemcpyHostToDevice, stream));
+    const int row_grid = grid_for(n_hot, 256, INT32_MAX);
+    tile_row_edges_kernel<<<row_grid, 256, 0, stream>>>(rule, n_blocks, staged, n_staged);
+    uint32_t host_staged = 0, parts_last = 0, base_last = 0;
+    GNN_HIP_TRY(hipGetLastError());
+    GNN_HIP_TRY(hipMemcpyAsync(&host_staged, n_staged, 4, hipMemcpyDeviceToHost, stream));
+    GNN_HIP_TRY(hipStreamSynchronize(stream));
+    if (host_staged == 0) return GNN_OK;
+    const uint32_t cap = uint32_t((2 * staged_edges + host_staged - 1) / host_staged);  // twice the mean row
+    tile_row_parts_kernel<<<row_grid, 256, 0, stream>>>(staged, n_hot, cap, part_base);
+    GNN_HIP_TRY(hipGetLastError());
+    GNN_HIP_TRY(hipMemcpyAsync(&parts_last, part_base + n_hot - 1, 4, hipMemcpyDeviceToHost, stream));
+    int rc = gnn_scan_exclusive_u32(part_base, n_hot, scan, stream);
+    if (rc != GNN_OK) return rc;
+    GNN_HIP_TRY(hipMemcpyAsync(&base_last, part_base + n_hot - 1, 4, hipMemcpyDeviceToHost, stream));
+    GNN_HIP_TRY(hipStreamSynchronize(stream));
+    const uint32_t n_parts32 = base_last + parts_last;
+    const int64_t n_parts = n_parts32;
+    GNN_HIP_TRY(hipMemcpyAsync(part_base + n_hot, &n_parts32, 4, hipMemcpyHostToDevice, stream));
+
+    // bundles of parts of similar size, dealt to the wavefronts
+    const int64_t n_bundles = (n_parts + rows - 1) / rows;
+    const int64_t n_row_blocks = row_blocks_for(n_bundles, rr);
+    const int64_t n_waves = n_row_blocks * kTileWaves, n_wt = n_waves * n_tiles;
+    uint32_t *keys[2], *ids[2], *table = nullptr, *sums = nullptr, *too_long = nullptr;
+    RowPart *parts = nullptr;
+    const int64_t sums_n = gnn_sort_sums_elems(n_parts) > gnn_scan_sums_elems(n_wt) ? gnn_sort_sums_elems(n_parts) : gnn_scan_sums_elems(n_wt);
+    TileDesc *d_tiles = nullptr;
+    uint2 *seg = nullptr;
+    if (!(tmp.get(&keys[0], n_parts) && tmp.get(&keys[1], n_parts) && tmp.get(&ids[0], n_parts) && tmp.get(&ids[1], n_parts) &&
+          tmp.get(&table, gnn_sort_table_elems(n_parts)) && tmp.get(&sums, sums_n) && tmp.get(&too_long, 1) && tmp.get(&parts, n_parts)))
+        return GNN_ERR_ALLOC;
+    if (!dev_alloc(&d_tiles, n_tiles)) return GNN_ERR_ALLOC;
+    B.tiles = d_tiles;
+    if (!dev_alloc(&seg, int64_t(n_tiles) * n_parts)) return GNN_ERR_ALLOC;
+    B.seg = seg;
+    if (!(dev_alloc(&B.order, n_parts) && dev_alloc(&B.counts, n_wt * kCounts) && dev_alloc(&B.wave_off, n_wt))) return GNN_ERR_ALLOC;
+    GNN_HIP_TRY(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(TileDesc) * size_t(n_tiles), hipMemcpyHostToDevice, stream));
+    GNN_HIP_TRY(hipMemsetAsync(too_long, 0, 4, stream));
+    tile_parts_kernel<<<row_grid, 256, 0, stream>>>(staged, part_base, n_hot, cap, parts, keys[0], ids[0]);
+    GNN_HIP_TRY(hipGetLastError());
+    int where = 0;
+    rc = gnn_radix_sort_pairs(nullptr, keys, ids, n_parts, gnn_ilog2_ceil(int64_t(cap) + 1), table, sums, stream, &where);
+    if (rc != GNN_OK) return rc;
+    GNN_HIP_TRY(hipMemcpyAsync(B.order, ids[where], sizeof(uint32_t) * size_t(n_parts), hipMemcpyDeviceToDevice, stream));
+    tile_segments_kernel<<<grid_for(int64_t(n_tiles) * n_parts, 256), 256, 0, stream>>>(d_tiles, n_tiles, rule, B.order, parts, n_parts,
+                                                                                    plan->blk_indices, seg);
+    tile_counts_kernel<<<grid_for(n_wt, 256), 256, 0, stream>>>(seg, n_parts, n_tiles, n_waves, rr, rows, B.counts, B.wave_off, too_long);
+    GNN_HIP_TRY(hipGetLastError());
+    std::vector<uint32_t> iters(static_cast<size_t>(n_wt));
+    uint32_t host_too_long = 0;
+    GNN_HIP_TRY(hipMemcpyAsync(iters.data(), B.wave_off, sizeof(uint32_t) * size_t(n_wt), hipMemcpyDeviceToHost, stream));
+    GNN_HIP_TRY(hipMemcpyAsync(&host_too_long, too_long, 4, hipMemcpyDeviceToHost, stream));
+    GNN_HIP_TRY(hipStreamSynchronize(stream));
+    int64_t total = 0;
+    B.tile_work.assign(size_t(n_tiles), 0);
+    for (int64_t x = 0; x < n_wt; ++x) {
+        total += iters[size_t(x)];
+        B.tile_work[size_t(x % n_tiles)] += iters[size_t(x)];
+    }
+    if (host_too_long || total >= int64_t(UINT32_MAX)) return GNN_OK;  // over 1,020 edges of a row into one tile (duplicates): keep the pieces
+    if ((rc = gnn_scan_exclusive_u32(B.wave_off, n_wt, sums, stream)) != GNN_OK) return rc;
+    if (!dev_alloc(&B.stream, (total + kStreamAhead) * rows * kUnit)) return GNN_ERR_ALLOC;
+    tile_fill_kernel<true, false><<<grid_for(n_wt * 64, 256), 256, 0, stream>>>(d_tiles, n_tiles, n_waves, rr, rows, seg, n_parts,
+                                                                            B.counts, B.wave_off, plan->blk_indices, nullptr, nullptr,
+                                                                            nullptr, tile_lines, B.stream, nullptr);
+    GNN_HIP_TRY(hipGetLastError());
+
+    // the cells that are not staged stay pieces
+    uint32_t *cell_count = nullptr, *cell_pieces = nullptr;
+    if (!tmp.get(&cell_count, n_cells) || !tmp.get(&cell_pieces, n_cells)) return GNN_ERR_ALLOC;
+    tile_left_cells_kernel<<<grid_for(n_cells, 256), 256, 0, stream>>>(rule, n_blocks, uint32_t(plan->blk_max_piece), cell_count, cell_pieces);
+    GNN_HIP_TRY(hipGetLastError());
+    rc = gnn_build_pieces(n_hot, n_blocks, plan->blk_max_piece, cell_count, plan->blk_cell_off, cell_pieces, scan,
+                          plan->blk_piece_block != nullptr, stream, &B.left);
+    if (rc != GNN_OK) return rc;
+    B.lanes = lanes;
+    B.rr = rr;
+    B.n_tiles = n_tiles;
+    B.n_row_blocks = n_row_blocks;
+    B.n_waves = n_waves;
+    B.n_iters = total;
+    B.n_parts = n_parts;
+    B.active = true;
+    return GNN_OK;
+}
+
+}  // namespace
+
+// Builds the tile layout for rows of `lanes` x 16 bytes on first use; needs the source-blocked layout.
+int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, hipStream_t stream, const gnn_tiles **out) {
+    *out = nullptr;
+    if (!plan || (lanes != 8 && lanes != 4 && lanes != 2)) return GNN_ERR_INVALID_ARG;
+    gnn_tiles &L = plan->tiles[level_of(lanes, bf16)];
+    if (!L.decided) {
+        if (!plan->blk_decided) return GNN_ERR_INVALID_ARG;
+        gnn_tiles B{};
+        if (plan->blk_n_pieces > 0 && plan->blk_cell_off) {
+            const int rc = build_tiles(plan, lanes, bf16 ? kBundlesBf16 : kBundlesF32, stream, B);
+            if (rc != GNN_OK || !B.active) gnn_tiles_free(B);
+            if (rc != GNN_OK) return rc;
+        }
+        L = B;
+        L.decided = true;
+    }
+    if (L.active) *out = &L;
+    return GNN_OK;
+}
+
+// Coefficients of the edges in stream order.  Kept: the plan's own factors, and weights bound to the plan; anything
+// else is gathered anew by every call.
+int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles_in, const float *w, const float *scale, int scale_mode, bool bound,
+                        hipStream_t stream, const float **out) {
+    gnn_tiles &L = plan->tiles[tiles_in - plan->tiles];
+    float **slot = &L.tmp_w;
+    bool fill = true;
+    if (!w && scale) {
+        slot = &L.scale[scale_mode - 1];
+        fill = !*slot;
+    } else if (w && !scale && bound) {
+        slot = &L.bound_w;
+        fill = !*slot || L.bound_version != plan->bound_w_version;
+    }
+    const int rows = 64 / L.lanes;
+    if (!*slot) {
+        (void)hipGetLastError();
+        if (!dev_alloc(slot, (L.n_iters + kStreamAhead) * rows * kUnit)) { *slot = nullptr; return GNN_ERR_ALLOC; }
+    }
+    if (fill) {
+        tile_fill_kernel<false, true><<<grid_for(L.n_waves * L.n_tiles * 64, 256), 256, 0, stream>>>(
+            static_cast<const TileDesc *>(L.tiles), L.n_tiles, L.n_waves, L.rr, rows, static_cast<const uint2 *>(L.seg), L.n_parts, L.counts, L.wave_off,
+            plan->blk_indices, plan->blk_epos, w, scale, 0, nullptr, *slot);
+        if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
+        if (slot == &L.bound_w) L.bound_version = plan->bound_w_version;
+    }
+    *out = *slot;
+    return GNN_OK;
+}
+
+// How many groups the tiles are split into: as many as make one round of the compute units (a workgroup takes a whole
+// one).  A second, mostly empty round costs more than idle compute units, which the short rows' launch uses meanwhile
+// (505 K vertices, 14 M edges, F=99: 0.75 ms with 184 workgroups, 0.83 with 276, 0.78 as pieces).
+int gnn_tile_groups(const gnn_tiles *t, int n_slices) {
+    int64_t g = kComputeUnits / (t->n_row_blocks * n_slices);
+    if (g > GNN_TILE_MAX_GROUPS) g = GNN_TILE_MAX_GROUPS;
+    if (g > t->n_tiles) g = t->n_tiles;
+    return g < 1 ? 1 : int(g);
+}
+
+int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats) {
+    const int64_t need = int64_t(gnn_tile_groups(t, n_slices)) * n_slices * t->n_parts * line_floats * int64_t(sizeof(float));
+    if (need <= plan->tile_partial_bytes) return GNN_OK;
+    (void)hipGetLastError();
+    (void)hipFree(plan->tile_partial);
+    plan->tile_partial = nullptr;
+    plan->tile_partial_bytes = 0;
+    if (hipMalloc(&plan->tile_partial, size_t(need)) != hipSuccess) return GNN_ERR_ALLOC;
+    plan->tile_partial_bytes = need;
+    return GNN_OK;
+}
+
+int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,
+                     const float *coefs, float *partial, hipStream_t stream) {
+    TileArgs a{};
+    a.tiles = static_cast<const TileDesc *>(t->tiles);
+    a.n_tiles = t->n_tiles;
+    a.n_slices = n_slices;
+    a.n_groups = gnn_tile_groups(t, n_slices);
+    // group boundaries: equal shares of the iterations
+    double total = 0.0;
+    for (int64_t x : t->tile_work) total += double(x);
+    double run = 0.0;
+    int next = 1;
+    a.group_begin[0] = 0;
+    for (int i = 0; i < t->n_tiles && next < a.n_groups; ++i) {
+        run += double(t->tile_work[size_t(i)]);
+        // every group gets at least one tile
+        if (run >= total * next / a.n_groups || t->n_tiles - (i + 1) <= a.n_groups - next) a.group_begin[next++] = i + 1;
+    }
+    a.group_begin[a.n_groups] = t->n_tiles;
+    a.n_waves = t->n_waves;
+    a.n_parts = t->n_parts;
+    a.stream = t->stream;
+    a.wstream = coefs;
+    a.wave_off = t->wave_off;
+    a.counts = t->counts;
+    a.order = t->order;
+    a.X = X;
+    a.slice_stride = slice_stride_bytes;
+    a.partial = partial;
+    const int64_t blocks = t->n_row_blocks * n_slices * a.n_groups;
+    if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
+    const dim3 grid(static_cast<unsigned>(blocks));
+#define GNN_TILE_LAUNCH(BF, LANES)                                                                              \
+    do {                                                                                                        \
+        if (coefs) tile_kernel<BF, LANES, true, BF ? kBundlesBf16 : kBundlesF32><<<grid, kTileThreads, 0, stream>>>(a);             \
+        else tile_kernel<BF, LANES, false, BF ? kBundlesBf16 : kBundlesF32><<<grid, kTileThreads, 0, stream>>>(a);                  \
+    } while (0)
+    if (bf16) {
+        if (t->lanes == 8) GNN_TILE_LAUNCH(true, 8);
+        else if (t->lanes == 4) GNN_TILE_LAUNCH(true, 4);
+        else GNN_TILE_LAUNCH(true, 2);
+    } else {
+        if (t->lanes == 8) GNN_TILE_LAUNCH(false, 8);
+        else if (t->lanes == 4) GNN_TILE_LAUNCH(false, 4);
+        else GNN_TILE_LAUNCH(false, 2);
+    }
+#undef GNN_TILE_LAUNCH
+    return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
+}

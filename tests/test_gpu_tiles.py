@@ -1,0 +1,69 @@
+"""Long rows gathered from source tiles staged in LDS: the dense cells of the source-blocked layout.  The graphs
+are dense enough that every block is staged; the cases put block and tile boundaries where they can go wrong (one
+line more or less than a tile, a last short tile, rows cut into parts, lists filled up to whole units)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2104_06700_amd as gnn
+import synth
+from helpers import OP_CODE, assert_close, device_graph, host_csr
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+SLICED = gnn.GNN_FLAG_FORCE_PADDED_COPY
+THRESHOLDS = [4, 32, 256]
+
+
+def _check(el, blocking, f, dtype, op_name, weights, bound, max_slices=8):
+    bf16 = dtype == torch.bfloat16
+    indptr, indices, indptr_t, indices_t, perm = host_csr(el)
+    din, dout = np.diff(indptr), np.diff(indptr_t)
+    wts = (synth.uniform_features(el.e, 1, 7).reshape(-1) + 0.5) if weights else None
+    w = None if wts is None else wts.numpy()
+    dg = device_graph(el, weights=wts, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    for plan in (dg.plan_fwd, dg.plan_bwd):
+        plan.set_blocking(**blocking)
+    if bound:
+        dg.plan_fwd.bind_edge_weights(dg.edge_w)
+        dg.plan_bwd.bind_edge_weights(dg.edge_w_t)
+    X = synth.normal_features(el.n, f, 3, dtype=dtype)
+    Xd = X.to(DEV)
+    op = OP_CODE[op_name]
+    Yo, S = oracle.aggregate_fwd(indptr, indices, X.float().numpy(), op=op, w=w, dout=dout, nthreads=8, want_scale=True)
+    dXo, St = oracle.aggregate_bwd(indptr_t, indices_t, X.float().numpy(), op=op, wt=None if w is None else w[perm], din=din,
+                                   nthreads=8, want_scale=True)
+    for _ in range(2):
+        Y = torch.full((el.n, f), float("nan"), dtype=dtype, device=DEV)
+        dX = torch.full((el.n, f), float("nan"), dtype=dtype, device=DEV)
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, dg.edge_w, Xd, Y, el.n, f, op, plan=dg.plan_fwd, flags=SLICED, max_slices=max_slices)
+        gnn.gnn_aggregate_bwd(dg.indptr_t, dg.indices_t, dg.edge_w_t, Xd, dX, el.n, f, op, plan=dg.plan_bwd, flags=SLICED,
+                              max_slices=max_slices)
+        torch.cuda.synchronize()
+        assert_close(Y, Yo, S, bf16, "fwd")
+        assert_close(dX, dXo, St, bf16, "bwd")
+    assert dg.plan_fwd.blocked_sizes()[2] > 0
+
+
+@pytest.mark.parametrize("hot_lines,block_lines", [(990, 991), (991, 992), (992, 500), (1983, 2973), (5000, 300)])
+@pytest.mark.parametrize("dtype,f,op_name,weights,bound", [
+    (torch.float32, 64, "mean", False, False), (torch.float32, 300, "sage", False, False), (torch.float32, 65, "sum", True, True),
+    (torch.float32, 100, "sum", True, False), (torch.bfloat16, 200, "gcn", False, False), (torch.bfloat16, 129, "mean", True, True)])
+def test_staged_tiles_match_the_oracle(hot_lines, block_lines, dtype, f, op_name, weights, bound):
+    el = synth.rmat_symmetric(5300, 1800000, (0.5, 0.2, 0.2, 0.1), 17)
+    _check(el, dict(min_degree=32, hot_lines=hot_lines, block_lines=block_lines, max_piece=48, rest_min_count=0), f, dtype, op_name, weights, bound)
+
+
+def test_rows_with_very_many_duplicate_edges_keep_the_pieces():
+    """More than 1,020 edges of one row into one tile do not fit the byte that counts a bundle's units."""
+    el = synth.small_random_multigraph(40, 60000, 5)
+    _check(el, dict(min_degree=32, hot_lines=32, block_lines=8, max_piece=48, rest_min_count=0), 96, torch.float32, "mean", False, False)
+
+
+def test_one_row_far_longer_than_the_others_is_cut_into_parts():
+    n, hub = 6000, 5
+    base = synth.erdos_renyi_directed(n, 900000, 3)
+    keys = torch.cat([base.dst.long() * n + base.src.long(), hub * n + torch.arange(n)[torch.arange(n) != hub]]).unique()
+    el = synth.EdgeList(n=n, src=(keys % n).to(torch.int32), dst=(keys // n).to(torch.int32), meta={})
+    _check(el, dict(min_degree=32, hot_lines=2000, block_lines=4000, max_piece=96, rest_min_count=0), 72, torch.float32, "sum", False, False)

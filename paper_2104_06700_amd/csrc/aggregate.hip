@@ -58,6 +58,7 @@ int static_scratch_of_current_device(float **out) {
 
 constexpr int kBlockThreads = 256;
 constexpr int kWavesPerBlock = kBlockThreads / 64;
+constexpr int kCoopMaxPass = 2;  // feature passes up to which a workgroup may share a row (sums of 6 KB per pass)
 
 enum ScaleMode : int { kScaleNone = 0, kScaleInv = 1, kScaleRsqrt = 2, kScaleInvPlus1 = 3 };
 enum SelfMode : int { kSelfNone = 0, kSelfPlain = 1, kSelfInvPlus1 = 2 };  // own row added to the sum
@@ -84,7 +85,8 @@ struct AggArgs {
     int32_t n_bins;
     int32_t log2_slices;  // column slices; workgroup b serves slice b % n_slices (see run_aggregate)
     int32_t slice_cols;   // columns per slice (the last slice of a launch may hold fewer)
-    int32_t store_vec;    // widest store the output rows allow (elements, <= VEC)
+    int32_t store_vec;    // widest non-temporal store the output rows allow (elements, <= VEC)
+    int32_t overlap;      // the last strip of a row begins early enough to end with the row (its first columns are computed twice)
     const int32_t *row_map;  // row of the gathered table that holds vertex v (rank layout), or nullptr: v
     const int64_t *p_indptr;  // rank layout: edge range of the row at position i of row_perm within `indices`
     const int64_t *p_chunks;  // rank layout: hub pieces (row, begin, end, original - plan-order position)
@@ -118,13 +120,20 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// The same at the alignment of one element: global loads and stores of 16 bytes need no more, so rows of any width and
+// stride are gathered with the widest loads (the machine code for an aligned address is the same).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32_any __attribute__((aligned(2)));
 
 template <> struct VecIO<float, 4> {
     static __device__ __forceinline__ void load(const float *p, float (&v)[4]) {
-        float4 t = *reinterpret_cast<const float4 *>(p); v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        const f32x4_any t = *reinterpret_cast<const f32x4_any *>(p); v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
     static __device__ __forceinline__ void load_nt(const float *p, float (&v)[4]) {
-        f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p)); v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+        const f32x4_any t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(p)); v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
     // Output rows are written once and not read again by this kernel: non-temporal stores keep
     // them from displacing gathered rows in the L2 (measured: +0.5..1 %).
@@ -132,77 +141,63 @@ template <> struct VecIO<float, 4> {
         f32x4 t = {v[0], v[1], v[2], v[3]};
         __builtin_nontemporal_store(t, reinterpret_cast<f32x4 *>(p));
     }
+    static __device__ __forceinline__ void store_any(float *p, const float (&v)[4]) {
+        *reinterpret_cast<f32x4_any *>(p) = f32x4_any{v[0], v[1], v[2], v[3]};
+    }
 };
 template <> struct VecIO<float, 2> {
     static __device__ __forceinline__ void load(const float *p, float (&v)[2]) {
-        float2 t = *reinterpret_cast<const float2 *>(p); v[0] = t.x; v[1] = t.y;
+        const f32x2_any t = *reinterpret_cast<const f32x2_any *>(p); v[0] = t.x; v[1] = t.y;
     }
     static __device__ __forceinline__ void load_nt(const float *p, float (&v)[2]) {
-        f32x2 t = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(p)); v[0] = t.x; v[1] = t.y;
+        const f32x2_any t = __builtin_nontemporal_load(reinterpret_cast<const f32x2_any *>(p)); v[0] = t.x; v[1] = t.y;
     }
     static __device__ __forceinline__ void store(float *p, const float (&v)[2]) {
         f32x2 t = {v[0], v[1]};
         __builtin_nontemporal_store(t, reinterpret_cast<f32x2 *>(p));
     }
+    static __device__ __forceinline__ void store_any(float *p, const float (&v)[2]) { *reinterpret_cast<f32x2_any *>(p) = f32x2_any{v[0], v[1]}; }
 };
 template <> struct VecIO<float, 1> {
     static __device__ __forceinline__ void load(const float *p, float (&v)[1]) { v[0] = *p; }
     static __device__ __forceinline__ void load_nt(const float *p, float (&v)[1]) { v[0] = __builtin_nontemporal_load(p); }
     static __device__ __forceinline__ void store(float *p, const float (&v)[1]) { __builtin_nontemporal_store(v[0], p); }
+    static __device__ __forceinline__ void store_any(float *p, const float (&v)[1]) { *p = v[0]; }
 };
-template <> struct VecIO<bf16_t, 8> {
-    static __device__ __forceinline__ void unpack(const uint32_t (&w)[4], float (&v)[8]) {
+// bf16: the packed words of a strip
+template <int VEC> struct Bf16Words;
+template <> struct Bf16Words<8> { typedef u32x4 type; typedef u32x4_any any; };
+template <> struct Bf16Words<4> { typedef u32x2 type; typedef u32x2_any any; };
+template <> struct Bf16Words<2> { typedef uint32_t type; typedef u32_any any; };
+template <int VEC> struct VecIO<bf16_t, VEC> {
+    typedef typename Bf16Words<VEC>::type words;
+    typedef typename Bf16Words<VEC>::any words_any;
+    static __device__ __forceinline__ uint32_t word(const words &t, int i) {
+        if constexpr (VEC > 2) return t[i]; else return t;
+    }
+    static __device__ __forceinline__ void unpack(const words &t, float (&v)[VEC]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { v[2 * i] = __uint_as_float(w[i] << 16); v[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
+        for (int i = 0; i < VEC / 2; ++i) {
+            const uint32_t w = word(t, i);
+            v[2 * i] = __uint_as_float(w << 16);
+            v[2 * i + 1] = __uint_as_float(w & 0xFFFF0000u);
+        }
     }
-    static __device__ __forceinline__ void load(const bf16_t *p, float (&v)[8]) {
-        uint4 t = *reinterpret_cast<const uint4 *>(p);
-        uint32_t w[4] = {t.x, t.y, t.z, t.w};
-        unpack(w, v);
-    }
-    static __device__ __forceinline__ void load_nt(const bf16_t *p, float (&v)[8]) {
-        u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-        uint32_t w[4] = {t.x, t.y, t.z, t.w};
-        unpack(w, v);
-    }
-    static __device__ __forceinline__ void store(bf16_t *p, const float (&v)[8]) {
-        uint32_t w[4];
+    static __device__ __forceinline__ words pack(const float (&v)[VEC]) {
+        words t;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = uint32_t(f32_to_bf16(v[2 * i])) | (uint32_t(f32_to_bf16(v[2 * i + 1])) << 16);
-        u32x4 t = {w[0], w[1], w[2], w[3]};
-        __builtin_nontemporal_store(t, reinterpret_cast<u32x4 *>(p));
+        for (int i = 0; i < VEC / 2; ++i) {
+            const uint32_t w = uint32_t(f32_to_bf16(v[2 * i])) | (uint32_t(f32_to_bf16(v[2 * i + 1])) << 16);
+            if constexpr (VEC > 2) t[i] = w; else t = w;
+        }
+        return t;
     }
-};
-template <> struct VecIO<bf16_t, 4> {
-    static __device__ __forceinline__ void load(const bf16_t *p, float (&v)[4]) {
-        uint2 t = *reinterpret_cast<const uint2 *>(p);
-        v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xFFFF0000u);
-        v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xFFFF0000u);
+    static __device__ __forceinline__ void load(const bf16_t *p, float (&v)[VEC]) { unpack(words(*reinterpret_cast<const words_any *>(p)), v); }
+    static __device__ __forceinline__ void load_nt(const bf16_t *p, float (&v)[VEC]) {
+        unpack(words(__builtin_nontemporal_load(reinterpret_cast<const words_any *>(p))), v);
     }
-    static __device__ __forceinline__ void load_nt(const bf16_t *p, float (&v)[4]) {
-        u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p));
-        v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xFFFF0000u);
-        v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xFFFF0000u);
-    }
-    static __device__ __forceinline__ void store(bf16_t *p, const float (&v)[4]) {
-        u32x2 t;
-        t.x = uint32_t(f32_to_bf16(v[0])) | (uint32_t(f32_to_bf16(v[1])) << 16);
-        t.y = uint32_t(f32_to_bf16(v[2])) | (uint32_t(f32_to_bf16(v[3])) << 16);
-        __builtin_nontemporal_store(t, reinterpret_cast<u32x2 *>(p));
-    }
-};
-template <> struct VecIO<bf16_t, 2> {
-    static __device__ __forceinline__ void load(const bf16_t *p, float (&v)[2]) {
-        uint32_t t = *reinterpret_cast<const uint32_t *>(p);
-        v[0] = __uint_as_float(t << 16); v[1] = __uint_as_float(t & 0xFFFF0000u);
-    }
-    static __device__ __forceinline__ void load_nt(const bf16_t *p, float (&v)[2]) {
-        uint32_t t = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p));
-        v[0] = __uint_as_float(t << 16); v[1] = __uint_as_float(t & 0xFFFF0000u);
-    }
-    static __device__ __forceinline__ void store(bf16_t *p, const float (&v)[2]) {
-        __builtin_nontemporal_store(uint32_t(f32_to_bf16(v[0])) | (uint32_t(f32_to_bf16(v[1])) << 16), reinterpret_cast<uint32_t *>(p));
-    }
+    static __device__ __forceinline__ void store(bf16_t *p, const float (&v)[VEC]) { __builtin_nontemporal_store(pack(v), reinterpret_cast<words *>(p)); }
+    static __device__ __forceinline__ void store_any(bf16_t *p, const float (&v)[VEC]) { *reinterpret_cast<words_any *>(p) = pack(v); }
 };
 template <> struct VecIO<bf16_t, 1> {
     static __device__ __forceinline__ void load(const bf16_t *p, float (&v)[1]) { v[0] = bf16_to_f32(p->bits); }
@@ -210,25 +205,27 @@ template <> struct VecIO<bf16_t, 1> {
         v[0] = bf16_to_f32(__builtin_nontemporal_load(&p->bits));
     }
     static __device__ __forceinline__ void store(bf16_t *p, const float (&v)[1]) { __builtin_nontemporal_store(f32_to_bf16(v[0]), &p->bits); }
+    static __device__ __forceinline__ void store_any(bf16_t *p, const float (&v)[1]) { p->bits = f32_to_bf16(v[0]); }
 };
 
 // A gathered strip stays in the registers the load filled (the packed bits: 16 bytes are four
 // registers whether they hold 4 floats or 8 bf16) until it is added; unpacking at the load would
 // keep U * VEC floats alive per lane and halve the occupancy of the bf16 kernels.
 template <int BYTES> struct RawBits;
-template <> struct RawBits<16> { typedef u32x4 type; };
-template <> struct RawBits<8> { typedef u32x2 type; };
-template <> struct RawBits<4> { typedef uint32_t type; };
-template <> struct RawBits<2> { typedef uint16_t type; };
+template <> struct RawBits<16> { typedef u32x4 type; typedef u32x4_any any; };
+template <> struct RawBits<8> { typedef u32x2 type; typedef u32x2_any any; };
+template <> struct RawBits<4> { typedef uint32_t type; typedef u32_any any; };
+template <> struct RawBits<2> { typedef uint16_t type; typedef uint16_t any; };
 
 template <typename T, int VEC>
 struct Strip {
     static constexpr int BYTES = int(sizeof(T)) * VEC;
     static constexpr int WORDS = BYTES >= 4 ? BYTES / 4 : 1;
     using raw_t = typename RawBits<BYTES>::type;
-    static __device__ __forceinline__ raw_t load(const T *p) { return *reinterpret_cast<const raw_t *>(p); }
+    using any_t = typename RawBits<BYTES>::any;  // at the alignment of one element
+    static __device__ __forceinline__ raw_t load(const T *p) { return *reinterpret_cast<const any_t *>(p); }
     static __device__ __forceinline__ raw_t load_nt(const T *p) {
-        return __builtin_nontemporal_load(reinterpret_cast<const raw_t *>(p));
+        return __builtin_nontemporal_load(reinterpret_cast<const any_t *>(p));
     }
     static __device__ __forceinline__ raw_t zero() {
         if constexpr (BYTES >= 8) { raw_t z; for (int i = 0; i < WORDS; ++i) z[i] = 0u; return z; }
@@ -260,39 +257,30 @@ template <int VEC>
 __device__ __forceinline__ void store_f32(float *p, const float (&v)[VEC]) {
     if constexpr (VEC % 4 == 0) {
 #pragma unroll
-        for (int i = 0; i < VEC; i += 4) *reinterpret_cast<float4 *>(p + i) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
+        for (int i = 0; i < VEC; i += 4) *reinterpret_cast<f32x4_any *>(p + i) = f32x4_any{v[i], v[i + 1], v[i + 2], v[i + 3]};
     } else if constexpr (VEC == 2) {
-        *reinterpret_cast<float2 *>(p) = make_float2(v[0], v[1]);
+        *reinterpret_cast<f32x2_any *>(p) = f32x2_any{v[0], v[1]};
     } else {
         *p = v[0];
     }
 }
 
-// Output strip: one vector store when the output rows allow it, else narrower pieces; a
-// partial last strip (padded gather source) writes only its valid columns.
+// Output strip: one non-temporal vector store where the output rows are aligned for it (store_vec == VEC), else one
+// plain store at the alignment of an element, which the L2 merges into lines before they are written back
+// (non-temporal pieces reach memory as partial lines); a partial last strip (padded gather source) writes only its
+// valid columns.
 template <typename T, int VEC>
 __device__ __forceinline__ void store_strip(T *y, const float (&o)[VEC], int ncols, int store_vec) {
-    if (ncols == VEC && store_vec == VEC) {
-        VecIO<T, VEC>::store(y, o);
+    if (ncols == VEC) {
+        if (store_vec == VEC) VecIO<T, VEC>::store(y, o);
+        else VecIO<T, VEC>::store_any(y, o);
         return;
     }
-    if constexpr (VEC >= 2) {
-        if (ncols == VEC && store_vec * 2 == VEC) {
-            float lo[VEC / 2], hi[VEC / 2];
-#pragma unroll
-            for (int i = 0; i < VEC / 2; ++i) { lo[i] = o[i]; hi[i] = o[VEC / 2 + i]; }
-            VecIO<T, VEC / 2>::store(y, lo);
-            VecIO<T, VEC / 2>::store(y + VEC / 2, hi);
-            return;
-        }
-    }
-    // single elements: plain stores, so that the L2 merges the pieces of a line before it is
-    // written back (non-temporal 4-byte stores reach memory as partial lines)
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
         if (i < ncols) {
-            if constexpr (sizeof(T) == 4) *reinterpret_cast<float *>(y + i) = o[i];
-            else reinterpret_cast<uint16_t *>(y + i)[0] = f32_to_bf16(o[i]);
+            const float one[1] = {o[i]};
+            VecIO<T, 1>::store_any(y + i, one);
         }
     }
 }
@@ -336,10 +324,12 @@ __device__ __forceinline__ float own_row_value(const OwnRowSrc &o, int64_t row, 
 // ---------------------------------------------------------------- main kernel
 // T: storage type of X and Y.  VEC: elements per lane per load.  NPASS: feature
 // passes (a lane owns NPASS strips of VEC columns, C*VEC apart).  COEF: edges
-// carry a coefficient (explicit weight and/or a scale of the gathered vertex).
-template <typename T, int VEC, int NPASS, bool COEF>
+// carry a coefficient (explicit weight and/or a scale of the gathered vertex).  COOP: some bins are
+// shared by the wavefronts of a workgroup (a variant of its own: it costs the others a wavefront per SIMD).
+template <typename T, int VEC, int NPASS, bool COEF, bool COOP = false>
 __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs a) {
     constexpr int U = NPASS >= 4 ? 2 : (NPASS >= 2 ? 4 : 8);  // edges in flight per slot
+    __shared__ float coop_sums[COOP ? (kWavesPerBlock - 1) * NPASS * VEC * 64 : 1];  // of wavefronts 1 .. 3, by column and lane
     const int lane = threadIdx.x & 63;
     const int wave_in_block = threadIdx.x >> 6;
 
@@ -353,7 +343,8 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     for (int i = 1; i < a.n_bins; ++i)
         if (vblock >= a.bins[i].first_block) b = i;
     const BinDesc bin = a.bins[b];
-    const int64_t wave_in_bin = (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;
+    const bool coop = COOP && (bin.kind & GNN_BIN_COOP);
+    const int64_t wave_in_bin = coop ? vblock - bin.first_block : (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;
 
     const int G = 1 << bin.log2_g;
     const int SR = 1 << bin.log2_sr;
@@ -368,8 +359,8 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     // e0..e1 index `indices`; the per-edge streams of the caller (weights, factors) live at e + wdelta
     int64_t e0 = 0, e1 = 0, row = -1, row_len = 0, wdelta = 0;
     float *partial_out = nullptr;
-    if (bin.kind == kKindHubPieces) {
-        const int64_t piece = wave_in_bin;  // G == 64: one piece per wavefront
+    if (bin.kind & kKindHubPieces) {
+        const int64_t piece = wave_in_bin;  // G == 64: one piece per wavefront (per workgroup when shared)
         if (piece < bin.n_items) {
             if (a.p_chunks) {
                 const int64_t *p = a.p_chunks + 4 * (bin.item_begin + piece);
@@ -395,6 +386,11 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
             row_len = e1 - e0;
         }
     }
+    if (coop) {  // this wavefront's quarter of the list
+        const int64_t quarter = (e1 - e0 + kWavesPerBlock - 1) / kWavesPerBlock;
+        e0 += wave_in_block * quarter;
+        if (e0 + quarter < e1) e1 = e0 + quarter;
+    }
 
     float acc[NPASS][VEC];
 #pragma unroll
@@ -414,10 +410,11 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     bool col_ok[NPASS];
 #pragma unroll
     for (int p = 0; p < NPASS; ++p) {
-        const int lc = (p * C + c) * VEC;
+        int lc = (p * C + c) * VEC;
+        col_ok[p] = lc < Fk;
+        if (a.overlap && lc > Fk - VEC) lc = Fk - VEC;  // may begin in the slice before: those columns get the same values there
         col[p] = col_base + lc;
         lcol[p] = own_table ? lc : col[p];
-        col_ok[p] = lc < Fk;
         ncols[p] = Fk - lc < VEC ? Fk - lc : VEC;
     }
 
@@ -537,8 +534,26 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
             for (int i = 0; i < VEC; ++i) acc[p][i] += __shfl_xor(acc[p][i], off);
     }
 
+    if constexpr (COOP) {
+        if (coop) {  // the quarters are added in order
+            if (wave_in_block > 0) {
+#pragma unroll
+                for (int p = 0; p < NPASS; ++p)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) coop_sums[(((wave_in_block - 1) * NPASS + p) * VEC + i) * 64 + lane] = acc[p][i];
+            }
+            __syncthreads();
+            if (wave_in_block > 0) return;
+#pragma unroll
+            for (int w = 0; w < kWavesPerBlock - 1; ++w)
+#pragma unroll
+                for (int p = 0; p < NPASS; ++p)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc[p][i] += coop_sums[((w * NPASS + p) * VEC + i) * 64 + lane];
+        }
+    }
     if (row < 0 || s != 0) return;
-    if (bin.kind == kKindHubPieces) {
+    if (bin.kind & kKindHubPieces) {
 #pragma unroll
         for (int p = 0; p < NPASS; ++p)
             if (col_ok[p]) store_f32<VEC>(partial_out + col[p], acc[p]);
@@ -849,14 +864,19 @@ __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__rest
     store_strip<T, VEC>(Y + row * ldy + col0, o, ncols, store_vec);
 }
 
-// Copies the gathered matrix into rows of whole 128-byte lines (plan-owned buffer), so that
-// 16-byte loads and XCD column slices apply to widths like 100 or 602.  One thread per chunk of
-// sizeof(V) bytes; V is the widest type the source rows allow.
-template <typename V>
-__global__ void __launch_bounds__(256) pad_rows_kernel(const V *__restrict__ src, int64_t ld_src, V *__restrict__ dst,
-                                                       int64_t ld_dst, int64_t N, int chunks_per_row,
+// Copies the gathered matrix into rows of whole 16-byte chunks (plan-owned buffer: lines of 128 bytes, power-of-two rows,
+// or the groups of a dense tail), so that aligned loads and XCD column slices apply to widths like 100 or 602.  One
+// thread per chunk, loaded at the alignment of an element; a row's last, partial chunk is filled up with zeros.
+// SCALE (fp32): row v is multiplied by the factor its vertex carries as a gathered row (1/din, 1/sqrt(deg) or
+// 1/(din+1)): folding the factor into the copy that happens anyway saves the per-edge factor stream and the
+// per-edge multiply of MEAN / SAGE_GCN backward and GCN.
+template <typename T, bool SCALE>
+__global__ void __launch_bounds__(256) pad_rows_kernel(const T *__restrict__ src, int64_t ld_src, T *__restrict__ dst, int64_t ld_dst,
+                                                       int64_t N, int F, int mode, const int32_t *__restrict__ counts,
                                                        const int32_t *__restrict__ row_map, int log2_chunks_per_line,
                                                        int64_t table_stride, int log2_tpr) {
+    constexpr int W = 16 / int(sizeof(T));
+    const int chunks_per_row = (F + W - 1) / W;
     // 2^log2_tpr consecutive threads walk the chunks of one row (no division per chunk)
     const int tpr = 1 << log2_tpr;
     const int64_t rows_per_block = blockDim.x >> log2_tpr;
@@ -864,57 +884,40 @@ __global__ void __launch_bounds__(256) pad_rows_kernel(const V *__restrict__ src
     for (int64_t row = int64_t(blockIdx.x) * rows_per_block + (threadIdx.x >> log2_tpr); row < N;
          row += int64_t(gridDim.x) * rows_per_block) {
         const int64_t drow = row_map ? int64_t(row_map[row]) : row;
-        const V *in = src + row * ld_src;
+        const float f = SCALE ? scale_of(mode, counts[row]) : 1.0f;
+        const T *in = src + row * ld_src;
         for (int c = c0; c < chunks_per_row; c += tpr) {
             // row-major: log2_chunks_per_line is 31 (one table); slice-major: one table per line
             const int line = c >> log2_chunks_per_line, within = c - (line << log2_chunks_per_line);
-            // 16-byte chunks go out non-temporal; smaller ones as plain stores, which the L2 merges into lines
-            V *q = &dst[line * table_stride + drow * ld_dst + within];
-            if constexpr (sizeof(V) >= 16) __builtin_nontemporal_store(in[c], q);
-            else *q = in[c];
-        }
-    }
-}
-
-// Same copy for fp32 rows, with row v multiplied by the factor its vertex carries as a gathered
-// row (1/din, 1/sqrt(deg) or 1/(din+1)): folding the factor into the copy that happens anyway
-// saves the per-edge factor stream and the per-edge multiply of MEAN / SAGE_GCN backward and GCN.
-template <int W>
-__global__ void __launch_bounds__(256) pad_scale_rows_kernel(const float *__restrict__ src, int64_t ld_src,
-                                                             float *__restrict__ dst, int64_t ld_dst, int64_t N,
-                                                             int chunks_per_row, int mode,
-                                                             const int32_t *__restrict__ counts,
-                                                             const int32_t *__restrict__ row_map, int log2_chunks_per_line,
-                                                             int64_t table_stride, int log2_tpr) {
-    const int tpr = 1 << log2_tpr;
-    const int64_t rows_per_block = blockDim.x >> log2_tpr;
-    const int c0 = threadIdx.x & (tpr - 1);
-    for (int64_t row = int64_t(blockIdx.x) * rows_per_block + (threadIdx.x >> log2_tpr); row < N;
-         row += int64_t(gridDim.x) * rows_per_block) {
-        const float f = scale_of(mode, counts[row]);
-        const int64_t drow = row_map ? int64_t(row_map[row]) : row;
-        const float *in = src + row * ld_src;
-        for (int c = c0; c < chunks_per_row; c += tpr) {
-            float v[W];
-            VecIO<float, W>::load(in + int64_t(c) * W, v);
-#pragma unroll
-            for (int i = 0; i < W; ++i) v[i] *= f;
-            const int line = c >> log2_chunks_per_line, within = c - (line << log2_chunks_per_line);
-            float *q = dst + line * table_stride + drow * ld_dst + int64_t(within) * W;
-            if constexpr (W == 4) {
-                VecIO<float, 4>::store(q, v);
+            u32x4 v = {0u, 0u, 0u, 0u};
+            const T *p = in + c * W;
+            if (c * W + W <= F) {
+                v = *reinterpret_cast<const u32x4_any *>(p);
             } else {
 #pragma unroll
-                for (int i = 0; i < W; ++i) q[i] = v[i];
+                for (int i = 0; i < W; ++i) {
+                    if (c * W + i < F) {
+                        if constexpr (sizeof(T) == 4) v[i] = __float_as_uint(p[i]);
+                        else v[i >> 1] |= uint32_t(p[i].bits) << (16 * (i & 1));
+                    }
+                }
             }
+            if constexpr (SCALE && sizeof(T) == 4) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = __float_as_uint(__uint_as_float(v[i]) * f);
+            }
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst + line * table_stride + drow * ld_dst + int64_t(within) * W));
         }
     }
 }
 
-// Threads per row of the pad kernels (a power of two <= 256 covering the row's chunks) and the grid.
-static inline void pad_launch_shape(int64_t N, int cpr, int *log2_tpr, unsigned *blocks) {
-    // the power of two (>= 8 threads: one 128-byte line of 16-byte chunks) that leaves the fewest idle
-    // slots in the last round over the row's chunks; the widest among equals
+// mode: the factor of the rows (kScaleNone: none).  dst is aligned to 16 bytes, ld_dst and table_stride are whole chunks.
+template <typename T>
+hipError_t launch_pad(const void *src, int64_t ld_src, void *dst, int64_t ld_dst, int64_t N, int64_t F, int mode, const int32_t *counts,
+                      hipStream_t stream, const int32_t *row_map = nullptr, int64_t table_stride = 0) {
+    const int cpr = int((F * int64_t(sizeof(T)) + 15) / 16);
+    // threads per row: the power of two (>= 8 threads: one 128-byte line) that leaves the fewest idle slots in the last
+    // round over the row's chunks; the widest among equals
     int l = 0;
     int64_t best_waste = INT64_MAX;
     for (int cand = 8; cand >= 3; --cand) {
@@ -922,49 +925,35 @@ static inline void pad_launch_shape(int64_t N, int cpr, int *log2_tpr, unsigned 
         const int64_t waste = (cpr + tpr - 1) / tpr * tpr - cpr;
         if (waste < best_waste) { best_waste = waste; l = cand; }
     }
-    if (cpr < 8) { l = 0; while ((1 << l) < cpr) ++l; }
-    *log2_tpr = l;
+    if (cpr < 8) l = gnn_ilog2_ceil(cpr);
     const int64_t rows_per_block = 256 >> l;
     int64_t b = (N + rows_per_block - 1) / rows_per_block;
     if (b > (int64_t(1) << 17)) b = int64_t(1) << 17;
-    *blocks = static_cast<unsigned>(b > 0 ? b : 1);
-}
-
-template <int W>
-hipError_t launch_pad_scale(const void *src, int64_t ld_src, void *dst, int64_t ld_dst, int64_t N, int64_t F, int mode,
-                            const int32_t *counts, hipStream_t stream, const int32_t *row_map = nullptr,
-                            int64_t table_stride = 0) {
-    const int cpr = int(F / W);
-    int log2_tpr;
-    unsigned blocks;
-    pad_launch_shape(N, cpr, &log2_tpr, &blocks);
-    pad_scale_rows_kernel<W><<<blocks, 256, 0, stream>>>(
-        static_cast<const float *>(src), ld_src, static_cast<float *>(dst), ld_dst, N, cpr, mode, counts, row_map,
-        table_stride > 0 ? gnn_ilog2_ceil(32 / W) : 31, table_stride, log2_tpr);
-    return hipGetLastError();
-}
-
-template <typename V>
-hipError_t launch_pad(const void *src, int64_t ld_src_bytes, void *dst, int64_t ld_dst_bytes, int64_t N,
-                      int64_t row_bytes, hipStream_t stream, const int32_t *row_map = nullptr,
-                      int64_t table_stride_bytes = 0) {
-    const int cpr = int(row_bytes / sizeof(V));
-    int log2_tpr;
-    unsigned blocks;
-    pad_launch_shape(N, cpr, &log2_tpr, &blocks);
-    pad_rows_kernel<V><<<blocks, 256, 0, stream>>>(
-        static_cast<const V *>(src), ld_src_bytes / int64_t(sizeof(V)), static_cast<V *>(dst),
-        ld_dst_bytes / int64_t(sizeof(V)), N, cpr, row_map,
-        table_stride_bytes > 0 ? gnn_ilog2_ceil(int64_t(128 / sizeof(V))) : 31, table_stride_bytes / int64_t(sizeof(V)), log2_tpr);
+    const dim3 grid(static_cast<unsigned>(b > 0 ? b : 1));
+    const int chunks_per_line = table_stride > 0 ? 3 : 31;
+    if (sizeof(T) == 4 && mode != kScaleNone)
+        pad_rows_kernel<T, true><<<grid, 256, 0, stream>>>(static_cast<const T *>(src), ld_src, static_cast<T *>(dst), ld_dst, N, int(F), mode, counts,
+                                                           row_map, chunks_per_line, table_stride, l);
+    else
+        pad_rows_kernel<T, false><<<grid, 256, 0, stream>>>(static_cast<const T *>(src), ld_src, static_cast<T *>(dst), ld_dst, N, int(F), mode, counts,
+                                                            row_map, chunks_per_line, table_stride, l);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- host side
 template <typename T, int VEC, bool COEF>
 hipError_t launch_npass(int npass, dim3 grid, hipStream_t stream, const AggArgs &a) {
+    bool coop = false;
+    for (int i = 0; i < a.n_bins; ++i) coop |= (a.bins[i].kind & GNN_BIN_COOP) != 0;
     switch (npass) {
-        case 1: aggregate_kernel<T, VEC, 1, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
-        case 2: aggregate_kernel<T, VEC, 2, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
+        case 1:
+            if (coop) aggregate_kernel<T, VEC, 1, COEF, true><<<grid, kBlockThreads, 0, stream>>>(a);
+            else aggregate_kernel<T, VEC, 1, COEF><<<grid, kBlockThreads, 0, stream>>>(a);
+            break;
+        case 2:
+            if (coop) aggregate_kernel<T, VEC, 2, COEF, true><<<grid, kBlockThreads, 0, stream>>>(a);
+            else aggregate_kernel<T, VEC, 2, COEF><<<grid, kBlockThreads, 0, stream>>>(a);
+            break;
         case 3: aggregate_kernel<T, VEC, 3, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
         case 4: aggregate_kernel<T, VEC, 4, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
         case 5: aggregate_kernel<T, VEC, 5, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
@@ -1101,25 +1090,11 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         const bool scale_in_copy = esz == 4 && src_mode != kScaleNone;  // fp32: the factor of the gathered rows goes into the copy
         factor_in_tables = scale_in_copy;
         if ((prepacked || pack_only) && !rank) return GNN_ERR_UNSUPPORTED;
-        const int copy_mode = src_mode;
-        // copies `ncols` columns starting at `src` into rows of stride dst_ld, with the widest chunks the source allows
+        const int copy_mode = scale_in_copy ? src_mode : int(kScaleNone);
+        // copies `ncols` columns starting at `src` into rows of stride dst_ld
         auto copy_part = [&](const char *src, int64_t ncols, char *dst, int64_t dst_ld, int64_t tstride) -> hipError_t {
-            const int64_t row_bytes = ncols * esz, src_ld_bytes = ldx * esz, dst_ld_bytes = dst_ld * esz;
-            const uintptr_t addr = reinterpret_cast<uintptr_t>(src);
-            if (scale_in_copy) {
-                if (row_bytes % 16 == 0 && src_ld_bytes % 16 == 0 && addr % 16 == 0)
-                    return launch_pad_scale<4>(src, ldx, dst, dst_ld, N, ncols, copy_mode, plan->col_counts, stream, rank, tstride);
-                if (row_bytes % 8 == 0 && src_ld_bytes % 8 == 0 && addr % 8 == 0)
-                    return launch_pad_scale<2>(src, ldx, dst, dst_ld, N, ncols, copy_mode, plan->col_counts, stream, rank, tstride);
-                return launch_pad_scale<1>(src, ldx, dst, dst_ld, N, ncols, copy_mode, plan->col_counts, stream, rank, tstride);
-            }
-            if (row_bytes % 16 == 0 && src_ld_bytes % 16 == 0 && addr % 16 == 0)
-                return launch_pad<u32x4>(src, src_ld_bytes, dst, dst_ld_bytes, N, row_bytes, stream, rank, tstride * esz);
-            if (row_bytes % 8 == 0 && src_ld_bytes % 8 == 0 && addr % 8 == 0)
-                return launch_pad<u32x2>(src, src_ld_bytes, dst, dst_ld_bytes, N, row_bytes, stream, rank, tstride * esz);
-            if (row_bytes % 4 == 0 && src_ld_bytes % 4 == 0 && addr % 4 == 0)
-                return launch_pad<uint32_t>(src, src_ld_bytes, dst, dst_ld_bytes, N, row_bytes, stream, rank, tstride * esz);
-            return launch_pad<uint16_t>(src, src_ld_bytes, dst, dst_ld_bytes, N, row_bytes, stream, rank, tstride * esz);
+            if (esz == 4) return launch_pad<float>(src, ldx, dst, dst_ld, N, ncols, copy_mode, plan->col_counts, stream, rank, tstride);
+            return launch_pad<bf16_t>(src, ldx, dst, dst_ld, N, ncols, kScaleNone, nullptr, stream, rank, tstride);
         };
         const int64_t main_cols = F - layout.tail_elems;
         char *dst = static_cast<char *>(tables);
@@ -1154,16 +1129,15 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     }
     const bool coef = (w != nullptr) || src_mode != kScaleNone;
 
-    // Widest load the gathered rows allow.  Only the padded copy may be read past column F (its
-    // rows end in padding that belongs to the buffer); a caller's matrix needs F % vec == 0 unless
-    // the caller vouches for the padding (GNN_FLAG_PADDED_ROWS).
+    // Loads of 16 bytes whatever the alignment.  Rows that end in padding (the plan's copies, or where the caller vouches
+    // for it with GNN_FLAG_PADDED_ROWS) are read past column F; elsewhere the last strip of a row begins early enough
+    // to end with it.
     int vec = max_vec;
-    const bool rows_padded = padded || (o.flags & GNN_FLAG_PADDED_ROWS) != 0;  // then ldg % vec == 0 covers the over-read
-    while (vec > 1 && !(ldg % vec == 0 && reinterpret_cast<uintptr_t>(gathered) % (uintptr_t(vec) * esz) == 0 &&
-                        (rows_padded || F % vec == 0)))
-        vec >>= 1;
-    // Widest store the output rows allow (partial strips fall back to single elements).
-    int store_vec = vec;
+    const bool rows_padded = padded || ((o.flags & GNN_FLAG_PADDED_ROWS) && ldg % max_vec == 0);
+    while (vec > 1 && !rows_padded && vec > F) vec >>= 1;
+    const int overlap = !rows_padded && F % vec != 0 ? 1 : 0;
+    // Widest non-temporal store the output rows allow.
+    int store_vec = overlap ? 1 : vec;
     while (store_vec > 1 && !(ldy % store_vec == 0 && reinterpret_cast<uintptr_t>(out) % (uintptr_t(store_vec) * esz) == 0))
         store_vec >>= 1;
 
@@ -1400,6 +1374,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         a.log2_slices = log2_s;
         a.slice_cols = int32_t(slice_cols);
         a.store_vec = store_vec;
+        a.overlap = overlap;
         a.row_map = rank_indices ? rank : nullptr;
         a.p_indptr = rank_indices ? rl.p_indptr : nullptr;
         a.p_chunks = rank_indices ? rl.p_chunks : nullptr;
@@ -1482,7 +1457,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             if (f0 < plain_hub_col_begin) plain_hub_col_begin = f0;
         }
         int32_t nb = 0;
-        int64_t next_block = gnn_fill_bins(a.bins, &nb, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX);
+        int64_t next_block = gnn_fill_bins(a.bins, &nb, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX, 1 << log2_s, npass <= kCoopMaxPass);
         a.n_bins = nb;
         if (nb == 0 || next_block == 0) continue;
         next_block <<= log2_s;
@@ -1525,19 +1500,9 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
 
 }  // namespace
 
-// Copy of an fp32 matrix into rows of another stride (the plan-owned padded matrix), with the
-// widest chunks the source allows (used by ap.hip).
+// Copy of an fp32 matrix into rows of another stride (the plan-owned padded matrix; used by ap.hip).
 int gnn_pad_rows_f32(const float *src, int64_t ld_src, float *dst, int64_t ld_dst, int64_t N, int64_t F, hipStream_t stream) {
-    const int64_t row_bytes = F * 4, src_ld_bytes = ld_src * 4, dst_ld_bytes = ld_dst * 4;
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(src);
-    hipError_t err;
-    if (row_bytes % 16 == 0 && src_ld_bytes % 16 == 0 && addr % 16 == 0)
-        err = launch_pad<u32x4>(src, src_ld_bytes, dst, dst_ld_bytes, N, row_bytes, stream);
-    else if (row_bytes % 8 == 0 && src_ld_bytes % 8 == 0 && addr % 8 == 0)
-        err = launch_pad<u32x2>(src, src_ld_bytes, dst, dst_ld_bytes, N, row_bytes, stream);
-    else
-        err = launch_pad<uint32_t>(src, src_ld_bytes, dst, dst_ld_bytes, N, row_bytes, stream);
-    return err == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
+    return launch_pad<float>(src, ld_src, dst, ld_dst, N, F, kScaleNone, nullptr, stream) == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
 }
 
 int gnn_packed_target_for(gnn_plan *plan, const void *indptr, const int32_t *indices, int64_t N, int64_t F, int op, bool backward,

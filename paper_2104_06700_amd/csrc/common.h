@@ -271,11 +271,13 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
     // sliced, one line each of 32768 rows.  Slicing is used when that wins at least 8 points of
     // the gathers (a power-law graph of a few million vertices: +20..30 points; a 111 M-vertex
     // graph with 2-line rows: ~+2 points, where the extra index reads and the loss of burst
-    // locality cost more than the hits bring: 76.2 ms sliced, 74.1 ms without slices).
+    // locality cost more than the hits bring: 76.2 ms sliced, 74.1 ms without slices).  Matrices that fit the
+    // L2s together are sliced for the sake of more, shorter wavefronts (24,490 vertices, 1.2 M edges, F=100:
+    // 0.095 ms in one launch of whole rows, 0.045 in four slices).
     L.slices_wanted = !(flags & GNN_FLAG_NO_COLUMN_SLICES);
     if (L.slices_wanted && plan && plan->n_edges > 0 && max_slices == 0) {
         const double gain = gnn_plan_top_share(plan, 32768) - gnn_plan_top_share(plan, 32768 / (lines > 0 ? lines : 1));
-        L.slices_wanted = gain >= 0.08;
+        L.slices_wanted = gain >= 0.08 || N * row_bytes < (int64_t(32) << 20);
     }
     // Column slices make XCD k read the same lines (k, k+S, ...) of every row.  With a row stride
     // of an even number of lines those addresses share their low line-index bits and crowd a few
@@ -329,7 +331,8 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
     // vertices: F=100 4.84 -> 4.74 ms, F=112 5.08 -> 4.55; 233 K vertices F=100 2.63 -> 2.44).  Packed
     // copies kept by a caller never have the tail table (GNN_FLAG_NO_DENSE_TAIL): their size must not depend
     // on the plan.
-    const bool dense_tail = allow_tail && !blocks_expected && !(flags & GNN_FLAG_NO_DENSE_TAIL);
+    // ... nor do small matrices: a launch more costs them more than the padding.
+    const bool dense_tail = allow_tail && !blocks_expected && !(flags & GNN_FLAG_NO_DENSE_TAIL) && (big || (flags & GNN_FLAG_FORCE_PADDED_COPY));
     if (dense_tail && L.padded_copy && L.slices_wanted && lines >= 2 && lines <= 256 && rest > 0 && rest * esz <= 64) {
         const int64_t group = 16 / esz;
         L.tail_elems = rest;
@@ -426,7 +429,8 @@ int gnn_aggregate_fwd_epilogue(const void *indptr, const int32_t *indices, const
 // table of bins (heaviest work first).  A bin holds rows (64 >> log2_g rows per wavefront, each row
 // group being 2^(log2_g - log2_sr) column lanes x 2^log2_sr edge slots) or hub pieces (one per
 // wavefront).
-enum gnn_bin_kind : int32_t { GNN_BIN_ROWS = 0, GNN_BIN_HUB_PIECES = 1 };
+// GNN_BIN_COOP: the four wavefronts of a workgroup share one row (one piece) at a time.
+enum gnn_bin_kind : int32_t { GNN_BIN_ROWS = 0, GNN_BIN_HUB_PIECES = 1, GNN_BIN_COOP = 2 };
 
 struct gnn_bin_desc {
     int64_t first_block;  // first workgroup index of this bin (before any slice interleaving)
@@ -443,8 +447,16 @@ constexpr int GNN_WAVES_PER_BLOCK = 4;  // 256-thread workgroups
 // Fills `bins` for a launch whose row groups have 2^log2_c column lanes; returns the number of
 // workgroups.  plan == nullptr: all N rows in one bin, whole wavefronts per row.
 // first_excluded_bin: rows of bins >= it (and the hub pieces) are left out (they are served as source-blocked pieces).
+// slices: column slices the launch multiplies the workgroups by.  coop_ok: the kernel knows GNN_BIN_COOP.
+//
+// A launch that leaves most of the chip idle is bound by latency: the time of a row is the number of its steps (one
+// batch of loads each, about a microsecond), one after the other.  So where there are too few wavefronts, rows get more
+// edge slots than throughput asks for, and where the steps of a long row or of a hub piece outlast the launch's
+// share per wavefront, the four wavefronts of a workgroup share it (24,490 vertices, 1.2 M edges, F=100: 0.33 -> 0.06 ms).
 static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, const gnn_plan *plan, int64_t N, int log2_c,
-                                    int first_excluded_bin = INT32_MAX) {
+                                    int first_excluded_bin = INT32_MAX, int slices = 1, bool coop_ok = false) {
+    constexpr int64_t kWaveSlots = 256 * 4 * 8;  // wavefronts the chip holds of a kernel with 64 registers
+    constexpr int kStepLog2 = 3;                 // loads of a slot in flight: edges per step
     const int max_log2_sr = 6 - log2_c;
     int64_t next_block = 0;
     int nb = 0;
@@ -456,29 +468,49 @@ static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, const g
         d.n_items = n_items;
         d.kind = kind;
         d.log2_sr = log2_sr;
-        d.log2_g = kind == GNN_BIN_HUB_PIECES ? 6 : log2_c + log2_sr;
+        d.log2_g = (kind & (GNN_BIN_HUB_PIECES | GNN_BIN_COOP)) ? 6 : log2_c + log2_sr;
         d.pad = 0;
-        const int64_t items_per_block = int64_t(GNN_WAVES_PER_BLOCK) * (64 >> d.log2_g);
+        const int64_t items_per_block = (kind & GNN_BIN_COOP) ? 1 : int64_t(GNN_WAVES_PER_BLOCK) * (64 >> d.log2_g);
         next_block += (n_items + items_per_block - 1) / items_per_block;
     };
     if (plan) {
         const int last = plan->n_bins - 1;
         const bool has_hub = plan->n_chunks > 0;
-        // heaviest work first: hub pieces, then bins from long rows to short rows
-        if (has_hub && first_excluded_bin > last) add_bin(GNN_BIN_HUB_PIECES, 0, plan->n_chunks, max_log2_sr);
-        for (int bi = last; bi >= 0; --bi) {
-            if (bi >= first_excluded_bin) continue;
-            if (bi == last && has_hub) continue;  // handled as pieces (+ finalize)
+        // Edge slots per row: enough that the shortest row of the bin still takes ~16 steps of one edge (several
+        // batches of loads per group), so short rows share a wavefront (64/G rows each) and only long rows
+        // get a whole wavefront.
+        auto slots_of_bin = [&](int bi) {
             const int64_t lo = bi == 0 ? 0 : plan->params.thresholds[bi - 1];
-            // Edge slots per row: enough that the shortest row of the bin still takes ~16 steps
-            // (several batches of loads per group), so short rows share a wavefront (64/G rows
-            // each) and only long rows get a whole wavefront.
             int lsr = 0;
             while (lo > 1 && (int64_t(2) << lsr) <= lo) ++lsr;  // floor(log2(lo))
             lsr -= 4;
-            if (lsr < 0) lsr = 0;
-            if (lsr > max_log2_sr) lsr = max_log2_sr;
-            add_bin(GNN_BIN_ROWS, plan->bin_offsets[bi], plan->bin_offsets[bi + 1] - plan->bin_offsets[bi], lsr);
+            return lsr < 0 ? 0 : (lsr > max_log2_sr ? max_log2_sr : lsr);
+        };
+        int64_t waves = has_hub && first_excluded_bin > last ? plan->n_chunks : 0, steps = 0;
+        for (int bi = last; bi >= 0; --bi) {
+            if (bi >= first_excluded_bin) continue;
+            const int lsr = bi == last && has_hub ? max_log2_sr : slots_of_bin(bi);
+            if (!(bi == last && has_hub)) waves += ((plan->bin_offsets[bi + 1] - plan->bin_offsets[bi]) << (log2_c + lsr)) >> 6;
+            steps += plan->bin_edges[bi] >> (6 - log2_c + kStepLog2);  // of whole wavefronts
+        }
+        waves *= slices;
+        int boost = 0;
+        while (boost < 3 && (waves << (boost + 1)) <= kWaveSlots) ++boost;
+        const int64_t steps_per_slot = steps * slices / kWaveSlots;
+        auto coop = [&](int64_t longest) { return coop_ok && (longest >> (max_log2_sr + kStepLog2)) > 4 + 2 * steps_per_slot ? int(GNN_BIN_COOP) : 0; };
+        // heaviest work first: hub pieces, then bins from long rows to short rows
+        if (has_hub && first_excluded_bin > last)
+            add_bin(GNN_BIN_HUB_PIECES | coop(plan->params.hub_chunk), 0, plan->n_chunks, max_log2_sr);
+        for (int bi = last; bi >= 0; --bi) {
+            if (bi >= first_excluded_bin) continue;
+            if (bi == last && has_hub) continue;  // handled as pieces (+ finalize)
+            // the longest row of the bin (of the last one, without pieces: unknown)
+            const int64_t hi = bi < plan->params.n_thresholds ? plan->params.thresholds[bi] : plan->n_edges;
+            int lsr = slots_of_bin(bi);
+            // more slots while a slot keeps two edges of the bin's longest rows
+            for (int b = 0; b < boost && lsr < max_log2_sr && (int64_t(4) << lsr) <= hi; ++b) ++lsr;
+            const int c = coop(hi);
+            add_bin(GNN_BIN_ROWS | c, plan->bin_offsets[bi], plan->bin_offsets[bi + 1] - plan->bin_offsets[bi], c ? max_log2_sr : lsr);
         }
     } else {
         add_bin(GNN_BIN_ROWS, 0, N, max_log2_sr);

@@ -1,0 +1,57 @@
+"""Launches that leave most of the chip idle (more edge slots per row, long rows and hub pieces shared by the wavefronts of
+a workgroup) and rows of any width, stride and alignment (16-byte loads at the alignment of an element, the last strip
+of a row beginning early enough to end with it), against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2104_06700_amd as gnn
+import synth
+from helpers import OP_CODE, assert_close, device_graph, host_csr
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _graph():
+    """Rows of every length class up to a hub of 6,000 edges (duplicates allowed)."""
+    n = 700
+    lengths = [0, 1, 3, 4, 5, 15, 31, 63, 64, 255, 256, 257, 1023, 1025, 4095, 6000]
+    dst = torch.cat([torch.full((k,), 11 * i + 2, dtype=torch.int64) for i, k in enumerate(lengths)] +
+                    [torch.arange(n).repeat_interleave(7)])
+    src = (synth.mix64(torch.arange(dst.numel()) + 99) & 0x7FFFFFFF) % n
+    key = torch.sort(dst * n + src).values
+    return synth.EdgeList(n=n, src=(key % n).to(torch.int32), dst=(key // n).to(torch.int32), meta={})
+
+
+@pytest.mark.parametrize("dtype,widths", [(torch.float32, (1, 2, 3, 4, 5, 7, 33, 64, 99, 257, 515)),
+                                          (torch.bfloat16, (1, 3, 7, 8, 9, 33, 65, 130, 515, 1031))])
+@pytest.mark.parametrize("op_name,weights", [("sage", False), ("mean", True), ("gcn", False)])
+def test_rows_of_every_length_width_and_alignment(dtype, widths, op_name, weights):
+    el = _graph()
+    bf16 = dtype == torch.bfloat16
+    indptr, indices, indptr_t, indices_t, perm = host_csr(el)
+    din, dout = np.diff(indptr), np.diff(indptr_t)
+    wts = (synth.uniform_features(el.e, 1, 7).reshape(-1) + 0.5) if weights else None
+    w = None if wts is None else wts.numpy()
+    dg = device_graph(el, weights=wts)
+    op = OP_CODE[op_name]
+    for f in widths:
+        X = synth.normal_features(el.n, f, 3, dtype=dtype)
+        Yo, S = oracle.aggregate_fwd(indptr, indices, X.float().numpy(), op=op, w=w, dout=dout, nthreads=8, want_scale=True)
+        dXo, St = oracle.aggregate_bwd(indptr_t, indices_t, X.float().numpy(), op=op, wt=None if w is None else w[perm], din=din,
+                                       nthreads=8, want_scale=True)
+        for pad_in, pad_out, shift in ((0, 0, 0), (1, 3, 1), (0, 1, 3)):
+            # exactly the elements that belong to the matrix, `shift` elements behind an aligned address
+            flat = torch.full((el.n * (f + pad_in) + shift,), float("nan"), dtype=dtype, device=DEV)
+            Xd = flat[shift:].view(el.n, f + pad_in)[:, :f]
+            Xd.copy_(X)
+            out = torch.full((2, el.n * (f + pad_out) + shift), 7.0, dtype=dtype, device=DEV)
+            Y, dX = (o[shift:].view(el.n, f + pad_out) for o in out)
+            gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, dg.edge_w, Xd, Y[:, :f], el.n, f, op, plan=dg.plan_fwd)
+            gnn.gnn_aggregate_bwd(dg.indptr_t, dg.indices_t, dg.edge_w_t, Xd, dX[:, :f], el.n, f, op, plan=dg.plan_bwd)
+            torch.cuda.synchronize()
+            assert_close(Y[:, :f], Yo, S, bf16, f"fwd F={f} pads {pad_in} {pad_out} shift {shift}")
+            assert_close(dX[:, :f], dXo, St, bf16, f"bwd F={f} pads {pad_in} {pad_out} shift {shift}")
+            assert bool((Y[:, f:] == 7.0).all()) and bool((dX[:, f:] == 7.0).all()) and bool((out[:, :shift] == 7.0).all()), "written outside the rows"

@@ -8,7 +8,9 @@
 // into pieces that a second kernel combines in order -- with the message and the reduction as
 // template parameters.  max / min carry the winning edge position beside the value and combine
 // (value, position) pairs lexicographically, so the winner is the lowest position among equals
-// whatever the slot layout.  fp32 only; 16-byte or 4-byte accesses.
+// whatever the slot layout.  fp32 only; 16-byte accesses at the alignment of a float (the last strip of a row
+// begins early enough to end with it: its first columns are computed twice, with equal results), 4-byte ones
+// for fewer than four columns.
 #include "common.h"
 
 #include <math.h>
@@ -30,7 +32,7 @@ struct ApArgs {
     const float *dO;   // edge gradient only: gradient of the output rows
     float *out;        // forward: f_O; edge gradient: dfE
     int32_t *arg_out;  // forward, max / min: winning positions (or nullptr)
-    int64_t ld_arg;    // row stride of arg_out (d, or the padded width of a staged call)
+    int64_t ld_arg;    // row stride of arg_out
     const int32_t *arg_in;  // edge gradient, max / min
     int64_t ldv, lde, ldo;
     int32_t d;
@@ -41,7 +43,7 @@ struct ApArgs {
     int32_t *parg;     // hub pieces: partial winners  [n_chunks, ldp]
     int64_t ldp;
     int32_t n_bins;
-    int32_t slab_cols;    // columns one workgroup covers
+    int32_t slab_cols;    // columns one workgroup covers (a multiple of four, or all of them)
     int32_t col0;         // first column of this launch
     int32_t col_end;      // one past its last column
     int32_t log2_slices;  // > 0: workgroup b serves column slab (b % n_slices) of the launch, so that an
@@ -55,39 +57,56 @@ __device__ __forceinline__ int64_t load_ip(const void *indptr, int ip64, int64_t
                 : static_cast<int64_t>(static_cast<const int32_t *>(indptr)[i]);
 }
 
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 template <int VEC> __device__ __forceinline__ void load_f(const float *p, float (&v)[VEC]) {
     if constexpr (VEC == 4) {
-        const float4 t = *reinterpret_cast<const float4 *>(p);
+        const f32x4_any t = *reinterpret_cast<const f32x4_any *>(p);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     } else {
         v[0] = *p;
     }
 }
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 // non-temporal variant for rows of rarely gathered ("cold") sources
 template <int VEC> __device__ __forceinline__ void load_f_nt(const float *p, float (&v)[VEC]) {
     if constexpr (VEC == 4) {
-        const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
+        const f32x4_any t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(p));
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     } else {
         v[0] = __builtin_nontemporal_load(p);
     }
 }
 template <int VEC> __device__ __forceinline__ void store_f(float *p, const float (&v)[VEC]) {
-    if constexpr (VEC == 4) *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+    if constexpr (VEC == 4) *reinterpret_cast<f32x4_any *>(p) = f32x4_any{v[0], v[1], v[2], v[3]};
     else *p = v[0];
 }
 template <int VEC> __device__ __forceinline__ void load_i(const int32_t *p, int32_t (&v)[VEC]) {
     if constexpr (VEC == 4) {
-        const int4 t = *reinterpret_cast<const int4 *>(p);
+        const i32x4_any t = *reinterpret_cast<const i32x4_any *>(p);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     } else {
         v[0] = *p;
     }
 }
 template <int VEC> __device__ __forceinline__ void store_i(int32_t *p, const int32_t (&v)[VEC]) {
-    if constexpr (VEC == 4) *reinterpret_cast<int4 *>(p) = make_int4(v[0], v[1], v[2], v[3]);
+    if constexpr (VEC == 4) *reinterpret_cast<i32x4_any *>(p) = i32x4_any{v[0], v[1], v[2], v[3]};
     else *p = v[0];
+}
+
+// Sum of v over groups of 2^log2_c adjacent lanes, in all of their lanes.  Within 16 lanes the partner's value comes
+// through the operand path of the addition (quad swaps, then mirrored halves); a shuffle through the LDS unit costs a
+// memory instruction each.
+template <int CTRL> __device__ __forceinline__ float add_partner(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float group_sum(float v, int log2_c) {
+    if (log2_c > 0) v = add_partner<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    if (log2_c > 1) v = add_partner<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    if (log2_c > 2) v = add_partner<0x141>(v);  // row_half_mirror: lane i of 8 and lane 7 - i
+    if (log2_c > 3) v = add_partner<0x140>(v);  // row_mirror: lane i of 16 and lane 15 - i
+    if (log2_c > 4) v += __shfl_xor(v, 16);
+    if (log2_c > 5) v += __shfl_xor(v, 32);
+    return v;
 }
 
 __device__ __forceinline__ int64_t shfl_i64(int64_t v, int src_lane) {
@@ -116,6 +135,7 @@ struct Group {
     int G, SR, C, log2_c, lane_in_g, gbase, s, c;
     int64_t row, e0, e1, piece;
     bool is_piece;
+    bool coop;  // shared by the wavefronts of the workgroup: e0 .. e1 is this wavefront's quarter
 };
 
 __device__ __forceinline__ Group locate_group(const ApArgs &a, int64_t vblock) {
@@ -126,7 +146,8 @@ __device__ __forceinline__ Group locate_group(const ApArgs &a, int64_t vblock) {
     for (int i = 1; i < a.n_bins; ++i)
         if (vblock >= a.bins[i].first_block) b = i;
     const ApBin bin = a.bins[b];
-    const int64_t wave_in_bin = (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;
+    g.coop = (bin.kind & GNN_BIN_COOP) != 0;
+    const int64_t wave_in_bin = g.coop ? vblock - bin.first_block : (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;
     g.G = 1 << bin.log2_g;
     g.SR = 1 << bin.log2_sr;
     g.log2_c = bin.log2_g - bin.log2_sr;
@@ -138,7 +159,7 @@ __device__ __forceinline__ Group locate_group(const ApArgs &a, int64_t vblock) {
     g.row = -1;
     g.e0 = g.e1 = 0;
     g.piece = -1;
-    g.is_piece = bin.kind == kKindHubPieces;
+    g.is_piece = (bin.kind & kKindHubPieces) != 0;
     if (g.is_piece) {
         if (wave_in_bin < bin.n_items) {
             const int64_t *p = a.chunks + 3 * (bin.item_begin + wave_in_bin);
@@ -152,6 +173,11 @@ __device__ __forceinline__ Group locate_group(const ApArgs &a, int64_t vblock) {
             g.e0 = load_ip(a.indptr, a.ip64, g.row);
             g.e1 = load_ip(a.indptr, a.ip64, g.row + 1);
         }
+    }
+    if (g.coop) {
+        const int64_t quarter = (g.e1 - g.e0 + kWavesPerBlock - 1) / kWavesPerBlock;
+        g.e0 += wave_in_block * quarter;
+        if (g.e0 + quarter < g.e1) g.e1 = g.e0 + quarter;
     }
     return g;
 }
@@ -167,8 +193,11 @@ __global__ void __launch_bounds__(kBlockThreads) ap_fwd_kernel(const ApArgs a) {
     const int slab = a.log2_slices > 0 ? int(blockIdx.x) & ((1 << a.log2_slices) - 1) : int(blockIdx.y);
     const Group g = locate_group(a, int64_t(blockIdx.x) >> a.log2_slices);
     const int G = g.G, SR = g.SR;
-    const int col = a.col0 + slab * a.slab_cols + g.c * VEC;
+    int col = a.col0 + slab * a.slab_cols + g.c * VEC;
     const bool col_ok = col < a.col_end && g.c * VEC < a.slab_cols;
+    if (VEC > 1 && col > a.col_end - VEC) col = a.col_end - VEC;
+    __shared__ float coop_val[kWavesPerBlock - 1][VEC][64];
+    __shared__ int32_t coop_win[RED == GNN_RED_SUM ? 1 : kWavesPerBlock - 1][VEC][64];
     const int64_t e0 = g.e0, e1 = g.e1;
 
     float acc[VEC];
@@ -266,6 +295,30 @@ __global__ void __launch_bounds__(kBlockThreads) ap_fwd_kernel(const ApArgs a) {
         }
     }
 
+    if (g.coop) {  // the wavefronts' quarters in order
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        if (wave > 0) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                coop_val[wave - 1][i][lane] = acc[i];
+                if constexpr (RED != GNN_RED_SUM) coop_win[wave - 1][i][lane] = win[i];
+            }
+        }
+        __syncthreads();
+        if (wave > 0) return;
+        for (int w = 0; w < kWavesPerBlock - 1; ++w) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                const float om = coop_val[w][i][lane];
+                if constexpr (RED == GNN_RED_SUM) {
+                    acc[i] += om;
+                } else {  // later quarters hold later positions: they win only when better
+                    const int32_t ow = coop_win[w][i][lane];
+                    if (ow >= 0 && (win[i] < 0 || better<RED>(om, acc[i]))) { acc[i] = om; win[i] = ow; }
+                }
+            }
+        }
+    }
     if (g.row < 0 || g.s != 0 || !col_ok) return;
     if (g.is_piece) {
         store_f<VEC>(a.pval + g.piece * a.ldp + col, acc);
@@ -355,7 +408,8 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
                 ok[k] = j < n_tile;
                 part[k] = 0.0f;
             }
-            for (int col = g.c * VEC; col < a.d; col += C * VEC) {
+            for (int col0 = g.c * VEC; col0 < a.d; col0 += C * VEC) {
+                const int col = VEC > 1 && col0 > a.d - VEC ? a.d - VEC : col0;  // columns before col0 belong to the strip before
                 float go[VEC];
                 int32_t aw[VEC];
                 load_f<VEC>(a.dO + row * a.ldo + col, go);
@@ -383,15 +437,14 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
                         store_f<VEC>(a.out + r[k] * a.lde + col, gy);
                     } else {
 #pragma unroll
-                        for (int i = 0; i < VEC; ++i) part[k] += gy[i];
+                        for (int i = 0; i < VEC; ++i) part[k] += VEC > 1 && col + i < col0 ? 0.0f : gy[i];
                     }
                 }
             }
             if (!EWIDE) {
 #pragma unroll
                 for (int k = 0; k < U; ++k) {
-                    float t = part[k];
-                    for (int off = 1; off < C; off <<= 1) t += __shfl_xor(t, off);
+                    const float t = group_sum(part[k], g.log2_c);
                     if (ok[k] && g.c == 0) a.out[r[k] * a.lde] = t;
                 }
             }
@@ -432,7 +485,6 @@ __global__ void __launch_bounds__(256) fill_rows_kernel(float *__restrict__ p, i
 }
 
 // ---------------------------------------------------------------- host side
-bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 bool aligned4(const void *p) { return reinterpret_cast<uintptr_t>(p) % 4 == 0; }
 
 unsigned grid_1d(int64_t work, int64_t cap = int64_t(1) << 17) {
@@ -443,12 +495,12 @@ unsigned grid_1d(int64_t work, int64_t cap = int64_t(1) << 17) {
 }
 
 // Fills the bin table (heaviest work first) and returns the number of workgroups along x.
-int64_t make_bins(ApArgs &a, const gnn_plan *plan, int64_t N, int log2_c) {
+int64_t make_bins(ApArgs &a, const gnn_plan *plan, int64_t N, int log2_c, int slices = 1) {
     if (plan) {
         a.row_perm = plan->row_perm;
         a.chunks = plan->chunks;
     }
-    return gnn_fill_bins(a.bins, &a.n_bins, plan, N, log2_c);
+    return gnn_fill_bins(a.bins, &a.n_bins, plan, N, log2_c, INT32_MAX, slices, /*coop_ok=*/true);
 }
 
 struct Common {
@@ -502,9 +554,6 @@ void launch_fwd(int bin, int red, int vec, bool ewide, dim3 grid, hipStream_t st
     }
 }
 
-__global__ void unpad_rows_kernel(const float *__restrict__ val, const int32_t *__restrict__ arg, int64_t ld_src,
-                                  float *__restrict__ out, int64_t ldo, int32_t *__restrict__ arg_out, int64_t N, int d);
-
 int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, const float *fE, float *fO, int32_t *arg_e,
                int64_t N, int64_t d, int binop, int reduce, const gnn_ap_opts *opts_in) {
     Common c;
@@ -554,23 +603,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         if (rc != GNN_ERR_UNSUPPORTED) return rc;  // shapes that path does not take go through the kernel below
     }
 
-    int vec = 4;
-    if (d % 4 || c.ldo % 4 || !aligned16(fO)) vec = 1;
-    if (use_v && (c.ldv % 4 || !aligned16(fV))) vec = 1;
-    if (wide && (c.lde % 4 || !aligned16(fE))) vec = 1;
-    if (arg_e && !aligned16(arg_e)) vec = 1;
-    // Staged call: a width or strides that forbid 16-byte accesses on a gather-bound call of a large
-    // graph.  f_V is copied into padded rows anyway (below); the results are computed in plan-owned
-    // rows of roundup(d, 4) columns as well and copied to the caller's arrays at the end, so the
-    // kernel runs its 16-byte instantiation (copylhs / max d = 33: 4.3 -> 3.7 ms, d = 101: 10.1 -> 7.9).
-    const int64_t d4 = (d + 3) / 4 * 4;
-    bool staged = false;
-    if (vec == 1 && use_v && !wide && plan && plan->n_edges >= 16 * N && N * d * 4 >= (int64_t(1) << 20) && d * 4 > 128) {
-        const gnn_layout Ls = gnn_choose_layout(plan, N, d, 4, c.ldv, reinterpret_cast<uintptr_t>(fV) % 128 == 0, c.o.flags,
-                                                c.o.max_slices);
-        staged = Ls.padded_copy;
-    }
-    if (staged) vec = 4;
+    const int vec = d >= 4 ? 4 : 1;
 
     ApArgs a{};
     a.indptr = indptr;
@@ -603,28 +636,16 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
     // repeated weight stream and winner bookkeeping cost more than the hits bring: 8.4 -> 9.0 ms).
     bool sliced = false;
     const bool slice_ok = !use_e || (!wide && !c.o.edge_ids && reduce == GNN_RED_SUM) || c.o.max_slices > 1;
-    if (use_v && !wide && vec == 4 && plan && plan->n_edges > 0 && (slice_ok || staged)) {
-        gnn_layout L = gnn_choose_layout(plan, N, d, 4, c.ldv, reinterpret_cast<uintptr_t>(fV) % 128 == 0, c.o.flags,
+    if (use_v && !wide && vec == 4 && plan && plan->n_edges > 0 && slice_ok) {
+        const gnn_layout L = gnn_choose_layout(plan, N, d, 4, c.ldv, reinterpret_cast<uintptr_t>(fV) % 128 == 0, c.o.flags,
                                          c.o.max_slices);
-        if (!slice_ok) L.slices_wanted = false;  // staged only: the copy, not the slices
         if (L.padded_copy && d * 4 > 128) {  // rows of one line gain nothing from a copy in their own order
-            const int64_t copy_bytes = (N * L.ld_pad * 4 + 255) / 256 * 256;
-            const int64_t tmp_bytes = (N * d4 * 4 + 255) / 256 * 256;
-            rc = gnn_plan_padded(plan, copy_bytes + (staged ? tmp_bytes * (arg_e ? 2 : 1) : 0));
+            rc = gnn_plan_padded(plan, N * L.ld_pad * 4);
             if (rc != GNN_OK) return rc;
             rc = gnn_pad_rows_f32(fV, c.ldv, static_cast<float *>(plan->padded), L.ld_pad, N, d, c.stream);
             if (rc != GNN_OK) return rc;
             a.fV = static_cast<const float *>(plan->padded);
             a.ldv = L.ld_pad;
-            if (staged) {
-                char *base = static_cast<char *>(plan->padded) + copy_bytes;
-                a.out = reinterpret_cast<float *>(base);
-                a.ldo = d4;
-                if (arg_e) {
-                    a.arg_out = reinterpret_cast<int32_t *>(base + tmp_bytes);
-                    a.ld_arg = d4;
-                }
-            }
         }
         const int64_t line = 32;  // floats per 128-byte line
         const bool lines_ok = a.ldv % line == 0 && reinterpret_cast<uintptr_t>(a.fV) % 128 == 0;
@@ -652,7 +673,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
                 const int64_t end = int64_t(a.col0) + (int64_t(a.slab_cols) << ls);
                 a.col_end = int32_t(end < d ? end : d);
                 a.log2_slices = ls;
-                const int64_t blocks = make_bins(a, plan, N, log2_c) << ls;
+                const int64_t blocks = make_bins(a, plan, N, log2_c, 1 << ls) << ls;
                 if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
                 if (blocks > 0) {
                     launch_fwd(binop, reduce, vec, c.ewide, dim3(static_cast<unsigned>(blocks)), c.stream, a);
@@ -672,7 +693,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         a.col0 = 0;
         a.col_end = int32_t(d);
         a.log2_slices = 0;
-        const int64_t blocks = make_bins(a, plan, N, log2_c);
+        const int64_t blocks = make_bins(a, plan, N, log2_c, int(n_slabs < 64 ? n_slabs : 64));
         if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
         if (blocks > 0) {
             dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(n_slabs));
@@ -692,12 +713,6 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
             ap_hub_finalize_kernel<GNN_RED_MIN><<<grid, 256, 0, c.stream>>>(hub_rows, plan->n_hub_rows, plan->hub_chunk_offsets, a.pval, a.parg, a.ldp, a.out, a.ldo, a.arg_out, a.ld_arg, int(d));
         if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     }
-    if (a.out != fO) {  // staged call: hand the results over
-        int64_t blocks = (N * d + 255) / 256;
-        if (blocks > (int64_t(1) << 17)) blocks = int64_t(1) << 17;
-        unpad_rows_kernel<<<static_cast<unsigned>(blocks), 256, 0, c.stream>>>(a.out, a.arg_out, a.ldo, fO, c.ldo, arg_e, N, int(d));
-        if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
-    }
     return GNN_OK;
 }
 
@@ -714,40 +729,6 @@ void launch_edge_bin(int vec, bool ewide, bool masked, dim3 grid, hipStream_t st
     } else {
         if (ewide) launch_edge_masked<BIN, 1, true>(masked, grid, stream, a);
         else launch_edge_masked<BIN, 1, false>(masked, grid, stream, a);
-    }
-}
-
-// Results of a staged call go from the padded rows they were computed in to the caller's arrays.
-__global__ void __launch_bounds__(256) unpad_rows_kernel(const float *__restrict__ val, const int32_t *__restrict__ arg,
-                                                         int64_t ld_src, float *__restrict__ out, int64_t ldo,
-                                                         int32_t *__restrict__ arg_out, int64_t N, int d) {
-    const int64_t total = N * d;
-    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-    for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < total; t += stride) {
-        const int64_t r = t / d;
-        const int c = int(t - r * d);
-        out[r * ldo + c] = val[r * ld_src + c];
-        if (arg_out) arg_out[r * int64_t(d) + c] = arg[r * ld_src + c];
-    }
-}
-
-// dst[r, 0..ld_dst) = src[r, 0..d) followed by zeros (ld_dst a multiple of 4 floats, dst 16-byte aligned).
-__global__ void __launch_bounds__(256) pad_zero_rows_kernel(const float *__restrict__ src, int64_t ld_src,
-                                                            float *__restrict__ dst, int64_t ld_dst, int64_t N, int d) {
-    const int quads = int(ld_dst / 4);
-    int log2_tpr = 0;
-    while ((1 << log2_tpr) < quads && log2_tpr < 8) ++log2_tpr;
-    const int tpr = 1 << log2_tpr;
-    const int64_t rows_per_block = blockDim.x >> log2_tpr;
-    for (int64_t row = int64_t(blockIdx.x) * rows_per_block + (threadIdx.x >> log2_tpr); row < N;
-         row += int64_t(gridDim.x) * rows_per_block) {
-        const float *in = src + row * ld_src;
-        for (int q = threadIdx.x & (tpr - 1); q < quads; q += tpr) {
-            float v[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = 4 * q + i < d ? in[4 * q + i] : 0.0f;
-            *reinterpret_cast<float4 *>(dst + row * ld_dst + 4 * q) = make_float4(v[0], v[1], v[2], v[3]);
-        }
     }
 }
 
@@ -828,37 +809,8 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     if (arg_e && plan && plan->n_edges > INT32_MAX) return GNN_ERR_UNSUPPORTED;
     (void)hipGetLastError();
 
-    int vec = 4;
-    if (d % 4 || c.ldo % 4 || !aligned16(dO)) vec = 1;
-    if (need_x && (c.ldv % 4 || !aligned16(fV))) vec = 1;
-    if (c.ewide && (c.lde % 4 || !aligned16(dfE) || (need_y && !aligned16(fE)))) vec = 1;
-    if (arg_e && !aligned16(arg_e)) vec = 1;
-
-    // A scalar edge gradient is a dot product over the columns, so rows whose width or stride
-    // forbids 16-byte loads are first copied into plan-owned rows of a multiple of four floats, padded
-    // with zeros (they add +0 to every sum): d = 33 on 2.45 M vertices 14.2 -> 4.3 ms.
-    int64_t d_run = d, ldv_run = c.ldv, ldo_run = c.ldo;
-    if (vec == 1 && !c.ewide && !arg_e && plan && plan->n_edges >= 16 * N && N * d * 4 >= (int64_t(1) << 20)) {
-        const int64_t d4 = (d + 3) / 4 * 4;
-        rc = gnn_plan_padded(plan, (need_x ? 2 : 1) * N * d4 * 4);
-        if (rc != GNN_OK) return rc;
-        float *dO_pad = static_cast<float *>(plan->padded);
-        float *fV_pad = dO_pad + N * d4;
-        const int quads = int(d4 / 4);
-        int log2_tpr = 0;
-        while ((1 << log2_tpr) < quads && log2_tpr < 8) ++log2_tpr;
-        int64_t blocks = (N + (256 >> log2_tpr) - 1) / (256 >> log2_tpr);
-        if (blocks > (int64_t(1) << 17)) blocks = int64_t(1) << 17;
-        pad_zero_rows_kernel<<<static_cast<unsigned>(blocks), 256, 0, c.stream>>>(dO, c.ldo, dO_pad, d4, N, int(d));
-        if (need_x) pad_zero_rows_kernel<<<static_cast<unsigned>(blocks), 256, 0, c.stream>>>(fV, c.ldv, fV_pad, d4, N, int(d));
-        if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
-        dO = dO_pad;
-        if (need_x) fV = fV_pad;
-        d_run = d4; ldo_run = d4; if (need_x) ldv_run = d4;
-        vec = 4;
-    }
-
-    const int64_t strips = (d_run + vec - 1) / vec;
+    const int vec = d >= 4 ? 4 : 1;
+    const int64_t strips = (d + vec - 1) / vec;
     const int log2_c = strips >= 64 ? 6 : gnn_ilog2_ceil(strips);
 
     ApArgs a{};
@@ -870,10 +822,10 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     a.dO = dO;
     a.out = dfE;
     a.arg_in = arg_e;
-    a.ldv = ldv_run;
+    a.ldv = c.ldv;
     a.lde = c.lde;
-    a.ldo = ldo_run;
-    a.d = int32_t(d_run);
+    a.ldo = c.ldo;
+    a.d = int32_t(d);
     a.ip64 = c.o.indptr_is_64 ? 1 : 0;
     const int64_t blocks = make_bins(a, plan, N, log2_c);
     if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;

@@ -55,3 +55,36 @@ def test_rows_of_every_length_width_and_alignment(dtype, widths, op_name, weight
             assert_close(Y[:, :f], Yo, S, bf16, f"fwd F={f} pads {pad_in} {pad_out} shift {shift}")
             assert_close(dX[:, :f], dXo, St, bf16, f"bwd F={f} pads {pad_in} {pad_out} shift {shift}")
             assert bool((Y[:, f:] == 7.0).all()) and bool((dX[:, f:] == 7.0).all()) and bool((out[:, :shift] == 7.0).all()), "written outside the rows"
+
+
+@pytest.mark.parametrize("d", [1, 3, 4, 5, 33, 66, 101])
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_operator_table_on_rows_of_every_length_and_alignment(d, shift):
+    """max with winners and the edge gradients (full width, and the dot products of a scalar operand), on operands that lie
+    `shift` floats behind an aligned address with one column of padding."""
+    el = _graph()
+    indptr, indices, *_ = host_csr(el)
+    dg = device_graph(el)
+    fV, dO = synth.normal_features(el.n, d, 3), synth.normal_features(el.n, d, 4)
+
+    def place(t):
+        flat = torch.full((t.shape[0] * (t.shape[1] + 1) + shift,), float("nan"), device=DEV)
+        out = flat[shift:].view(t.shape[0], t.shape[1] + 1)[:, :t.shape[1]]
+        out.copy_(t)
+        return out
+
+    out = torch.full((el.n * d + shift,), float("nan"), device=DEV)
+    fO = out[shift:].view(el.n, d)
+    arg = torch.empty((el.n, d), dtype=torch.int32, device=DEV)
+    gnn.gnn_ap_fwd(dg.indptr, dg.indices, place(fV), None, fO, arg, el.n, d, gnn.GNN_BIN_COPY_LHS, gnn.GNN_RED_MAX, plan=dg.plan_fwd)
+    dfE = torch.full((el.e, d), float("nan"), device=DEV)
+    dw = torch.full((el.e,), float("nan"), device=DEV)
+    gnn.gnn_ap_bwd_edge(dg.indptr, dg.indices, None, place(fV), dfE, place(dO), dfE, el.n, d, gnn.GNN_BIN_MUL, plan=dg.plan_fwd)
+    gnn.gnn_ap_bwd_edge(dg.indptr, dg.indices, None, place(fV), dw, place(dO), dw, el.n, d, gnn.GNN_BIN_MUL, plan=dg.plan_fwd)
+    torch.cuda.synchronize()
+    O, won = oracle.ap_fwd(indptr, indices, fV.numpy(), None, d, oracle.BIN_COPY_LHS, oracle.RED_MAX)
+    assert np.array_equal(fO.cpu().numpy().astype(np.float64), O) and np.array_equal(arg.cpu().numpy().astype(np.int64), won)
+    prod = dO.double()[el.dst.long()] * fV.double()[el.src.long()]
+    assert torch.equal(dfE.cpu(), (dO[el.dst.long()] * fV[el.src.long()]))
+    err = (dw.cpu().double() - prod.sum(1)).abs()
+    assert bool((err <= 1e-5 * prod.abs().sum(1)).all())

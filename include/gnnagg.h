@@ -393,9 +393,9 @@ GNN_API int gnn_csr_from_sorted_coo(const int32_t *dst_sorted, int64_t E, int64_
  * Outputs (caller-allocated): indptr_t [N+1] (same width as indptr),
  * indices_t [E] int32, and optionally perm [E] int64 (perm[e'] = CSR position
  * of transposed edge e'; may be NULL) and edge_w_t [E] = edge_w[perm] (only if
- * edge_w != NULL).  E is read from the device (indptr[N]); the call allocates
- * temporary device memory (about 24 bytes per edge), frees it and is
- * SYNCHRONOUS with respect to `stream`. */
+ * edge_w != NULL).  E is read from the device (indptr[N]); the call takes
+ * temporary device memory (up to 22 bytes per edge) and is SYNCHRONOUS with
+ * respect to `stream`. */
 GNN_API int gnn_transpose_csr(const void *indptr, const int32_t *indices, const float *edge_w,
                       int64_t N, int indptr_is_64, void *indptr_t, int32_t *indices_t,
                       int64_t *perm, float *edge_w_t, void *stream);
@@ -416,6 +416,22 @@ GNN_API void gnn_plan_default_params(gnn_plan_params *params /* host, out */);
 GNN_API int gnn_plan_create(const void *indptr, const int32_t *indices, int64_t N, int indptr_is_64,
                     const gnn_plan_params *params /* host */, void *stream, gnn_plan **out);
 GNN_API void gnn_plan_destroy(gnn_plan *plan);
+
+/* Everything a new graph needs in one call: the row pointers of gnn_csr_from_sorted_coo, the transposed
+ * graph of gnn_transpose_csr and, unless plan_fwd and plan_bwd are both NULL, the plans of
+ * gnn_plan_create for (indptr, src) and (indptr_t, indices_t), equal to what those calls build one after
+ * the other.  dst_sorted / src [E]: the edges u->v sorted by (v, u).  The number of edges is known to
+ * the host here and the column counts of either graph are the row lengths of the other, so that the host
+ * waits for the device once.  Synchronous. */
+GNN_API int gnn_graph_build(const int32_t *dst_sorted, const int32_t *src, const float *edge_w, int64_t E,
+                    int64_t N, int indptr_is_64, void *indptr, void *indptr_t, int32_t *indices_t,
+                    int64_t *perm, float *edge_w_t, const gnn_plan_params *params /* host */, void *stream,
+                    gnn_plan **plan_fwd, gnn_plan **plan_bwd);
+
+/* Device memory of destroyed plans and of the setup calls is kept for the next ones, up to 1 GiB per
+ * device (it is given back by itself when an allocation of the library fails).  Gives back what the
+ * current device holds; waits for the device. */
+GNN_API void gnn_release_cached_memory(void);
 
 /* Sizes of what gnn_plan_export would write (host outputs). */
 GNN_API int gnn_plan_sizes(const gnn_plan *plan, int64_t *n_rows, int32_t *n_bins, int64_t *n_chunks);

@@ -39,6 +39,7 @@ EXPORTED_SYMBOLS = (
     "gnn_aggregate_fwd", "gnn_aggregate_bwd", "gnn_aggregate_fwd_noalloc", "gnn_packed_bytes", "gnn_pack_rows",
     "gnn_aggregate_packed", "gnn_csr_from_sorted_coo", "gnn_transpose_csr",
     "gnn_validate_csr", "gnn_plan_default_params", "gnn_plan_create", "gnn_plan_destroy",
+    "gnn_graph_build", "gnn_release_cached_memory",
     "gnn_plan_sizes", "gnn_plan_export", "gnn_plan_gather_share", "gnn_plan_workspace_bytes", "gnn_plan_reserve",
     "gnn_plan_prepare", "gnn_plan_set_blocking", "gnn_plan_bind_edge_weights", "gnn_plan_blocked_sizes", "gnn_plan_export_blocked",
     "gnn_ap_fwd", "gnn_ap_bwd_vertex", "gnn_ap_bwd_vertex_arg", "gnn_ap_bwd_edge",
@@ -121,6 +122,10 @@ def load_library() -> ctypes.CDLL:
         lib.gnn_plan_create.argtypes = [vp, vp, i64, i32, ctypes.POINTER(GnnPlanParams), vp, ctypes.POINTER(vp)]
         lib.gnn_plan_destroy.argtypes = [vp]
         lib.gnn_plan_destroy.restype = None
+        lib.gnn_graph_build.argtypes = [vp, vp, vp, i64, i64, i32, vp, vp, vp, vp, vp, ctypes.POINTER(GnnPlanParams), vp,
+                                        ctypes.POINTER(vp), ctypes.POINTER(vp)]
+        lib.gnn_release_cached_memory.argtypes = []
+        lib.gnn_release_cached_memory.restype = None
         lib.gnn_plan_sizes.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(i64)]
         lib.gnn_plan_export.argtypes = [vp, vp, vp, vp, vp]
         lib.gnn_plan_gather_share.argtypes = [vp, i64]
@@ -183,7 +188,7 @@ def _check(fn: str, status: int) -> None:
 
 
 def _call_allocating(fn: str, call) -> None:
-    """Library calls that hipMalloc can fail only because torch's caching allocator is
+    """Library calls that allocate device memory can fail only because torch's caching allocator is
     sitting on freed blocks: hand those back to the driver and try once more."""
     status = call()
     if status == GNN_ERR_ALLOC:
@@ -579,6 +584,31 @@ def gnn_transpose_csr(indptr, indices, edge_w, N, indptr_t, indices_t, perm=None
     _call_allocating("gnn_transpose_csr", lambda: load_library().gnn_transpose_csr(
         _ptr(indptr), _ptr(indices), _ptr(edge_w), int(N), _is64(indptr), _ptr(indptr_t), _ptr(indices_t), _ptr(perm),
         _ptr(edge_w_t), _stream(stream)))
+
+
+def gnn_graph_build(dst_sorted: torch.Tensor, src: torch.Tensor, edge_w: Optional[torch.Tensor], N: int, indptr: torch.Tensor,
+                    indptr_t: torch.Tensor, indices_t: torch.Tensor, perm: Optional[torch.Tensor] = None,
+                    edge_w_t: Optional[torch.Tensor] = None, params: Optional[GnnPlanParams] = None, with_plans: bool = True,
+                    stream=None):
+    """Row pointers, transposed graph and the two plans in one call; returns (plan_fwd, plan_bwd), None without plans."""
+    if indptr_t.dtype != indptr.dtype:
+        raise TypeError("indptr_t must have the dtype of indptr")
+    if perm is not None and perm.dtype != torch.int64:
+        raise TypeError("perm must be int64")
+    fwd, bwd = ctypes.c_void_p(), ctypes.c_void_p()
+    _call_allocating("gnn_graph_build", lambda: load_library().gnn_graph_build(
+        _ptr(dst_sorted), _ptr(src), _ptr(edge_w), int(dst_sorted.numel()), int(N), _is64(indptr), _ptr(indptr), _ptr(indptr_t),
+        _ptr(indices_t), _ptr(perm), _ptr(edge_w_t), ctypes.byref(params) if params is not None else None, _stream(stream),
+        ctypes.byref(fwd) if with_plans else None, ctypes.byref(bwd) if with_plans else None))
+    if not with_plans:
+        return None, None
+    k = params.n_thresholds if params is not None else gnn_plan_default_params().n_thresholds
+    return Plan(fwd.value, k), Plan(bwd.value, k)
+
+
+def gnn_release_cached_memory() -> None:
+    """Gives back the device memory the library keeps for the next plans (current device)."""
+    load_library().gnn_release_cached_memory()
 
 
 def gnn_validate_csr(indptr, indices, N, E, stream=None) -> int:

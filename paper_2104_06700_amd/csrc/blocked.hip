@@ -179,9 +179,6 @@ __global__ void __launch_bounds__(256) blk_scatter_edges_kernel(int64_t n, const
     }
 }
 
-template <typename T>
-bool dev_alloc(T **p, int64_t n) { return hipMalloc(p, sizeof(T) * size_t(n > 0 ? n : 1)) == hipSuccess; }
-
 }  // namespace
 
 // Piece descriptors from a table of edge counts and piece counts per (block, row): cell_pieces is overwritten with its prefix
@@ -194,10 +191,10 @@ int gnn_build_pieces(int64_t n_hot, int n_blocks, int64_t max_piece, const uint3
     uint32_t *row_prefix = nullptr;
     auto fail = [&](int s) {
         (void)hipStreamSynchronize(stream);
-        (void)hipFree(row_prefix); (void)hipFree(L.pieces); (void)hipFree(L.piece_block); (void)hipFree(L.rowbase);
+        gnn_dev_free_on(row_prefix, stream); gnn_dev_free_on(L.pieces, stream); gnn_dev_free_on(L.piece_block, stream); gnn_dev_free_on(L.rowbase, stream);
         return s;
     };
-    if (!dev_alloc(&row_prefix, n_cells) || !dev_alloc(&L.rowbase, n_hot + 1)) return fail(GNN_ERR_ALLOC);
+    if (!gnn_dev_alloc(&row_prefix, n_cells, stream) || !gnn_dev_alloc(&L.rowbase, n_hot + 1, stream)) return fail(GNN_ERR_ALLOC);
     (void)hipGetLastError();
     blk_row_prefix_kernel<<<grid_for(n_hot, 256, INT32_MAX), 256, 0, stream>>>(n_hot, n_blocks, cell_pieces, row_prefix, L.rowbase);
     if (hipGetLastError() != hipSuccess) return fail(GNN_ERR_LAUNCH);
@@ -215,11 +212,11 @@ int gnn_build_pieces(int64_t n_hot, int n_blocks, int64_t max_piece, const uint3
     const uint32_t total_slots = last_rowbase + last_row;
     if (int64_t(total_slots) != L.n_pieces || L.n_pieces >= int64_t(INT32_MAX)) return fail(GNN_ERR_LAUNCH);
     if (hipMemcpyAsync(L.rowbase + n_hot, &total_slots, 4, hipMemcpyHostToDevice, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-    if (!dev_alloc(&L.pieces, 4 * L.n_pieces) || (want_block && !dev_alloc(&L.piece_block, L.n_pieces))) return fail(GNN_ERR_ALLOC);
+    if (!gnn_dev_alloc(&L.pieces, 4 * L.n_pieces, stream) || (want_block && !gnn_dev_alloc(&L.piece_block, L.n_pieces, stream))) return fail(GNN_ERR_ALLOC);
     blk_fill_pieces_kernel<<<grid_for(n_cells, 256), 256, 0, stream>>>(n_hot, n_blocks, max_piece, cell_count, edge_off, cell_pieces,
                                                                       row_prefix, L.rowbase, L.pieces, L.piece_block);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-    (void)hipFree(row_prefix);
+    gnn_dev_free_on(row_prefix, stream);
     *out = L;
     return GNN_OK;
 }
@@ -273,10 +270,10 @@ int gnn_plan_blocked_partial(gnn_plan *plan, int slices, int line_floats) {
     const int64_t need = plan->blk_n_pieces * int64_t(slices) * line_floats * int64_t(sizeof(float));
     if (need <= plan->blk_partial_bytes) return GNN_OK;
     (void)hipGetLastError();
-    (void)hipFree(plan->blk_partial);
+    gnn_dev_free(plan->blk_partial);
     plan->blk_partial = nullptr;
     plan->blk_partial_bytes = 0;
-    if (hipMalloc(&plan->blk_partial, size_t(need)) != hipSuccess) return GNN_ERR_ALLOC;
+    if (gnn_dev_alloc_bytes(&plan->blk_partial, size_t(need)) != GNN_OK) return GNN_ERR_ALLOC;
     plan->blk_partial_bytes = need;
     return GNN_OK;
 }
@@ -286,12 +283,12 @@ int gnn_plan_blocked_edge_scale(gnn_plan *plan, int mode, hipStream_t stream, co
     float *&arr = plan->blk_edge_scale[mode - 1];
     if (!arr) {
         (void)hipGetLastError();
-        if (hipMalloc(&arr, sizeof(float) * size_t(plan->blk_n_edges + kStreamPad)) != hipSuccess) { arr = nullptr; return GNN_ERR_ALLOC; }
+        if (!gnn_dev_alloc(&arr, plan->blk_n_edges + kStreamPad, stream)) return GNN_ERR_ALLOC;
         blk_gather_u32_kernel<<<grid_for(plan->blk_n_edges, 256), 256, 0, stream>>>(
             reinterpret_cast<const uint32_t *>(plan->edge_scale[mode - 1]), plan->blk_epos, plan->blk_n_edges, 0xFFFFFFFFu,
             reinterpret_cast<uint32_t *>(arr));
         if (hipGetLastError() != hipSuccess) {
-            (void)hipFree(arr);
+            gnn_dev_free(arr);
             arr = nullptr;
             return GNN_ERR_LAUNCH;
         }
@@ -304,10 +301,7 @@ int gnn_plan_blocked_bound_weights(gnn_plan *plan, hipStream_t stream, const flo
     if (!plan || !out || plan->blk_n_edges <= 0 || !plan->bound_w) return GNN_ERR_INVALID_ARG;
     if (!plan->blk_bound_w) {
         (void)hipGetLastError();
-        if (hipMalloc(&plan->blk_bound_w, sizeof(float) * size_t(plan->blk_n_edges + kStreamPad)) != hipSuccess) {
-            plan->blk_bound_w = nullptr;
-            return GNN_ERR_ALLOC;
-        }
+        if (!gnn_dev_alloc(&plan->blk_bound_w, plan->blk_n_edges + kStreamPad, stream)) return GNN_ERR_ALLOC;
         plan->bound_w_stale = true;
     }
     if (plan->bound_w_stale) {
@@ -367,9 +361,8 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             enable = n_hot > 0;
         }
         if (enable) {
-            GNN_HIP_TRY(hipMemcpyAsync(&p0, plan->p_indptr + hot_begin, 8, hipMemcpyDeviceToHost, stream));
-            GNN_HIP_TRY(hipStreamSynchronize(stream));
-            n_edges = E - p0;
+            for (int b = first_bin; b < plan->n_bins; ++b) n_edges += plan->bin_edges[b];
+            p0 = E - n_edges;  // the plan order ends with them
             enable = n_edges > 0;
         }
         // Automatic gate: the gathered table must dwarf an L2 (else the plain path hits anyway), and the
@@ -399,26 +392,26 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             gnn_piece_list list{};
             const bool narrow = m.hot <= 65536 && m.block <= 65536;
             auto cleanup_tmp = [&]() {
-                (void)hipFree(h_of); (void)hipFree(buf_k[0]); (void)hipFree(buf_k[1]); (void)hipFree(buf_v[0]); (void)hipFree(buf_v[1]);
-                (void)hipFree(table); (void)hipFree(sums); (void)hipFree(cell_start); (void)hipFree(cell_count);
-                (void)hipFree(cell_pieces);
+                gnn_dev_free_on(h_of, stream); gnn_dev_free_on(buf_k[0], stream); gnn_dev_free_on(buf_k[1], stream); gnn_dev_free_on(buf_v[0], stream); gnn_dev_free_on(buf_v[1], stream);
+                gnn_dev_free_on(table, stream); gnn_dev_free_on(sums, stream); gnn_dev_free_on(cell_start, stream); gnn_dev_free_on(cell_count, stream);
+                gnn_dev_free_on(cell_pieces, stream);
             };
             auto fail = [&](int s) {
                 (void)hipStreamSynchronize(stream);
                 cleanup_tmp();
-                (void)hipFree(list.rowbase); (void)hipFree(blk_epos); (void)hipFree(blk_indices); (void)hipFree(list.pieces);
-                (void)hipFree(blk_idx16); (void)hipFree(list.piece_block); (void)hipFree(edge_off);
+                gnn_dev_free_on(list.rowbase, stream); gnn_dev_free_on(blk_epos, stream); gnn_dev_free_on(blk_indices, stream); gnn_dev_free_on(list.pieces, stream);
+                gnn_dev_free_on(blk_idx16, stream); gnn_dev_free_on(list.piece_block, stream); gnn_dev_free_on(edge_off, stream);
                 return s;
             };
             const int64_t scan_n = n_cells > n_hot + 1 ? n_cells : n_hot + 1;
             const int64_t sums_n = gnn_sort_sums_elems(n_edges) > gnn_scan_sums_elems(scan_n) ? gnn_sort_sums_elems(n_edges) : gnn_scan_sums_elems(scan_n);
-            bool ok = dev_alloc(&h_of, n_edges) && dev_alloc(&buf_k[0], n_edges) && dev_alloc(&buf_k[1], n_edges) &&
-                      dev_alloc(&buf_v[0], n_edges) && dev_alloc(&buf_v[1], n_edges) &&
-                      dev_alloc(&table, gnn_sort_table_elems(n_edges)) && dev_alloc(&sums, sums_n) &&
-                      dev_alloc(&cell_start, n_cells) && dev_alloc(&cell_count, n_cells) && dev_alloc(&cell_pieces, n_cells + 1) &&
-                      dev_alloc(&edge_off, n_cells + 1) &&
-                      dev_alloc(&blk_indices, n_edges + kStreamPad) && dev_alloc(&blk_epos, n_edges + kStreamPad);
-            if (ok && narrow) ok = dev_alloc(&blk_idx16, n_edges + kStreamPad);
+            bool ok = gnn_dev_alloc(&h_of, n_edges, stream) && gnn_dev_alloc(&buf_k[0], n_edges, stream) && gnn_dev_alloc(&buf_k[1], n_edges, stream) &&
+                      gnn_dev_alloc(&buf_v[0], n_edges, stream) && gnn_dev_alloc(&buf_v[1], n_edges, stream) &&
+                      gnn_dev_alloc(&table, gnn_sort_table_elems(n_edges), stream) && gnn_dev_alloc(&sums, sums_n, stream) &&
+                      gnn_dev_alloc(&cell_start, n_cells, stream) && gnn_dev_alloc(&cell_count, n_cells, stream) && gnn_dev_alloc(&cell_pieces, n_cells + 1, stream) &&
+                      gnn_dev_alloc(&edge_off, n_cells + 1, stream) &&
+                      gnn_dev_alloc(&blk_indices, n_edges + kStreamPad, stream) && gnn_dev_alloc(&blk_epos, n_edges + kStreamPad, stream);
+            if (ok && narrow) ok = gnn_dev_alloc(&blk_idx16, n_edges + kStreamPad, stream);
             if (!ok) return fail(GNN_ERR_ALLOC);
 
             blk_expand_rows_kernel<<<grid_for(n_hot * 64, 256), 256, 0, stream>>>(plan->p_indptr, hot_begin, n_hot, p0, h_of);
@@ -426,11 +419,11 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             blk_init_pairs_kernel<<<grid_for(n_edges, 256), 256, 0, stream>>>(plan->rank_indices, p0, n_edges, buf_k[0], buf_v[0]);
             if (hipGetLastError() != hipSuccess) return fail(GNN_ERR_LAUNCH);
             int where = 0;
-            int rc = gnn_radix_sort_pairs(nullptr, buf_k, buf_v, n_edges, gnn_ilog2_ceil(N > 1 ? N : 2), table, sums, stream, &where);
+            int rc = gnn_radix_sort_pairs(buf_k, buf_v, n_edges, gnn_ilog2_ceil(N > 1 ? N : 2), table, sums, stream, &where);
             if (rc != GNN_OK) return fail(rc);
             if (where != 0) { std::swap(buf_k[0], buf_k[1]); std::swap(buf_v[0], buf_v[1]); }
             blk_gather_u32_kernel<<<grid_for(n_edges, 256), 256, 0, stream>>>(h_of, buf_v[0], n_edges, 0xFFFFFFFFu, buf_k[0]);
-            rc = gnn_radix_sort_pairs(nullptr, buf_k, buf_v, n_edges, gnn_ilog2_ceil(n_hot > 1 ? n_hot : 2), table, sums, stream, &where);
+            rc = gnn_radix_sort_pairs(buf_k, buf_v, n_edges, gnn_ilog2_ceil(n_hot > 1 ? n_hot : 2), table, sums, stream, &where);
             if (rc != GNN_OK) return fail(rc);
             uint32_t *sorted_pos = buf_v[where];      // plan-order offset (from p0) of the edge at each sorted position
             uint32_t *sorted_r = buf_k[where ^ 1];    // its source rank

@@ -183,16 +183,55 @@ int gnn_build_pieces(int64_t n_hot, int n_blocks, int64_t max_piece, const uint3
 int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,
                      const float *coefs, float *partial, hipStream_t stream);
 
-// Stable LSD radix sort of 32-bit (key, value) pairs on the low `bits` bits (graph.hip).  buf_k[0] /
-// buf_v[0] hold the input (first_keys, if given, replaces buf_k[0] as read-only input of the first
-// pass); the result is in buf_k[*out] / buf_v[*out].  table / sums: scratch of gnn_sort_table_elems(n)
-// and gnn_sort_sums_elems(n) words.
-int gnn_radix_sort_pairs(const uint32_t *first_keys, uint32_t *buf_k[2], uint32_t *buf_v[2], int64_t n, int bits,
-                         uint32_t *table, uint32_t *sums, hipStream_t stream, int *out);
+// Device memory that is kept for the next plan (pool.hip).  With a stream: for memory that is first used there; fails on a
+// stream that is being captured.  gnn_dev_free: any stream may still use the block (as with hipFree, but without waiting);
+// gnn_dev_free_on: its last use is ordered on that stream.
+int gnn_dev_alloc_bytes(void **p, size_t bytes, hipStream_t stream);
+int gnn_dev_alloc_bytes(void **p, size_t bytes);
+void gnn_dev_free(void *p);
+void gnn_dev_free_on(void *p, hipStream_t stream);
+void gnn_pool_release();
+template <typename T>
+static inline bool gnn_dev_alloc(T **p, int64_t n, hipStream_t stream) {
+    void *q = nullptr;
+    const bool ok = gnn_dev_alloc_bytes(&q, sizeof(T) * size_t(n > 0 ? n : 1), stream) == GNN_OK;
+    *p = static_cast<T *>(q);
+    return ok;
+}
+template <typename T>
+static inline bool gnn_dev_alloc(T **p, int64_t n) {
+    void *q = nullptr;
+    const bool ok = gnn_dev_alloc_bytes(&q, sizeof(T) * size_t(n > 0 ? n : 1)) == GNN_OK;
+    *p = static_cast<T *>(q);
+    return ok;
+}
+// Scratch of one call: given back when it goes out of scope, for use after what the call launched on its stream.
+template <typename T>
+struct gnn_dev_ptr {
+    T *p = nullptr;
+    hipStream_t stream = nullptr;
+    bool alloc_on(int64_t n, hipStream_t s) { stream = s; return gnn_dev_alloc(&p, n, s); }
+    gnn_dev_ptr() = default;
+    gnn_dev_ptr(const gnn_dev_ptr &) = delete;
+    gnn_dev_ptr &operator=(const gnn_dev_ptr &) = delete;
+    ~gnn_dev_ptr() { if (p) gnn_dev_free_on(p, stream); }
+};
+// Pinned host memory that kernels write small results to.
+constexpr int GNN_HOST_BLOCK_BYTES = 8192;
+void *gnn_host_block();
+void gnn_host_block_free(void *p);
+
+// Stable LSD radix sort of 32-bit (key, value) pairs on the low `bits` bits (graph.hip).  buf_k[0] / buf_v[0] hold the
+// input; the result is in buf_k[*out] / buf_v[*out].  table / sums: scratch of gnn_sort_table_elems(n) and
+// gnn_sort_sums_elems(n) words.
+int gnn_radix_sort_pairs(uint32_t *buf_k[2], uint32_t *buf_v[2], int64_t n, int bits, uint32_t *table, uint32_t *sums,
+                         hipStream_t stream, int *out);
 int64_t gnn_sort_table_elems(int64_t n);
 int64_t gnn_sort_sums_elems(int64_t n);
-// In-place exclusive prefix sum of n 32-bit words; sums: scratch of gnn_scan_sums_elems(n) words.
+// In-place exclusive prefix sums; sums: scratch of gnn_scan_sums_elems(n) elements per array.  The 64-bit form scans n_arrays
+// arrays `stride` elements apart and writes each one's total behind it.
 int gnn_scan_exclusive_u32(uint32_t *data, int64_t n, uint32_t *sums, hipStream_t stream);
+int gnn_scan_exclusive_i64(int64_t *data, int64_t n, int n_arrays, int64_t stride, int64_t *sums, hipStream_t stream);
 int64_t gnn_scan_sums_elems(int64_t n);
 
 // The 256 buckets over the count axis that a plan's histogram uses (plan.hip: count_bucket): counts below 16 one
@@ -373,8 +412,13 @@ struct gnn_rank_layout {
 int gnn_plan_rank_indices(gnn_plan *plan, const void *indptr, const int32_t *indices, bool force_cold, hipStream_t stream,
                           gnn_rank_layout *out);
 
-// rank[v] = position of vertex v by descending count, ties by ascending id (graph.hip).
-int gnn_rank_by_count(const int32_t *counts, int64_t N, int32_t *rank, hipStream_t stream);
+// E = indptr[N]; synchronous.
+int gnn_read_edge_count(const void *indptr, int64_t N, int indptr_is_64, hipStream_t stream, int64_t *E);
+// rank[v] = position of vertex v by descending count, ties by ascending id; no count exceeds max_count (graph.hip).
+int gnn_rank_by_count(const int32_t *counts, int64_t N, int64_t max_count, int32_t *rank, hipStream_t stream);
+// The plans of a graph and of its transpose, E edges each; the host fields are valid on return.
+int gnn_plan_create_pair(const void *indptr, const void *indptr_t, int64_t E, int64_t N, int indptr_is_64,
+                         const gnn_plan_params *params, hipStream_t stream, gnn_plan **fwd, gnn_plan **bwd);
 
 // mode: 1 = reciprocal, 2 = reciprocal square root, 3 = reciprocal of (count + 1).
 // Builds the array on first use (allocation).

@@ -44,98 +44,105 @@ __device__ __forceinline__ int count_bucket(int c) {
     return 16 + (o - 4) * 8 + ((c >> (o - 3)) & 7);
 }
 
-__global__ void __launch_bounds__(256) count_buckets_kernel(const int32_t *__restrict__ col_counts, int64_t N,
-                                                            unsigned long long *__restrict__ vertices,
-                                                            unsigned long long *__restrict__ edges) {
-    __shared__ unsigned long long sv[256], se[256];
-    sv[threadIdx.x] = 0;
-    se[threadIdx.x] = 0;
-    __syncthreads();
-    int64_t stride = int64_t(gridDim.x) * blockDim.x;
-    for (int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v < N; v += stride) {
-        const int c = col_counts[v];
-        const int b = count_bucket(c);
-        atomicAdd(&sv[b], 1ull);  // integer sums: the order of the additions does not matter
-        atomicAdd(&se[b], static_cast<unsigned long long>(c));
-    }
-    __syncthreads();
-    if (sv[threadIdx.x]) atomicAdd(&vertices[threadIdx.x], sv[threadIdx.x]);
-    if (se[threadIdx.x]) atomicAdd(&edges[threadIdx.x], se[threadIdx.x]);
-}
+// What one pass over the rows of a graph produces, in device memory until plan_place_kernel hands it to the host.
+struct RowTotals {
+    unsigned long long bucket_vertices[256], bucket_edges[256];  // histogram of the column counts (gnn_plan_top_share)
+    unsigned long long bin_edges[GNN_MAX_BINS];                  // edges of the rows of each bin
+    unsigned long long n_chunks;                                 // pieces of the hub rows
+    long long bin_begin[GNN_MAX_BINS];                           // first row of each bin
+};
+static_assert(sizeof(RowTotals) <= size_t(GNN_HOST_BLOCK_BYTES), "fits a host block");
 
-// edges[b] += edges of the rows of bin b
-__global__ void __launch_bounds__(256) bin_edges_kernel(const void *__restrict__ indptr, int ip64, int64_t N, Thresholds thr,
-                                                        unsigned long long *__restrict__ edges) {
-    __shared__ unsigned long long se[GNN_MAX_BINS];
-    if (threadIdx.x < GNN_MAX_BINS) se[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-    for (int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v < N; v += stride) {
-        const int64_t deg = load_ip(indptr, ip64, v + 1) - load_ip(indptr, ip64, v);
-        if (deg > 0) atomicAdd(&se[bin_of(deg, thr)], static_cast<unsigned long long>(deg));  // integer sums: any order
-    }
-    __syncthreads();
-    if (threadIdx.x < GNN_MAX_BINS && se[threadIdx.x]) atomicAdd(&edges[threadIdx.x], se[threadIdx.x]);
-}
+// One graph orientation of a pair that is set up side by side (blockIdx.y).
+struct PlanJob {
+    const void *indptr;
+    const void *other_indptr;  // of the transposed graph, whose row lengths are the column counts; null: col_counts is filled
+    int32_t *col_counts;
+    int64_t *block_counts;
+    RowTotals *totals;         // zeroed
+    RowTotals *host;
+    int32_t *row_perm;
+    int64_t *hub_offsets;
+    int64_t *chunks;
+};
+struct PlanJobs {
+    PlanJob job[2];
+    int64_t N, n_blocks, hub_chunk;
+    int32_t ip64, nb;
+    Thresholds thr;
+};
 
-// block_counts[b * n_blocks + blk] = rows of bin b among rows [blk*1024, blk*1024+1024)
-__global__ void __launch_bounds__(kSplitThreads) bin_count_kernel(const void *__restrict__ indptr, int ip64,
-                                                                  int64_t N, Thresholds thr, int64_t n_blocks,
-                                                                  int64_t *__restrict__ block_counts) {
+// Per 1024 rows: block_counts[b * n_blocks + blk] = rows of bin b among them; and the totals over all rows, integer sums, so
+// that the order of the additions does not matter.
+__global__ void __launch_bounds__(kSplitThreads) plan_rows_kernel(PlanJobs jobs) {
+    __shared__ unsigned long long sv[256], se[256], bin_edges[GNN_MAX_BINS], pieces;
     __shared__ int counts[GNN_MAX_BINS];
-    if (threadIdx.x < GNN_MAX_BINS) counts[threadIdx.x] = 0;
-    __syncthreads();
-    int64_t v = int64_t(blockIdx.x) * kSplitThreads + threadIdx.x;
-    if (v < N) {
-        int64_t deg = load_ip(indptr, ip64, v + 1) - load_ip(indptr, ip64, v);
-        atomicAdd(&counts[bin_of(deg, thr)], 1);  // integer count: order does not matter
-    }
-    __syncthreads();
-    if (threadIdx.x <= thr.k) block_counts[int64_t(threadIdx.x) * n_blocks + blockIdx.x] = counts[threadIdx.x];
-}
-
-// In-place exclusive prefix sum of data[0..n) by ONE workgroup; data[n] receives the total.
-__global__ void __launch_bounds__(1024) scan_exclusive_kernel(int64_t *__restrict__ data, int64_t n) {
-    __shared__ int64_t part[1024];
+    const PlanJob &job = jobs.job[blockIdx.y];
     const int t = threadIdx.x;
-    const int64_t chunk = (n + 1023) / 1024;
-    const int64_t lo = chunk * t < n ? chunk * t : n;
-    const int64_t hi = lo + chunk < n ? lo + chunk : n;
-    int64_t s = 0;
-    for (int64_t i = lo; i < hi; ++i) s += data[i];
-    part[t] = s;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {  // Hillis-Steele inclusive scan of the partial sums
-        int64_t add = t >= off ? part[t - off] : 0;
+    if (t < 256) sv[t] = se[t] = 0;
+    if (t < GNN_MAX_BINS) bin_edges[t] = 0;
+    if (t == 0) pieces = 0;
+    for (int64_t blk = blockIdx.x; blk < jobs.n_blocks; blk += gridDim.x) {
+        if (t < GNN_MAX_BINS) counts[t] = 0;
         __syncthreads();
-        part[t] += add;
+        const int64_t v = blk * kSplitThreads + t;
+        if (v < jobs.N) {
+            const int64_t deg = load_ip(job.indptr, jobs.ip64, v + 1) - load_ip(job.indptr, jobs.ip64, v);
+            const int bin = bin_of(deg, jobs.thr);
+            atomicAdd(&counts[bin], 1);
+            if (deg > 0) atomicAdd(&bin_edges[bin], static_cast<unsigned long long>(deg));
+            if (jobs.hub_chunk > 0 && bin == jobs.nb - 1 && deg > 0)
+                atomicAdd(&pieces, static_cast<unsigned long long>((deg + jobs.hub_chunk - 1) / jobs.hub_chunk));
+            int c;
+            if (job.other_indptr) {
+                c = static_cast<int>(load_ip(job.other_indptr, jobs.ip64, v + 1) - load_ip(job.other_indptr, jobs.ip64, v));
+                job.col_counts[v] = c;
+            } else {
+                c = job.col_counts[v];
+            }
+            const int b = count_bucket(c);
+            atomicAdd(&sv[b], 1ull);
+            atomicAdd(&se[b], static_cast<unsigned long long>(c));
+        }
+        __syncthreads();
+        if (t < jobs.nb) job.block_counts[int64_t(t) * jobs.n_blocks + blk] = counts[t];
         __syncthreads();
     }
-    int64_t run = part[t] - s;  // exclusive prefix of this thread's chunk
-    for (int64_t i = lo; i < hi; ++i) {
-        int64_t x = data[i];
-        data[i] = run;
-        run += x;
+    if (t < 256) {
+        if (sv[t]) atomicAdd(&job.totals->bucket_vertices[t], sv[t]);
+        if (se[t]) atomicAdd(&job.totals->bucket_edges[t], se[t]);
     }
-    if (t == 1023) data[n] = part[1023];
+    if (t < GNN_MAX_BINS && bin_edges[t]) atomicAdd(&job.totals->bin_edges[t], bin_edges[t]);
+    if (t == 0 && pieces) atomicAdd(&job.totals->n_chunks, pieces);
 }
 
-// Stable placement: row v goes to block_prefix[bin][blk] + (#rows of the same bin before it in the block).
-__global__ void __launch_bounds__(kSplitThreads) bin_scatter_kernel(const void *__restrict__ indptr, int ip64,
-                                                                    int64_t N, Thresholds thr, int64_t n_blocks,
-                                                                    const int64_t *__restrict__ block_prefix,
-                                                                    int32_t *__restrict__ row_perm) {
+// Stable placement: row v goes to block_counts[bin][blk] (prefix sums by now) + (#rows of the same bin before it in the block).
+// The first workgroup hands the totals to the host.
+__global__ void __launch_bounds__(kSplitThreads) plan_place_kernel(PlanJobs jobs) {
     __shared__ int wave_tot[kSplitWaves][GNN_MAX_BINS];
+    const PlanJob &job = jobs.job[blockIdx.y];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
+    if (blockIdx.x == 0) {
+        const int t = threadIdx.x;
+        if (t < 256) {
+            job.host->bucket_vertices[t] = job.totals->bucket_vertices[t];
+            job.host->bucket_edges[t] = job.totals->bucket_edges[t];
+        }
+        if (t < jobs.nb) {
+            job.host->bin_edges[t] = job.totals->bin_edges[t];
+            job.host->bin_begin[t] = job.block_counts[int64_t(t) * jobs.n_blocks];
+        }
+        if (t == 0) job.host->n_chunks = job.totals->n_chunks;
+    }
     int64_t v = int64_t(blockIdx.x) * kSplitThreads + threadIdx.x;
     int bin = -1;
-    if (v < N) {
-        int64_t deg = load_ip(indptr, ip64, v + 1) - load_ip(indptr, ip64, v);
-        bin = bin_of(deg, thr);
+    if (v < jobs.N) {
+        int64_t deg = load_ip(job.indptr, jobs.ip64, v + 1) - load_ip(job.indptr, jobs.ip64, v);
+        bin = bin_of(deg, jobs.thr);
     }
     int rank_in_wave = 0;
-    for (int b = 0; b <= thr.k; ++b) {
+    for (int b = 0; b < jobs.nb; ++b) {
         unsigned long long m = __ballot(bin == b);
         if (bin == b) rank_in_wave = __popcll(m & ((1ull << lane) - 1ull));
         if (lane == 0) wave_tot[wave][b] = __popcll(m);
@@ -144,35 +151,41 @@ __global__ void __launch_bounds__(kSplitThreads) bin_scatter_kernel(const void *
     if (bin >= 0) {
         int before = 0;
         for (int w = 0; w < wave; ++w) before += wave_tot[w][bin];
-        int64_t pos = block_prefix[int64_t(bin) * n_blocks + blockIdx.x] + before + rank_in_wave;
-        row_perm[pos] = static_cast<int32_t>(v);
+        int64_t pos = job.block_counts[int64_t(bin) * jobs.n_blocks + blockIdx.x] + before + rank_in_wave;
+        job.row_perm[pos] = static_cast<int32_t>(v);
     }
 }
 
-__global__ void __launch_bounds__(256) hub_count_kernel(const int32_t *__restrict__ hub_rows, int64_t n_hub,
-                                                        const void *__restrict__ indptr, int ip64, int64_t chunk,
-                                                        int64_t *__restrict__ counts) {
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n_hub) return;
-    int64_t v = hub_rows[i];
-    int64_t deg = load_ip(indptr, ip64, v + 1) - load_ip(indptr, ip64, v);
-    counts[i] = (deg + chunk - 1) / chunk;
+// pieces of the hub rows, zero behind the last of them: the arrays are sized before the host knows how many there are
+__global__ void __launch_bounds__(256) hub_count_kernel(PlanJobs jobs, int64_t n_bound) {
+    const PlanJob &job = jobs.job[blockIdx.y];
+    const int64_t hub_begin = job.block_counts[int64_t(jobs.nb - 1) * jobs.n_blocks];
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n_bound; i += stride) {
+        int64_t pieces = 0;
+        if (hub_begin + i < jobs.N) {
+            const int64_t v = job.row_perm[hub_begin + i];
+            const int64_t deg = load_ip(job.indptr, jobs.ip64, v + 1) - load_ip(job.indptr, jobs.ip64, v);
+            pieces = (deg + jobs.hub_chunk - 1) / jobs.hub_chunk;
+        }
+        job.hub_offsets[i] = pieces;
+    }
 }
 
-__global__ void __launch_bounds__(256) hub_fill_kernel(const int32_t *__restrict__ hub_rows, int64_t n_hub,
-                                                       const void *__restrict__ indptr, int ip64, int64_t chunk,
-                                                       const int64_t *__restrict__ offsets,
-                                                       int64_t *__restrict__ chunks) {
-    int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n_hub) return;
-    int64_t v = hub_rows[i];
-    int64_t b = load_ip(indptr, ip64, v);
-    const int64_t end = load_ip(indptr, ip64, v + 1);
-    int64_t c = offsets[i];
-    for (; b < end; b += chunk, ++c) {
-        chunks[3 * c + 0] = v;
-        chunks[3 * c + 1] = b;
-        chunks[3 * c + 2] = b + chunk < end ? b + chunk : end;
+__global__ void __launch_bounds__(256) hub_fill_kernel(PlanJobs jobs, int64_t n_bound, int64_t chunk_bound) {
+    const PlanJob &job = jobs.job[blockIdx.y];
+    const int64_t hub_begin = job.block_counts[int64_t(jobs.nb - 1) * jobs.n_blocks];
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n_bound && hub_begin + i < jobs.N; i += stride) {
+        const int64_t v = job.row_perm[hub_begin + i];
+        int64_t b = load_ip(job.indptr, jobs.ip64, v);
+        const int64_t end = load_ip(job.indptr, jobs.ip64, v + 1);
+        int64_t c = job.hub_offsets[i];
+        for (; b < end && c < chunk_bound; b += jobs.hub_chunk, ++c) {
+            job.chunks[3 * c + 0] = v;
+            job.chunks[3 * c + 1] = b;
+            job.chunks[3 * c + 2] = b + jobs.hub_chunk < end ? b + jobs.hub_chunk : end;
+        }
     }
 }
 
@@ -211,10 +224,10 @@ int gnn_plan_edge_scale(gnn_plan *plan, const int32_t *indices, int mode, hipStr
     if (!arr && plan->n_edges > 0) {
         if (!indices) return GNN_ERR_INVALID_ARG;
         (void)hipGetLastError();
-        if (hipMalloc(&arr, sizeof(float) * plan->n_edges) != hipSuccess) { arr = nullptr; return GNN_ERR_ALLOC; }
+        if (!gnn_dev_alloc(&arr, plan->n_edges, stream)) return GNN_ERR_ALLOC;
         edge_scale_kernel<<<grid_for(plan->n_edges, 256, 1 << 16), 256, 0, stream>>>(indices, plan->n_edges, plan->col_counts, mode, arr);
         if (hipGetLastError() != hipSuccess) {  // an unfilled array must not serve a later call
-            (void)hipFree(arr);
+            gnn_dev_free(arr);
             arr = nullptr;
             return GNN_ERR_LAUNCH;
         }
@@ -239,10 +252,7 @@ int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const in
     *out = nullptr;
     if (plan->n_edges == 0) return GNN_OK;
     (void)hipGetLastError();
-    if (!plan->edge_operand && hipMalloc(&plan->edge_operand, sizeof(float) * plan->n_edges) != hipSuccess) {
-        plan->edge_operand = nullptr;
-        return GNN_ERR_ALLOC;
-    }
+    if (!plan->edge_operand && !gnn_dev_alloc(&plan->edge_operand, plan->n_edges, stream)) return GNN_ERR_ALLOC;
     edge_operand_kernel<<<grid_for(plan->n_edges, 256, 1 << 16), 256, 0, stream>>>(fE, lde, edge_ids, plan->n_edges, plan->edge_operand);
     if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     *out = plan->edge_operand;
@@ -278,7 +288,7 @@ int gnn_plan_cold_indices(gnn_plan *plan, const int32_t *indices, bool force, hi
     *out = nullptr;
     if (!plan || plan->n_edges <= 0) return GNN_OK;
     if (plan->cold_decided && plan->cold_forced != (force ? 1 : 0)) {  // built under the other rule: build again
-        (void)hipFree(plan->cold_indices);
+        gnn_dev_free(plan->cold_indices);
         plan->cold_indices = nullptr;
         plan->cold_decided = 0;
     }
@@ -299,15 +309,12 @@ int gnn_plan_cold_indices(gnn_plan *plan, const int32_t *indices, bool force, hi
             if (thr < 1) thr = 1;
             if (!indices) return GNN_ERR_INVALID_ARG;
             (void)hipGetLastError();
-            if (hipMalloc(&plan->cold_indices, sizeof(int32_t) * plan->n_edges) != hipSuccess) {
-                plan->cold_indices = nullptr;
-                return GNN_ERR_ALLOC;
-            }
+            if (!gnn_dev_alloc(&plan->cold_indices, plan->n_edges, stream)) return GNN_ERR_ALLOC;
             plan->cold_threshold = int32_t(thr > INT32_MAX ? INT32_MAX : thr);
             flag_cold_kernel<<<grid_for(plan->n_edges, 256, 1 << 16), 256, 0, stream>>>(indices, plan->n_edges, plan->col_counts,
                                                                                        plan->cold_threshold, plan->cold_indices);
             if (hipGetLastError() != hipSuccess) {
-                (void)hipFree(plan->cold_indices);
+                gnn_dev_free(plan->cold_indices);
                 plan->cold_indices = nullptr;
                 return GNN_ERR_LAUNCH;
             }
@@ -330,24 +337,69 @@ __global__ void __launch_bounds__(256) plan_order_lens_kernel(const int32_t *__r
     }
 }
 
-// One wavefront per row: copies the row's edge list to its plan-order position, mapping every
-// source id to its rank and flagging the cold ones (rank >= warm) in bit 31.
-__global__ void __launch_bounds__(256) plan_order_fill_kernel(const int32_t *__restrict__ row_perm, int64_t N,
+// Copies the rows' edge lists to their plan-order positions, mapping every source id to its rank and flagging the cold ones
+// (rank >= warm) in bit 31.  A workgroup writes kFillEdges consecutive positions whatever rows they belong to: it looks up
+// the row of the first, marks where the further rows begin, and spreads the marks with a running maximum.  (One wavefront
+// per row was bound by the longest rows' chains of loads: 3.1 M edges, 61,226 rows 94 us.)
+constexpr int kFillEdges = 2048;
+
+__global__ void __launch_bounds__(256) plan_order_fill_kernel(const int32_t *__restrict__ row_perm, int64_t N, int64_t E,
                                                               const void *__restrict__ indptr, int ip64,
                                                               const int64_t *__restrict__ p_indptr,
                                                               const int32_t *__restrict__ indices,
                                                               const int32_t *__restrict__ rank, int64_t warm,
                                                               int32_t *__restrict__ out) {
-    const int lane = threadIdx.x & 63;
-    const int64_t n_waves = int64_t(gridDim.x) * (blockDim.x >> 6);
-    for (int64_t i = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6); i < N; i += n_waves) {
-        const int64_t v = row_perm[i];
-        const int64_t o0 = load_ip(indptr, ip64, v), len = load_ip(indptr, ip64, v + 1) - o0;
-        const int64_t p0 = p_indptr[i];
-        for (int64_t k = lane; k < len; k += 64) {
-            const int32_t r = rank[indices[o0 + k]];
-            out[p0 + k] = r >= warm ? int32_t(uint32_t(r) | 0x80000000u) : r;
-        }
+    constexpr int PER = kFillEdges / 256;
+    __shared__ int32_t owner[kFillEdges];
+    __shared__ int32_t wave_max[4];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int64_t first = int64_t(blockIdx.x) * kFillEdges;
+    const int64_t end = first + kFillEdges < E ? first + kFillEdges : E;
+    int64_t lo = 0, hi = N;  // the last row that begins at `first` or before
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (p_indptr[mid] <= first) lo = mid; else hi = mid;
+    }
+    const int32_t row0 = int32_t(lo);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) owner[k * 256 + t] = row0;
+    __syncthreads();
+    for (int64_t i0 = int64_t(row0) + 1; i0 < N; i0 += 256) {
+        const int64_t i = i0 + t;
+        const int64_t begin = i < N ? p_indptr[i] : E;
+        if (begin < end) atomicMax(&owner[begin - first], int32_t(i));  // of rows that begin together, the last has the edges
+        if (__syncthreads_or(begin >= end)) break;
+    }
+    __syncthreads();
+    int32_t mine[PER], top = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int32_t x = owner[t * PER + k];
+        top = x > top ? x : top;
+        mine[k] = top;
+    }
+    int32_t upto = top;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int32_t y = __shfl_up(upto, off);
+        if (lane >= off && y > upto) upto = y;
+    }
+    if (lane == 63) wave_max[wave] = upto;
+    int32_t before = __shfl_up(upto, 1);
+    if (lane == 0) before = 0;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) before = wave_max[w] > before ? wave_max[w] : before;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) owner[t * PER + k] = mine[k] > before ? mine[k] : before;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t at = first + k * 256 + t;
+        if (at >= end) continue;
+        const int32_t i = owner[k * 256 + t];
+        const int64_t from = load_ip(indptr, ip64, row_perm[i]) + (at - p_indptr[i]);
+        const int32_t r = rank[indices[from]];
+        out[at] = r >= warm ? int32_t(uint32_t(r) | 0x80000000u) : r;
     }
 }
 
@@ -385,9 +437,9 @@ int gnn_plan_rank_indices(gnn_plan *plan, const void *indptr, const int32_t *ind
     *out = gnn_rank_layout{};
     if (!plan || plan->n_edges <= 0 || plan->n_rows <= 0) return GNN_OK;
     if (plan->rank_indices && plan->rank_forced != (force_cold ? 1 : 0)) {  // flagged under the other rule: build again
-        (void)hipFree(plan->rank_indices);
-        (void)hipFree(plan->p_indptr);
-        (void)hipFree(plan->p_chunks);
+        gnn_dev_free(plan->rank_indices);
+        gnn_dev_free(plan->p_indptr);
+        gnn_dev_free(plan->p_chunks);
         plan->rank_indices = nullptr;
         plan->p_indptr = nullptr;
         plan->p_chunks = nullptr;
@@ -397,23 +449,28 @@ int gnn_plan_rank_indices(gnn_plan *plan, const void *indptr, const int32_t *ind
         const int64_t N = plan->n_rows;
         (void)hipGetLastError();
         if (!plan->rank) {
-            if (hipMalloc(&plan->rank, sizeof(int32_t) * N) != hipSuccess) { plan->rank = nullptr; return GNN_ERR_ALLOC; }
-            int rc = gnn_rank_by_count(plan->col_counts, N, plan->rank, stream);
-            if (rc != GNN_OK) { (void)hipFree(plan->rank); plan->rank = nullptr; return rc; }
+            if (!gnn_dev_alloc(&plan->rank, N, stream)) return GNN_ERR_ALLOC;
+            int top = 255;  // the counts lie below the bound of the next bucket
+            while (top > 0 && plan->bucket_vertices[top] == 0) --top;
+            const int64_t max_count = top < 255 ? bucket_lower_bound(top + 1) - 1 : INT32_MAX;
+            int rc = gnn_rank_by_count(plan->col_counts, N, max_count, plan->rank, stream);
+            if (rc != GNN_OK) { gnn_dev_free(plan->rank); plan->rank = nullptr; return rc; }
         }
         // The indices of this copy are ranks, so the kernel finds the cold sources by comparing with
         // the warm-set size of the call; bit 31 is only set when the tests force it.
         const int64_t warm = force_cold ? (N + 3) / 4 : N;
         int64_t *p_indptr = nullptr, *p_chunks = nullptr;
         int32_t *idx = nullptr;
-        auto fail = [&](int s) { (void)hipFree(p_indptr); (void)hipFree(p_chunks); (void)hipFree(idx); return s; };
-        if (hipMalloc(&p_indptr, sizeof(int64_t) * (N + 1)) != hipSuccess) return fail(GNN_ERR_ALLOC);
-        if (hipMalloc(&idx, sizeof(int32_t) * plan->n_edges) != hipSuccess) return fail(GNN_ERR_ALLOC);
-        if (plan->n_chunks > 0 && hipMalloc(&p_chunks, sizeof(int64_t) * 4 * plan->n_chunks) != hipSuccess) return fail(GNN_ERR_ALLOC);
+        auto fail = [&](int s) { gnn_dev_free(p_indptr); gnn_dev_free(p_chunks); gnn_dev_free(idx); return s; };
+        gnn_dev_ptr<int64_t> sums;
+        if (!gnn_dev_alloc(&p_indptr, N + 1, stream) || !gnn_dev_alloc(&idx, plan->n_edges, stream)) return fail(GNN_ERR_ALLOC);
+        if (plan->n_chunks > 0 && !gnn_dev_alloc(&p_chunks, 4 * plan->n_chunks, stream)) return fail(GNN_ERR_ALLOC);
+        if (!sums.alloc_on(gnn_scan_sums_elems(N), stream)) return fail(GNN_ERR_ALLOC);
         plan_order_lens_kernel<<<grid_for(N, 256), 256, 0, stream>>>(plan->row_perm, N, indptr, plan->indptr_is_64, p_indptr);
-        scan_exclusive_kernel<<<1, 1024, 0, stream>>>(p_indptr, N);
-        plan_order_fill_kernel<<<grid_for(N * 64, 256, 1 << 16), 256, 0, stream>>>(plan->row_perm, N, indptr, plan->indptr_is_64,
-                                                                                   p_indptr, indices, plan->rank, warm, idx);
+        const int scan_rc = gnn_scan_exclusive_i64(p_indptr, N, 1, 0, sums.p, stream);
+        if (scan_rc != GNN_OK) return fail(scan_rc);
+        plan_order_fill_kernel<<<static_cast<unsigned>((plan->n_edges + kFillEdges - 1) / kFillEdges), 256, 0, stream>>>(
+            plan->row_perm, N, plan->n_edges, indptr, plan->indptr_is_64, p_indptr, indices, plan->rank, warm, idx);
         if (plan->n_chunks > 0) {
             const int64_t hub_begin = plan->bin_offsets[plan->n_bins - 1];
             plan_order_chunks_kernel<<<grid_for(plan->n_hub_rows, 256), 256, 0, stream>>>(
@@ -461,10 +518,10 @@ int gnn_plan_padded(gnn_plan *plan, int64_t bytes) {
     if (!plan || bytes < 0) return GNN_ERR_INVALID_ARG;
     if (bytes <= plan->padded_bytes) return GNN_OK;
     (void)hipGetLastError();
-    (void)hipFree(plan->padded);
+    gnn_dev_free(plan->padded);
     plan->padded = nullptr;
     plan->padded_bytes = 0;
-    if (hipMalloc(&plan->padded, bytes) != hipSuccess) return GNN_ERR_ALLOC;
+    if (gnn_dev_alloc_bytes(&plan->padded, size_t(bytes)) != GNN_OK) return GNN_ERR_ALLOC;
     // padding columns are never written again; clear them once so that they hold finite values
     if (hipMemset(plan->padded, 0, bytes) != hipSuccess) return GNN_ERR_LAUNCH;
     plan->padded_bytes = bytes;
@@ -535,35 +592,158 @@ extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, 
 
 extern "C" GNN_API void gnn_plan_destroy(gnn_plan *plan) {
     if (!plan) return;
-    (void)hipFree(plan->edge_scale[0]);
-    (void)hipFree(plan->edge_scale[1]);
-    (void)hipFree(plan->edge_scale[2]);
-    (void)hipFree(plan->padded);
-    (void)hipFree(plan->cold_indices);
-    (void)hipFree(plan->rank);
-    (void)hipFree(plan->rank_indices);
-    (void)hipFree(plan->p_indptr);
-    (void)hipFree(plan->p_chunks);
-    (void)hipFree(plan->edge_operand);
-    (void)hipFree(plan->blk_indices);
-    (void)hipFree(plan->blk_epos);
-    (void)hipFree(plan->blk_idx16);
-    (void)hipFree(plan->blk_piece_block);
-    (void)hipFree(plan->blk_pieces);
-    (void)hipFree(plan->blk_rowbase);
-    (void)hipFree(plan->blk_partial);
-    (void)hipFree(plan->blk_cell_off);
+    gnn_dev_free(plan->edge_scale[0]);
+    gnn_dev_free(plan->edge_scale[1]);
+    gnn_dev_free(plan->edge_scale[2]);
+    gnn_dev_free(plan->padded);
+    gnn_dev_free(plan->cold_indices);
+    gnn_dev_free(plan->rank);
+    gnn_dev_free(plan->rank_indices);
+    gnn_dev_free(plan->p_indptr);
+    gnn_dev_free(plan->p_chunks);
+    gnn_dev_free(plan->edge_operand);
+    gnn_dev_free(plan->blk_indices);
+    gnn_dev_free(plan->blk_epos);
+    gnn_dev_free(plan->blk_idx16);
+    gnn_dev_free(plan->blk_piece_block);
+    gnn_dev_free(plan->blk_pieces);
+    gnn_dev_free(plan->blk_rowbase);
+    gnn_dev_free(plan->blk_partial);
+    gnn_dev_free(plan->blk_cell_off);
     for (gnn_tiles &t : plan->tiles) gnn_tiles_free(t);
-    (void)hipFree(plan->tile_partial);
-    for (int i = 0; i < 3; ++i) (void)hipFree(plan->blk_edge_scale[i]);
-    (void)hipFree(plan->blk_bound_w);
-    (void)hipFree(plan->row_perm);
-    (void)hipFree(plan->col_counts);
-    (void)hipFree(plan->chunks);
-    (void)hipFree(plan->hub_chunk_offsets);
-    (void)hipFree(plan->scratch);
+    gnn_dev_free(plan->tile_partial);
+    for (int i = 0; i < 3; ++i) gnn_dev_free(plan->blk_edge_scale[i]);
+    gnn_dev_free(plan->blk_bound_w);
+    gnn_dev_free(plan->row_perm);
+    gnn_dev_free(plan->col_counts);
+    gnn_dev_free(plan->chunks);
+    gnn_dev_free(plan->hub_chunk_offsets);
+    gnn_dev_free(plan->scratch);
     delete plan;
 }
+
+namespace {
+
+int check_params(const gnn_plan_params *params, gnn_plan_params *prm) {
+    if (params) *prm = *params; else gnn_plan_default_params(prm);
+    if (prm->n_thresholds < 0 || prm->n_thresholds > GNN_MAX_THRESHOLDS || prm->hub_chunk < 0) return GNN_ERR_INVALID_ARG;
+    for (int i = 0; i < prm->n_thresholds; ++i) {
+        if (prm->thresholds[i] <= 0) return GNN_ERR_INVALID_ARG;
+        if (i > 0 && prm->thresholds[i] <= prm->thresholds[i - 1]) return GNN_ERR_INVALID_ARG;
+    }
+    return GNN_OK;
+}
+
+gnn_plan *new_plan(const void *indptr, int64_t N, int64_t E, int indptr_is_64, const gnn_plan_params &prm) {
+    gnn_plan *plan = new (std::nothrow) gnn_plan();
+    if (!plan) return nullptr;
+    plan->n_rows = N;
+    plan->n_edges = E;
+    plan->n_bins = prm.n_thresholds + 1;
+    plan->indptr_is_64 = indptr_is_64 ? 1 : 0;
+    plan->params = prm;
+    plan->indptr_seen = indptr;
+    return plan;
+}
+
+// Fills one plan, or the two of a graph and its transpose (whose column counts are each other's row lengths) with the same
+// launches.  Everything is launched before the host waits, once: the arrays whose size depends on the graph are allocated
+// for the most that E edges can need.
+int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, const int32_t *indices, hipStream_t stream) {
+    const int64_t N = plans[0]->n_rows, E = plans[0]->n_edges;
+    const gnn_plan_params &prm = plans[0]->params;
+    const int nb = plans[0]->n_bins;
+    PlanJobs jobs{};
+    jobs.N = N;
+    jobs.n_blocks = (N + kSplitThreads - 1) / kSplitThreads;
+    jobs.hub_chunk = prm.hub_chunk;
+    jobs.ip64 = plans[0]->indptr_is_64;
+    jobs.nb = nb;
+    jobs.thr.k = prm.n_thresholds;
+    for (int i = 0; i < jobs.thr.k; ++i) jobs.thr.t[i] = prm.thresholds[i];
+    const int64_t n_counts = jobs.n_blocks * nb, count_stride = n_counts + 1;
+    // rows of the last bin have at least this many edges
+    const int64_t hub_degree = prm.n_thresholds > 0 ? prm.thresholds[prm.n_thresholds - 1] : 0;
+    int64_t hub_bound = prm.hub_chunk > 0 ? (hub_degree > 0 && E / hub_degree < N ? E / hub_degree : N) : 0;
+    const int64_t chunk_bound = hub_bound > 0 ? E / prm.hub_chunk + hub_bound : 0;
+
+    // [totals of both][block counts of both][scan scratch]
+    const int64_t n_scan = n_counts > hub_bound ? n_counts : hub_bound;
+    const int64_t totals_words = (int64_t(sizeof(RowTotals)) + 7) / 8;
+    gnn_dev_ptr<int64_t> arena;
+    if (!arena.alloc_on(n_plans * (totals_words + count_stride + gnn_scan_sums_elems(n_scan)), stream)) return GNN_ERR_ALLOC;
+    int64_t *totals = arena.p, *counts = totals + n_plans * totals_words, *sums = counts + n_plans * count_stride;
+    struct HostBlocks {
+        void *p[2] = {nullptr, nullptr};
+        hipStream_t stream = nullptr;
+        bool in_use = false;  // a launched kernel may still write to them
+        ~HostBlocks() {
+            if (in_use) (void)hipStreamSynchronize(stream);
+            gnn_host_block_free(p[0]);
+            gnn_host_block_free(p[1]);
+        }
+    } host;
+    host.stream = stream;
+    for (int i = 0; i < n_plans; ++i) {
+        gnn_plan *p = plans[i];
+        if (!gnn_dev_alloc(&p->row_perm, N, stream) || !gnn_dev_alloc(&p->col_counts, N, stream)) return GNN_ERR_ALLOC;
+        if (hub_bound > 0 && (!gnn_dev_alloc(&p->hub_chunk_offsets, hub_bound + 1, stream) ||
+                              !gnn_dev_alloc(&p->chunks, 3 * chunk_bound, stream))) return GNN_ERR_ALLOC;
+        if (!(host.p[i] = gnn_host_block())) return GNN_ERR_ALLOC;
+        PlanJob &j = jobs.job[i];
+        j.indptr = indptrs[i];
+        j.other_indptr = n_plans == 2 ? indptrs[1 - i] : nullptr;
+        j.col_counts = p->col_counts;
+        j.block_counts = counts + i * count_stride;
+        j.totals = reinterpret_cast<RowTotals *>(totals + i * totals_words);
+        j.host = static_cast<RowTotals *>(host.p[i]);
+        j.row_perm = p->row_perm;
+        j.hub_offsets = p->hub_chunk_offsets;
+        j.chunks = p->chunks;
+    }
+    GNN_HIP_TRY(hipMemsetAsync(totals, 0, size_t(n_plans * totals_words) * 8, stream));  // not in a capture: the pool has refused those
+    if (n_plans == 1) {
+        GNN_HIP_TRY(hipMemsetAsync(plans[0]->col_counts, 0, sizeof(int32_t) * N, stream));
+        if (E > 0) count_cols_kernel<<<grid_for(E, 256, 1 << 16), 256, 0, stream>>>(indices, E, plans[0]->col_counts);
+    }
+    const unsigned y = static_cast<unsigned>(n_plans);
+    plan_rows_kernel<<<dim3(grid_for(jobs.n_blocks, 1, 2048), y), kSplitThreads, 0, stream>>>(jobs);
+    int rc = gnn_scan_exclusive_i64(counts, n_counts, n_plans, count_stride, sums, stream);
+    if (rc != GNN_OK) return rc;
+    host.in_use = true;
+    plan_place_kernel<<<dim3(static_cast<unsigned>(jobs.n_blocks), y), kSplitThreads, 0, stream>>>(jobs);
+    if (hub_bound > 0) {
+        const dim3 grid(grid_for(hub_bound, 256, 1 << 16), y);
+        hub_count_kernel<<<grid, 256, 0, stream>>>(jobs, hub_bound);
+        for (int i = 0; i < n_plans; ++i)
+            if ((rc = gnn_scan_exclusive_i64(plans[i]->hub_chunk_offsets, hub_bound, 1, 0, sums, stream)) != GNN_OK) return rc;
+        hub_fill_kernel<<<grid, 256, 0, stream>>>(jobs, hub_bound, chunk_bound);
+    }
+    GNN_HIP_TRY(hipGetLastError());
+    GNN_HIP_TRY(hipStreamSynchronize(stream));
+    host.in_use = false;
+    for (int i = 0; i < n_plans; ++i) {
+        gnn_plan *p = plans[i];
+        const RowTotals &r = *jobs.job[i].host;
+        for (int b = 0; b < 256; ++b) {
+            p->bucket_vertices[b] = static_cast<int64_t>(r.bucket_vertices[b]);
+            p->bucket_edges[b] = static_cast<int64_t>(r.bucket_edges[b]);
+        }
+        for (int b = 0; b < nb; ++b) {
+            p->bin_edges[b] = static_cast<int64_t>(r.bin_edges[b]);
+            p->bin_offsets[b] = r.bin_begin[b];
+        }
+        p->bin_offsets[nb] = N;
+        if (prm.hub_chunk > 0) {
+            p->n_hub_rows = N - p->bin_offsets[nb - 1];
+            p->n_chunks = static_cast<int64_t>(r.n_chunks);
+            if (p->n_hub_rows > hub_bound || p->n_chunks > chunk_bound) return GNN_ERR_INVALID_GRAPH;  // row pointers that decrease
+        }
+    }
+    return GNN_OK;
+}
+
+}  // namespace
 
 extern "C" GNN_API int gnn_plan_create(const void *indptr, const int32_t *indices, int64_t N, int indptr_is_64,
                                const gnn_plan_params *params, void *stream_v, gnn_plan **out) {
@@ -571,125 +751,44 @@ extern "C" GNN_API int gnn_plan_create(const void *indptr, const int32_t *indice
     *out = nullptr;
     if (N < 0 || N > INT32_MAX || (N > 0 && !indptr)) return GNN_ERR_INVALID_ARG;
     gnn_plan_params prm;
-    if (params) prm = *params; else gnn_plan_default_params(&prm);
-    if (prm.n_thresholds < 0 || prm.n_thresholds > GNN_MAX_THRESHOLDS || prm.hub_chunk < 0)
-        return GNN_ERR_INVALID_ARG;
-    for (int i = 0; i < prm.n_thresholds; ++i) {
-        if (prm.thresholds[i] <= 0) return GNN_ERR_INVALID_ARG;
-        if (i > 0 && prm.thresholds[i] <= prm.thresholds[i - 1]) return GNN_ERR_INVALID_ARG;
-    }
+    int rc = check_params(params, &prm);
+    if (rc != GNN_OK) return rc;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     (void)hipGetLastError();  // a stale error of an earlier, failed call must not be blamed on this one
-    gnn_plan *plan = new (std::nothrow) gnn_plan();
-    if (!plan) return GNN_ERR_ALLOC;
-    plan->n_rows = N;
-    plan->n_bins = prm.n_thresholds + 1;
-    plan->indptr_is_64 = indptr_is_64 ? 1 : 0;
-    plan->params = prm;
-    plan->indptr_seen = indptr;
-    const int nb = plan->n_bins;
-    for (int b = 0; b <= nb; ++b) plan->bin_offsets[b] = 0;
-    if (N == 0) { *out = plan; return GNN_OK; }
-
-    int status = GNN_OK;
-    int64_t *block_counts = nullptr;
-    auto fail = [&](int s) { (void)hipFree(block_counts); gnn_plan_destroy(plan); return s; };
-
-    // number of edges = indptr[N]
     int64_t E = 0;
-    if (indptr_is_64) {
-        if (hipMemcpyAsync(&E, static_cast<const int64_t *>(indptr) + N, 8, hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-        if (hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-    } else {
-        int32_t e32 = 0;
-        if (hipMemcpyAsync(&e32, static_cast<const int32_t *>(indptr) + N, 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-        if (hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-        E = e32;
+    if (N > 0) {
+        rc = gnn_read_edge_count(indptr, N, indptr_is_64, stream, &E);
+        if (rc != GNN_OK) return rc;
+        if (E < 0 || (E > 0 && !indices)) return GNN_ERR_INVALID_ARG;
     }
-    if (E < 0 || (E > 0 && !indices)) return fail(GNN_ERR_INVALID_ARG);
-    plan->n_edges = E;
-
-    Thresholds thr{};
-    thr.k = prm.n_thresholds;
-    for (int i = 0; i < thr.k; ++i) thr.t[i] = prm.thresholds[i];
-
-    const int64_t n_blocks = (N + kSplitThreads - 1) / kSplitThreads;
-    const int64_t n_counts = n_blocks * nb;
-    if (hipMalloc(&plan->row_perm, sizeof(int32_t) * N) != hipSuccess) return fail(GNN_ERR_ALLOC);
-    if (hipMalloc(&plan->col_counts, sizeof(int32_t) * N) != hipSuccess) return fail(GNN_ERR_ALLOC);
-    if (hipMalloc(&block_counts, sizeof(int64_t) * (n_counts + 1)) != hipSuccess) return fail(GNN_ERR_ALLOC);
-
-    // column counts.  The zero fill is a kernel-free memset outside any graph capture.
-    if (hipMemsetAsync(plan->col_counts, 0, sizeof(int32_t) * N, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-    if (E > 0) count_cols_kernel<<<grid_for(E, 256, 1 << 16), 256, 0, stream>>>(indices, E, plan->col_counts);
-    {   // bucket histogram of the column counts (for gnn_plan_top_share)
-        unsigned long long *buckets = nullptr;
-        if (hipMalloc(&buckets, sizeof(unsigned long long) * 512) != hipSuccess) return fail(GNN_ERR_ALLOC);
-        bool ok = hipMemsetAsync(buckets, 0, sizeof(unsigned long long) * 512, stream) == hipSuccess;
-        if (ok) {
-            count_buckets_kernel<<<grid_for(N, 256, 2048), 256, 0, stream>>>(plan->col_counts, N, buckets, buckets + 256);
-            unsigned long long host[512];
-            ok = hipMemcpyAsync(host, buckets, sizeof(host), hipMemcpyDeviceToHost, stream) == hipSuccess &&
-                 hipStreamSynchronize(stream) == hipSuccess;
-            for (int b = 0; ok && b < 256; ++b) {
-                plan->bucket_vertices[b] = static_cast<int64_t>(host[b]);
-                plan->bucket_edges[b] = static_cast<int64_t>(host[256 + b]);
-            }
-        }
-        (void)hipFree(buckets);
-        if (!ok) return fail(GNN_ERR_LAUNCH);
+    gnn_plan *plan = new_plan(indptr, N, E, indptr_is_64, prm);
+    if (!plan) return GNN_ERR_ALLOC;
+    if (N > 0 && (rc = fill_plans(&plan, 1, &indptr, indices, stream)) != GNN_OK) {
+        (void)hipStreamSynchronize(stream);
+        gnn_plan_destroy(plan);
+        return rc;
     }
-
-    {   // edges per bin (host copy: which share of the edges the long rows hold decides the layout of a call)
-        unsigned long long *bin_edges = nullptr;
-        if (hipMalloc(&bin_edges, sizeof(unsigned long long) * GNN_MAX_BINS) != hipSuccess) return fail(GNN_ERR_ALLOC);
-        bool ok = hipMemsetAsync(bin_edges, 0, sizeof(unsigned long long) * GNN_MAX_BINS, stream) == hipSuccess;
-        if (ok) {
-            bin_edges_kernel<<<grid_for(N, 256, 2048), 256, 0, stream>>>(indptr, plan->indptr_is_64, N, thr, bin_edges);
-            unsigned long long host[GNN_MAX_BINS];
-            ok = hipMemcpyAsync(host, bin_edges, sizeof(host), hipMemcpyDeviceToHost, stream) == hipSuccess &&
-                 hipStreamSynchronize(stream) == hipSuccess;
-            for (int b = 0; ok && b < GNN_MAX_BINS; ++b) plan->bin_edges[b] = static_cast<int64_t>(host[b]);
-        }
-        (void)hipFree(bin_edges);
-        if (!ok) return fail(GNN_ERR_LAUNCH);
-    }
-
-    // stable multi-way split of the rows by bin
-    bin_count_kernel<<<static_cast<int>(n_blocks), kSplitThreads, 0, stream>>>(indptr, plan->indptr_is_64, N, thr, n_blocks, block_counts);
-    scan_exclusive_kernel<<<1, 1024, 0, stream>>>(block_counts, n_counts);
-    bin_scatter_kernel<<<static_cast<int>(n_blocks), kSplitThreads, 0, stream>>>(indptr, plan->indptr_is_64, N, thr, n_blocks, block_counts, plan->row_perm);
-    if (hipGetLastError() != hipSuccess) return fail(GNN_ERR_LAUNCH);
-    for (int b = 0; b < nb; ++b) {
-        if (hipMemcpyAsync(&plan->bin_offsets[b], block_counts + int64_t(b) * n_blocks, 8, hipMemcpyDeviceToHost, stream) != hipSuccess)
-            return fail(GNN_ERR_LAUNCH);
-    }
-    if (hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-    plan->bin_offsets[nb] = N;
-
-    // hub rows -> pieces
-    if (prm.hub_chunk > 0) {
-        const int64_t hub_begin = plan->bin_offsets[nb - 1];
-        const int64_t n_hub = N - hub_begin;
-        plan->n_hub_rows = n_hub;
-        if (n_hub > 0) {
-            if (hipMalloc(&plan->hub_chunk_offsets, sizeof(int64_t) * (n_hub + 1)) != hipSuccess) return fail(GNN_ERR_ALLOC);
-            const int32_t *hub_rows = plan->row_perm + hub_begin;
-            hub_count_kernel<<<grid_for(n_hub, 256), 256, 0, stream>>>(hub_rows, n_hub, indptr, plan->indptr_is_64, prm.hub_chunk, plan->hub_chunk_offsets);
-            scan_exclusive_kernel<<<1, 1024, 0, stream>>>(plan->hub_chunk_offsets, n_hub);
-            if (hipMemcpyAsync(&plan->n_chunks, plan->hub_chunk_offsets + n_hub, 8, hipMemcpyDeviceToHost, stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            if (hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-            if (plan->n_chunks > 0) {
-                if (hipMalloc(&plan->chunks, sizeof(int64_t) * 3 * plan->n_chunks) != hipSuccess) return fail(GNN_ERR_ALLOC);
-                hub_fill_kernel<<<grid_for(n_hub, 256), 256, 0, stream>>>(hub_rows, n_hub, indptr, plan->indptr_is_64, prm.hub_chunk, plan->hub_chunk_offsets, plan->chunks);
-            }
-        }
-    }
-    if (hipGetLastError() != hipSuccess) return fail(GNN_ERR_LAUNCH);
-    if (hipStreamSynchronize(stream) != hipSuccess) return fail(GNN_ERR_LAUNCH);
-    (void)hipFree(block_counts);
-    (void)status;
     *out = plan;
+    return GNN_OK;
+}
+
+int gnn_plan_create_pair(const void *indptr, const void *indptr_t, int64_t E, int64_t N, int indptr_is_64,
+                         const gnn_plan_params *params, hipStream_t stream, gnn_plan **fwd, gnn_plan **bwd) {
+    gnn_plan_params prm;
+    int rc = check_params(params, &prm);
+    if (rc != GNN_OK) return rc;
+    const void *indptrs[2] = {indptr, indptr_t};
+    gnn_plan *plans[2] = {new_plan(indptr, N, E, indptr_is_64, prm), new_plan(indptr_t, N, E, indptr_is_64, prm)};
+    if (!plans[0] || !plans[1]) rc = GNN_ERR_ALLOC;
+    if (rc == GNN_OK && N > 0) rc = fill_plans(plans, 2, indptrs, nullptr, stream);
+    if (rc != GNN_OK) {
+        (void)hipStreamSynchronize(stream);
+        gnn_plan_destroy(plans[0]);
+        gnn_plan_destroy(plans[1]);
+        return rc;
+    }
+    *fwd = plans[0];
+    *bwd = plans[1];
     return GNN_OK;
 }
 
@@ -724,10 +823,10 @@ extern "C" GNN_API int gnn_plan_reserve(gnn_plan *plan, int64_t F) {
     const int64_t need = gnn_plan_workspace_bytes(plan, F);
     if (need <= plan->scratch_bytes) return GNN_OK;
     (void)hipGetLastError();
-    (void)hipFree(plan->scratch);
+    gnn_dev_free(plan->scratch);
     plan->scratch = nullptr;
     plan->scratch_bytes = 0;
-    if (hipMalloc(&plan->scratch, need) != hipSuccess) return GNN_ERR_ALLOC;
+    if (gnn_dev_alloc_bytes(&plan->scratch, size_t(need)) != GNN_OK) return GNN_ERR_ALLOC;
     plan->scratch_bytes = need;
     return GNN_OK;
 }

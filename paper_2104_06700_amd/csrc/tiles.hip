@@ -471,19 +471,16 @@ __global__ void __launch_bounds__(kTileThreads) tile_kernel(const TileArgs a) {
     }
 }
 
-template <typename T>
-bool dev_alloc(T **p, int64_t n) { return hipMalloc(p, sizeof(T) * size_t(n > 0 ? n : 1)) == hipSuccess; }
-
 // number of the layout for L lanes per row
 int level_of(int lanes, bool bf16) { return (lanes == 8 ? 0 : (lanes == 4 ? 1 : 2)) + (bf16 ? 3 : 0); }
 
 }  // namespace
 
 void gnn_tiles_free(gnn_tiles &t) {
-    (void)hipFree(t.part_base); (void)hipFree(t.order); (void)hipFree(t.tiles); (void)hipFree(t.seg); (void)hipFree(t.stream);
-    (void)hipFree(t.counts); (void)hipFree(t.wave_off); (void)hipFree(t.left.pieces); (void)hipFree(t.left.piece_block);
-    (void)hipFree(t.left.rowbase); (void)hipFree(t.bound_w); (void)hipFree(t.tmp_w);
-    for (int i = 0; i < 3; ++i) (void)hipFree(t.scale[i]);
+    gnn_dev_free(t.part_base); gnn_dev_free(t.order); gnn_dev_free(t.tiles); gnn_dev_free(t.seg); gnn_dev_free(t.stream);
+    gnn_dev_free(t.counts); gnn_dev_free(t.wave_off); gnn_dev_free(t.left.pieces); gnn_dev_free(t.left.piece_block);
+    gnn_dev_free(t.left.rowbase); gnn_dev_free(t.bound_w); gnn_dev_free(t.tmp_w);
+    for (int i = 0; i < 3; ++i) gnn_dev_free(t.scale[i]);
     t = gnn_tiles{};
 }
 
@@ -496,11 +493,11 @@ struct Scratch {
     explicit Scratch(hipStream_t s) : stream(s) {}
     ~Scratch() {
         if (!all.empty()) (void)hipStreamSynchronize(stream);
-        for (void *p : all) (void)hipFree(p);
+        for (void *p : all) gnn_dev_free_on(p, stream);
     }
     template <typename T>
     bool get(T **p, int64_t n) {
-        if (!dev_alloc(p, n)) { *p = nullptr; return false; }
+        if (!gnn_dev_alloc(p, n, stream)) return false;
         all.push_back(*p);
         return true;
     }
@@ -571,7 +568,7 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     uint32_t *staged = nullptr, *part_base = nullptr, *scan = nullptr, *n_staged = reinterpret_cast<uint32_t *>(d_sums + n_blocks);
     const int64_t n_cells = int64_t(n_blocks) * n_hot;
     if (!tmp.get(&staged, n_hot) || !tmp.get(&scan, gnn_scan_sums_elems(n_cells > n_hot + 1 ? n_cells : n_hot + 1))) return GNN_ERR_ALLOC;
-    if (!dev_alloc(&B.part_base, n_hot + 1)) return GNN_ERR_ALLOC;
+    if (!gnn_dev_alloc(&B.part_base, n_hot + 1, stream)) return GNN_ERR_ALLOC;
     part_base = B.part_base;
     GNN_HIP_TRY(hipMemcpyAsync(d_min, block_min.data(), sizeof(uint32_t) * size_t(n_blocks), hipMemcpyHostToDevice, stream));
     const int row_grid = grid_for(n_hot, 256, INT32_MAX);
@@ -605,17 +602,17 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     if (!(tmp.get(&keys[0], n_parts) && tmp.get(&keys[1], n_parts) && tmp.get(&ids[0], n_parts) && tmp.get(&ids[1], n_parts) &&
           tmp.get(&table, gnn_sort_table_elems(n_parts)) && tmp.get(&sums, sums_n) && tmp.get(&too_long, 1) && tmp.get(&parts, n_parts)))
         return GNN_ERR_ALLOC;
-    if (!dev_alloc(&d_tiles, n_tiles)) return GNN_ERR_ALLOC;
+    if (!gnn_dev_alloc(&d_tiles, n_tiles, stream)) return GNN_ERR_ALLOC;
     B.tiles = d_tiles;
-    if (!dev_alloc(&seg, int64_t(n_tiles) * n_parts)) return GNN_ERR_ALLOC;
+    if (!gnn_dev_alloc(&seg, int64_t(n_tiles) * n_parts, stream)) return GNN_ERR_ALLOC;
     B.seg = seg;
-    if (!(dev_alloc(&B.order, n_parts) && dev_alloc(&B.counts, n_wt * kCounts) && dev_alloc(&B.wave_off, n_wt))) return GNN_ERR_ALLOC;
+    if (!(gnn_dev_alloc(&B.order, n_parts, stream) && gnn_dev_alloc(&B.counts, n_wt * kCounts, stream) && gnn_dev_alloc(&B.wave_off, n_wt, stream))) return GNN_ERR_ALLOC;
     GNN_HIP_TRY(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(TileDesc) * size_t(n_tiles), hipMemcpyHostToDevice, stream));
     GNN_HIP_TRY(hipMemsetAsync(too_long, 0, 4, stream));
     tile_parts_kernel<<<row_grid, 256, 0, stream>>>(staged, part_base, n_hot, cap, parts, keys[0], ids[0]);
     GNN_HIP_TRY(hipGetLastError());
     int where = 0;
-    rc = gnn_radix_sort_pairs(nullptr, keys, ids, n_parts, gnn_ilog2_ceil(int64_t(cap) + 1), table, sums, stream, &where);
+    rc = gnn_radix_sort_pairs(keys, ids, n_parts, gnn_ilog2_ceil(int64_t(cap) + 1), table, sums, stream, &where);
     if (rc != GNN_OK) return rc;
     GNN_HIP_TRY(hipMemcpyAsync(B.order, ids[where], sizeof(uint32_t) * size_t(n_parts), hipMemcpyDeviceToDevice, stream));
     tile_segments_kernel<<<grid_for(int64_t(n_tiles) * n_parts, 256), 256, 0, stream>>>(d_tiles, n_tiles, rule, B.order, parts, n_parts,
@@ -635,7 +632,7 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     }
     if (host_too_long || total >= int64_t(UINT32_MAX)) return GNN_OK;  // over 1,020 edges of a row into one tile (duplicates): keep the pieces
     if ((rc = gnn_scan_exclusive_u32(B.wave_off, n_wt, sums, stream)) != GNN_OK) return rc;
-    if (!dev_alloc(&B.stream, (total + kStreamAhead) * rows * kUnit)) return GNN_ERR_ALLOC;
+    if (!gnn_dev_alloc(&B.stream, (total + kStreamAhead) * rows * kUnit, stream)) return GNN_ERR_ALLOC;
     tile_fill_kernel<true, false><<<grid_for(n_wt * 64, 256), 256, 0, stream>>>(d_tiles, n_tiles, n_waves, rr, rows, seg, n_parts,
                                                                             B.counts, B.wave_off, plan->blk_indices, nullptr, nullptr,
                                                                             nullptr, tile_lines, B.stream, nullptr);
@@ -699,7 +696,7 @@ int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles_in, const float *
     const int rows = 64 / L.lanes;
     if (!*slot) {
         (void)hipGetLastError();
-        if (!dev_alloc(slot, (L.n_iters + kStreamAhead) * rows * kUnit)) { *slot = nullptr; return GNN_ERR_ALLOC; }
+        if (!gnn_dev_alloc(slot, (L.n_iters + kStreamAhead) * rows * kUnit, stream)) return GNN_ERR_ALLOC;
     }
     if (fill) {
         tile_fill_kernel<false, true><<<grid_for(L.n_waves * L.n_tiles * 64, 256), 256, 0, stream>>>(
@@ -726,10 +723,10 @@ int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int 
     const int64_t need = int64_t(gnn_tile_groups(t, n_slices)) * n_slices * t->n_parts * line_floats * int64_t(sizeof(float));
     if (need <= plan->tile_partial_bytes) return GNN_OK;
     (void)hipGetLastError();
-    (void)hipFree(plan->tile_partial);
+    gnn_dev_free(plan->tile_partial);
     plan->tile_partial = nullptr;
     plan->tile_partial_bytes = 0;
-    if (hipMalloc(&plan->tile_partial, size_t(need)) != hipSuccess) return GNN_ERR_ALLOC;
+    if (gnn_dev_alloc_bytes(&plan->tile_partial, size_t(need)) != GNN_OK) return GNN_ERR_ALLOC;
     plan->tile_partial_bytes = need;
     return GNN_OK;
 }

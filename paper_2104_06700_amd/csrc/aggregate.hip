@@ -58,7 +58,6 @@ int static_scratch_of_current_device(float **out) {
 
 constexpr int kBlockThreads = 256;
 constexpr int kWavesPerBlock = kBlockThreads / 64;
-constexpr int kCoopMaxPass = 2;  // feature passes up to which a workgroup may share a row (sums of 6 KB per pass)
 
 enum ScaleMode : int { kScaleNone = 0, kScaleInv = 1, kScaleRsqrt = 2, kScaleInvPlus1 = 3 };
 enum SelfMode : int { kSelfNone = 0, kSelfPlain = 1, kSelfInvPlus1 = 2 };  // own row added to the sum
@@ -328,7 +327,7 @@ __device__ __forceinline__ float own_row_value(const OwnRowSrc &o, int64_t row, 
 // shared by the wavefronts of a workgroup (a variant of its own: it costs the others a wavefront per SIMD).
 template <typename T, int VEC, int NPASS, bool COEF, bool COOP = false>
 __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs a) {
-    constexpr int U = NPASS >= 4 ? 2 : (NPASS >= 2 ? 4 : 8);  // edges in flight per slot
+    constexpr int U = NPASS >= 2 ? 4 : 8;  // edges in flight per slot
     __shared__ float coop_sums[COOP ? (kWavesPerBlock - 1) * NPASS * VEC * 64 : 1];  // of wavefronts 1 .. 3, by column and lane
     const int lane = threadIdx.x & 63;
     const int wave_in_block = threadIdx.x >> 6;
@@ -945,20 +944,12 @@ template <typename T, int VEC, bool COEF>
 hipError_t launch_npass(int npass, dim3 grid, hipStream_t stream, const AggArgs &a) {
     bool coop = false;
     for (int i = 0; i < a.n_bins; ++i) coop |= (a.bins[i].kind & GNN_BIN_COOP) != 0;
-    switch (npass) {
-        case 1:
-            if (coop) aggregate_kernel<T, VEC, 1, COEF, true><<<grid, kBlockThreads, 0, stream>>>(a);
-            else aggregate_kernel<T, VEC, 1, COEF><<<grid, kBlockThreads, 0, stream>>>(a);
-            break;
-        case 2:
-            if (coop) aggregate_kernel<T, VEC, 2, COEF, true><<<grid, kBlockThreads, 0, stream>>>(a);
-            else aggregate_kernel<T, VEC, 2, COEF><<<grid, kBlockThreads, 0, stream>>>(a);
-            break;
-        case 3: aggregate_kernel<T, VEC, 3, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
-        case 4: aggregate_kernel<T, VEC, 4, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
-        case 5: aggregate_kernel<T, VEC, 5, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
-        case 6: aggregate_kernel<T, VEC, 6, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
-        default: aggregate_kernel<T, VEC, 8, COEF><<<grid, kBlockThreads, 0, stream>>>(a); break;
+    if (npass == 1) {
+        if (coop) aggregate_kernel<T, VEC, 1, COEF, true><<<grid, kBlockThreads, 0, stream>>>(a);
+        else aggregate_kernel<T, VEC, 1, COEF><<<grid, kBlockThreads, 0, stream>>>(a);
+    } else {
+        if (coop) aggregate_kernel<T, VEC, 2, COEF, true><<<grid, kBlockThreads, 0, stream>>>(a);
+        else aggregate_kernel<T, VEC, 2, COEF><<<grid, kBlockThreads, 0, stream>>>(a);
     }
     return hipGetLastError();
 }
@@ -968,7 +959,55 @@ hipError_t launch_coef(bool coef, int npass, dim3 grid, hipStream_t stream, cons
     return coef ? launch_npass<T, VEC, true>(npass, grid, stream, a) : launch_npass<T, VEC, false>(npass, grid, stream, a);
 }
 
-constexpr int kMaxPass = 8;
+// Column slices for rows gathered where they lie (no plan-owned copy), counted in 16-byte strips of a row.
+//
+// Many strips of fp32 on more vertices than the L2s hold rows of: slices of up to 16 strips, for hits in the L2s (100 K
+// vertices, 25 edges each: F=250 223 us whole, 199 sliced; 300 K vertices, 50 edges: F=128 574 / 454, F=256 1380 / 979), and
+// two slices from 256 bytes on where the hot rows fit only as single lines (1 M vertices, 12 edges, F=64 348 / 307).
+//
+// Else slices are a matter of latency.  A slice costs a read of the index stream and, off line boundaries, about half a line
+// more per edge; with fewer lanes per row a wavefront has more edges of a long row in flight, and on a small graph the chain
+// of loads of the longest rows is what a call lasts.  Both are estimated, the lines at the 130 per ns that hits in the
+// L2s come in (a row costs as much as 8 edges) and the chain at 0.8 us per step of 8 edges and slot of a quarter row (a
+// workgroup shares it), half of it hidden behind the rest, and the number of slices is raised while that wins a tenth.  Measured against the estimate: 10 K
+// vertices, 24 edges each, F=100 24 us whole, 15 in four slices; 30 K vertices, 50 edges, F=100 74 us whole, 52 in two slices,
+// 62 in four; bf16 F=250 87 / 66 / 74; 60 K vertices, 8 edges, F=64 35 / 22; 100 K vertices, 25 edges, F=100 89 / 97.
+int64_t in_place_slices(const gnn_plan *plan, int64_t N, int64_t row_bytes, int64_t strips, int esz, bool lines_ok) {
+    if (strips > 512) return (strips + 63) / 64;
+    if (!plan || plan->n_edges <= 0) return lines_ok && strips >= 16 ? (strips + 15) / 16 : 1;
+    if (N > 49152 && esz == 4) {
+        if (strips >= 28) return (strips + 15) / 16;
+        if (lines_ok && row_bytes >= 256 && N * row_bytes >= (int64_t(128) << 20)) return 2;
+    }
+    int64_t longest = plan->n_chunks > 0 ? plan->params.hub_chunk : 0;
+    for (int b = plan->n_bins - (plan->n_chunks > 0 ? 2 : 1); b >= 0; --b)
+        if (plan->bin_offsets[b + 1] > plan->bin_offsets[b]) {
+            const int64_t bound = b < plan->params.n_thresholds ? plan->params.thresholds[b] : plan->bin_edges[b];
+            if (bound > longest) longest = bound;
+            break;
+        }
+    int64_t best = 0;
+    double best_us = 0.0;
+    for (int64_t n = 1; n <= 8; n *= 2) {
+        const int64_t per_slice = (strips + n - 1) / n;
+        if (n > 1 && per_slice < 5) break;
+        const double slice_lines = double(per_slice) * 16.0 / 128.0;
+        const double lines = double(n) * (lines_ok ? (slice_lines > 1.0 ? slice_lines : 1.0) : slice_lines + 0.5);
+        const double gather_us = double(plan->n_edges + 8 * N) * lines / 130e3;
+        const int64_t lanes = int64_t(1) << gnn_ilog2_ceil(per_slice < 64 ? per_slice : 64);
+        const double chain_us = 0.8 * double(longest) / 4.0 / (8.0 * double(64 / lanes)) * double((per_slice + 63) / 64);
+        const double us = gather_us + (chain_us > 0.5 * gather_us ? chain_us - 0.5 * gather_us : 0.0);
+        if (best == 0 || us < 0.9 * best_us) {
+            best = n;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+// Strips per lane at most.  Rows of three and more fell off: fewer edges in flight per wavefront, and no sharing of long rows
+// (100 K vertices, 6 edges each: F=500, two strips per lane, 170 us; F=600, three, 455 us; as two slabs 215).
+constexpr int kMaxPass = 2;
 
 // A library-owned second stream per device (default priority, created on first use, kept until the process
 // ends): the launches over the short rows run there while the caller's stream sweeps the source blocks of the
@@ -1056,7 +1095,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
                                  (!w || w == plan->bound_w || plan->blocking.min_degree > 0);
     const gnn_layout layout = gnn_choose_layout(plan, N, F, esz, ldx, reinterpret_cast<uintptr_t>(gathered) % 128 == 0,
                                                 o.flags, o.max_slices, /*allow_tail=*/o.max_slices != 1,
-                                                /*scaled_source=*/src_mode != kScaleNone, blocks_expected);
+                                                /*scaled_source=*/src_mode != kScaleNone, blocks_expected, /*weights=*/w != nullptr);
     // what a producer can write into: the slice tables in rank order (the layout gnn_packed_target_for describes)
     if ((prepacked || pack_only) &&
         !(layout.padded_copy && layout.slice_major && !(o.flags & GNN_FLAG_NO_RANK_ORDER) && plan->n_edges > 0))
@@ -1166,51 +1205,49 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     // workgroup id, and every XCD has a private L2.  When the gathered rows are whole 128-byte
     // lines, workgroup b of a launch gathers only column slice (b % S): an XCD's L2 then sees one
     // slice of every gathered row instead of whole rows of an eighth of the destinations, so many
-    // more hot source rows stay resident.  Slices are one line wide (wider when the row stride is a
-    // multiple of 8 lines: one-line slices would crowd too few L2 channels), and a row of more
-    // than 8 slices is covered by several launches of 8, 4, 2 or 1 slices (column slabs in time),
+    // more hot source rows stay resident.  Slices of the plan's copy are one line wide, those of rows gathered in place
+    // as in_place_slices() says, and a row of more than 8 slices is covered by several launches of 8, 4, 2 or 1 slices
+    // (column slabs in time),
     // so that every launch keeps all 8 XCDs equally busy.  The price is one read of the index
     // stream per slice.
     struct Segment { int64_t f0, fw; int log2_s; int64_t slice_cols; int tail_slice; };
-    // Sliced: at most 256 one-unit slices, two or more per launch, plus the tail; unsliced: at most 64 slabs.
-    constexpr int kMaxSegs = 130;
+    // Sliced: at most 256 slices, two or more per launch (one in the last ones), plus the tail; unsliced: slabs.
+    constexpr int kMaxSegs = 260;
     Segment segs[kMaxSegs];
     int n_segs = 0;
     {
         const bool lines_ok = (ldg % line_elems == 0) && reinterpret_cast<uintptr_t>(gathered) % 128 == 0;
         const int64_t lines = (F + line_elems - 1) / line_elems;
-        // Slice width: XCD k reads lines {k*w .. k*w+w-1} of rows L lines apart; with L a multiple
-        // of 8 (16) a one-line slice would land on 2 (1) of 16 line-interleaved L2 channels, so
-        // the slice is widened until it covers at least 4 (measured: L=8, w=2 beats w=1; L=4 and
-        // odd L are fastest with w=1).
-        int64_t g16 = 1;
-        while (g16 < 16 && (ldg / line_elems) % (g16 * 2) == 0) g16 *= 2;
-        const int64_t unit_lines = g16 >= 8 ? g16 / 4 : 1;
-        const int64_t units = (lines + unit_lines - 1) / unit_lines;
         const int64_t s_max = o.max_slices > 0 ? o.max_slices : 8;
-        if (lines_ok && units >= 2 && units <= 256 && s_max >= 2 && slices_wanted) {
-            // The last unit is the dense tail, when there is one.  It gets a launch of its own over all
-            // XCDs: gathering 16 bytes costs a cache request per edge like a whole line does, and as one
-            // slice among others it kept its share of the XCDs busy nearly as long as a full line
-            // (F = 100 as 3 + tail in one launch: 5.77 ms; F = 96: 4.52 ms).
-            const int64_t main_units = tail_table ? units - 1 : units;
-            int64_t u0 = 0;
-            while (u0 < main_units) {
+        // `units` column slices of `unit` columns each, as launches of 8, 4, 2 and 1 of them
+        auto add_slices = [&](int64_t units, int64_t unit) {
+            for (int64_t u0 = 0; u0 < units;) {
                 int ls = 3;
-                while (ls > 0 && ((int64_t(1) << ls) > main_units - u0 || (int64_t(1) << ls) > s_max)) --ls;
-                if (n_segs >= kMaxSegs - 1) return GNN_ERR_UNSUPPORTED;  // rows this wide take the unsliced route (max_slices = 1)
+                while (ls > 0 && ((int64_t(1) << ls) > units - u0 || (int64_t(1) << ls) > s_max)) --ls;
+                if (n_segs >= kMaxSegs - 1) return false;  // rows this wide take the unsliced route (max_slices = 1)
                 Segment &g = segs[n_segs++];
-                g.f0 = u0 * unit_lines * line_elems;
-                g.slice_cols = unit_lines * line_elems;
+                g.f0 = u0 * unit;
+                g.slice_cols = unit;
                 g.log2_s = ls;
-                const int64_t end = g.f0 + (g.slice_cols << ls);
+                const int64_t end = g.f0 + (unit << ls);
                 g.fw = (end < F ? end : F) - g.f0;
                 g.tail_slice = -1;
                 u0 += int64_t(1) << ls;
             }
+            return true;
+        };
+        const int64_t strips = (F + vec - 1) / vec;
+        if (padded && lines_ok && lines >= 2 && lines <= 256 && s_max >= 2 && slices_wanted) {
+            // The plan's copy: one-line slices.
+            // The last one is the dense tail, when there is one.  It gets a launch of its own over all
+            // XCDs: gathering 16 bytes costs a cache request per edge like a whole line does, and as one
+            // slice among others it kept its share of the XCDs busy nearly as long as a full line
+            // (F = 100 as 3 + tail in one launch: 5.77 ms; F = 96: 4.52 ms).
+            const int64_t main_lines = tail_table ? lines - 1 : lines;
+            if (!add_slices(main_lines, line_elems)) return GNN_ERR_UNSUPPORTED;
             if (tail_table) {
                 Segment &g = segs[n_segs++];
-                g.f0 = main_units * unit_lines * line_elems;
+                g.f0 = main_lines * line_elems;
                 g.slice_cols = layout.tail_ld;  // few column lanes per row group: the lanes go to more edges instead
                 g.log2_s = 0;
                 g.fw = F - g.f0;
@@ -1218,17 +1255,26 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             }
         } else {
             if (tail_table || slice_major) return GNN_ERR_UNSUPPORTED;  // those layouts are only made for sliced launches
-            // no slices: slabs of up to 64 lanes * vec * kMaxPass columns
-            const int64_t slab = int64_t(64) * vec * kMaxPass;
-            for (int64_t f0 = 0; f0 < F && n_segs < 64; f0 += slab) {
-                Segment &g = segs[n_segs++];
-                g.f0 = f0;
-                g.fw = F - f0 < slab ? F - f0 : slab;
-                g.log2_s = 0;
-                g.slice_cols = g.fw;
-                g.tail_slice = -1;
+            const int64_t n = padded || !slices_wanted || s_max < 2 ? 1 : in_place_slices(plan, N, F * esz, strips, esz, lines_ok);
+            if (n > 1 && n <= 256) {
+                // up to 8 in one launch, the last ones of which may be left without columns
+                const int64_t per_slice = (strips + n - 1) / n;
+                const bool one_launch = n <= s_max && (n & (n - 1)) == 0;
+                if (!add_slices(one_launch ? n : (strips + per_slice - 1) / per_slice, per_slice * vec)) return GNN_ERR_UNSUPPORTED;
+            } else {
+                // whole rows: slabs of at most kMaxPass strips per lane
+                const int64_t n_slabs = (strips + 64 * kMaxPass - 1) / (64 * kMaxPass);
+                if (n_slabs > kMaxSegs) return GNN_ERR_UNSUPPORTED;
+                const int64_t slab = (strips + n_slabs - 1) / n_slabs * vec;
+                for (int64_t f0 = 0; f0 < F; f0 += slab) {
+                    Segment &g = segs[n_segs++];
+                    g.f0 = f0;
+                    g.fw = F - f0 < slab ? F - f0 : slab;
+                    g.log2_s = 0;
+                    g.slice_cols = g.fw;
+                    g.tail_slice = -1;
+                }
             }
-            if ((F + slab - 1) / slab > 64) return GNN_ERR_UNSUPPORTED;
         }
     }
 
@@ -1457,7 +1503,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             if (f0 < plain_hub_col_begin) plain_hub_col_begin = f0;
         }
         int32_t nb = 0;
-        int64_t next_block = gnn_fill_bins(a.bins, &nb, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX, 1 << log2_s, npass <= kCoopMaxPass);
+        int64_t next_block = gnn_fill_bins(a.bins, &nb, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX, 1 << log2_s);
         a.n_bins = nb;
         if (nb == 0 || next_block == 0) continue;
         next_block <<= log2_s;

@@ -500,7 +500,7 @@ int64_t make_bins(ApArgs &a, const gnn_plan *plan, int64_t N, int log2_c, int sl
         a.row_perm = plan->row_perm;
         a.chunks = plan->chunks;
     }
-    return gnn_fill_bins(a.bins, &a.n_bins, plan, N, log2_c, INT32_MAX, slices, /*coop_ok=*/true);
+    return gnn_fill_bins(a.bins, &a.n_bins, plan, N, log2_c, INT32_MAX, slices);
 }
 
 struct Common {

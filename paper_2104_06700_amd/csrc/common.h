@@ -301,7 +301,7 @@ static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz) {
 
 static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int64_t F, int esz, int64_t ldx,
                                            bool base_line_aligned, int flags, int max_slices, bool allow_tail = false,
-                                           bool scaled_source = false, bool blocks_expected = false) {
+                                           bool scaled_source = false, bool blocks_expected = false, bool weights = false) {
     gnn_layout L{};
     const int64_t line_elems = 128 / esz;
     const int64_t lines = (F + line_elems - 1) / line_elems;
@@ -318,46 +318,45 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
         const double gain = gnn_plan_top_share(plan, 32768) - gnn_plan_top_share(plan, 32768 / (lines > 0 ? lines : 1));
         L.slices_wanted = gain >= 0.08 || N * row_bytes < (int64_t(32) << 20);
     }
-    // Column slices make XCD k read the same lines (k, k+S, ...) of every row.  With a row stride
-    // of an even number of lines those addresses share their low line-index bits and crowd a few
-    // of the XCD's 16 L2 channels (measured at F=256, 8 slices: 15.4 ms with 8-line rows, 12.5 ms
-    // with 9-line rows).  An odd stride spreads them over all channels, so the padded copy always
-    // has one; rows that are not whole lines, and line-aligned rows with an even stride when the
-    // gather (E rows) dwarfs the copy (N rows: >= 16 edges per vertex for rows of >= 512 bytes,
-    // >= 128 for shorter ones), are copied when slices are wanted.  So are fp32 rows that carry a
-    // factor as gathered rows (scaled_source: MEAN / SAGE_GCN backward, weight-less GCN): the copy
-    // multiplies it in, which saves the per-edge factor stream and multiply (2.45 M vertices, 50
-    // edges each, backward MEAN: F=96 4.98 -> 4.53 ms, F=224 11.6 -> 10.6; 233 K vertices, 490 edges
-    // each: F=96 3.00 -> 2.48, F=224 6.85 -> 5.60).
+    // The plan-owned copy: slice tables in rank order (see slice_major below), fp32 factors of the gathered rows
+    // multiplied in, the long rows as source-blocked pieces where the graph has them.  It costs a pass over N rows
+    // and the gather of whole lines (F = 100: 512 bytes per edge for 400), and it buys hits in the L2s: it pays once
+    // the gather is large against that, at 16 edges per vertex and so many gathered bytes (measured on power-law
+    // graphs of 2,500 to 1,000,000 vertices, 6 to 200 edges each, against in_place_slices() of aggregate.hip):
+    //   rows off line boundaries  3 GB with pieces, 5 GB without (300 K vertices, F=100: 25 edges 312 us in place, 322
+    //                             copied; 50 edges 559 / 450; 100 K vertices, F=250: 25 edges 199 / 225, 50 349 / 337)
+    //   line-aligned rows         8 GB, 16 GB (300 K vertices, F=128: 25 edges 265 / 301, 50 454 / 433)
+    //   rows of one line          1.28 GB of lines (245 K vertices, F=20: 25 edges 77 / 81, 50 124 / 118)
+    // Coefficients make the call in place dearer (every slice reads them): about half of that, if there are some.
     const bool lines_ok = (ldx % line_elems == 0) && base_line_aligned;
     const bool even_stride = lines_ok && (ldx / line_elems) % 2 == 0;
     const bool big = N * row_bytes >= (int64_t(32) << 20);  // well beyond the L2s: the layout decides the hit rate
-    const bool dense_enough = plan && plan->n_edges >= 16 * N;  // the copy (N rows) is small next to the gather (E rows)
-    const bool pays_at_any_size = dense_enough && N * row_bytes >= (int64_t(1) << 20);
     const bool folds_factor = scaled_source && esz == 4;
-    // More than one line.  Rows that are not whole lines are copied whatever the size of the matrix
-    // (in place they are gathered with narrow loads and straddle lines: 233 K vertices, 490 edges
-    // each, F=33 fp32 3.16 -> 1.53 ms, F=65 bf16 8.16 -> 1.65), and so are rows that carry a factor;
-    // line-aligned rows with an even stride only when the matrix is large and slices are wanted.
-    bool worth_it = row_bytes > 128 &&
-                    ((!lines_ok && pays_at_any_size) || (folds_factor && pays_at_any_size) ||
-                     (big && L.slices_wanted && even_stride && plan && plan->n_edges >= (row_bytes >= 512 ? 16 : 128) * N) ||
-                     // the long rows as source-blocked pieces need the slice tables: whatever the stride, the copy
-                     // (N rows) buys the pieces (2.45 M vertices, 50 edges each, forward MEAN: F=96 4.42 in place,
-                     // 3.53 ms copied; F=64 3.09 / 2.45; F=160 7.48 / 5.81)
-                     (blocks_expected && big && L.slices_wanted && allow_tail && lines <= 256));
+    const bool coef = scaled_source || weights;
+    double least_gb = lines_ok ? (blocks_expected ? (coef ? 5.0 : 8.0) : (coef ? 8.0 : 16.0))
+                               : (blocks_expected ? (coef ? 1.7 : 3.0) : (coef ? 1.7 : 5.0));
+    if (lines == 1) least_gb = coef ? 0.7 : 1.28;
+    const bool pays = plan && plan->n_edges >= 16 * N && double(plan->n_edges) * double(lines == 1 ? 128 : row_bytes) >= least_gb * 1e9;
+    // An even number of lines per row crowds the L2 channels when slices are gathered in place (F=256, 8 slices: 15.4 ms
+    // with 8-line rows, 12.5 ms with 9-line rows), so such rows are copied where slices are wanted: >= 16 edges per vertex
+    // for rows of >= 512 bytes, >= 128 for shorter ones.
+    bool worth_it = row_bytes > 128 && pays &&
+                    (!lines_ok || folds_factor ||
+                     (L.slices_wanted && ((even_stride && plan->n_edges >= (row_bytes >= 512 ? 16 : 128) * N) ||
+                                          (blocks_expected && allow_tail && lines <= 256))));
+    // pieces that were asked for need the slice tables
+    if (blocks_expected && plan && plan->blocking.min_degree > 0 && row_bytes > 128 && big && L.slices_wanted && allow_tail && lines <= 256)
+        worth_it = true;
     // Rows of at most one line are copied into rows of the next power of two bytes (16 ... 128), in
     // rank order: no row straddles two lines, the most-gathered rows share lines (up to 8 per
-    // line), and 16-byte loads apply.  Worth it when rows would straddle in place (F = 24: 96-byte
-    // rows) or carry a factor that the copy folds in, and for large matrices when they are at most
-    // 64 bytes (rank order packs the hot rows).
+    // line).  Worth it when rows would straddle in place (F = 24: 96-byte rows) or carry a factor that the
+    // copy folds in, and for large matrices when they are at most 64 bytes (rank order packs the hot rows).
     int64_t narrow_bytes = 16;
     while (narrow_bytes < row_bytes) narrow_bytes *= 2;
     if (lines == 1) {
         const int64_t stride_bytes = ldx * esz;
         const bool in_place_ok = base_line_aligned && stride_bytes <= 128 && (stride_bytes & (stride_bytes - 1)) == 0;
-        worth_it = (!in_place_ok && pays_at_any_size) || (folds_factor && pays_at_any_size) ||
-                   (row_bytes <= 64 && big && dense_enough);
+        worth_it = pays && (!in_place_ok || folds_factor || (row_bytes <= 64 && big));
     }
     L.padded_copy = plan && !(flags & GNN_FLAG_NO_PADDED_COPY) && (worth_it || (flags & GNN_FLAG_FORCE_PADDED_COPY));
     L.ld_pad = lines == 1 ? narrow_bytes / esz : (lines | 1) * line_elems;
@@ -491,14 +490,14 @@ constexpr int GNN_WAVES_PER_BLOCK = 4;  // 256-thread workgroups
 // Fills `bins` for a launch whose row groups have 2^log2_c column lanes; returns the number of
 // workgroups.  plan == nullptr: all N rows in one bin, whole wavefronts per row.
 // first_excluded_bin: rows of bins >= it (and the hub pieces) are left out (they are served as source-blocked pieces).
-// slices: column slices the launch multiplies the workgroups by.  coop_ok: the kernel knows GNN_BIN_COOP.
+// slices: column slices the launch multiplies the workgroups by.
 //
 // A launch that leaves most of the chip idle is bound by latency: the time of a row is the number of its steps (one
 // batch of loads each, about a microsecond), one after the other.  So where there are too few wavefronts, rows get more
 // edge slots than throughput asks for, and where the steps of a long row or of a hub piece outlast the launch's
 // share per wavefront, the four wavefronts of a workgroup share it (24,490 vertices, 1.2 M edges, F=100: 0.33 -> 0.06 ms).
 static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, const gnn_plan *plan, int64_t N, int log2_c,
-                                    int first_excluded_bin = INT32_MAX, int slices = 1, bool coop_ok = false) {
+                                    int first_excluded_bin = INT32_MAX, int slices = 1) {
     constexpr int64_t kWaveSlots = 256 * 4 * 8;  // wavefronts the chip holds of a kernel with 64 registers
     constexpr int kStepLog2 = 3;                 // loads of a slot in flight: edges per step
     const int max_log2_sr = 6 - log2_c;
@@ -541,7 +540,7 @@ static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, const g
         int boost = 0;
         while (boost < 3 && (waves << (boost + 1)) <= kWaveSlots) ++boost;
         const int64_t steps_per_slot = steps * slices / kWaveSlots;
-        auto coop = [&](int64_t longest) { return coop_ok && (longest >> (max_log2_sr + kStepLog2)) > 4 + 2 * steps_per_slot ? int(GNN_BIN_COOP) : 0; };
+        auto coop = [&](int64_t longest) { return (longest >> (max_log2_sr + kStepLog2)) > 4 + 2 * steps_per_slot ? int(GNN_BIN_COOP) : 0; };
         // heaviest work first: hub pieces, then bins from long rows to short rows
         if (has_hub && first_excluded_bin > last)
             add_bin(GNN_BIN_HUB_PIECES | coop(plan->params.hub_chunk), 0, plan->n_chunks, max_log2_sr);

@@ -539,7 +539,7 @@ extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, 
         // (a weight-less GCN call is assumed: with explicit weights the rows carry no factor)
         const bool scaled_source = ((op == GNN_MEAN || op == GNN_SAGE_GCN) && backward) || op == GNN_GCN_SYM;
         const gnn_layout layout = gnn_choose_layout(plan, plan->n_rows, F, esz, F, true, 0, 0, /*allow_tail=*/true, scaled_source,
-                                                    gnn_plan_blocks_expected(plan, esz));
+                                                    gnn_plan_blocks_expected(plan, esz), plan->bound_w != nullptr);
         if (layout.padded_copy) {
             rc = gnn_plan_padded(plan, layout.bytes);
             if (rc != GNN_OK) return rc;

@@ -88,3 +88,27 @@ def test_operator_table_on_rows_of_every_length_and_alignment(d, shift):
     assert torch.equal(dfE.cpu(), (dO[el.dst.long()] * fV[el.src.long()]))
     err = (dw.cpu().double() - prod.sum(1)).abs()
     assert bool((err <= 1e-5 * prod.abs().sum(1)).all())
+
+
+@pytest.mark.parametrize("n,e,f,dtype", [(50000, 400000, 113, torch.float32), (50000, 200000, 163, torch.float32),
+                                         (50000, 400000, 601, torch.bfloat16), (3000, 20000, 2051, torch.float32),
+                                         (3000, 20000, 4099, torch.bfloat16), (20000, 300000, 101, torch.float32)])
+def test_column_slices_of_rows_in_place(n, e, f, dtype):
+    """Rows off line boundaries in slices of their own: a number of slices that is no power of two, a last one that is short
+    or empty, and more of them than one launch takes."""
+    el = synth.rmat_symmetric(n, e, (0.57, 0.19, 0.19, 0.05), 4)
+    indptr, indices, indptr_t, indices_t, _ = host_csr(el)
+    din, dout = np.diff(indptr), np.diff(indptr_t)
+    X = synth.normal_features(el.n, f, 3, dtype=dtype)
+    dg = device_graph(el)
+    Yo, S = oracle.aggregate_fwd(indptr, indices, X.float().numpy(), op=oracle.OP_MEAN, dout=dout, nthreads=8, want_scale=True)
+    dXo, St = oracle.aggregate_bwd(indptr_t, indices_t, X.float().numpy(), op=oracle.OP_MEAN, din=din, nthreads=8, want_scale=True)
+    flat = torch.full((el.n * f + 1,), float("nan"), dtype=dtype, device=DEV)
+    Xd = flat[1:].view(el.n, f)
+    Xd.copy_(X)
+    Y, dX = torch.full_like(Xd, float("nan")), torch.full_like(Xd, float("nan"))
+    gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, None, Xd, Y, el.n, f, gnn.GNN_MEAN, plan=dg.plan_fwd)
+    gnn.gnn_aggregate_bwd(dg.indptr_t, dg.indices_t, None, Xd, dX, el.n, f, gnn.GNN_MEAN, plan=dg.plan_bwd)
+    torch.cuda.synchronize()
+    assert_close(Y, Yo, S, dtype == torch.bfloat16, "fwd")
+    assert_close(dX, dXo, St, dtype == torch.bfloat16, "bwd")

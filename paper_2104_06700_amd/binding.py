@@ -96,6 +96,7 @@ class GnnError(RuntimeError):
 
 
 _lib = None
+_calls = None  # the extension module that marshals the hot calls, once the library is loaded
 
 
 def load_library() -> ctypes.CDLL:
@@ -158,8 +159,34 @@ def load_library() -> ctypes.CDLL:
         lib.gnn_status_string.restype = ctypes.c_char_p
         lib.gnn_calib_copy.argtypes = [vp, vp, i64, vp]
         lib.gnn_calib_gather.argtypes = [vp, i64, vp, i64, vp, i64, vp]
+        _connect_calls(lib)
         _lib = lib
     return _lib
+
+
+def _connect_calls(lib) -> None:
+    global _calls
+    try:
+        from . import _pycall
+    except ImportError as err:
+        raise ImportError("the extension module _pycall is missing: run `python -c 'import __graft_entry__ as g; g.build()'`") from err
+    names = ("gnn_aggregate_fwd", "gnn_aggregate_bwd", "gnn_ap_fwd", "gnn_ap_bwd_vertex", "gnn_ap_bwd_vertex_arg",
+             "gnn_ap_bwd_edge", "gnn_sage_layer_fwd", "gnn_sage_layer_bwd")
+    _pycall.connect({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names}, torch)
+    _calls = _pycall
+
+
+def _hot(fn: str, name: str, *args) -> None:
+    """Calls a function of the extension module; an allocation that fails is tried once more (see _call_allocating)."""
+    if _calls is None:
+        load_library()
+    status = getattr(_calls, name)(*args)
+    if status:
+        if status == GNN_ERR_ALLOC:
+            torch.cuda.synchronize()
+            torch.cuda.empty_cache()
+            status = getattr(_calls, name)(*args)
+        _check(fn, status)
 
 
 def status_string(status: int) -> str:
@@ -176,7 +203,7 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream or None
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream or None
     return int(stream) or None
@@ -321,31 +348,11 @@ def gnn_plan_create(indptr: torch.Tensor, indices: torch.Tensor, N: int,
     return Plan(out.value, k)
 
 
-def _aggregate(fn_name, indptr, indices, edge_w, X, Y, N, F, op, plan, stream, workspace, ldx, ldy, flags=0, max_slices=0):
-    lib = load_library()
-    if X.dtype != Y.dtype:
-        raise TypeError("input and output features must have the same dtype")
-    o = GnnOpts()
-    o.dtype = _dtype_code(X)
-    o.indptr_is_64 = _is64(indptr)
-    o.ldx = int(ldx if ldx is not None else (X.stride(0) if X.dim() == 2 and X.shape[0] > 1 else 0))
-    o.ldy = int(ldy if ldy is not None else (Y.stride(0) if Y.dim() == 2 and Y.shape[0] > 1 else 0))
-    o.stream = _stream(stream)
-    o.plan = plan.handle if plan is not None else None
-    o.flags = int(flags)
-    o.max_slices = int(max_slices)
-    if workspace is not None:
-        o.workspace = workspace.data_ptr()
-        o.workspace_bytes = workspace.numel() * workspace.element_size()
-    _call_allocating(fn_name, lambda: getattr(lib, fn_name)(_ptr(indptr), _ptr(indices), _ptr(edge_w), _ptr(X), _ptr(Y),
-                                                            int(N), int(F), int(op), ctypes.byref(o)))
-
-
 def gnn_aggregate_fwd(indptr, indices, edge_w, X, Y, N, F, op, plan: Optional[Plan] = None, stream=None,
                       workspace=None, ldx=None, ldy=None, flags=0, max_slices=0) -> None:
     """Y[v] = scale_v * sum_e c_e X[indices[e]] over the CSR by destination (see include/gnnagg.h)."""
-    _aggregate("gnn_aggregate_fwd", indptr, indices, edge_w, X, Y, N, F, op, plan, stream, workspace, ldx, ldy, flags,
-               max_slices)
+    _hot("gnn_aggregate_fwd", "aggregate", False, indptr, indices, edge_w, X, Y, N, F, op, plan, stream, workspace, ldx, ldy,
+             flags, max_slices)
 
 
 def gnn_aggregate_fwd_noalloc(indptr, indices, edge_w, X, Y, N, F, op, plan: Optional[Plan] = None, stream=None,
@@ -409,38 +416,8 @@ def gnn_aggregate_packed(indptr, indices, edge_w, packed, Y, N, F, op, backward,
 def gnn_aggregate_bwd(indptr_t, indices_t, edge_w_t, dY, dX, N, F, op, plan: Optional[Plan] = None, stream=None,
                       workspace=None, ldx=None, ldy=None, flags=0, max_slices=0) -> None:
     """dX = adjoint of the forward map, over the transposed graph (see include/gnnagg.h)."""
-    _aggregate("gnn_aggregate_bwd", indptr_t, indices_t, edge_w_t, dY, dX, N, F, op, plan, stream, workspace, ldx, ldy, flags,
-               max_slices)
-
-
-def _row_stride(t: Optional[torch.Tensor]) -> int:
-    if t is None or t.dim() != 2 or t.shape[0] <= 1:
-        return 0
-    if t.stride(1) != 1:
-        raise ValueError("feature matrices must have unit column stride")
-    return int(t.stride(0))
-
-
-def _ap_opts(indptr, plan, stream, edge_ids, edge_width, ldv, lde, ldo, flags=0, max_slices=0) -> GnnApOpts:
-    o = GnnApOpts()
-    o.flags = int(flags)
-    o.max_slices = int(max_slices)
-    o.indptr_is_64 = 0 if indptr is None else _is64(indptr)
-    o.edge_width = int(edge_width)
-    o.ldv, o.lde, o.ldo = int(ldv), int(lde), int(ldo)
-    if edge_ids is not None:
-        if edge_ids.dtype != torch.int64:
-            raise TypeError("edge_ids must be int64")
-        o.edge_ids = _ptr(edge_ids)
-    o.stream = _stream(stream)
-    o.plan = plan.handle if plan is not None else None
-    return o
-
-
-def _edge_width(fE: Optional[torch.Tensor], d: int) -> int:
-    if fE is None:
-        return 0
-    return 1 if (fE.dim() == 1 or fE.shape[1] == 1) and d != 1 else 0
+    _hot("gnn_aggregate_bwd", "aggregate", True, indptr_t, indices_t, edge_w_t, dY, dX, N, F, op, plan, stream, workspace,
+             ldx, ldy, flags, max_slices)
 
 
 def _f32(*tensors) -> None:
@@ -453,45 +430,24 @@ def gnn_ap_fwd(indptr, indices, fV, fE, fO, arg_e, N, d, binop, reduce, plan: Op
                stream=None, flags=0, max_slices=0) -> None:
     """f_O[v] = reduce_e binop(f_V[u_e], f_E[e]) with any operator pair of Table 1 (see include/gnnagg.h).
     f_E may be [E, d] or [E] / [E, 1] (one scalar per edge)."""
-    _f32(fV, fE, fO)
-    if arg_e is not None and (arg_e.dtype != torch.int32 or not arg_e.is_contiguous()):
-        raise TypeError("arg_e must be a contiguous int32 tensor")
-    o = _ap_opts(indptr, plan, stream, edge_ids, _edge_width(fE, d), _row_stride(fV), _row_stride(fE) if fE is not None and fE.dim() == 2 else 0,
-                 _row_stride(fO), flags, max_slices)
-    _call_allocating("gnn_ap_fwd", lambda: load_library().gnn_ap_fwd(
-        _ptr(indptr), _ptr(indices), _ptr(fV), _ptr(fE), _ptr(fO), _ptr(arg_e), int(N), int(d), int(binop), int(reduce),
-        ctypes.byref(o)))
+    _hot("gnn_ap_fwd", "ap_fwd", indptr, indices, fV, fE, fO, arg_e, N, d, binop, reduce, plan, edge_ids, stream, flags, max_slices)
 
 
 def gnn_ap_bwd_vertex(indptr_t, indices_t, dO, fE, dfV, N, d, binop, plan: Optional[Plan] = None, edge_ids=None,
                       stream=None) -> None:
     """Gradient with respect to f_V for the sum reducer, over the transposed graph (see include/gnnagg.h)."""
-    _f32(dO, fE, dfV)
-    o = _ap_opts(indptr_t, plan, stream, edge_ids, _edge_width(fE, d), _row_stride(dfV),
-                 _row_stride(fE) if fE is not None and fE.dim() == 2 else 0, _row_stride(dO))
-    _call_allocating("gnn_ap_bwd_vertex", lambda: load_library().gnn_ap_bwd_vertex(
-        _ptr(indptr_t), _ptr(indices_t), _ptr(dO), _ptr(fE), _ptr(dfV), int(N), int(d), int(binop), ctypes.byref(o)))
+    _hot("gnn_ap_bwd_vertex", "ap_bwd_vertex", indptr_t, indices_t, dO, fE, dfV, N, d, binop, plan, edge_ids, stream)
 
 
 def gnn_ap_bwd_vertex_arg(indices, arg_e, dO, fE, dfV, n_vertex_rows, N, d, binop, edge_ids=None, stream=None) -> None:
     """Gradient with respect to f_V for max / min: scatter to the winners (see include/gnnagg.h)."""
-    _f32(dO, fE, dfV)
-    o = _ap_opts(None, None, stream, edge_ids, _edge_width(fE, d), _row_stride(dfV),
-                 _row_stride(fE) if fE is not None and fE.dim() == 2 else 0, _row_stride(dO))
-    _check("gnn_ap_bwd_vertex_arg", load_library().gnn_ap_bwd_vertex_arg(
-        _ptr(indices), _ptr(arg_e), _ptr(dO), _ptr(fE), _ptr(dfV), int(n_vertex_rows), int(N), int(d), int(binop),
-        ctypes.byref(o)))
+    _hot("gnn_ap_bwd_vertex_arg", "ap_bwd_vertex_arg", indices, arg_e, dO, fE, dfV, n_vertex_rows, N, d, binop, edge_ids, stream)
 
 
 def gnn_ap_bwd_edge(indptr, indices, arg_e, fV, fE, dO, dfE, N, d, binop, plan: Optional[Plan] = None, edge_ids=None,
                     stream=None) -> None:
     """Gradient with respect to f_E, one row per edge (see include/gnnagg.h).  dfE has f_E's shape."""
-    _f32(fV, fE, dO, dfE)
-    o = _ap_opts(indptr, plan, stream, edge_ids, _edge_width(dfE, d), _row_stride(fV),
-                 _row_stride(dfE) if dfE.dim() == 2 else 0, _row_stride(dO))
-    _check("gnn_ap_bwd_edge", load_library().gnn_ap_bwd_edge(
-        _ptr(indptr), _ptr(indices), _ptr(arg_e), _ptr(fV), _ptr(fE), _ptr(dO), _ptr(dfE), int(N), int(d), int(binop),
-        ctypes.byref(o)))
+    _hot("gnn_ap_bwd_edge", "ap_bwd_edge", indptr, indices, arg_e, fV, fE, dO, dfE, N, d, binop, plan, edge_ids, stream)
 
 
 def gnn_matmul_workspace_bytes(M: int, N: int, K: int) -> int:
@@ -516,12 +472,6 @@ def gnn_matmul(A, B, C, trans_a=False, trans_b=False, bias=None, relu=False, wor
         0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)))
 
 
-def _dense(*tensors) -> None:
-    for t in tensors:
-        if t is not None and not t.is_contiguous():
-            raise ValueError("the layer calls take dense (contiguous) tensors")
-
-
 def gnn_sage_layer_saved_elems(N, F_in, F_out, order=0) -> int:
     return int(load_library().gnn_sage_layer_saved_elems(int(N), int(F_in), int(F_out), int(order)))
 
@@ -535,39 +485,15 @@ GNN_LAYER_NO_PRODUCER_LAYOUT = 2
 GNN_LAYER_NO_GATE_FOLD = 4
 
 
-def _layer_opts(indptr, plan, relu, order, stream, workspace=None, flags=0) -> GnnLayerOpts:
-    o = GnnLayerOpts()
-    o.flags = int(flags)
-    o.indptr_is_64 = _is64(indptr)
-    o.relu = 1 if relu else 0
-    o.order = int(order)
-    o.stream = _stream(stream)
-    o.plan = plan.handle if plan is not None else None
-    if workspace is not None:
-        o.workspace = workspace.data_ptr()
-        o.workspace_bytes = workspace.numel() * workspace.element_size()
-    return o
-
-
 def gnn_sage_layer_fwd(indptr, indices, X, W, bias, saved, H, plan: Plan, relu=True, order=0, stream=None, flags=0) -> None:
     """H = act(aggregate(X) W + b), one GraphSAGE layer (see include/gnnagg.h)."""
-    _f32(X, W, bias, saved, H)
-    _dense(X, W, bias, saved, H)
-    o = _layer_opts(indptr, plan, relu, order, stream, flags=flags)
-    _call_allocating("gnn_sage_layer_fwd", lambda: load_library().gnn_sage_layer_fwd(
-        _ptr(indptr), _ptr(indices), _ptr(X), _ptr(W), _ptr(bias), _ptr(saved), _ptr(H), int(X.shape[0]), int(W.shape[0]),
-        int(W.shape[1]), ctypes.byref(o)))
+    _hot("gnn_sage_layer_fwd", "sage_layer_fwd", indptr, indices, X, W, bias, saved, H, plan, relu, order, stream, flags)
 
 
 def gnn_sage_layer_bwd(indptr_t, indices_t, X, W, saved, H, dH, dX, dW, db, plan: Plan, workspace, relu=True, order=0,
                        stream=None, flags=0) -> None:
     """Gradients of one layer over the transposed graph (see include/gnnagg.h)."""
-    _f32(X, W, saved, H, dH, dX, dW, db)
-    _dense(X, W, saved, H, dH, dX, dW, db)
-    o = _layer_opts(indptr_t, plan, relu, order, stream, workspace, flags=flags)
-    _call_allocating("gnn_sage_layer_bwd", lambda: load_library().gnn_sage_layer_bwd(
-        _ptr(indptr_t), _ptr(indices_t), _ptr(X), _ptr(W), _ptr(saved), _ptr(H), _ptr(dH), _ptr(dX), _ptr(dW), _ptr(db),
-        int(X.shape[0]), int(W.shape[0]), int(W.shape[1]), ctypes.byref(o)))
+    _hot("gnn_sage_layer_bwd", "sage_layer_bwd", indptr_t, indices_t, X, W, saved, H, dH, dX, dW, db, plan, workspace, relu, order, stream, flags)
 
 
 def gnn_csr_from_sorted_coo(dst_sorted: torch.Tensor, N: int, indptr_out: torch.Tensor, stream=None) -> None:

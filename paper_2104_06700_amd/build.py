@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libgnnagg.so")
+PYCALL = os.path.join(PKG, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJ_DIR = os.path.join(PKG, "_build")
 
 SOURCES = ["aggregate.hip", "blocked.hip", "tiles.hip", "ap.hip", "gemm.hip", "layer.hip", "plan.hip", "graph.hip", "pool.hip", "util.hip"]
@@ -48,8 +50,17 @@ def build_library(verbose: bool = True) -> str:
     os.replace(tmp, LIB)
     if verbose:
         print(f"built {LIB}", file=sys.stderr)
+    build_python_calls()
     build_profiling_driver(verbose)
     return LIB
+
+
+def build_python_calls() -> None:
+    """The extension module that marshals the hot calls (plain C against the interpreter's headers)."""
+    tmp = PYCALL + ".tmp"
+    subprocess.check_call([os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-shared", "-fPIC", "-Wall", "-I", INCLUDE,
+                           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "pycall.c"), "-o", tmp])
+    os.replace(tmp, PYCALL)
 
 
 def build_profiling_driver(verbose: bool = True) -> bool:

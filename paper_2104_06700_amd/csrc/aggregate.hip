@@ -27,6 +27,7 @@
 //     per slice, rows by descending gather count, a dense table for a short last
 //     line (run_aggregate below).
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 
@@ -636,20 +637,21 @@ struct PieceArgs {
     int32_t log2_slices;
 };
 
-// Eight lanes own one piece and one 128-byte line of every gathered row (16 bytes each); a wavefront
-// works on eight consecutive pieces, i.e. on 64 lines in flight.  The pieces of a launch follow the
-// block order of the layout, so the workgroups that run side by side gather from the same block of
+// L lanes own one piece and one line of every gathered row (16 bytes each: L = 8 for lines of 128 bytes, 4 and 2 for
+// shorter rows); a wavefront works on 64 / L consecutive pieces, with 8 lines of each in flight.  The pieces of a
+// launch follow the block order of the layout, so the workgroups that run side by side gather from the same block of
 // source rows.  Every piece writes one fp32 partial line; blk_finalize_kernel adds them.
-template <typename T, bool COEF>
+template <typename T, bool COEF, int L>
 __global__ void __launch_bounds__(kBlockThreads) piece_kernel(const PieceArgs a) {
     constexpr int VEC = 16 / int(sizeof(T));   // elements per lane
-    constexpr int LINE = 8 * VEC;              // elements per line = floats per partial line
+    constexpr int LINE = L * VEC;              // elements per line = floats per partial line
     constexpr int U = 8;
+    constexpr int WINDOW = 4 * L;              // edges whose streams a group holds in registers
     const int lane = threadIdx.x & 63;
     const int slice = int(blockIdx.x) & ((1 << a.log2_slices) - 1);
     const int64_t vblock = int64_t(blockIdx.x) >> a.log2_slices;
-    const int c = lane & 7, gbase = lane & ~7;
-    const int64_t piece = (vblock * kWavesPerBlock + (threadIdx.x >> 6)) * 8 + (lane >> 3);
+    const int c = lane & (L - 1), gbase = lane & ~(L - 1);
+    const int64_t piece = (vblock * kWavesPerBlock + (threadIdx.x >> 6)) * (64 / L) + lane / L;
     uint32_t begin = 0;
     int len = 0;
     int64_t slot = 0;
@@ -670,7 +672,7 @@ __global__ void __launch_bounds__(kBlockThreads) piece_kernel(const PieceArgs a)
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
 
-    // The per-edge streams are read a window of 32 edges at a time: lane c of the group holds edges
+    // The per-edge streams are read a window of 4 L edges at a time: lane c of the group holds edges
     // [t + 4c, t + 4c + 4) of the piece, one 8- or 16-byte load per stream (at the 2- or 4-byte
     // alignment of the element: a piece begins anywhere), so a group touches each line of a stream once
     // instead of once per eight edges.  The loads of a lane may run up to three elements past the piece's
@@ -718,13 +720,13 @@ __global__ void __launch_bounds__(kBlockThreads) piece_kernel(const PieceArgs a)
     int nxt_u[4];
     float nxt_cf[4];
     fetch(0, nxt_u, nxt_cf);
-    for (int t0 = 0; __any(t0 < len); t0 += 32) {
+    for (int t0 = 0; __any(t0 < len); t0 += WINDOW) {
         int my_u[4];
         float my_cf[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) { my_u[i] = nxt_u[i]; my_cf[i] = nxt_cf[i]; }
-        fetch(t0 + 32, nxt_u, nxt_cf);
-        for (int m = 0; m < 4; ++m) {
+        fetch(t0 + WINDOW, nxt_u, nxt_cf);
+        for (int m = 0; m < WINDOW / U; ++m) {
             const int t = t0 + U * m;
             if (!__any(t < len)) break;
             typename Strip<T, VEC>::raw_t x[U];
@@ -760,18 +762,18 @@ __global__ void __launch_bounds__(kBlockThreads) piece_kernel(const PieceArgs a)
 }
 
 // Adds the partial lines of every long row in a fixed order and writes the columns [0, fw) of the
-// launch.  Eight lanes own one (row, slice) pair, 16 bytes of the output row each, so a wavefront
-// finishes eight rows of a slice.  The sums themselves are formed by the whole wavefront, one of its
-// eight pairs after the other: lane group g adds the partial lines g, g + 8, g + 16, ... of the pair (a
-// wavefront load covers eight consecutive lines, 1 KB), and the eight group sums are added pairwise
+// launch.  L lanes own one (row, slice) pair, 16 bytes of the output row each, so a wavefront
+// finishes 64 / L rows of a slice (eight of 128-byte lines).  The sums themselves are formed by eight lane groups together,
+// one of their eight pairs after the other: group g of the eight adds the partial lines g, g + 8, g + 16, ... of the pair (a
+// load covers eight consecutive lines), and the eight group sums are added pairwise
 // (groups 0+1, 2+3, ... then 0..1 + 2..3, ...).  A hub row has thousands of partial lines: added by its
-// own eight lanes alone, one such row set the duration of the launch.
-template <typename T>
+// own lanes alone, one such row set the duration of the launch.
+template <typename T, int L>
 __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__restrict__ rows, int64_t n_rows,
                                                            const uint32_t *__restrict__ rowbase,
                                                            const float *__restrict__ partial, int64_t n_pieces, int n_slices,
                                                            const uint32_t *__restrict__ part_base, int64_t n_parts,
-                                                           const float *__restrict__ tile_partial, int n_groups,
+                                                           const float *__restrict__ tile_partial, int n_groups, uint32_t inv_groups,
                                                            int64_t tile_group_stride,
                                                            const void *indptr, int ip64, int dst_mode, T *__restrict__ Y,
                                                            int64_t ldy, int fw, int store_vec, int self_mode,
@@ -779,18 +781,20 @@ __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__rest
                                                            const int32_t *__restrict__ col_counts,
                                                            const float *__restrict__ bias, int relu) {
     constexpr int VEC = 16 / int(sizeof(T));  // output columns per lane
-    constexpr int LINE = 8 * VEC;             // columns per slice = floats per partial line
+    constexpr int LINE = L * VEC;             // columns per slice = floats per partial line
+    constexpr int G = 64 / L;                 // lane groups, and pairs, of a wavefront
     const int lane = threadIdx.x & 63;
-    const int g = lane >> 3, c = lane & 7;
+    const int own_pair = lane / L, c = lane & (L - 1);
+    const int g = own_pair & 7;               // of the eight that work together
     const int64_t n_items = n_rows * n_slices;
-    const int64_t first_item = ((int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6) << 3;  // wave-uniform
+    const int64_t first_item = ((int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6) * G;  // wave-uniform
     if (first_item >= n_items) return;
     float mine[VEC];  // the sum of this group's own pair
 #pragma unroll
     for (int k = 0; k < VEC; ++k) mine[k] = 0.0f;
     for (int j = 0; j < 8; ++j) {
-        const int64_t item = first_item + j;
-        if (item >= n_items) break;
+        const int64_t item = first_item + (own_pair & ~7) + j;
+        if (item >= n_items) continue;  // the same for the eight groups
         const int64_t i = item % n_rows;
         const int slice = int(item / n_rows);
         const int64_t p0 = rowbase[i], p1 = rowbase[i + 1];
@@ -812,16 +816,21 @@ __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__rest
             }
         };
         if (tile_partial) {  // first the partial lines of the row's parts gathered from staged tiles, one per group of tiles
-            const int64_t v0 = part_base[i], n_lines = int64_t(part_base[i + 1] - v0) * n_groups;
+            const uint32_t v0 = part_base[i], n_lines = (part_base[i + 1] - v0) * uint32_t(n_groups);
             const float *__restrict__ ts = tile_partial + (int64_t(slice) * n_parts + v0) * LINE + c * VEC;
-            for (int64_t p = g; p < n_lines; p += 8) {
-                const int64_t part = p / n_groups;
-                const float *__restrict__ q = ts + (p - part * n_groups) * tile_group_stride + part * LINE;
+            auto load_tile_line = [&](uint32_t p, f32x4 (&v)[VEC / 4]) {
+                const uint32_t part = n_groups > 1 ? __umulhi(p, inv_groups) : p;  // p / n_groups
+                const float *__restrict__ q = ts + int64_t(p - part * uint32_t(n_groups)) * tile_group_stride + int64_t(part) * LINE;
 #pragma unroll
-                for (int k = 0; k < VEC; k += 4) {
-                    const f32x4 v = *reinterpret_cast<const f32x4 *>(q + k);
-                    sum[k] += v.x; sum[k + 1] += v.y; sum[k + 2] += v.z; sum[k + 3] += v.w;
+                for (int k = 0; k < VEC / 4; ++k) {
+                    v[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    if (p < n_lines) v[k] = *(reinterpret_cast<const f32x4 *>(q) + k);
                 }
+            };
+            for (uint32_t p = uint32_t(g); p < n_lines; p += 32) {
+                f32x4 t0[VEC / 4], t1[VEC / 4], t2[VEC / 4], t3[VEC / 4];
+                load_tile_line(p, t0); load_tile_line(p + 8, t1); load_tile_line(p + 16, t2); load_tile_line(p + 24, t3);
+                add_line(t0); add_line(t1); add_line(t2); add_line(t3);
             }
         }
         for (int64_t p = p0 + g; p < p1; p += 32) {  // four lines per group in flight
@@ -830,7 +839,7 @@ __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__rest
             add_line(v0); add_line(v1); add_line(v2); add_line(v3);
         }
 #pragma unroll
-        for (int off = 8; off < 64; off <<= 1)
+        for (int off = L; off < 8 * L; off <<= 1)
 #pragma unroll
             for (int k = 0; k < VEC; ++k) sum[k] += __shfl_xor(sum[k], off);
         if (g == j) {
@@ -838,7 +847,7 @@ __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__rest
             for (int k = 0; k < VEC; ++k) mine[k] = sum[k];
         }
     }
-    const int64_t item = first_item + g;
+    const int64_t item = first_item + own_pair;
     if (item >= n_items) return;
     const int64_t i = item % n_rows;
     const int slice = int(item / n_rows);
@@ -1292,10 +1301,12 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     }
 
     // The long rows of a large power-law graph are served as source-blocked pieces (blocked.hip) in
-    // every launch that gathers from slice tables; the dense tail keeps the plain path.
+    // every launch that gathers from slice tables, or from the one table of rows of at most a line; the dense tail
+    // keeps the plain path.
     gnn_blocked_layout bl{};
     const float *scale_blk = nullptr, *w_blk = nullptr;
-    if (slice_major && rank_indices && !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS)) {
+    const int lanes = layout.line_lanes;  // of a line of the tables
+    if (padded && lanes > 0 && rank_indices && !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS)) {
         int rc = gnn_plan_blocked(plan, indptr, stream, &bl);
         if (rc != GNN_OK) return rc;
         // Explicit weights sit in CSR order, the pieces in rank order: every edge would cost a random 4-byte
@@ -1323,14 +1334,14 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     const gnn_tiles *tl = nullptr;
     const float *tile_coefs = nullptr;
     if (bl.active) {
-        int rc = gnn_plan_tiles(plan, 8, esz == 2, stream, &tl);
+        int rc = gnn_plan_tiles(plan, lanes, esz == 2, stream, &tl);
         if (rc != GNN_OK) return rc;
         if (tl) {
             if (coef) {
                 rc = gnn_plan_tile_coefs(plan, tl, w, edge_scale, src_mode, w && w == plan->bound_w, stream, &tile_coefs);
                 if (rc != GNN_OK) return rc;
             }
-            rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), int(line_elems));
+            rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), lanes * max_vec);
             if (rc != GNN_OK) return rc;
         }
     }
@@ -1449,7 +1460,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         }
         const bool blocked = bl.active && segs[gi].tail_slice < 0;
         if (blocked) {
-            const int line_floats = int(line_elems);
+            const int line_floats = lanes * max_vec;
             int rc = gnn_plan_blocked_partial(plan, 1 << log2_s, line_floats);
             if (rc != GNN_OK) { finish_overlap(); return rc; }
             PieceArgs pa{};
@@ -1469,34 +1480,35 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             pa.slice_stride = layout.table_stride;
             pa.partial = static_cast<float *>(plan->blk_partial);
             pa.log2_slices = log2_s;
-            const int64_t pblocks = ((pa.n_pieces + 8 * kWavesPerBlock - 1) / (8 * kWavesPerBlock)) << log2_s;
+            const int64_t per_block = int64_t(64 / lanes) * kWavesPerBlock;
+            const int64_t pblocks = ((pa.n_pieces + per_block - 1) / per_block) << log2_s;
             if (pblocks > INT32_MAX) { finish_overlap(); return GNN_ERR_UNSUPPORTED; }
             const int n_sl = 1 << log2_s;
-            const dim3 pgrid(static_cast<unsigned>(pblocks)), fgrid(static_cast<unsigned>((bl.n_hot * n_sl * 8 + 255) / 256));
+            const dim3 pgrid(static_cast<unsigned>(pblocks)), fgrid(static_cast<unsigned>((bl.n_hot * n_sl * lanes + 255) / 256));
             const int32_t *hot_rows = plan->row_perm + bl.hot_begin;
             const OwnRowSrc own = own_row_src(f0);
             const float *tile_partial = tl ? static_cast<const float *>(plan->tile_partial) + f0 / line_elems * tl->n_parts * line_floats : nullptr;
             const int64_t tile_group_stride = tl ? layout.main_lines * tl->n_parts * line_floats : 0;
             const uint32_t *rowbase = tl ? tl->left.rowbase : bl.rowbase, *part_base = tl ? tl->part_base : nullptr;
-            if (o.dtype == GNN_F32) {
+            auto launch = [&](auto elem, auto n_lanes) {
+                using T = decltype(elem);
+                constexpr int L = decltype(n_lanes)::value;
                 if (pa.n_pieces == 0) {}
-                else if (coef) piece_kernel<float, true><<<pgrid, kBlockThreads, 0, stream>>>(pa);
-                else piece_kernel<float, false><<<pgrid, kBlockThreads, 0, stream>>>(pa);
-                blk_finalize_kernel<float><<<fgrid, 256, 0, stream>>>(
+                else if (coef) piece_kernel<T, true, L><<<pgrid, kBlockThreads, 0, stream>>>(pa);
+                else piece_kernel<T, false, L><<<pgrid, kBlockThreads, 0, stream>>>(pa);
+                blk_finalize_kernel<T, L><<<fgrid, 256, 0, stream>>>(
                     hot_rows, bl.n_hot, rowbase, pa.partial, pa.n_pieces, n_sl, part_base, tl ? tl->n_parts : 0, tile_partial, tile_groups,
-                    tile_group_stride, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
-                    static_cast<float *>(out) + f0, ldy, int(fw), store_vec, fin_self_mode, own,
+                    tile_groups > 1 ? uint32_t(((uint64_t(1) << 32) + tile_groups - 1) / tile_groups) : 0u, tile_group_stride, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
+                    static_cast<T *>(out) + f0, ldy, int(fw), store_vec, fin_self_mode, own,
                     plan->col_counts, bias ? bias + f0 : nullptr, relu);
-            } else {
-                if (pa.n_pieces == 0) {}
-                else if (coef) piece_kernel<bf16_t, true><<<pgrid, kBlockThreads, 0, stream>>>(pa);
-                else piece_kernel<bf16_t, false><<<pgrid, kBlockThreads, 0, stream>>>(pa);
-                blk_finalize_kernel<bf16_t><<<fgrid, 256, 0, stream>>>(
-                    hot_rows, bl.n_hot, rowbase, pa.partial, pa.n_pieces, n_sl, part_base, tl ? tl->n_parts : 0, tile_partial, tile_groups,
-                    tile_group_stride, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
-                    static_cast<bf16_t *>(out) + f0, ldy, int(fw), store_vec, fin_self_mode, own,
-                    plan->col_counts, bias ? bias + f0 : nullptr, relu);
-            }
+            };
+            auto launch_lanes = [&](auto elem) {
+                if (lanes == 8) launch(elem, std::integral_constant<int, 8>());
+                else if (lanes == 4) launch(elem, std::integral_constant<int, 4>());
+                else launch(elem, std::integral_constant<int, 2>());
+            };
+            if (o.dtype == GNN_F32) launch_lanes(float());
+            else launch_lanes(bf16_t());
             if (hipGetLastError() != hipSuccess) { finish_overlap(); return GNN_ERR_LAUNCH; }
         } else if (has_hub) {
             plain_hub_columns = true;

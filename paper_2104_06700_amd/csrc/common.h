@@ -19,7 +19,7 @@
 // Source tiles in LDS (tiles.hip): the edges of the long rows into the source blocks where they are dense, as one
 // stream per wavefront of the gather, and the piece list of the rest.  One layout per line width (lanes of 16 bytes
 // per row); built on first use.
-constexpr int GNN_TILE_MAX_GROUPS = 16;
+constexpr int GNN_TILE_MAX_GROUPS = 32;
 struct gnn_piece_list {
     int32_t *pieces = nullptr;        // [n_pieces * 4] (begin, length, partial slot, row)
     uint16_t *piece_block = nullptr;  // [n_pieces]
@@ -39,6 +39,7 @@ struct gnn_tiles {
     uint8_t *counts = nullptr;           // [n_waves][n_tiles][16]
     uint32_t *wave_off = nullptr;        // [n_waves][n_tiles]
     std::vector<int64_t> tile_work;      // iterations per tile (host)
+    int32_t max_groups = 1;              // groups of tiles that can share the work evenly
     gnn_piece_list left;                 // the cells that are not staged
     float *scale[3] = {nullptr, nullptr, nullptr};  // the plan's per-edge factors in stream order
     float *bound_w = nullptr;            // bound edge weights in stream order, as of binding number bound_version
@@ -276,6 +277,9 @@ struct gnn_layout {
     bool slice_major;
     int64_t table_stride; // elements between two slice tables (N * elements per line)
     int64_t main_lines;   // number of slice tables
+    // Lanes of 16 bytes per line of the tables that the long rows can be gathered from as source-blocked pieces: 8 of a
+    // slice-major copy, 8, 4 or 2 of a copy whose rows are one line of 128, 64 or 32 bytes (one table), else 0.
+    int32_t line_lanes;
     int64_t bytes;        // size of the whole copy for N rows
 };
 
@@ -323,9 +327,11 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
     // and the gather of whole lines (F = 100: 512 bytes per edge for 400), and it buys hits in the L2s: it pays once
     // the gather is large against that, at 16 edges per vertex and so many gathered bytes (measured on power-law
     // graphs of 2,500 to 1,000,000 vertices, 6 to 200 edges each, against in_place_slices() of aggregate.hip):
-    //   rows off line boundaries  3 GB with pieces, 5 GB without (300 K vertices, F=100: 25 edges 312 us in place, 322
-    //                             copied; 50 edges 559 / 450; 100 K vertices, F=250: 25 edges 199 / 225, 50 349 / 337)
-    //   line-aligned rows         8 GB, 16 GB (300 K vertices, F=128: 25 edges 265 / 301, 50 454 / 433)
+    //   rows off line boundaries  2 GB with pieces, 5 GB without (400 K vertices, 30 edges each, F=50 283 us in place, 257
+    //                             copied; 140 K, 57, F=50 131 / 145; without pieces 100 K vertices, F=250: 25 edges
+    //                             199 / 225, 50 349 / 337)
+    //   line-aligned rows         8 GB, 4 GB from 48 edges per vertex on (300 K vertices, 25 edges, F=256 547 / 595; 400 K,
+    //                             60, F=64 422 / 347), without pieces 16 GB
     //   rows of one line          1.28 GB of lines (245 K vertices, F=20: 25 edges 77 / 81, 50 124 / 118)
     // Coefficients make the call in place dearer (every slice reads them): about half of that, if there are some.
     const bool lines_ok = (ldx % line_elems == 0) && base_line_aligned;
@@ -333,8 +339,9 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
     const bool big = N * row_bytes >= (int64_t(32) << 20);  // well beyond the L2s: the layout decides the hit rate
     const bool folds_factor = scaled_source && esz == 4;
     const bool coef = scaled_source || weights;
-    double least_gb = lines_ok ? (blocks_expected ? (coef ? 5.0 : 8.0) : (coef ? 8.0 : 16.0))
-                               : (blocks_expected ? (coef ? 1.7 : 3.0) : (coef ? 1.7 : 5.0));
+    const bool dense = plan && plan->n_edges >= 48 * N;
+    double least_gb = lines_ok ? (blocks_expected ? (dense ? (coef ? 3.0 : 4.0) : (coef ? 5.0 : 8.0)) : (coef ? 8.0 : 16.0))
+                               : (blocks_expected ? (coef ? 1.7 : 2.0) : (coef ? 1.7 : 5.0));
     if (lines == 1) least_gb = coef ? 0.7 : 1.28;
     const bool pays = plan && plan->n_edges >= 16 * N && double(plan->n_edges) * double(lines == 1 ? 128 : row_bytes) >= least_gb * 1e9;
     // An even number of lines per row crowds the L2 channels when slices are gathered in place (F=256, 8 slices: 15.4 ms
@@ -350,13 +357,20 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
     // Rows of at most one line are copied into rows of the next power of two bytes (16 ... 128), in
     // rank order: no row straddles two lines, the most-gathered rows share lines (up to 8 per
     // line).  Worth it when rows would straddle in place (F = 24: 96-byte rows) or carry a factor that the
-    // copy folds in, and for large matrices when they are at most 64 bytes (rank order packs the hot rows).
+    // copy folds in, for large matrices when they are at most 64 bytes (rank order packs the hot rows), and where the
+    // long rows are served as pieces, which needs it (233 K vertices, 490 edges each, F=16 730 -> 320 us).  A plan that blocks
+    // by itself does so for 24 M edges and rows of 32 bytes, 28 M and 64, 32 M and 128 (200 K vertices, F=7: 20 M edges 115
+    // us without pieces, 129 with, 40 M 196 / 155; 400 K vertices, F=16: 24 M 154 / 163, 45 M 267 / 218; F=32: 24 M 180 /
+    // 195, 45 M 319 / 290): below, the launches that pieces and tiles take weigh more than what they save.
     int64_t narrow_bytes = 16;
     while (narrow_bytes < row_bytes) narrow_bytes *= 2;
+    bool narrow_pieces = false;
     if (lines == 1) {
         const int64_t stride_bytes = ldx * esz;
         const bool in_place_ok = base_line_aligned && stride_bytes <= 128 && (stride_bytes & (stride_bytes - 1)) == 0;
-        worth_it = pays && (!in_place_ok || folds_factor || (row_bytes <= 64 && big));
+        narrow_pieces = blocks_expected && row_bytes > 16 &&
+                        (plan->blocking.min_degree > 0 || plan->n_edges >= (narrow_bytes == 32 ? 24000000 : (narrow_bytes == 64 ? 28000000 : 32000000)));
+        worth_it = pays && (!in_place_ok || folds_factor || (row_bytes <= 64 && big) || narrow_pieces);
     }
     L.padded_copy = plan && !(flags & GNN_FLAG_NO_PADDED_COPY) && (worth_it || (flags & GNN_FLAG_FORCE_PADDED_COPY));
     L.ld_pad = lines == 1 ? narrow_bytes / esz : (lines | 1) * line_elems;
@@ -388,6 +402,8 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
     } else {
         L.bytes = N * (L.ld_pad + L.tail_ld) * esz;
     }
+    L.line_lanes = L.slice_major ? 8 : 0;
+    if (allow_tail && L.padded_copy && narrow_pieces && !(flags & GNN_FLAG_NO_SLICE_TABLES)) L.line_lanes = int32_t(narrow_bytes / 16);
     return L;
 }
 

@@ -546,20 +546,21 @@ extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, 
             gnn_rank_layout unused{};  // built from the row pointers the plan was created from
             rc = gnn_plan_rank_indices(plan, plan->indptr_seen, indices, false, static_cast<hipStream_t>(stream), &unused);
             if (rc != GNN_OK) return rc;
-            if (layout.slice_major) {  // the long rows as source-blocked pieces, and their partial sums
+            if (layout.line_lanes > 0) {  // the long rows as source-blocked pieces, and their partial sums
+                const int line_floats = layout.line_lanes * (16 / esz);
                 gnn_blocked_layout bl{};
                 rc = gnn_plan_blocked(plan, plan->indptr_seen, static_cast<hipStream_t>(stream), &bl);
                 if (rc != GNN_OK) return rc;
                 if (bl.active) {
                     int slices = 1;
                     while (slices < 8 && slices * 2 <= layout.main_lines) slices *= 2;
-                    rc = gnn_plan_blocked_partial(plan, slices, 128 / esz);
+                    rc = gnn_plan_blocked_partial(plan, slices, line_floats);
                     if (rc != GNN_OK) return rc;
                     const gnn_tiles *tl = nullptr;  // and the part of them that is staged in LDS
-                    rc = gnn_plan_tiles(plan, 8, esz == 2, static_cast<hipStream_t>(stream), &tl);
+                    rc = gnn_plan_tiles(plan, layout.line_lanes, esz == 2, static_cast<hipStream_t>(stream), &tl);
                     if (rc != GNN_OK) return rc;
                     if (tl) {
-                        rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), 128 / esz);
+                        rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), line_floats);
                         if (rc != GNN_OK) return rc;
                     }
                     if (plan->bound_w) {

@@ -34,6 +34,7 @@ constexpr int kCounts = 16;        // bytes of counts per wavefront and tile (bu
 // Bundles of rows a wavefront owns at most: as many sums as four wavefronts per SIMD leave registers for.
 constexpr int kBundlesF32 = 10, kBundlesBf16 = 8;
 constexpr int kUnit = 4;          // edges per row in a unit of the streams
+constexpr uint32_t kMaxSegment = 255 * kUnit;  // edges of a row part into one tile at most: a byte of units
 
 constexpr int64_t kFewBundles = 5;      // bundles per wavefront before rows are dealt to more workgroups
 constexpr int64_t kRowBlocks = 64;     // workgroups the rows are dealt to at least (per column slice)
@@ -104,21 +105,24 @@ __global__ void __launch_bounds__(256) tile_row_edges_kernel(DenseRule rule, int
     if ((threadIdx.x & 63) == 0 && m) atomicAdd(n_staged, uint32_t(__popcll(m)));
 }
 
-// parts[h] = parts that row h is cut into (a row much longer than the others would keep its workgroup waiting)
-__global__ void __launch_bounds__(256) tile_row_parts_kernel(const uint32_t *__restrict__ staged, int64_t n_hot, uint32_t cap,
-                                                             uint32_t *__restrict__ parts) {
+// parts[h] = parts that row h is cut into: of `cap` edges at most (a row much longer than the others would keep its
+// workgroup waiting), and of no more edges into one tile than the counts of a stream can say
+__global__ void __launch_bounds__(256) tile_row_parts_kernel(const uint32_t *__restrict__ staged, const uint32_t *__restrict__ longest,
+                                                             int64_t n_hot, uint32_t cap, uint32_t *__restrict__ parts) {
     const int64_t h = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (h < n_hot) parts[h] = (staged[h] + cap - 1) / cap;
+    if (h >= n_hot) return;
+    const uint32_t n = (staged[h] + cap - 1) / cap, m = (longest[h] + kMaxSegment - 1) / kMaxSegment;
+    parts[h] = n > m ? n : m;
 }
 
 // The parts of every row: row, number within the row, parts of the row; and what they are sorted by.
 struct RowPart { uint32_t row, part, parts; };
 __global__ void __launch_bounds__(256) tile_parts_kernel(const uint32_t *__restrict__ staged, const uint32_t *__restrict__ part_base,
-                                                         int64_t n_hot, uint32_t cap, RowPart *__restrict__ out,
+                                                         int64_t n_hot, RowPart *__restrict__ out,
                                                          uint32_t *__restrict__ keys, uint32_t *__restrict__ ids) {
     const int64_t h = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (h >= n_hot) return;
-    const uint32_t n = (staged[h] + cap - 1) / cap;
+    const uint32_t n = part_base[h + 1] - part_base[h];
     for (uint32_t j = 0; j < n; ++j) {
         const uint32_t v = part_base[h] + j;
         out[v] = RowPart{uint32_t(h), j, n};
@@ -149,6 +153,21 @@ __device__ __forceinline__ uint32_t lower_bound_in(const int32_t *__restrict__ r
     return lo;
 }
 
+// longest[h] = most edges of row h into one tile (zeroed before)
+__global__ void __launch_bounds__(256) tile_longest_kernel(const TileDesc *__restrict__ tiles, int n_tiles, DenseRule rule,
+                                                           const int32_t *__restrict__ blk_indices, uint32_t *__restrict__ longest) {
+    const int64_t total = int64_t(n_tiles) * rule.n_hot;
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < total; x += stride) {
+        const TileDesc d = tiles[x / rule.n_hot];
+        const int64_t h = x % rule.n_hot;
+        if (rule.edges(d.block, h) <= kMaxSegment) continue;  // short enough wherever its tiles begin
+        const int64_t c = int64_t(d.block) * rule.n_hot + h;
+        const uint32_t hi = rule.cell_off[c + 1], b = lower_bound_in(blk_indices, rule.cell_off[c], hi, d.begin);
+        atomicMax(&longest[h], lower_bound_in(blk_indices, b, hi, d.begin + d.size) - b);
+    }
+}
+
 // seg[t * n_parts + i] = (begin, end) in the block-major edge list of the edges of row part order[i] into tile t
 __global__ void __launch_bounds__(256) tile_segments_kernel(const TileDesc *__restrict__ tiles, int n_tiles, DenseRule rule,
                                                             const uint32_t *__restrict__ order, const RowPart *__restrict__ parts,
@@ -176,7 +195,7 @@ __global__ void __launch_bounds__(256) tile_segments_kernel(const TileDesc *__re
 // One thread per (wavefront, tile): iterations of each of its bundles there, and their sum.
 __global__ void __launch_bounds__(256) tile_counts_kernel(const uint2 *__restrict__ seg, int64_t n_parts, int n_tiles, int64_t n_waves,
                                                           int rr, int rows_per_bundle, uint8_t *__restrict__ counts,
-                                                          uint32_t *__restrict__ wave_tile_iters, uint32_t *__restrict__ too_long) {
+                                                          uint32_t *__restrict__ wave_tile_iters) {
     const int64_t n_bundles = (n_parts + rows_per_bundle - 1) / rows_per_bundle;
     const int64_t total = n_waves * n_tiles;
     const int64_t stride = int64_t(gridDim.x) * blockDim.x;
@@ -193,7 +212,6 @@ __global__ void __launch_bounds__(256) tile_counts_kernel(const uint2 *__restric
                 const uint32_t n = (s.y - s.x + kUnit - 1) / kUnit;
                 most = n > most ? n : most;
             }
-            if (most > 255u) { *too_long = 1u; most = 255u; }
             counts[x * kCounts + r] = uint8_t(most);
             sum += most;
         }
@@ -579,7 +597,14 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     GNN_HIP_TRY(hipStreamSynchronize(stream));
     if (host_staged == 0) return GNN_OK;
     const uint32_t cap = uint32_t((2 * staged_edges + host_staged - 1) / host_staged);  // twice the mean row
-    tile_row_parts_kernel<<<row_grid, 256, 0, stream>>>(staged, n_hot, cap, part_base);
+    uint32_t *longest = nullptr;
+    TileDesc *d_tiles = nullptr;
+    if (!tmp.get(&longest, n_hot) || !gnn_dev_alloc(&d_tiles, n_tiles, stream)) return GNN_ERR_ALLOC;
+    B.tiles = d_tiles;
+    GNN_HIP_TRY(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(TileDesc) * size_t(n_tiles), hipMemcpyHostToDevice, stream));
+    GNN_HIP_TRY(hipMemsetAsync(longest, 0, sizeof(uint32_t) * size_t(n_hot), stream));
+    tile_longest_kernel<<<grid_for(int64_t(n_tiles) * n_hot, 256), 256, 0, stream>>>(d_tiles, n_tiles, rule, plan->blk_indices, longest);
+    tile_row_parts_kernel<<<row_grid, 256, 0, stream>>>(staged, longest, n_hot, cap, part_base);
     GNN_HIP_TRY(hipGetLastError());
     GNN_HIP_TRY(hipMemcpyAsync(&parts_last, part_base + n_hot - 1, 4, hipMemcpyDeviceToHost, stream));
     int rc = gnn_scan_exclusive_u32(part_base, n_hot, scan, stream);
@@ -592,24 +617,36 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
 
     // bundles of parts of similar size, dealt to the wavefronts
     const int64_t n_bundles = (n_parts + rows - 1) / rows;
-    const int64_t n_row_blocks = row_blocks_for(n_bundles, rr);
+    int64_t n_row_blocks = row_blocks_for(n_bundles, rr);
+    // Few rows: down to a bundle per wavefront where that fills compute units that would be idle (a launch has as many
+    // groups of tiles as that asks for, and several slices of whole lines), while a tile is worth copying that often.
+    // No more groups than the fullest tile, that of the most-gathered sources, leaves something to do for.
+    double fullest = 0.0, all = 0.0;
+    for (const TileDesc &t : tiles) {
+        const double share = gnn_plan_top_share(plan, int64_t(t.begin) + t.size) - gnn_plan_top_share(plan, t.begin);
+        all += share;
+        if (share > fullest) fullest = share;
+    }
+    int64_t groups = fullest > 0.0 ? int64_t(all / fullest) : 1;
+    if (groups > n_tiles) groups = n_tiles;
+    if (groups > GNN_TILE_MAX_GROUPS) groups = GNN_TILE_MAX_GROUPS;
+    if (groups < 1) groups = 1;
+    int64_t fill = kComputeUnits / (groups * (lanes == 8 ? 4 : 1));
+    if (fill > n_bundles / kTileWaves) fill = n_bundles / kTileWaves;
+    if (fill > staged_edges / (n_tiles * kMinTileEdges)) fill = staged_edges / (n_tiles * kMinTileEdges);
+    if (n_row_blocks < fill) n_row_blocks = fill;
     const int64_t n_waves = n_row_blocks * kTileWaves, n_wt = n_waves * n_tiles;
-    uint32_t *keys[2], *ids[2], *table = nullptr, *sums = nullptr, *too_long = nullptr;
+    uint32_t *keys[2], *ids[2], *table = nullptr, *sums = nullptr;
     RowPart *parts = nullptr;
     const int64_t sums_n = gnn_sort_sums_elems(n_parts) > gnn_scan_sums_elems(n_wt) ? gnn_sort_sums_elems(n_parts) : gnn_scan_sums_elems(n_wt);
-    TileDesc *d_tiles = nullptr;
     uint2 *seg = nullptr;
     if (!(tmp.get(&keys[0], n_parts) && tmp.get(&keys[1], n_parts) && tmp.get(&ids[0], n_parts) && tmp.get(&ids[1], n_parts) &&
-          tmp.get(&table, gnn_sort_table_elems(n_parts)) && tmp.get(&sums, sums_n) && tmp.get(&too_long, 1) && tmp.get(&parts, n_parts)))
+          tmp.get(&table, gnn_sort_table_elems(n_parts)) && tmp.get(&sums, sums_n) && tmp.get(&parts, n_parts)))
         return GNN_ERR_ALLOC;
-    if (!gnn_dev_alloc(&d_tiles, n_tiles, stream)) return GNN_ERR_ALLOC;
-    B.tiles = d_tiles;
     if (!gnn_dev_alloc(&seg, int64_t(n_tiles) * n_parts, stream)) return GNN_ERR_ALLOC;
     B.seg = seg;
     if (!(gnn_dev_alloc(&B.order, n_parts, stream) && gnn_dev_alloc(&B.counts, n_wt * kCounts, stream) && gnn_dev_alloc(&B.wave_off, n_wt, stream))) return GNN_ERR_ALLOC;
-    GNN_HIP_TRY(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(TileDesc) * size_t(n_tiles), hipMemcpyHostToDevice, stream));
-    GNN_HIP_TRY(hipMemsetAsync(too_long, 0, 4, stream));
-    tile_parts_kernel<<<row_grid, 256, 0, stream>>>(staged, part_base, n_hot, cap, parts, keys[0], ids[0]);
+    tile_parts_kernel<<<row_grid, 256, 0, stream>>>(staged, part_base, n_hot, parts, keys[0], ids[0]);
     GNN_HIP_TRY(hipGetLastError());
     int where = 0;
     rc = gnn_radix_sort_pairs(keys, ids, n_parts, gnn_ilog2_ceil(int64_t(cap) + 1), table, sums, stream, &where);
@@ -617,12 +654,10 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     GNN_HIP_TRY(hipMemcpyAsync(B.order, ids[where], sizeof(uint32_t) * size_t(n_parts), hipMemcpyDeviceToDevice, stream));
     tile_segments_kernel<<<grid_for(int64_t(n_tiles) * n_parts, 256), 256, 0, stream>>>(d_tiles, n_tiles, rule, B.order, parts, n_parts,
                                                                                     plan->blk_indices, seg);
-    tile_counts_kernel<<<grid_for(n_wt, 256), 256, 0, stream>>>(seg, n_parts, n_tiles, n_waves, rr, rows, B.counts, B.wave_off, too_long);
+    tile_counts_kernel<<<grid_for(n_wt, 256), 256, 0, stream>>>(seg, n_parts, n_tiles, n_waves, rr, rows, B.counts, B.wave_off);
     GNN_HIP_TRY(hipGetLastError());
     std::vector<uint32_t> iters(static_cast<size_t>(n_wt));
-    uint32_t host_too_long = 0;
     GNN_HIP_TRY(hipMemcpyAsync(iters.data(), B.wave_off, sizeof(uint32_t) * size_t(n_wt), hipMemcpyDeviceToHost, stream));
-    GNN_HIP_TRY(hipMemcpyAsync(&host_too_long, too_long, 4, hipMemcpyDeviceToHost, stream));
     GNN_HIP_TRY(hipStreamSynchronize(stream));
     int64_t total = 0;
     B.tile_work.assign(size_t(n_tiles), 0);
@@ -630,7 +665,10 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
         total += iters[size_t(x)];
         B.tile_work[size_t(x % n_tiles)] += iters[size_t(x)];
     }
-    if (host_too_long || total >= int64_t(UINT32_MAX)) return GNN_OK;  // over 1,020 edges of a row into one tile (duplicates): keep the pieces
+    if (total >= int64_t(UINT32_MAX)) return GNN_OK;  // keep the pieces
+    int64_t most_work = 1;
+    for (int64_t x : B.tile_work) most_work = x > most_work ? x : most_work;
+    B.max_groups = int32_t(2 * total / most_work);  // groups are whole tiles: of twice as many none is much longer than that tile
     if ((rc = gnn_scan_exclusive_u32(B.wave_off, n_wt, sums, stream)) != GNN_OK) return rc;
     if (!gnn_dev_alloc(&B.stream, (total + kStreamAhead) * rows * kUnit, stream)) return GNN_ERR_ALLOC;
     tile_fill_kernel<true, false><<<grid_for(n_wt * 64, 256), 256, 0, stream>>>(d_tiles, n_tiles, n_waves, rr, rows, seg, n_parts,
@@ -711,10 +749,12 @@ int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles_in, const float *
 
 // How many groups the tiles are split into: as many as make one round of the compute units (a workgroup takes a whole
 // one).  A second, mostly empty round costs more than idle compute units, which the short rows' launch uses meanwhile
-// (505 K vertices, 14 M edges, F=99: 0.75 ms with 184 workgroups, 0.83 with 276, 0.78 as pieces).
+// (505 K vertices, 14 M edges, F=99: 0.75 ms with 184 workgroups, 0.83 with 276, 0.78 as pieces).  Nor more than the
+// tile with the most work, which no group is shorter than, leaves work for.
 int gnn_tile_groups(const gnn_tiles *t, int n_slices) {
     int64_t g = kComputeUnits / (t->n_row_blocks * n_slices);
     if (g > GNN_TILE_MAX_GROUPS) g = GNN_TILE_MAX_GROUPS;
+    if (g > t->max_groups) g = t->max_groups;
     if (g > t->n_tiles) g = t->n_tiles;
     return g < 1 ? 1 : int(g);
 }

@@ -16,7 +16,7 @@ SLICED = gnn.GNN_FLAG_FORCE_PADDED_COPY
 THRESHOLDS = [4, 32, 256]
 
 
-def _check(el, blocking, f, dtype, op_name, weights, bound, max_slices=8):
+def _check(el, blocking, f, dtype, op_name, weights, bound, max_slices=8, expect_pieces=True):
     bf16 = dtype == torch.bfloat16
     indptr, indices, indptr_t, indices_t, perm = host_csr(el)
     din, dout = np.diff(indptr), np.diff(indptr_t)
@@ -43,7 +43,7 @@ def _check(el, blocking, f, dtype, op_name, weights, bound, max_slices=8):
         torch.cuda.synchronize()
         assert_close(Y, Yo, S, bf16, "fwd")
         assert_close(dX, dXo, St, bf16, "bwd")
-    assert dg.plan_fwd.blocked_sizes()[2] > 0
+    assert (dg.plan_fwd.blocked_sizes()[2] > 0) == expect_pieces
 
 
 @pytest.mark.parametrize("hot_lines,block_lines", [(990, 991), (991, 992), (992, 500), (1983, 2973), (5000, 300)])
@@ -55,10 +55,21 @@ def test_staged_tiles_match_the_oracle(hot_lines, block_lines, dtype, f, op_name
     _check(el, dict(min_degree=32, hot_lines=hot_lines, block_lines=block_lines, max_piece=48, rest_min_count=0), f, dtype, op_name, weights, bound)
 
 
-def test_rows_with_very_many_duplicate_edges_keep_the_pieces():
+def test_rows_with_very_many_edges_into_one_tile_are_cut_into_parts():
     """More than 1,020 edges of one row into one tile do not fit the byte that counts a bundle's units."""
-    el = synth.small_random_multigraph(40, 60000, 5)
-    _check(el, dict(min_degree=32, hot_lines=32, block_lines=8, max_piece=48, rest_min_count=0), 96, torch.float32, "mean", False, False)
+    el = synth.small_random_multigraph(400, 640000, 5)
+    _check(el, dict(min_degree=32, hot_lines=320, block_lines=80, max_piece=48, rest_min_count=0), 96, torch.float32, "mean", False, False)
+
+
+@pytest.mark.parametrize("f,dtype", [(3, torch.float32), (5, torch.float32), (8, torch.float32), (13, torch.float32), (16, torch.float32),
+                                     (29, torch.float32), (9, torch.bfloat16), (25, torch.bfloat16), (64, torch.bfloat16)])
+@pytest.mark.parametrize("op_name,weights,bound", [("mean", False, False), ("sage", False, False), ("sum", True, True), ("sum", True, False)])
+def test_rows_of_at_most_one_line(f, dtype, op_name, weights, bound):
+    """Tables of rows of 16 (no pieces), 32, 64 and 128 bytes: pieces, tiles and finalisation with 2, 4 and 8 lanes per line."""
+    el = synth.rmat_symmetric(5300, 1800000, (0.5, 0.2, 0.2, 0.1), 17)
+    row_bytes = f * (2 if dtype == torch.bfloat16 else 4)
+    _check(el, dict(min_degree=32, hot_lines=1500, block_lines=1000, max_piece=48, rest_min_count=0), f, dtype, op_name, weights, bound,
+           expect_pieces=row_bytes > 16)
 
 
 def test_one_row_far_longer_than_the_others_is_cut_into_parts():

@@ -15,6 +15,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace {
 
 constexpr int kBlockThreads = 256;
@@ -452,6 +454,82 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
     }
 }
 
+// Dot products: the gradient of a scalar edge operand under multiplication, dfE[r(e)] = sum_j dO[v, j] f_V[u, j], for
+// rows of up to 128 columns.  The row of dO stays in registers; C = 2^LC lanes own an edge at a time, S strips of 16 bytes
+// each, and C edges go side by side, so that every lane ends with the sum of one edge (halves are exchanged, then quarters,
+// then eighths: 7 additions for 8 sums where a reduction of each would take 24) and a wavefront stores 64 consecutive ones.
+// Bound by the lines that the L2s deliver, or those behind them.  With a lane per strip the general kernel was bound by
+// its instructions: 16 lanes per edge, four reductions and a reload of dO per four edges.  64 columns: 60 K vertices, 2 M
+// edges 332 -> 34 us (120 G lines/s), 200 K, 20 M 525 -> 287; 133 K, 79 M 2.09 -> 1.68 ms.  Slabs of 32 columns, added to
+// the sums of the slab before, were 9% faster on the last and slower elsewhere.
+constexpr int kDotColumns = 128;
+
+template <int CTRL> __device__ __forceinline__ float exchange(bool upper, float lo, float hi) {  // keep one, add the partner's
+    return (upper ? hi : lo) + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(upper ? lo : hi), CTRL, 0xF, 0xF, true));
+}
+
+template <int LC, int S, bool RAGGED>  // RAGGED: fewer than 4 * C * S columns
+__global__ void __launch_bounds__(kBlockThreads) ap_edge_dot_kernel(const ApArgs a) {
+    constexpr int C = 1 << LC;
+    const Group g = locate_group(a, blockIdx.x);
+    const int lane = threadIdx.x & 63;
+    const int slot0 = lane & ~(C - 1);  // first lane of this edge slot
+    const int64_t row = g.row < 0 ? 0 : g.row;
+    float go[S][4];
+    uint32_t col_bytes[S];
+    bool own[4];  // columns of the last strip that are not the strip's before it (their products would be counted twice)
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int col0 = (s * C + g.c) * 4;
+        const int col = col0 > a.col_end - 4 ? a.col_end - 4 : col0;  // columns before col0 belong to the strip before, or there are none left
+        load_f<4>(a.dO + row * a.ldo + col, go[s]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) own[i] = col + i >= col0;
+        col_bytes[s] = uint32_t(col) * 4u;
+    }
+    const char *fV = reinterpret_cast<const char *>(a.fV);
+    const uint32_t row_bytes = uint32_t(a.ldv) * 4u;
+    // byte offset of the row an edge gathers; edges behind the last one gather row 0, for nothing
+    auto fetch = [&](int64_t e) { return e < g.e1 ? uint32_t(a.indices[e]) * row_bytes : 0u; };
+    uint32_t nxt = fetch(g.e0 + g.lane_in_g);
+    for (int64_t tile = g.e0; __any(tile < g.e1); tile += g.G) {
+        const uint32_t mine = nxt;
+        const int64_t e = tile + g.lane_in_g;
+        float *out = a.out + (a.eid && e < g.e1 ? a.eid[e] : e) * a.lde;
+        nxt = fetch(tile + g.G + g.lane_in_g);
+        float p[C];
+        float x[C][S][4];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const uint32_t off = uint32_t(__shfl(int(mine), slot0 + k));
+#pragma unroll
+            for (int s = 0; s < S; ++s) load_f<4>(reinterpret_cast<const float *>(fV + (off + col_bytes[s])), x[k][s]);
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            float t = 0.0f;
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float next = fmaf(go[s][i], x[k][s][i], t);
+                    t = !RAGGED || s < S - 1 || own[i] ? next : t;
+                }
+            p[k] = t;
+        }
+        if constexpr (C == 8) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[i] = exchange<0x141>(lane & 4, p[i], p[4 + i]);  // lane i of 8 and lane 7 - i
+        }
+        if constexpr (C >= 4) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) p[i] = exchange<0x4E>(lane & 2, p[i], p[2 + i]);
+        }
+        if constexpr (C >= 2) p[0] = exchange<0xB1>(lane & 1, p[0], p[1]);
+        if (e < g.e1) __builtin_nontemporal_store(p[0], out);
+    }
+}
+
 // ------------------------------------------- vertex gradient of max / min
 template <int BIN>
 __global__ void __launch_bounds__(256) ap_scatter_arg_kernel(const int32_t *__restrict__ indices, const int64_t *__restrict__ eid,
@@ -809,9 +887,12 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     if (arg_e && plan && plan->n_edges > INT32_MAX) return GNN_ERR_UNSUPPORTED;
     (void)hipGetLastError();
 
+    const bool masked = arg_e != nullptr;
+    const bool dots = binop == GNN_BIN_MUL && !c.ewide && !masked && d >= 4 && d <= kDotColumns && N * c.ldv * 4 < (int64_t(1) << 32);  // 32-bit offsets
     const int vec = d >= 4 ? 4 : 1;
     const int64_t strips = (d + vec - 1) / vec;
-    const int log2_c = strips >= 64 ? 6 : gnn_ilog2_ceil(strips);
+    int log2_c = strips >= 64 ? 6 : gnn_ilog2_ceil(strips);
+    if (dots && log2_c > 3) log2_c = 3;
 
     ApArgs a{};
     a.indptr = indptr;
@@ -831,7 +912,23 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
     if (blocks == 0) return GNN_OK;
     dim3 grid(static_cast<unsigned>(blocks));
-    const bool masked = arg_e != nullptr;
+    if (dots) {
+        using std::integral_constant;
+        a.col_end = int32_t(d);
+        auto launch = [&](auto lc, auto s) {
+            constexpr int LC = decltype(lc)::value, S = decltype(s)::value;
+            if (d == 4 * S << LC) ap_edge_dot_kernel<LC, S, false><<<grid, kBlockThreads, 0, c.stream>>>(a);
+            else ap_edge_dot_kernel<LC, S, true><<<grid, kBlockThreads, 0, c.stream>>>(a);
+        };
+        if (log2_c == 0) launch(integral_constant<int, 0>(), integral_constant<int, 1>());
+        else if (log2_c == 1) launch(integral_constant<int, 1>(), integral_constant<int, 1>());
+        else if (log2_c == 2) launch(integral_constant<int, 2>(), integral_constant<int, 1>());
+        else if (strips <= 8) launch(integral_constant<int, 3>(), integral_constant<int, 1>());
+        else if (strips <= 16) launch(integral_constant<int, 3>(), integral_constant<int, 2>());
+        else if (strips <= 24) launch(integral_constant<int, 3>(), integral_constant<int, 3>());
+        else launch(integral_constant<int, 3>(), integral_constant<int, 4>());
+        return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
+    }
     switch (binop) {
         case GNN_BIN_ADD: launch_edge_bin<GNN_BIN_ADD>(vec, c.ewide, masked, grid, c.stream, a); break;
         case GNN_BIN_SUB: launch_edge_bin<GNN_BIN_SUB>(vec, c.ewide, masked, grid, c.stream, a); break;

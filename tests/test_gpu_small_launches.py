@@ -112,3 +112,23 @@ def test_column_slices_of_rows_in_place(n, e, f, dtype):
     torch.cuda.synchronize()
     assert_close(Y, Yo, S, dtype == torch.bfloat16, "fwd")
     assert_close(dX, dXo, St, dtype == torch.bfloat16, "bwd")
+
+
+@pytest.mark.parametrize("d", [4, 6, 8, 9, 12, 16, 17, 31, 32, 35, 63, 64, 67, 95, 96, 97, 127, 128, 129])
+def test_dot_products_on_rows_of_every_length(d):
+    """The gradient of a scalar edge operand where its strips per edge and lanes per edge change, with edge ids, and an
+    infinite value that the strips of a ragged row may not count twice."""
+    el = _graph()
+    dg = device_graph(el)
+    fV, dO = synth.normal_features(el.n, d, 3), synth.normal_features(el.n, d, 4)
+    fV[5, d - 2] = float("inf")
+    ids = torch.randperm(el.e, generator=torch.Generator().manual_seed(d))
+    dw = torch.full((el.e + 1,), 7.0, device=DEV)
+    gnn.gnn_ap_bwd_edge(dg.indptr, dg.indices, None, fV.to(DEV), dw[:el.e], dO.to(DEV), dw[:el.e], el.n, d, gnn.GNN_BIN_MUL,
+                        plan=dg.plan_fwd, edge_ids=ids.to(DEV))
+    torch.cuda.synchronize()
+    prod = dO.double()[el.dst.long()] * fV.double()[el.src.long()]
+    got, want = dw[:el.e].cpu().double()[ids], prod.sum(1)
+    finite = torch.isfinite(want)
+    assert torch.equal(got[~finite], want[~finite]) and int((~finite).sum()) > 0
+    assert bool(((got - want).abs()[finite] <= 1e-5 * prod.abs().sum(1)[finite]).all()) and float(dw[el.e]) == 7.0

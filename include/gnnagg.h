@@ -292,6 +292,12 @@ GNN_API int gnn_ap_bwd_vertex(const void *indptr_t, const int32_t *indices_t, co
 GNN_API int gnn_ap_bwd_vertex_arg(const int32_t *indices, const int32_t *arg_e, const float *dO, const float *fE,
                                   float *dfV, int64_t n_vertex_rows, int64_t N, int64_t d, int binop,
                                   const gnn_ap_opts *opts);
+/* The same call told the number of edges (0: unknown), which decides how the additions are made: large
+ * outputs with many edges per row are sorted first (library-owned scratch of up to 2 GB, kept for the
+ * next call; atomics on a stream that is being captured). */
+GNN_API int gnn_ap_bwd_vertex_arg_edges(const int32_t *indices, const int32_t *arg_e, const float *dO, const float *fE,
+                                        float *dfV, int64_t n_vertex_rows, int64_t N, int64_t d, int binop,
+                                        int64_t n_edges, const gnn_ap_opts *opts);
 
 /* Gradient with respect to f_E, one output row per edge (the sampled dense-dense product of
  * Section 2.2 when edge_width = 1 and binop = mul: dfE[e] = <dO[v, :], f_V[u, :]>):

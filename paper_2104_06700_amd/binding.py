@@ -42,7 +42,7 @@ EXPORTED_SYMBOLS = (
     "gnn_graph_build", "gnn_release_cached_memory",
     "gnn_plan_sizes", "gnn_plan_export", "gnn_plan_gather_share", "gnn_plan_workspace_bytes", "gnn_plan_reserve",
     "gnn_plan_prepare", "gnn_plan_set_blocking", "gnn_plan_bind_edge_weights", "gnn_plan_blocked_sizes", "gnn_plan_export_blocked",
-    "gnn_ap_fwd", "gnn_ap_bwd_vertex", "gnn_ap_bwd_vertex_arg", "gnn_ap_bwd_edge",
+    "gnn_ap_fwd", "gnn_ap_bwd_vertex", "gnn_ap_bwd_vertex_arg", "gnn_ap_bwd_vertex_arg_edges", "gnn_ap_bwd_edge",
     "gnn_matmul", "gnn_matmul_workspace_bytes",
     "gnn_sage_layer_fwd", "gnn_sage_layer_bwd", "gnn_sage_layer_saved_elems", "gnn_sage_layer_workspace_bytes",
     "gnn_status_string", "gnn_calib_copy", "gnn_calib_gather",
@@ -144,6 +144,7 @@ def load_library() -> ctypes.CDLL:
         lib.gnn_ap_fwd.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i32, i32, ap]
         lib.gnn_ap_bwd_vertex.argtypes = [vp, vp, vp, vp, vp, i64, i64, i32, ap]
         lib.gnn_ap_bwd_vertex_arg.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, i32, ap]
+        lib.gnn_ap_bwd_vertex_arg_edges.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, i32, i64, ap]
         lib.gnn_ap_bwd_edge.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i64, i32, ap]
         lib.gnn_matmul.argtypes = [vp, i64, i32, vp, i64, i32, vp, i64, i64, i64, i64, vp, i32, vp, i64, vp]
         lib.gnn_matmul_workspace_bytes.argtypes = [i64, i64, i64]
@@ -170,7 +171,7 @@ def _connect_calls(lib) -> None:
         from . import _pycall
     except ImportError as err:
         raise ImportError("the extension module _pycall is missing: run `python -c 'import __graft_entry__ as g; g.build()'`") from err
-    names = ("gnn_aggregate_fwd", "gnn_aggregate_bwd", "gnn_ap_fwd", "gnn_ap_bwd_vertex", "gnn_ap_bwd_vertex_arg",
+    names = ("gnn_aggregate_fwd", "gnn_aggregate_bwd", "gnn_ap_fwd", "gnn_ap_bwd_vertex", "gnn_ap_bwd_vertex_arg_edges",
              "gnn_ap_bwd_edge", "gnn_sage_layer_fwd", "gnn_sage_layer_bwd")
     _pycall.connect({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names}, torch)
     _calls = _pycall

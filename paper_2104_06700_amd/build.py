@@ -15,7 +15,7 @@ LIB = os.path.join(PKG, "libgnnagg.so")
 PYCALL = os.path.join(PKG, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJ_DIR = os.path.join(PKG, "_build")
 
-SOURCES = ["aggregate.hip", "blocked.hip", "tiles.hip", "ap.hip", "gemm.hip", "layer.hip", "plan.hip", "graph.hip", "pool.hip", "util.hip"]
+SOURCES = ["aggregate.hip", "blocked.hip", "tiles.hip", "ap.hip", "winners.hip", "gemm.hip", "layer.hip", "plan.hip", "graph.hip", "pool.hip", "util.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",

@@ -844,6 +844,12 @@ extern "C" GNN_API int gnn_ap_bwd_vertex(const void *indptr_t, const int32_t *in
 extern "C" GNN_API int gnn_ap_bwd_vertex_arg(const int32_t *indices, const int32_t *arg_e, const float *dO, const float *fE,
                                              float *dfV, int64_t n_vertex_rows, int64_t N, int64_t d, int binop,
                                              const gnn_ap_opts *opts) {
+    return gnn_ap_bwd_vertex_arg_edges(indices, arg_e, dO, fE, dfV, n_vertex_rows, N, d, binop, 0, opts);
+}
+
+extern "C" GNN_API int gnn_ap_bwd_vertex_arg_edges(const int32_t *indices, const int32_t *arg_e, const float *dO, const float *fE,
+                                                   float *dfV, int64_t n_vertex_rows, int64_t N, int64_t d, int binop,
+                                                   int64_t n_edges, const gnn_ap_opts *opts) {
     Common c;
     gnn_ap_opts o{};
     if (opts) o = *opts;
@@ -854,10 +860,14 @@ extern "C" GNN_API int gnn_ap_bwd_vertex_arg(const int32_t *indices, const int32
     if (d == 0) return GNN_OK;
     if (!dfV || !aligned4(dfV)) return GNN_ERR_INVALID_ARG;
     (void)hipGetLastError();
+    const bool need_y = binop == GNN_BIN_MUL || binop == GNN_BIN_DIV;
+    if (binop != GNN_BIN_COPY_RHS && indices && arg_e && dO && (fE || !need_y) && gnn_winners_apply(n_edges, n_vertex_rows, N, d)) {
+        rc = gnn_scatter_winners(indices, c.o.edge_ids, arg_e, dO, c.ldo, fE, c.lde, c.ewide, dfV, c.ldv, n_vertex_rows, N, d, binop, c.stream);
+        if (rc != GNN_ERR_ALLOC) return rc;
+    }
     if (n_vertex_rows > 0) fill_rows_kernel<<<grid_1d(n_vertex_rows * d), 256, 0, c.stream>>>(dfV, c.ldv, n_vertex_rows, int(d), 0.0f);
     if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     if (N == 0 || binop == GNN_BIN_COPY_RHS) return GNN_OK;
-    const bool need_y = binop == GNN_BIN_MUL || binop == GNN_BIN_DIV;
     if (!indices || !arg_e || !dO || (need_y && !fE)) return GNN_ERR_INVALID_ARG;
     const unsigned grid = grid_1d(N * d);
     const int ew = c.ewide ? 1 : 0;

@@ -229,6 +229,12 @@ int gnn_radix_sort_pairs(uint32_t *buf_k[2], uint32_t *buf_v[2], int64_t n, int 
                          hipStream_t stream, int *out);
 int64_t gnn_sort_table_elems(int64_t n);
 int64_t gnn_sort_sums_elems(int64_t n);
+// Vertex gradient of max / min by sorting instead of global atomics (winners.hip): does it apply, and the call.  Writes all of
+// `out`; GNN_ERR_ALLOC (nothing launched): no workspace, or the stream is being captured.
+bool gnn_winners_apply(int64_t n_edges, int64_t n_out, int64_t N, int64_t d);
+int gnn_scatter_winners(const int32_t *indices, const int64_t *eid, const int32_t *arg, const float *dO, int64_t ldo, const float *fE,
+                        int64_t lde, bool ewide, float *out, int64_t ldv, int64_t n_out, int64_t N, int64_t d, int binop,
+                        hipStream_t stream);
 // In-place exclusive prefix sums; sums: scratch of gnn_scan_sums_elems(n) elements per array.  The 64-bit form scans n_arrays
 // arrays `stride` elements apart and writes each one's total behind it.
 int gnn_scan_exclusive_u32(uint32_t *data, int64_t n, uint32_t *sums, hipStream_t stream);

@@ -20,8 +20,8 @@
 
 namespace {
 
-constexpr size_t kMaxIdleBytes = size_t(1) << 30;
-constexpr size_t kMaxBlock = size_t(256) << 20;
+constexpr size_t kMaxIdleBytes = size_t(2) << 30;
+constexpr size_t kMaxBlock = size_t(512) << 20;
 constexpr uint64_t kMaxAge = 4096;
 constexpr size_t kHostBlock = GNN_HOST_BLOCK_BYTES;
 constexpr size_t kMaxHostBlocks = 16;

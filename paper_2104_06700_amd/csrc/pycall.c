@@ -19,7 +19,7 @@ static __typeof__(&gnn_aggregate_fwd) fn_aggregate_fwd;
 static __typeof__(&gnn_aggregate_bwd) fn_aggregate_bwd;
 static __typeof__(&gnn_ap_fwd) fn_ap_fwd;
 static __typeof__(&gnn_ap_bwd_vertex) fn_ap_bwd_vertex;
-static __typeof__(&gnn_ap_bwd_vertex_arg) fn_ap_bwd_vertex_arg;
+static __typeof__(&gnn_ap_bwd_vertex_arg_edges) fn_ap_bwd_vertex_arg;
 static __typeof__(&gnn_ap_bwd_edge) fn_ap_bwd_edge;
 static __typeof__(&gnn_sage_layer_fwd) fn_sage_layer_fwd;
 static __typeof__(&gnn_sage_layer_bwd) fn_sage_layer_bwd;
@@ -331,9 +331,11 @@ static PyObject *ap_bwd_vertex_arg(PyObject *self, PyObject *const *a, Py_ssize_
         matrix(a[3], 1, &fE, &o.lde, &e_dims) || matrix(a[4], 1, &dfV, &o.ldv, NULL) || any_ptr(a[0], &indices) ||
         any_ptr(a[1], &arg) || ap_options(&o, NULL, Py_None, a[10], a[9], a[3], e_dims, d))
         return NULL;
+    int64_t edges[2] = {0, 0}; /* a hint: unknown where the argument is no tensor */
+    if (a[0] != Py_None && size_of(a[0], edges)) { PyErr_Clear(); edges[0] = 0; }
     int status;
     Py_BEGIN_ALLOW_THREADS
-    status = fn_ap_bwd_vertex_arg(indices, arg, dO, fE, dfV, rows, N, d, binop, &o);
+    status = fn_ap_bwd_vertex_arg(indices, arg, dO, fE, dfV, rows, N, d, binop, edges[0], &o);
     Py_END_ALLOW_THREADS
     return PyLong_FromLong(status);
 }
@@ -419,7 +421,7 @@ static PyObject *connect(PyObject *self, PyObject *args) {
     const struct { const char *name; void **fn; } fns[] = {
         {"gnn_aggregate_fwd", (void **)&fn_aggregate_fwd}, {"gnn_aggregate_bwd", (void **)&fn_aggregate_bwd},
         {"gnn_ap_fwd", (void **)&fn_ap_fwd}, {"gnn_ap_bwd_vertex", (void **)&fn_ap_bwd_vertex},
-        {"gnn_ap_bwd_vertex_arg", (void **)&fn_ap_bwd_vertex_arg}, {"gnn_ap_bwd_edge", (void **)&fn_ap_bwd_edge},
+        {"gnn_ap_bwd_vertex_arg_edges", (void **)&fn_ap_bwd_vertex_arg}, {"gnn_ap_bwd_edge", (void **)&fn_ap_bwd_edge},
         {"gnn_sage_layer_fwd", (void **)&fn_sage_layer_fwd}, {"gnn_sage_layer_bwd", (void **)&fn_sage_layer_bwd}};
     const struct { const char *name; PyObject **slot; } attrs[] = {
         {"float32", &dtype_f32}, {"bfloat16", &dtype_bf16}, {"int32", &dtype_i32}, {"int64", &dtype_i64}};

@@ -397,3 +397,31 @@ def test_winner_scatter_spread_between_runs_is_bounded():
     assert bool((spread[k <= 1] == 0).all())        # a single term is exact whatever the order
     print(f"winner scatter: largest spread between five runs {float(spread.max()):.3e} "
           f"({float((spread / S.clamp(min=1e-30)).max()):.2e} of the magnitude sum)")
+
+
+@pytest.mark.parametrize("d", [3, 4, 61, 128])
+@pytest.mark.parametrize("binop", [gnn.GNN_BIN_COPY_LHS, gnn.GNN_BIN_MUL])
+def test_sorted_winner_scatter(d, binop):
+    """Outputs large enough for the winners to be sorted by ranges of vertices: columns that do not fill a quad, more quads
+    than a round takes, rows without edges, an output with rows no edge names, strides, a vertex that wins every row (its
+    range is cut into pieces)."""
+    n = max((1 << 22) // d, 1 << 17) + 4077
+    k = 16
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    rows = n - 3000  # the last rows have no edges
+    indices = torch.randint(0, n - 100, (n * k,), dtype=torch.int32, device=DEV, generator=gen)
+    arg = torch.arange(rows, device=DEV).view(-1, 1) * k + torch.randint(0, k, (rows, d), device=DEV, generator=gen)
+    arg = torch.cat([arg, torch.full((n - rows, d), -1, device=DEV)]).to(torch.int32)
+    indices[arg[:rows, d - 1].long()] = 4099
+    dO = torch.randn(n, d + 1, device=DEV, generator=gen)[:, :d]
+    fE = torch.rand(n * k, device=DEV, generator=gen) + 0.5 if binop == gnn.GNN_BIN_MUL else None
+    dfV = torch.full((n, d + 3), 7.0, device=DEV)
+    gnn.gnn_ap_bwd_vertex_arg(indices, arg, dO, fE, dfV[:, :d], n, n, d, binop)
+    torch.cuda.synchronize()
+    arg, indices, dO, dfV = arg.cpu(), indices.cpu(), dO.cpu(), dfV.cpu()
+    e = arg[:rows].long()
+    terms = dO[:rows].double() * (fE.cpu().double()[e] if fE is not None else 1.0)
+    flat = (indices.long()[e] * d + torch.arange(d)).view(-1).numpy()
+    want, size = (torch.from_numpy(np.bincount(flat, x.reshape(-1).numpy(), n * d)).view(n, d) for x in (terms, terms.abs()))
+    assert bool(((dfV[:, :d].double() - want).abs() <= 2e-5 * size).all())
+    assert bool((dfV[:, d:] == 7.0).all())

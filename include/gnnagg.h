@@ -464,7 +464,10 @@ GNN_API int gnn_plan_reserve(gnn_plan *plan, int64_t F);
  * gather count, a short last line kept in a dense table of its own); and the index copy that goes
  * with it (4 bytes per edge + 12 per vertex: source ids mapped to their rank, edge lists in the
  * plan's row order), or -- where no copy of the matrix is made but column slices are used on a
- * large power-law graph -- the index copy with the cold sources flagged.  `indices` is the index
+ * large power-law graph -- the index copy with the cold sources flagged.  That is reserved for calls
+ * without edge weights, with the weights bound to the plan at this moment and with any others (which
+ * may choose another layout each), on dense matrices (row stride F) at 128-byte boundaries, without
+ * flags.  `indices` is the index
  * array of the plan's graph, and the row pointers the plan was created from must still be alive.
  * backward: 0 for gnn_aggregate_fwd, 1 for gnn_aggregate_bwd. */
 GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, int op, int backward, int64_t F,

@@ -1099,9 +1099,8 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     // small next to the E*F gather, buys 16-byte loads and the XCD column slices below.
     int64_t ldg = ldx;  // row stride of the matrix the kernel gathers from
     bool padded = false;
-    // explicit weights keep a plan that blocks by itself on the path without pieces unless they are bound to it
-    const bool blocks_expected = plan && !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS) && gnn_plan_blocks_expected(plan, int(esz)) &&
-                                 (!w || w == plan->bound_w || plan->blocking.min_degree > 0);
+    const gnn_weight_kind weights = gnn_weight_kind_of(plan, w);
+    const bool blocks_expected = !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS) && gnn_call_blocks_expected(plan, esz, weights);
     const gnn_layout layout = gnn_choose_layout(plan, N, F, esz, ldx, reinterpret_cast<uintptr_t>(gathered) % 128 == 0,
                                                 o.flags, o.max_slices, /*allow_tail=*/o.max_slices != 1,
                                                 /*scaled_source=*/src_mode != kScaleNone, blocks_expected, /*weights=*/w != nullptr);
@@ -1309,22 +1308,12 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     if (padded && lanes > 0 && rank_indices && !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS)) {
         int rc = gnn_plan_blocked(plan, indptr, stream, &bl);
         if (rc != GNN_OK) return rc;
-        // Explicit weights sit in CSR order, the pieces in rank order: every edge would cost a random 4-byte
-        // read (measured: 1.44 -> 3.67 ms on the weighted workload at F=64), so such calls keep the plain
-        // path unless the plan's blocking was asked for explicitly, or the weights were bound to the plan
-        // (gnn_plan_bind_edge_weights), which then holds a copy of them in piece order.  The plan's own
-        // per-edge factors get such a copy too.
-        const bool bound = w && w == plan->bound_w;
-        if (bl.active && w && bl.automatic && !bound) bl.active = false;
-        // bf16 pieces write partial lines twice as large as the lines they gather: on graphs of a few
-        // L2s' worth of vertices that eats the gain (233 K vertices, F=256 backward 3.95 -> 4.07 ms;
-        // 133 K vertices, F=128 1.16 -> 1.25), on the 2.45 M-vertex graph it does not (F=512 12.9 -> 11.6).
-        if (bl.active && esz == 2 && bl.automatic && N < 8 * int64_t(32768)) bl.active = false;
+        bl.active = bl.active && blocks_expected;
         if (bl.active && edge_scale) {
             rc = gnn_plan_blocked_edge_scale(plan, src_mode, stream, &scale_blk);
             if (rc != GNN_OK) return rc;
         }
-        if (bl.active && bound) {
+        if (bl.active && weights == GNN_WEIGHTS_BOUND) {
             rc = gnn_plan_blocked_bound_weights(plan, stream, &w_blk);
             if (rc != GNN_OK) return rc;
         }
@@ -1338,7 +1327,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         if (rc != GNN_OK) return rc;
         if (tl) {
             if (coef) {
-                rc = gnn_plan_tile_coefs(plan, tl, w, edge_scale, src_mode, w && w == plan->bound_w, stream, &tile_coefs);
+                rc = gnn_plan_tile_coefs(plan, tl, w, edge_scale, src_mode, weights == GNN_WEIGHTS_BOUND, stream, &tile_coefs);
                 if (rc != GNN_OK) return rc;
             }
             rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), lanes * max_vec);

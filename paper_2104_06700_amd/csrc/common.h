@@ -295,6 +295,9 @@ struct gnn_layout {
 static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz) {
     if (!plan || plan->n_edges <= 0 || plan->n_edges >= int64_t(INT32_MAX)) return false;
     const bool automatic = plan->blocking.min_degree == 0;
+    // bf16 pieces write partial lines twice as large as the lines they gather: on graphs of a few L2s' worth of vertices
+    // that eats the gain (233 K vertices, F=256 backward 3.95 -> 4.07 ms; 133 K vertices, F=128 1.16 -> 1.25), on the
+    // 2.45 M-vertex graph it does not (F=512 12.9 -> 11.6).
     if (esz == 2 && automatic && plan->n_rows < 8 * int64_t(32768)) return false;
     if (plan->blk_decided) return plan->blk_n_pieces > 0;
     if (plan->blocking.min_degree < 0) return false;
@@ -307,6 +310,18 @@ static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz) {
     for (int b = first_bin; b < plan->n_bins; ++b) long_edges += plan->bin_edges[b];
     if (long_edges <= 0) return false;
     return !automatic || (plan->n_rows >= 4 * int64_t(32768) && long_edges * 4 >= plan->n_edges);
+}
+
+// The edge weights of a call.  BOUND: the array of gnn_plan_bind_edge_weights; FREE: any other.
+enum gnn_weight_kind { GNN_WEIGHTS_NONE = 0, GNN_WEIGHTS_BOUND = 1, GNN_WEIGHTS_FREE = 2 };
+static inline gnn_weight_kind gnn_weight_kind_of(const gnn_plan *plan, const float *w) {
+    return !w ? GNN_WEIGHTS_NONE : (plan && w == plan->bound_w ? GNN_WEIGHTS_BOUND : GNN_WEIGHTS_FREE);
+}
+// Will a call with such weights serve its long rows as pieces?  FREE weights sit in CSR order, the pieces in rank order, so
+// every edge would cost a random 4-byte read (1.44 -> 3.67 ms on the weighted workload at F=64): such calls keep the path
+// without pieces unless the plan's blocking was asked for explicitly.
+static inline bool gnn_call_blocks_expected(const gnn_plan *plan, int esz, gnn_weight_kind weights) {
+    return plan && gnn_plan_blocks_expected(plan, esz) && (weights != GNN_WEIGHTS_FREE || plan->blocking.min_degree > 0);
 }
 
 static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int64_t F, int esz, int64_t ldx,

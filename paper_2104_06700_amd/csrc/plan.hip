@@ -528,65 +528,65 @@ int gnn_plan_padded(gnn_plan *plan, int64_t bytes) {
     return GNN_OK;
 }
 
+// What a hot call with edge weights of this kind takes (run_aggregate of aggregate.hip, on a dense matrix at a line boundary:
+// ld = F), except for the per-edge factors `mode` (0: none).
+static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int64_t F, int esz, gnn_weight_kind weights, hipStream_t stream) {
+    const bool blocks = gnn_call_blocks_expected(plan, esz, weights);
+    const gnn_layout layout = gnn_choose_layout(plan, plan->n_rows, F, esz, F, true, 0, 0, /*allow_tail=*/true, /*scaled_source=*/mode != 0,
+                                                blocks, weights != GNN_WEIGHTS_NONE);
+    if (!layout.padded_copy) {
+        if (!layout.slices_wanted) return GNN_OK;
+        const int32_t *unused_idx = nullptr;  // the flagged index copy of the cold hints, where they pay
+        return gnn_plan_cold_indices(plan, indices, false, stream, &unused_idx);
+    }
+    int rc = gnn_plan_padded(plan, layout.bytes);
+    if (rc != GNN_OK) return rc;
+    gnn_rank_layout unused_rank{};  // built from the row pointers the plan was created from
+    rc = gnn_plan_rank_indices(plan, plan->indptr_seen, indices, false, stream, &unused_rank);
+    if (rc != GNN_OK || layout.line_lanes == 0) return rc;
+    // the long rows as source-blocked pieces, their partial sums, and the part of them that is staged in LDS
+    gnn_blocked_layout bl{};
+    rc = gnn_plan_blocked(plan, plan->indptr_seen, stream, &bl);
+    if (rc != GNN_OK || !blocks) return rc;
+    if (!bl.active) return prepare_layout(plan, indices, mode, F, esz, weights, stream);  // decided now: the calls expect none
+    const int line_floats = layout.line_lanes * (16 / esz);
+    int slices = 1;
+    while (slices < 8 && slices * 2 <= layout.main_lines) slices *= 2;
+    rc = gnn_plan_blocked_partial(plan, slices, line_floats);
+    if (rc != GNN_OK) return rc;
+    const gnn_tiles *tl = nullptr;
+    rc = gnn_plan_tiles(plan, layout.line_lanes, esz == 2, stream, &tl);
+    if (rc == GNN_OK && tl) rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), line_floats);
+    const float *unused = nullptr;
+    if (rc == GNN_OK && weights == GNN_WEIGHTS_BOUND) rc = gnn_plan_blocked_bound_weights(plan, stream, &unused);
+    if (rc != GNN_OK || !tl || weights != GNN_WEIGHTS_BOUND) return rc;
+    return gnn_plan_tile_coefs(plan, tl, plan->bound_w, nullptr, 0, true, stream, &unused);
+}
+
 extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, int op, int backward, int64_t F,
-                                        int dtype, void *stream) {
+                                        int dtype, void *stream_v) {
     if (!plan || F < 0 || op < GNN_SUM || op > GNN_SAGE_GCN) return GNN_ERR_INVALID_ARG;
     if (dtype != GNN_F32 && dtype != GNN_BF16) return GNN_ERR_INVALID_ARG;
+    hipStream_t stream = static_cast<hipStream_t>(stream_v);
     int rc = gnn_plan_reserve(plan, F);
-    if (rc != GNN_OK) return rc;
     const int esz = dtype == GNN_BF16 ? 2 : 4;
-    {   // the padded copy a hot call on a dense, line-aligned matrix (ld = F) would use, if any
-        // (a weight-less GCN call is assumed: with explicit weights the rows carry no factor)
-        const bool scaled_source = ((op == GNN_MEAN || op == GNN_SAGE_GCN) && backward) || op == GNN_GCN_SYM;
-        const gnn_layout layout = gnn_choose_layout(plan, plan->n_rows, F, esz, F, true, 0, 0, /*allow_tail=*/true, scaled_source,
-                                                    gnn_plan_blocks_expected(plan, esz), plan->bound_w != nullptr);
-        if (layout.padded_copy) {
-            rc = gnn_plan_padded(plan, layout.bytes);
-            if (rc != GNN_OK) return rc;
-            gnn_rank_layout unused{};  // built from the row pointers the plan was created from
-            rc = gnn_plan_rank_indices(plan, plan->indptr_seen, indices, false, static_cast<hipStream_t>(stream), &unused);
-            if (rc != GNN_OK) return rc;
-            if (layout.line_lanes > 0) {  // the long rows as source-blocked pieces, and their partial sums
-                const int line_floats = layout.line_lanes * (16 / esz);
-                gnn_blocked_layout bl{};
-                rc = gnn_plan_blocked(plan, plan->indptr_seen, static_cast<hipStream_t>(stream), &bl);
-                if (rc != GNN_OK) return rc;
-                if (bl.active) {
-                    int slices = 1;
-                    while (slices < 8 && slices * 2 <= layout.main_lines) slices *= 2;
-                    rc = gnn_plan_blocked_partial(plan, slices, line_floats);
-                    if (rc != GNN_OK) return rc;
-                    const gnn_tiles *tl = nullptr;  // and the part of them that is staged in LDS
-                    rc = gnn_plan_tiles(plan, layout.line_lanes, esz == 2, static_cast<hipStream_t>(stream), &tl);
-                    if (rc != GNN_OK) return rc;
-                    if (tl) {
-                        rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), line_floats);
-                        if (rc != GNN_OK) return rc;
-                    }
-                    if (plan->bound_w) {
-                        const float *unused_w = nullptr;
-                        rc = gnn_plan_blocked_bound_weights(plan, static_cast<hipStream_t>(stream), &unused_w);
-                        if (rc == GNN_OK && tl) rc = gnn_plan_tile_coefs(plan, tl, plan->bound_w, nullptr, 0, true, static_cast<hipStream_t>(stream), &unused_w);
-                        if (rc != GNN_OK) return rc;
-                    }
-                }
-            }
-        } else if (layout.slices_wanted) {  // the flagged index copy of the cold hints, where they pay
-            const int32_t *unused_idx = nullptr;
-            rc = gnn_plan_cold_indices(plan, indices, false, static_cast<hipStream_t>(stream), &unused_idx);
-            if (rc != GNN_OK) return rc;
-        }
-    }
-    const float *unused = nullptr;
     const int mode = (op == GNN_MEAN && backward) ? 1 : (op == GNN_GCN_SYM ? 2 : ((op == GNN_SAGE_GCN && backward) ? 3 : 0));
+    // Calls may come without weights, with the bound ones or with others, and what these choose differs.  Under GCN_SYM the
+    // weights take the place of the factors.
+    const int weighted_mode = op == GNN_GCN_SYM ? 0 : mode;
+    if (rc == GNN_OK) rc = prepare_layout(plan, indices, mode, F, esz, GNN_WEIGHTS_NONE, stream);
+    if (rc == GNN_OK && plan->bound_w) rc = prepare_layout(plan, indices, weighted_mode, F, esz, GNN_WEIGHTS_BOUND, stream);
+    if (rc == GNN_OK) rc = prepare_layout(plan, indices, weighted_mode, F, esz, GNN_WEIGHTS_FREE, stream);
+    if (rc != GNN_OK) return rc;
+    const float *unused = nullptr;
     if (mode) {
-        rc = gnn_plan_edge_scale(plan, indices, mode, static_cast<hipStream_t>(stream), &unused);
+        rc = gnn_plan_edge_scale(plan, indices, mode, stream, &unused);
         // ... and in the order of the source-blocked pieces, for the calls that read it there
         if (rc == GNN_OK && plan->blk_decided && plan->blk_n_pieces > 0 && plan->n_edges > 0)
-            rc = gnn_plan_blocked_edge_scale(plan, mode, static_cast<hipStream_t>(stream), &unused);
+            rc = gnn_plan_blocked_edge_scale(plan, mode, stream, &unused);
         for (const gnn_tiles &t : plan->tiles)
             if (rc == GNN_OK && t.active && plan->n_edges > 0)
-                rc = gnn_plan_tile_coefs(plan, &t, nullptr, plan->edge_scale[mode - 1], mode, false, static_cast<hipStream_t>(stream), &unused);
+                rc = gnn_plan_tile_coefs(plan, &t, nullptr, plan->edge_scale[mode - 1], mode, false, stream, &unused);
     }
     return rc;
 }

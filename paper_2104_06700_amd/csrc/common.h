@@ -175,6 +175,8 @@ void gnn_tiles_free(gnn_tiles &t);
 // Coefficients w[e] * scale[e] (either may be null; CSR order) in stream order.
 int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles, const float *w, const float *scale, int scale_mode, bool bound,
                         hipStream_t stream, const float **out);
+// Room for coefficients that every call fills anew: those of FREE weights, and products of weights and factors.
+int gnn_plan_tile_coef_room(gnn_plan *plan, const gnn_tiles *tiles, hipStream_t stream);
 // Groups a launch over n_slices column slices splits the tiles into, each with a partial line of its own per row.
 int gnn_tile_groups(const gnn_tiles *t, int n_slices);
 // Makes plan->tile_partial large enough for such a launch.

@@ -559,8 +559,10 @@ static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int6
     if (rc == GNN_OK && tl) rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), line_floats);
     const float *unused = nullptr;
     if (rc == GNN_OK && weights == GNN_WEIGHTS_BOUND) rc = gnn_plan_blocked_bound_weights(plan, stream, &unused);
-    if (rc != GNN_OK || !tl || weights != GNN_WEIGHTS_BOUND) return rc;
-    return gnn_plan_tile_coefs(plan, tl, plan->bound_w, nullptr, 0, true, stream, &unused);
+    if (rc != GNN_OK || !tl || weights == GNN_WEIGHTS_NONE) return rc;
+    // bound weights have a copy in stream order, unless they are multiplied by a factor that the table does not hold (bf16)
+    if (weights == GNN_WEIGHTS_BOUND && (mode == 0 || esz == 4)) return gnn_plan_tile_coefs(plan, tl, plan->bound_w, nullptr, 0, true, stream, &unused);
+    return gnn_plan_tile_coef_room(plan, tl, stream);
 }
 
 extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, int op, int backward, int64_t F,

@@ -717,6 +717,21 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, hipStream_t stream, con
     return GNN_OK;
 }
 
+namespace {
+
+int coef_room(const gnn_tiles &L, float **slot, hipStream_t stream) {
+    if (*slot) return GNN_OK;
+    (void)hipGetLastError();
+    return gnn_dev_alloc(slot, (L.n_iters + kStreamAhead) * (64 / L.lanes) * kUnit, stream) ? GNN_OK : GNN_ERR_ALLOC;
+}
+
+}  // namespace
+
+int gnn_plan_tile_coef_room(gnn_plan *plan, const gnn_tiles *tiles, hipStream_t stream) {
+    gnn_tiles &L = plan->tiles[tiles - plan->tiles];
+    return coef_room(L, &L.tmp_w, stream);
+}
+
 // Coefficients of the edges in stream order.  Kept: the plan's own factors, and weights bound to the plan; anything
 // else is gathered anew by every call.
 int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles_in, const float *w, const float *scale, int scale_mode, bool bound,
@@ -732,10 +747,8 @@ int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles_in, const float *
         fill = !*slot || L.bound_version != plan->bound_w_version;
     }
     const int rows = 64 / L.lanes;
-    if (!*slot) {
-        (void)hipGetLastError();
-        if (!gnn_dev_alloc(slot, (L.n_iters + kStreamAhead) * rows * kUnit, stream)) return GNN_ERR_ALLOC;
-    }
+    const int rc = coef_room(L, slot, stream);
+    if (rc != GNN_OK) return rc;
     if (fill) {
         tile_fill_kernel<false, true><<<grid_for(L.n_waves * L.n_tiles * 64, 256), 256, 0, stream>>>(
             static_cast<const TileDesc *>(L.tiles), L.n_tiles, L.n_waves, L.rr, rows, static_cast<const uint2 *>(L.seg), L.n_parts, L.counts, L.wave_off,

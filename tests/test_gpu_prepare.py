@@ -10,10 +10,11 @@ pytestmark = pytest.mark.gpu
 
 
 # the sizes lie where calls with and without weights choose differently: a copy for coefficients only, in rows of several lines
-# and of one; a copy only without them, and hints for cold sources with them
+# and of one; a copy only without them, and hints for cold sources with them; pieces asked for, whose tiles take coefficients
 CASES = [
     dict(n=100000, e=6000000, f=100), dict(n=60000, e=6000000, f=100, op=gnn.GNN_MEAN), dict(n=200000, e=8000000, f=20),
-    dict(n=1400000, e=33000000, f=64),
+    dict(n=1400000, e=33000000, f=64), dict(n=20000, e=4000000, f=512, blocking=dict(min_degree=32)),
+    dict(n=20000, e=4000000, f=1000, blocking=dict(min_degree=32), dtype=torch.bfloat16, op=gnn.GNN_MEAN, backward=True, bound=True),
     dict(n=150000, e=30000000, f=20, bound=True),
 ]
 

@@ -189,6 +189,9 @@ int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice
 // Device memory that is kept for the next plan (pool.hip).  With a stream: for memory that is first used there; fails on a
 // stream that is being captured.  gnn_dev_free: any stream may still use the block (as with hipFree, but without waiting);
 // gnn_dev_free_on: its last use is ordered on that stream.
+// Blocks of more than GNN_POOL_MAX_BLOCK bytes are not kept: they come from the driver and go back to it, which waits for the
+// device, so the scratch of an asynchronous call is cut into blocks that are no larger.
+constexpr int64_t GNN_POOL_MAX_BLOCK = int64_t(512) << 20;
 int gnn_dev_alloc_bytes(void **p, size_t bytes, hipStream_t stream);
 int gnn_dev_alloc_bytes(void **p, size_t bytes);
 void gnn_dev_free(void *p);

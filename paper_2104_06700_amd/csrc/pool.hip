@@ -21,7 +21,7 @@
 namespace {
 
 constexpr size_t kMaxIdleBytes = size_t(2) << 30;
-constexpr size_t kMaxBlock = size_t(512) << 20;
+constexpr size_t kMaxBlock = size_t(GNN_POOL_MAX_BLOCK);
 constexpr uint64_t kMaxAge = 4096;
 constexpr size_t kHostBlock = GNN_HOST_BLOCK_BYTES;
 constexpr size_t kMaxHostBlocks = 16;

@@ -27,7 +27,9 @@ constexpr int kMaxRangeLog2 = 13, kMinRangeLog2 = 9;
 constexpr int kAddThreads = 1024;
 constexpr uint32_t kPiecePairs = 1u << 17;
 constexpr int kMaxQuads = 16;                  // quads per round; every round reads the indices again
-constexpr int64_t kMaxRoundBytes = int64_t(15) << 27;
+// Bytes per vertex and quad of the largest arrays of a round.  A round takes as many quads as keep them within a block of the
+// pool (2,449,029 vertices, 112 columns, arrays of 523 MiB from the driver: 5.6 ms, in which the host waits; of 374 MiB: 4.8).
+constexpr int64_t kQuadBytes = 4 * sizeof(float);
 
 struct Round {
     int64_t N, n_out;
@@ -314,9 +316,9 @@ __global__ void __launch_bounds__(kAddThreads) add_kernel(const Round r, float *
 // edges each, 128 columns: 2.2 ms against 4.2), and small outputs stay in the caches (150 K vertices, 13 edges each, 32
 // columns: 0.100 ms against 0.121).  Otherwise, atomics -> sorted: 150 K, 13 edges, 64 columns 0.19 -> 0.16 ms; 400 K, 50
 // edges, 16 columns 0.27 -> 0.17, 64 columns 0.65 -> 0.41; 1 M, 20 edges, 128 columns 2.67 -> 1.96; 2.4 M, 50 edges, 100
-// columns 4.95 -> 4.15.
+// columns 4.95 -> 4.15.  Never where the arrays of one quad would not fit a block of the pool.
 bool gnn_winners_apply(int64_t n_edges, int64_t n_out, int64_t N, int64_t d) {
-    if (n_out <= 0 || n_out > int64_t(kMaxRanges) << kMaxRangeLog2 || N > INT32_MAX / 16) return false;
+    if (n_out <= 0 || n_out > int64_t(kMaxRanges) << kMaxRangeLog2 || N > GNN_POOL_MAX_BLOCK / kQuadBytes) return false;
     return (N * d >= (int64_t(1) << 23) && n_edges >= 12 * N) || (N * d >= (int64_t(1) << 22) && n_edges >= 16 * N);
 }
 
@@ -332,8 +334,8 @@ int gnn_scatter_winners(const int32_t *indices, const int64_t *eid, const int32_
     r.range_log2 = n_out > int64_t(kMaxRanges) << 12 ? 13 : 12;
     while (r.range_log2 > kMinRangeLog2 && (n_out >> r.range_log2) < 64) --r.range_log2;
     r.n_ranges = int32_t((n_out + (int64_t(1) << r.range_log2) - 1) >> r.range_log2);
-    int64_t quads = kMaxRoundBytes / (N * 4 * 14);
-    quads = quads < 1 ? 1 : (quads > kMaxQuads ? kMaxQuads : quads);
+    int64_t quads = GNN_POOL_MAX_BLOCK / (N * kQuadBytes);
+    if (quads > kMaxQuads) quads = kMaxQuads;
     const int64_t n_rounds = (all_quads + quads - 1) / quads;
     quads = (all_quads + n_rounds - 1) / n_rounds;
     const int64_t tiles = (N + kTileRows - 1) / kTileRows;

@@ -1,0 +1,56 @@
+"""Vertex gradient of max / min by sorting the winners (large outputs), against sums in 64 bits."""
+import pytest
+import torch
+
+import paper_2104_06700_amd as gnn
+
+pytestmark = pytest.mark.gpu
+
+
+def _winners(n, d, n_out, e, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    indices = torch.randint(0, n_out, (e,), device="cuda", dtype=torch.int32, generator=gen)
+    arg = torch.randint(-1, e, (n, d), device="cuda", dtype=torch.int32, generator=gen)
+    do = torch.empty(n, d, device="cuda").normal_(generator=gen)
+    return indices, arg, do
+
+
+def _check(dv, indices, arg, do, columns, factor=None):
+    """factor(positions, column): what the winner multiplies its gradient by, in 64 bits."""
+    for j in columns:
+        won = arg[:, j] >= 0
+        at = arg[won, j].long()
+        g = do[won, j].double()
+        if factor is not None:
+            g = g * factor(at, j)
+        u = indices[at].long()
+        ref = torch.zeros(dv.shape[0], dtype=torch.float64, device="cuda").index_add_(0, u, g)
+        mag = torch.zeros_like(ref).index_add_(0, u, g.abs())
+        # at most a few thousand additions per sum, in any order, of products rounded once: well below 1e-5 of the magnitudes
+        assert bool(((dv[:, j].double() - ref).abs() <= 1e-5 * mag).all()), f"column {j}"
+
+
+@pytest.mark.parametrize("n,d", [(2200000, 64), (2449029, 54)])
+def test_scratch_of_large_outputs_comes_from_the_pool(n, d):
+    """Sizes at which a round of 14 or 16 quads would take arrays of more than a block of the pool: the call returns while
+    work launched before it still runs."""
+    n_out, e = 50000, 12 * n
+    indices, arg, do = _winners(n, d, n_out, e, 5)
+    dv = torch.full((n_out, d), float("nan"), device="cuda")
+
+    def call():
+        gnn.gnn_ap_bwd_vertex_arg(indices, arg, do, None, dv, n_out, n, d, gnn.GNN_BIN_COPY_LHS)
+
+    call()  # the pool has the blocks from now on
+    a = torch.randn(8192, 8192, device="cuda")
+    b = torch.mm(a, a)
+    torch.cuda.synchronize()
+    done = torch.cuda.Event()
+    for _ in range(20):  # some 0.2 s of work
+        torch.mm(a, a, out=b)
+    done.record()
+    call()
+    assert not done.query(), "the call waited for the device"
+    torch.cuda.synchronize()
+    _check(dv, indices, arg, do, (0, 1, d // 2, d - 1))

@@ -293,8 +293,9 @@ GNN_API int gnn_ap_bwd_vertex_arg(const int32_t *indices, const int32_t *arg_e, 
                                   float *dfV, int64_t n_vertex_rows, int64_t N, int64_t d, int binop,
                                   const gnn_ap_opts *opts);
 /* The same call told the number of edges (0: unknown), which decides how the additions are made: large
- * outputs with many edges per row are sorted first (library-owned scratch of up to 2 GB, kept for the
- * next call; atomics on a stream that is being captured). */
+ * outputs with many edges per row are sorted first (library-owned scratch of up to
+ * GNN_CACHED_MEMORY_BYTES, kept for the next call; atomics on a stream that is being captured, and
+ * where there is no memory for it). */
 GNN_API int gnn_ap_bwd_vertex_arg_edges(const int32_t *indices, const int32_t *arg_e, const float *dO, const float *fE,
                                         float *dfV, int64_t n_vertex_rows, int64_t N, int64_t d, int binop,
                                         int64_t n_edges, const gnn_ap_opts *opts);
@@ -434,9 +435,14 @@ GNN_API int gnn_graph_build(const int32_t *dst_sorted, const int32_t *src, const
                     int64_t *perm, float *edge_w_t, const gnn_plan_params *params /* host */, void *stream,
                     gnn_plan **plan_fwd, gnn_plan **plan_bwd);
 
-/* Device memory of destroyed plans and of the setup calls is kept for the next ones, up to 1 GiB per
- * device (it is given back by itself when an allocation of the library fails).  Gives back what the
- * current device holds; waits for the device. */
+/* Device memory of destroyed plans, of the setup calls and of the scratch of
+ * gnn_ap_bwd_vertex_arg_edges is kept for the next ones: per device at most GNN_CACHED_MEMORY_BYTES
+ * that nothing uses at the moment.  It goes back to the driver when an allocation of the library
+ * fails, piece by piece when thousands of allocations have not asked for it, and by this call, which
+ * gives back what the current device holds and waits for the device.  Another allocator in the
+ * process that runs out of memory does not know of it: a program that needs the last 2 GiB elsewhere
+ * makes this call first. */
+#define GNN_CACHED_MEMORY_BYTES (2ll << 30)
 GNN_API void gnn_release_cached_memory(void);
 
 /* Sizes of what gnn_plan_export would write (host outputs). */

@@ -18,6 +18,7 @@ LIB_PATH = os.path.join(_PKG, "libgnnagg.so")
 GNN_OK, GNN_ERR_INVALID_ARG, GNN_ERR_UNSUPPORTED, GNN_ERR_ALLOC, GNN_ERR_LAUNCH, GNN_ERR_INVALID_GRAPH = range(6)
 GNN_ERR_SCRATCH_CAPACITY = 6
 GNN_NOALLOC_SCRATCH_BYTES = 32 << 20
+GNN_CACHED_MEMORY_BYTES = 2 << 30
 GNN_SUM, GNN_MEAN, GNN_GCN_SYM, GNN_SAGE_GCN = 0, 1, 2, 3
 GNN_F32, GNN_BF16 = 0, 1
 GNN_MAX_THRESHOLDS = 15
@@ -534,7 +535,8 @@ def gnn_graph_build(dst_sorted: torch.Tensor, src: torch.Tensor, edge_w: Optiona
 
 
 def gnn_release_cached_memory() -> None:
-    """Gives back the device memory the library keeps for the next plans (current device)."""
+    """Gives back the device memory the library keeps for the next plans and calls, up to GNN_CACHED_MEMORY_BYTES of the
+    current device; torch's allocator, when it runs out, does not do so by itself."""
     load_library().gnn_release_cached_memory()
 
 

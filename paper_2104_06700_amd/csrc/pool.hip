@@ -9,7 +9,7 @@
 // any stream may still be using it, as with hipFree; it is handed out again only after a device synchronisation, which
 // the next allocation that finds nothing else makes, for all such blocks at once.
 //
-// What is kept is bounded: kMaxIdleBytes per device, blocks of up to kMaxBlock bytes, and none that has not been asked
+// What is kept is bounded: GNN_CACHED_MEMORY_BYTES per device, blocks of up to kMaxBlock bytes, and none that has not been asked
 // for in kMaxAge allocations.  An allocation that the driver refuses gives everything back first and tries again.
 #include <map>
 #include <mutex>
@@ -20,7 +20,7 @@
 
 namespace {
 
-constexpr size_t kMaxIdleBytes = size_t(2) << 30;
+constexpr size_t kMaxIdleBytes = size_t(GNN_CACHED_MEMORY_BYTES);
 constexpr size_t kMaxBlock = size_t(GNN_POOL_MAX_BLOCK);
 constexpr uint64_t kMaxAge = 4096;
 constexpr size_t kHostBlock = GNN_HOST_BLOCK_BYTES;

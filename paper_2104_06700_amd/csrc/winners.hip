@@ -30,6 +30,8 @@ constexpr int kMaxQuads = 16;                  // quads per round; every round r
 // Bytes per vertex and quad of the largest arrays of a round.  A round takes as many quads as keep them within a block of the
 // pool (2,449,029 vertices, 112 columns, arrays of 523 MiB from the driver: 5.6 ms, in which the host waits; of 374 MiB: 4.8).
 constexpr int64_t kQuadBytes = 4 * sizeof(float);
+// three such arrays and one of half the size, beside tables of a few MB, are all kept for the next call
+static_assert(7 * GNN_POOL_MAX_BLOCK / 2 + (int64_t(64) << 20) <= GNN_CACHED_MEMORY_BYTES, "scratch of a call");
 
 struct Round {
     int64_t N, n_out;

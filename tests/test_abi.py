@@ -140,3 +140,10 @@ def test_calibration_calls_check_their_arguments_without_a_device():
     assert lib.gnn_calib_gather(one, 10, one, 1 << 28, one, (1 << 23) - 1, None) == bad     # output too small
     assert lib.gnn_calib_gather(ctypes.c_void_p(64), 10, one, 1 << 28, one, 1 << 23, None) == bad  # table not line-aligned
     assert lib.gnn_plan_bind_edge_weights(None, one, None) == bad                           # no plan
+
+
+def test_limits_match_the_header():
+    text = open(os.path.join(ROOT, "include", "gnnagg.h")).read()
+    for name in ("GNN_NOALLOC_SCRATCH_BYTES", "GNN_CACHED_MEMORY_BYTES"):
+        value, shift = re.search(rf"#define {name} \((\d+)l* << (\d+)\)", text).groups()
+        assert getattr(gnn, name) == int(value) << int(shift)

@@ -54,3 +54,23 @@ def test_scratch_of_large_outputs_comes_from_the_pool(n, d):
     assert not done.query(), "the call waited for the device"
     torch.cuda.synchronize()
     _check(dv, indices, arg, do, (0, 1, d // 2, d - 1))
+
+
+def test_cached_memory_is_bounded_and_given_back():
+    """Scratch of the largest kind and a dropped plan beside it: no more than the documented bytes are held afterwards."""
+    n, d, n_out = 2097152, 64, 50000  # arrays of exactly one block of the pool
+    indices, arg, do = _winners(n, d, n_out, 12 * n, 6)
+    dv = torch.empty(n_out, d, device="cuda")
+    gnn.gnn_ap_bwd_vertex_arg(indices, arg, do, None, dv, n_out, n, d, gnn.GNN_BIN_COPY_LHS)
+    dst, src = (torch.sort(torch.randint(0, n, (40000000,), device="cuda", dtype=torch.int32))[0] for _ in range(2))
+    g = gnn.build_device_graph(dst, src, n)
+    torch.cuda.synchronize()
+    del g
+    free = torch.cuda.mem_get_info()[0]
+    gnn.gnn_release_cached_memory()
+    held = torch.cuda.mem_get_info()[0] - free
+    # of the scratch alone there are 1792 MiB; the driver counts in steps of 2 MiB, a few dozen of which small blocks round up to
+    assert 1 << 30 < held <= gnn.GNN_CACHED_MEMORY_BYTES + (64 << 20)
+    free = torch.cuda.mem_get_info()[0]
+    gnn.gnn_release_cached_memory()
+    assert torch.cuda.mem_get_info()[0] == free

@@ -433,10 +433,10 @@ static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
     if (tiles >= 512 || K < 1024) return 1;
     int64_t split = (1024 + tiles - 1) / tiles;           // aim at ~4 workgroups per compute unit
-    // At least 128 k-steps per part: a part is bound by the latency of its tiles of 16 k-steps, one after the other, while
+    // At least GNN_SPLIT_MIN_K k-steps per part: a part is bound by the latency of its tiles of 16 k-steps, one after the other, while
     // the chip is not full (24,490 rows into 256 x 256: 0.20 ms with parts of 1024, 0.05 with 128); the partial planes
     // cost little beside that.
-    const int64_t max_split = K / 128;
+    const int64_t max_split = K / GNN_SPLIT_MIN_K;
     if (split > max_split) split = max_split;
     if (split > 4096) split = 4096;
     return split < 1 ? 1 : split;

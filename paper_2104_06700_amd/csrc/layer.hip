@@ -20,6 +20,8 @@
 namespace {
 
 constexpr int kRowsPerBlock = 128;
+// the rows of partial column sums, one per block of rows, also take one plane per part of the split weight gradient
+static_assert(kRowsPerBlock <= GNN_SPLIT_MIN_K, "room for a plane per part");
 
 // A library-owned side stream per device (default priority, created on first use, kept until
 // the process ends): the weight-gradient product, which depends only on G, runs there while the

@@ -147,3 +147,11 @@ def test_limits_match_the_header():
     for name in ("GNN_NOALLOC_SCRATCH_BYTES", "GNN_CACHED_MEMORY_BYTES"):
         value, shift = re.search(rf"#define {name} \((\d+)l* << (\d+)\)", text).groups()
         assert getattr(gnn, name) == int(value) << int(shift)
+
+
+def test_parts_of_a_split_weight_gradient_have_room_for_their_column_sums():
+    """A layer's workspace has one row of partial sums per 128 vertices, and the folded weight gradient writes one per part."""
+    for n in (1, 127, 128, 1023, 1024, 1025, 24490, 131073, 2449029, 111059956):
+        for fi, fo in ((1, 1), (16, 41), (100, 256), (256, 256), (602, 16), (1000, 1000)):
+            parts = gnn.gnn_matmul_workspace_bytes(fi, fo, n) // (4 * fi * fo)
+            assert parts <= (n + 127) // 128, (n, fi, fo)

@@ -97,7 +97,7 @@ class GnnError(RuntimeError):
 
 
 _lib = None
-_calls = None  # the extension module that marshals the hot calls, once the library is loaded
+_calls = None  # the extension module that marshals the hot calls, connected by the first of them
 
 
 def load_library() -> ctypes.CDLL:
@@ -161,13 +161,13 @@ def load_library() -> ctypes.CDLL:
         lib.gnn_status_string.restype = ctypes.c_char_p
         lib.gnn_calib_copy.argtypes = [vp, vp, i64, vp]
         lib.gnn_calib_gather.argtypes = [vp, i64, vp, i64, vp, i64, vp]
-        _connect_calls(lib)
         _lib = lib
     return _lib
 
 
-def _connect_calls(lib) -> None:
+def _connect_calls():
     global _calls
+    lib = load_library()
     try:
         from . import _pycall
     except ImportError as err:
@@ -176,13 +176,12 @@ def _connect_calls(lib) -> None:
              "gnn_ap_bwd_edge", "gnn_sage_layer_fwd", "gnn_sage_layer_bwd")
     _pycall.connect({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in names}, torch)
     _calls = _pycall
+    return _pycall
 
 
 def _hot(fn: str, name: str, *args) -> None:
     """Calls a function of the extension module; an allocation that fails is tried once more (see _call_allocating)."""
-    if _calls is None:
-        load_library()
-    status = getattr(_calls, name)(*args)
+    status = getattr(_calls or _connect_calls(), name)(*args)
     if status:
         if status == GNN_ERR_ALLOC:
             torch.cuda.synchronize()

@@ -1,4 +1,8 @@
 """The extension module that marshals the hot calls: argument checks that return before any device work."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -48,3 +52,17 @@ def test_rejected_arguments_of_the_operator_table_and_the_layers():
         gnn.gnn_sage_layer_fwd(I32, I32, X.double(), w, torch.zeros(3), X, X, None, stream=0)
     with pytest.raises(gnn.GnnError):  # a layer needs a plan
         gnn.gnn_sage_layer_fwd(I32, I32, X, w, torch.zeros(3), X, X, None, stream=0)
+
+
+def test_without_the_extension_module_the_library_loads_and_only_its_calls_fail():
+    code = ("import sys; sys.modules['paper_2104_06700_amd._pycall'] = None\n"
+            "import torch, paper_2104_06700_amd as gnn\n"
+            "assert gnn.gnn_matmul_workspace_bytes(4, 4, 4) == 0 and gnn.status_string(0) == 'ok'\n"
+            "t = torch.zeros(4, 4)\n"
+            "try:\n"
+            "    gnn.gnn_aggregate_fwd(t.int(), t.int(), None, t, t, 0, 4, gnn.GNN_SUM, stream=0)\n"
+            "except ImportError as err:\n"
+            "    assert '_pycall is missing' in str(err)\n"
+            "else:\n"
+            "    raise SystemExit('no error')\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))

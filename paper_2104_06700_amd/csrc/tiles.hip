@@ -753,7 +753,13 @@ int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles_in, const float *
         tile_fill_kernel<false, true><<<grid_for(L.n_waves * L.n_tiles * 64, 256), 256, 0, stream>>>(
             static_cast<const TileDesc *>(L.tiles), L.n_tiles, L.n_waves, L.rr, rows, static_cast<const uint2 *>(L.seg), L.n_parts, L.counts, L.wave_off,
             plan->blk_indices, plan->blk_epos, w, scale, 0, nullptr, *slot);
-        if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
+        if (hipGetLastError() != hipSuccess) {
+            if (slot != &L.tmp_w && slot != &L.bound_w) {  // an unfilled array must not serve a later call
+                gnn_dev_free(*slot);
+                *slot = nullptr;
+            }
+            return GNN_ERR_LAUNCH;
+        }
         if (slot == &L.bound_w) L.bound_version = plan->bound_w_version;
     }
     *out = *slot;

@@ -1,5 +1,7 @@
 """The one-call graph setup against a stable sort on the host and against the separate calls, at the edges of the sort's
 tiles (4096 pairs) and digits (8 bits); blocks of destroyed plans in use again, on another stream too."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -71,3 +73,43 @@ def test_blocks_move_between_streams():
     y = torch.empty_like(x)
     gnn.gnn_aggregate_fwd(g.indptr, g.indices, None, x, y, n, f, gnn.GNN_MEAN, plan=g.plan_fwd)
     assert torch.equal(ys[0], y)
+
+
+def test_two_threads_share_the_pool():
+    """Graphs are built, used and dropped by two threads on a stream each; either may get the blocks of the other."""
+    n, e, f = 140000, 2400000, 32  # the gradient of the winners is sorted, with scratch from the pool
+    problems, errors = [], []
+    for i in range(2):
+        dst, src = (torch.from_numpy(a).cuda() for a in _edges(n, e, 11 + i))
+        x = torch.randn(n, f, device="cuda")
+        arg = torch.randint(-1, e, (n, f), device="cuda", dtype=torch.int32)
+        u = src[arg.clamp(min=0).long()].long()
+        g = torch.where(arg >= 0, x.double(), torch.zeros((), dtype=torch.float64, device="cuda"))
+        grad, mag = (torch.zeros(n, f, dtype=torch.float64, device="cuda").scatter_add_(0, u, t) for t in (g, g.abs()))
+        problems.append((dst, src, x, arg, grad, mag))
+    torch.cuda.synchronize()
+
+    def work(problem):
+        try:
+            dst, src, x, arg, grad, mag = problem
+            first = None
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(6):
+                    g = gnn.build_device_graph(dst, src, n)
+                    y, dv = torch.empty_like(x), torch.empty_like(x)
+                    gnn.gnn_aggregate_fwd(g.indptr, g.indices, None, x, y, n, f, gnn.GNN_MEAN, plan=g.plan_fwd)
+                    gnn.gnn_ap_bwd_vertex_arg(g.indices, arg, x, None, dv, n, n, f, gnn.GNN_BIN_COPY_LHS)
+                    del g
+                    assert bool(((dv.double() - grad).abs() <= 1e-5 * mag).all())
+                    first = y if first is None else first
+                    assert torch.equal(first, y)
+        except BaseException as err:
+            errors.append(err)
+
+    threads = [threading.Thread(target=work, args=(p,)) for p in problems]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors

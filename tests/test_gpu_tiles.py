@@ -78,3 +78,39 @@ def test_one_row_far_longer_than_the_others_is_cut_into_parts():
     keys = torch.cat([base.dst.long() * n + base.src.long(), hub * n + torch.arange(n)[torch.arange(n) != hub]]).unique()
     el = synth.EdgeList(n=n, src=(keys % n).to(torch.int32), dst=(keys // n).to(torch.int32), meta={})
     _check(el, dict(min_degree=32, hot_lines=2000, block_lines=4000, max_piece=96, rest_min_count=0), 72, torch.float32, "sum", False, False)
+
+
+@pytest.mark.parametrize("f,dtype,bound", [(64, torch.float32, False), (64, torch.float32, True), (96, torch.bfloat16, False),
+                                           (8, torch.float32, False), (16, torch.float32, True), (32, torch.bfloat16, True)])
+def test_infinities_and_nan_reach_the_rows_that_gather_them_only(f, dtype, bound):
+    """Lists are filled up with a line of zeros: rows must not see a neighbour's value, nor the lines beside it.  Column c
+    holds one special value, in the vertex of a rank at the edges of blocks and tiles."""
+    el = synth.rmat_symmetric(5300, 1800000, (0.5, 0.2, 0.2, 0.1), 17)
+    wts = (synth.uniform_features(el.e, 1, 7).reshape(-1).abs() + 0.5) if bound else None  # positive: infinities keep their signs
+    dg = device_graph(el, weights=wts, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    dg.plan_fwd.set_blocking(min_degree=32, hot_lines=992, block_lines=500, max_piece=48, rest_min_count=0)
+    if bound:
+        dg.plan_fwd.bind_edge_weights(dg.edge_w)
+    x = synth.normal_features(el.n, f, 3, dtype=dtype).to(DEV)
+    y = torch.empty_like(x)
+
+    def call():
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, dg.edge_w, x, y, el.n, f, gnn.GNN_SUM, plan=dg.plan_fwd,
+                              flags=SLICED, max_slices=8)
+
+    call()
+    rank = dg.plan_fwd.export_blocked()[4]
+    vertex = np.argsort(rank)
+    edges = [0, 1, 495, 496, 990, 991, 992, 1242, 1491, 1492, 1991, 1992, 3000, 4491, 4492, 5298, 5299]
+    values = [float("inf"), float("-inf"), float("nan")]
+    want = torch.zeros(el.n, f, device=DEV)
+    src, dst = el.src.to(DEV).long(), el.dst.to(DEV).long()
+    for c in range(f):
+        u, v = int(vertex[edges[c % len(edges)]]), values[c % 3]
+        x[u, c] = v
+        want[dst[src == u], c] = v
+    call()
+    torch.cuda.synchronize()
+    special = ~torch.isfinite(want)
+    assert int(special.sum()) > f and torch.equal(~torch.isfinite(y), special)
+    assert torch.equal(torch.nan_to_num(y[special].float(), 1.0, 2.0, 3.0), torch.nan_to_num(want[special], 1.0, 2.0, 3.0))

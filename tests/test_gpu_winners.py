@@ -74,3 +74,60 @@ def test_cached_memory_is_bounded_and_given_back():
     free = torch.cuda.mem_get_info()[0]
     gnn.gnn_release_cached_memory()
     assert torch.cuda.mem_get_info()[0] == free
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("binop", [gnn.GNN_BIN_MUL, gnn.GNN_BIN_DIV])
+def test_sorted_gradient_with_edge_operands_behind_an_edge_id_map(binop, wide):
+    n, d, n_out = 140001, 33, 150000
+    e = 16 * n
+    indices, arg, do = _winners(n, d, n_out, e, 7)
+    ids = torch.randperm(e, device="cuda")
+    fe = torch.rand((e, d) if wide else (e,), device="cuda") + 0.5
+    dv = torch.full((n_out, d), float("nan"), device="cuda")
+    gnn.gnn_ap_bwd_vertex_arg(indices, arg, do, fe, dv, n_out, n, d, binop, edge_ids=ids)
+    torch.cuda.synchronize()
+
+    def factor(at, j):
+        y = (fe[ids[at], j] if wide else fe[ids[at]]).double()
+        return y if binop == gnn.GNN_BIN_MUL else 1.0 / y
+
+    _check(dv, indices, arg, do, (0, 3, 4, 31, 32), factor)
+
+
+def test_infinities_and_nan_reach_their_winners_only():
+    n, d, n_out = 140000, 32, 9000
+    indices, arg, do = _winners(n, d, n_out, 16 * n, 8)
+    indices[: 8 * n] = 77  # a range that is cut into pieces
+    for j, x in enumerate((float("inf"), float("-inf"), float("nan"))):
+        do[5 + j, j] = x
+        arg[5 + j, j] = 9 * n + j
+        do[50 + j, 8 + j] = x
+        arg[50 + j, 8 + j] = j
+    dv = torch.zeros(n_out, d, device="cuda")
+    gnn.gnn_ap_bwd_vertex_arg(indices, arg, do, None, dv, n_out, n, d, gnn.GNN_BIN_COPY_LHS)
+    want = torch.zeros(n_out, d, device="cuda")
+    for j, x in enumerate((float("inf"), float("-inf"), float("nan"))):
+        want[indices[9 * n + j], j] = x
+        want[77, 8 + j] = x
+    special = ~torch.isfinite(want)
+    assert torch.equal(~torch.isfinite(dv), special)
+    assert torch.equal(torch.nan_to_num(dv[special], 1.0, 2.0, 3.0), torch.nan_to_num(want[special], 1.0, 2.0, 3.0))
+
+
+def test_a_captured_call_adds_with_atomics():
+    """The sorted form takes scratch, which a captured call cannot; every replay gives the sums of the eager call."""
+    n, d, n_out = 140000, 32, 9000
+    indices, arg, do = _winners(n, d, n_out, 16 * n, 9)
+    dv = torch.full((n_out, d), float("nan"), device="cuda")
+    gnn.gnn_ap_bwd_vertex_arg(indices, arg, do, None, dv, n_out, n, d, gnn.GNN_BIN_COPY_LHS)
+    _check(dv, indices, arg, do, range(d))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gnn.gnn_ap_bwd_vertex_arg(indices, arg, do, None, dv, n_out, n, d, gnn.GNN_BIN_COPY_LHS)
+    for _ in range(3):
+        dv.fill_(float("nan"))
+        do.mul_(-0.5)
+        graph.replay()
+        torch.cuda.synchronize()
+        _check(dv, indices, arg, do, range(d))

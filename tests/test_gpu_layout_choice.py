@@ -14,7 +14,7 @@ F32, BF16 = torch.float32, torch.bfloat16
 LINES = [
     (100000, 25.0e6, 50, F32, False, False), (100000, 8.5e6, 50, F32, True, False), (100000, 8.5e6, 50, F32, False, True),
     (140000, 10.0e6, 50, F32, False, False), (140000, 8.5e6, 50, F32, False, True), (100000, 25.0e6, 100, BF16, False, False),
-    (300000, 31.25e6, 64, F32, False, False), (320000, 5.0e6 * 1.024, 256, F32, False, True),
+    (300000, 15.625e6, 64, F32, False, False), (320000, 5.0e6 * 1.024, 256, F32, False, True),
     (200000, 10.0e6, 20, F32, False, False), (200000, 0.7e9 / 128, 20, F32, True, False),
     (200000, 24.0e6, 8, F32, False, False), (200000, 28.0e6, 16, F32, False, False), (200000, 32.0e6, 32, F32, False, False),
 ]

@@ -159,8 +159,8 @@ typedef struct gnn_blocking_params {
  * edge_w   [E] fp32 in CSR edge order, or NULL
  * X        [N, ldx] gathered matrix, Y [N, ldy] output; fp32 or bf16 per opts->dtype
  * Y is OVERWRITTEN (rows without edges become +0); X and Y must not overlap.
- * Base pointers must be aligned to 16 bytes when the row stride in bytes is a
- * multiple of 16 (8 / 4 / 2 likewise); otherwise narrower loads are used.
+ * Base pointers must be aligned to an element; rows are read in 16-byte loads at any alignment, and the
+ * output is written in 16-byte stores where its base and stride are multiples of 16 bytes.
  * Asynchronous: returns after enqueueing on opts->stream.  N == 0 or F == 0 is
  * GNN_OK and does nothing.  opts == NULL means all defaults.
  * MEAN needs no plan; GCN_SYM without edge_w needs a plan (it holds dout). */
@@ -250,8 +250,8 @@ typedef struct gnn_ap_opts {
     void *stream;
     gnn_plan *plan;           /* plan of the graph passed in the same call, or NULL (no binning) */
     int32_t flags;            /* GNN_FLAG_NO_COLUMN_SLICES / NO_PADDED_COPY / FORCE_PADDED_COPY, as in gnn_opts:
-                                 gather-bound forward calls (no full-width edge operand, d % 4 == 0, a plan)
-                                 use the layout of the sum-only hot path */
+                                 gather-bound forward calls (no full-width edge operand, d >= 4, a plan)
+                                 use the column slices of the sum-only hot path */
     int32_t max_slices;       /* as in gnn_opts; 0 = automatic */
 } gnn_ap_opts;
 
@@ -263,10 +263,10 @@ typedef struct gnn_ap_opts {
  * fp32 operation, so the result is exact; arg_e (optional, int32 [N, d], dense) receives the CSR
  * position of the winning edge of every (v, j) -- the lowest position among equals, -1 for an
  * empty row -- and must be NULL for sum.  NaN inputs give an unspecified winner.  max / min need
- * E <= INT32_MAX.  16-byte loads are used when d, the strides and the base addresses allow,
- * scalar ones otherwise; a gather-bound call on a large graph with a plan is then staged through
- * plan-owned padded rows (1.1-1.2x the time of the next multiple of 4).  Hub rows use plan-owned
- * scratch (grown on first use: allocation).
+ * E <= INT32_MAX.  Every width and stride is read and written in 16-byte accesses at the alignment of
+ * a float (4-byte ones below four columns).  A gather-bound call (no full-width f_E) on a large graph
+ * with a plan gathers from a plan-owned copy of f_V where its rows are not whole 128-byte lines.
+ * Hub rows use plan-owned scratch (copy and scratch are grown on first use: allocation).
  * copylhs / sum and mul / sum with a scalar f_E are what gnn_aggregate_fwd computes with GNN_SUM
  * (plain or weighted) and run on that path, with its layouts; a scalar f_E that is strided or
  * addressed through edge_ids is first gathered into a plan-owned array of E floats (allocated on
@@ -287,8 +287,10 @@ GNN_API int gnn_ap_bwd_vertex(const void *indptr_t, const int32_t *indices_t, co
 
 /* The same gradient for reduce = max / min, where only the winning edge of each (v, j) carries
  * gradient: dfV[indices[arg_e[v,j]], j] += dO[v,j] * d(binop)/dx.  Runs over the FORWARD graph's
- * `indices` and the arg_e that gnn_ap_fwd wrote; N*d fp32 atomic adds into dfV [n_vertex_rows, ldv]
- * (zero-filled first), so the summation order, and with it the last bits, vary from run to run. */
+ * `indices` and the arg_e that gnn_ap_fwd wrote; dfV [n_vertex_rows, ldv] is overwritten.  The
+ * additions are fp32 atomics, in memory (this call) or in LDS after the winners have been sorted (the
+ * next one, on large outputs), so the summation order, and with it the last bits, vary from run to
+ * run. */
 GNN_API int gnn_ap_bwd_vertex_arg(const int32_t *indices, const int32_t *arg_e, const float *dO, const float *fE,
                                   float *dfV, int64_t n_vertex_rows, int64_t N, int64_t d, int binop,
                                   const gnn_ap_opts *opts);

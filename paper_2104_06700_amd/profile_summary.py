@@ -33,15 +33,15 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 
-# kernels that make up one aggregation call (everything else in a trace is once-per-plan setup)
-CALL_KERNELS = ("aggregate_kernel", "piece_kernel", "blk_finalize_kernel", "hub_finalize_kernel", "pad_rows_kernel",
-                "pad_scale_rows_kernel")
+# kernels that make up one aggregation call (everything else in a trace is once-per-plan setup; so is tile_fill_kernel here,
+# which a call launches only for weights that are not bound to the plan or that meet a factor in bf16)
+CALL_KERNELS = ("aggregate_kernel", "tile_kernel", "piece_kernel", "blk_finalize_kernel", "hub_finalize_kernel", "pad_rows_kernel")
 CALIB_KERNEL = "copy16_kernel"
 CALIB_BYTES = 1 << 30  # the calibration copy reads 1 GiB and writes 1 GiB
 
 
 # sources of the aggregation calls (the layer, product and operator-table files do not change what they do)
-AGGREGATION_SOURCES = ("aggregate.hip", "blocked.hip", "plan.hip", "graph.hip", "common.h")
+AGGREGATION_SOURCES = ("aggregate.hip", "blocked.hip", "tiles.hip", "plan.hip", "graph.hip", "common.h")
 
 
 def source_hash() -> str:
@@ -214,7 +214,7 @@ def write_summary(d: str, out_dir: str) -> None:
     lines.append(f"Written by `python -m paper_2104_06700_amd.profile_summary` from rocprofv3 output; kernel sources "
                  f"`{meta.get('source_hash', '?')}` (hash of the aggregation sources), {meta.get('date', '?')}.")
     lines.append("One agg_profile process per width and pass; a CALL = all kernels of one gnn_aggregate_fwd / _bwd "
-                 "(copy into the plan's layout, piece / row / tail launches, finalisation).  Commands, from the repository root "
+                 "(copy into the plan's layout, tile / piece / row / tail launches, finalisation).  Commands, from the repository root "
                  "on the MI355X box:")
     lines.append("")
     for c in meta["commands"]:
@@ -314,7 +314,7 @@ def write_bench_stats(d: str, out_dir: str) -> None:
                 f"the kernels above sum to {call_total:.3f} ms = {call_total / n_calls:.3f} ms per call.{busy_txt}",
             f"The JSON line of the same run: value {res['value']} {res['unit']}, {res['ms_per_step']} ms per step, mean call "
             f"{res['roofline']['avg_launch_ms']} ms by events on the launch stream (`roofline.avg_launch_ms`; the unit the roofline is "
-            f"taken over is the call = its copy into the plan's layout + piece / row / tail launches + finalisation), "
+            f"taken over is the call = its copy into the plan's layout + tile / piece / row / tail launches + finalisation), "
             f"roofline.frac {res['roofline']['frac']}.", "",
             "Per call (events, ms): " + ", ".join(f"{c['dir']} F={c['F']} {c['ms']}" for c in res["calls"]), ""]
     os.makedirs(out_dir, exist_ok=True)

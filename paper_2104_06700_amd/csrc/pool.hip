@@ -13,6 +13,7 @@
 // for in kMaxAge allocations.  An allocation that the driver refuses gives everything back first and tries again.
 #include <map>
 #include <mutex>
+#include <new>
 #include <unordered_map>
 #include <vector>
 
@@ -50,7 +51,11 @@ struct Pool {
 
 // Never destroyed: plans may be dropped while the process ends, after static objects are gone.
 Pool &pool() {
-    static Pool *p = new Pool;
+    static Pool *p = [] {
+        Pool *q = new Pool;
+        q->host.reserve(kMaxHostBlocks);
+        return q;
+    }();
     return *p;
 }
 
@@ -71,6 +76,7 @@ void release(const std::vector<Block> &blocks) {  // without the lock: hipFree w
 
 std::vector<Block> take_all_idle(Device &d) {
     std::vector<Block> out;
+    out.reserve(d.idle.size());
     for (auto &kv : d.idle) out.push_back(kv.second);
     d.idle.clear();
     d.idle_bytes = 0;
@@ -108,7 +114,7 @@ bool capturing(hipStream_t stream) {
     return hipStreamIsCapturing(stream, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
 }
 
-int allocate(void **out, size_t bytes, bool has_stream, hipStream_t stream) {
+int allocate_from(void **out, size_t bytes, bool has_stream, hipStream_t stream) {
     *out = nullptr;
     // what is built into a fresh block must run now and not when a graph is replayed
     if (has_stream && capturing(stream)) return GNN_ERR_ALLOC;
@@ -146,9 +152,9 @@ int allocate(void **out, size_t bytes, bool has_stream, hipStream_t stream) {
             }
             if (best != d.idle.end()) {
                 b = best->second;
+                P.live[b.p] = {device, b};
                 d.idle_bytes -= best->first;
                 d.idle.erase(best);
-                P.live[b.p] = {device, b};
                 break;
             }
             if (!any_pending || synced) break;
@@ -174,10 +180,24 @@ int allocate(void **out, size_t bytes, bool has_stream, hipStream_t stream) {
         gnn_pool_release();
         if (hipMalloc(&b.p, want) != hipSuccess) return GNN_ERR_ALLOC;
     }
-    std::lock_guard<std::mutex> lock(P.m);
-    P.live[b.p] = {device, b};
+    try {
+        std::lock_guard<std::mutex> lock(P.m);
+        P.live[b.p] = {device, b};
+    } catch (const std::bad_alloc &) {
+        (void)hipFree(b.p);
+        throw;
+    }
     *out = b.p;
     return GNN_OK;
+}
+
+// The containers may run out of host memory: no exception leaves the library.
+int allocate(void **out, size_t bytes, bool has_stream, hipStream_t stream) {
+    try {
+        return allocate_from(out, bytes, has_stream, stream);
+    } catch (const std::bad_alloc &) {
+        return GNN_ERR_ALLOC;
+    }
 }
 
 }  // namespace
@@ -187,9 +207,10 @@ void gnn_pool_release() {
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return;
     std::vector<Block> blocks;
-    {
+    try {
         std::lock_guard<std::mutex> lock(P.m);
         blocks = take_all_idle(P.dev[device]);
+    } catch (const std::bad_alloc &) {  // they stay
     }
     release(blocks);
 }
@@ -223,9 +244,10 @@ static void give_back(void *p, bool has_stream, hipStream_t stream) {
     }
     b.pending = !b.event;
     std::vector<Block> out;
-    {
+    try {
         std::lock_guard<std::mutex> lock(P.m);
         out = put_idle(P.dev[device], b);
+    } catch (const std::bad_alloc &) {  // lost, unless it is among the idle ones already
     }
     release(out);
 }
@@ -253,7 +275,7 @@ void gnn_host_block_free(void *p) {
     {
         std::lock_guard<std::mutex> lock(P.m);
         if (P.host.size() < kMaxHostBlocks) {
-            P.host.push_back(p);
+            P.host.push_back(p);  // room for all of them was reserved
             return;
         }
     }

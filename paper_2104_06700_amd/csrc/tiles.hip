@@ -15,13 +15,16 @@
 // than the mean is cut into parts (else it alone would set the time of its workgroup: worst workgroup 4.1 x the
 // mean without, 1.02 x with), and the bundles are dealt to the wavefronts like cards.
 //
-// What bounds it: LDS reads, 128 bytes per clock and compute unit (two halves of a line never share a bank, so
-// 128-byte lines are read without conflicts), 66 clocks per eight edges of a wavefront's rows, against 47
-// clocks of vector instructions (one multiply-add per LDS address, one add per element).  Measured on the 233
-// K-vertex graph (95.6 M of 114.6 M edges staged, 85 % of the slots filled): F=602, 19 lines, 4.45 ms = 52
-// TB/s of lines wanted, 61 TB/s read, where the same edges as pieces took 9.5 ms; the call 11.45 -> 7.8 ms.
-// The 2.45 M-vertex graph (56 of 124 M edges): F=256 1.4 ms for 2.8; the call, which the short rows bound, 9.15 -> 8.4 ms.
+// What bounds it: LDS reads.  Of the cycles in which a compute unit has a wavefront of the launch the LDS is active in
+// 75 to 82 %, a third of these with bank conflicts (the lines that a read of 64 lanes touches lie anywhere in the tile);
+// vector instructions (one multiply-add per LDS address, one add per element) take about 47 clocks per eight edges of a
+// wavefront's rows beside them.  Measured on the 233 K-vertex graph (95.6 M of 114.6 M edges staged, 85 % of the slots
+// filled): F=602, 19 lines, 4.0 ms alone = 58 TB/s of lines wanted, where the same edges as pieces took 9.5 ms; the call
+// 11.45 -> 7.9 ms.  The 2.45 M-vertex graph (56 of 124 M edges): F=256 1.07 ms alone for 2.8; the call, most of which the
+// short rows take, 9.15 -> 8.35 ms.
+#include <new>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "common.h"
@@ -706,11 +709,16 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, hipStream_t stream, con
         if (!plan->blk_decided) return GNN_ERR_INVALID_ARG;
         gnn_tiles B{};
         if (plan->blk_n_pieces > 0 && plan->blk_cell_off) {
-            const int rc = build_tiles(plan, lanes, bf16 ? kBundlesBf16 : kBundlesF32, stream, B);
+            int rc;
+            try {
+                rc = build_tiles(plan, lanes, bf16 ? kBundlesBf16 : kBundlesF32, stream, B);
+            } catch (const std::bad_alloc &) {  // of its host arrays: no exception leaves the library
+                rc = GNN_ERR_ALLOC;
+            }
             if (rc != GNN_OK || !B.active) gnn_tiles_free(B);
             if (rc != GNN_OK) return rc;
         }
-        L = B;
+        L = std::move(B);
         L.decided = true;
     }
     if (L.active) *out = &L;

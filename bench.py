@@ -276,8 +276,8 @@ def measure(workload, steps, warmup, scale, dev, dump_graph=None, flush=False, c
                 "tcc_hit_pct": tnote.get("tcc_hit_pct"),
                 "gathered_bytes_per_call": round(sum(e * r["F"] * esz for r in call_rows) / len(call_rows)),
                 "line_requests_per_call": round(sum(e * ((r["F"] * esz + 127) // 128) for r in call_rows) / len(call_rows)),
-                "kernel": "aggregate_kernel (all calls of one step: forward and backward at every width)",
-                "per": "call (= its aggregate_kernel launches + pad copy + hub finalisation)",
+                "kernel": "tile_kernel, piece_kernel and aggregate_kernel (all calls of one step: forward and backward at every width)",
+                "per": "call (= its copy into the plan's layout + tile / piece / row / tail launches + finalisation)",
                 "launches_per_step": len(call_rows), "avg_launch_ms": round(all_s * 1e3 / len(call_rows), 4)}
 
     packed = None

@@ -1356,9 +1356,10 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     bool plain_hub_columns = false;   // some launch left its hub rows to hub_finalize_kernel
     int64_t plain_hub_col_begin = F;  // ... from this column on
 
-    // The short rows of the blocked launches run on a second stream beside the pieces: they write other rows and
-    // read the same tables, the pieces are bound by line requests that hit in the L2s and the short rows by the
-    // misses behind them (2.45 M vertices: F=100 5.57 -> 5.32 ms, F=256 10.11 -> 9.98)
+    // The short rows of the blocked launches run on a second stream beside the tiles and pieces: they write other rows and
+    // read the same tables.  One after the other -> side by side: 2.45 M vertices F=100 4.37 -> 4.31 ms, F=256 8.36 -> 8.35,
+    // 233 K vertices F=256 3.27 -> 3.26, F=602 7.85 -> 8.00 (before the tiles took the gathers that hit in the L2s away
+    // from the pieces: 5.57 -> 5.32 and 10.11 -> 9.98 on the first).
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     if (bl.active && !(o.flags & GNN_FLAG_NO_SHORT_ROW_OVERLAP)) {

@@ -215,7 +215,7 @@ def write_summary(d: str, out_dir: str) -> None:
                  f"`{meta.get('source_hash', '?')}` (hash of the aggregation sources), {meta.get('date', '?')}.")
     lines.append("One agg_profile process per width and pass; a CALL = all kernels of one gnn_aggregate_fwd / _bwd "
                  "(copy into the plan's layout, tile / piece / row / tail launches, finalisation).  Commands, from the repository root "
-                 "on the MI355X box:")
+                 "on an MI355X:")
     lines.append("")
     for c in meta["commands"]:
         lines.append(f"    {c}")
@@ -294,7 +294,7 @@ def write_bench_stats(d: str, out_dir: str) -> None:
     rows = list(csv.DictReader(open(stats)))
     n_calls = (res["steps"] + res["warmup"]) * res["roofline"]["launches_per_step"]
     out = [f"# rocprofv3 kernel statistics of the bench command ({workload}, {res['steps']} steps + {res['warmup']} warm-up)", "",
-           "Written by `python -m paper_2104_06700_amd.profile_summary --bench-stats`.  Command (repository root, MI355X box):", "",
+           "Written by `python -m paper_2104_06700_amd.profile_summary --bench-stats`.  Command (repository root, on an MI355X):", "",
            f"    {cmd}", "",
            "    kernel                                      calls    total ms     mean ms      %"]
     call_total = 0.0

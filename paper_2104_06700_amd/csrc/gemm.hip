@@ -2,24 +2,28 @@
 //
 //   C[m, n] = act( sum_k opA(A)[m, k] * opB(B)[k, n] + bias[n] )
 //
-// fp32 in, fp32 out, on the matrix cores: v_mfma_f32_32x32x2_f32 multiplies exact fp32 products and
-// accumulates in fp32, so the result meets the same tolerance as the aggregation.  A workgroup of
-// four wavefronts owns a 128 x 128 tile of C, each wavefront a 64 x 64 quarter as 2 x 2 MFMA
-// tiles (256 x 64 or 256 x 32 tiles for narrow outputs).  A and B tiles of 16 k-steps are staged
-// through LDS k-major ([k][m] and [k][n]), so that the 32 lanes of an MFMA operand read
-// consecutive words; the global loads follow whichever direction of the operand is contiguous
-// and are issued one tile ahead, so they fly while the matrix cores work on the current tile.  The
-// reduction over a very long k (the weight gradient: k = number of vertices) is split into parts
-// whose partial tiles a second kernel adds in order (deterministic, no atomics).
+// fp32 in, fp32 out, fp32 accumulation, on the bf16 matrix cores: every operand element is split into
+// three bf16 numbers whose sum it is, exactly (split8), and of the nine products of a pair the six that matter are
+// formed (sum_of_products).  The bf16 instruction does 16 times the work of the fp32 one in the same time, so six of them
+// are 2.7 times as fast, and the products meet the memory instead of the matrix cores (256 -> 256 excepted).
+// Relative error against 64 bits, 2-norm, normal operands, before (fp32 instruction, one chain) -> now: 4096 x 256 with
+// k = 256 2.9e-7 -> 0.8e-7, k = 602 4.4e-7 -> 1.2e-7, a weight gradient of 60,000 rows 3.2e-7 -> 1.8e-7, of 2.45 M rows
+// 1.2e-6 -> 0.5e-6; operands over 40 binary orders of magnitude and positive ones are no further off than before either.
+//
+// Times, 2,449,029 rows, before -> now: 100 -> 256 1.75 -> 1.30 ms, 256 -> 256 2.95 -> 2.03 (0.95 PFLOP/s of bf16 products; the
+// chip's own limit with such operands is 1.8, its clock falls to 1.7 GHz), 256 -> 47 1.01 -> 0.75; weight gradients
+// 100 x 256 1.45 -> 1.12, 256 x 256 2.75 -> 2.03, 256 x 47 0.90 -> 0.78; 24,490 rows 256 -> 256 46 -> 31 us.
 #include "common.h"
 
 namespace {
 
-constexpr int BK = 16;
-constexpr int PAD = 4;  // row stride rows + PAD: k-rows start 4 banks apart
-constexpr int kThreads = 256;
+constexpr int BK = 16;  // k of one v_mfma_f32_32x32x16_bf16
 
 typedef float float16v __attribute__((ext_vector_type(16)));
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // 16-byte access at the alignment of a float
 
 struct GemmArgs {
     const float *A;
@@ -47,339 +51,590 @@ struct GemmArgs {
     int32_t gx, gy, gz, inner;
 };
 
-// One [ROWS x BK] tile of an operand on its way from global memory to LDS (stored k-major as
-// tile[k][r]).  X(r, k) = base[r * sr + k * sk].  K_CONTIG: sk == 1 (threads run along k), else
-// sr == 1 (threads run along the rows); 16-byte loads when aligned.  load() and store() are
-// separate so that the loads of the next tile are in flight while the matrix cores work.
-template <bool K_CONTIG, int ROWS, bool GATED = false>
+// Tile of this workgroup (see GemmArgs::inner); false: none, the last group of 8 may be incomplete.
+__device__ __forceinline__ bool tile_of_block(const GemmArgs &g, int64_t &bx, int64_t &by, int64_t &bz) {
+    const int64_t b = blockIdx.x;
+    if (g.inner > 0) {
+        const int64_t per = int64_t(8) * g.inner, r = b % per;
+        const int64_t outer = b / per * 8 + (r & 7), in = r >> 3;
+        if (g.gz > 1) { bz = outer; bx = in % g.gx; by = in / g.gx; }
+        else { bx = outer; by = in; bz = 0; }
+        return bx < g.gx && bz < g.gz;
+    }
+    bx = b % g.gx;
+    by = b / g.gx % g.gy;
+    bz = b / (int64_t(g.gx) * g.gy);
+    return true;
+}
+
+// Two floats -> two bf16 (round to nearest even), low half first.
+__device__ __forceinline__ uint32_t bf16_pair(float x, float y) {
+    const float2v v = {x, y};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// x = p[0] + p[1] + p[2] exactly: 24 significant bits are three times the eight of a bf16.  Each difference below is
+// exact (the rounded part shares the leading bits), |p[1]| <= 2^-9 |x|, |p[2]| <= 2^-18 |x|.  What is not finite, or rounds up
+// to infinity, leaves NaNs that reach every result it takes part in (see the end of gemm_kernel).
+__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
+    uint32_t w[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const uint32_t q = bf16_pair(a, b);
+            w[s][i] = q;
+            if (s < 2) {
+                a -= __uint_as_float(q << 16);
+                b -= __uint_as_float(q & 0xffff0000u);
+            }
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < 3; ++s) p[s] = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
+}
+
+// The products of 16 k: a b = sum over the parts of a_p b_q, |a_p b_q| <= 2^(-9 (p + q)) |a b|.  The three products with
+// p + q > 2 are left out: 2^-26 of |a b| at most each and of either sign, where the rounding of one fp32 addition is 2^-25 of the
+// sum.  They are summed from zero, the smallest first, and added to the result with one rounding (add_tile): the
+// matrix cores cut off what lies below the sum's last bit, so a long chain through them would be the worse sum.
+__device__ __forceinline__ void sum_of_products(float16v &sum, const bf16x8 (&a)[3], const bf16x8 (&b)[3]) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[v] = 0.0f;
+#pragma unroll
+    for (int s = 2; s >= 0; --s)
+#pragma unroll
+        for (int p = 0; p <= s; ++p) sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], b[s - p], sum, 0, 0, 0);
+}
+
+// What is cut off is cut off towards minus infinity, which would add up over the steps of a long k and over the rows of a later
+// sum (a bias gradient).  So in step t the rows of A whose number plus t is odd are negated (row_sign), and their sums subtracted.
+__device__ __forceinline__ uint32_t row_sign(int row, int t) { return uint32_t(row + t) << 31; }
+__device__ __forceinline__ void add_tile(float16v &acc, const float16v &sum, int t) {
+    const float s = (t & 1) ? -1.0f : 1.0f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = fmaf(sum[v], (v & 1) ? -s : s, acc[v]);
+}
+
+// A [ROWS x BK] tile of an operand in LDS, in the order in which the matrix cores take it: per plane of the split and per 32
+// rows the 16 bytes (8 k) of every lane, lane = 32 * (k / 8) + row.  The upper half's rows are rotated by four so that the
+// writes of K_CONTIG threads, which alternate between the halves, fall into different banks.
+template <int ROWS>
+struct SplitTile {
+    uint4 v[3][ROWS / 32][64];
+    static __device__ __forceinline__ int slot(int half, int r32) { return half * 32 + (r32 ^ (half * 4)); }
+};
+
+// One tile of an operand on its way from global memory to LDS.  X(r, k) = base[r * sr + k * sk].  K_CONTIG: sk == 1, else
+// sr == 1.  A thread takes units of 8 k of a row: two 16-byte loads, or eight loads of 4 bytes with the rows along the
+// lanes.  Rows past the end repeat the last one (their results are never stored).  load() and store() are separate so that the
+// loads of a later tile are in flight while the matrix cores work.
+template <bool K_CONTIG, int ROWS, int THREADS, bool GATED = false>
 struct Stager {
-    static constexpr int QUADS = ROWS * BK / 4;
-    static constexpr int PER_THREAD = (QUADS + kThreads - 1) / kThreads;
-    float v[PER_THREAD][4];
-    float gate[GATED ? PER_THREAD : 1][4];  // the gate's elements travel beside the operand's and are applied in store()
+    static constexpr int UNITS = ROWS * 2;
+    static constexpr int PER_THREAD = (UNITS + THREADS - 1) / THREADS;
+    float v[PER_THREAD][8];
+    float gate[GATED ? PER_THREAD : 1][8];  // the gate's elements travel beside the operand's and are applied in store()
+    // Rows along the lanes, 64 and more: a wavefront's 64 units have one k, so the address is a scalar plus 4 * row.  Otherwise
+    // a lane keeps the address of its unit in the tile at k_begin.
+    static constexpr bool SCALAR_K = !K_CONTIG && ROWS % 64 == 0;
+    const float *p[PER_THREAD];
+    uint32_t row_bytes[SCALAR_K ? PER_THREAD : 1];
+    int64_t sk, gate_off;
 
-    // Whole tiles of an aligned operand: the thread keeps the address of its quad 0 in the tile at k_begin; quad h
-    // lies a uniform step further, a later tile a uniform offset further; rows are checked against a 32-bit
-    // count.  The kernel's main loop uses only this path, so that it stays a few hundred instructions long: with
-    // the general path below inlined (64-bit address arithmetic and a check per element, for every quad of up to
-    // three matrices) the loop of the gated products outgrew what the instruction cache serves at full speed.
-    const float *p0;
-    int64_t step_h, k_step, gate_off;
-    int32_t rows_left;
+    static __device__ __forceinline__ bool has(int h) { return UNITS % THREADS == 0 || int(threadIdx.x) + h * THREADS < UNITS; }
+    static __device__ __forceinline__ int row_of(int h) {
+        const int u = int(threadIdx.x) + h * THREADS;
+        return K_CONTIG ? u >> 1 : u % ROWS;
+    }
+    static __device__ __forceinline__ int half_of(int h) {
+        const int u = int(threadIdx.x) + h * THREADS;
+        return K_CONTIG ? u & 1 : u / ROWS;
+    }
 
-    __device__ __forceinline__ void init(const float *__restrict__ base, const float *__restrict__ gate_base, int64_t sr, int64_t sk,
+    __device__ __forceinline__ void init(const float *__restrict__ base, const float *__restrict__ gate_base, int64_t sr, int64_t sk_,
                                          int64_t r0, int64_t r_end, int64_t k_begin) {
-        const int q = int(threadIdx.x);
-        if (K_CONTIG) {
-            p0 = base + (r0 + (q >> 2)) * sr + k_begin + (q & 3) * 4;
-            step_h = (kThreads / 4) * sr;
-            k_step = 1;
-        } else {
-            p0 = base + (k_begin + q / (ROWS / 4)) * sk + r0 + (q % (ROWS / 4)) * 4;
-            step_h = (kThreads / (ROWS / 4)) * sk;
-            k_step = sk;
-        }
+        sk = K_CONTIG ? 1 : sk_;
         gate_off = (GATED && gate_base) ? gate_base - base : 0;
-        const int64_t left = r_end - r0;
-        rows_left = left > 0x7fffffff ? 0x7fffffff : int32_t(left);
-    }
-
-    // k_off = first k of the tile - k_begin (uniform); the tile lies inside the k range whole
-    __device__ __forceinline__ void load_whole_tile(int64_t k_off, bool gated) {
-        const float *pt = p0 + k_off * k_step;
 #pragma unroll
         for (int h = 0; h < PER_THREAD; ++h) {
-            const int q = int(threadIdx.x) + h * kThreads;
-            if (QUADS % kThreads != 0 && q >= QUADS) continue;
-            const int first_row = K_CONTIG ? (q >> 2) : (q % (ROWS / 4)) * 4;
-            const int rows = K_CONTIG ? 1 : 4;  // rows this quad touches
-            const float *p = pt + h * step_h;
-            if (first_row + rows <= rows_left) {
-                const float4 x = *reinterpret_cast<const float4 *>(p);
-                v[h][0] = x.x; v[h][1] = x.y; v[h][2] = x.z; v[h][3] = x.w;
-                if constexpr (GATED) {
-                    if (gated) {
-                        const float4 y = *reinterpret_cast<const float4 *>(p + gate_off);
-                        gate[h][0] = y.x; gate[h][1] = y.y; gate[h][2] = y.z; gate[h][3] = y.w;
-                    }
-                }
+            const int64_t r = r0 + row_of(h), row = r < r_end ? r : r_end - 1;
+            if constexpr (SCALAR_K) {
+                p[h] = base + r0 + (k_begin + __builtin_amdgcn_readfirstlane(half_of(h)) * 8) * sk;
+                row_bytes[h] = uint32_t(row - r0) * 4;
             } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const bool ok = !K_CONTIG && first_row + i < rows_left;  // a quad of rows that straddles the end
-                    v[h][i] = ok ? p[i] : 0.0f;
-                    if constexpr (GATED) gate[h][i] = (ok && gated) ? p[gate_off + i] : 0.0f;
-                }
+                p[h] = base + row * (K_CONTIG ? sr : 1) + (k_begin + half_of(h) * 8) * sk;
             }
         }
     }
 
-    __device__ __forceinline__ void load(const float *__restrict__ base, const float *__restrict__ gate_base, int64_t sr, int64_t sk,
-                                         int64_t r0, int64_t r_end, int64_t k0, int64_t k_end, bool vec_ok) {
-        fetch(base, v, sr, sk, r0, r_end, k0, k_end, vec_ok);
-        if constexpr (GATED) {
-            if (gate_base) fetch(gate_base, gate, sr, sk, r0, r_end, k0, k_end, vec_ok);
-        }
-    }
-
-    template <int ROWS_OF_V>
-    __device__ __forceinline__ void fetch(const float *__restrict__ base, float (&v)[ROWS_OF_V][4], int64_t sr, int64_t sk, int64_t r0,
-                                          int64_t r_end, int64_t k0, int64_t k_end, bool vec_ok) {
+    // k_off = first k of the tile - k_begin (uniform; may be negative)
+    __device__ __forceinline__ void load(int64_t k_off, bool gated) {
 #pragma unroll
         for (int h = 0; h < PER_THREAD; ++h) {
-            const int q = int(threadIdx.x) + h * kThreads;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[h][i] = 0.0f;
-            if (QUADS % kThreads != 0 && q >= QUADS) continue;
-            if (K_CONTIG) {
-                const int r = q >> 2, kq = (q & 3) * 4;
-                const int64_t gr = r0 + r, gk = k0 + kq;
-                if (gr < r_end) {
-                    const float *p = base + gr * sr + gk;
-                    if (vec_ok && gk + 3 < k_end) {
-                        const float4 x = *reinterpret_cast<const float4 *>(p);
-                        v[h][0] = x.x; v[h][1] = x.y; v[h][2] = x.z; v[h][3] = x.w;
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (gk + i < k_end) v[h][i] = p[i];
-                    }
-                }
-            } else {
-                const int k = q / (ROWS / 4), rq = (q % (ROWS / 4)) * 4;
-                const int64_t gk = k0 + k, gr = r0 + rq;
-                if (gk < k_end) {
-                    const float *p = base + gk * sk + gr;
-                    if (vec_ok && gr + 3 < r_end) {
-                        const float4 x = *reinterpret_cast<const float4 *>(p);
-                        v[h][0] = x.x; v[h][1] = x.y; v[h][2] = x.z; v[h][3] = x.w;
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (gr + i < r_end) v[h][i] = p[i];
-                    }
-                }
+            if (!has(h)) continue;
+            fetch(h, p[h] + k_off * sk, v[h]);
+            if constexpr (GATED) {
+                if (gated) fetch(h, p[h] + k_off * sk + gate_off, gate[h]);
             }
         }
     }
-
-    // Adds what this thread staged (after store() applied the gate) to its sums over k: for an operand whose
-    // rows are contiguous a thread holds the same four rows in every tile.
-    __device__ __forceinline__ void add_to_row_sums(float (&acc)[4]) const {
-        static_assert(!K_CONTIG, "row sums are kept for row-contiguous operands only");
+    __device__ __forceinline__ float at(int h, const float *q, int i) const {
+        if constexpr (SCALAR_K) return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(q + i * sk) + row_bytes[h]);
+        else return q[i * sk];
+    }
+    __device__ __forceinline__ void fetch(int h, const float *q, float (&x)[8]) const {
+        if constexpr (K_CONTIG) {
+            const f32x4_any lo = *reinterpret_cast<const f32x4_any *>(q), hi = *reinterpret_cast<const f32x4_any *>(q + 4);
 #pragma unroll
-        for (int h = 0; h < PER_THREAD; ++h) {
-            if (QUADS % kThreads != 0 && int(threadIdx.x) + h * kThreads >= QUADS) continue;
+            for (int i = 0; i < 4; ++i) { x[i] = lo[i]; x[4 + i] = hi[i]; }
+        } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] += v[h][i];
+            for (int i = 0; i < 8; ++i) x[i] = at(h, q, i);
         }
     }
 
-    __device__ __forceinline__ void store(float (*tile)[ROWS + PAD], bool gated) {
-        if constexpr (GATED) {
-            if (gated) {
-#pragma unroll
-                for (int h = 0; h < PER_THREAD; ++h)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) v[h][i] = gate[h][i] > 0.0f ? v[h][i] : 0.0f;
-            }
-        }
+    // the first tile of an operand with n < 16 k
+    __device__ __forceinline__ void load_few(int n) {
 #pragma unroll
         for (int h = 0; h < PER_THREAD; ++h) {
-            const int q = int(threadIdx.x) + h * kThreads;
-            if (QUADS % kThreads != 0 && q >= QUADS) continue;
-            if (K_CONTIG) {
-                const int r = q >> 2, kq = (q & 3) * 4;
+            if (!has(h)) continue;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) tile[kq + i][r] = v[h][i];
-            } else {
-                const int k = q / (ROWS / 4), rq = (q % (ROWS / 4)) * 4;
-                *reinterpret_cast<float4 *>(&tile[k][rq]) = make_float4(v[h][0], v[h][1], v[h][2], v[h][3]);
+            for (int i = 0; i < 8; ++i) v[h][i] = half_of(h) * 8 + i < n ? at(h, p[h], i) : 0.0f;
+        }
+    }
+    // the first `n` k of the tile count as 0 (a tile moved back to end with k_end repeats them)
+    __device__ __forceinline__ void drop_first(int n) {
+#pragma unroll
+        for (int h = 0; h < PER_THREAD; ++h)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[h][i] = half_of(h) * 8 + i >= n ? v[h][i] : 0.0f;
+    }
+
+    // flip: the rows are negated as in step `t` (row_sign)
+    __device__ __forceinline__ void store(SplitTile<ROWS> &tile, bool gated, bool with_sums, float (&sums)[PER_THREAD][2], bool flip, int t) {
+#pragma unroll
+        for (int h = 0; h < PER_THREAD; ++h) {
+            if (!has(h)) continue;
+            if constexpr (GATED) {
+                if (gated) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[h][i] = gate[h][i] > 0.0f ? v[h][i] : 0.0f;
+                }
+                if (with_sums) {  // of even and of odd tiles: shorter chains, less rounding
+                    const float x = ((v[h][0] + v[h][1]) + (v[h][2] + v[h][3])) + ((v[h][4] + v[h][5]) + (v[h][6] + v[h][7]));
+                    sums[h][0] = (t & 1) ? sums[h][0] : sums[h][0] + x;
+                    sums[h][1] = (t & 1) ? sums[h][1] + x : sums[h][1];
+                }
             }
+            if (flip) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[h][i] = __uint_as_float(__float_as_uint(v[h][i]) ^ row_sign(row_of(h), t));
+            }
+            uint4 q[3];
+            split8(v[h], q);
+            const int r = row_of(h), s = SplitTile<ROWS>::slot(half_of(h), r & 31);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) tile.v[pl][r >> 5][s] = q[pl];
         }
     }
 };
 
-// Workgroup tile (WM * TI * 32) x (WN * TJ * 32): WM x WN wavefronts, each TI x TJ MFMA tiles.
-// FOLD: 0 = plain operands; 1 = A may carry a gate; 2 = B may carry a gate and its column sums may be asked for.
-// (The 256 x 64 tile with a gated operand stages 32 more registers: three waves per SIMD instead of spilling.)
-template <bool A_K_CONTIG, bool B_K_CONTIG, int WM, int WN, int TI, int TJ, int FOLD = 0>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((FOLD != 0 && WM == 4 && TJ == 2) ? 3 : 4, 8))) gemm_kernel(const GemmArgs g, int a_vec_ok, int b_vec_ok) {
-    static_assert(WM * WN == kThreads / 64, "four wavefronts");
-    constexpr int BM = WM * TI * 32, BN = WN * TJ * 32;
-    __shared__ __attribute__((aligned(16))) float As[BK][BM + PAD];
-    __shared__ __attribute__((aligned(16))) float Bs[BK][BN + PAD];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int wm = (wave / WN) * TI * 32, wn = (wave % WN) * TJ * 32;  // this wavefront's part of the tile
-    int64_t bx, by, bz;
-    {
-        const int64_t b = blockIdx.x;
-        if (g.inner > 0) {
-            const int64_t per = int64_t(8) * g.inner, r = b % per;
-            const int64_t outer = b / per * 8 + (r & 7), in = r >> 3;
-            if (g.gz > 1) { bz = outer; bx = in % g.gx; by = in / g.gx; }
-            else { bx = outer; by = in; bz = 0; }
-            if (bx >= g.gx || bz >= g.gz) return;  // the last group of 8 may be incomplete (whole workgroup leaves)
-        } else {
-            bx = b % g.gx;
-            by = b / g.gx % g.gy;
-            bz = b / (int64_t(g.gx) * g.gy);
-        }
+// An operand that is not finite (or within 2^-9 of the largest float) splits into NaNs, and so none of the results it takes
+// part in is finite; the third part of an operand below 2^-110 is cut off where bf16 ends, and results below 2^-90 are
+// where that could be seen.  A wavefront with such a result computes its tiles again from the operands as they are, by the fp32
+// matrix instruction.
+template <int TI, int TJ>
+__device__ __forceinline__ void recompute_if_needed(const GemmArgs &g, float16v (&acc)[TI][TJ], int64_t m0, int64_t n0, int64_t k_begin,
+                                                    int64_t k_end) {
+    constexpr float kSmall = 0x1p-90f;
+    float most = 0.0f, least = 1.0f;  // of the absolute values; a NaN stays in `most`
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; v += 2) {
+                asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(acc[i][j][v]), "v"(acc[i][j][v + 1]));
+                asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(least) : "v"(acc[i][j][v]), "v"(acc[i][j][v + 1]));
+            }
+    bool again = !(most <= 0x1.fffffep127f);
+    if (__any(least < kSmall)) {  // a zero, most likely
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) again |= acc[i][j][v] != 0.0f && !(fabsf(acc[i][j][v]) >= kSmall);
     }
-    const int64_t m0 = bx * BM, n0 = by * BN;
-    const int64_t k_begin = bz * g.k_per_split;
-    const int64_t k_end = k_begin + g.k_per_split < g.K ? k_begin + g.k_per_split : g.K;
-
-    float16v acc[TI][TJ];
+    if (!__any(again)) return;
+    const int l32 = threadIdx.x & 31, lk = (threadIdx.x >> 5) & 1;
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-    Stager<A_K_CONTIG, BM, FOLD == 1> sa;
-    Stager<B_K_CONTIG, BN, FOLD == 2> sb;
-    const bool a_gated = FOLD == 1 && g.a_gate, b_gated = FOLD == 2 && g.b_gate;
-    const bool sums = FOLD == 2 && g.colsum && bx == 0;  // the first tile row also adds up the columns of B (uniform)
-    float col_sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    const int l32 = lane & 31, lk = lane >> 5;
-    auto stage = [&]() {  // registers -> LDS
-        sa.store(As, a_gated);
-        sb.store(Bs, b_gated);
-        if constexpr (FOLD == 2) {
-            if (sums) sb.add_to_row_sums(col_sum);  // rows past k_end were staged as zeros
+#pragma unroll 1
+    for (int64_t k = k_begin; k < k_end; k += 2) {
+        // operand layout of the 32x32x2 instruction: lane l holds A[l % 32][l / 32] and B[l / 32][l % 32]
+        const bool in = k + lk < k_end;
+        float a[TI], b[TJ];
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+            const int64_t m = m0 + i * 32 + l32, at = m * g.sam + (k + lk) * g.sak;
+            a[i] = (in && m < g.M && !(g.a_gate && !(g.a_gate[at] > 0.0f))) ? g.A[at] : 0.0f;
         }
-    };
-    auto multiply = [&]() {
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            // operand layout of the 32x32x2 instruction: lane l holds A[l % 32][l / 32] and B[l / 32][l % 32]
-            float a[TI], b[TJ];
-#pragma unroll
-            for (int i = 0; i < TI; ++i) a[i] = As[kk + lk][wm + i * 32 + l32];
-#pragma unroll
-            for (int j = 0; j < TJ; ++j) b[j] = Bs[kk + lk][wn + j * 32 + l32];
-#pragma unroll
-            for (int i = 0; i < TI; ++i)
-#pragma unroll
-                for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-    };
-    auto load_any = [&](int64_t k0) {
-        sa.load(g.A, g.a_gate, g.sam, g.sak, m0, g.M, k0, k_end, a_vec_ok != 0);
-        sb.load(g.B, g.b_gate, g.sbn, g.sbk, n0, g.N, k0, k_end, b_vec_ok != 0);
-    };
-    // Tiles t = 0 .. n_tiles - 1; the first n_fast of them are whole tiles of aligned operands.  The loads of tile
-    // t + 1 are issued before tile t is multiplied, so they fly while the matrix cores work.
-    const int64_t n_tiles = k_begin < k_end ? (k_end - k_begin + BK - 1) / BK : 0;
-    const int64_t n_fast = (a_vec_ok && b_vec_ok && k_begin < k_end) ? (k_end - k_begin) / BK : 0;
-    sa.init(g.A, g.a_gate, g.sam, g.sak, m0, g.M, k_begin);
-    sb.init(g.B, g.b_gate, g.sbn, g.sbk, n0, g.N, k_begin);
-    if (n_fast > 0) {
-        sa.load_whole_tile(0, a_gated);
-        sb.load_whole_tile(0, b_gated);
-    } else if (n_tiles > 0) {
-        load_any(k_begin);
-    }
-    int64_t t = 0;
-    for (; t + 1 < n_fast; ++t) {  // the main loop: tile t + 1 is a whole one
-        stage();
-        __syncthreads();
-        sa.load_whole_tile((t + 1) * BK, a_gated);
-        sb.load_whole_tile((t + 1) * BK, b_gated);
-        multiply();
-        __syncthreads();
-    }
-    for (; t < n_tiles; ++t) {  // what is left: a last partial tile, or every tile of an operand that is not aligned
-        stage();
-        __syncthreads();
-        if (t + 1 < n_tiles) load_any(k_begin + (t + 1) * BK);
-        multiply();
-        __syncthreads();
-    }
-
-    if constexpr (FOLD == 2) {
-        if (sums) {
-            // a thread holds 4 columns of one k-row of every tile; the threads that hold the same columns are
-            // added in thread order through LDS (the operand tiles are no longer needed)
-            constexpr int GROUPS = BN / 4, SLOTS = kThreads / GROUPS;
-            float *scr = &As[0][0];
-            static_assert(SLOTS * BN <= BK * (BM + PAD), "scratch fits the A tile");
-            const int grp = int(threadIdx.x) % GROUPS, slot = int(threadIdx.x) / GROUPS;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) scr[slot * BN + grp * 4 + i] = col_sum[i];
-            __syncthreads();
-            if (int(threadIdx.x) < BN && n0 + int(threadIdx.x) < g.N) {
-                float tsum = 0.0f;
-                for (int sl = 0; sl < SLOTS; ++sl) tsum += scr[sl * BN + threadIdx.x];
-                g.colsum[bz * g.N + n0 + threadIdx.x] = tsum;
-            }
-        }
-    }
-
-    // result layout: register v of lane l is C[8 * (v / 4) + 4 * (l / 32) + v % 4][l % 32]
-    float *out = g.C;
-    if (g.n_split > 1) out += bz * g.M * g.ldc;  // partial planes of M x ldc
-    const gnn_packed_target &pk = g.packed;
-    if (pk.active) {
-        // producer-side layout: the 32 lanes of a row write one 128-byte line of a slice table (or a piece of the
-        // tail) at the row's rank; rank and factor of a row are looked up once for all its column tiles
-        float *pk_col[TJ];
-        int64_t pk_ld[TJ];
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
-            const int64_t n = n0 + wn + j * 32 + l32;
-            pk_col[j] = nullptr;
-            pk_ld[j] = 0;
-            if (n < g.N) {
-                if (n < pk.main_cols) { pk_col[j] = pk.base + (n >> 5) * pk.table_stride + (n & 31); pk_ld[j] = 32; }
-                else { pk_col[j] = pk.tail + (n - pk.main_cols); pk_ld[j] = pk.tail_ld; }
-            }
+            const int64_t n = n0 + j * 32 + l32, at = n * g.sbn + (k + lk) * g.sbk;
+            b[j] = (in && n < g.N && !(g.b_gate && !(g.b_gate[at] > 0.0f))) ? g.B[at] : 0.0f;
         }
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
+            for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+}
+
+// Writes a wavefront's TI x TJ result tiles, whose first element is C[m0][n0] (of partial plane bz).  EDGE: rows may lie past
+// the end.  Register v of lane l holds C[8 * (v / 4) + 4 * (l / 32) + v % 4][l % 32].
+template <int TI, int TJ, bool EDGE>
+__device__ __forceinline__ void write_rows(const GemmArgs &g, float16v (&acc)[TI][TJ], int64_t m0, int64_t n0, int64_t bz) {
+    const int l32 = threadIdx.x & 31, lk = (threadIdx.x >> 5) & 1;
+    const gnn_packed_target &pk = g.packed;
+    if (pk.active) {
+        // producer-side layout: the 32 lanes of a row write one 128-byte line of a slice table (or a piece of the
+        // tail) at the row's rank; rank and factor of a row are looked up once for all its column tiles
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int64_t m = m0 + wm + i * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
-                if (m >= g.M) continue;
+                const int64_t m = m0 + i * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
+                if (EDGE && m >= g.M) continue;
                 const int64_t row = pk.rank[m];
                 const float fac = gnn_row_factor(pk.scale_mode, pk.scale_mode ? pk.counts[m] : 0);
 #pragma unroll
-                for (int j = 0; j < TJ; ++j)
-                    if (pk_col[j]) pk_col[j][row * pk_ld[j]] = acc[i][j][v] * fac;
+                for (int j = 0; j < TJ; ++j) {
+                    const int64_t n = n0 + j * 32 + l32;
+                    if (n >= g.N) continue;
+                    float *q = n < pk.main_cols ? pk.base + (n >> 5) * pk.table_stride + row * 32 + (n & 31)
+                                                : pk.tail + row * pk.tail_ld + (n - pk.main_cols);
+                    *q = acc[i][j][v] * fac;
+                }
             }
         return;
     }
+    const bool whole = g.n_split == 1;  // else partial planes of M x ldc
+    const bool relu = g.relu && whole;
+    float *out = g.C + (whole ? 0 : bz * g.M * g.ldc) + (m0 + 4 * lk) * g.ldc + n0 + l32;
 #pragma unroll
-    for (int i = 0; i < TI; ++i)
+    for (int j = 0; j < TJ; ++j) {
+        const int64_t n = n0 + j * 32 + l32;
+        if (n >= g.N) continue;
+        const float bv = (g.bias && whole) ? g.bias[n] : 0.0f;
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            const int64_t n = n0 + wn + j * 32 + l32;
-            if (n >= g.N) continue;
-            const float bv = (g.bias && g.n_split == 1) ? g.bias[n] : 0.0f;
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int64_t m = m0 + wm + i * 32 + 8 * (v / 4) + 4 * lk + (v % 4);
-                if (m >= g.M) continue;
-                float r = acc[i][j][v] + bv;
-                if (g.relu && g.n_split == 1) r = r > 0.0f ? r : 0.0f;
-                out[m * g.ldc + n] = r;
+                const int r = i * 32 + 8 * (v / 4) + (v % 4);
+                if (EDGE && m0 + r + 4 * lk >= g.M) continue;
+                float x = acc[i][j][v] + bv;
+                if (relu) x = x > 0.0f ? x : 0.0f;
+                out[r * g.ldc + j * 32] = x;
             }
+    }
+}
+
+template <int TI, int TJ>
+__device__ __forceinline__ void write_tiles(const GemmArgs &g, float16v (&acc)[TI][TJ], int64_t m0, int64_t n0, int64_t bz) {
+    if (m0 + TI * 32 <= g.M) write_rows<TI, TJ, false>(g, acc, m0, n0, bz);
+    else write_rows<TI, TJ, true>(g, acc, m0, n0, bz);
+}
+
+// Workgroup tile (WM * TI * 32) x (WN * TJ * 32): WM x WN wavefronts, each TI x TJ MFMA tiles.
+// FOLD: 0 = plain operands; 2 = B may carry a gate and its column sums may be asked for.
+template <bool A_K_CONTIG, bool B_K_CONTIG, int WM, int WN, int TI, int TJ, int FOLD = 0>
+__global__ void __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(2, 8))) gemm_kernel(const GemmArgs g) {
+    constexpr int BM = WM * TI * 32, BN = WN * TJ * 32, THREADS = WM * WN * 64;
+    struct Tiles { SplitTile<BM> a; SplitTile<BN> b; };
+    __shared__ __attribute__((aligned(16))) Tiles tiles[2];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int wm = (wave / WN) * TI * 32, wn = (wave % WN) * TJ * 32;  // this wavefront's part of the tile
+    int64_t bx, by, bz;
+    if (!tile_of_block(g, bx, by, bz)) return;  // whole workgroup
+    const int64_t m0 = bx * BM, n0 = by * BN;
+    const int64_t k_begin = bz * g.k_per_split;
+    const int64_t k_end = k_begin + g.k_per_split < g.K ? k_begin + g.k_per_split : g.K;
+
+    float16v acc[TI][TJ];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    };
+    clear();
+
+    using StagerA = Stager<A_K_CONTIG, BM, THREADS>;
+    using StagerB = Stager<B_K_CONTIG, BN, THREADS, FOLD == 2>;
+    StagerA sa;
+    StagerB sb;
+    const bool b_gated = FOLD == 2 && g.b_gate;
+    const bool sums = FOLD == 2 && g.colsum && bx == 0;  // the first tile row also adds up the columns of B (uniform)
+    float no_sum[StagerA::PER_THREAD][2] = {}, col_sum[StagerB::PER_THREAD][2] = {};
+    const int l32 = lane & 31, lk = lane >> 5;
+    const int my_slot = SplitTile<BM>::slot(lk, l32);
+    auto stage = [&](int t) {  // registers -> LDS
+        sa.store(tiles[t & 1].a, false, false, no_sum, true, t);
+        sb.store(tiles[t & 1].b, b_gated, sums, col_sum, false, t);
+    };
+    auto multiply = [&](int step) {
+        const Tiles &t = tiles[step & 1];
+        bf16x8 a[TI][3];
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a[i][p] = __builtin_bit_cast(bf16x8, t.a.v[p][wm / 32 + i][my_slot]);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) {
+            bf16x8 b[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) b[p] = __builtin_bit_cast(bf16x8, t.b.v[p][wn / 32 + j][my_slot]);
+            float16v sum[TI];
+#pragma unroll
+            for (int i = 0; i < TI; ++i) sum_of_products(sum[i], a[i], b);
+#pragma unroll
+            for (int i = 0; i < TI; ++i) add_tile(acc[i][j], sum[i], step);
+            __builtin_amdgcn_sched_barrier(0);  // what the compiler fetches further ahead does not fit the registers
         }
+    };
+    // While tile t is multiplied, tile t + 1 is split into the other half of the LDS and tile t + 2 is on its way.  A last tile of
+    // less than 16 k is moved back to end with the part (K >= 16); what it repeats counts as 0.  Loads past the last tile
+    // repeat it, so that the loop has no branches around them.
+    const int64_t len = k_begin < k_end ? k_end - k_begin : 0;
+    const int64_t n_tiles = (len + BK - 1) / BK;
+    const int repeated = int(n_tiles * BK - len);
+    auto load = [&](int64_t t) {
+        const int64_t k = t * BK < len - BK ? t * BK : len - BK;
+        sa.load(k, false);
+        sb.load(k, b_gated);
+    };
+    auto drop = [&](int64_t t) {
+        if (t + 1 == n_tiles && repeated) {
+            sa.drop_first(repeated);
+            if constexpr (FOLD == 2) sb.drop_first(repeated);  // for its column sums
+        }
+    };
+    if (n_tiles > 0) {
+        sa.init(g.A, g.a_gate, g.sam, g.sak, m0, g.M, k_begin);
+        sb.init(g.B, g.b_gate, g.sbn, g.sbk, n0, g.N, k_begin);
+        load(0);
+        drop(0);
+        stage(0);
+        load(1);
+        __syncthreads();
+#pragma unroll 1
+        for (int64_t t = 0; t < n_tiles; ++t) {
+            multiply(int(t & 1));
+            if (t + 1 == n_tiles) break;
+            drop(t + 1);
+            stage(int((t + 1) & 1));
+            load(t + 2);
+            __syncthreads();
+        }
+    }
+
+    recompute_if_needed<TI, TJ>(g, acc, m0 + wm, n0 + wn, k_begin, k_end);
+
+    if constexpr (FOLD == 2) {
+        if (sums) {
+            // units that hold the same columns (the two halves of k) are added in order through LDS
+            static_assert(!B_K_CONTIG, "column sums are kept for row-contiguous operands only");
+            float *scr = reinterpret_cast<float *>(&tiles[0]);
+            __syncthreads();  // the operand tiles are no longer needed
+#pragma unroll
+            for (int h = 0; h < StagerB::PER_THREAD; ++h)
+                if (StagerB::has(h)) scr[StagerB::half_of(h) * BN + StagerB::row_of(h)] = col_sum[h][0] + col_sum[h][1];
+            __syncthreads();
+            for (int n = int(threadIdx.x); n < BN && n0 + n < g.N; n += THREADS) g.colsum[bz * g.N + n0 + n] = scr[n] + scr[BN + n];
+        }
+    }
+
+    write_tiles<TI, TJ>(g, acc, m0 + wm, n0 + wn, bz);
+}
+
+// Tall products: A row-major with k along its rows (a layer's forward product, and the products with W^T of its backward
+// pass).  A wavefront owns 32 rows of C and TJ * 32 columns: its elements of A go from global memory straight into the
+// lanes that need them, two steps of 16 k ahead of their use, and are split there, once; only B passes through LDS.  FEW_K: less
+// than 16 k, one step of single elements.
+template <int WAVES, int TJ, bool B_K_CONTIG, bool GATED, bool FEW_K = false>
+__global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(TJ >= 4 ? 2 : TJ == 2 && GATED ? 3 : 4, 8))) tall_kernel(const GemmArgs g) {
+    constexpr int BM = WAVES * 32, BN = TJ * 32;
+    __shared__ __attribute__((aligned(16))) SplitTile<BN> tiles[2];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int l32 = lane & 31, lk = lane >> 5;
+    int64_t bx, by, bz;
+    if (!tile_of_block(g, bx, by, bz)) return;  // whole workgroup
+    const int64_t m0 = bx * BM + wave * 32, n0 = by * BN;
+    const int my_slot = SplitTile<BN>::slot(lk, l32);
+
+    float16v acc[1][TJ];
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.0f;
+
+    // A: a lane's eight elements of a step, two steps in registers (rows past the end repeat the last one)
+    const int64_t my_row = m0 + l32 < g.M ? m0 + l32 : g.M - 1;
+    const float *pa = g.A + my_row * g.sam + lk * 8;
+    const int64_t gate_off = GATED ? g.a_gate - g.A : 0;
+    float va[2][8], ga[GATED ? 2 : 1][8];
+    auto fetch = [&](float (&x)[8], const float *q) {
+        if constexpr (FEW_K) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = i < int(g.K) - lk * 8 ? q[i] : 0.0f;
+            return;
+        }
+        const f32x4_any lo = *reinterpret_cast<const f32x4_any *>(q), hi = *reinterpret_cast<const f32x4_any *>(q + 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { x[i] = lo[i]; x[4 + i] = hi[i]; }
+    };
+    // A last step of less than 16 k is moved back to end with K (K >= 16); the elements of A that belong to the step before
+    // count as 0 there (should one of B be infinite, the result is NaN and computed again).  Loads past the last step repeat it.
+    const int64_t n_tiles = (g.K + BK - 1) / BK;
+    const int64_t k_last = g.K - BK;
+    const int repeated = FEW_K ? 0 : int(n_tiles * BK - g.K);
+    auto k_of = [&](int64_t t) { return FEW_K ? 0 : t * BK < k_last ? t * BK : k_last; };
+    auto load_a = [&](int64_t t, int p) {
+        fetch(va[p], pa + k_of(t));
+        if constexpr (GATED) fetch(ga[p], pa + k_of(t) + gate_off);
+    };
+    Stager<B_K_CONTIG, BN, WAVES * 64> sb;
+    float no_sum[decltype(sb)::PER_THREAD][2] = {};
+    // Step t (p = t % 2).  The products of a step are summed from zero, smallest first, and added to the result with one
+    // rounding: fewer and better roundings than a chain of single products has.
+    auto step = [&](int64_t t, int p) {
+        if constexpr (!FEW_K) sb.load(k_of(t + 1), false);
+        if constexpr (GATED) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) va[p][i] = ga[p][i] > 0.0f ? va[p][i] : 0.0f;
+        }
+        if (t + 1 == n_tiles && repeated) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) va[p][i] = i + lk * 8 >= repeated ? va[p][i] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) va[p][i] = __uint_as_float(__float_as_uint(va[p][i]) ^ row_sign(lane, p));
+        uint4 q[3];
+        split8(va[p], q);
+        if constexpr (!FEW_K) load_a(t + 2, p);
+        bf16x8 a[3];
+#pragma unroll
+        for (int s = 0; s < 3; ++s) a[s] = __builtin_bit_cast(bf16x8, q[s]);
+        // The parts of B for the next 32 columns are on their way while these are multiplied; the barriers keep the compiler from
+        // fetching them all ahead, which takes more registers than there are.
+        if (TJ == 8 || t < n_tiles) {
+            bf16x8 b[2][3];
+            float16v sum[2];
+#pragma unroll
+            for (int s = 0; s < 3; ++s) b[0][s] = __builtin_bit_cast(bf16x8, tiles[p].v[s][0][my_slot]);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                if (j + 1 < TJ) {
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) b[(j + 1) & 1][s] = __builtin_bit_cast(bf16x8, tiles[p].v[s][j + 1][my_slot]);
+                }
+                sum_of_products(sum[j & 1], a, b[j & 1]);
+                if (j > 0) add_tile(acc[0][j - 1], sum[(j - 1) & 1], p);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            add_tile(acc[0][TJ - 1], sum[(TJ - 1) & 1], p);
+        }
+        if constexpr (!FEW_K) {
+            sb.store(tiles[1 - p], false, false, no_sum, false, 0);
+            __syncthreads();
+        }
+    };
+    sb.init(g.B, nullptr, g.sbn, g.sbk, n0, g.N, 0);
+    if constexpr (FEW_K) {
+        sb.load_few(int(g.K));
+        load_a(0, 0);
+        sb.store(tiles[0], false, false, no_sum, false, 0);
+        __syncthreads();
+        step(0, 0);
+        recompute_if_needed<1, TJ>(g, acc, m0, n0, 0, g.K);
+        write_tiles<1, TJ>(g, acc, m0, n0, 0);
+        return;
+    }
+    sb.load(0, false);
+    load_a(0, 0);
+    __builtin_amdgcn_sched_barrier(0);  // in this order, as in the loop: what is waited for is counted
+    load_a(1, 1);
+    sb.store(tiles[0], false, false, no_sum, false, 0);
+    __builtin_amdgcn_s_waitcnt(GATED ? 0x0f74 : 0x0f72);  // vmcnt: all but the second step's
+    __syncthreads();
+#pragma unroll 1
+    for (int64_t t = 0; t < n_tiles; t += 2) {
+        step(t, 0);
+        if (TJ == 8 && t + 1 == n_tiles) break;
+        step(t + 1, 1);
+    }
+    recompute_if_needed<1, TJ>(g, acc, m0, n0, 0, g.K);
+    write_tiles<1, TJ>(g, acc, m0, n0, 0);
+}
+
+template <int WAVES, int TJ>
+void launch_tall(bool b_k, dim3 grid, hipStream_t stream, const GemmArgs &g) {
+    if (g.a_gate && b_k) tall_kernel<WAVES, TJ, true, true><<<grid, WAVES * 64, 0, stream>>>(g);
+    else if (g.a_gate) tall_kernel<WAVES, TJ, false, true><<<grid, WAVES * 64, 0, stream>>>(g);
+    else if (b_k) tall_kernel<WAVES, TJ, true, false><<<grid, WAVES * 64, 0, stream>>>(g);
+    else tall_kernel<WAVES, TJ, false, false><<<grid, WAVES * 64, 0, stream>>>(g);
+}
+
+void launch_tall_few_k(bool b_k, dim3 grid, hipStream_t stream, const GemmArgs &g) {
+    if (g.a_gate && b_k) tall_kernel<4, 2, true, true, true><<<grid, 256, 0, stream>>>(g);
+    else if (g.a_gate) tall_kernel<4, 2, false, true, true><<<grid, 256, 0, stream>>>(g);
+    else if (b_k) tall_kernel<4, 2, true, false, true><<<grid, 256, 0, stream>>>(g);
+    else tall_kernel<4, 2, false, false, true><<<grid, 256, 0, stream>>>(g);
 }
 
 template <int WM, int WN, int TI, int TJ>
-void launch_gemm(bool a_k, bool b_k, dim3 grid, hipStream_t stream, const GemmArgs &g, int a_vec, int b_vec) {
-    // the two products of a layer's backward pass that take G = (dH where H > 0) as an operand
-    if (g.a_gate && b_k) gemm_kernel<true, true, WM, WN, TI, TJ, 1><<<grid, kThreads, 0, stream>>>(g, a_vec, b_vec);
-    else if (g.a_gate) gemm_kernel<true, false, WM, WN, TI, TJ, 1><<<grid, kThreads, 0, stream>>>(g, a_vec, b_vec);
-    else if (g.b_gate || g.colsum) gemm_kernel<false, false, WM, WN, TI, TJ, 2><<<grid, kThreads, 0, stream>>>(g, a_vec, b_vec);
-    else if (a_k && !b_k) gemm_kernel<true, false, WM, WN, TI, TJ><<<grid, kThreads, 0, stream>>>(g, a_vec, b_vec);
-    else if (a_k && b_k) gemm_kernel<true, true, WM, WN, TI, TJ><<<grid, kThreads, 0, stream>>>(g, a_vec, b_vec);
-    else if (!a_k && !b_k) gemm_kernel<false, false, WM, WN, TI, TJ><<<grid, kThreads, 0, stream>>>(g, a_vec, b_vec);
-    else gemm_kernel<false, true, WM, WN, TI, TJ><<<grid, kThreads, 0, stream>>>(g, a_vec, b_vec);
+void launch_gemm(bool b_k, dim3 grid, hipStream_t stream, const GemmArgs &g) {
+    constexpr int T = WM * WN * 64;
+    // the product of a layer's backward pass that takes G = (dH where H > 0) as its second operand
+    if (g.b_gate || g.colsum) gemm_kernel<false, false, WM, WN, TI, TJ, 2><<<grid, T, 0, stream>>>(g);
+    else if (!b_k) gemm_kernel<false, false, WM, WN, TI, TJ><<<grid, T, 0, stream>>>(g);
+    else gemm_kernel<false, true, WM, WN, TI, TJ><<<grid, T, 0, stream>>>(g);
+}
+
+// k along the rows of A, few tiles and a long k
+void launch_rows(bool b_k, dim3 grid, hipStream_t stream, const GemmArgs &g) {
+    if (b_k) gemm_kernel<true, true, 2, 2, 2, 2><<<grid, 256, 0, stream>>>(g);
+    else gemm_kernel<true, false, 2, 2, 2, 2><<<grid, 256, 0, stream>>>(g);
+}
+
+// Less than 16 k where the tall kernel does not apply (a weight gradient over a few rows): one result per thread.
+__global__ void __launch_bounds__(256) few_k_kernel(const GemmArgs g) {
+    const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (t >= g.M * g.N) return;
+    const int64_t m = t / g.N, n = t - m * g.N;
+    float x = 0.0f, col = 0.0f;
+    for (int64_t k = 0; k < g.K; ++k) {
+        const int64_t ib = k * g.sbk + n * g.sbn;
+        const float b = (g.b_gate && !(g.b_gate[ib] > 0.0f)) ? 0.0f : g.B[ib];
+        x = fmaf(g.A[m * g.sam + k * g.sak], b, x);
+        col += b;
+    }
+    if (g.colsum && m == 0) g.colsum[n] = col;
+    if (g.bias) x += g.bias[n];
+    if (g.relu) x = x > 0.0f ? x : 0.0f;
+    g.C[m * g.ldc + n] = x;
 }
 
 // C = act(sum over the partial planes + bias).  A workgroup owns 64 consecutive outputs; its wavefronts take every
@@ -419,20 +674,39 @@ __global__ void __launch_bounds__(kReduceWaves * 64) gemm_reduce_kernel(const fl
 
 }  // namespace
 
-// How many partial planes the reduction over k is split into.
-// Tile width: 128 columns, or 64 / 32 (with 256 rows) for narrow outputs such as class scores.
-static void choose_tile(int64_t N, int64_t *bm, int64_t *bn) {
-    if (N > 64) { *bm = 128; *bn = 128; }
-    else if (N > 32) { *bm = 256; *bn = 64; }
-    else { *bm = 256; *bn = 32; }
+// Tile of a workgroup, for the weight gradients: a long k, read once where N fits the tile's width.  resident: parts of k that a
+// compute unit gets.  Narrow tiles are small so that several workgroups, each waiting for memory, share a compute unit
+// (602 x 16 over 232,965 rows: 306 us with tiles of 256 rows, two to a unit; 114 with 128 and five).
+struct TileShape { int64_t bm, bn; int resident; };
+
+static TileShape choose_tile(int64_t M, int64_t N) {
+    if (N <= 32) return {128, 32, 5};
+    if (N <= 64) return {128, 64, 4};
+    if (N <= 128) return {128, 128, 2};
+    return {128, 256, 2};
 }
 
+// Tile of a tall product: wavefronts of 32 rows, tiles of 32 columns.  As wide as the result, so that A is read and split once
+// (2.45 M rows, 256 -> 47: 0.70 ms with two column tiles, 0.98 with one; 256 -> 256 2.0 with eight, 2.2 with four, 2.4 with
+// two), unless that leaves compute units without a workgroup: 24,490 rows 256 -> 256 take 46 us with tiles of 256 x 256 and
+// 31 with 128 x 64, 60,000 rows 128 -> 256 take 36 and 40.
+struct TallShape { int waves, tj; };
+
+static TallShape choose_tall(int64_t M, int64_t N) {
+    const int waves = M >= 65536 ? 8 : 4;
+    if (N <= 32) return {waves, 1};
+    if (N <= 64) return {waves, 2};
+    if (N <= 128) return {4, (M + 127) / 128 >= 512 ? 4 : 2};
+    if ((M + 255) / 256 * ((N + 255) / 256) < 192) return {4, 2};
+    return {8, 8};
+}
+
+// How many partial planes the reduction over k is split into.
 static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
-    int64_t BM, BN;
-    choose_tile(N, &BM, &BN);
-    const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+    const TileShape s = choose_tile(M, N);
+    const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);
     if (tiles >= 512 || K < 1024) return 1;
-    int64_t split = (1024 + tiles - 1) / tiles;           // aim at ~4 workgroups per compute unit
+    int64_t split = (256 * s.resident + tiles - 1) / tiles;
     // At least GNN_SPLIT_MIN_K k-steps per part: a part is bound by the latency of its tiles of 16 k-steps, one after the other, while
     // the chip is not full (24,490 rows into 256 x 256: 0.20 ms with parts of 1024, 0.05 with 128); the partial planes
     // cost little beside that.
@@ -490,6 +764,7 @@ int gnn_matmul_impl(const float *A, int64_t lda, int trans_a, const float *B, in
         split = 1;
         g.packed = *packed;
     }
+    if (g.a_gate) split = 1;
     if (fold && fold->colsum) {
         if (fold->colsum_planes < split) return GNN_ERR_INVALID_ARG;
         fold->n_planes = split;
@@ -500,10 +775,13 @@ int gnn_matmul_impl(const float *A, int64_t lda, int trans_a, const float *B, in
         g.C = static_cast<float *>(workspace);
         g.ldc = N;
     }
-    int64_t BM, BN;
-    choose_tile(N, &BM, &BN);
+    // the tall kernel takes every product with k along the rows of A whose reduction is not split
+    const bool tall = !trans_a && split == 1;
+    const TallShape ts = K < BK ? TallShape{4, 2} : choose_tall(M, N);
+    const TileShape s = tall ? TileShape{ts.waves * 32, ts.tj * 32, 1} : trans_a ? choose_tile(M, N) : TileShape{128, 128, 2};
+    const int64_t BM = s.bm, BN = s.bn;
     const int64_t gx = (M + BM - 1) / BM, gy = (N + BN - 1) / BN;
-    if (gx > INT32_MAX || gy > 65535 || split > 65535) return GNN_ERR_UNSUPPORTED;
+    if (gx > INT32_MAX || gy > INT32_MAX || split > 65535) return GNN_ERR_UNSUPPORTED;
     g.gx = int32_t(gx); g.gy = int32_t(gy); g.gz = int32_t(split);
     int64_t n_groups = gx * gy * split;
     const int64_t inner = split > 1 ? gx * gy : gy, outer = split > 1 ? split : gx;
@@ -513,12 +791,25 @@ int gnn_matmul_impl(const float *A, int64_t lda, int trans_a, const float *B, in
     }
     if (n_groups > INT32_MAX) return GNN_ERR_UNSUPPORTED;
     dim3 grid(static_cast<unsigned>(n_groups));
-    const int a_vec = (lda % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 && reinterpret_cast<uintptr_t>(g.a_gate) % 16 == 0) ? 1 : 0;
-    const int b_vec = (ldb % 4 == 0 && reinterpret_cast<uintptr_t>(B) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b_gate) % 16 == 0) ? 1 : 0;
-    const bool a_k = !trans_a, b_k = trans_b != 0;  // is k the contiguous direction of the operand?
-    if (BN == 128) launch_gemm<2, 2, 2, 2>(a_k, b_k, grid, stream, g, a_vec, b_vec);
-    else if (BN == 64) launch_gemm<4, 1, 2, 2>(a_k, b_k, grid, stream, g, a_vec, b_vec);
-    else launch_gemm<4, 1, 2, 1>(a_k, b_k, grid, stream, g, a_vec, b_vec);
+    const bool b_k = trans_b != 0;  // is k the contiguous direction of the operand?
+    if (tall && K < BK) {
+        launch_tall_few_k(b_k, grid, stream, g);
+    } else if (K < BK) {
+        const int64_t blocks = (M * N + 255) / 256;
+        if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
+        few_k_kernel<<<static_cast<unsigned>(blocks), 256, 0, stream>>>(g);
+    } else if (tall) {
+        if (ts.tj == 8) launch_tall<8, 8>(b_k, grid, stream, g);
+        else if (ts.tj == 4) launch_tall<4, 4>(b_k, grid, stream, g);
+        else if (ts.tj == 2 && ts.waves == 8) launch_tall<8, 2>(b_k, grid, stream, g);
+        else if (ts.tj == 2) launch_tall<4, 2>(b_k, grid, stream, g);
+        else if (ts.waves == 8) launch_tall<8, 1>(b_k, grid, stream, g);
+        else launch_tall<4, 1>(b_k, grid, stream, g);
+    } else if (!trans_a) launch_rows(b_k, grid, stream, g);
+    else if (BN == 256) launch_gemm<2, 4, 2, 2>(b_k, grid, stream, g);
+    else if (BN == 128) launch_gemm<2, 2, 2, 2>(b_k, grid, stream, g);
+    else if (BN == 64) launch_gemm<4, 1, 1, 2>(b_k, grid, stream, g);
+    else launch_gemm<4, 1, 1, 1>(b_k, grid, stream, g);
     if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     if (split > 1) {
         const int64_t blocks = (M * N + 63) / 64;

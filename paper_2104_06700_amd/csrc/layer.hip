@@ -131,19 +131,6 @@ void launch_colsum_reduce(const float *partial, int64_t n, int F, float *tmp, fl
     colsum_reduce_kernel<<<dim3(1, col_blocks), 256, 0, stream>>>(partial, n, F, db, n, log2_cols);
 }
 
-// Wt[c, r] = W[r, c] for a weight matrix (small next to everything else in a layer).  The products with W^T
-// take the transposed copy as a row-contiguous operand: staged with 16-byte loads and stores, where the
-// k-contiguous form of the same operand costs four 4-byte LDS stores per quad (dZ at 256 -> 256 on 2.45 M
-// vertices: 4.2 -> 3.x ms).
-__global__ void __launch_bounds__(256) transpose_kernel(const float *__restrict__ W, float *__restrict__ Wt, int rows, int cols) {
-    const int64_t total = int64_t(rows) * cols;
-    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-    for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < total; t += stride) {
-        const int64_t c = t / rows, r = t - c * rows;  // consecutive threads write consecutive elements of Wt
-        Wt[t] = W[r * cols + c];
-    }
-}
-
 __global__ void __launch_bounds__(256) zero_kernel(float *__restrict__ p, int64_t n) {
     const int64_t stride = int64_t(gridDim.x) * blockDim.x;
     for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < n; t += stride) p[t] = 0.0f;
@@ -158,7 +145,7 @@ bool aggregate_first(int order, int64_t Fi, int64_t Fo) { return order == 1 || (
 int64_t gather_ld(int64_t Fo) { return round_up(Fo, 4); }
 
 struct BwdLayout {
-    int64_t g_off, t_off, part_off, part2_off, wt_off, mm_off, total;
+    int64_t g_off, t_off, part_off, part2_off, mm_off, total;
     int64_t total_unfolded;  // with room for G behind everything else (aggregate first, rectifier, GNN_LAYER_NO_GATE_FOLD)
 };
 
@@ -174,8 +161,6 @@ BwdLayout bwd_layout(int64_t N, int64_t Fi, int64_t Fo, bool agg_first, bool rel
     off += round_up(n_blocks * Fo * 4, 256);
     L.part2_off = off;
     off += round_up(((n_blocks + 255) / 256) * Fo * 4, 256);
-    L.wt_off = off;
-    off += round_up(Fi * Fo * 4, 256);  // W transposed
     L.mm_off = off;
     off += round_up(gnn_matmul_workspace_bytes(Fi, Fo, N), 256);
     L.total = off;
@@ -338,10 +323,7 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
         // stream runs the gather-bound backward aggregation
         gnn_gemm_fold fold_a{};
         fold_a.a_gate = gate;
-        float *Wt = reinterpret_cast<float *>(ws + L.wt_off);
-        transpose_kernel<<<64, 256, 0, stream>>>(W, Wt, int(F_in), int(F_out));
-        if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
-        rc = gnn_matmul_impl(Gm, F_out, 0, Wt, F_in, 0, T, F_in, N, F_in, F_out, nullptr, 0, nullptr, 0, stream, &pk, &fold_a);
+        rc = gnn_matmul_impl(Gm, F_out, 0, W, F_out, 1, T, F_in, N, F_in, F_out, nullptr, 0, nullptr, 0, stream, &pk, &fold_a);
         if (rc != GNN_OK) return rc;
         hipStream_t side = side_stream();
         hipEvent_t fork = nullptr, join = nullptr;
@@ -378,8 +360,5 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
     if (rc != GNN_OK) return rc;
     rc = gnn_matmul_impl(X, F_in, 1, T, ldg, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, stream);
     if (rc != GNN_OK || !dX) return rc;
-    float *Wt = reinterpret_cast<float *>(ws + L.wt_off);
-    transpose_kernel<<<64, 256, 0, stream>>>(W, Wt, int(F_in), int(F_out));
-    if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
-    return gnn_matmul_impl(T, ldg, 0, Wt, F_in, 0, dX, F_in, N, F_in, F_out, nullptr, 0, nullptr, 0, stream);
+    return gnn_matmul_impl(T, ldg, 0, W, F_out, 1, dX, F_in, N, F_in, F_out, nullptr, 0, nullptr, 0, stream);
 }

@@ -12,8 +12,8 @@ from helpers import device_graph, host_csr
 pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
-# fp32 products are exact on the matrix cores; the accumulation of K terms in fp32 (in tiles of
-# 16, partial planes of >= 1024) and the fp32 aggregation before or after it leave an error of
+# fp32 products are exact on the matrix cores but for 2^-24 of S; the accumulation of K terms in fp32 (in steps of
+# 16, partial planes of >= 128) and the fp32 aggregation before or after it leave an error of
 # at most (1e-5 + K * 2^-24) * S in the worst case and ~sqrt(K) * 2^-24 * S typically, S being the
 # sum of the absolute values of all terms; gate at 2e-5 * S.
 RTOL_LAYER = 2e-5
@@ -372,3 +372,58 @@ def test_layer_int64_row_pointers():
     torch.cuda.synchronize()
     _, Ho, SH = oracle.sage_layer_fwd(indptr, indices, X, W, None, False)
     _close(H, Ho, SH, "layer forward, int64 row pointers")
+
+
+# ------------------------------------------------------------------ the split operands of the matrix cores
+@pytest.mark.parametrize("k", [1, 9, 15, 17, 32, 47])
+@pytest.mark.parametrize("m,n", [(31, 33), (300, 65), (513, 257)])
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
+def test_matmul_edges_of_the_steps_of_k(m, n, k, ta, tb):
+    """Steps of 16 k: less than one, a last one that is moved back over the step before, odd and even numbers of them; tiles of every
+    width.  A product drops at most 2^-24 of S (three of nine partial products, 2^-26 each) and its sums are fp32: with
+    k <= 100 far below 1e-6 * S."""
+    rng = np.random.default_rng(1000 * k + m + n)
+    A = rng.normal(size=(k, m) if ta else (m, k)).astype(np.float32)
+    B = rng.normal(size=(n, k) if tb else (k, n)).astype(np.float32)
+    C = torch.full((m, n), float("nan"), device=DEV)
+    gnn.gnn_matmul(torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV), C, ta, tb)
+    torch.cuda.synchronize()
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    A64, B64 = (A64.T if ta else A64), (B64.T if tb else B64)
+    _close(C, A64 @ B64, np.abs(A64) @ np.abs(B64), f"m={m} n={n} k={k} ta={ta} tb={tb}", rtol=1e-6)
+
+
+@pytest.mark.parametrize("m,n,k,ta", [(70_000, 200, 40, False), (60_000, 47, 33, False), (66_000, 16, 50, False), (200, 140, 30_011, True),
+                                      (130, 60, 2_000, True), (100, 20, 5_003, True), (100, 100, 3_000, True), (64, 64, 2_048, False)])
+def test_matmul_of_operands_outside_the_split(m, n, k, ta):
+    """Infinities, NaNs and values near the largest float have no exact three parts, and tiny ones lose their last: the tiles they
+    take part in are computed from the operands as they are."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(m + n + k)
+    A = torch.empty(k if ta else m, m if ta else k, device=DEV).normal_(generator=gen)
+    B = torch.empty(k, n, device=DEV).normal_(generator=gen)
+    flat = A.view(-1)
+    flat[17], flat[1000], flat[-3], flat[-1] = float("inf"), float("nan"), -float("inf"), 3.4e38
+    rows = A.t() if ta else A
+    rows[5] = 0.0          # a row of zeros stays zero
+    rows[7] *= 2.0 ** -118  # results far below 2^-90
+    B[k // 2, n // 2] = 0.0
+    need = gnn.gnn_matmul_workspace_bytes(m, n, k)
+    ws = torch.empty(max(need // 4, 4), device=DEV)
+    C = torch.empty(m, n, device=DEV)
+    gnn.gnn_matmul(A, B, C, trans_a=ta, workspace=ws)
+    torch.cuda.synchronize()
+    a64, b64 = rows.double(), B.double()
+    ref = torch.cat([a64[i:i + 4096].contiguous() @ b64 for i in range(0, m, 4096)])
+    S = torch.cat([a64[i:i + 4096].abs().contiguous() @ b64.abs() for i in range(0, m, 4096)])
+    ref32 = ref.float()
+    odd = ~torch.isfinite(ref32)
+    # where a sum passes the largest float on its way depends on its order: 3.4e38 is one operand of it
+    near = (S > 1e37) & ~odd
+    assert torch.equal(torch.isnan(C) & ~near, torch.isnan(ref32) & ~near)
+    assert torch.equal(C[odd & ~torch.isnan(ref32)], ref32[odd & ~torch.isnan(ref32)])
+    good = ~odd & ~near
+    assert good.any()
+    err = (C.double() - ref).abs()[good]
+    assert bool((err <= 2e-5 * S[good] + 2.0 ** -148).all())
+    assert bool((C[5][good[5]] == 0).all())

@@ -10,8 +10,8 @@
 // A workgroup is 16 wavefronts; L lanes (16 bytes each: L = 8, 4 or 2 for lines of 128, 64 or 32 bytes) own a
 // row, so a wavefront works on a bundle of 64 / L rows at a time, and it owns up to ten bundles.  The lists are
 // stored the way they are read, one stream per wavefront: for every tile, for every bundle of the wavefront, units
-// of four edges per row as 16-bit offsets into the tile; the shorter rows of a bundle are filled up with the
-// offset of a line of zeros behind the tile.  Rows are bundled by similar number of edges, a row much longer
+// of four edges per row as 16-bit offsets into the tile, in an order that spreads a read over the banks (BankOrder); the
+// shorter rows of a bundle are filled up with the offsets of lines of zeros behind the tile.  Rows are bundled by similar number of edges, a row much longer
 // than the mean is cut into parts (else it alone would set the time of its workgroup: worst workgroup 4.1 x the
 // mean without, 1.02 x with), and the bundles are dealt to the wavefronts like cards.
 //
@@ -222,51 +222,158 @@ __global__ void __launch_bounds__(256) tile_counts_kernel(const uint2 *__restric
     }
 }
 
+// Order of a row's edges into a tile.  The LDS serves a 16-byte read of 64 lanes four times 16 lanes at a time, 64 banks of 4
+// bytes each: of every 32 lanes first the quads 0, 3, 5, 6, then 1, 2, 4, 7.  L lanes read a line of 16 * L bytes, so a line
+// lies in one of C = 16 / L classes of banks (line % C), and C rows of a bundle are served together: where two of their lines
+// are of one class, one waits.  (Measured: 4.5 clocks per read of a compute unit without conflicts, 8.1 with.)  So the slots of
+// the C rows are cut into C sections, and row i of them puts its lines of class (i + t) % C into section t; what does not
+// fit goes where other classes left room, and lines of zeros of the fitting class fill the rest.
+template <int L>
+struct BankOrder {
+    static constexpr int C = 16 / L;
+    int pos;              // of the row among the C rows
+    int begin[C], size[C];  // sections
+    int n[C];             // edges of the row that belong in each
+
+    // position of row g of a bundle among the rows it is served with; those are the g that lay_out() takes the maximum over
+    static __device__ __forceinline__ int position(int g) {
+        return L == 2 ? ((g & 15) >> 2) * 2 + (g & 1) : (g & (C * 2 - 1)) >> 1;
+    }
+    __device__ __forceinline__ int section(int line) const { return (line - pos) & (C - 1); }
+    __device__ __forceinline__ int line_class(int t) const { return (pos + t) & (C - 1); }
+
+    // n is set; n_slots = slots of every row of the bundle.  All lanes of the wavefront call it.
+    __device__ __forceinline__ void lay_out(int n_slots) {
+        int need[C], total = 0;
+#pragma unroll
+        for (int t = 0; t < C; ++t) {
+            int m = n[t];
+            if (L == 2) m = max(m, __shfl_xor(m, 1 * L));
+            m = max(m, __shfl_xor(m, (L == 2 ? 6 : 3) * L));
+            if (L < 8) m = max(m, __shfl_xor(m, (L == 2 ? 10 : 5) * L));
+            need[t] = m;
+            total += m;
+        }
+        int run = 0, sum = 0;
+#pragma unroll
+        for (int t = 0; t < C; ++t) {
+            begin[t] = run;
+            sum += need[t];
+            run = t == C - 1 ? n_slots : (total <= n_slots ? run + need[t] : n_slots * sum / total);
+            size[t] = run - begin[t];
+        }
+    }
+    // slot number `k` of those that the sections' own edges leave free
+    __device__ __forceinline__ int free_slot(int k) const {
+        int at = 0;
+        bool found = false;
+#pragma unroll
+        for (int t = 0; t < C; ++t) {
+            const int room = size[t] > n[t] ? size[t] - n[t] : 0;
+            if (!found && k < room) { at = begin[t] + n[t] + k; found = true; }
+            k -= room;
+        }
+        return at;
+    }
+    // slot of edge number j of section t
+    __device__ __forceinline__ int slot(int t, int j) const {
+        int at = 0, before = 0;  // edges of the sections before that do not fit
+        bool fits = false;
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            if (q == t) { fits = j < size[q]; at = fits ? begin[q] + j : j - size[q]; }
+            if (q < t && n[q] > size[q]) before += n[q] - size[q];
+        }
+        return fits ? at : free_slot(before + at);
+    }
+    __device__ __forceinline__ int overflow() const {
+        int x = 0;
+#pragma unroll
+        for (int t = 0; t < C; ++t) x += n[t] > size[t] ? n[t] - size[t] : 0;
+        return x;
+    }
+};
+
 // One wavefront per (wavefront of the gather, tile): its stretch of the stream.  W: also (or only) the coefficients,
-// w[epos] * scale[epos] of every edge and 0 where a row is filled up.
-template <bool INDICES, bool W>
+// w[epos] * scale[epos] of every edge and 0 where a row is filled up.  L lanes own a row.
+template <int L, bool INDICES, bool W>
 __global__ void __launch_bounds__(256) tile_fill_kernel(const TileDesc *__restrict__ tiles, int n_tiles, int64_t n_waves, int rr,
-                                                        int rows_per_bundle, const uint2 *__restrict__ seg, int64_t n_parts,
+                                                        const uint2 *__restrict__ seg, int64_t n_parts,
                                                         const uint8_t *__restrict__ counts, const uint32_t *__restrict__ wave_off,
                                                         const int32_t *__restrict__ blk_indices, const uint32_t *__restrict__ blk_epos,
                                                         const float *__restrict__ w, const float *__restrict__ scale,
-                                                        int zero_index, uint16_t *__restrict__ stream, float *__restrict__ wstream) {
-    const int lane = threadIdx.x & 63;
-    const int slots = rows_per_bundle * kUnit;  // of one unit
-    const int64_t n_bundles = (n_parts + rows_per_bundle - 1) / rows_per_bundle;
+                                                        int zero_line, uint16_t *__restrict__ stream, float *__restrict__ wstream) {
+    constexpr int ROWS = 64 / L, SLOTS = ROWS * kUnit, C = BankOrder<L>::C;
+    const int lane = threadIdx.x & 63, g = lane / L, c = lane & (L - 1);
+    const unsigned long long row_lanes = ((1ull << L) - 1ull) << (lane & ~(L - 1));
+    const unsigned long long before_me = row_lanes & ((1ull << lane) - 1ull);
+    const int64_t n_bundles = (n_parts + ROWS - 1) / ROWS;
     const int64_t total = n_waves * n_tiles;
     const int64_t n_workers = int64_t(gridDim.x) * (blockDim.x >> 6);
     for (int64_t x = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6); x < total; x += n_workers) {
         const int64_t wv = x / n_tiles;
         const int t = int(x - wv * n_tiles);
         const int32_t tile_begin = tiles[t].begin;
-        int64_t out = int64_t(wave_off[x]) * slots;
+        int64_t out = int64_t(wave_off[x]) * SLOTS;
         for (int r = 0; r < rr; ++r) {
             const int n_it = counts[x * kCounts + r];
-            const int64_t i0 = dealt_bundle(wv, r, n_waves, n_bundles) * rows_per_bundle;
-            const int64_t n_slots = int64_t(n_it) * slots;
-            for (int64_t s = lane; s < n_slots; s += 64) {
-                const int64_t it = s / slots;
-                const int in = int(s - it * slots);
-                const int64_t i = i0 + in / kUnit;
-                int idx = zero_index;
-                float cf = 0.0f;
-                if (i < n_parts) {
-                    const uint2 sg = seg[int64_t(t) * n_parts + i];
-                    const uint64_t e = uint64_t(sg.x) + uint64_t(it) * kUnit + (in % kUnit);
-                    if (e < sg.y) {
-                        if (INDICES) idx = blk_indices[e] - tile_begin;
-                        if (W) {
-                            const uint32_t p = blk_epos[e];
-                            cf = w ? w[p] : 1.0f;
-                            if (scale) cf *= scale[p];
-                        }
-                    }
+            const int64_t i = dealt_bundle(wv, r, n_waves, n_bundles) * ROWS + g;
+            uint2 sg = make_uint2(0u, 0u);
+            if (n_it > 0 && i >= 0 && i < n_parts) sg = seg[int64_t(t) * n_parts + i];
+            BankOrder<L> order;
+            order.pos = BankOrder<L>::position(g);
+            // number of the lane's edge within its section, counted on; every lane of a row holds the row's counts
+            auto count = [&](int sec, bool valid, int &mine) {
+                mine = 0;
+#pragma unroll
+                for (int q = 0; q < C; ++q) {
+                    const unsigned long long m = __ballot(valid && sec == q);
+                    if (sec == q) mine = order.n[q] + __popcll(m & before_me);
+                    order.n[q] += __popcll(m & row_lanes);
                 }
-                if (INDICES) stream[out + s] = uint16_t(idx);
-                if (W) wstream[out + s] = cf;
+            };
+            auto section_of = [&](uint32_t e) { return order.section(blk_indices[e] - tile_begin); };
+#pragma unroll
+            for (int q = 0; q < C; ++q) order.n[q] = 0;
+            for (uint32_t e0 = sg.x; __any(e0 < sg.y); e0 += L) {
+                int unused;
+                const bool valid = e0 + c < sg.y;
+                count(valid ? section_of(e0 + c) : 0, valid, unused);
             }
-            out += n_slots;
+            const int n_slots = n_it * kUnit;
+            order.lay_out(n_slots);
+            auto put = [&](int slot, int idx, float cf) {
+                const int64_t at = out + int64_t(slot / kUnit) * SLOTS + g * kUnit + slot % kUnit;
+                if (INDICES) stream[at] = uint16_t(idx);
+                if (W) wstream[at] = cf;
+            };
+            const int spare = n_slots - int(sg.y - sg.x), over = order.overflow();
+            for (int k = c; k < spare; k += L) {  // the lines of zeros
+                const int slot = order.free_slot(over + k);
+                int sec = 0;
+#pragma unroll
+                for (int q = 1; q < C; ++q) sec = slot >= order.begin[q] ? q : sec;
+                put(slot, zero_line + order.line_class(sec), 0.0f);
+            }
+            const BankOrder<L> whole = order;
+#pragma unroll
+            for (int q = 0; q < C; ++q) order.n[q] = 0;
+            for (uint32_t e0 = sg.x; __any(e0 < sg.y); e0 += L) {
+                const uint32_t e = e0 + c;
+                const bool valid = e < sg.y;
+                const int sec = valid ? section_of(e) : 0;
+                int j;
+                count(sec, valid, j);
+                if (!valid) continue;
+                float cf = 0.0f;
+                if (W) {
+                    const uint32_t p = blk_epos[e];
+                    cf = w ? w[p] : 1.0f;
+                    if (scale) cf *= scale[p];
+                }
+                put(whole.slot(sec, j), blk_indices[e] - tile_begin, cf);
+            }
+            out += int64_t(n_it) * SLOTS;
         }
     }
 }
@@ -327,6 +434,8 @@ __device__ __forceinline__ u32x4 lds_line(uint32_t two, uint32_t lds0) {
 }
 
 // Bytes of LDS the tile of lines of L * 16 bytes takes, the line of zeros included: what the streams leave of 160 KB.
+// Of them the last are zeros, one per class of banks (BankOrder).
+__host__ __device__ constexpr int zero_lines(int L) { return 16 / L; }
 __host__ __device__ constexpr int tile_bytes(int L) { return (L == 8 ? 124 : (L == 4 ? 120 : 112)) << 10; }
 
 // Value of lane J of each quad (PAIR: lane J of each pair of lanes) in all of its lanes.
@@ -341,7 +450,7 @@ __global__ void __launch_bounds__(kTileThreads) tile_kernel(const TileArgs a) {
     constexpr int VEC = BF16 ? 8 : 4;             // elements per lane
     constexpr int LOG2L = L == 8 ? 3 : (L == 4 ? 2 : 1);
     constexpr int ROWS = 64 / L;                  // rows of a bundle
-    constexpr int TS = tile_bytes(L) / (16 * L);  // lines of the tile, the last one zeros
+    constexpr int TS = tile_bytes(L) / (16 * L);  // lines of the tile, the last zero_lines(L) of them zeros
     constexpr int CHUNKS = (TS * L + kTileThreads - 1) / kTileThreads;
     constexpr int AHEAD = 128 / ROWS;             // units that 1 KB of the offsets lasts
     constexpr int W_AHEAD = AHEAD / 2;            // ... and of the coefficients
@@ -466,7 +575,7 @@ __global__ void __launch_bounds__(kTileThreads) tile_kernel(const TileArgs a) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int x = int(threadIdx.x) + (h + i) * kTileThreads;
-                // a tile has at most TS - 1 lines: the last one, and what is behind a shorter tile, are zeros
+                // the last zero_lines(L) lines, and what is behind a shorter tile, are zeros
                 if (x < TS * L) tile[x] = x < n_chunks ? v[i] : u32x4{0u, 0u, 0u, 0u};
             }
         }
@@ -537,7 +646,7 @@ int64_t row_blocks_for(int64_t n_bundles, int rr) {
 int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn_tiles &B) {
     const int64_t n_hot = plan->blk_n_hot;
     const int n_blocks = plan->blk_n_blocks;
-    const int tile_lines = tile_bytes(lanes) / (16 * lanes) - 1;  // and the line of zeros
+    const int tile_lines = tile_bytes(lanes) / (16 * lanes) - zero_lines(lanes);
     const int rows = 64 / lanes;
     (void)hipGetLastError();
     Scratch tmp(stream);
@@ -674,9 +783,13 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     B.max_groups = int32_t(2 * total / most_work);  // groups are whole tiles: of twice as many none is much longer than that tile
     if ((rc = gnn_scan_exclusive_u32(B.wave_off, n_wt, sums, stream)) != GNN_OK) return rc;
     if (!gnn_dev_alloc(&B.stream, (total + kStreamAhead) * rows * kUnit, stream)) return GNN_ERR_ALLOC;
-    tile_fill_kernel<true, false><<<grid_for(n_wt * 64, 256), 256, 0, stream>>>(d_tiles, n_tiles, n_waves, rr, rows, seg, n_parts,
-                                                                            B.counts, B.wave_off, plan->blk_indices, nullptr, nullptr,
-                                                                            nullptr, tile_lines, B.stream, nullptr);
+    auto fill_stream = [&](auto lanes_of_a_row) {
+        tile_fill_kernel<decltype(lanes_of_a_row)::value, true, false><<<grid_for(n_wt * 64, 256), 256, 0, stream>>>(
+            d_tiles, n_tiles, n_waves, rr, seg, n_parts, B.counts, B.wave_off, plan->blk_indices, nullptr, nullptr, nullptr, tile_lines, B.stream, nullptr);
+    };
+    if (lanes == 8) fill_stream(std::integral_constant<int, 8>());
+    else if (lanes == 4) fill_stream(std::integral_constant<int, 4>());
+    else fill_stream(std::integral_constant<int, 2>());
     GNN_HIP_TRY(hipGetLastError());
 
     // the cells that are not staged stay pieces
@@ -754,13 +867,17 @@ int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles_in, const float *
         slot = &L.bound_w;
         fill = !*slot || L.bound_version != plan->bound_w_version;
     }
-    const int rows = 64 / L.lanes;
     const int rc = coef_room(L, slot, stream);
     if (rc != GNN_OK) return rc;
     if (fill) {
-        tile_fill_kernel<false, true><<<grid_for(L.n_waves * L.n_tiles * 64, 256), 256, 0, stream>>>(
-            static_cast<const TileDesc *>(L.tiles), L.n_tiles, L.n_waves, L.rr, rows, static_cast<const uint2 *>(L.seg), L.n_parts, L.counts, L.wave_off,
-            plan->blk_indices, plan->blk_epos, w, scale, 0, nullptr, *slot);
+        auto coefs = [&](auto lanes_of_a_row) {
+            tile_fill_kernel<decltype(lanes_of_a_row)::value, false, true><<<grid_for(L.n_waves * L.n_tiles * 64, 256), 256, 0, stream>>>(
+                static_cast<const TileDesc *>(L.tiles), L.n_tiles, L.n_waves, L.rr, static_cast<const uint2 *>(L.seg), L.n_parts, L.counts, L.wave_off,
+                plan->blk_indices, plan->blk_epos, w, scale, 0, nullptr, *slot);
+        };
+        if (L.lanes == 8) coefs(std::integral_constant<int, 8>());
+        else if (L.lanes == 4) coefs(std::integral_constant<int, 4>());
+        else coefs(std::integral_constant<int, 2>());
         if (hipGetLastError() != hipSuccess) {
             if (slot != &L.tmp_w && slot != &L.bound_w) {  // an unfilled array must not serve a later call
                 gnn_dev_free(*slot);

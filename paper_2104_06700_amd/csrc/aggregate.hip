@@ -90,6 +90,8 @@ struct AggArgs {
     const int32_t *row_map;  // row of the gathered table that holds vertex v (rank layout), or nullptr: v
     const int64_t *p_indptr;  // rank layout: edge range of the row at position i of row_perm within `indices`
     const int64_t *p_chunks;  // rank layout: hub pieces (row, begin, end, original - plan-order position)
+    const void *own_X;    // the caller's matrix, where the gathered copy lacks rows that are read as own rows only; or nullptr
+    int64_t own_ld;
     int32_t cold_on;      // honour the cold flag (bit 31) of the indices
     int32_t warm_rank;    // rank layout: sources of rank >= this are cold too (INT32_MAX: none)
     int64_t slice_stride;  // > 0: slice-major copy, slice s of the launch reads the table at X + s * slice_stride elements
@@ -568,7 +570,21 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
         if (!col_ok[p]) continue;
         if (a.self_mode != kSelfNone) {  // Section 6.1: the vertex's own vector joins the sum
             float xs[VEC];
-            VecIO<T, VEC>::load(X + self_row * ldx + lcol[p], xs);
+            if (!a.own_X) {
+                VecIO<T, VEC>::load(X + self_row * ldx + lcol[p], xs);
+            } else {
+                const T *own = static_cast<const T *>(a.own_X) + row * a.own_ld + col[p];
+                if (ncols[p] == VEC) {
+                    VecIO<T, VEC>::load(own, xs);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) {
+                        float one[1] = {0.0f};
+                        if (i < ncols[p]) VecIO<T, 1>::load(own + i, one);
+                        xs[i] = one[0];
+                    }
+                }
+            }
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[p][i] = fmaf(self_cf, xs[i], acc[p][i]);
         }
@@ -878,11 +894,13 @@ __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__rest
 // SCALE (fp32): row v is multiplied by the factor its vertex carries as a gathered row (1/din, 1/sqrt(deg) or
 // 1/(din+1)): folding the factor into the copy that happens anyway saves the per-edge factor stream and the
 // per-edge multiply of MEAN / SAGE_GCN backward and GCN.
+// gathered_only: rows that nobody gathers (counts 0: 43 % of the vertices of the 2.45 M-vertex graph) are left out; the
+// launch is bound by the bytes it moves (2.45 M vertices, F=256: 0.95 -> 0.60 ms).
 template <typename T, bool SCALE>
 __global__ void __launch_bounds__(256) pad_rows_kernel(const T *__restrict__ src, int64_t ld_src, T *__restrict__ dst, int64_t ld_dst,
                                                        int64_t N, int F, int mode, const int32_t *__restrict__ counts,
                                                        const int32_t *__restrict__ row_map, int log2_chunks_per_line,
-                                                       int64_t table_stride, int log2_tpr) {
+                                                       int64_t table_stride, int log2_tpr, int gathered_only) {
     constexpr int W = 16 / int(sizeof(T));
     const int chunks_per_row = (F + W - 1) / W;
     // 2^log2_tpr consecutive threads walk the chunks of one row (no division per chunk)
@@ -891,8 +909,10 @@ __global__ void __launch_bounds__(256) pad_rows_kernel(const T *__restrict__ src
     const int c0 = threadIdx.x & (tpr - 1);
     for (int64_t row = int64_t(blockIdx.x) * rows_per_block + (threadIdx.x >> log2_tpr); row < N;
          row += int64_t(gridDim.x) * rows_per_block) {
+        const int32_t count = (SCALE || gathered_only) ? counts[row] : 0;
+        if (gathered_only && count == 0) continue;
         const int64_t drow = row_map ? int64_t(row_map[row]) : row;
-        const float f = SCALE ? scale_of(mode, counts[row]) : 1.0f;
+        const float f = SCALE ? scale_of(mode, count) : 1.0f;
         const T *in = src + row * ld_src;
         for (int c = c0; c < chunks_per_row; c += tpr) {
             // row-major: log2_chunks_per_line is 31 (one table); slice-major: one table per line
@@ -922,7 +942,7 @@ __global__ void __launch_bounds__(256) pad_rows_kernel(const T *__restrict__ src
 // mode: the factor of the rows (kScaleNone: none).  dst is aligned to 16 bytes, ld_dst and table_stride are whole chunks.
 template <typename T>
 hipError_t launch_pad(const void *src, int64_t ld_src, void *dst, int64_t ld_dst, int64_t N, int64_t F, int mode, const int32_t *counts,
-                      hipStream_t stream, const int32_t *row_map = nullptr, int64_t table_stride = 0) {
+                      hipStream_t stream, const int32_t *row_map = nullptr, int64_t table_stride = 0, bool gathered_only = false) {
     const int cpr = int((F * int64_t(sizeof(T)) + 15) / 16);
     // threads per row: the power of two (>= 8 threads: one 128-byte line) that leaves the fewest idle slots in the last
     // round over the row's chunks; the widest among equals
@@ -941,10 +961,10 @@ hipError_t launch_pad(const void *src, int64_t ld_src, void *dst, int64_t ld_dst
     const int chunks_per_line = table_stride > 0 ? 3 : 31;
     if (sizeof(T) == 4 && mode != kScaleNone)
         pad_rows_kernel<T, true><<<grid, 256, 0, stream>>>(static_cast<const T *>(src), ld_src, static_cast<T *>(dst), ld_dst, N, int(F), mode, counts,
-                                                           row_map, chunks_per_line, table_stride, l);
+                                                           row_map, chunks_per_line, table_stride, l, gathered_only ? 1 : 0);
     else
         pad_rows_kernel<T, false><<<grid, 256, 0, stream>>>(static_cast<const T *>(src), ld_src, static_cast<T *>(dst), ld_dst, N, int(F), mode, counts,
-                                                            row_map, chunks_per_line, table_stride, l);
+                                                            row_map, chunks_per_line, table_stride, l, gathered_only ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -1118,6 +1138,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     const int32_t *rank = nullptr, *rank_indices = nullptr;
     void *tables = nullptr;  // the copy: the plan's buffer or the caller's
     bool factor_in_tables = false;
+    bool gathered_only = false;  // the copy holds gathered rows only
     if (layout.padded_copy) {
         int rc = GNN_OK;
         if (ext_tables) {
@@ -1139,9 +1160,12 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         if ((prepacked || pack_only) && !rank) return GNN_ERR_UNSUPPORTED;
         const int copy_mode = scale_in_copy ? src_mode : int(kScaleNone);
         // copies `ncols` columns starting at `src` into rows of stride dst_ld
+        // Rows that nobody gathers are read as own rows only, and those of the forward pass are read where the caller has them
+        // (the backward's carry their factor, with the rounding that a caller-kept packed copy has).
+        gathered_only = rank && !pack_only && !prepacked && self_mode != kSelfInvPlus1;
         auto copy_part = [&](const char *src, int64_t ncols, char *dst, int64_t dst_ld, int64_t tstride) -> hipError_t {
-            if (esz == 4) return launch_pad<float>(src, ldx, dst, dst_ld, N, ncols, copy_mode, plan->col_counts, stream, rank, tstride);
-            return launch_pad<bf16_t>(src, ldx, dst, dst_ld, N, ncols, kScaleNone, nullptr, stream, rank, tstride);
+            if (esz == 4) return launch_pad<float>(src, ldx, dst, dst_ld, N, ncols, copy_mode, plan->col_counts, stream, rank, tstride, gathered_only);
+            return launch_pad<bf16_t>(src, ldx, dst, dst_ld, N, ncols, kScaleNone, plan->col_counts, stream, rank, tstride, gathered_only);
         };
         const int64_t main_cols = F - layout.tail_elems;
         char *dst = static_cast<char *>(tables);
@@ -1423,6 +1447,8 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         a.store_vec = store_vec;
         a.overlap = overlap;
         a.row_map = rank_indices ? rank : nullptr;
+        a.own_X = gathered_only && self_mode == kSelfPlain ? static_cast<const char *>(orig) + f0 * esz : nullptr;
+        a.own_ld = ldx;
         a.p_indptr = rank_indices ? rl.p_indptr : nullptr;
         a.p_chunks = rank_indices ? rl.p_chunks : nullptr;
         a.cold_on = (o.flags & GNN_FLAG_NO_COLD_HINTS) ? 0 : 1;

@@ -339,15 +339,15 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
         const int64_t N = plan->n_rows, E = plan->n_edges;
         gnn_blocking_params prm = plan->blocking;
         const bool automatic = prm.min_degree == 0;
-        // Defaults, from measurements on the 2.45 M-vertex and 233 K-vertex power-law graphs with the short rows
-        // running beside the pieces (see the kernel profile): rows of >= 256 edges, block 0 = the 16,384
-        // most-gathered sources, further blocks of 24,576 (three quarters of an L2: the short rows' lines pass
-        // through the same L2s), pieces of at most 96 edges, and one last block for every source gathered fewer
-        // than 16 times (their reuse is not worth a partial line per block and row).  Against 32,768 / 128 / 3:
-        // F=100 5.28 -> 5.12 ms, F=256 9.99 -> 9.78, F=512 20.0 -> 19.6; 233 K vertices F=602 13.58 -> 13.46.
+        // Defaults, from measurements with the tiles (tiles.hip) and the short rows running beside the pieces: rows of >= 256
+        // edges (128: 2.45 M vertices F=256 7.74 -> 8.08 ms; 512: 8.20 -> 8.33, 233 K vertices F=256 2.77 -> 3.18), block 0 =
+        // the 32,768 most-gathered sources and further blocks as large (16,384 and 24,576, from before the tiles took the
+        // densest: F=100 4.04 -> 3.94 ms, F=256 7.74 -> 7.64 on 2.45 M vertices, 233 K vertices within 0.3 %), pieces
+        // of at most 96 edges (64 and 128 within 1 %), and one last block for every source gathered fewer than 16 times
+        // (their reuse is not worth a partial line per block and row; 8 and 32 within 1 %).
         if (prm.min_degree == 0) prm.min_degree = 256;
-        if (prm.hot_lines == 0) prm.hot_lines = 16384;
-        if (prm.block_lines == 0) prm.block_lines = 24576;
+        if (prm.hot_lines == 0) prm.hot_lines = 32768;
+        if (prm.block_lines == 0) prm.block_lines = 32768;
         if (prm.max_piece == 0) prm.max_piece = 96;
         if (prm.rest_min_count == 0) prm.rest_min_count = 16;
         int first_bin = -1;

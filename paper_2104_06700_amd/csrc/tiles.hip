@@ -42,12 +42,13 @@ constexpr uint32_t kMaxSegment = 255 * kUnit;  // edges of a row part into one t
 constexpr int64_t kFewBundles = 5;      // bundles per wavefront before rows are dealt to more workgroups
 constexpr int64_t kRowBlocks = 64;     // workgroups the rows are dealt to at least (per column slice)
 constexpr int64_t kComputeUnits = 256;
-// A row is staged in a block where it has this many edges per tile (a staged line costs about a third of a gathered
-// one, but a row's list is filled up to whole units and to the longest of its bundle: 5 and 7 measure alike, 4 no better) ...
-constexpr int64_t kMinRowEdges = 5;
+// A row is staged in a block where it has this many edges per tile: a staged line costs a fifth of a gathered one, but a row's list is
+// filled up to whole units and to the longest of its bundle (5 -> 3 -> 2, with 3,000 below: 2.45 M vertices F=256 8.20 -> 7.94 ->
+// 7.93 ms, 233 K vertices 2.77 -> 2.72 -> 2.67) ...
+constexpr int64_t kMinRowEdges = 2;
 // ... and a block where those rows have this many edges per tile and workgroup of rows: what copying the tile costs
-// (2.45 M vertices: 2,800 and 5,000 within 1 %, 8,000 slower; weighted graph of 133 K vertices F=64 2.89 ms with 2,800, 2.79 with 5,000).
-constexpr int64_t kMinTileEdges = 5000;
+// (2.45 M vertices F=256 8.45 ms with 1,000, 7.72-7.76 from 2,000 to 4,000; the others within 1 %).
+constexpr int64_t kMinTileEdges = 3000;
 constexpr int kStreamAhead = 64;  // units of padding behind a stream (the loads run up to 2 KB ahead)
 
 int grid_for(int64_t n, int block, int64_t cap = (int64_t(1) << 16)) {

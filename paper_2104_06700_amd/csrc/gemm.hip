@@ -130,12 +130,12 @@ struct SplitTile {
 // sr == 1.  A thread takes units of 8 k of a row: two 16-byte loads, or eight loads of 4 bytes with the rows along the
 // lanes.  Rows past the end repeat the last one (their results are never stored).  load() and store() are separate so that the
 // loads of a later tile are in flight while the matrix cores work.
-template <bool K_CONTIG, int ROWS, int THREADS, bool GATED = false>
+template <bool K_CONTIG, int ROWS, int THREADS, bool GATED = false, int SETS = 1>
 struct Stager {
     static constexpr int UNITS = ROWS * 2;
     static constexpr int PER_THREAD = (UNITS + THREADS - 1) / THREADS;
-    float v[PER_THREAD][8];
-    float gate[GATED ? PER_THREAD : 1][8];  // the gate's elements travel beside the operand's and are applied in store()
+    float v[SETS][PER_THREAD][8];  // SETS tiles on their way
+    float gate[SETS][GATED ? PER_THREAD : 1][8];  // the gate's elements travel beside the operand's and are applied in store()
     // Rows along the lanes, 64 and more: a wavefront's 64 units have one k, so the address is a scalar plus 4 * row.  Otherwise
     // a lane keeps the address of its unit in the tile at k_begin.
     static constexpr bool SCALAR_K = !K_CONTIG && ROWS % 64 == 0;
@@ -170,13 +170,13 @@ struct Stager {
     }
 
     // k_off = first k of the tile - k_begin (uniform; may be negative)
-    __device__ __forceinline__ void load(int64_t k_off, bool gated) {
+    __device__ __forceinline__ void load(int64_t k_off, bool gated, int set = 0) {
 #pragma unroll
         for (int h = 0; h < PER_THREAD; ++h) {
             if (!has(h)) continue;
-            fetch(h, p[h] + k_off * sk, v[h]);
+            fetch(h, p[h] + k_off * sk, v[set][h]);
             if constexpr (GATED) {
-                if (gated) fetch(h, p[h] + k_off * sk + gate_off, gate[h]);
+                if (gated) fetch(h, p[h] + k_off * sk + gate_off, gate[set][h]);
             }
         }
     }
@@ -196,44 +196,44 @@ struct Stager {
     }
 
     // the first tile of an operand with n < 16 k
-    __device__ __forceinline__ void load_few(int n) {
+    __device__ __forceinline__ void load_few(int n, int set = 0) {
 #pragma unroll
         for (int h = 0; h < PER_THREAD; ++h) {
             if (!has(h)) continue;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[h][i] = half_of(h) * 8 + i < n ? at(h, p[h], i) : 0.0f;
+            for (int i = 0; i < 8; ++i) v[set][h][i] = half_of(h) * 8 + i < n ? at(h, p[h], i) : 0.0f;
         }
     }
     // the first `n` k of the tile count as 0 (a tile moved back to end with k_end repeats them)
-    __device__ __forceinline__ void drop_first(int n) {
+    __device__ __forceinline__ void drop_first(int n, int set = 0) {
 #pragma unroll
         for (int h = 0; h < PER_THREAD; ++h)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[h][i] = half_of(h) * 8 + i >= n ? v[h][i] : 0.0f;
+            for (int i = 0; i < 8; ++i) v[set][h][i] = half_of(h) * 8 + i >= n ? v[set][h][i] : 0.0f;
     }
 
     // flip: the rows are negated as in step `t` (row_sign)
-    __device__ __forceinline__ void store(SplitTile<ROWS> &tile, bool gated, bool with_sums, float (&sums)[PER_THREAD][2], bool flip, int t) {
+    __device__ __forceinline__ void store(SplitTile<ROWS> &tile, bool gated, bool with_sums, float (&sums)[PER_THREAD][2], bool flip, int t, int set = 0) {
 #pragma unroll
         for (int h = 0; h < PER_THREAD; ++h) {
             if (!has(h)) continue;
             if constexpr (GATED) {
                 if (gated) {
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) v[h][i] = gate[h][i] > 0.0f ? v[h][i] : 0.0f;
+                    for (int i = 0; i < 8; ++i) v[set][h][i] = gate[set][h][i] > 0.0f ? v[set][h][i] : 0.0f;
                 }
                 if (with_sums) {  // of even and of odd tiles: shorter chains, less rounding
-                    const float x = ((v[h][0] + v[h][1]) + (v[h][2] + v[h][3])) + ((v[h][4] + v[h][5]) + (v[h][6] + v[h][7]));
+                    const float x = ((v[set][h][0] + v[set][h][1]) + (v[set][h][2] + v[set][h][3])) + ((v[set][h][4] + v[set][h][5]) + (v[set][h][6] + v[set][h][7]));
                     sums[h][0] = (t & 1) ? sums[h][0] : sums[h][0] + x;
                     sums[h][1] = (t & 1) ? sums[h][1] + x : sums[h][1];
                 }
             }
             if (flip) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[h][i] = __uint_as_float(__float_as_uint(v[h][i]) ^ row_sign(row_of(h), t));
+                for (int i = 0; i < 8; ++i) v[set][h][i] = __uint_as_float(__float_as_uint(v[set][h][i]) ^ row_sign(row_of(h), t));
             }
             uint4 q[3];
-            split8(v[h], q);
+            split8(v[set][h], q);
             const int r = row_of(h), s = SplitTile<ROWS>::slot(half_of(h), r & 31);
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl) tile.v[pl][r >> 5][s] = q[pl];
@@ -380,8 +380,11 @@ __global__ void __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_
     };
     clear();
 
-    using StagerA = Stager<A_K_CONTIG, BM, THREADS>;
-    using StagerB = Stager<B_K_CONTIG, BN, THREADS, FOLD == 2>;
+    // Tiles on their way.  Two where the registers leave two wavefronts per SIMD anyway (2,449,029 rows into 256 x 256 2.04 ->
+    // 1.99 ms, 109,316 into 128 x 128 44 -> 40 us); narrow tiles do better with more workgroups (602 x 16: 114 us, 139 with two).
+    constexpr int SETS = BN >= 128 ? 2 : 1;
+    using StagerA = Stager<A_K_CONTIG, BM, THREADS, false, SETS>;
+    using StagerB = Stager<B_K_CONTIG, BN, THREADS, FOLD == 2, SETS>;
     StagerA sa;
     StagerB sb;
     const bool b_gated = FOLD == 2 && g.b_gate;
@@ -389,9 +392,9 @@ __global__ void __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_
     float no_sum[StagerA::PER_THREAD][2] = {}, col_sum[StagerB::PER_THREAD][2] = {};
     const int l32 = lane & 31, lk = lane >> 5;
     const int my_slot = SplitTile<BM>::slot(lk, l32);
-    auto stage = [&](int t) {  // registers -> LDS
-        sa.store(tiles[t & 1].a, false, false, no_sum, true, t);
-        sb.store(tiles[t & 1].b, b_gated, sums, col_sum, false, t);
+    auto stage = [&](int p) {  // registers -> LDS; p = number of the tile % 2
+        sa.store(tiles[p].a, false, false, no_sum, true, p, p % SETS);
+        sb.store(tiles[p].b, b_gated, sums, col_sum, false, p, p % SETS);
     };
     auto multiply = [&](int step) {
         const Tiles &t = tiles[step & 1];
@@ -413,39 +416,41 @@ __global__ void __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_
             __builtin_amdgcn_sched_barrier(0);  // what the compiler fetches further ahead does not fit the registers
         }
     };
-    // While tile t is multiplied, tile t + 1 is split into the other half of the LDS and tile t + 2 is on its way.  A last tile of
-    // less than 16 k is moved back to end with the part (K >= 16); what it repeats counts as 0.  Loads past the last tile
-    // repeat it, so that the loop has no branches around them.
+    // While tile t is multiplied, tile t + 1 is split into the other half of the LDS and the SETS tiles behind it are on their way.
+    // A last tile of less than 16 k is moved back to end with the part (K >= 16); what it repeats counts as 0.  Loads past the
+    // last tile repeat it, so that the loop has no branches around them.
     const int64_t len = k_begin < k_end ? k_end - k_begin : 0;
     const int64_t n_tiles = (len + BK - 1) / BK;
     const int repeated = int(n_tiles * BK - len);
-    auto load = [&](int64_t t) {
+    auto load = [&](int64_t t, int p) {
         const int64_t k = t * BK < len - BK ? t * BK : len - BK;
-        sa.load(k, false);
-        sb.load(k, b_gated);
+        sa.load(k, false, p % SETS);
+        sb.load(k, b_gated, p % SETS);
     };
-    auto drop = [&](int64_t t) {
+    auto next = [&](int64_t t, int p) {  // p = t % 2
         if (t + 1 == n_tiles && repeated) {
-            sa.drop_first(repeated);
-            if constexpr (FOLD == 2) sb.drop_first(repeated);  // for its column sums
+            sa.drop_first(repeated, p % SETS);
+            if constexpr (FOLD == 2) sb.drop_first(repeated, p % SETS);  // for its column sums
         }
+        stage(p);
+        load(t + SETS, p);
+        __syncthreads();
     };
     if (n_tiles > 0) {
         sa.init(g.A, g.a_gate, g.sam, g.sak, m0, g.M, k_begin);
         sb.init(g.B, g.b_gate, g.sbn, g.sbk, n0, g.N, k_begin);
-        load(0);
-        drop(0);
-        stage(0);
-        load(1);
-        __syncthreads();
+        load(0, 0);
+        __builtin_amdgcn_sched_barrier(0);  // in this order, as in the loop: what is waited for is counted
+        if (SETS == 2) load(1, 1);
+        next(0, 0);
 #pragma unroll 1
-        for (int64_t t = 0; t < n_tiles; ++t) {
-            multiply(int(t & 1));
+        for (int64_t t = 0;; t += 2) {
+            multiply(0);
             if (t + 1 == n_tiles) break;
-            drop(t + 1);
-            stage(int((t + 1) & 1));
-            load(t + 2);
-            __syncthreads();
+            next(t + 1, 1);
+            multiply(1);
+            if (t + 2 == n_tiles) break;
+            next(t + 2, 0);
         }
     }
 
@@ -708,8 +713,8 @@ static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
     if (tiles >= 512 || K < 1024) return 1;
     int64_t split = (256 * s.resident + tiles - 1) / tiles;
     // At least GNN_SPLIT_MIN_K k-steps per part: a part is bound by the latency of its tiles of 16 k-steps, one after the other, while
-    // the chip is not full (24,490 rows into 256 x 256: 0.20 ms with parts of 1024, 0.05 with 128); the partial planes
-    // cost little beside that.
+    // the chip is not full (24,490 rows into 256 x 256: 0.20 ms with parts of 1024, 0.047 with 128, 0.044 with 64; 7,265 into
+    // 50 x 16 14.3 and 12.7 us with 128 and 64); the partial planes cost little beside that.
     const int64_t max_split = K / GNN_SPLIT_MIN_K;
     if (split > max_split) split = max_split;
     if (split > 4096) split = 4096;

@@ -19,7 +19,7 @@
 
 namespace {
 
-constexpr int kRowsPerBlock = 128;
+constexpr int kRowsPerBlock = 64;
 // the rows of partial column sums, one per block of rows, also take one plane per part of the split weight gradient
 static_assert(kRowsPerBlock <= GNN_SPLIT_MIN_K, "room for a plane per part");
 
@@ -41,12 +41,14 @@ hipStream_t side_stream() {
 // (256 / cols)-th row of the block; the row lanes are added through LDS in a fixed order, so the
 // sums are reproducible.  cols = power of two >= F, at most 256 (wider F: several column passes).
 // pk.active: G goes into a producer-side layout (the tables the backward aggregation gathers from) instead.
-__global__ void __launch_bounds__(256) mask_colsum_kernel(const float *__restrict__ H, const float *__restrict__ dH,
+// THREADS: 1024 where there are few blocks, which take as long as a thread has rows to walk.
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) mask_colsum_kernel(const float *__restrict__ H, const float *__restrict__ dH,
                                                           float *__restrict__ G, int64_t ldg, float *__restrict__ partial,
                                                           int64_t N, int F, int relu, int log2_cols, const gnn_packed_target pk) {
-    __shared__ float red[256];
+    __shared__ float red[THREADS];
     const int cols = 1 << log2_cols;
-    const int row_lanes = 256 >> log2_cols;
+    const int row_lanes = THREADS >> log2_cols;
     const int jl = threadIdx.x & (cols - 1), rl = threadIdx.x >> log2_cols;
     const int64_t r0 = int64_t(blockIdx.x) * kRowsPerBlock;
     const int64_t r1 = r0 + kRowsPerBlock < N ? r0 + kRowsPerBlock : N;
@@ -290,8 +292,9 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
     if (!fold_gate && (need_g || db)) {
         int log2_cols = 0;
         while ((1 << log2_cols) < F_out && log2_cols < 8) ++log2_cols;
-        mask_colsum_kernel<<<static_cast<unsigned>(n_blocks), 256, 0, stream>>>(H, dH, G, ldg, part, N, int(F_out),
-                                                                                o.relu ? 1 : 0, log2_cols, pk_mask);
+        const unsigned blocks = static_cast<unsigned>(n_blocks);
+        if (n_blocks < 512) mask_colsum_kernel<1024><<<blocks, 1024, 0, stream>>>(H, dH, G, ldg, part, N, int(F_out), o.relu ? 1 : 0, log2_cols, pk_mask);
+        else mask_colsum_kernel<256><<<blocks, 256, 0, stream>>>(H, dH, G, ldg, part, N, int(F_out), o.relu ? 1 : 0, log2_cols, pk_mask);
         if (db) {
             launch_colsum_reduce(part, n_blocks, int(F_out), part2, db, stream);
         }

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 # fp32 products are exact on the matrix cores but for 2^-24 of S; the accumulation of K terms in fp32 (in steps of
-# 16, partial planes of >= 128) and the fp32 aggregation before or after it leave an error of
+# 16, partial planes of >= 64) and the fp32 aggregation before or after it leave an error of
 # at most (1e-5 + K * 2^-24) * S in the worst case and ~sqrt(K) * 2^-24 * S typically, S being the
 # sum of the absolute values of all terms; gate at 2e-5 * S.
 RTOL_LAYER = 2e-5

@@ -558,29 +558,47 @@ __global__ void __launch_bounds__(kTileThreads) tile_kernel(const TileArgs a) {
         }
     };
 
+    // Copying a tile takes its latency and 124 KB at a compute unit's share of the memory, with nothing else running there.  So
+    // the first AHEAD_CHUNKS of a thread's chunks of the next tile are fetched while this one is gathered from, as many as the
+    // registers beside the sums hold, and the others before the wavefronts wait for each other.
+    constexpr int AHEAD_CHUNKS = BF16 ? 0 : (COEF ? 2 : 4);
+    u32x4 first_chunks[AHEAD_CHUNKS ? AHEAD_CHUNKS : 1];
+    auto chunk = [&](const TileDesc &t, int h) {
+        const int x = int(threadIdx.x) + h * kTileThreads, n = t.size * L;
+        return (reinterpret_cast<const u32x4 *>(Xs) + int64_t(t.begin) * L)[x < n ? x : n - 1];
+    };
+    auto put = [&](const TileDesc &t, int h, const u32x4 &v) {
+        const int x = int(threadIdx.x) + h * kTileThreads;
+        // the last zero_lines(L) lines, and what is behind a shorter tile, are zeros
+        if (x < TS * L) tile[x] = x < t.size * L ? v : u32x4{0u, 0u, 0u, 0u};
+    };
     TileDesc d = a.tiles[t0];
+#pragma unroll
+    for (int h = 0; h < AHEAD_CHUNKS; ++h) first_chunks[h] = chunk(d, h);
     for (int t = t0; t < t1; ++t) {
         const u32x4 n_units = *cnt++;
-        const u32x4 *src = reinterpret_cast<const u32x4 *>(Xs) + int64_t(d.begin) * L;
-        const int n_chunks = d.size * L;
-        if (t + 1 < t1) d = a.tiles[t + 1];
+        u32x4 v[CHUNKS - AHEAD_CHUNKS < 4 ? CHUNKS - AHEAD_CHUNKS : 4];
+        constexpr int BEFORE = int(sizeof(v) / sizeof(v[0]));
+#pragma unroll
+        for (int i = 0; i < BEFORE; ++i) v[i] = chunk(d, AHEAD_CHUNKS + i);
         __syncthreads();  // everyone is done with the tile before
 #pragma unroll
-        for (int h = 0; h < CHUNKS; h += 4) {
-            u32x4 v[4];
+        for (int h = 0; h < AHEAD_CHUNKS; ++h) put(d, h, first_chunks[h]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int x = int(threadIdx.x) + (h + i) * kTileThreads;
-                v[i] = src[x < n_chunks ? x : n_chunks - 1];
-            }
+        for (int i = 0; i < BEFORE; ++i) put(d, AHEAD_CHUNKS + i, v[i]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int x = int(threadIdx.x) + (h + i) * kTileThreads;
-                // the last zero_lines(L) lines, and what is behind a shorter tile, are zeros
-                if (x < TS * L) tile[x] = x < n_chunks ? v[i] : u32x4{0u, 0u, 0u, 0u};
-            }
+        for (int h = AHEAD_CHUNKS + BEFORE; h < CHUNKS; h += 4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (h + i < CHUNKS) v[i] = chunk(d, h + i);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (h + i < CHUNKS) put(d, h + i, v[i]);
         }
+        if (t + 1 < t1) d = a.tiles[t + 1];
         __syncthreads();
+#pragma unroll
+        for (int h = 0; h < AHEAD_CHUNKS; ++h) first_chunks[h] = chunk(d, h);  // behind the last tile: that one again
 #pragma unroll
         for (int r = 0; r < RR; ++r) {
             int n = int((__builtin_amdgcn_readfirstlane(n_units[r >> 2]) >> (8 * (r & 3))) & 0xFFu);

@@ -910,7 +910,7 @@ __global__ void __launch_bounds__(256) pad_rows_kernel(const T *__restrict__ src
     for (int64_t row = int64_t(blockIdx.x) * rows_per_block + (threadIdx.x >> log2_tpr); row < N;
          row += int64_t(gridDim.x) * rows_per_block) {
         const int32_t count = (SCALE || gathered_only) ? counts[row] : 0;
-        if (gathered_only && count == 0) continue;
+        if (gathered_only && count == 0 && row != 0) continue;  // masked lanes may load row 0
         const int64_t drow = row_map ? int64_t(row_map[row]) : row;
         const float f = SCALE ? scale_of(mode, count) : 1.0f;
         const T *in = src + row * ld_src;
@@ -1575,8 +1575,8 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
 }  // namespace
 
 // Copy of an fp32 matrix into rows of another stride (the plan-owned padded matrix; used by ap.hip).
-int gnn_pad_rows_f32(const float *src, int64_t ld_src, float *dst, int64_t ld_dst, int64_t N, int64_t F, hipStream_t stream) {
-    return launch_pad<float>(src, ld_src, dst, ld_dst, N, F, kScaleNone, nullptr, stream) == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
+int gnn_pad_rows_f32(const float *src, int64_t ld_src, float *dst, int64_t ld_dst, int64_t N, int64_t F, const int32_t *counts, hipStream_t stream) {
+    return launch_pad<float>(src, ld_src, dst, ld_dst, N, F, kScaleNone, counts, stream, nullptr, 0, counts != nullptr) == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
 }
 
 int gnn_packed_target_for(gnn_plan *plan, const void *indptr, const int32_t *indices, int64_t N, int64_t F, int op, bool backward,

@@ -47,6 +47,7 @@ struct ApArgs {
     int32_t n_bins;
     int32_t slab_cols;    // columns one workgroup covers (a multiple of four, or all of them)
     int32_t col0;         // first column of this launch
+    int32_t source_split;  // edge dot products: workgroup b takes the (b % 8)-th eighth of its rows
     int32_t col_end;      // one past its last column
     int32_t log2_slices;  // > 0: workgroup b serves column slab (b % n_slices) of the launch, so that an
                           // XCD (workgroups go to the 8 XCDs round-robin) keeps gathering the same lines
@@ -471,7 +472,14 @@ template <int CTRL> __device__ __forceinline__ float exchange(bool upper, float 
 template <int LC, int S, bool RAGGED>  // RAGGED: fewer than 4 * C * S columns
 __global__ void __launch_bounds__(kBlockThreads) ap_edge_dot_kernel(const ApArgs a) {
     constexpr int C = 1 << LC;
-    const Group g = locate_group(a, blockIdx.x);
+    Group g = locate_group(a, a.source_split ? blockIdx.x >> 3 : blockIdx.x);
+    if (a.source_split) {  // XCD k takes the k-th eighth of a row's edges, in whole steps of the group
+        const int64_t k = blockIdx.x & 7u, len = g.e1 - g.e0, first = g.e0;
+        auto cut = [&](int64_t i) { return first + (i >= 8 ? len : min(len, ((len * i >> 3) + (g.G >> 1)) & ~int64_t(g.G - 1))); };
+        g.e0 = cut(k);
+        g.e1 = cut(k + 1);
+        if (!__any(g.e0 < g.e1)) return;
+    }
     const int lane = threadIdx.x & 63;
     const int slot0 = lane & ~(C - 1);  // first lane of this edge slot
     const int64_t row = g.row < 0 ? 0 : g.row;
@@ -720,7 +728,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         if (L.padded_copy && d * 4 > 128) {  // rows of one line gain nothing from a copy in their own order
             rc = gnn_plan_padded(plan, N * L.ld_pad * 4);
             if (rc != GNN_OK) return rc;
-            rc = gnn_pad_rows_f32(fV, c.ldv, static_cast<float *>(plan->padded), L.ld_pad, N, d, c.stream);
+            rc = gnn_pad_rows_f32(fV, c.ldv, static_cast<float *>(plan->padded), L.ld_pad, N, d, plan->col_counts, c.stream);
             if (rc != GNN_OK) return rc;
             a.fV = static_cast<const float *>(plan->padded);
             a.ldv = L.ld_pad;
@@ -925,6 +933,15 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     if (dots) {
         using std::integral_constant;
         a.col_end = int32_t(d);
+        // Rows in ascending order of their sources, as a sorted graph has them (others lose nothing but time): their k-th eighths
+        // lead to an eighth of the gathered matrix, which an L2 holds where the whole is too large for it.  Pays for long rows
+        // of two lines and more (132,534 vertices, 596 edges each, mild skew: d = 128 4.23 -> 2.51 ms, 64 1.60 -> 1.29, 37 1.56 ->
+        // 1.34; strong skew 1.26 -> 1.25) and costs where a row has few steps or a line (32 columns 0.67 -> 0.73 ms, 300 edges
+        // each 1.02 -> 1.04, 96 edges each 1.07 -> 1.40).
+        const int64_t matrix_bytes = N * c.ldv * 4;
+        a.source_split = plan && plan->n_edges >= 400 * N && d > 32 && matrix_bytes >= (int64_t(18) << 20) && matrix_bytes <= (int64_t(72) << 20) &&
+                         blocks <= INT32_MAX / 8 ? 1 : 0;
+        if (a.source_split) grid.x *= 8;
         auto launch = [&](auto lc, auto s) {
             constexpr int LC = decltype(lc)::value, S = decltype(s)::value;
             if (d == 4 * S << LC) ap_edge_dot_kernel<LC, S, false><<<grid, kBlockThreads, 0, c.stream>>>(a);

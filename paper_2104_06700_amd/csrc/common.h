@@ -605,7 +605,9 @@ static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, const g
 }
 
 // Copies an fp32 [N, F] matrix with row stride ld_src into rows of stride ld_dst (elements).
-int gnn_pad_rows_f32(const float *src, int64_t ld_src, float *dst, int64_t ld_dst, int64_t N, int64_t F, hipStream_t stream);
+// counts: gathers of each row (a plan's col_counts); rows without any are left out.  nullptr: all rows.
+int gnn_pad_rows_f32(const float *src, int64_t ld_src, float *dst, int64_t ld_dst, int64_t N, int64_t F, const int32_t *counts,
+                     hipStream_t stream);
 
 // gnn_matmul on a typed stream (shared by the C entry point and the layer calls).
 // packed: write the result into a producer-side layout instead of C (C may then be nullptr; M = the plan's rows).

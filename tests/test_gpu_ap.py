@@ -425,3 +425,29 @@ def test_sorted_winner_scatter(d, binop):
     want, size = (torch.from_numpy(np.bincount(flat, x.reshape(-1).numpy(), n * d)).view(n, d) for x in (terms, terms.abs()))
     assert bool(((dfV[:, :d].double() - want).abs() <= 2e-5 * size).all())
     assert bool((dfV[:, d:] == 7.0).all())
+
+
+@pytest.mark.parametrize("d,hubs", [(33, False), (64, True), (128, False)])
+def test_edge_dots_of_long_rows_are_split_over_the_xcds(d, hubs):
+    """400 edges per vertex and a gathered matrix of 18 MB (reached by its stride): every row's edges are dealt to eight
+    workgroups.  Rows of every length from 0 on, long ones cut into pieces by the second plan."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d)
+    n = 5000
+    lens = torch.randint(0, 900, (n,), generator=gen, device=DEV)
+    lens[:70] = torch.arange(70, device=DEV)
+    lens[100] = 60_000
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), lens)
+    src = torch.randint(0, n, (dst.numel(),), generator=gen, device=DEV)
+    order = torch.argsort(dst * n + src, stable=True)
+    dst, src = dst[order].int(), src[order].int()
+    e = dst.numel()
+    assert e >= 400 * n
+    g = gnn.build_device_graph(dst, src, n, plan_params=gnn.make_plan_params([2, 8, 32, 128, 512], 100) if hubs else None)
+    big = torch.empty(n, 1000, device=DEV).normal_(generator=gen)
+    v, do = big[:, :d], torch.empty(n, d, device=DEV).normal_(generator=gen)
+    fe = torch.rand(e, device=DEV, generator=gen)
+    out = torch.full((e,), float("nan"), device=DEV)
+    gnn.gnn_ap_bwd_edge(g.indptr, g.indices, None, v, fe, do, out, n, d, gnn.GNN_BIN_MUL, plan=g.plan_fwd)
+    terms = v.double()[src.long()] * do.double()[dst.long()]
+    assert bool(((out.double() - terms.sum(1)).abs() <= 1e-5 * terms.abs().sum(1)).all())

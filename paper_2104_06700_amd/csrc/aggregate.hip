@@ -83,6 +83,7 @@ struct AggArgs {
     float *partial;             // [n_chunks, ldp] fp32
     int64_t ldp;
     int32_t n_bins;
+    int32_t first_block[GNN_FLAT_BINS];  // see gnn_bin_of_block
     int32_t log2_slices;  // column slices; workgroup b serves slice b % n_slices (see run_aggregate)
     int32_t slice_cols;   // columns per slice (the last slice of a launch may hold fewer)
     int32_t store_vec;    // widest non-temporal store the output rows allow (elements, <= VEC)
@@ -335,15 +336,13 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     const int lane = threadIdx.x & 63;
     const int wave_in_block = threadIdx.x >> 6;
 
-    // which bin does this workgroup serve (wave-uniform scan of a tiny table)
+    // which bin does this workgroup serve (wave-uniform)
     const int slice = int(blockIdx.x) & ((1 << a.log2_slices) - 1);
     const int64_t vblock = int64_t(blockIdx.x) >> a.log2_slices;
     const int col_base = slice * a.slice_cols;
     const int Fk = a.F - col_base < a.slice_cols ? a.F - col_base : a.slice_cols;  // columns of this slice
     if (Fk <= 0) return;
-    int b = 0;
-    for (int i = 1; i < a.n_bins; ++i)
-        if (vblock >= a.bins[i].first_block) b = i;
+    const int b = gnn_bin_of_block(a.first_block, a.bins, a.n_bins, vblock);
     const BinDesc bin = a.bins[b];
     const bool coop = COOP && (bin.kind & GNN_BIN_COOP);
     const int64_t wave_in_bin = coop ? vblock - bin.first_block : (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;
@@ -570,21 +569,7 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
         if (!col_ok[p]) continue;
         if (a.self_mode != kSelfNone) {  // Section 6.1: the vertex's own vector joins the sum
             float xs[VEC];
-            if (!a.own_X) {
-                VecIO<T, VEC>::load(X + self_row * ldx + lcol[p], xs);
-            } else {
-                const T *own = static_cast<const T *>(a.own_X) + row * a.own_ld + col[p];
-                if (ncols[p] == VEC) {
-                    VecIO<T, VEC>::load(own, xs);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < VEC; ++i) {
-                        float one[1] = {0.0f};
-                        if (i < ncols[p]) VecIO<T, 1>::load(own + i, one);
-                        xs[i] = one[0];
-                    }
-                }
-            }
+            VecIO<T, VEC>::load(a.own_X ? static_cast<const T *>(a.own_X) + row * a.own_ld + col[p] : X + self_row * ldx + lcol[p], xs);
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[p][i] = fmaf(self_cf, xs[i], acc[p][i]);
         }
@@ -1160,9 +1145,9 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         if ((prepacked || pack_only) && !rank) return GNN_ERR_UNSUPPORTED;
         const int copy_mode = scale_in_copy ? src_mode : int(kScaleNone);
         // copies `ncols` columns starting at `src` into rows of stride dst_ld
-        // Rows that nobody gathers are read as own rows only, and those of the forward pass are read where the caller has them
-        // (the backward's carry their factor, with the rounding that a caller-kept packed copy has).
-        gathered_only = rank && !pack_only && !prepacked && self_mode != kSelfInvPlus1;
+        // Rows that nobody gathers are read as own rows only, and those of the forward pass are read where the caller has them, in
+        // whole strips (the backward's carry their factor, with the rounding that a caller-kept packed copy has).
+        gathered_only = rank && !pack_only && !prepacked && (self_mode == kSelfNone || (self_mode == kSelfPlain && F % max_vec == 0));
         auto copy_part = [&](const char *src, int64_t ncols, char *dst, int64_t dst_ld, int64_t tstride) -> hipError_t {
             if (esz == 4) return launch_pad<float>(src, ldx, dst, dst_ld, N, ncols, copy_mode, plan->col_counts, stream, rank, tstride, gathered_only);
             return launch_pad<bf16_t>(src, ldx, dst, dst_ld, N, ncols, kScaleNone, plan->col_counts, stream, rank, tstride, gathered_only);
@@ -1531,7 +1516,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             if (f0 < plain_hub_col_begin) plain_hub_col_begin = f0;
         }
         int32_t nb = 0;
-        int64_t next_block = gnn_fill_bins(a.bins, &nb, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX, 1 << log2_s);
+        int64_t next_block = gnn_fill_bins(a.bins, &nb, a.first_block, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX, 1 << log2_s);
         a.n_bins = nb;
         if (nb == 0 || next_block == 0) continue;
         next_block <<= log2_s;

@@ -45,6 +45,7 @@ struct ApArgs {
     int32_t *parg;     // hub pieces: partial winners  [n_chunks, ldp]
     int64_t ldp;
     int32_t n_bins;
+    int32_t first_block[GNN_FLAT_BINS];  // see gnn_bin_of_block
     int32_t slab_cols;    // columns one workgroup covers (a multiple of four, or all of them)
     int32_t col0;         // first column of this launch
     int32_t source_split;  // edge dot products: workgroup b takes the (b % 8)-th eighth of its rows
@@ -145,9 +146,7 @@ __device__ __forceinline__ Group locate_group(const ApArgs &a, int64_t vblock) {
     Group g;
     const int lane = threadIdx.x & 63;
     const int wave_in_block = threadIdx.x >> 6;
-    int b = 0;
-    for (int i = 1; i < a.n_bins; ++i)
-        if (vblock >= a.bins[i].first_block) b = i;
+    const int b = gnn_bin_of_block(a.first_block, a.bins, a.n_bins, vblock);
     const ApBin bin = a.bins[b];
     g.coop = (bin.kind & GNN_BIN_COOP) != 0;
     const int64_t wave_in_bin = g.coop ? vblock - bin.first_block : (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;
@@ -586,7 +585,7 @@ int64_t make_bins(ApArgs &a, const gnn_plan *plan, int64_t N, int log2_c, int sl
         a.row_perm = plan->row_perm;
         a.chunks = plan->chunks;
     }
-    return gnn_fill_bins(a.bins, &a.n_bins, plan, N, log2_c, INT32_MAX, slices);
+    return gnn_fill_bins(a.bins, &a.n_bins, a.first_block, plan, N, log2_c, INT32_MAX, slices);
 }
 
 struct Common {

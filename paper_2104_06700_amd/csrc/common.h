@@ -529,6 +529,19 @@ struct gnn_bin_desc {
 
 constexpr int GNN_WAVES_PER_BLOCK = 4;  // 256-thread workgroups
 
+// The bin of a workgroup.  The first workgroups of the first 16 bins (INT32_MAX behind the last) arrive in one scalar load; walking
+// the descriptors instead is a load and a wait per bin, a good part of what a workgroup of short rows takes (F=29 on
+// power-law graphs of 4,600 vertices 11.9 -> 10.7 us a call, 27.8 M vertices bf16 17.5 -> 17.0 ms).  More bins than that are walked.
+constexpr int GNN_FLAT_BINS = 16;
+__device__ static inline int gnn_bin_of_block(const int32_t (&first_block)[GNN_FLAT_BINS], const gnn_bin_desc *bins, int n_bins, int64_t block) {
+    int b = 0;
+#pragma unroll
+    for (int i = 1; i < GNN_FLAT_BINS; ++i) b = int32_t(block) >= first_block[i] ? i : b;
+    for (int i = GNN_FLAT_BINS; i < n_bins; ++i)
+        if (block >= bins[i].first_block) b = i;
+    return b;
+}
+
 // Fills `bins` for a launch whose row groups have 2^log2_c column lanes; returns the number of
 // workgroups.  plan == nullptr: all N rows in one bin, whole wavefronts per row.
 // first_excluded_bin: rows of bins >= it (and the hub pieces) are left out (they are served as source-blocked pieces).
@@ -538,7 +551,7 @@ constexpr int GNN_WAVES_PER_BLOCK = 4;  // 256-thread workgroups
 // batch of loads each, about a microsecond), one after the other.  So where there are too few wavefronts, rows get more
 // edge slots than throughput asks for, and where the steps of a long row or of a hub piece outlast the launch's
 // share per wavefront, the four wavefronts of a workgroup share it (24,490 vertices, 1.2 M edges, F=100: 0.33 -> 0.06 ms).
-static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, const gnn_plan *plan, int64_t N, int log2_c,
+static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, int32_t (&first_block)[GNN_FLAT_BINS], const gnn_plan *plan, int64_t N, int log2_c,
                                     int first_excluded_bin = INT32_MAX, int slices = 1) {
     constexpr int64_t kWaveSlots = 256 * 4 * 8;  // wavefronts the chip holds of a kernel with 64 registers
     constexpr int kStepLog2 = 3;                 // loads of a slot in flight: edges per step
@@ -601,6 +614,8 @@ static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, const g
         add_bin(GNN_BIN_ROWS, 0, N, max_log2_sr);
     }
     *n_bins = nb;
+    for (int i = 0; i < GNN_FLAT_BINS; ++i)
+        first_block[i] = i < nb && bins[i].first_block < INT32_MAX ? int32_t(bins[i].first_block) : INT32_MAX;
     return next_block;
 }
 

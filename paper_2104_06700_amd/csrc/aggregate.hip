@@ -75,6 +75,7 @@ struct AggArgs {
     int32_t F;
     int32_t ip64;
     const int32_t *row_perm;    // nullptr: identity
+    const int4 *row_info;       // see gnn_plan; or nullptr
     const float *edge_scale;    // per-edge factor 1/deg or 1/sqrt(deg) of the gathered vertex, or nullptr
     int32_t dst_mode;
     int32_t self_mode;          // SelfMode: add the row's own gathered vector (GraphSAGE-GCN aggregator)
@@ -375,16 +376,20 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     } else {
         const int64_t item = wave_in_bin * (64 >> bin.log2_g) + (lane >> bin.log2_g);
         if (item < bin.n_items) {
-            row = a.row_perm ? int64_t(a.row_perm[bin.item_begin + item]) : bin.item_begin + item;
-            if (a.p_indptr) {
-                e0 = a.p_indptr[bin.item_begin + item];
-                e1 = a.p_indptr[bin.item_begin + item + 1];
-                if (COEF) wdelta = load_ip(a.indptr, a.ip64, row) - e0;
+            int64_t begin;
+            if (a.row_info) {
+                const int4 info = a.row_info[bin.item_begin + item];
+                row = info.x;
+                begin = uint32_t(info.y);
+                row_len = info.z;
             } else {
-                e0 = load_ip(a.indptr, a.ip64, row);
-                e1 = load_ip(a.indptr, a.ip64, row + 1);
+                row = a.row_perm ? int64_t(a.row_perm[bin.item_begin + item]) : bin.item_begin + item;
+                begin = load_ip(a.indptr, a.ip64, row);
+                row_len = load_ip(a.indptr, a.ip64, row + 1) - begin;
             }
-            row_len = e1 - e0;
+            e0 = a.p_indptr ? a.p_indptr[bin.item_begin + item] : begin;
+            e1 = e0 + row_len;
+            if (COEF) wdelta = begin - e0;
         }
     }
     if (coop) {  // this wavefront's quarter of the list
@@ -1454,6 +1459,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         a.relu = relu;
         if (plan) {
             a.row_perm = plan->row_perm;
+            a.row_info = plan->row_info;
             a.chunks = plan->chunks;
             // The scratch rows are F wide for every slab; point at this slab's columns.
             a.partial = partial ? partial + f0 : nullptr;

@@ -40,6 +40,7 @@ struct ApArgs {
     int32_t d;
     int32_t ip64;
     const int32_t *row_perm;
+    const int4 *row_info;  // see gnn_plan; or nullptr
     const int64_t *chunks;
     float *pval;       // hub pieces: partial values   [n_chunks, ldp]
     int32_t *parg;     // hub pieces: partial winners  [n_chunks, ldp]
@@ -171,9 +172,16 @@ __device__ __forceinline__ Group locate_group(const ApArgs &a, int64_t vblock) {
     } else {
         const int64_t item = wave_in_bin * (64 >> bin.log2_g) + (lane >> bin.log2_g);
         if (item < bin.n_items) {
-            g.row = a.row_perm ? int64_t(a.row_perm[bin.item_begin + item]) : bin.item_begin + item;
-            g.e0 = load_ip(a.indptr, a.ip64, g.row);
-            g.e1 = load_ip(a.indptr, a.ip64, g.row + 1);
+            if (a.row_info) {
+                const int4 info = a.row_info[bin.item_begin + item];
+                g.row = info.x;
+                g.e0 = uint32_t(info.y);
+                g.e1 = g.e0 + info.z;
+            } else {
+                g.row = a.row_perm ? int64_t(a.row_perm[bin.item_begin + item]) : bin.item_begin + item;
+                g.e0 = load_ip(a.indptr, a.ip64, g.row);
+                g.e1 = load_ip(a.indptr, a.ip64, g.row + 1);
+            }
         }
     }
     if (g.coop) {
@@ -583,6 +591,7 @@ unsigned grid_1d(int64_t work, int64_t cap = int64_t(1) << 17) {
 int64_t make_bins(ApArgs &a, const gnn_plan *plan, int64_t N, int log2_c, int slices = 1) {
     if (plan) {
         a.row_perm = plan->row_perm;
+        a.row_info = plan->row_info;
         a.chunks = plan->chunks;
     }
     return gnn_fill_bins(a.bins, &a.n_bins, a.first_block, plan, N, log2_c, INT32_MAX, slices);

@@ -62,6 +62,7 @@ struct PlanJob {
     RowTotals *totals;         // zeroed
     RowTotals *host;
     int32_t *row_perm;
+    int4 *row_info;            // or null
     int64_t *hub_offsets;
     int64_t *chunks;
 };
@@ -137,8 +138,10 @@ __global__ void __launch_bounds__(kSplitThreads) plan_place_kernel(PlanJobs jobs
     }
     int64_t v = int64_t(blockIdx.x) * kSplitThreads + threadIdx.x;
     int bin = -1;
+    int64_t begin = 0, deg = 0;
     if (v < jobs.N) {
-        int64_t deg = load_ip(job.indptr, jobs.ip64, v + 1) - load_ip(job.indptr, jobs.ip64, v);
+        begin = load_ip(job.indptr, jobs.ip64, v);
+        deg = load_ip(job.indptr, jobs.ip64, v + 1) - begin;
         bin = bin_of(deg, jobs.thr);
     }
     int rank_in_wave = 0;
@@ -153,6 +156,7 @@ __global__ void __launch_bounds__(kSplitThreads) plan_place_kernel(PlanJobs jobs
         for (int w = 0; w < wave; ++w) before += wave_tot[w][bin];
         int64_t pos = job.block_counts[int64_t(bin) * jobs.n_blocks + blockIdx.x] + before + rank_in_wave;
         job.row_perm[pos] = static_cast<int32_t>(v);
+        if (job.row_info) job.row_info[pos] = make_int4(static_cast<int32_t>(v), static_cast<int32_t>(begin), static_cast<int32_t>(deg), 0);
     }
 }
 
@@ -618,6 +622,7 @@ extern "C" GNN_API void gnn_plan_destroy(gnn_plan *plan) {
     for (int i = 0; i < 3; ++i) gnn_dev_free(plan->blk_edge_scale[i]);
     gnn_dev_free(plan->blk_bound_w);
     gnn_dev_free(plan->row_perm);
+    gnn_dev_free(plan->row_info);
     gnn_dev_free(plan->col_counts);
     gnn_dev_free(plan->chunks);
     gnn_dev_free(plan->hub_chunk_offsets);
@@ -690,6 +695,7 @@ int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, 
     for (int i = 0; i < n_plans; ++i) {
         gnn_plan *p = plans[i];
         if (!gnn_dev_alloc(&p->row_perm, N, stream) || !gnn_dev_alloc(&p->col_counts, N, stream)) return GNN_ERR_ALLOC;
+        if (E <= INT32_MAX && !gnn_dev_alloc(&p->row_info, N, stream)) return GNN_ERR_ALLOC;
         if (hub_bound > 0 && (!gnn_dev_alloc(&p->hub_chunk_offsets, hub_bound + 1, stream) ||
                               !gnn_dev_alloc(&p->chunks, 3 * chunk_bound, stream))) return GNN_ERR_ALLOC;
         if (!(host.p[i] = gnn_host_block())) return GNN_ERR_ALLOC;
@@ -701,6 +707,7 @@ int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, 
         j.totals = reinterpret_cast<RowTotals *>(totals + i * totals_words);
         j.host = static_cast<RowTotals *>(host.p[i]);
         j.row_perm = p->row_perm;
+        j.row_info = p->row_info;
         j.hub_offsets = p->hub_chunk_offsets;
         j.chunks = p->chunks;
     }

@@ -342,9 +342,16 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     const int64_t vblock = int64_t(blockIdx.x) >> a.log2_slices;
     const int col_base = slice * a.slice_cols;
     const int Fk = a.F - col_base < a.slice_cols ? a.F - col_base : a.slice_cols;  // columns of this slice
-    if (Fk <= 0) return;
-    const int b = gnn_bin_of_block(a.first_block, a.bins, a.n_bins, vblock);
+    // What the way to the first gather needs arrives with the bins: one wait, where the compiler would load each at its use.
+    const int4 *row_info = a.row_info;
+    const int64_t *p_indptr = a.p_indptr;
+    const int32_t *indices = a.indices;
+    const void *table = a.X;
+    int64_t table_ld = a.ldx, slice_stride = a.slice_stride;
+    asm volatile("" : "+s"(row_info), "+s"(p_indptr), "+s"(indices), "+s"(table), "+s"(table_ld), "+s"(slice_stride));
+    const int b = gnn_bin_of_block(a.first_block, vblock);
     const BinDesc bin = a.bins[b];
+    if (Fk <= 0) return;
     const bool coop = COOP && (bin.kind & GNN_BIN_COOP);
     const int64_t wave_in_bin = coop ? vblock - bin.first_block : (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;
 
@@ -377,8 +384,8 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
         const int64_t item = wave_in_bin * (64 >> bin.log2_g) + (lane >> bin.log2_g);
         if (item < bin.n_items) {
             int64_t begin;
-            if (a.row_info) {
-                const int4 info = a.row_info[bin.item_begin + item];
+            if (row_info) {
+                const int4 info = row_info[bin.item_begin + item];
                 row = info.x;
                 begin = uint32_t(info.y);
                 row_len = info.z;
@@ -387,7 +394,7 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
                 begin = load_ip(a.indptr, a.ip64, row);
                 row_len = load_ip(a.indptr, a.ip64, row + 1) - begin;
             }
-            e0 = a.p_indptr ? a.p_indptr[bin.item_begin + item] : begin;
+            e0 = p_indptr ? p_indptr[bin.item_begin + item] : begin;
             e1 = e0 + row_len;
             if (COEF) wdelta = begin - e0;
         }
@@ -406,10 +413,10 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
 
     // the slice that holds the last, short line of the rows gathers it from the dense tail table
     const bool is_tail = slice == a.tail_slice;
-    const bool own_table = is_tail || a.slice_stride > 0;  // columns are addressed within the slice
+    const bool own_table = is_tail || slice_stride > 0;  // columns are addressed within the slice
     const T *__restrict__ X = is_tail ? static_cast<const T *>(a.X_tail)
-                                      : static_cast<const T *>(a.X) + int64_t(slice) * a.slice_stride;
-    const int64_t ldx = is_tail ? a.ld_tail : (a.slice_stride > 0 ? int64_t(a.slice_cols) : a.ldx);
+                                      : static_cast<const T *>(table) + int64_t(slice) * slice_stride;
+    const int64_t ldx = is_tail ? a.ld_tail : (slice_stride > 0 ? int64_t(a.slice_cols) : table_ld);
     int col[NPASS];    // column in the output (and in a caller's matrix)
     int lcol[NPASS];   // column in the table this slice gathers from
     int ncols[NPASS];  // valid columns of the strip (< VEC only for the last strip of a padded matrix)
@@ -438,7 +445,7 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
             u_out[q] = 0;
             cf_out[q] = 0.0f;
             if (e < e1) {
-                u_out[q] = a.indices[e];
+                u_out[q] = indices[e];
                 if (COEF) {
                     cf_out[q] = a.w ? a.w[e + wdelta] : 1.0f;
                     if (a.edge_scale) cf_out[q] *= a.edge_scale[e + wdelta];

@@ -147,7 +147,7 @@ __device__ __forceinline__ Group locate_group(const ApArgs &a, int64_t vblock) {
     Group g;
     const int lane = threadIdx.x & 63;
     const int wave_in_block = threadIdx.x >> 6;
-    const int b = gnn_bin_of_block(a.first_block, a.bins, a.n_bins, vblock);
+    const int b = gnn_bin_of_block(a.first_block, vblock);
     const ApBin bin = a.bins[b];
     g.coop = (bin.kind & GNN_BIN_COOP) != 0;
     const int64_t wave_in_bin = g.coop ? vblock - bin.first_block : (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;

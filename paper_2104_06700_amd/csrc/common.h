@@ -532,18 +532,17 @@ struct gnn_bin_desc {
 
 constexpr int GNN_WAVES_PER_BLOCK = 4;  // 256-thread workgroups
 
-// The bin of a workgroup.  The first workgroups of the first 16 bins (INT32_MAX behind the last) arrive in one scalar load; walking
+// The bin of a workgroup.  The first workgroups of the bins (INT32_MAX behind the last) arrive in one scalar load; walking
 // the descriptors instead is a load and a wait per bin, a good part of what a workgroup of short rows takes (F=29 on
-// power-law graphs of 4,600 vertices 11.9 -> 10.7 us a call, 27.8 M vertices bf16 17.5 -> 17.0 ms).  More bins than that are walked.
+// power-law graphs of 4,600 vertices 11.9 -> 10.7 us a call, 27.8 M vertices bf16 17.5 -> 17.0 ms).
 constexpr int GNN_FLAT_BINS = 16;
-__device__ static inline int gnn_bin_of_block(const int32_t (&first_block)[GNN_FLAT_BINS], const gnn_bin_desc *bins, int n_bins, int64_t block) {
+__device__ static inline int gnn_bin_of_block(const int32_t (&first_block)[GNN_FLAT_BINS], int64_t block) {
     int b = 0;
 #pragma unroll
     for (int i = 1; i < GNN_FLAT_BINS; ++i) b = int32_t(block) >= first_block[i] ? i : b;
-    for (int i = GNN_FLAT_BINS; i < n_bins; ++i)
-        if (block >= bins[i].first_block) b = i;
     return b;
 }
+static_assert(GNN_MAX_BINS <= GNN_FLAT_BINS, "a launch has at most one bin per bin of the plan");
 
 // Fills `bins` for a launch whose row groups have 2^log2_c column lanes; returns the number of
 // workgroups.  plan == nullptr: all N rows in one bin, whole wavefronts per row.

@@ -59,7 +59,7 @@ struct gnn_plan {
     int64_t bin_edges[GNN_MAX_BINS] = {0};        // edges of the rows of each bin (host)
     int32_t *row_perm = nullptr;      // [n_rows]
     // The row at every position of row_perm, the first of its edges, their number (and nothing): one load in the place of two
-    // that wait for each other.  E <= INT32_MAX, else nullptr.
+    // that wait for each other.  E <= INT32_MAX, else nullptr; row_perm lies behind it in the same block.
     int4 *row_info = nullptr;
     int32_t *col_counts = nullptr;    // [n_rows] occurrences of each vertex in indices
     // hub rows = rows of the last bin when params.hub_chunk > 0

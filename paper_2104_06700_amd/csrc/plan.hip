@@ -621,8 +621,8 @@ extern "C" GNN_API void gnn_plan_destroy(gnn_plan *plan) {
     gnn_dev_free(plan->tile_partial);
     for (int i = 0; i < 3; ++i) gnn_dev_free(plan->blk_edge_scale[i]);
     gnn_dev_free(plan->blk_bound_w);
-    gnn_dev_free(plan->row_perm);
-    gnn_dev_free(plan->row_info);
+    if (plan->row_info) gnn_dev_free(plan->row_info);  // with row_perm behind it
+    else gnn_dev_free(plan->row_perm);
     gnn_dev_free(plan->col_counts);
     gnn_dev_free(plan->chunks);
     gnn_dev_free(plan->hub_chunk_offsets);
@@ -694,8 +694,13 @@ int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, 
     host.stream = stream;
     for (int i = 0; i < n_plans; ++i) {
         gnn_plan *p = plans[i];
-        if (!gnn_dev_alloc(&p->row_perm, N, stream) || !gnn_dev_alloc(&p->col_counts, N, stream)) return GNN_ERR_ALLOC;
-        if (E <= INT32_MAX && !gnn_dev_alloc(&p->row_info, N, stream)) return GNN_ERR_ALLOC;
+        if (E <= INT32_MAX) {  // one block for both: a plan of a mini-batch is made in every step
+            if (!gnn_dev_alloc(&p->row_info, N + (N + 3) / 4, stream)) return GNN_ERR_ALLOC;
+            p->row_perm = reinterpret_cast<int32_t *>(p->row_info + N);
+        } else if (!gnn_dev_alloc(&p->row_perm, N, stream)) {
+            return GNN_ERR_ALLOC;
+        }
+        if (!gnn_dev_alloc(&p->col_counts, N, stream)) return GNN_ERR_ALLOC;
         if (hub_bound > 0 && (!gnn_dev_alloc(&p->hub_chunk_offsets, hub_bound + 1, stream) ||
                               !gnn_dev_alloc(&p->chunks, 3 * chunk_bound, stream))) return GNN_ERR_ALLOC;
         if (!(host.p[i] = gnn_host_block())) return GNN_ERR_ALLOC;

@@ -617,7 +617,13 @@ __global__ void __launch_bounds__(256) hub_finalize_kernel(const int32_t *__rest
     const float ds = scale_of(dst_mode, load_ip(indptr, ip64, row + 1) - load_ip(indptr, ip64, row));
     for (int colx = col_begin + threadIdx.x; colx < F; colx += blockDim.x) {
         float sum = 0.0f;
-        for (int64_t p = p0; p < p1; ++p) sum += partial[p * ldp + colx];
+        for (int64_t p = p0; p < p1; p += 8) {  // eight pieces on their way at a time, added in order
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = partial[(p + k < p1 ? p + k : p1 - 1) * ldp + colx];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sum = p + k < p1 ? sum + v[k] : sum;
+        }
         if (self_mode != kSelfNone)
             sum = fmaf(self_mode == kSelfInvPlus1 ? scale_of(kScaleInvPlus1, col_counts[row]) : 1.0f,
                        own_row_value<T>(own, row, colx), sum);

@@ -1384,9 +1384,10 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     int64_t plain_hub_col_begin = F;  // ... from this column on
 
     // The short rows of the blocked launches run on a second stream beside the tiles and pieces: they write other rows and
-    // read the same tables.  One after the other -> side by side: 2.45 M vertices F=100 4.37 -> 4.31 ms, F=256 8.36 -> 8.35,
-    // 233 K vertices F=256 3.27 -> 3.26, F=602 7.85 -> 8.00 (before the tiles took the gathers that hit in the L2s away
-    // from the pieces: 5.57 -> 5.32 and 10.11 -> 9.98 on the first).
+    // read the same tables.  It paid when pieces and short rows were bound by different things (2.45 M vertices F=100 5.57 -> 5.32
+    // ms); since the tiles took the gathers that hit in the L2s, one after the other, side by side, and the short rows behind the
+    // tiles measure the same within 1 % on every large graph tried (2.45 M vertices F=100 + 256 23.2 and 23.1 ms, 233 K vertices
+    // 19.0 and 19.0).
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     if (bl.active && !(o.flags & GNN_FLAG_NO_SHORT_ROW_OVERLAP)) {

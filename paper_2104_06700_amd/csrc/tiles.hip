@@ -15,13 +15,12 @@
 // than the mean is cut into parts (else it alone would set the time of its workgroup: worst workgroup 4.1 x the
 // mean without, 1.02 x with), and the bundles are dealt to the wavefronts like cards.
 //
-// What bounds it: LDS reads.  Of the cycles in which a compute unit has a wavefront of the launch the LDS is active in
-// 75 to 82 %, a third of these with bank conflicts (the lines that a read of 64 lanes touches lie anywhere in the tile);
-// vector instructions (one multiply-add per LDS address, one add per element) take about 47 clocks per eight edges of a
-// wavefront's rows beside them.  Measured on the 233 K-vertex graph (95.6 M of 114.6 M edges staged, 85 % of the slots
-// filled): F=602, 19 lines, 4.0 ms alone = 58 TB/s of lines wanted, where the same edges as pieces took 9.5 ms; the call
-// 11.45 -> 7.9 ms.  The 2.45 M-vertex graph (56 of 124 M edges): F=256 1.07 ms alone for 2.8; the call, most of which the
-// short rows take, 9.15 -> 8.35 ms.
+// What bounds it: vector instructions (four additions per lane and line, one multiply-add for the line's address, half a
+// move), which fill 88 % of the cycles in which a compute unit has a wavefront of the launch; the LDS is active in 70 %, one
+// hundredth of that in bank conflicts (a third before the streams were ordered by banks).  Measured on the 233 K-vertex graph: F=602,
+// 19 lines, 3.8 ms alone, where the same edges as pieces took over 9.5 ms; the call 11.45 -> 8.0 (tiles) -> 7.0 (order) ->
+// 6.85 ms (half of the next tile fetched ahead).  The 2.45 M-vertex graph: F=256 1.23 ms alone; the call, half of which the
+// short rows take, 9.15 -> 8.35 -> 7.50 ms.
 #include <new>
 #include <type_traits>
 #include <utility>

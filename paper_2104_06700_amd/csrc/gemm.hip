@@ -713,8 +713,8 @@ static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
     if (tiles >= 512 || K < 1024) return 1;
     int64_t split = (256 * s.resident + tiles - 1) / tiles;
     // At least GNN_SPLIT_MIN_K k-steps per part: a part is bound by the latency of its tiles of 16 k-steps, one after the other, while
-    // the chip is not full (24,490 rows into 256 x 256: 0.20 ms with parts of 1024, 0.047 with 128, 0.044 with 64; 7,265 into
-    // 50 x 16 14.3 and 12.7 us with 128 and 64); the partial planes cost little beside that.
+    // the chip is not full (24,490 rows into 256 x 256: 0.20 ms with parts of 1024, 0.047 with 128); the partial planes cost little
+    // beside that.  Parts of 64 were another 3 us faster, but callers and the layers count on one plane per 128 rows at most.
     const int64_t max_split = K / GNN_SPLIT_MIN_K;
     if (split > max_split) split = max_split;
     if (split > 4096) split = 4096;

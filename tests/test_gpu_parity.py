@@ -228,6 +228,31 @@ def test_padded_copy_route(f, dtype, hubs):
         assert torch.isnan(out[:, f:]).all()
 
 
+@pytest.mark.parametrize("f,dtype", [(64, torch.float32), (65, torch.float32), (100, torch.float32), (129, torch.float32),
+                                     (100, torch.bfloat16), (104, torch.bfloat16)])
+@pytest.mark.parametrize("max_slices", [1, 8])
+def test_copies_leave_out_rows_that_nobody_gathers(f, dtype, max_slices):
+    """Only every third vertex has outgoing edges, some have no edges at all; the plan's copy holds NaN in all rows before
+    each call (a backward SAGE call copies every row), so a read of a row that was left out shows."""
+    full = synth.small_random_multigraph(900, 30000, 77)
+    keep = (full.src % 3 == 1) & (full.dst % 7 != 2)
+    el = synth.EdgeList(n=full.n, src=full.src[keep], dst=full.dst[keep])
+    dg = device_graph(el, plan_params=gnn.make_plan_params([2, 16], 24))
+    indptr, indices, indptr_t, _, _ = host_csr(el)
+    X = synth.normal_features(el.n, f, 10, dtype=dtype)
+    Xd, poison = X.to(DEV), torch.full((el.n, f), float("nan"), dtype=dtype, device=DEV)
+    for op_name, oop in (("sum", oracle.OP_SUM), ("mean", oracle.OP_MEAN), ("gcn", oracle.OP_GCN_SYM), ("sage", oracle.OP_SAGE_GCN)):
+        Yo, S = oracle.aggregate_fwd(indptr, indices, X.float().numpy(), op=oop, dout=np.diff(indptr_t), nthreads=8, want_scale=True)
+        Y = torch.empty_like(Xd)
+        gnn.gnn_aggregate_bwd(dg.indptr, dg.indices, None, poison, Y, el.n, f, gnn.GNN_SAGE_GCN, plan=dg.plan_fwd,
+                              flags=gnn.GNN_FLAG_FORCE_PADDED_COPY, max_slices=max_slices)
+        Y.fill_(float("nan"))
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, None, Xd, Y, el.n, f, OP_CODE[op_name], plan=dg.plan_fwd,
+                              flags=gnn.GNN_FLAG_FORCE_PADDED_COPY, max_slices=max_slices)
+        torch.cuda.synchronize()
+        assert_close(Y, Yo, S, dtype == torch.bfloat16, f"{op_name} F={f}")
+
+
 # -------------------------------------------------------------- integer parts
 @pytest.mark.parametrize("name,scale,ip64", [("er_tiny", 1.0, False), ("rmat_sparse_stack", 0.02, False),
                                              ("rmat_dense_wide", 0.01, True), ("rmat_capacity", 0.0005, True)])

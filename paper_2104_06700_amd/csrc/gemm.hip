@@ -714,7 +714,8 @@ static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
     int64_t split = (256 * s.resident + tiles - 1) / tiles;
     // At least GNN_SPLIT_MIN_K k-steps per part: a part is bound by the latency of its tiles of 16 k-steps, one after the other, while
     // the chip is not full (24,490 rows into 256 x 256: 0.20 ms with parts of 1024, 0.047 with 128); the partial planes cost little
-    // beside that.  Parts of 64 were another 3 us faster, but callers and the layers count on one plane per 128 rows at most.
+    // beside that.  Parts of 64 gain another 3 us in the product alone, but the three layers of such a graph take 565 us with them
+    // and 541 with 128: twice the planes to add up.
     const int64_t max_split = K / GNN_SPLIT_MIN_K;
     if (split > max_split) split = max_split;
     if (split > 4096) split = 4096;

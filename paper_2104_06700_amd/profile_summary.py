@@ -323,7 +323,7 @@ def write_bench_stats(d: str, out_dir: str) -> None:
     print(f"wrote {path}")
 
 
-LAYER_KERNELS = CALL_KERNELS + ("gemm_kernel", "gemm_reduce_kernel", "mask_colsum_kernel", "colsum_reduce_kernel", "zero_kernel")
+LAYER_KERNELS = CALL_KERNELS + ("gemm_kernel", "tall_kernel", "few_k_kernel", "gemm_reduce_kernel", "mask_colsum_kernel", "colsum_reduce_kernel", "zero_kernel")
 
 
 def write_layer_summary(d: str, out_dir: str) -> None:

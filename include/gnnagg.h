@@ -316,9 +316,10 @@ GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indices, const in
 /* ------------------------------------------------ dense update of a layer (fp32) */
 
 /* The MLP step that follows the aggregation in every layer (Section 6.3, "Memory": weight
- * matrices f x h1, h1 x h2, h2 x l), on the matrix cores: every operand as three bf16 numbers whose sum
- * it is, six of their nine products, fp32 sums (closer to the exact result than a chain of fp32
- * multiply-adds; infinities, NaNs and very small results are formed by fp32 instructions):
+ * matrices f x h1, h1 x h2, h2 x l), on the matrix cores: every operand, of any magnitude, as three bf16
+ * numbers whose sum (times a power of two) it is, six of their nine products, fp32 sums (closer to the exact
+ * result than a chain of fp32 multiply-adds; where operands of 2^112 and more, infinities or NaNs take part, or
+ * sums of products reach 2^96, fp32 instructions form the results):
  *     C[m, n] = act( sum_k opA(A)[m, k] * opB(B)[k, n] + bias[n] ),   act = max(., 0) if relu
  * A is stored [M, K] with row stride lda, or [K, M] when trans_a; B is stored [K, N] with row
  * stride ldb, or [N, K] when trans_b; C [M, ldc] is overwritten; bias [N] or NULL.  All device

@@ -73,9 +73,14 @@ __device__ __forceinline__ uint32_t bf16_pair(float x, float y) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// x = p[0] + p[1] + p[2] exactly: 24 significant bits are three times the eight of a bf16.  Each difference below is
-// exact (the rounded part shares the leading bits), |p[1]| <= 2^-9 |x|, |p[2]| <= 2^-18 |x|.  What is not finite, or rounds up
-// to infinity, leaves NaNs that reach every result it takes part in (see the end of gemm_kernel).
+// Operands are multiplied by 2^16 before they are split, and the sums of their products by 2^-32 (add_tile), both exact: a float is a
+// multiple of 2^-149, so what is split is one of 2^-133, bf16's smallest number, and no part of any operand is cut off there;
+// and sums of products lose nothing to underflow that the result could show.
+constexpr float kOperandScale = 0x1p16f, kSumScale = 0x1p-32f;
+
+// x = p[0] + p[1] + p[2] exactly: 24 significant bits are three times the eight of a bf16, and x is a multiple of 2^-133.  Each
+// difference below is exact (the rounded part shares the leading bits), |p[1]| <= 2^-9 |x|, |p[2]| <= 2^-18 |x|.  What is not
+// finite, or rounds up to infinity, leaves infinities and NaNs that reach every result it takes part in (recompute_if_needed).
 __device__ __forceinline__ void split8(const float (&x)[8], uint4 (&p)[3]) {
     uint32_t w[3][4];
 #pragma unroll
@@ -109,10 +114,12 @@ __device__ __forceinline__ void sum_of_products(float16v &sum, const bf16x8 (&a)
 }
 
 // What is cut off is cut off towards minus infinity, which would add up over the steps of a long k and over the rows of a later
-// sum (a bias gradient).  So in step t the rows of A whose number plus t is odd are negated (row_sign), and their sums subtracted.
-__device__ __forceinline__ uint32_t row_sign(int row, int t) { return uint32_t(row + t) << 31; }
+// sum (a bias gradient).  So in step t the rows of A whose number plus t is odd are negated (row_scale), and their sums subtracted.
+__device__ __forceinline__ float row_scale(int row, int t) {
+    return __uint_as_float(__float_as_uint(kOperandScale) ^ (uint32_t(row + t) << 31));
+}
 __device__ __forceinline__ void add_tile(float16v &acc, const float16v &sum, int t) {
-    const float s = (t & 1) ? -1.0f : 1.0f;
+    const float s = (t & 1) ? -kSumScale : kSumScale;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = fmaf(sum[v], (v & 1) ? -s : s, acc[v]);
 }
@@ -212,7 +219,7 @@ struct Stager {
             for (int i = 0; i < 8; ++i) v[set][h][i] = half_of(h) * 8 + i >= n ? v[set][h][i] : 0.0f;
     }
 
-    // flip: the rows are negated as in step `t` (row_sign)
+    // flip: the rows are negated as in step `t` (row_scale)
     __device__ __forceinline__ void store(SplitTile<ROWS> &tile, bool gated, bool with_sums, float (&sums)[PER_THREAD][2], bool flip, int t, int set = 0) {
 #pragma unroll
         for (int h = 0; h < PER_THREAD; ++h) {
@@ -228,10 +235,9 @@ struct Stager {
                     sums[h][1] = (t & 1) ? sums[h][1] + x : sums[h][1];
                 }
             }
-            if (flip) {
+            const float scale = flip ? row_scale(row_of(h), t) : kOperandScale;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[set][h][i] = __uint_as_float(__float_as_uint(v[set][h][i]) ^ row_sign(row_of(h), t));
-            }
+            for (int i = 0; i < 8; ++i) v[set][h][i] *= scale;
             uint4 q[3];
             split8(v[set][h], q);
             const int r = row_of(h), s = SplitTile<ROWS>::slot(half_of(h), r & 31);
@@ -241,33 +247,21 @@ struct Stager {
     }
 };
 
-// An operand that is not finite (or within 2^-9 of the largest float) splits into NaNs, and so none of the results it takes
-// part in is finite; the third part of an operand below 2^-110 is cut off where bf16 ends, and results below 2^-90 are
-// where that could be seen.  A wavefront with such a result computes its tiles again from the operands as they are, by the fp32
-// matrix instruction.
+// An operand that is not finite, or 2^112 and more, splits into infinities and NaNs, and so do the sums of 16 products that reach
+// 2^96: none of the results they take part in is finite.  A wavefront with such a result computes its tiles again from the
+// operands as they are, by the fp32 matrix instruction.
 template <int TI, int TJ>
 __device__ __forceinline__ void recompute_if_needed(const GemmArgs &g, float16v (&acc)[TI][TJ], int64_t m0, int64_t n0, int64_t k_begin,
                                                     int64_t k_end) {
-    constexpr float kSmall = 0x1p-90f;
-    float most = 0.0f, least = 1.0f;  // of the absolute values; a NaN stays in `most`
+    float most = 0.0f;  // of the absolute values; a NaN stays
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; v += 2) {
+            for (int v = 0; v < 16; v += 2)
                 asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(acc[i][j][v]), "v"(acc[i][j][v + 1]));
-                asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(least) : "v"(acc[i][j][v]), "v"(acc[i][j][v + 1]));
-            }
-    bool again = !(most <= 0x1.fffffep127f);
-    if (__any(least < kSmall)) {  // a zero, most likely
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int j = 0; j < TJ; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) again |= acc[i][j][v] != 0.0f && !(fabsf(acc[i][j][v]) >= kSmall);
-    }
+    const bool again = !(most <= 0x1.fffffep127f);
     if (!__any(again)) return;
     const int l32 = threadIdx.x & 31, lk = (threadIdx.x >> 5) & 1;
 #pragma unroll
@@ -535,7 +529,7 @@ __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu
             for (int i = 0; i < 8; ++i) va[p][i] = i + lk * 8 >= repeated ? va[p][i] : 0.0f;
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) va[p][i] = __uint_as_float(__float_as_uint(va[p][i]) ^ row_sign(lane, p));
+        for (int i = 0; i < 8; ++i) va[p][i] *= row_scale(lane, p);
         uint4 q[3];
         split8(va[p], q);
         if constexpr (!FEW_K) load_a(t + 2, p);

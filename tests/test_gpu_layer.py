@@ -396,8 +396,8 @@ def test_matmul_edges_of_the_steps_of_k(m, n, k, ta, tb):
 @pytest.mark.parametrize("m,n,k,ta", [(70_000, 200, 40, False), (60_000, 47, 33, False), (66_000, 16, 50, False), (200, 140, 30_011, True),
                                       (130, 60, 2_000, True), (100, 20, 5_003, True), (100, 100, 3_000, True), (64, 64, 2_048, False)])
 def test_matmul_of_operands_outside_the_split(m, n, k, ta):
-    """Infinities, NaNs and values near the largest float have no exact three parts, and tiny ones lose their last: the tiles they
-    take part in are computed from the operands as they are."""
+    """Infinities, NaNs and values from 2^112 on have no exact three parts: the tiles they take part in are computed from the operands
+    as they are."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(m + n + k)
     A = torch.empty(k if ta else m, m if ta else k, device=DEV).normal_(generator=gen)
@@ -406,7 +406,7 @@ def test_matmul_of_operands_outside_the_split(m, n, k, ta):
     flat[17], flat[1000], flat[-3], flat[-1] = float("inf"), float("nan"), -float("inf"), 3.4e38
     rows = A.t() if ta else A
     rows[5] = 0.0          # a row of zeros stays zero
-    rows[7] *= 2.0 ** -118  # results far below 2^-90
+    rows[7] *= 2.0 ** -118
     B[k // 2, n // 2] = 0.0
     need = gnn.gnn_matmul_workspace_bytes(m, n, k)
     ws = torch.empty(max(need // 4, 4), device=DEV)
@@ -427,3 +427,57 @@ def test_matmul_of_operands_outside_the_split(m, n, k, ta):
     err = (C.double() - ref).abs()[good]
     assert bool((err <= 2e-5 * S[good] + 2.0 ** -148).all())
     assert bool((C[5][good[5]] == 0).all())
+
+
+@pytest.mark.parametrize("m,n,k,ta", [(64, 64, 64, False), (300, 47, 100, False), (300, 130, 33, False), (130, 33, 9, False), (70, 65, 9, True),
+                                      (66_000, 16, 20, False), (96, 140, 64, True), (130, 60, 2_048, True), (64, 64, 2_048, False)])
+@pytest.mark.parametrize("tb", [False, True])
+def test_matmul_of_tiny_operands_beside_large_ones(m, n, k, ta, tb):
+    """Every magnitude of a float in either operand, subnormal ones included, against every magnitude of the other; results on both
+    sides of 2^96, where the sums of scaled products end.  The error of a product is 3 * 2^-26 (the partial products left out), that of
+    a chain of k additions k * 2^-24, of the sum of absolute terms; a split reduction has parts of 128 and 16 of them here."""
+    if ta and tb:
+        tb = False  # the remaining layout of a weight gradient
+    rng = np.random.default_rng(17 * m + n + k)
+    A = rng.normal(size=(m, k)) * 2.0 ** rng.integers(-145, 118, size=(m, 1))
+    B = rng.normal(size=(k, n)) * 2.0 ** rng.integers(-145, 118, size=(1, n))
+    A[:, ::5] *= 2.0 ** -20  # and different ones within a row
+    A[3], B[:, 3] = rng.normal(size=k) * 2.0 ** -136, rng.normal(size=k) * 2.0 ** 110
+    A, B = A.astype(np.float32), B.astype(np.float32)
+    Ad = torch.from_numpy(np.ascontiguousarray(A.T) if ta else A).to(DEV)
+    Bd = torch.from_numpy(np.ascontiguousarray(B.T) if tb else B).to(DEV)
+    ws = torch.empty(max(gnn.gnn_matmul_workspace_bytes(m, n, k) // 4, 4), device=DEV)
+    C = torch.empty(m, n, device=DEV)
+    gnn.gnn_matmul(Ad, Bd, C, ta, tb, workspace=ws)
+    torch.cuda.synchronize()
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    ref, S = A64 @ B64, np.abs(A64) @ np.abs(B64)
+    fits = S < 2.0 ** 127  # no order of the additions passes the largest float
+    got = C.cpu().numpy().astype(np.float64)
+    assert np.isfinite(got[fits]).all()
+    # subnormal sums: each addition rounds to a multiple of 2^-149 (the tiles of results above 2^96 are one chain of k)
+    bound = (min(k, 128 + 16) + 1) * 2.0 ** -24 * S + k * 2.0 ** -149
+    err = np.abs(got - ref)
+    bad = fits & (err > bound)
+    worst = np.unravel_index(np.argmax(np.where(fits, err / bound, 0)), err.shape)
+    assert not bad.any(), f"{bad.sum()} of {bad.size}, worst {worst}: {got[worst]!r} for {ref[worst]!r}, S {S[worst]!r}"
+    for lo, hi in ((0.0, 2.0 ** -100), (2.0 ** -100, 2.0 ** 90), (2.0 ** 90, 2.0 ** 100), (2.0 ** 100, 2.0 ** 127)):
+        assert ((S > lo) & (S < hi)).any()
+
+
+@pytest.mark.parametrize("k", [5, 16, 40])
+def test_matmul_of_sums_that_cancel_where_scaled_products_overflow(k):
+    """Products of 2^94 to 2^126 of both signs whose sums are small or cancel: no step may lose an overflow."""
+    rng = np.random.default_rng(k)
+    m, n = 256, 64
+    A = rng.normal(size=(m, k)) * 2.0 ** rng.integers(47, 60, size=(m, 1))
+    B = rng.normal(size=(k, n)) * 2.0 ** rng.integers(47, 60, size=(1, n))
+    A[:, k // 2:2 * (k // 2)] = A[:, :k // 2]
+    B[k // 2:2 * (k // 2)] = -B[:k // 2] * (1 + 2.0 ** -12)
+    A, B = A.astype(np.float32), B.astype(np.float32)
+    C = torch.empty(m, n, device=DEV)
+    gnn.gnn_matmul(torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV), C)
+    torch.cuda.synchronize()
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    err, S = np.abs(C.cpu().numpy().astype(np.float64) - A64 @ B64), np.abs(A64) @ np.abs(B64)
+    assert S.max() < 2.0 ** 127 and (err <= (k + 1) * 2.0 ** -24 * S).all()

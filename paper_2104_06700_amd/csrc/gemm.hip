@@ -249,10 +249,10 @@ struct Stager {
 
 // An operand that is not finite, or 2^112 and more, splits into infinities and NaNs, and so do the sums of 16 products that reach
 // 2^96: none of the results they take part in is finite.  A wavefront with such a result computes its tiles again from the
-// operands as they are, by the fp32 matrix instruction.
+// operands as they are, by the fp32 matrix instruction.  always: in any case.
 template <int TI, int TJ>
 __device__ __forceinline__ void recompute_if_needed(const GemmArgs &g, float16v (&acc)[TI][TJ], int64_t m0, int64_t n0, int64_t k_begin,
-                                                    int64_t k_end) {
+                                                    int64_t k_end, bool always = false) {
     float most = 0.0f;  // of the absolute values; a NaN stays
 #pragma unroll
     for (int i = 0; i < TI; ++i)
@@ -261,7 +261,7 @@ __device__ __forceinline__ void recompute_if_needed(const GemmArgs &g, float16v 
 #pragma unroll
             for (int v = 0; v < 16; v += 2)
                 asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(acc[i][j][v]), "v"(acc[i][j][v + 1]));
-    const bool again = !(most <= 0x1.fffffep127f);
+    const bool again = always || !(most <= 0x1.fffffep127f);
     if (!__any(again)) return;
     const int l32 = threadIdx.x & 31, lk = (threadIdx.x >> 5) & 1;
 #pragma unroll
@@ -467,12 +467,18 @@ __global__ void __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_
     write_tiles<TI, TJ>(g, acc, m0 + wm, n0 + wn, bz);
 }
 
+// Of up to this many products fp32 instructions make the better sum: they round where the split sum is cut off.  2-norm error, normal
+// operands, split and fp32: k = 1 3.5e-8 and 2.5e-8, 2 3.3e-8 and 3.1e-8, 3 3.3e-8 and 3.6e-8, 15 3.4e-8 and 7.2e-8.  What bounds
+// such a product is its stores, and those of rows that are not whole lines get in each other's way if more than five wavefronts per
+// SIMD are at it: 2.45 M rows, k = 1, 47 columns 122 us, 193 with eight (split: 144); 256 columns 437 and 462 (split: 509).
+constexpr int kFewProducts = 2;
+
 // Tall products: A row-major with k along its rows (a layer's forward product, and the products with W^T of its backward
 // pass).  A wavefront owns 32 rows of C and TJ * 32 columns: its elements of A go from global memory straight into the
-// lanes that need them, two steps of 16 k ahead of their use, and are split there, once; only B passes through LDS.  FEW_K: less
-// than 16 k, one step of single elements.
-template <int WAVES, int TJ, bool B_K_CONTIG, bool GATED, bool FEW_K = false>
-__global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(TJ >= 4 ? 2 : TJ == 2 && GATED ? 3 : 4, 8))) tall_kernel(const GemmArgs g) {
+// lanes that need them, two steps of 16 k ahead of their use, and are split there, once; only B passes through LDS.  FEW_K: 1 =
+// less than 16 k, one step of single elements; 2 = at most kFewProducts.
+template <int WAVES, int TJ, bool B_K_CONTIG, bool GATED, int FEW_K = 0>
+__global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(FEW_K == 2 ? 4 : TJ >= 4 ? 2 : TJ == 2 && GATED ? 3 : 4, FEW_K == 2 ? 5 : 8))) tall_kernel(const GemmArgs g) {
     constexpr int BM = WAVES * 32, BN = TJ * 32;
     __shared__ __attribute__((aligned(16))) SplitTile<BN> tiles[2];
     const int lane = threadIdx.x & 63;
@@ -562,12 +568,14 @@ __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu
     };
     sb.init(g.B, nullptr, g.sbn, g.sbk, n0, g.N, 0);
     if constexpr (FEW_K) {
-        sb.load_few(int(g.K));
-        load_a(0, 0);
-        sb.store(tiles[0], false, false, no_sum, false, 0);
-        __syncthreads();
-        step(0, 0);
-        recompute_if_needed<1, TJ>(g, acc, m0, n0, 0, g.K);
+        if constexpr (FEW_K != 2) {
+            sb.load_few(int(g.K));
+            load_a(0, 0);
+            sb.store(tiles[0], false, false, no_sum, false, 0);
+            __syncthreads();
+            step(0, 0);
+        }
+        recompute_if_needed<1, TJ>(g, acc, m0, n0, 0, g.K, FEW_K == 2);
         write_tiles<1, TJ>(g, acc, m0, n0, 0);
         return;
     }
@@ -596,11 +604,12 @@ void launch_tall(bool b_k, dim3 grid, hipStream_t stream, const GemmArgs &g) {
     else tall_kernel<WAVES, TJ, false, false><<<grid, WAVES * 64, 0, stream>>>(g);
 }
 
+template <int FEW_K>
 void launch_tall_few_k(bool b_k, dim3 grid, hipStream_t stream, const GemmArgs &g) {
-    if (g.a_gate && b_k) tall_kernel<4, 2, true, true, true><<<grid, 256, 0, stream>>>(g);
-    else if (g.a_gate) tall_kernel<4, 2, false, true, true><<<grid, 256, 0, stream>>>(g);
-    else if (b_k) tall_kernel<4, 2, true, false, true><<<grid, 256, 0, stream>>>(g);
-    else tall_kernel<4, 2, false, false, true><<<grid, 256, 0, stream>>>(g);
+    if (g.a_gate && b_k) tall_kernel<4, 2, true, true, FEW_K><<<grid, 256, 0, stream>>>(g);
+    else if (g.a_gate) tall_kernel<4, 2, false, true, FEW_K><<<grid, 256, 0, stream>>>(g);
+    else if (b_k) tall_kernel<4, 2, true, false, FEW_K><<<grid, 256, 0, stream>>>(g);
+    else tall_kernel<4, 2, false, false, FEW_K><<<grid, 256, 0, stream>>>(g);
 }
 
 template <int WM, int WN, int TI, int TJ>
@@ -793,7 +802,8 @@ int gnn_matmul_impl(const float *A, int64_t lda, int trans_a, const float *B, in
     dim3 grid(static_cast<unsigned>(n_groups));
     const bool b_k = trans_b != 0;  // is k the contiguous direction of the operand?
     if (tall && K < BK) {
-        launch_tall_few_k(b_k, grid, stream, g);
+        if (K <= kFewProducts) launch_tall_few_k<2>(b_k, grid, stream, g);
+        else launch_tall_few_k<1>(b_k, grid, stream, g);
     } else if (K < BK) {
         const int64_t blocks = (M * N + 255) / 256;
         if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;

@@ -481,3 +481,19 @@ def test_matmul_of_sums_that_cancel_where_scaled_products_overflow(k):
     A64, B64 = A.astype(np.float64), B.astype(np.float64)
     err, S = np.abs(C.cpu().numpy().astype(np.float64) - A64 @ B64), np.abs(A64) @ np.abs(B64)
     assert S.max() < 2.0 ** 127 and (err <= (k + 1) * 2.0 ** -24 * S).all()
+
+
+@pytest.mark.parametrize("m,n", [(33, 31), (300, 130), (2048, 256)])
+@pytest.mark.parametrize("tb", [False, True])
+def test_matmul_of_one_or_two_products_rounds_as_fp32_does(m, n, tb):
+    """One product is rounded once, to half a last bit; two are one product and one multiply-add, half a last bit each."""
+    rng = np.random.default_rng(m + n)
+    for k in (1, 2):
+        A = rng.normal(size=(m, k)).astype(np.float32)
+        B = rng.normal(size=(n, k) if tb else (k, n)).astype(np.float32)
+        C = torch.empty(m, n, device=DEV)
+        gnn.gnn_matmul(torch.from_numpy(A).to(DEV), torch.from_numpy(B).to(DEV), C, False, tb)
+        torch.cuda.synchronize()
+        A64, B64 = A.astype(np.float64), B.astype(np.float64).T if tb else B.astype(np.float64)
+        err, S = np.abs(C.cpu().numpy().astype(np.float64) - A64 @ B64), np.abs(A64) @ np.abs(B64)
+        assert (err <= k * 2.0 ** -24 * S).all(), (k, (err / S).max() * 2 ** 24)

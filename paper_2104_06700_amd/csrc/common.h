@@ -45,6 +45,7 @@ struct gnn_tiles {
     float *bound_w = nullptr;            // bound edge weights in stream order, as of binding number bound_version
     int64_t bound_version = -1;
     float *tmp_w = nullptr;              // other coefficients, refilled by every call
+    uint32_t *positions = nullptr;       // CSR position of the edge in every slot of the stream; made for coefficients that are refilled
 };
 
 // One plan = one graph orientation.  All pointers are device memory owned by

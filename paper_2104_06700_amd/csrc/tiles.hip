@@ -294,15 +294,29 @@ struct BankOrder {
     }
 };
 
-// One wavefront per (wavefront of the gather, tile): its stretch of the stream.  W: also (or only) the coefficients,
-// w[epos] * scale[epos] of every edge and 0 where a row is filled up.  L lanes own a row.
-template <int L, bool INDICES, bool W>
+// What tile_fill_kernel writes for every slot of the stream.
+enum TileFill {
+    kFillIndices,    // line of the tile; a line of zeros where a row is filled up
+    kFillCoefs,      // w[epos] * scale[epos]; 0 where a row is filled up
+    kFillPositions,  // epos; kNoEdge where a row is filled up
+};
+constexpr uint32_t kNoEdge = 0xFFFFFFFFu;
+
+__device__ __forceinline__ float coefficient(const float *__restrict__ w, const float *__restrict__ scale, uint32_t p) {
+    if (p == kNoEdge) return 0.0f;
+    const float cf = w ? w[p] : 1.0f;
+    return scale ? cf * scale[p] : cf;
+}
+
+// One wavefront per (wavefront of the gather, tile): its stretch of the stream.  L lanes own a row.
+template <int L, TileFill WHAT>
 __global__ void __launch_bounds__(256) tile_fill_kernel(const TileDesc *__restrict__ tiles, int n_tiles, int64_t n_waves, int rr,
                                                         const uint2 *__restrict__ seg, int64_t n_parts,
                                                         const uint8_t *__restrict__ counts, const uint32_t *__restrict__ wave_off,
                                                         const int32_t *__restrict__ blk_indices, const uint32_t *__restrict__ blk_epos,
                                                         const float *__restrict__ w, const float *__restrict__ scale,
-                                                        int zero_line, uint16_t *__restrict__ stream, float *__restrict__ wstream) {
+                                                        int zero_line, uint16_t *__restrict__ stream, float *__restrict__ wstream,
+                                                        uint32_t *__restrict__ positions) {
     constexpr int ROWS = 64 / L, SLOTS = ROWS * kUnit, C = BankOrder<L>::C;
     const int lane = threadIdx.x & 63, g = lane / L, c = lane & (L - 1);
     const unsigned long long row_lanes = ((1ull << L) - 1ull) << (lane & ~(L - 1));
@@ -342,10 +356,11 @@ __global__ void __launch_bounds__(256) tile_fill_kernel(const TileDesc *__restri
             }
             const int n_slots = n_it * kUnit;
             order.lay_out(n_slots);
-            auto put = [&](int slot, int idx, float cf) {
+            auto put = [&](int slot, int idx, uint32_t p) {
                 const int64_t at = out + int64_t(slot / kUnit) * SLOTS + g * kUnit + slot % kUnit;
-                if (INDICES) stream[at] = uint16_t(idx);
-                if (W) wstream[at] = cf;
+                if constexpr (WHAT == kFillIndices) stream[at] = uint16_t(idx);
+                else if constexpr (WHAT == kFillPositions) positions[at] = p;
+                else wstream[at] = coefficient(w, scale, p);
             };
             const int spare = n_slots - int(sg.y - sg.x), over = order.overflow();
             for (int k = c; k < spare; k += L) {  // the lines of zeros
@@ -353,7 +368,7 @@ __global__ void __launch_bounds__(256) tile_fill_kernel(const TileDesc *__restri
                 int sec = 0;
 #pragma unroll
                 for (int q = 1; q < C; ++q) sec = slot >= order.begin[q] ? q : sec;
-                put(slot, zero_line + order.line_class(sec), 0.0f);
+                put(slot, zero_line + order.line_class(sec), kNoEdge);
             }
             const BankOrder<L> whole = order;
 #pragma unroll
@@ -364,17 +379,20 @@ __global__ void __launch_bounds__(256) tile_fill_kernel(const TileDesc *__restri
                 const int sec = valid ? section_of(e) : 0;
                 int j;
                 count(sec, valid, j);
-                if (!valid) continue;
-                float cf = 0.0f;
-                if (W) {
-                    const uint32_t p = blk_epos[e];
-                    cf = w ? w[p] : 1.0f;
-                    if (scale) cf *= scale[p];
-                }
-                put(whole.slot(sec, j), blk_indices[e] - tile_begin, cf);
+                if (valid) put(whole.slot(sec, j), blk_indices[e] - tile_begin, WHAT == kFillIndices ? 0u : blk_epos[e]);
             }
             out += int64_t(n_it) * SLOTS;
         }
+    }
+}
+
+// The same coefficients from the positions of a kFillPositions: four slots per thread, no order to work out again.
+__global__ void __launch_bounds__(256) tile_refill_kernel(const uint4 *__restrict__ positions, int64_t n, const float *__restrict__ w,
+                                                          const float *__restrict__ scale, float4 *__restrict__ wstream) {
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const uint4 p = positions[i];
+        wstream[i] = make_float4(coefficient(w, scale, p.x), coefficient(w, scale, p.y), coefficient(w, scale, p.z), coefficient(w, scale, p.w));
     }
 }
 
@@ -627,7 +645,7 @@ int level_of(int lanes, bool bf16) { return (lanes == 8 ? 0 : (lanes == 4 ? 1 : 
 void gnn_tiles_free(gnn_tiles &t) {
     gnn_dev_free(t.part_base); gnn_dev_free(t.order); gnn_dev_free(t.tiles); gnn_dev_free(t.seg); gnn_dev_free(t.stream);
     gnn_dev_free(t.counts); gnn_dev_free(t.wave_off); gnn_dev_free(t.left.pieces); gnn_dev_free(t.left.piece_block);
-    gnn_dev_free(t.left.rowbase); gnn_dev_free(t.bound_w); gnn_dev_free(t.tmp_w);
+    gnn_dev_free(t.left.rowbase); gnn_dev_free(t.bound_w); gnn_dev_free(t.tmp_w); gnn_dev_free(t.positions);
     for (int i = 0; i < 3; ++i) gnn_dev_free(t.scale[i]);
     t = gnn_tiles{};
 }
@@ -802,8 +820,9 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     if ((rc = gnn_scan_exclusive_u32(B.wave_off, n_wt, sums, stream)) != GNN_OK) return rc;
     if (!gnn_dev_alloc(&B.stream, (total + kStreamAhead) * rows * kUnit, stream)) return GNN_ERR_ALLOC;
     auto fill_stream = [&](auto lanes_of_a_row) {
-        tile_fill_kernel<decltype(lanes_of_a_row)::value, true, false><<<grid_for(n_wt * 64, 256), 256, 0, stream>>>(
-            d_tiles, n_tiles, n_waves, rr, seg, n_parts, B.counts, B.wave_off, plan->blk_indices, nullptr, nullptr, nullptr, tile_lines, B.stream, nullptr);
+        tile_fill_kernel<decltype(lanes_of_a_row)::value, kFillIndices><<<grid_for(n_wt * 64, 256), 256, 0, stream>>>(
+            d_tiles, n_tiles, n_waves, rr, seg, n_parts, B.counts, B.wave_off, plan->blk_indices, nullptr, nullptr, nullptr, tile_lines, B.stream, nullptr,
+            nullptr);
     };
     if (lanes == 8) fill_stream(std::integral_constant<int, 8>());
     else if (lanes == 4) fill_stream(std::integral_constant<int, 4>());
@@ -858,17 +877,54 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, hipStream_t stream, con
 
 namespace {
 
+int64_t stream_slots(const gnn_tiles &L) { return L.n_iters * (64 / L.lanes) * kUnit; }
+
 int coef_room(const gnn_tiles &L, float **slot, hipStream_t stream) {
     if (*slot) return GNN_OK;
     (void)hipGetLastError();
-    return gnn_dev_alloc(slot, (L.n_iters + kStreamAhead) * (64 / L.lanes) * kUnit, stream) ? GNN_OK : GNN_ERR_ALLOC;
+    return gnn_dev_alloc(slot, stream_slots(L) + int64_t(kStreamAhead) * (64 / L.lanes) * kUnit, stream) ? GNN_OK : GNN_ERR_ALLOC;
+}
+
+hipError_t fill(const gnn_plan *plan, const gnn_tiles &L, const float *w, const float *scale, float *wstream, uint32_t *positions,
+                hipStream_t stream) {
+    auto launch = [&](auto lanes_of_a_row, auto what) {
+        tile_fill_kernel<decltype(lanes_of_a_row)::value, decltype(what)::value><<<grid_for(L.n_waves * L.n_tiles * 64, 256), 256, 0, stream>>>(
+            static_cast<const TileDesc *>(L.tiles), L.n_tiles, L.n_waves, L.rr, static_cast<const uint2 *>(L.seg), L.n_parts, L.counts, L.wave_off,
+            plan->blk_indices, plan->blk_epos, w, scale, 0, nullptr, wstream, positions);
+    };
+    auto launch_for = [&](auto what) {
+        if (L.lanes == 8) launch(std::integral_constant<int, 8>(), what);
+        else if (L.lanes == 4) launch(std::integral_constant<int, 4>(), what);
+        else launch(std::integral_constant<int, 2>(), what);
+    };
+    if (positions) launch_for(std::integral_constant<TileFill, kFillPositions>());
+    else launch_for(std::integral_constant<TileFill, kFillCoefs>());
+    return hipGetLastError();
+}
+
+// The edge of every slot, for coefficients that are filled in again and again, because working out the order of the slots takes
+// longer than reading the weights (233 K vertices, F=64: weights of every call's own 3.7 -> 1.9 ms a call, bound anew before
+// each call, for two widths 11.2 -> 3.1).  4 bytes a slot, as much as the coefficients.  Without room for it (and under
+// capture) they are filled in as the first time.
+void want_positions(const gnn_plan *plan, gnn_tiles &L, hipStream_t stream) {
+    if (L.positions) return;
+    (void)hipGetLastError();
+    if (!gnn_dev_alloc(&L.positions, stream_slots(L), stream)) {
+        (void)hipGetLastError();
+        L.positions = nullptr;
+    } else if (fill(plan, L, nullptr, nullptr, nullptr, L.positions, stream) != hipSuccess) {
+        gnn_dev_free(L.positions);
+        L.positions = nullptr;
+    }
 }
 
 }  // namespace
 
 int gnn_plan_tile_coef_room(gnn_plan *plan, const gnn_tiles *tiles, hipStream_t stream) {
     gnn_tiles &L = plan->tiles[tiles - plan->tiles];
-    return coef_room(L, &L.tmp_w, stream);
+    const int rc = coef_room(L, &L.tmp_w, stream);
+    if (rc == GNN_OK) want_positions(plan, L, stream);
+    return rc;
 }
 
 // Coefficients of the edges in stream order.  Kept: the plan's own factors, and weights bound to the plan; anything
@@ -877,26 +933,29 @@ int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles_in, const float *
                         hipStream_t stream, const float **out) {
     gnn_tiles &L = plan->tiles[tiles_in - plan->tiles];
     float **slot = &L.tmp_w;
-    bool fill = true;
+    bool need = true;
     if (!w && scale) {
         slot = &L.scale[scale_mode - 1];
-        fill = !*slot;
+        need = !*slot;
     } else if (w && !scale && bound) {
         slot = &L.bound_w;
-        fill = !*slot || L.bound_version != plan->bound_w_version;
+        need = !*slot || L.bound_version != plan->bound_w_version;
     }
+    const bool again = slot == &L.tmp_w || (slot == &L.bound_w && *slot);
     const int rc = coef_room(L, slot, stream);
     if (rc != GNN_OK) return rc;
-    if (fill) {
-        auto coefs = [&](auto lanes_of_a_row) {
-            tile_fill_kernel<decltype(lanes_of_a_row)::value, false, true><<<grid_for(L.n_waves * L.n_tiles * 64, 256), 256, 0, stream>>>(
-                static_cast<const TileDesc *>(L.tiles), L.n_tiles, L.n_waves, L.rr, static_cast<const uint2 *>(L.seg), L.n_parts, L.counts, L.wave_off,
-                plan->blk_indices, plan->blk_epos, w, scale, 0, nullptr, *slot);
-        };
-        if (L.lanes == 8) coefs(std::integral_constant<int, 8>());
-        else if (L.lanes == 4) coefs(std::integral_constant<int, 4>());
-        else coefs(std::integral_constant<int, 2>());
-        if (hipGetLastError() != hipSuccess) {
+    if (need) {
+        if (again) want_positions(plan, L, stream);
+        hipError_t e;
+        if (again && L.positions) {
+            const int64_t n = stream_slots(L) / 4;
+            tile_refill_kernel<<<grid_for(n, 256), 256, 0, stream>>>(reinterpret_cast<const uint4 *>(L.positions), n, w, scale,
+                                                                     reinterpret_cast<float4 *>(*slot));
+            e = hipGetLastError();
+        } else {
+            e = fill(plan, L, w, scale, *slot, nullptr, stream);
+        }
+        if (e != hipSuccess) {
             if (slot != &L.tmp_w && slot != &L.bound_w) {  // an unfilled array must not serve a later call
                 gnn_dev_free(*slot);
                 *slot = nullptr;

@@ -114,3 +114,62 @@ def test_infinities_and_nan_reach_the_rows_that_gather_them_only(f, dtype, bound
     special = ~torch.isfinite(want)
     assert int(special.sum()) > f and torch.equal(~torch.isfinite(y), special)
     assert torch.equal(torch.nan_to_num(y[special].float(), 1.0, 2.0, 3.0), torch.nan_to_num(want[special], 1.0, 2.0, 3.0))
+
+
+@pytest.mark.parametrize("f,dtype,op_name", [(64, torch.float32, "sum"), (8, torch.float32, "sum"), (16, torch.float32, "sum"), (64, torch.bfloat16, "mean")])
+@pytest.mark.parametrize("bound", [False, True])
+def test_coefficients_follow_weights_that_change(f, dtype, op_name, bound):
+    """Coefficients of tiles are filled in over and over, from the second time on through the positions kept for that: new weights in
+    the same array and in another one, factors beside them (bf16 mean, backward), and a refill under capture, where no room for
+    the positions can be had."""
+    el = synth.rmat_symmetric(5300, 1800000, (0.5, 0.2, 0.2, 0.1), 17)
+    indptr, indices, indptr_t, indices_t, perm = host_csr(el)
+    backward = op_name == "mean"
+    dg = device_graph(el, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    plan, ip, ix = (dg.plan_bwd, dg.indptr_t, dg.indices_t) if backward else (dg.plan_fwd, dg.indptr, dg.indices)
+    plan.set_blocking(min_degree=32, hot_lines=992, block_lines=500, max_piece=48, rest_min_count=0)
+    fn = gnn.gnn_aggregate_bwd if backward else gnn.gnn_aggregate_fwd
+    x = synth.normal_features(el.n, f, 3, dtype=dtype)
+    xd, y = x.to(DEV), torch.empty(el.n, f, dtype=dtype, device=DEV)
+    weights = [synth.uniform_features(el.e, 1, seed).reshape(-1) + 0.5 for seed in range(4)]
+    w = torch.empty(el.e, device=DEV)
+
+    def call(array):
+        fn(ip, ix, array, xd, y, el.n, f, OP_CODE[op_name], plan=plan, flags=SLICED, max_slices=8)
+
+    def check(host, what):
+        torch.cuda.synchronize()
+        if backward:
+            ref, S = oracle.aggregate_bwd(indptr_t, indices_t, x.float().numpy(), op=OP_CODE[op_name], wt=host.numpy(), din=np.diff(indptr),
+                                          nthreads=8, want_scale=True)
+        else:
+            ref, S = oracle.aggregate_fwd(indptr, indices, x.float().numpy(), op=OP_CODE[op_name], w=host.numpy(), dout=np.diff(indptr_t),
+                                          nthreads=8, want_scale=True)
+        assert_close(y, ref, S, dtype == torch.bfloat16, what)
+
+    def step(host):
+        w.copy_(host)
+        if bound:
+            plan.bind_edge_weights(w)
+        call(w)
+
+    step(weights[0])
+    check(weights[0], "first")
+    if bound:  # the second filling, captured before there are positions
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            plan.bind_edge_weights(w)
+            call(w)
+        for host in weights[1:3]:
+            w.copy_(host)
+            y.fill_(float("nan"))
+            graph.replay()
+            check(host, "replay")
+    for i, host in enumerate(weights[1:]):
+        step(host)
+        check(host, f"refill {i}")
+        other = weights[i].to(DEV)
+        call(other)  # unbound weights of another array between
+        check(weights[i], f"other array {i}")
+        call(w)
+        check(host, f"refill {i}, after another array")

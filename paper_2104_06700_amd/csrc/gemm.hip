@@ -247,12 +247,41 @@ struct Stager {
     }
 };
 
+// Four k of a row on their way to the fp32 instruction, with their gate.
+template <bool K_CONTIG, bool GATED>
+struct Four {
+    float x[4], gate[GATED ? 4 : 1];
+    static __device__ __forceinline__ void fetch(float (&v)[4], const float *p, int64_t sk) {
+        if constexpr (K_CONTIG) {
+            const f32x4_any q = *reinterpret_cast<const f32x4_any *>(p);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = q[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = p[i * sk];
+        }
+    }
+    __device__ __forceinline__ void load(const float *p, int64_t sk, bool gated, int64_t gate_off) {
+        fetch(x, p, sk);
+        if constexpr (GATED) {
+            if (gated) fetch(gate, p + gate_off, sk);
+        }
+    }
+    __device__ __forceinline__ float at(int i, bool gated) const {
+        if constexpr (GATED) return !gated || gate[i] > 0.0f ? x[i] : 0.0f;
+        else return x[i];
+    }
+};
+
 // An operand that is not finite, or 2^112 and more, splits into infinities and NaNs, and so do the sums of 16 products that reach
 // 2^96: none of the results they take part in is finite.  A wavefront with such a result computes its tiles again from the
-// operands as they are, by the fp32 matrix instruction.  always: in any case.
-template <int TI, int TJ>
+// operands as they are, by the fp32 matrix instruction.  FEW_K: less than 16 products, 2 = in any case.
+// What that costs, 2,449,029 rows, with single elements loaded as they are used -> now, beside finite operands: a row of A that is
+// not finite nothing measurable; one element of B, which every wavefront meets, 256 -> 256 7.4 -> 6.1 ms beside 2.0, 256 -> 47
+// 2.4 -> 1.6 beside 0.74; an element in the weight gradient 256 x 256 4.9 -> 2.6 beside 2.0, nothing finite 9.2 -> 5.9.
+template <bool A_K_CONTIG, bool B_K_CONTIG, bool A_GATED, bool B_GATED, int FEW_K, int TI, int TJ>
 __device__ __forceinline__ void recompute_if_needed(const GemmArgs &g, float16v (&acc)[TI][TJ], int64_t m0, int64_t n0, int64_t k_begin,
-                                                    int64_t k_end, bool always = false) {
+                                                    int64_t k_end) {
     float most = 0.0f;  // of the absolute values; a NaN stays
 #pragma unroll
     for (int i = 0; i < TI; ++i)
@@ -261,7 +290,7 @@ __device__ __forceinline__ void recompute_if_needed(const GemmArgs &g, float16v 
 #pragma unroll
             for (int v = 0; v < 16; v += 2)
                 asm("v_maximum3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(acc[i][j][v]), "v"(acc[i][j][v + 1]));
-    const bool again = always || !(most <= 0x1.fffffep127f);
+    const bool again = FEW_K == 2 || !(most <= 0x1.fffffep127f);
     if (!__any(again)) return;
     const int l32 = threadIdx.x & 31, lk = (threadIdx.x >> 5) & 1;
 #pragma unroll
@@ -270,20 +299,67 @@ __device__ __forceinline__ void recompute_if_needed(const GemmArgs &g, float16v 
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    // Operand layout of the 32x32x2 instruction: lane l holds A[l % 32][l / 32] and B[l / 32][l % 32].  Rows past the end repeat
+    // the last one.  Steps of 8 k: the lower lanes' instructions take the first four, the upper lanes' the others.
+    const float *pa[TI], *pb[TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+        const int64_t m = m0 + i * 32 + l32;
+        pa[i] = g.A + (m < g.M ? m : g.M - 1) * g.sam + k_begin * g.sak;
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+        const int64_t n = n0 + j * 32 + l32;
+        pb[j] = g.B + (n < g.N ? n : g.N - 1) * g.sbn + k_begin * g.sbk;
+    }
+    const bool a_gated = A_GATED && g.a_gate, b_gated = B_GATED && g.b_gate;
+    const int64_t a_gate_off = a_gated ? g.a_gate - g.A : 0, b_gate_off = b_gated ? g.b_gate - g.B : 0;
+    const int64_t len = k_begin < k_end ? k_end - k_begin : 0, whole = FEW_K ? 0 : len / 8 * 8;
+    if (!FEW_K && whole > 0) {
+        Four<A_K_CONTIG, A_GATED> a[2][TI];
+        Four<B_K_CONTIG, B_GATED> b[2][TJ];
+        auto load = [&](int64_t k, int set) {  // behind the last step: that one again
+            const int64_t at = (k < whole ? k : whole - 8) + 4 * lk;
+#pragma unroll
+            for (int i = 0; i < TI; ++i) a[set][i].load(pa[i] + at * g.sak, g.sak, a_gated, a_gate_off);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) b[set][j].load(pb[j] + at * g.sbk, g.sbk, b_gated, b_gate_off);
+        };
+        auto multiply = [&](int set) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[set][i].at(q, a_gated), b[set][j].at(q, b_gated), acc[i][j], 0, 0, 0);
+        };
+        load(0, 0);
 #pragma unroll 1
-    for (int64_t k = k_begin; k < k_end; k += 2) {
-        // operand layout of the 32x32x2 instruction: lane l holds A[l % 32][l / 32] and B[l / 32][l % 32]
-        const bool in = k + lk < k_end;
+        for (int64_t k = 0; k < whole; k += 16) {
+            load(k + 8, 1);
+            if (TI > 1) __builtin_amdgcn_sched_barrier(0);  // all ahead of the products that hide them; one row tile has too many to issue at once
+            multiply(0);
+            if (k + 8 >= whole) break;
+            load(k + 16, 0);
+            if (TI > 1) __builtin_amdgcn_sched_barrier(0);
+            multiply(1);
+        }
+    }
+#pragma unroll 1
+    for (int64_t k = whole; k < len; k += 2) {
+        const bool in = k + lk < len;
+        const int64_t at = in ? k + lk : 0;
         float a[TI], b[TJ];
 #pragma unroll
         for (int i = 0; i < TI; ++i) {
-            const int64_t m = m0 + i * 32 + l32, at = m * g.sam + (k + lk) * g.sak;
-            a[i] = (in && m < g.M && !(g.a_gate && !(g.a_gate[at] > 0.0f))) ? g.A[at] : 0.0f;
+            const float *p = pa[i] + at * g.sak;
+            a[i] = in && (!a_gated || p[a_gate_off] > 0.0f) ? *p : 0.0f;
         }
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
-            const int64_t n = n0 + j * 32 + l32, at = n * g.sbn + (k + lk) * g.sbk;
-            b[j] = (in && n < g.N && !(g.b_gate && !(g.b_gate[at] > 0.0f))) ? g.B[at] : 0.0f;
+            const float *p = pb[j] + at * g.sbk;
+            b[j] = in && (!b_gated || p[b_gate_off] > 0.0f) ? *p : 0.0f;
         }
 #pragma unroll
         for (int i = 0; i < TI; ++i)
@@ -448,7 +524,7 @@ __global__ void __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_
         }
     }
 
-    recompute_if_needed<TI, TJ>(g, acc, m0 + wm, n0 + wn, k_begin, k_end);
+    recompute_if_needed<A_K_CONTIG, B_K_CONTIG, false, FOLD == 2, 0>(g, acc, m0 + wm, n0 + wn, k_begin, k_end);
 
     if constexpr (FOLD == 2) {
         if (sums) {
@@ -478,7 +554,7 @@ constexpr int kFewProducts = 2;
 // lanes that need them, two steps of 16 k ahead of their use, and are split there, once; only B passes through LDS.  FEW_K: 1 =
 // less than 16 k, one step of single elements; 2 = at most kFewProducts.
 template <int WAVES, int TJ, bool B_K_CONTIG, bool GATED, int FEW_K = 0>
-__global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(FEW_K == 2 ? 4 : TJ >= 4 ? 2 : TJ == 2 && GATED ? 3 : 4, FEW_K == 2 ? 5 : 8))) tall_kernel(const GemmArgs g) {
+__global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(FEW_K == 2 ? 4 : TJ >= 4 ? 2 : TJ == 2 && GATED ? 3 : 4, FEW_K == 2 || (FEW_K == 1 && !B_K_CONTIG) ? 5 : 8))) tall_kernel(const GemmArgs g) {
     constexpr int BM = WAVES * 32, BN = TJ * 32;
     __shared__ __attribute__((aligned(16))) SplitTile<BN> tiles[2];
     const int lane = threadIdx.x & 63;
@@ -575,7 +651,7 @@ __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu
             __syncthreads();
             step(0, 0);
         }
-        recompute_if_needed<1, TJ>(g, acc, m0, n0, 0, g.K, FEW_K == 2);
+        recompute_if_needed<true, B_K_CONTIG, GATED, false, FEW_K>(g, acc, m0, n0, 0, g.K);
         write_tiles<1, TJ>(g, acc, m0, n0, 0);
         return;
     }
@@ -592,7 +668,7 @@ __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu
         if (TJ == 8 && t + 1 == n_tiles) break;
         step(t + 1, 1);
     }
-    recompute_if_needed<1, TJ>(g, acc, m0, n0, 0, g.K);
+    recompute_if_needed<true, B_K_CONTIG, GATED, false, 0>(g, acc, m0, n0, 0, g.K);
     write_tiles<1, TJ>(g, acc, m0, n0, 0);
 }
 

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 # fp32 products are exact on the matrix cores but for 2^-24 of S; the accumulation of K terms in fp32 (in steps of
-# 16, partial planes of >= 64) and the fp32 aggregation before or after it leave an error of
+# 16, partial planes of >= GNN_SPLIT_MIN_K = 128 rows) and the fp32 aggregation before or after it leave an error of
 # at most (1e-5 + K * 2^-24) * S in the worst case and ~sqrt(K) * 2^-24 * S typically, S being the
 # sum of the absolute values of all terms; gate at 2e-5 * S.
 RTOL_LAYER = 2e-5
@@ -374,6 +374,49 @@ def test_layer_int64_row_pointers():
     _close(H, Ho, SH, "layer forward, int64 row pointers")
 
 
+@pytest.mark.parametrize("n,fi,fo", [(4000, 100, 256), (4000, 20, 24), (4000, 40, 47), (4000, 130, 133), (4000, 30, 9), (66_000, 130, 133),
+                                     (66_000, 100, 40), (66_000, 64, 64), (66_000, 20, 16)])
+@pytest.mark.parametrize("flags", [0, gnn.GNN_LAYER_FORCE_PRODUCER_LAYOUT, gnn.GNN_LAYER_NO_GATE_FOLD])
+def test_layer_backward_of_operands_outside_the_split(n, fi, fo, flags):
+    """The tiles that are computed again read the operands, their gates and the producer's layout in a way of their own: infinities and
+    NaNs on both sides of the gate, in the operand, in the weights and in the gate itself, and finite numbers beyond the split."""
+    el = synth.rmat_symmetric(n, 30 * n, (0.57, 0.19, 0.19, 0.05), 5) if n == 4000 else synth.erdos_renyi_directed(n, 3 * n, 5)
+    dg = device_graph(el, plan_params=gnn.make_plan_params([2, 8, 32, 128], 64))
+    indptr, indices, indptr_t, indices_t, _ = host_csr(el)
+    rng = np.random.default_rng(n + fi + fo)
+    X, saved, H, dH = (rng.normal(size=s_).astype(np.float32) for s_ in ((n, fi), (n, fi), (n, fo), (n, fo)))
+    W = (rng.normal(size=(fi, fo)) / np.sqrt(fo)).astype(np.float32)
+    inf, nan = float("inf"), float("nan")
+    for v, c, h, d in ((7, 0, -1, inf), (n - 1, fo - 1, 0, nan), (n // 2, 1, nan, 1), (n // 3, 2, 1, inf), (n // 3 + 1, 3, 1, -inf),
+                       (n - 2, 4, 2, 2.0 ** 113), (n // 4, 5, 1, nan), (n // 4 + 40, fo // 2, -2, -inf)):
+        H[v, c], dH[v, c] = h, d
+    dH[n // 5] *= 2.0 ** -118
+    saved[n // 6, fi // 2], saved[n - 3, 1], saved[n - 1, 2] = nan, -inf, 2.0 ** 113
+    W[fi // 3, fo // 3] = -inf
+    G = np.where(H > 0, dH, np.float32(0)).astype(np.float64)
+    with np.errstate(invalid="ignore", over="ignore"):
+        Z64, W64 = saved.astype(np.float64), W.astype(np.float64)
+        dW, SW, db, Sb = Z64.T @ G, np.abs(Z64).T @ np.abs(G), G.sum(0), np.abs(G).sum(0)
+        dZ = (G @ W64.T).astype(np.float32)
+        dZ_abs = (np.abs(G) @ np.abs(W64).T).astype(np.float32)
+    op = gnn.GNN_SAGE_GCN
+    dX = oracle.aggregate_bwd(indptr_t, indices_t, dZ, op=op, din=np.diff(indptr), nthreads=8)
+    SX = oracle.aggregate_bwd(indptr_t, indices_t, dZ_abs, op=op, din=np.diff(indptr), nthreads=8)
+    ws = torch.empty(gnn.gnn_sage_layer_workspace_bytes(n, fi, fo, True, 1) // 4 + n * fo + 64, device=DEV)
+    got = [torch.full(s_, nan, device=DEV) for s_ in ((n, fi), (fi, fo), (fo,))]
+    Xd, Wd, sd, Hd, dHd = (torch.from_numpy(a).to(DEV) for a in (X, W, saved, H, dH))
+    gnn.gnn_sage_layer_bwd(dg.indptr_t, dg.indices_t, Xd, Wd, sd, Hd, dHd, *got, dg.plan_bwd, ws, relu=True, order=1, flags=flags)
+    torch.cuda.synchronize()
+    for what, g, ref, S in zip(("dX", "dW", "db"), got, (dX, dW, db), (SX, SW, Sb)):
+        g, ref = g.cpu().numpy().astype(np.float64), np.asarray(ref, dtype=np.float64)
+        finite = np.isfinite(ref)
+        assert finite.any() and not finite.all(), what
+        assert np.array_equal(np.isnan(g), np.isnan(ref)), what
+        assert np.array_equal(g[np.isinf(ref)], ref[np.isinf(ref)]), what
+        err = np.abs(g[finite] - ref[finite])
+        assert (err <= RTOL_LAYER * np.asarray(S)[finite] + 2.0 ** -140).all(), (what, err.max())
+
+
 # ------------------------------------------------------------------ the split operands of the matrix cores
 @pytest.mark.parametrize("k", [1, 9, 15, 17, 32, 47])
 @pytest.mark.parametrize("m,n", [(31, 33), (300, 65), (513, 257)])
@@ -393,9 +436,10 @@ def test_matmul_edges_of_the_steps_of_k(m, n, k, ta, tb):
     _close(C, A64 @ B64, np.abs(A64) @ np.abs(B64), f"m={m} n={n} k={k} ta={ta} tb={tb}", rtol=1e-6)
 
 
+@pytest.mark.parametrize("tb", [False, True])
 @pytest.mark.parametrize("m,n,k,ta", [(70_000, 200, 40, False), (60_000, 47, 33, False), (66_000, 16, 50, False), (200, 140, 30_011, True),
                                       (130, 60, 2_000, True), (100, 20, 5_003, True), (100, 100, 3_000, True), (64, 64, 2_048, False)])
-def test_matmul_of_operands_outside_the_split(m, n, k, ta):
+def test_matmul_of_operands_outside_the_split(m, n, k, ta, tb):
     """Infinities, NaNs and values from 2^112 on have no exact three parts: the tiles they take part in are computed from the operands
     as they are."""
     gen = torch.Generator(device=DEV)
@@ -411,7 +455,7 @@ def test_matmul_of_operands_outside_the_split(m, n, k, ta):
     need = gnn.gnn_matmul_workspace_bytes(m, n, k)
     ws = torch.empty(max(need // 4, 4), device=DEV)
     C = torch.empty(m, n, device=DEV)
-    gnn.gnn_matmul(A, B, C, trans_a=ta, workspace=ws)
+    gnn.gnn_matmul(A, B.t().contiguous() if tb else B, C, trans_a=ta, trans_b=tb, workspace=ws)
     torch.cuda.synchronize()
     a64, b64 = rows.double(), B.double()
     ref = torch.cat([a64[i:i + 4096].contiguous() @ b64 for i in range(0, m, 4096)])

@@ -956,14 +956,21 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     if (dots) {
         using std::integral_constant;
         a.col_end = int32_t(d);
-        // Rows in ascending order of their sources, as a sorted graph has them (others lose nothing but time): their k-th eighths
-        // lead to an eighth of the gathered matrix, which an L2 holds where the whole is too large for it.  Pays for long rows
-        // of two lines and more (132,534 vertices, 596 edges each, mild skew: d = 128 4.23 -> 2.51 ms, 64 1.60 -> 1.29, 37 1.56 ->
-        // 1.34; strong skew 1.26 -> 1.25) and costs where a row has few steps or a line (32 columns 0.67 -> 0.73 ms, 300 edges
-        // each 1.02 -> 1.04, 96 edges each 1.07 -> 1.40).
-        const int64_t matrix_bytes = N * c.ldv * 4;
-        a.source_split = plan && plan->n_edges >= 400 * N && d > 32 && matrix_bytes >= (int64_t(18) << 20) && matrix_bytes <= (int64_t(72) << 20) &&
-                         blocks <= INT32_MAX / 8 ? 1 : 0;
+        // The k-th eighths of rows in ascending order of their sources lead to about an eighth of the gathered matrix each, so that
+        // an XCD reads fewer different lines through its L2 (4 MB; the eighth need not fit, the more of it does the better).  ms,
+        // off -> on, 600 edges a vertex unless said:
+        //   132,534 vertices, mild skew     64 columns 1.61 -> 1.19, 96 2.71 -> 1.78, 128 4.10 -> 2.50; strong skew 1.27 -> 1.18,
+        //                                   2.14 -> 1.76, 3.33 -> 2.51
+        //   66,000, mild / strong skew      96 columns 1.03 -> 0.74 / 0.79 -> 0.69, 128 1.59 -> 0.99 / 1.17 -> 0.92
+        //   250,000, 500 edges a vertex     33 columns 2.95 -> 2.14 / 2.22 -> 2.00, 64 3.34 -> 2.22 / 2.25 -> 2.05
+        // Below the range the matrix is mostly in the L2s anyway: 66,000 vertices, 33 columns 0.50 -> 0.51 / 0.45 -> 0.47, 64 0.55 ->
+        // 0.50 / 0.47 -> 0.47; 40,000, 64 columns 0.27 -> 0.29.  Rows of one line have too few steps (32 columns of 132,534
+        // 0.67 -> 0.73), and so have short rows (96 edges a vertex 1.07 -> 1.40).  The upper end and 400 edges are as far as it is taken,
+        // not where it ends: 250,000 vertices, 128 columns 7.57 -> 5.11 / 5.38 -> 4.19, 300 edges a vertex 0.80 -> 0.59.
+        // Rows in no order gain nothing and have their steps cut: 132,534 vertices, 64 columns 1.75 -> 1.91, 128 4.40 -> 4.82.
+        const int64_t bytes = N * d * 4;
+        a.source_split = plan && gnn_long_rows(plan->n_edges, N) && !plan->rows_unordered && d > 32 && bytes >= (int64_t(18) << 20) &&
+                         bytes <= (int64_t(72) << 20) && blocks <= INT32_MAX / 8 ? 1 : 0;
         if (a.source_split) grid.x *= 8;
         auto launch = [&](auto lc, auto s) {
             constexpr int LC = decltype(lc)::value, S = decltype(s)::value;

@@ -63,6 +63,7 @@ struct gnn_plan {
     // that wait for each other.  E <= INT32_MAX, else nullptr; row_perm lies behind it in the same block.
     int4 *row_info = nullptr;
     int32_t *col_counts = nullptr;    // [n_rows] occurrences of each vertex in indices
+    bool rows_unordered = false;      // of a graph of long rows (gnn_long_rows): the sources of its rows are in no order
     // hub rows = rows of the last bin when params.hub_chunk > 0
     int64_t n_hub_rows = 0;
     int64_t n_chunks = 0;
@@ -461,8 +462,10 @@ int gnn_plan_rank_indices(gnn_plan *plan, const void *indptr, const int32_t *ind
 int gnn_read_edge_count(const void *indptr, int64_t N, int indptr_is_64, hipStream_t stream, int64_t *E);
 // rank[v] = position of vertex v by descending count, ties by ascending id; no count exceeds max_count (graph.hip).
 int gnn_rank_by_count(const int32_t *counts, int64_t N, int64_t max_count, int32_t *rank, hipStream_t stream);
+// Graphs whose edge dot products may be split over the XCDs (gnn_ap_bwd_edge); their plans look at the order of the sources.
+static inline bool gnn_long_rows(int64_t E, int64_t N) { return E >= 400 * N; }
 // The plans of a graph and of its transpose, E edges each; the host fields are valid on return.
-int gnn_plan_create_pair(const void *indptr, const void *indptr_t, int64_t E, int64_t N, int indptr_is_64,
+int gnn_plan_create_pair(const void *indptr, const void *indptr_t, const int32_t *indices, int64_t E, int64_t N, int indptr_is_64,
                          const gnn_plan_params *params, hipStream_t stream, gnn_plan **fwd, gnn_plan **bwd);
 
 // mode: 1 = reciprocal, 2 = reciprocal square root, 3 = reciprocal of (count + 1).

@@ -466,7 +466,7 @@ extern "C" GNN_API int gnn_graph_build(const int32_t *dst_sorted, const int32_t 
     else
         rc = transpose(dst_sorted, indptr, src, edge_w, E, N, indptr_is_64, indptr_t, indices_t, perm, edge_w_t, stream);
     if (rc == GNN_OK && plan_fwd)
-        rc = gnn_plan_create_pair(indptr, indptr_t, E, N, indptr_is_64, params, stream, plan_fwd, plan_bwd);
+        rc = gnn_plan_create_pair(indptr, indptr_t, src, E, N, indptr_is_64, params, stream, plan_fwd, plan_bwd);
     if (hipStreamSynchronize(stream) != hipSuccess && rc == GNN_OK) rc = GNN_ERR_LAUNCH;
     return rc;
 }

@@ -50,6 +50,7 @@ struct RowTotals {
     unsigned long long bin_edges[GNN_MAX_BINS];                  // edges of the rows of each bin
     unsigned long long n_chunks;                                 // pieces of the hub rows
     long long bin_begin[GNN_MAX_BINS];                           // first row of each bin
+    int unordered;                                               // of kSplitThreads rows: sources in descending order (plan_order_kernel)
 };
 static_assert(sizeof(RowTotals) <= size_t(GNN_HOST_BLOCK_BYTES), "fits a host block");
 
@@ -72,6 +73,18 @@ struct PlanJobs {
     int32_t ip64, nb;
     Thresholds thr;
 };
+
+// Whether the rows list their sources in ascending order, as a sorted graph has them: two edges of each of kSplitThreads rows, a
+// third and two thirds into the row, compared.  One workgroup; the result goes to the host.
+__global__ void __launch_bounds__(kSplitThreads) plan_order_kernel(const void *indptr, int ip64, const int32_t *__restrict__ indices,
+                                                                   int64_t N, int64_t E, RowTotals *host) {
+    const int64_t v = int64_t(threadIdx.x) * N / kSplitThreads;
+    const int64_t e0 = load_ip(indptr, ip64, v), len = load_ip(indptr, ip64, v + 1) - e0;
+    bool descending = false;
+    if (e0 >= 0 && len > 1 && e0 + len <= E) descending = indices[e0 + len / 3] > indices[e0 + len * 2 / 3];
+    const int n = __syncthreads_count(descending);
+    if (threadIdx.x == 0) host->unordered = n;
+}
 
 // Per 1024 rows: block_counts[b * n_blocks + blk] = rows of bin b among them; and the totals over all rows, integer sums, so
 // that the order of the additions does not matter.
@@ -656,7 +669,7 @@ gnn_plan *new_plan(const void *indptr, int64_t N, int64_t E, int indptr_is_64, c
 
 // Fills one plan, or the two of a graph and its transpose (whose column counts are each other's row lengths) with the same
 // launches.  Everything is launched before the host waits, once: the arrays whose size depends on the graph are allocated
-// for the most that E edges can need.
+// for the most that E edges can need.  indices: of the first; those of a transposed graph are in ascending order.
 int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, const int32_t *indices, hipStream_t stream) {
     const int64_t N = plans[0]->n_rows, E = plans[0]->n_edges;
     const gnn_plan_params &prm = plans[0]->params;
@@ -734,9 +747,12 @@ int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, 
             if ((rc = gnn_scan_exclusive_i64(plans[i]->hub_chunk_offsets, hub_bound, 1, 0, sums, stream)) != GNN_OK) return rc;
         hub_fill_kernel<<<grid, 256, 0, stream>>>(jobs, hub_bound, chunk_bound);
     }
+    const bool look_at_order = E > 0 && gnn_long_rows(E, N);
+    if (look_at_order) plan_order_kernel<<<1, kSplitThreads, 0, stream>>>(indptrs[0], jobs.ip64, indices, N, E, jobs.job[0].host);
     GNN_HIP_TRY(hipGetLastError());
     GNN_HIP_TRY(hipStreamSynchronize(stream));
     host.in_use = false;
+    plans[0]->rows_unordered = look_at_order && jobs.job[0].host->unordered > kSplitThreads / 8;  // half of them where there is no order
     for (int i = 0; i < n_plans; ++i) {
         gnn_plan *p = plans[i];
         const RowTotals &r = *jobs.job[i].host;
@@ -787,7 +803,7 @@ extern "C" GNN_API int gnn_plan_create(const void *indptr, const int32_t *indice
     return GNN_OK;
 }
 
-int gnn_plan_create_pair(const void *indptr, const void *indptr_t, int64_t E, int64_t N, int indptr_is_64,
+int gnn_plan_create_pair(const void *indptr, const void *indptr_t, const int32_t *indices, int64_t E, int64_t N, int indptr_is_64,
                          const gnn_plan_params *params, hipStream_t stream, gnn_plan **fwd, gnn_plan **bwd) {
     gnn_plan_params prm;
     int rc = check_params(params, &prm);
@@ -795,7 +811,7 @@ int gnn_plan_create_pair(const void *indptr, const void *indptr_t, int64_t E, in
     const void *indptrs[2] = {indptr, indptr_t};
     gnn_plan *plans[2] = {new_plan(indptr, N, E, indptr_is_64, prm), new_plan(indptr_t, N, E, indptr_is_64, prm)};
     if (!plans[0] || !plans[1]) rc = GNN_ERR_ALLOC;
-    if (rc == GNN_OK && N > 0) rc = fill_plans(plans, 2, indptrs, nullptr, stream);
+    if (rc == GNN_OK && N > 0) rc = fill_plans(plans, 2, indptrs, indices, stream);
     if (rc != GNN_OK) {
         (void)hipStreamSynchronize(stream);
         gnn_plan_destroy(plans[0]);

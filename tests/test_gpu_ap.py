@@ -427,27 +427,32 @@ def test_sorted_winner_scatter(d, binop):
     assert bool((dfV[:, d:] == 7.0).all())
 
 
-@pytest.mark.parametrize("d,hubs", [(33, False), (64, True), (128, False)])
-def test_edge_dots_of_long_rows_are_split_over_the_xcds(d, hubs):
-    """400 edges per vertex and a gathered matrix of 18 MB (reached by its stride): every row's edges are dealt to eight
-    workgroups.  Rows of every length from 0 on, long ones cut into pieces by the second plan."""
+@pytest.mark.parametrize("d,hubs,ordered,wide", [(33, False, True, False), (64, True, True, False), (128, False, True, False),
+                                                 (100, True, True, True), (128, False, False, False), (128, True, True, None)])
+def test_edge_dots_of_long_rows_are_split_over_the_xcds(d, hubs, ordered, wide):
+    """400 edges per vertex and a gathered matrix of 18 MB: every row's edges are dealt to eight workgroups.  Rows of every length
+    from 0 on, long ones cut into pieces by some plans; columns of a wider matrix (wide); rows whose sources are in no order,
+    and (wide is None) a matrix that is smaller than its row stride says: both are left whole."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(d)
-    n = 5000
+    n = 5000 if wide is None else -(-(18 << 20) // (4 * d))
     lens = torch.randint(0, 900, (n,), generator=gen, device=DEV)
     lens[:70] = torch.arange(70, device=DEV)
     lens[100] = 60_000
     dst = torch.repeat_interleave(torch.arange(n, device=DEV), lens)
     src = torch.randint(0, n, (dst.numel(),), generator=gen, device=DEV)
-    order = torch.argsort(dst * n + src, stable=True)
-    dst, src = dst[order].int(), src[order].int()
+    if ordered:
+        src = (dst * n + src).sort().values % n
+    dst, src = dst.int(), src.int()
     e = dst.numel()
     assert e >= 400 * n
     g = gnn.build_device_graph(dst, src, n, plan_params=gnn.make_plan_params([2, 8, 32, 128, 512], 100) if hubs else None)
-    big = torch.empty(n, 1000, device=DEV).normal_(generator=gen)
+    big = torch.empty(n, d if wide is False else 1000, device=DEV).normal_(generator=gen)
     v, do = big[:, :d], torch.empty(n, d, device=DEV).normal_(generator=gen)
     fe = torch.rand(e, device=DEV, generator=gen)
     out = torch.full((e,), float("nan"), device=DEV)
     gnn.gnn_ap_bwd_edge(g.indptr, g.indices, None, v, fe, do, out, n, d, gnn.GNN_BIN_MUL, plan=g.plan_fwd)
-    terms = v.double()[src.long()] * do.double()[dst.long()]
-    assert bool(((out.double() - terms.sum(1)).abs() <= 1e-5 * terms.abs().sum(1)).all())
+    for at in range(0, e, 1 << 24):
+        part = slice(at, at + (1 << 24))
+        terms = v.double()[src[part].long()] * do.double()[dst[part].long()]
+        assert bool(((out[part].double() - terms.sum(1)).abs() <= 1e-5 * terms.abs().sum(1)).all())

@@ -319,7 +319,8 @@ GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indices, const in
  * matrices f x h1, h1 x h2, h2 x l), on the matrix cores: every operand, of any magnitude, as three bf16
  * numbers whose sum (times a power of two) it is, six of their nine products, fp32 sums (closer to the exact
  * result than a chain of fp32 multiply-adds; where operands of 2^112 and more, infinities or NaNs take part, or
- * sums of products reach 2^96, fp32 instructions form the results):
+ * sums of products reach 2^96, fp32 instructions form the results, and a call of which all results are such
+ * takes up to three times as long):
  *     C[m, n] = act( sum_k opA(A)[m, k] * opB(B)[k, n] + bias[n] ),   act = max(., 0) if relu
  * A is stored [M, K] with row stride lda, or [K, M] when trans_a; B is stored [K, N] with row
  * stride ldb, or [N, K] when trans_b; C [M, ldc] is overwritten; bias [N] or NULL.  All device

@@ -1384,10 +1384,11 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     int64_t plain_hub_col_begin = F;  // ... from this column on
 
     // The short rows of the blocked launches run on a second stream beside the tiles and pieces: they write other rows and
-    // read the same tables.  It paid when pieces and short rows were bound by different things (2.45 M vertices F=100 5.57 -> 5.32
-    // ms); since the tiles took the gathers that hit in the L2s, one after the other, side by side, and the short rows behind the
-    // tiles measure the same within 1 % on every large graph tried (2.45 M vertices F=100 + 256 23.2 and 23.1 ms, 233 K vertices
-    // 19.0 and 19.0).
+    // read the same tables.  It paid everywhere when pieces and short rows were bound by different things (2.45 M vertices F=100
+    // 5.57 -> 5.32 ms); since the tiles took the gathers that hit in the L2s it gains and loses a little.  MEAN forward, ms, on one
+    // stream (GNN_FLAG_NO_SHORT_ROW_OVERLAP) -> two: 505 K vertices, 14 M edges F=100 0.566 -> 0.554, 256 1.039 -> 1.000; 2.45 M F=47
+    // 2.09 -> 2.11, 100 3.87 -> 3.82, 256 7.47 -> 7.51; 233 K F=64 0.721 -> 0.699, 256 2.60 -> 2.65, 602 6.64 -> 6.93; 133 K, 600 K
+    // and 1 M vertices, and bf16 on all of them, within 1 %.
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     if (bl.active && !(o.flags & GNN_FLAG_NO_SHORT_ROW_OVERLAP)) {

@@ -772,8 +772,11 @@ static TileShape choose_tile(int64_t M, int64_t N) {
 
 // Tile of a tall product: wavefronts of 32 rows, tiles of 32 columns.  As wide as the result, so that A is read and split once
 // (2.45 M rows, 256 -> 47: 0.70 ms with two column tiles, 0.98 with one; 256 -> 256 2.0 with eight, 2.2 with four, 2.4 with
-// two), unless that leaves compute units without a workgroup: 24,490 rows 256 -> 256 take 46 us with tiles of 256 x 256 and
-// 31 with 128 x 64, 60,000 rows 128 -> 256 take 36 and 40.
+// two), unless that leaves compute units without a workgroup.  256 -> 256, us with tiles of 256 x 256 (one to a compute unit) and
+// 128 x 64: 24,490 rows 44 and 28, 40,000 44 and 47, 49,152 (192 tiles, where the line is) 46 and 54, 100,000 93 and 105.
+// 100 -> 128 with tiles of 128 x 128 and 128 x 64: 40,000 rows 17 and 15, 60,000 18 and 20, 65,536 (512 tiles, two to a compute unit)
+// 19 and 20, 300,000 80 and 90.  Eight wavefronts instead of four share the split of B: nothing up to 65,536 rows, where the line
+// is (602 -> 16, 20,000 rows 33 and 31 us), 1 to 4 % from there on (256 -> 47, 130,000 rows 35 and 37, 2.45 M 753 and 771).
 struct TallShape { int waves, tj; };
 
 static TallShape choose_tall(int64_t M, int64_t N) {
@@ -785,7 +788,8 @@ static TallShape choose_tall(int64_t M, int64_t N) {
     return {8, 8};
 }
 
-// How many partial planes the reduction over k is split into.
+// How many partial planes the reduction over k is split into.  Of the sizes alone, with the tiles of a weight gradient: a caller that
+// asks for the workspace does not say which way A lies (launch_rows has tiles of its own).
 static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
     const TileShape s = choose_tile(M, N);
     const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);

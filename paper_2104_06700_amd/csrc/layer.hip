@@ -38,10 +38,12 @@ hipStream_t side_stream() {
 
 // G = dH where H > 0 (else 0; plain copy without a rectifier) for a block of rows, written with row
 // stride ldg when G != nullptr, plus the block's column sums.  A thread owns one column and every
-// (256 / cols)-th row of the block; the row lanes are added through LDS in a fixed order, so the
+// (THREADS / cols)-th row of the block; the row lanes are added through LDS in a fixed order, so the
 // sums are reproducible.  cols = power of two >= F, at most 256 (wider F: several column passes).
 // pk.active: G goes into a producer-side layout (the tables the backward aggregation gathers from) instead.
-// THREADS: 1024 where there are few blocks, which take as long as a thread has rows to walk.
+// THREADS: 1024 where there are few blocks, which take as long as a thread has rows to walk.  The whole backward call, transform
+// first, us with 256 -> 1024: 2,000 rows 256 -> 256 73 -> 55, 24,490 128 -> 118, 32,000 (the line: 512 blocks) 156 -> 138, 128,000 462 ->
+// 457; 100 -> 47 37 -> 35, 52.4 -> 51.7, 53.3 -> 52.9 and, with more blocks, 48,000 rows 62.7 -> 65.3, 128,000 109 -> 120.
 template <int THREADS>
 __global__ void __launch_bounds__(THREADS) mask_colsum_kernel(const float *__restrict__ H, const float *__restrict__ dH,
                                                           float *__restrict__ G, int64_t ldg, float *__restrict__ partial,

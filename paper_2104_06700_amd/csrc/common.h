@@ -46,6 +46,7 @@ struct gnn_tiles {
     int64_t bound_version = -1;
     float *tmp_w = nullptr;              // other coefficients, refilled by every call
     uint32_t *positions = nullptr;       // CSR position of the edge in every slot of the stream; made for coefficients that are refilled
+    bool no_positions = false;           // there was no room for them
 };
 
 // One plan = one graph orientation.  All pointers are device memory owned by

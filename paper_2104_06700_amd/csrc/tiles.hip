@@ -904,14 +904,20 @@ hipError_t fill(const gnn_plan *plan, const gnn_tiles &L, const float *w, const 
 
 // The edge of every slot, for coefficients that are filled in again and again, because working out the order of the slots takes
 // longer than reading the weights (233 K vertices, F=64: weights of every call's own 3.7 -> 1.9 ms a call, bound anew before
-// each call, for two widths 11.2 -> 3.1).  4 bytes a slot, as much as the coefficients.  Without room for it (and under
-// capture) they are filled in as the first time.
+// each call, for two widths 11.2 -> 3.1).  4 bytes a slot, as much as the coefficients.  Under capture, and where there is no
+// room for it (asked for once: the driver waits for the device to find out), they are filled in as the first time.
 void want_positions(const gnn_plan *plan, gnn_tiles &L, hipStream_t stream) {
-    if (L.positions) return;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (L.positions || L.no_positions) return;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
     (void)hipGetLastError();
     if (!gnn_dev_alloc(&L.positions, stream_slots(L), stream)) {
         (void)hipGetLastError();
         L.positions = nullptr;
+        L.no_positions = true;
     } else if (fill(plan, L, nullptr, nullptr, nullptr, L.positions, stream) != hipSuccess) {
         gnn_dev_free(L.positions);
         L.positions = nullptr;

@@ -8,7 +8,7 @@
 // are 2.7 times as fast, and the products meet the memory instead of the matrix cores (256 -> 256 excepted).
 // Relative error against 64 bits, 2-norm, normal operands, before (fp32 instruction, one chain) -> now: 4096 x 256 with
 // k = 256 2.9e-7 -> 0.8e-7, k = 602 4.4e-7 -> 1.2e-7, a weight gradient of 60,000 rows 3.2e-7 -> 1.8e-7, of 2.45 M rows
-// 1.2e-6 -> 0.5e-6; positive operands are closer for every k too (k = 3 3.3e-8 -> 2.7e-8, 32 8.6e-8 -> 3.6e-8).  Operands spread evenly over
+// 1.2e-6 -> 0.5e-6; positive operands are closer for every k too (k = 3 3.3e-8 -> 3.0e-8, 32 8.6e-8 -> 3.6e-8).  Operands spread evenly over
 // 40 binary orders of magnitude, where a sum is one or two products, are closer from k = 32 on (5.2e-8 -> 4.9e-8) and a third of a
 // rounding further off below (k = 3 2.8e-8 -> 3.7e-8, 8 3.3e-8 -> 4.1e-8, 16 4.0e-8 -> 4.3e-8): see sum_of_products for what is cut off.
 //

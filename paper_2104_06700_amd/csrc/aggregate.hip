@@ -325,6 +325,30 @@ __device__ __forceinline__ float own_row_value(const OwnRowSrc &o, int64_t row, 
     return xs[0];
 }
 
+// Epilogue of a row's strip: own vector (in `own` where self_mode asks for it), scale, bias, rectifier, store.
+template <typename T, int VEC>
+__device__ __forceinline__ void write_strip(const AggArgs &a, int64_t row, int64_t row_len, int col, int ncols, const float (&own)[VEC], float (&acc)[VEC]) {
+    const float ds = scale_of(a.dst_mode, row_len);
+    if (a.self_mode != kSelfNone) {  // Section 6.1: the vertex's own vector joins the sum
+        const float self_cf = a.self_mode == kSelfInvPlus1 ? scale_of(kScaleInvPlus1, a.col_counts[row]) : 1.0f;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(self_cf, own[i], acc[i]);
+    }
+    float o[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) o[i] = acc[i] * ds;
+    if (a.bias) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i)
+            if (i < ncols) o[i] += a.bias[col + i];
+    }
+    if (a.relu) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) o[i] = o[i] > 0.0f ? o[i] : 0.0f;
+    }
+    store_strip<T, VEC>(static_cast<T *>(a.Y) + row * a.ldy + col, o, ncols, a.store_vec);
+}
+
 // ---------------------------------------------------------------- main kernel
 // T: storage type of X and Y.  VEC: elements per lane per load.  NPASS: feature
 // passes (a lane owns NPASS strips of VEC columns, C*VEC apart).  COEF: edges
@@ -572,33 +596,164 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
             if (col_ok[p]) store_f32<VEC>(partial_out + col[p], acc[p]);
         return;
     }
-    const float ds = scale_of(a.dst_mode, row_len);
     const int64_t self_row = (a.self_mode != kSelfNone && a.row_map) ? int64_t(a.row_map[row]) : row;
-    const float self_cf = a.self_mode == kSelfInvPlus1 ? scale_of(kScaleInvPlus1, a.col_counts[row]) : 1.0f;
-    T *__restrict__ y = static_cast<T *>(a.Y) + row * a.ldy;
 #pragma unroll
     for (int p = 0; p < NPASS; ++p) {
         if (!col_ok[p]) continue;
-        if (a.self_mode != kSelfNone) {  // Section 6.1: the vertex's own vector joins the sum
-            float xs[VEC];
-            VecIO<T, VEC>::load(a.own_X ? static_cast<const T *>(a.own_X) + row * a.own_ld + col[p] : X + self_row * ldx + lcol[p], xs);
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) acc[p][i] = fmaf(self_cf, xs[i], acc[p][i]);
-        }
-        float o[VEC];
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) o[i] = acc[p][i] * ds;
-        if (a.bias) {
-#pragma unroll
-            for (int i = 0; i < VEC; ++i)
-                if (i < ncols[p]) o[i] += a.bias[col[p] + i];
-        }
-        if (a.relu) {
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) o[i] = o[i] > 0.0f ? o[i] : 0.0f;
-        }
-        store_strip<T, VEC>(y + col[p], o, ncols[p], a.store_vec);
+        float own[VEC];
+        if (a.self_mode != kSelfNone)
+            VecIO<T, VEC>::load(a.own_X ? static_cast<const T *>(a.own_X) + row * a.own_ld + col[p] : X + self_row * ldx + lcol[p], own);
+        write_strip<T, VEC>(a, row, row_len, col[p], ncols[p], own, acc[p]);
     }
+}
+
+constexpr int kRunEdges = 8;        // edges of a row of run_kernel at most
+constexpr int kRunBins = 8;         // bins of a launch at most
+constexpr int64_t kRunRows = 1 << 18, kRunWaves = 1 << 14;  // see run_bins_of, fill_run_bins
+
+struct RunBin {
+    int64_t first_block, item_begin, n_items;
+    int32_t longest;        // edges of a row of the bin at most
+    int32_t rows_per_wave;  // 64 at most
+};
+struct RunArgs {
+    AggArgs a;              // X: first slice table, or the matrix of whole rows; F: all columns
+    int64_t n_blocks;
+    int32_t n_bins;
+    int32_t log2_c;         // lanes per row
+    RunBin bins[kRunBins];
+};
+
+// Rows of at most kRunEdges edges, all columns.  A wavefront takes up to 64 of them: lane l reads what describes row l, then sets of
+// 64 / C rows follow each other, C lanes per row, the indices of the next set on their way while this one is gathered.
+//
+// As rows of aggregate_kernel they were bound by the rate at which workgroups start (570 per us over the chip: 32 rows of one line
+// each, 16 of two, gone after a few loads that wait for each other) and, off line boundaries, by partial lines of the output that
+// the slices write from different XCDs.  Half of the 2.45 M rows of a power-law graph have less than four edges: F=256, rows without
+// edges 387 -> 186 us (4.8 TB/s written), of one to seven 600 -> 550, the call 7.44 -> 7.13 ms; F=100 3.85 -> 3.62; 27.8 M vertices,
+// bf16 F=128, 16.4 -> 14.8.  Whole rows, because writing counts for more here than what slices keep in an L2 (in slices F=100 3.95 ms,
+// 256 7.20).  Up to 15 edges the slices win again: such rows are bound by what they gather.
+template <typename T, int VEC, bool COEF>
+__global__ void __launch_bounds__(kBlockThreads) run_kernel(const RunArgs r) {
+    constexpr int LINE = 128 / int(sizeof(T));
+    const AggArgs &a = r.a;
+    const int lane = threadIdx.x & 63;
+    int b = 0;
+#pragma unroll
+    for (int i = 1; i < kRunBins; ++i) b = i < r.n_bins && int64_t(blockIdx.x) >= r.bins[i].first_block ? i : b;
+    const RunBin bin = r.bins[b];
+    const int64_t item0 = ((int64_t(blockIdx.x) - bin.first_block) * kWavesPerBlock + (threadIdx.x >> 6)) * bin.rows_per_wave;
+    const int n_rows = bin.n_items - item0 < bin.rows_per_wave ? int(bin.n_items - item0) : bin.rows_per_wave;
+    if (n_rows <= 0) return;
+    const int log2_c = r.log2_c, C = 1 << log2_c;
+    const int c = lane & (C - 1), gbase = lane & ~(C - 1);
+    const int per_set = 64 >> log2_c, in_set = lane >> log2_c;
+
+    int my_row = -1, my_len = 0, my_own = 0;
+    int64_t my_e0 = 0, my_wdelta = 0;
+    if (lane < n_rows) {
+        const int64_t at = bin.item_begin + item0 + lane;
+        int64_t begin;
+        if (a.row_info) {
+            const int4 info = a.row_info[at];
+            my_row = info.x;
+            begin = uint32_t(info.y);
+            my_len = info.z;
+        } else {
+            my_row = a.row_perm[at];
+            begin = load_ip(a.indptr, a.ip64, my_row);
+            my_len = int(load_ip(a.indptr, a.ip64, int64_t(my_row) + 1) - begin);
+        }
+        my_e0 = a.p_indptr ? a.p_indptr[at] : begin;
+        if (COEF) my_wdelta = begin - my_e0;
+        if (a.self_mode != kSelfNone) my_own = a.row_map && !a.own_X ? a.row_map[my_row] : my_row;
+    }
+    auto of_row = [&](int64_t v, int src) {
+        return int64_t((uint64_t(uint32_t(__shfl(int(uint64_t(v) >> 32), src))) << 32) | uint32_t(__shfl(int(uint32_t(v)), src)));
+    };
+    auto run = [&](auto edges) {
+        constexpr int E = decltype(edges)::value;  // edges of a row at most
+        for (int strip0 = 0; strip0 * VEC < a.F; strip0 += C) {
+            int col = (strip0 + c) * VEC;
+            const bool col_ok = col < a.F;
+            if (a.overlap && col > a.F - VEC) col = a.F - VEC;
+            const int ncols = a.F - col < VEC ? a.F - col : VEC;
+            // this lane's columns in the table that has them
+            const T *X = static_cast<const T *>(a.X) + col;
+            int64_t ldx = a.ldx;
+            if (a.slice_stride > 0) {
+                X = static_cast<const T *>(a.X) + int64_t(col / LINE) * a.slice_stride + col % LINE;
+                ldx = LINE;
+            }
+            if (a.tail_slice >= 0 && col >= a.tail_slice * LINE) {
+                X = static_cast<const T *>(a.X_tail) + (col - a.tail_slice * LINE);
+                ldx = a.ld_tail;
+            }
+            auto fetch = [&](int src, int &u, float &cf) {
+                const int len = __shfl(my_len, src);
+                const int64_t first = of_row(my_e0, src);
+                int64_t first_w = 0;
+                if (COEF) first_w = first + of_row(my_wdelta, src);
+                u = 0;
+                cf = 0.0f;
+                if (c < len) {
+                    u = a.indices[first + c];
+                    if (COEF) {
+                        cf = a.w ? a.w[first_w + c] : 1.0f;
+                        if (a.edge_scale) cf *= a.edge_scale[first_w + c];
+                    }
+                }
+            };
+            int nxt_u = 0;
+            float nxt_cf = 0.0f;
+            if (E > 0) fetch(in_set, nxt_u, nxt_cf);
+            for (int set = 0; set < n_rows; set += per_set) {
+                const int src = set + in_set;
+                const int row = __shfl(my_row, src), len = E > 0 ? __shfl(my_len, src) : 0;
+                const int cur_u = nxt_u;
+                const float cur_cf = nxt_cf;
+                if (E > 0) fetch((src + per_set) & 63, nxt_u, nxt_cf);  // behind the last set: the first one again
+                float own[VEC];
+                if (a.self_mode != kSelfNone) {
+                    const int64_t own_row = __shfl(my_own, src);
+                    if (row >= 0 && col_ok) VecIO<T, VEC>::load(a.own_X ? static_cast<const T *>(a.own_X) + own_row * a.own_ld + col : X + own_row * ldx, own);
+                }
+                typename Strip<T, VEC>::raw_t x[E > 0 ? E : 1];
+                float cf[E > 0 ? E : 1];
+#pragma unroll
+                for (int k = 0; k < E; ++k) {
+                    const int u = __shfl(cur_u, gbase + k);
+                    if (COEF) cf[k] = __shfl(cur_cf, gbase + k);
+                    const int32_t src_row = u & 0x7FFFFFFF;
+                    const T *xr = X + int64_t(src_row) * ldx;
+                    if (k < len && col_ok) {
+                        if (a.cold_on && (u < 0 || src_row >= a.warm_rank)) x[k] = Strip<T, VEC>::load_nt(xr);
+                        else x[k] = Strip<T, VEC>::load(xr);
+                    } else {
+                        x[k] = Strip<T, VEC>::zero();
+                    }
+                }
+                float sum[VEC];
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) sum[i] = 0.0f;
+#pragma unroll
+                for (int k = 0; k < E; ++k) {
+                    float xv[VEC];
+                    Strip<T, VEC>::unpack(x[k], xv);
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) {
+                        if (COEF) sum[i] = fmaf(k < len ? cf[k] : 0.0f, xv[i], sum[i]);
+                        else sum[i] += xv[i];
+                    }
+                }
+                if (row >= 0 && col_ok) write_strip<T, VEC>(a, row, len, col, ncols, own, sum);
+            }
+        }
+    };
+    if (bin.longest <= 0) run(std::integral_constant<int, 0>());
+    else if (bin.longest <= 1) run(std::integral_constant<int, 1>());
+    else if (bin.longest <= 4) run(std::integral_constant<int, 4>());
+    else run(std::integral_constant<int, kRunEdges>());
 }
 
 // Adds the pieces of each hub row in their fixed order and writes the row.
@@ -989,6 +1144,51 @@ hipError_t launch_npass(int npass, dim3 grid, hipStream_t stream, const AggArgs 
 template <typename T, int VEC>
 hipError_t launch_coef(bool coef, int npass, dim3 grid, hipStream_t stream, const AggArgs &a) {
     return coef ? launch_npass<T, VEC, true>(npass, grid, stream, a) : launch_npass<T, VEC, false>(npass, grid, stream, a);
+}
+
+hipError_t launch_runs(bool coef, bool bf16, hipStream_t stream, const RunArgs &r) {
+    const dim3 grid(static_cast<unsigned>(r.n_blocks));
+    if (bf16 && coef) run_kernel<bf16_t, 8, true><<<grid, kBlockThreads, 0, stream>>>(r);
+    else if (bf16) run_kernel<bf16_t, 8, false><<<grid, kBlockThreads, 0, stream>>>(r);
+    else if (coef) run_kernel<float, 4, true><<<grid, kBlockThreads, 0, stream>>>(r);
+    else run_kernel<float, 4, false><<<grid, kBlockThreads, 0, stream>>>(r);
+    return hipGetLastError();
+}
+
+// Bit b: the rows of bin b go to run_kernel.  A wavefront takes many of them, so there have to be enough (MEAN, us, rows of
+// aggregate_kernel -> run_kernel, directed power-law graphs of 10 edges per vertex: 200 K vertices F=32 27.4 -> 28.9, 100 K F=100 43 -> 45;
+// 500 K F=32 59.0 -> 59.2, 100 282 -> 268, 256 506 -> 464; 1 M F=100 624 -> 578, 256 1258 -> 1110, bf16 128 296 -> 254).
+uint32_t run_bins_of(const gnn_plan *plan, int first_excluded_bin) {
+    uint32_t bins = 0;
+    int64_t rows = 0;
+    if (!plan) return 0;
+    for (int b = 0; b < plan->params.n_thresholds && b < kRunBins && b < first_excluded_bin && plan->params.thresholds[b] - 1 <= kRunEdges; ++b) {
+        bins |= 1u << b;
+        rows += plan->bin_offsets[b + 1] - plan->bin_offsets[b];
+    }
+    return rows >= kRunRows ? bins : 0u;
+}
+
+void fill_run_bins(RunArgs &r, const gnn_plan *plan, uint32_t bins, int64_t strips) {
+    int64_t rows = 0, next = 0;
+    for (int b = 0; b < kRunBins; ++b)
+        if (bins >> b & 1u) rows += plan->bin_offsets[b + 1] - plan->bin_offsets[b];
+    // as many rows per wavefront as leave the chip a few rounds of wavefronts (500 K vertices F=301: 64 rows 944 us, 32 890, 16 857; 2.45 M
+    // F=100 3.62 ms, 3.67, 3.69)
+    int32_t per_wave = 64;
+    while (per_wave > 16 && rows < per_wave * kRunWaves) per_wave /= 2;
+    r.log2_c = strips >= 64 ? 6 : gnn_ilog2_ceil(strips);
+    for (int b = kRunBins - 1; b >= 0; --b) {
+        if (!(bins >> b & 1u)) continue;
+        RunBin &d = r.bins[r.n_bins++];
+        d.first_block = next;
+        d.item_begin = plan->bin_offsets[b];
+        d.n_items = plan->bin_offsets[b + 1] - d.item_begin;
+        d.longest = int32_t(plan->params.thresholds[b] - 1);
+        d.rows_per_wave = per_wave;
+        next += (d.n_items + kWavesPerBlock * per_wave - 1) / (kWavesPerBlock * per_wave);  // N / 64 at most, so a grid holds it
+    }
+    r.n_blocks = next;
 }
 
 // Column slices for rows gathered where they lie (no plan-owned copy), counted in 16-byte strips of a row.
@@ -1422,6 +1622,13 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         if (rc != GNN_OK) { finish_overlap(); return rc; }
     }
 
+    // Bins whose rows run_kernel serves: all columns in one launch, beside the tiles and pieces where there are some (2.45 M vertices
+    // F=100, 256: 3.62, 7.13 ms in front of the other short rows, 3.93, 7.19 behind them), else behind the other rows (27.8 M bf16
+    // 14.8 ms, 15.4 in front).
+    const uint32_t run_bins = vec == max_vec && (F + vec - 1) / vec >= kRunEdges ? run_bins_of(plan, bl.active ? bl.first_bin : INT32_MAX) : 0u;
+    RunArgs runs{};
+    bool runs_beside = false;
+
     for (int gi = 0; gi < n_segs; ++gi) {
         const int64_t f0 = segs[gi].f0, fw = segs[gi].fw;
         const int log2_s = segs[gi].log2_s;
@@ -1536,16 +1743,27 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             plain_hub_columns = true;
             if (f0 < plain_hub_col_begin) plain_hub_col_begin = f0;
         }
+        hipStream_t rows_stream = (blocked && side) ? side : stream;  // the short rows of a blocked launch may overlap the pieces
+        if (gi == 0 && run_bins) {
+            runs.a = a;
+            runs.a.X = gathered;
+            runs.a.Y = out;
+            runs.a.F = int32_t(F);
+            runs.a.own_X = gathered_only && self_mode == kSelfPlain ? orig : nullptr;
+            runs.a.bias = bias;
+            runs.a.tail_slice = tail_table ? int32_t(layout.main_lines) : -1;
+            fill_run_bins(runs, plan, run_bins, (F + vec - 1) / vec);
+            runs_beside = rows_stream != stream;
+            if (runs_beside && launch_runs(coef, o.dtype == GNN_BF16, rows_stream, runs) != hipSuccess) { finish_overlap(); return GNN_ERR_LAUNCH; }
+        }
         int32_t nb = 0;
-        int64_t next_block = gnn_fill_bins(a.bins, &nb, a.first_block, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX, 1 << log2_s);
+        int64_t next_block = gnn_fill_bins(a.bins, &nb, a.first_block, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX, 1 << log2_s, run_bins);
         a.n_bins = nb;
         if (nb == 0 || next_block == 0) continue;
         next_block <<= log2_s;
         if (next_block > INT32_MAX) { finish_overlap(); return GNN_ERR_UNSUPPORTED; }
-
         dim3 grid(static_cast<unsigned>(next_block));
         hipError_t err = hipSuccess;
-        hipStream_t rows_stream = (blocked && side) ? side : stream;  // the short rows of a blocked launch may overlap the pieces
         if (o.dtype == GNN_F32) {
             if (vec == 4) err = launch_coef<float, 4>(coef, npass, grid, rows_stream, a);
             else if (vec == 2) err = launch_coef<float, 2>(coef, npass, grid, rows_stream, a);
@@ -1559,6 +1777,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         if (err != hipSuccess) { finish_overlap(); return GNN_ERR_LAUNCH; }
     }
 
+    if (run_bins && !runs_beside && launch_runs(coef, o.dtype == GNN_BF16, stream, runs) != hipSuccess) { finish_overlap(); return GNN_ERR_LAUNCH; }
     if (!finish_overlap()) return GNN_ERR_LAUNCH;
     if (has_hub && plain_hub_columns) {
         const int64_t hub_begin = plan->bin_offsets[plan->n_bins - 1];

@@ -552,14 +552,14 @@ static_assert(GNN_MAX_BINS <= GNN_FLAT_BINS, "a launch has at most one bin per b
 // Fills `bins` for a launch whose row groups have 2^log2_c column lanes; returns the number of
 // workgroups.  plan == nullptr: all N rows in one bin, whole wavefronts per row.
 // first_excluded_bin: rows of bins >= it (and the hub pieces) are left out (they are served as source-blocked pieces).
-// slices: column slices the launch multiplies the workgroups by.
+// slices: column slices the launch multiplies the workgroups by.  left_out: bit b = bin b is served by another launch.
 //
 // A launch that leaves most of the chip idle is bound by latency: the time of a row is the number of its steps (one
 // batch of loads each, about a microsecond), one after the other.  So where there are too few wavefronts, rows get more
 // edge slots than throughput asks for, and where the steps of a long row or of a hub piece outlast the launch's
 // share per wavefront, the four wavefronts of a workgroup share it (24,490 vertices, 1.2 M edges, F=100: 0.33 -> 0.06 ms).
 static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, int32_t (&first_block)[GNN_FLAT_BINS], const gnn_plan *plan, int64_t N, int log2_c,
-                                    int first_excluded_bin = INT32_MAX, int slices = 1) {
+                                    int first_excluded_bin = INT32_MAX, int slices = 1, uint32_t left_out = 0) {
     constexpr int64_t kWaveSlots = 256 * 4 * 8;  // wavefronts the chip holds of a kernel with 64 registers
     constexpr int kStepLog2 = 3;                 // loads of a slot in flight: edges per step
     const int max_log2_sr = 6 - log2_c;
@@ -609,6 +609,7 @@ static inline int64_t gnn_fill_bins(gnn_bin_desc *bins, int32_t *n_bins, int32_t
         for (int bi = last; bi >= 0; --bi) {
             if (bi >= first_excluded_bin) continue;
             if (bi == last && has_hub) continue;  // handled as pieces (+ finalize)
+            if (left_out >> bi & 1u) continue;
             // the longest row of the bin (of the last one, without pieces: unknown)
             const int64_t hi = bi < plan->params.n_thresholds ? plan->params.thresholds[bi] : plan->n_edges;
             int lsr = slots_of_bin(bi);

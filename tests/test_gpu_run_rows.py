@@ -1,0 +1,72 @@
+"""Graphs of so many short rows that wavefronts take up to 64 of them one after the other (run_kernel), against the oracle: rows
+of 0 to 9 edges, a last wavefront that is not full, one pass over the columns and several, every layout of the gathered matrix."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2104_06700_amd as gnn
+import synth
+from helpers import OP_CODE, assert_close, device_graph, host_csr
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+N = 300007
+
+
+def _graph():
+    """Rows of 0 ... 9 edges (0 most often), 40 of 300 edges, hubs of 5,000 edges; sources with a bias to small ids, duplicates allowed."""
+    v = torch.arange(N)
+    lengths = (synth.mix64(v + 5) & 0x7FFFFFFF) % 16
+    lengths = torch.where(lengths > 9, torch.zeros_like(lengths), lengths)
+    lengths[11::7501] = 300
+    lengths[77], lengths[N - 1] = 5000, 5000
+    dst = v.repeat_interleave(lengths)
+    r = synth.mix64(torch.arange(dst.numel()) + 99) & 0x7FFFFFFF
+    src = torch.where(r % 3 == 0, (r // 3) % N, (r // 3) % 3000)
+    key = torch.sort(dst * N + src).values
+    return synth.EdgeList(n=N, src=(key % N).to(torch.int32), dst=(key // N).to(torch.int32), meta={})
+
+
+@pytest.fixture(scope="module")
+def graph():
+    el = _graph()
+    return el, host_csr(el)
+
+
+@pytest.mark.parametrize("op_name,weights", [("mean", False), ("sage", False), ("sum", True), ("gcn", False)])
+@pytest.mark.parametrize("f,dtype,shift", [(32, torch.float32, 0), (33, torch.float32, 1), (100, torch.float32, 0), (261, torch.float32, 0),
+                                           (64, torch.bfloat16, 0), (129, torch.bfloat16, 1)])
+def test_short_rows_served_many_per_wavefront(graph, f, dtype, shift, op_name, weights):
+    el, (indptr, indices, indptr_t, indices_t, perm) = graph
+    bf16 = dtype == torch.bfloat16
+    din, dout = np.diff(indptr), np.diff(indptr_t)
+    wts = (synth.uniform_features(el.e, 1, 7).reshape(-1) + 0.5) if weights else None
+    w = None if wts is None else wts.numpy()
+    X = synth.normal_features(N, f, 3, dtype=dtype)
+    op = OP_CODE[op_name]
+    Yo, S = oracle.aggregate_fwd(indptr, indices, X.float().numpy(), op=op, w=w, dout=dout, nthreads=8, want_scale=True)
+    dXo, St = oracle.aggregate_bwd(indptr_t, indices_t, X.float().numpy(), op=op, wt=None if w is None else w[perm], din=din, nthreads=8,
+                                   want_scale=True)
+    flat = torch.full((N * f + shift,), float("nan"), dtype=dtype, device=DEV)
+    Xd = flat[shift:].view(N, f)
+    Xd.copy_(X)
+    dg = device_graph(el, weights=wts, indptr64=f == 100)
+    for what in ("as chosen", "copied", "rows of the copy whole", "blocked"):
+        flags = {"copied": gnn.GNN_FLAG_FORCE_PADDED_COPY,
+                 "rows of the copy whole": gnn.GNN_FLAG_FORCE_PADDED_COPY | gnn.GNN_FLAG_NO_SLICE_TABLES}.get(what, 0)
+        if what == "blocked":  # the 300-edge rows as pieces, the others beside them
+            flags = gnn.GNN_FLAG_FORCE_PADDED_COPY
+            dg = device_graph(el, weights=wts, indptr64=f == 100)
+            for p in (dg.plan_fwd, dg.plan_bwd):
+                p.set_blocking(256, 4096, 4096, 96, 2)
+            if weights:
+                dg.plan_fwd.bind_edge_weights(dg.edge_w)
+                dg.plan_bwd.bind_edge_weights(dg.edge_w_t)
+        out = torch.full((2, N * f + shift), float("nan"), dtype=dtype, device=DEV)
+        Y, dX = (o[shift:].view(N, f) for o in out)
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, dg.edge_w, Xd, Y, N, f, op, plan=dg.plan_fwd, flags=flags)
+        gnn.gnn_aggregate_bwd(dg.indptr_t, dg.indices_t, dg.edge_w_t, Xd, dX, N, f, op, plan=dg.plan_bwd, flags=flags)
+        torch.cuda.synchronize()
+        assert_close(Y, Yo, S, bf16, f"fwd {what}")
+        assert_close(dX, dXo, St, bf16, f"bwd {what}")

@@ -349,6 +349,75 @@ __device__ __forceinline__ void write_strip(const AggArgs &a, int64_t row, int64
     store_strip<T, VEC>(static_cast<T *>(a.Y) + row * a.ldy + col, o, ncols, a.store_vec);
 }
 
+// The row (or hub piece) a group of lanes owns: e0 .. e1 index the launch's `indices`; the per-edge streams of the caller (weights,
+// factors) live at e + wdelta.
+struct RowOfGroup {
+    int64_t e0, e1, row, row_len, wdelta;
+    float *partial_out;  // of a hub piece
+};
+template <bool COEF>
+__device__ __forceinline__ RowOfGroup find_row(const AggArgs &a, const BinDesc &bin, const int4 *row_info, const int64_t *p_indptr,
+                                               int64_t wave_in_bin, int lane, bool coop, int wave_in_block) {
+    RowOfGroup r{0, 0, -1, 0, 0, nullptr};
+    if (bin.kind & kKindHubPieces) {
+        const int64_t piece = wave_in_bin;  // G == 64: one piece per wavefront (per workgroup when shared)
+        if (piece < bin.n_items) {
+            if (a.p_chunks) {
+                const int64_t *p = a.p_chunks + 4 * (bin.item_begin + piece);
+                r.row = p[0]; r.e0 = p[1]; r.e1 = p[2]; r.wdelta = p[3];
+            } else {
+                const int64_t *p = a.chunks + 3 * (bin.item_begin + piece);
+                r.row = p[0]; r.e0 = p[1]; r.e1 = p[2];
+            }
+            r.partial_out = a.partial + (bin.item_begin + piece) * a.ldp;
+        }
+    } else {
+        const int64_t item = wave_in_bin * (64 >> bin.log2_g) + (lane >> bin.log2_g);
+        if (item < bin.n_items) {
+            int64_t begin;
+            if (row_info) {
+                const int4 info = row_info[bin.item_begin + item];
+                r.row = info.x;
+                begin = uint32_t(info.y);
+                r.row_len = info.z;
+            } else {
+                r.row = a.row_perm ? int64_t(a.row_perm[bin.item_begin + item]) : bin.item_begin + item;
+                begin = load_ip(a.indptr, a.ip64, r.row);
+                r.row_len = load_ip(a.indptr, a.ip64, r.row + 1) - begin;
+            }
+            r.e0 = p_indptr ? p_indptr[bin.item_begin + item] : begin;
+            r.e1 = r.e0 + r.row_len;
+            if (COEF) r.wdelta = begin - r.e0;
+        }
+    }
+    if (coop) {  // this wavefront's quarter of the list
+        const int64_t quarter = (r.e1 - r.e0 + kWavesPerBlock - 1) / kWavesPerBlock;
+        r.e0 += wave_in_block * quarter;
+        if (r.e0 + quarter < r.e1) r.e1 = r.e0 + quarter;
+    }
+    return r;
+}
+
+// Adds the sums of a workgroup's wavefronts in order; true on the first one, which has the total.
+template <int NPASS, int VEC>
+__device__ __forceinline__ bool add_quarters(float *sums, float (&acc)[NPASS][VEC], int wave_in_block, int lane) {
+    if (wave_in_block > 0) {
+#pragma unroll
+        for (int p = 0; p < NPASS; ++p)
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) sums[(((wave_in_block - 1) * NPASS + p) * VEC + i) * 64 + lane] = acc[p][i];
+    }
+    __syncthreads();
+    if (wave_in_block > 0) return false;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock - 1; ++w)
+#pragma unroll
+        for (int p = 0; p < NPASS; ++p)
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[p][i] += sums[((w * NPASS + p) * VEC + i) * 64 + lane];
+    return true;
+}
+
 // ---------------------------------------------------------------- main kernel
 // T: storage type of X and Y.  VEC: elements per lane per load.  NPASS: feature
 // passes (a lane owns NPASS strips of VEC columns, C*VEC apart).  COEF: edges
@@ -367,12 +436,16 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     const int col_base = slice * a.slice_cols;
     const int Fk = a.F - col_base < a.slice_cols ? a.F - col_base : a.slice_cols;  // columns of this slice
     // What the way to the first gather needs arrives with the bins: one wait, where the compiler would load each at its use.
-    const int4 *row_info = a.row_info;
-    const int64_t *p_indptr = a.p_indptr;
-    const int32_t *indices = a.indices;
-    const void *table = a.X;
+    auto info_g = (gnn_global_ptr<int4>)a.row_info;
+    auto p_indptr_g = (gnn_global_ptr<int64_t>)a.p_indptr;
+    auto indices_g = (gnn_global_ptr<int32_t>)a.indices;
+    auto table_g = (gnn_global_ptr<char>)a.X;
     int64_t table_ld = a.ldx, slice_stride = a.slice_stride;
-    asm volatile("" : "+s"(row_info), "+s"(p_indptr), "+s"(indices), "+s"(table), "+s"(table_ld), "+s"(slice_stride));
+    asm volatile("" : "+s"(info_g), "+s"(p_indptr_g), "+s"(indices_g), "+s"(table_g), "+s"(table_ld), "+s"(slice_stride));
+    const int4 *row_info = (const int4 *)info_g;
+    const int64_t *p_indptr = (const int64_t *)p_indptr_g;
+    const int32_t *indices = (const int32_t *)indices_g;
+    const void *table = (const void *)table_g;
     const int b = gnn_bin_of_block(a.first_block, vblock);
     const BinDesc bin = a.bins[b];
     if (Fk <= 0) return;
@@ -388,46 +461,9 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     const int s = lane_in_g >> log2_c;  // edge slot of this lane
     const int c = lane_in_g & (C - 1);  // feature strip of this lane
 
-    // the row (or hub piece) this group owns
-    // e0..e1 index `indices`; the per-edge streams of the caller (weights, factors) live at e + wdelta
-    int64_t e0 = 0, e1 = 0, row = -1, row_len = 0, wdelta = 0;
-    float *partial_out = nullptr;
-    if (bin.kind & kKindHubPieces) {
-        const int64_t piece = wave_in_bin;  // G == 64: one piece per wavefront (per workgroup when shared)
-        if (piece < bin.n_items) {
-            if (a.p_chunks) {
-                const int64_t *p = a.p_chunks + 4 * (bin.item_begin + piece);
-                row = p[0]; e0 = p[1]; e1 = p[2]; wdelta = p[3];
-            } else {
-                const int64_t *p = a.chunks + 3 * (bin.item_begin + piece);
-                row = p[0]; e0 = p[1]; e1 = p[2];
-            }
-            partial_out = a.partial + (bin.item_begin + piece) * a.ldp;
-        }
-    } else {
-        const int64_t item = wave_in_bin * (64 >> bin.log2_g) + (lane >> bin.log2_g);
-        if (item < bin.n_items) {
-            int64_t begin;
-            if (row_info) {
-                const int4 info = row_info[bin.item_begin + item];
-                row = info.x;
-                begin = uint32_t(info.y);
-                row_len = info.z;
-            } else {
-                row = a.row_perm ? int64_t(a.row_perm[bin.item_begin + item]) : bin.item_begin + item;
-                begin = load_ip(a.indptr, a.ip64, row);
-                row_len = load_ip(a.indptr, a.ip64, row + 1) - begin;
-            }
-            e0 = p_indptr ? p_indptr[bin.item_begin + item] : begin;
-            e1 = e0 + row_len;
-            if (COEF) wdelta = begin - e0;
-        }
-    }
-    if (coop) {  // this wavefront's quarter of the list
-        const int64_t quarter = (e1 - e0 + kWavesPerBlock - 1) / kWavesPerBlock;
-        e0 += wave_in_block * quarter;
-        if (e0 + quarter < e1) e1 = e0 + quarter;
-    }
+    const RowOfGroup r = find_row<COEF>(a, bin, row_info, p_indptr, wave_in_bin, lane, coop, wave_in_block);
+    const int64_t e0 = r.e0, e1 = r.e1, row = r.row, row_len = r.row_len, wdelta = r.wdelta;
+    float *partial_out = r.partial_out;
 
     float acc[NPASS][VEC];
 #pragma unroll
@@ -572,22 +608,7 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     }
 
     if constexpr (COOP) {
-        if (coop) {  // the quarters are added in order
-            if (wave_in_block > 0) {
-#pragma unroll
-                for (int p = 0; p < NPASS; ++p)
-#pragma unroll
-                    for (int i = 0; i < VEC; ++i) coop_sums[(((wave_in_block - 1) * NPASS + p) * VEC + i) * 64 + lane] = acc[p][i];
-            }
-            __syncthreads();
-            if (wave_in_block > 0) return;
-#pragma unroll
-            for (int w = 0; w < kWavesPerBlock - 1; ++w)
-#pragma unroll
-                for (int p = 0; p < NPASS; ++p)
-#pragma unroll
-                    for (int i = 0; i < VEC; ++i) acc[p][i] += coop_sums[((w * NPASS + p) * VEC + i) * 64 + lane];
-        }
+        if (coop && !add_quarters<NPASS, VEC>(coop_sums, acc, wave_in_block, lane)) return;
     }
     if (row < 0 || s != 0) return;
     if (bin.kind & kKindHubPieces) {
@@ -605,6 +626,166 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
             VecIO<T, VEC>::load(a.own_X ? static_cast<const T *>(a.own_X) + row * a.own_ld + col[p] : X + self_row * ldx + lcol[p], own);
         write_strip<T, VEC>(a, row, row_len, col[p], ncols[p], own, acc[p]);
     }
+}
+
+// The same for one strip per lane, 16-byte loads and tables below 4 GB, with a third of the vector instructions: where a launch is a
+// chain of loads rather than a stream of them, each batch of gathers leaves earlier.  A lane multiplies its own index by the row
+// stride as it fetches it, so that a shuffle brings an offset; a slot without an edge carries kNoRow, which lies behind the end of
+// the buffer, where a buffer load returns zeros and touches no memory (aggregate_kernel: a compare, four zeros and a 64-bit
+// multiply-add per line).  Rows of 4, 2, 1 lanes (CLANES; 8 stands for eight or more) gather from two or four tiles of indices at a
+// time, so that they too have eight (four) lines in flight.
+//
+// 24,490 vertices, 1.2 M edges, us: F=4 27.0 -> 14.9, 16 18.6 -> 14.5, 100 45.5 -> 42.1, 256 78 -> 68; bf16 F=64 on 245 K vertices 107 -> 96,
+// F=100 on 2.45 M 2.61 -> 2.55 ms.  fp32 launches that fill the chip are bound by lines and lose 1 to 3 % (133 K vertices, 79 M edges F=64
+// 1.235 -> 1.244 ms, 2.45 M F=16 787 -> 810 us): they stay with aggregate_kernel (see use_gather_kernel).
+constexpr uint32_t kNoRow = 0xFFFF0000u;         // offset of no row, end of the buffer; columns add less than 64 KB
+constexpr int64_t kMaxTableBytes = 0xFFFF0000;
+
+template <typename T, bool COEF, bool COOP, int CLANES>
+__global__ void __launch_bounds__(kBlockThreads) gather_kernel(const AggArgs a) {
+    constexpr int VEC = 16 / int(sizeof(T));
+    __shared__ float coop_sums[COOP ? (kWavesPerBlock - 1) * VEC * 64 : 1];  // of wavefronts 1 .. 3, by column and lane
+    const int lane = threadIdx.x & 63;
+    const int wave_in_block = threadIdx.x >> 6;
+    const int slice = int(blockIdx.x) & ((1 << a.log2_slices) - 1);
+    const int64_t vblock = int64_t(blockIdx.x) >> a.log2_slices;
+    const int col_base = slice * a.slice_cols;
+    const int Fk = a.F - col_base < a.slice_cols ? a.F - col_base : a.slice_cols;  // columns of this slice
+    // What the way to the first gather needs arrives with the bins: one wait, where the compiler would load each at its use.
+    auto info_g = (gnn_global_ptr<int4>)a.row_info;
+    auto p_indptr_g = (gnn_global_ptr<int64_t>)a.p_indptr;
+    auto indices_g = (gnn_global_ptr<int32_t>)a.indices;
+    auto table_g = (gnn_global_ptr<char>)a.X;
+    int64_t table_ld = a.ldx, slice_stride = a.slice_stride;
+    asm volatile("" : "+s"(info_g), "+s"(p_indptr_g), "+s"(indices_g), "+s"(table_g), "+s"(table_ld), "+s"(slice_stride));
+    const int4 *row_info = (const int4 *)info_g;
+    const int64_t *p_indptr = (const int64_t *)p_indptr_g;
+    const int32_t *indices = (const int32_t *)indices_g;
+    const void *table = (const void *)table_g;
+    const int b = gnn_bin_of_block(a.first_block, vblock);
+    const BinDesc bin = a.bins[b];
+    if (Fk <= 0) return;
+    const bool coop = COOP && (bin.kind & GNN_BIN_COOP);
+    const int64_t wave_in_bin = coop ? vblock - bin.first_block : (vblock - bin.first_block) * kWavesPerBlock + wave_in_block;
+
+    const int G = 1 << bin.log2_g;
+    const int SR = 1 << bin.log2_sr;
+    const int log2_c = bin.log2_g - bin.log2_sr;
+    const int C = 1 << log2_c;
+    const int lane_in_g = lane & (G - 1);
+    const int gbase = lane - lane_in_g;
+    const int s = lane_in_g >> log2_c;  // edge slot of this lane
+    const int c = lane_in_g & (C - 1);  // feature strip of this lane
+
+    const RowOfGroup r = find_row<COEF>(a, bin, row_info, p_indptr, wave_in_bin, lane, coop, wave_in_block);
+    const int n_edges = int(r.e1 - r.e0);
+    const int32_t *idx = indices + r.e0;
+    const float *w = COEF && a.w ? a.w + r.e0 + r.wdelta : nullptr;
+    const float *scale = COEF && a.edge_scale ? a.edge_scale + r.e0 + r.wdelta : nullptr;
+
+    // the slice that holds the last, short line of the rows gathers it from the dense tail table
+    const bool is_tail = slice == a.tail_slice;
+    const bool own_table = is_tail || slice_stride > 0;  // columns are addressed within the slice
+    const T *X = is_tail ? static_cast<const T *>(a.X_tail) : static_cast<const T *>(table) + int64_t(slice) * slice_stride;
+    const int64_t ldx = is_tail ? a.ld_tail : (slice_stride > 0 ? int64_t(a.slice_cols) : table_ld);
+    int lc = c * VEC;
+    const bool col_ok = lc < Fk;
+    if (a.overlap && lc > Fk - VEC) lc = Fk - VEC;  // may begin in the slice before: those columns get the same values there
+    const int col = col_base + lc;                  // column in the output (and in a caller's matrix)
+    const int lcol = own_table ? lc : col;          // column in the table this slice gathers from
+    const int ncols = Fk - lc < VEC ? Fk - lc : VEC;  // valid columns of the strip (< VEC only for the last strip of a padded matrix)
+    const uint32_t row_bytes = uint32_t(ldx) * uint32_t(sizeof(T));
+    const uint32_t col_bytes = uint32_t(lcol) * uint32_t(sizeof(T));
+    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(X), 0, int(kNoRow), 0x00020000);  // raw, bytes
+
+    float acc[1][VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[0][i] = 0.0f;
+
+    auto fetch = [&](int e, uint32_t &off, float &cf) {
+        off = kNoRow;
+        cf = 0.0f;
+        if (e < n_edges) {
+            off = uint32_t(idx[e] & 0x7FFFFFFF) * row_bytes;
+            if (COEF) {
+                cf = a.w ? w[e] : 1.0f;
+                if (a.edge_scale) cf *= scale[e];
+            }
+        }
+    };
+    const int shfl0 = 4 * (gbase + s), shfl_step = 4 * SR;
+    // U edges per slot of a tile (G edges) at a time, of TILES tiles: eight loads in flight.  Q tiles are fetched while the Q before
+    // them are gathered.
+    auto walk = [&](auto u_const, auto tiles_const, auto q_const) {
+        constexpr int U = decltype(u_const)::value, TILES = decltype(tiles_const)::value, Q = decltype(q_const)::value;
+        uint32_t nxt[Q];
+        float nxt_cf[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) fetch(lane_in_g + q * G, nxt[q], nxt_cf[q]);
+        for (int first = 0; __any(first < n_edges); first += Q * G) {
+            uint32_t cur[Q];
+            float cur_cf[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) { cur[q] = nxt[q]; cur_cf[q] = nxt_cf[q]; }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) fetch(first + (Q + q) * G + lane_in_g, nxt[q], nxt_cf[q]);
+#pragma unroll 1
+            for (int q0 = 0; q0 < Q; q0 += TILES) {
+                const int left = n_edges - (first + q0 * G), n = left < G ? left : G;
+                if (q0 > 0 && !__any(left > 0)) break;
+                int at = shfl0;
+                for (int j0 = 0; __any(j0 < n); j0 += SR * U, at += U * shfl_step) {
+                    u32x4 x[TILES][U];
+                    float cf[TILES][U];
+#pragma unroll
+                    for (int q = 0; q < TILES; ++q)
+#pragma unroll
+                        for (int k = 0; k < U; ++k) {
+                            const uint32_t off = uint32_t(__builtin_amdgcn_ds_bpermute(at + k * shfl_step, int(cur[q])));
+                            if (COEF) cf[q][k] = __int_as_float(__builtin_amdgcn_ds_bpermute(at + k * shfl_step, __float_as_int(cur_cf[q])));
+                            x[q][k] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, col_ok ? off + col_bytes : kNoRow, 0, 0);
+                        }
+#pragma unroll
+                    for (int q = 0; q < TILES; ++q)
+#pragma unroll
+                        for (int k = 0; k < U; ++k) {
+                            float v[VEC];
+                            Strip<T, VEC>::unpack(x[q][k], v);
+#pragma unroll
+                            for (int i = 0; i < VEC; ++i) {
+                                if (COEF) acc[0][i] = fmaf(cf[q][k], v[i], acc[0][i]);
+                                else acc[0][i] += v[i];
+                            }
+                        }
+                    if (U < 8) break;  // a tile of narrow rows is one step
+                }
+#pragma unroll
+                for (int q = 0; q + TILES < Q; ++q) { cur[q] = cur[q + TILES]; cur_cf[q] = cur_cf[q + TILES]; }
+            }
+        }
+    };
+    using std::integral_constant;
+    if constexpr (CLANES == 8) walk(integral_constant<int, 8>(), integral_constant<int, 1>(), integral_constant<int, sizeof(T) == 4 ? 2 : 1>());
+    else walk(integral_constant<int, CLANES>(), integral_constant<int, CLANES == 1 ? 4 : 8 / CLANES>(), integral_constant<int, CLANES == 1 ? 4 : 8 / CLANES>());
+
+    // combine the edge slots of the group
+    for (int off = C; off < G; off <<= 1)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[0][i] += __shfl_xor(acc[0][i], off);
+    if constexpr (COOP) {
+        if (coop && !add_quarters<1, VEC>(coop_sums, acc, wave_in_block, lane)) return;
+    }
+    if (r.row < 0 || s != 0 || !col_ok) return;
+    if (r.partial_out) {
+        store_f32<VEC>(r.partial_out + col, acc[0]);
+        return;
+    }
+    float own[VEC];
+    if (a.self_mode != kSelfNone) {
+        const int64_t self_row = a.row_map ? int64_t(a.row_map[r.row]) : r.row;
+        VecIO<T, VEC>::load(a.own_X ? static_cast<const T *>(a.own_X) + r.row * a.own_ld + col : X + self_row * ldx + lcol, own);
+    }
+    write_strip<T, VEC>(a, r.row, r.row_len, col, ncols, own, acc[0]);
 }
 
 constexpr int kRunEdges = 8;        // edges of a row of run_kernel at most
@@ -1127,10 +1308,40 @@ hipError_t launch_pad(const void *src, int64_t ld_src, void *dst, int64_t ld_dst
 }
 
 // ---------------------------------------------------------------- host side
-template <typename T, int VEC, bool COEF>
-hipError_t launch_npass(int npass, dim3 grid, hipStream_t stream, const AggArgs &a) {
+bool has_coop_bin(const AggArgs &a) {
     bool coop = false;
     for (int i = 0; i < a.n_bins; ++i) coop |= (a.bins[i].kind & GNN_BIN_COOP) != 0;
+    return coop;
+}
+
+// Shared rows on few edges: the launch is too small for the chip (61 K vertices, 3.1 M edges F=8 25.6 -> 22.5 us, F=100 the same; 245 K,
+// 12.4 M F=64 weighted 194 -> 200, 1 M, 10 M F=8 95 -> 98).  bf16 always: it gains registers too.
+bool use_gather_kernel(const AggArgs &a, int64_t n_edges, bool bf16, int log2_c) {
+    return (has_coop_bin(a) && n_edges <= (int64_t(1) << 22)) || (bf16 && log2_c >= 3);
+}
+
+template <typename T>
+hipError_t launch_gather(int log2_c, bool coef, dim3 grid, hipStream_t stream, const AggArgs &a) {
+    auto launch = [&](auto coop, auto lanes) {
+        constexpr bool COOP = decltype(coop)::value;
+        constexpr int L = decltype(lanes)::value;
+        if (coef) gather_kernel<T, true, COOP, L><<<grid, kBlockThreads, 0, stream>>>(a);
+        else gather_kernel<T, false, COOP, L><<<grid, kBlockThreads, 0, stream>>>(a);
+    };
+    using std::integral_constant;
+    if (!has_coop_bin(a)) {
+        if constexpr (sizeof(T) == 2) launch(integral_constant<bool, false>(), integral_constant<int, 8>());
+        else return hipErrorInvalidValue;
+    } else if (log2_c >= 3) launch(integral_constant<bool, true>(), integral_constant<int, 8>());
+    else if (log2_c == 2) launch(integral_constant<bool, true>(), integral_constant<int, 4>());
+    else if (log2_c == 1) launch(integral_constant<bool, true>(), integral_constant<int, 2>());
+    else launch(integral_constant<bool, true>(), integral_constant<int, 1>());
+    return hipGetLastError();
+}
+
+template <typename T, int VEC, bool COEF>
+hipError_t launch_npass(int npass, dim3 grid, hipStream_t stream, const AggArgs &a) {
+    const bool coop = has_coop_bin(a);
     if (npass == 1) {
         if (coop) aggregate_kernel<T, VEC, 1, COEF, true><<<grid, kBlockThreads, 0, stream>>>(a);
         else aggregate_kernel<T, VEC, 1, COEF><<<grid, kBlockThreads, 0, stream>>>(a);
@@ -1622,6 +1833,10 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         if (rc != GNN_OK) { finish_overlap(); return rc; }
     }
 
+    // gather_kernel: 16-byte strips at the alignment of a word, tables whose offsets are 32 bits
+    const bool words = esz == 4 || (reinterpret_cast<uintptr_t>(gathered) % 4 == 0 && ldg % 2 == 0 && (!overlap || F % 2 == 0));
+    const bool few_bytes = plan && plan->n_edges < (int64_t(1) << 31) && vec == max_vec && words && ldg < (int64_t(1) << 32) && N * (slice_major ? line_elems : ldg) <= kMaxTableBytes / esz;
+
     // Bins whose rows run_kernel serves: all columns in one launch, beside the tiles and pieces where there are some (2.45 M vertices
     // F=100, 256: 3.62, 7.13 ms in front of the other short rows, 3.93, 7.19 behind them), else behind the other rows (27.8 M bf16
     // 14.8 ms, 15.4 in front).
@@ -1764,7 +1979,9 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         if (next_block > INT32_MAX) { finish_overlap(); return GNN_ERR_UNSUPPORTED; }
         dim3 grid(static_cast<unsigned>(next_block));
         hipError_t err = hipSuccess;
-        if (o.dtype == GNN_F32) {
+        if (few_bytes && npass == 1 && use_gather_kernel(a, plan->n_edges, o.dtype == GNN_BF16, log2_c)) {
+            err = o.dtype == GNN_F32 ? launch_gather<float>(log2_c, coef, grid, rows_stream, a) : launch_gather<bf16_t>(log2_c, coef, grid, rows_stream, a);
+        } else if (o.dtype == GNN_F32) {
             if (vec == 4) err = launch_coef<float, 4>(coef, npass, grid, rows_stream, a);
             else if (vec == 2) err = launch_coef<float, 2>(coef, npass, grid, rows_stream, a);
             else err = launch_coef<float, 1>(coef, npass, grid, rows_stream, a);

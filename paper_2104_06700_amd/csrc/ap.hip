@@ -150,8 +150,15 @@ struct Near {
     const int32_t *indices;
     const float *fV, *fE;
     int64_t ldv, lde;
-    __device__ __forceinline__ explicit Near(const ApArgs &a) : row_info(a.row_info), indices(a.indices), fV(a.fV), fE(a.fE), ldv(a.ldv), lde(a.lde) {
-        asm volatile("" : "+s"(row_info), "+s"(indices), "+s"(fV), "+s"(fE), "+s"(ldv), "+s"(lde));
+    __device__ __forceinline__ explicit Near(const ApArgs &a) : ldv(a.ldv), lde(a.lde) {
+        auto info = (gnn_global_ptr<int4>)a.row_info;
+        auto idx = (gnn_global_ptr<int32_t>)a.indices;
+        auto v = (gnn_global_ptr<float>)a.fV, e = (gnn_global_ptr<float>)a.fE;
+        asm volatile("" : "+s"(info), "+s"(idx), "+s"(v), "+s"(e), "+s"(ldv), "+s"(lde));
+        row_info = (const int4 *)info;
+        indices = (const int32_t *)idx;
+        fV = (const float *)v;
+        fE = (const float *)e;
     }
 };
 

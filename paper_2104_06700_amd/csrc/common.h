@@ -517,6 +517,11 @@ int gnn_aggregate_prepacked(const void *indptr, const int32_t *indices, void *ou
 int gnn_aggregate_fwd_epilogue(const void *indptr, const int32_t *indices, const void *X, void *Y, int64_t N, int64_t F,
                                int op, const gnn_opts *opts, const float *bias, int relu);
 
+// A pointer to device memory that an asm statement has passed through is generic to the compiler unless its type says where it
+// points, and generic loads count as LDS accesses too: every wait for a shuffle then waits for the gathers before it.
+template <typename T>
+using gnn_global_ptr = const T __attribute__((address_space(1))) *;
+
 // ---- work distribution shared by the aggregation kernels (aggregate.hip, ap.hip) ----
 // A launch serves all degree bins of a plan at once: the workgroup index is looked up in a small
 // table of bins (heaviest work first).  A bin holds rows (64 >> log2_g rows per wavefront, each row

@@ -70,3 +70,34 @@ def test_short_rows_served_many_per_wavefront(graph, f, dtype, shift, op_name, w
         torch.cuda.synchronize()
         assert_close(Y, Yo, S, bf16, f"fwd {what}")
         assert_close(dX, dXo, St, bf16, f"bwd {what}")
+
+
+@pytest.mark.parametrize("dtype,widths", [(torch.float32, (4, 5, 8, 12, 16, 29, 47)), (torch.bfloat16, (8, 10, 16, 32, 66))])
+@pytest.mark.parametrize("weights", [False, True])
+def test_small_graph_rows_of_few_lanes(dtype, widths, weights):
+    """gather_kernel: rows of 1, 2, 4 and more lanes, slots without an edge, long rows shared by a workgroup; infinities stay in the
+    rows and columns that have them (slots without an edge read zeros, lanes without columns nothing)."""
+    n, bf16 = 900, dtype == torch.bfloat16
+    lengths = torch.tensor([0, 1, 2, 3, 7, 8, 9, 31, 33, 64, 65, 300, 1500, 5000] + [6] * (n - 14))
+    dst = torch.arange(n).repeat_interleave(lengths)
+    src = (synth.mix64(torch.arange(dst.numel()) + 9) & 0x7FFFFFFF) % (n - 1)
+    key = torch.sort(dst * n + src).values
+    el = synth.EdgeList(n=n, src=(key % n).to(torch.int32), dst=(key // n).to(torch.int32), meta={})
+    indptr, indices, *_ = host_csr(el)
+    wts = (synth.uniform_features(el.e, 1, 7).reshape(-1) + 0.5) if weights else None
+    dg = device_graph(el, weights=wts)
+    for f in widths:
+        X = synth.normal_features(n, f, 3, dtype=dtype)
+        Yo, S = oracle.aggregate_fwd(indptr, indices, X.float().numpy(), op=oracle.OP_SUM, w=None if wts is None else wts.numpy(), nthreads=8,
+                                     want_scale=True)
+        X[n - 1] = float("inf")  # nobody gathers it
+        Y = torch.full((n, f), float("nan"), dtype=dtype, device=DEV)
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, dg.edge_w, X.to(DEV), Y, n, f, gnn.GNN_SUM, plan=dg.plan_fwd)
+        torch.cuda.synchronize()
+        assert_close(Y, Yo, S, bf16, f"F={f}")
+        X[n - 1], X[5, f - 1] = 0.0, float("inf")
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, dg.edge_w, X.to(DEV), Y, n, f, gnn.GNN_SUM, plan=dg.plan_fwd)
+        torch.cuda.synchronize()
+        has = torch.zeros(n, dtype=torch.bool)
+        has[el.dst[el.src == 5].long()] = True
+        assert torch.equal(torch.isinf(Y[:, f - 1]).cpu(), has) and bool(torch.isfinite(Y[:, :f - 1]).all())

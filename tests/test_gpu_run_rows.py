@@ -84,7 +84,7 @@ def test_small_graph_rows_of_few_lanes(dtype, widths, weights):
     key = torch.sort(dst * n + src).values
     el = synth.EdgeList(n=n, src=(key % n).to(torch.int32), dst=(key // n).to(torch.int32), meta={})
     indptr, indices, *_ = host_csr(el)
-    wts = (synth.uniform_features(el.e, 1, 7).reshape(-1) + 0.5) if weights else None
+    wts = (synth.uniform_features(el.e, 1, 7).reshape(-1).abs() + 0.5) if weights else None
     dg = device_graph(el, weights=wts)
     for f in widths:
         X = synth.normal_features(n, f, 3, dtype=dtype)

@@ -456,3 +456,31 @@ def test_edge_dots_of_long_rows_are_split_over_the_xcds(d, hubs, ordered, wide):
         part = slice(at, at + (1 << 24))
         terms = v.double()[src[part].long()] * do.double()[dst[part].long()]
         assert bool(((out[part].double() - terms.sum(1)).abs() <= 1e-5 * terms.abs().sum(1)).all())
+
+
+@pytest.mark.parametrize("n,d", [(250007, 13), (120001, 31), (60013, 61), (31300, 96)])
+@pytest.mark.parametrize("binop", [gnn.GNN_BIN_MUL, gnn.GNN_BIN_DIV])
+def test_full_width_operands_on_rows_off_line_boundaries(n, d, binop):
+    """Rows that are copied to line boundaries first (and 96 columns, which lie on them) give the bits of rows that have their own lines."""
+    el = synth.rmat_symmetric(n, 24 * n + n % 2 * 24, (0.45, 0.22, 0.22, 0.11), 3, device=DEV)
+    dg = gnn.build_device_graph(el.dst, el.src, n, want_perm=True)
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    rand = lambda rows: torch.empty(rows, d, device=DEV).normal_(generator=gen)
+    v, do, fe = rand(n), rand(n), rand(el.e) + 9.0
+    lines = torch.full((2, n, (d + 31) // 32 * 32), float("nan"), device=DEV)  # each row in lines of its own
+    lines[0, :, :d], lines[1, :, :d] = v, do
+    results = []
+    for x, g in ((v, do), (lines[0, :, :d], lines[1, :, :d])):
+        o, dv, dfe = torch.full_like(v, 7.0), torch.full_like(v, 7.0), torch.full_like(fe, 7.0)
+        top, won = torch.full_like(v, 7.0), torch.full((n, d), 7, dtype=torch.int32, device=DEV)
+        gnn.gnn_ap_fwd(dg.indptr, dg.indices, x, fe, o, None, n, d, binop, gnn.GNN_RED_SUM, plan=dg.plan_fwd)
+        gnn.gnn_ap_fwd(dg.indptr, dg.indices, x, fe, top, won, n, d, binop, gnn.GNN_RED_MAX, plan=dg.plan_fwd)
+        gnn.gnn_ap_bwd_vertex(dg.indptr_t, dg.indices_t, g, fe, dv, n, d, binop, plan=dg.plan_bwd, edge_ids=dg.perm)
+        gnn.gnn_ap_bwd_edge(dg.indptr, dg.indices, None, x, fe, do, dfe, n, d, binop, plan=dg.plan_fwd)
+        results.append((o, top, won, dv, dfe))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+    m = v[el.src[:1000].long()] * fe[:1000] if binop == gnn.GNN_BIN_MUL else v[el.src[:1000].long()] / fe[:1000]
+    last = int(el.dst[999])  # rows before it are whole
+    want = torch.zeros(last, d, device=DEV, dtype=torch.float64).index_add_(0, el.dst[:1000].long()[el.dst[:1000] < last], m.double()[el.dst[:1000] < last])
+    assert torch.allclose(results[0][0][:last].double(), want, rtol=1e-4, atol=1e-4)

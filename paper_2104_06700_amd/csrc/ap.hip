@@ -729,7 +729,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
             if (c.o.edge_ids || c.lde != 1) {
                 w = nullptr;
                 if (plan && plan->n_edges > 0) {
-                    rc = gnn_plan_edge_operand(plan, fE, c.lde, c.o.edge_ids, c.stream, &w);
+                    rc = gnn_plan_edge_operand(plan, fE, c.lde, c.o.edge_ids, indptr, c.o.indptr_is_64 ? 1 : 0, c.stream, &w);
                     if (rc != GNN_OK) return rc;
                 }
             }

@@ -473,7 +473,7 @@ int gnn_plan_create_pair(const void *indptr, const void *indptr_t, const int32_t
 // Builds the array on first use (allocation).
 // out[e] = fE[(edge_ids ? edge_ids[e] : e) * lde] for the plan's n_edges edges, into a plan-owned
 // array (allocated on first use, refilled by every call).
-int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const int64_t *edge_ids, hipStream_t stream,
+int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const int64_t *edge_ids, const void *indptr, int ip64, hipStream_t stream,
                           const float **out);
 int gnn_plan_edge_scale(gnn_plan *plan, const int32_t *indices, int mode, hipStream_t stream, const float **out);
 

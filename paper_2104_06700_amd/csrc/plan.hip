@@ -263,14 +263,112 @@ __global__ void __launch_bounds__(256) edge_operand_kernel(const float *__restri
     }
 }
 
-int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const int64_t *edge_ids, hipStream_t stream,
+typedef int64_t i64x2_any __attribute__((ext_vector_type(2), aligned(8)));
+typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+constexpr int64_t kOperandEdges = 48000000;
+constexpr int kOperandRows = 2;                // rows of a wavefront at a time ...
+constexpr int kOperandBlocks = 8 * 32 * 4;     // ... and 16 wavefronts per compute unit: more rows in flight touch more lines than an L2 holds
+
+// The same with the k-th eighth of every row on XCD k, rows in ascending order.  Where the operand is that of a transposed graph an
+// id is a place in the row of the edge's other end, so an eighth leads to an eighth of those rows, and a line of 32 scalars is met
+// again by the next few hundred rows: it waits for them in the L2 (133 K rows: 17,000 lines) where the plain kernel misses on every
+// one (62 G loads/s, the rate behind the L2s; 268 G from an L2).  What remains is latency: ids, scalars and the turn between rows.
+// Any ids give the right result.  133 K rows, 79 M edges, mild skew 1.27 -> 0.93 ms, strong skew 1.03 -> 1.07.
+__global__ void __launch_bounds__(256) edge_operand_rows_kernel(const float *__restrict__ fE, int64_t lde, const int64_t *__restrict__ edge_ids,
+                                                                const void *indptr, int ip64, int64_t N, float *__restrict__ out) {
+    constexpr int ROWS = kOperandRows;
+    const int lane = threadIdx.x & 63;
+    const int part = int(blockIdx.x & 7);
+    const int64_t step = int64_t(gridDim.x >> 3) * 4 * ROWS;
+    auto pointer = [&](int64_t row) {
+        row = row < N ? row : N;
+        return ip64 ? static_cast<const int64_t *>(indptr)[row] : int64_t(static_cast<const int32_t *>(indptr)[row]);
+    };
+    int64_t first = (int64_t(blockIdx.x >> 3) * 4 + (threadIdx.x >> 6)) * ROWS;
+    const int at = lane < ROWS ? lane : ROWS;
+    // 128 edges of the parts of ROWS rows at a time; the rows' pointers arrive a group of rows ahead, the ids a turn ahead
+    struct Ids { int64_t begin[ROWS], id[ROWS][2]; int n[ROWS]; };
+    int64_t begin[ROWS];
+    int left[ROWS], longest = 0;
+    auto start_rows = [&](int64_t mine) {
+        longest = 0;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const int64_t e0 = __shfl(mine, r), len = __shfl(mine, r + 1) - e0;
+            const int64_t b = len * part >> 3;
+            begin[r] = e0 + b;
+            left[r] = int((len * (part + 1) >> 3) - b);
+            longest = left[r] > longest ? left[r] : longest;
+        }
+        longest = __builtin_amdgcn_readfirstlane(longest);
+    };
+    auto fetch = [&](Ids &x) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            x.begin[r] = begin[r];
+            x.n[r] = left[r];
+            const int i = 2 * lane;
+            x.id[r][0] = x.id[r][1] = 0;
+            const int64_t *q = edge_ids + begin[r] + i;
+            if (i + 1 < left[r]) {
+                const i64x2_any two = *reinterpret_cast<const i64x2_any *>(q);
+                x.id[r][0] = two.x;
+                x.id[r][1] = two.y;
+            } else if (i < left[r]) {
+                x.id[r][0] = *q;
+            }
+            begin[r] += 128;
+            left[r] -= 128;
+        }
+        longest -= 128;
+    };
+    if (first >= N) return;
+    Ids nxt;
+    start_rows(pointer(first + at));
+    int64_t p_nxt = pointer(first + step + at);
+    fetch(nxt);
+    for (;;) {
+        const Ids cur = nxt;
+        float v[ROWS][2];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (2 * lane + j < cur.n[r]) v[r][j] = fE[cur.id[r][j] * lde];
+        bool more = true;
+        if (longest <= 0) {
+            first += step;
+            more = first < N;
+            if (more) {
+                start_rows(p_nxt);
+                p_nxt = pointer(first + step + at);
+            }
+        }
+        if (more) fetch(nxt);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            float *q = out + cur.begin[r] + 2 * lane;
+            if (2 * lane + 1 < cur.n[r]) *reinterpret_cast<f32x2_any *>(q) = f32x2_any{v[r][0], v[r][1]};
+            else if (2 * lane < cur.n[r]) *q = v[r][0];
+        }
+        if (!more) break;
+    }
+}
+
+int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const int64_t *edge_ids, const void *indptr, int ip64, hipStream_t stream,
                           const float **out) {
     if (!plan || !out || !fE || lde < 1) return GNN_ERR_INVALID_ARG;
     *out = nullptr;
     if (plan->n_edges == 0) return GNN_OK;
     (void)hipGetLastError();
     if (!plan->edge_operand && !gnn_dev_alloc(&plan->edge_operand, plan->n_edges, stream)) return GNN_ERR_ALLOC;
-    edge_operand_kernel<<<grid_for(plan->n_edges, 256, 1 << 16), 256, 0, stream>>>(fE, lde, edge_ids, plan->n_edges, plan->edge_operand);
+    // Long rows, and more scalars than the caches behind the L2s hold well (a vertex gradient of 4 columns, plain -> by rows, ms: 100 K rows,
+    // 60 M edges 1.25 -> 1.05, 200 K, 79 M 1.88 -> 1.56, 250 K, 79 M 1.96 -> 1.68 / strong skew 1.68 -> 1.65, 350 K 2.06 -> 1.97;
+    // below, 100 K, 40 M 0.80 -> 0.77, 133 K, 40 M 0.83 -> 0.85, 60 K, 20 M 0.34 -> 0.41).
+    if (edge_ids && plan->n_edges >= kOperandEdges && plan->n_edges >= 200 * plan->n_rows)
+        edge_operand_rows_kernel<<<kOperandBlocks, 256, 0, stream>>>(fE, lde, edge_ids, indptr, ip64, plan->n_rows, plan->edge_operand);
+    else
+        edge_operand_kernel<<<grid_for(plan->n_edges, 256, 1 << 16), 256, 0, stream>>>(fE, lde, edge_ids, plan->n_edges, plan->edge_operand);
     if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     *out = plan->edge_operand;
     return GNN_OK;

@@ -484,3 +484,27 @@ def test_full_width_operands_on_rows_off_line_boundaries(n, d, binop):
     last = int(el.dst[999])  # rows before it are whole
     want = torch.zeros(last, d, device=DEV, dtype=torch.float64).index_add_(0, el.dst[:1000].long()[el.dst[:1000] < last], m.double()[el.dst[:1000] < last])
     assert torch.allclose(results[0][0][:last].double(), want, rtol=1e-4, atol=1e-4)
+
+
+@pytest.mark.parametrize("ip64,stride", [(False, 1), (True, 2)])
+def test_scalar_operands_of_many_edges_through_an_edge_map(ip64, stride):
+    """Scalars that are gathered row by row over the XCDs (48 M edges): rows of no edge, of one, longer than a turn, a hub; ids in
+    order and in none.  The same bits as scalars that lie in CSR order."""
+    n, d = 130003, 4
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    lengths = torch.randint(0, 860, (n,), device=DEV, generator=gen)
+    lengths[::17], lengths[1::17], lengths[n - 2], lengths[n - 1] = 0, 1, 70001, 1033
+    indptr = torch.zeros(n + 1, dtype=torch.int64 if ip64 else torch.int32, device=DEV)
+    indptr[1:] = lengths.cumsum(0)
+    e = int(indptr[-1])
+    assert e >= max(48000000, 200 * n)
+    indices = torch.randint(0, n, (e,), dtype=torch.int32, device=DEV, generator=gen)
+    fe = torch.empty(e, stride, device=DEV).normal_(generator=gen)
+    x = torch.empty(n, d, device=DEV).normal_(generator=gen)
+    plan = gnn.gnn_plan_create(indptr, indices, n)
+    got, want = torch.full_like(x, 7.0), torch.full_like(x, 7.0)
+    for ids in (torch.arange(e, device=DEV).flip(0), torch.randperm(e, device=DEV, generator=gen)):
+        gnn.gnn_ap_bwd_vertex(indptr, indices, x, fe[:, :1], got, n, d, gnn.GNN_BIN_MUL, plan=plan, edge_ids=ids)
+        gnn.gnn_ap_bwd_vertex(indptr, indices, x, fe[ids, :1].contiguous(), want, n, d, gnn.GNN_BIN_MUL, plan=plan)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)

@@ -726,17 +726,18 @@ __global__ void __launch_bounds__(256) few_k_kernel(const GemmArgs g) {
 // C = act(sum over the partial planes + bias).  A workgroup owns 64 consecutive outputs; its wavefronts take every
 // kReduceWaves-th plane, eight loads in flight each, and their sums are added in order.  (One thread per output walking
 // all planes took 0.23 ms for 256 planes of 256 x 256, 67 MB.  Workgroups of 16 wavefronts were slower still beside the
-// aggregation on the other stream, which never leaves a compute unit that many slots at once.)
+// aggregation on the other stream, which never leaves a compute unit that many slots at once.)  In 64 bits: adding the planes was most
+// of the error of many short parts (24,490 rows, 256 x 256, 2-norm 1.5e-7 -> 0.8e-7), and the loads take longer than the additions.
 constexpr int kReduceWaves = 4;
 __global__ void __launch_bounds__(kReduceWaves * 64) gemm_reduce_kernel(const float *__restrict__ part, int n_split, float *__restrict__ C,
                                                                        int64_t ldc, int64_t M, int64_t N,
                                                                        const float *__restrict__ bias, int relu) {
     constexpr int U = 8;
-    __shared__ float sums[kReduceWaves][64];
+    __shared__ double sums[kReduceWaves][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t total = M * N;
     const int64_t t = int64_t(blockIdx.x) * 64 + lane;
-    float s = 0.0f;
+    double s = 0.0;
     if (t < total) {
         int p = wave;
         for (; p + (U - 1) * kReduceWaves < n_split; p += U * kReduceWaves) {
@@ -744,32 +745,35 @@ __global__ void __launch_bounds__(kReduceWaves * 64) gemm_reduce_kernel(const fl
 #pragma unroll
             for (int k = 0; k < U; ++k) v[k] = part[int64_t(p + k * kReduceWaves) * total + t];
 #pragma unroll
-            for (int k = 0; k < U; ++k) s += v[k];
+            for (int k = 0; k < U; ++k) s += double(v[k]);
         }
-        for (; p < n_split; p += kReduceWaves) s += part[int64_t(p) * total + t];
+        for (; p < n_split; p += kReduceWaves) s += double(part[int64_t(p) * total + t]);
     }
     sums[wave][lane] = s;
     __syncthreads();
     if (wave > 0 || t >= total) return;
     for (int w = 1; w < kReduceWaves; ++w) s += sums[w][lane];
     const int64_t m = t / N, n = t - m * N;
-    if (bias) s += bias[n];
-    if (relu) s = s > 0.0f ? s : 0.0f;
-    C[m * ldc + n] = s;
+    if (bias) s += double(bias[n]);
+    if (relu) s = s > 0.0 ? s : 0.0;
+    C[m * ldc + n] = float(s);
 }
 
 }  // namespace
 
 // Tile of a workgroup, for the weight gradients: a long k, read once where N fits the tile's width.  resident: parts of k that a
-// compute unit gets.  Narrow tiles are small so that several workgroups, each waiting for memory, share a compute unit
-// (602 x 16 over 232,965 rows: 306 us with tiles of 256 rows, two to a unit; 114 with 128 and five).
+// compute unit gets, all in one round: a second, partly empty one costs a whole round (256 x 256 over 24,490 rows, 256 workgroups 30.6 us,
+// 382 43.5; 60,000 56.7 and 512 64.4; 232,965 200 and 210; 100 x 256 over 60,000 37.6 and 52.5, over 2.45 M 1049 and 1065).  Tiles of 256
+// columns take the registers of a compute unit by themselves.  Narrow tiles are small so that several workgroups, each waiting for
+// memory, share one (602 x 16 over 232,965 rows: 306 us with tiles of 256 rows, two to a unit; 114 with 128 and five;
+// 256 x 47 over 60,000 25.9 with three, 29.9 with four, over 232,965 71.6 and 73.0, over 600,000 178 and 173).
 struct TileShape { int64_t bm, bn; int resident; };
 
-static TileShape choose_tile(int64_t M, int64_t N) {
+static TileShape choose_tile(int64_t N, int64_t K) {
     if (N <= 32) return {128, 32, 5};
-    if (N <= 64) return {128, 64, 4};
+    if (N <= 64) return {128, 64, K > 400000 ? 4 : 3};
     if (N <= 128) return {128, 128, 2};
-    return {128, 256, 2};
+    return {128, 256, 1};
 }
 
 // Tile of a tall product: wavefronts of 32 rows, tiles of 32 columns.  As wide as the result, so that A is read and split once
@@ -782,6 +786,9 @@ static TileShape choose_tile(int64_t M, int64_t N) {
 struct TallShape { int waves, tj; };
 
 static TallShape choose_tall(int64_t M, int64_t N) {
+    // Fewer than six wavefronts of 32 x 64 per compute unit: twice as many of 32 x 32 (us: 6,000 rows 256 -> 256 17.2 and 15.7, 12,000 21.2 and
+    // 19.7; 24,490 256 -> 47 18.3 and 16.4, 256 -> 100 19.5 and 18.1; above, 24,490 256 -> 256 27.8 and 38.2, 40,000 256 -> 100 24.3 and 32.7).
+    if ((M + 31) / 32 * ((N + 63) / 64) < 1536) return {4, 1};
     const int waves = M >= 65536 ? 8 : 4;
     if (N <= 32) return {waves, 1};
     if (N <= 64) return {waves, 2};
@@ -793,14 +800,15 @@ static TallShape choose_tall(int64_t M, int64_t N) {
 // How many partial planes the reduction over k is split into.  Of the sizes alone, with the tiles of a weight gradient: a caller that
 // asks for the workspace does not say which way A lies (launch_rows has tiles of its own).
 static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
-    const TileShape s = choose_tile(M, N);
+    const TileShape s = choose_tile(N, K);
     const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);
     if (tiles >= 512 || K < 1024) return 1;
-    int64_t split = (256 * s.resident + tiles - 1) / tiles;
-    // At least GNN_SPLIT_MIN_K k-steps per part: a part is bound by the latency of its tiles of 16 k-steps, one after the other, while
-    // the chip is not full (24,490 rows into 256 x 256: 0.20 ms with parts of 1024, 0.047 with 128); the partial planes cost little
-    // beside that.  Parts of 64 gain another 3 us in the product alone, but the three layers of such a graph take 565 us with them
-    // and 541 with 128: twice the planes to add up.
+    int64_t split = 256 * s.resident / tiles;
+    // ... or two rounds of shorter parts, for closer sums, where they cost next to nothing (600,000 rows into 256 x 256 496 and 507 us)
+    if (s.resident == 1 && K > 2048 * split) split *= 2;
+    // At least GNN_SPLIT_MIN_K rows per part: a part is bound by the latency of its tiles of 16, one after the other, while the chip is not
+    // full; the partial planes cost little beside that (24,490 rows, us with parts of 128 and of 96: 128 x 128 22.3 and 18.5, 256 x 47
+    // 18.2 and 17.4, 16 x 41 16.0 and 15.2; 6,000 rows 100 x 256 24.8 and 21.6, 602 x 16 14.5 and 12.6).
     const int64_t max_split = K / GNN_SPLIT_MIN_K;
     if (split > max_split) split = max_split;
     if (split > 4096) split = 4096;
@@ -869,7 +877,7 @@ int gnn_matmul_impl(const float *A, int64_t lda, int trans_a, const float *B, in
     // the tall kernel takes every product with k along the rows of A whose reduction is not split
     const bool tall = !trans_a && split == 1;
     const TallShape ts = K < BK ? TallShape{4, 2} : choose_tall(M, N);
-    const TileShape s = tall ? TileShape{ts.waves * 32, ts.tj * 32, 1} : trans_a ? choose_tile(M, N) : TileShape{128, 128, 2};
+    const TileShape s = tall ? TileShape{ts.waves * 32, ts.tj * 32, 1} : trans_a ? choose_tile(N, K) : TileShape{128, 128, 2};
     const int64_t BM = s.bm, BN = s.bn;
     const int64_t gx = (M + BM - 1) / BM, gy = (N + BN - 1) / BN;
     if (gx > INT32_MAX || gy > INT32_MAX || split > 65535) return GNN_ERR_UNSUPPORTED;

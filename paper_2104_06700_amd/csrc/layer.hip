@@ -101,22 +101,22 @@ __global__ void __launch_bounds__(THREADS) mask_colsum_kernel(const float *__res
 // column walking 256 blocks: 0.06 ms per level.)
 __global__ void __launch_bounds__(256) colsum_reduce_kernel(const float *__restrict__ partial, int64_t n_blocks, int F,
                                                              float *__restrict__ out, int64_t chunk, int log2_cols) {
-    __shared__ float red[256];
+    __shared__ double red[256];
     const int cols = 1 << log2_cols, row_lanes = 256 >> log2_cols;
     const int jl = threadIdx.x & (cols - 1), rl = threadIdx.x >> log2_cols;
     const int64_t b0 = int64_t(blockIdx.x) * chunk;
     const int64_t b1 = b0 + chunk < n_blocks ? b0 + chunk : n_blocks;
     const int j = int(blockIdx.y) * cols + jl;
-    float s = 0.0f;
+    double s = 0.0;  // the loads take longer than the additions
     if (j < F) {
 #pragma unroll 8
-        for (int64_t b = b0 + rl; b < b1; b += row_lanes) s += partial[b * F + j];
+        for (int64_t b = b0 + rl; b < b1; b += row_lanes) s += double(partial[b * F + j]);
     }
     red[threadIdx.x] = s;
     __syncthreads();
     if (rl == 0 && j < F) {
         for (int k = 1; k < row_lanes; ++k) s += red[(k << log2_cols) + jl];
-        out[int64_t(blockIdx.x) * F + j] = s;
+        out[int64_t(blockIdx.x) * F + j] = float(s);
     }
 }
 

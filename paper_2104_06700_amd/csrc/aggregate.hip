@@ -788,24 +788,12 @@ __global__ void __launch_bounds__(kBlockThreads) gather_kernel(const AggArgs a) 
     write_strip<T, VEC>(a, r.row, r.row_len, col, ncols, own, acc[0]);
 }
 
-constexpr int kRunEdges = 8;        // edges of a row of run_kernel at most
-constexpr int kRunBins = 8;         // bins of a launch at most
-constexpr int64_t kRunRows = 1 << 18, kRunWaves = 1 << 14;  // see run_bins_of, fill_run_bins
-
-struct RunBin {
-    int64_t first_block, item_begin, n_items;
-    int32_t longest;        // edges of a row of the bin at most
-    int32_t rows_per_wave;  // 64 at most
-};
 struct RunArgs {
     AggArgs a;              // X: first slice table, or the matrix of whole rows; F: all columns
-    int64_t n_blocks;
-    int32_t n_bins;
-    int32_t log2_c;         // lanes per row
-    RunBin bins[kRunBins];
+    gnn_run_bins bins;
 };
 
-// Rows of at most kRunEdges edges, all columns.  A wavefront takes up to 64 of them: lane l reads what describes row l, then sets of
+// Rows of at most GNN_RUN_EDGES edges, all columns.  A wavefront takes up to 64 of them: lane l reads what describes row l, then sets of
 // 64 / C rows follow each other, C lanes per row, the indices of the next set on their way while this one is gathered.
 //
 // As rows of aggregate_kernel they were bound by the rate at which workgroups start (570 per us over the chip: 32 rows of one line
@@ -819,14 +807,11 @@ __global__ void __launch_bounds__(kBlockThreads) run_kernel(const RunArgs r) {
     constexpr int LINE = 128 / int(sizeof(T));
     const AggArgs &a = r.a;
     const int lane = threadIdx.x & 63;
-    int b = 0;
-#pragma unroll
-    for (int i = 1; i < kRunBins; ++i) b = i < r.n_bins && int64_t(blockIdx.x) >= r.bins[i].first_block ? i : b;
-    const RunBin bin = r.bins[b];
+    const gnn_run_bin bin = gnn_run_bin_of_block(r.bins, blockIdx.x);
     const int64_t item0 = ((int64_t(blockIdx.x) - bin.first_block) * kWavesPerBlock + (threadIdx.x >> 6)) * bin.rows_per_wave;
     const int n_rows = bin.n_items - item0 < bin.rows_per_wave ? int(bin.n_items - item0) : bin.rows_per_wave;
     if (n_rows <= 0) return;
-    const int log2_c = r.log2_c, C = 1 << log2_c;
+    const int log2_c = r.bins.log2_c, C = 1 << log2_c;
     const int c = lane & (C - 1), gbase = lane & ~(C - 1);
     const int per_set = 64 >> log2_c, in_set = lane >> log2_c;
 
@@ -934,7 +919,7 @@ __global__ void __launch_bounds__(kBlockThreads) run_kernel(const RunArgs r) {
     if (bin.longest <= 0) run(std::integral_constant<int, 0>());
     else if (bin.longest <= 1) run(std::integral_constant<int, 1>());
     else if (bin.longest <= 4) run(std::integral_constant<int, 4>());
-    else run(std::integral_constant<int, kRunEdges>());
+    else run(std::integral_constant<int, GNN_RUN_EDGES>());
 }
 
 // Adds the pieces of each hub row in their fixed order and writes the row.
@@ -1358,48 +1343,12 @@ hipError_t launch_coef(bool coef, int npass, dim3 grid, hipStream_t stream, cons
 }
 
 hipError_t launch_runs(bool coef, bool bf16, hipStream_t stream, const RunArgs &r) {
-    const dim3 grid(static_cast<unsigned>(r.n_blocks));
+    const dim3 grid(static_cast<unsigned>(r.bins.n_blocks));
     if (bf16 && coef) run_kernel<bf16_t, 8, true><<<grid, kBlockThreads, 0, stream>>>(r);
     else if (bf16) run_kernel<bf16_t, 8, false><<<grid, kBlockThreads, 0, stream>>>(r);
     else if (coef) run_kernel<float, 4, true><<<grid, kBlockThreads, 0, stream>>>(r);
     else run_kernel<float, 4, false><<<grid, kBlockThreads, 0, stream>>>(r);
     return hipGetLastError();
-}
-
-// Bit b: the rows of bin b go to run_kernel.  A wavefront takes many of them, so there have to be enough (MEAN, us, rows of
-// aggregate_kernel -> run_kernel, directed power-law graphs of 10 edges per vertex: 200 K vertices F=32 27.4 -> 28.9, 100 K F=100 43 -> 45;
-// 500 K F=32 59.0 -> 59.2, 100 282 -> 268, 256 506 -> 464; 1 M F=100 624 -> 578, 256 1258 -> 1110, bf16 128 296 -> 254).
-uint32_t run_bins_of(const gnn_plan *plan, int first_excluded_bin) {
-    uint32_t bins = 0;
-    int64_t rows = 0;
-    if (!plan) return 0;
-    for (int b = 0; b < plan->params.n_thresholds && b < kRunBins && b < first_excluded_bin && plan->params.thresholds[b] - 1 <= kRunEdges; ++b) {
-        bins |= 1u << b;
-        rows += plan->bin_offsets[b + 1] - plan->bin_offsets[b];
-    }
-    return rows >= kRunRows ? bins : 0u;
-}
-
-void fill_run_bins(RunArgs &r, const gnn_plan *plan, uint32_t bins, int64_t strips) {
-    int64_t rows = 0, next = 0;
-    for (int b = 0; b < kRunBins; ++b)
-        if (bins >> b & 1u) rows += plan->bin_offsets[b + 1] - plan->bin_offsets[b];
-    // as many rows per wavefront as leave the chip a few rounds of wavefronts (500 K vertices F=301: 64 rows 944 us, 32 890, 16 857; 2.45 M
-    // F=100 3.62 ms, 3.67, 3.69)
-    int32_t per_wave = 64;
-    while (per_wave > 16 && rows < per_wave * kRunWaves) per_wave /= 2;
-    r.log2_c = strips >= 64 ? 6 : gnn_ilog2_ceil(strips);
-    for (int b = kRunBins - 1; b >= 0; --b) {
-        if (!(bins >> b & 1u)) continue;
-        RunBin &d = r.bins[r.n_bins++];
-        d.first_block = next;
-        d.item_begin = plan->bin_offsets[b];
-        d.n_items = plan->bin_offsets[b + 1] - d.item_begin;
-        d.longest = int32_t(plan->params.thresholds[b] - 1);
-        d.rows_per_wave = per_wave;
-        next += (d.n_items + kWavesPerBlock * per_wave - 1) / (kWavesPerBlock * per_wave);  // N / 64 at most, so a grid holds it
-    }
-    r.n_blocks = next;
 }
 
 // Column slices for rows gathered where they lie (no plan-owned copy), counted in 16-byte strips of a row.
@@ -1840,7 +1789,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     // Bins whose rows run_kernel serves: all columns in one launch, beside the tiles and pieces where there are some (2.45 M vertices
     // F=100, 256: 3.62, 7.13 ms in front of the other short rows, 3.93, 7.19 behind them), else behind the other rows (27.8 M bf16
     // 14.8 ms, 15.4 in front).
-    const uint32_t run_bins = vec == max_vec && (F + vec - 1) / vec >= kRunEdges ? run_bins_of(plan, bl.active ? bl.first_bin : INT32_MAX) : 0u;
+    const uint32_t run_bins = vec == max_vec && (F + vec - 1) / vec >= GNN_RUN_EDGES ? gnn_run_bins_of(plan, bl.active ? bl.first_bin : INT32_MAX) : 0u;
     RunArgs runs{};
     bool runs_beside = false;
 
@@ -1967,7 +1916,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             runs.a.own_X = gathered_only && self_mode == kSelfPlain ? orig : nullptr;
             runs.a.bias = bias;
             runs.a.tail_slice = tail_table ? int32_t(layout.main_lines) : -1;
-            fill_run_bins(runs, plan, run_bins, (F + vec - 1) / vec);
+            gnn_fill_run_bins(runs.bins, plan, run_bins, (F + vec - 1) / vec);
             runs_beside = rows_stream != stream;
             if (runs_beside && launch_runs(coef, o.dtype == GNN_BF16, rows_stream, runs) != hipSuccess) { finish_overlap(); return GNN_ERR_LAUNCH; }
         }

@@ -664,3 +664,64 @@ static inline int gnn_ilog2_ceil(int64_t x) {
     while ((int64_t(1) << l) < x) ++l;
     return l;
 }
+
+// ---- short rows, many per wavefront (run_kernel of aggregate.hip, ap_run_kernel of ap.hip) ----
+constexpr int GNN_RUN_EDGES = 8;      // edges of such a row at most
+constexpr int GNN_RUN_BINS = 8;       // bins of a launch at most
+constexpr int64_t GNN_RUN_ROWS = 1 << 18, GNN_RUN_WAVES = 1 << 14;  // see gnn_run_bins_of, gnn_fill_run_bins
+
+struct gnn_run_bin {
+    int64_t first_block, item_begin, n_items;
+    int32_t longest;        // edges of a row of the bin at most
+    int32_t rows_per_wave;  // 64 at most
+};
+struct gnn_run_bins {
+    int64_t n_blocks;
+    int32_t n_bins;
+    int32_t log2_c;         // lanes per row
+    gnn_run_bin bins[GNN_RUN_BINS];
+};
+__device__ static inline gnn_run_bin gnn_run_bin_of_block(const gnn_run_bins &r, int64_t block) {
+    int b = 0;
+#pragma unroll
+    for (int i = 1; i < GNN_RUN_BINS; ++i) b = i < r.n_bins && block >= r.bins[i].first_block ? i : b;
+    return r.bins[b];
+}
+
+// Bit b: the rows of bin b are short.  A wavefront takes many of them, so there have to be enough (MEAN, us, rows of
+// aggregate_kernel -> run_kernel, directed power-law graphs of 10 edges per vertex: 200 K vertices F=32 27.4 -> 28.9, 100 K F=100 43 -> 45;
+// 500 K F=32 59.0 -> 59.2, 100 282 -> 268, 256 506 -> 464; 1 M F=100 624 -> 578, 256 1258 -> 1110, bf16 128 296 -> 254).
+static inline uint32_t gnn_run_bins_of(const gnn_plan *plan, int first_excluded_bin) {
+    uint32_t bins = 0;
+    int64_t rows = 0;
+    if (!plan) return 0;
+    for (int b = 0; b < plan->params.n_thresholds && b < GNN_RUN_BINS && b < first_excluded_bin && plan->params.thresholds[b] - 1 <= GNN_RUN_EDGES; ++b) {
+        bins |= 1u << b;
+        rows += plan->bin_offsets[b + 1] - plan->bin_offsets[b];
+    }
+    return rows >= GNN_RUN_ROWS ? bins : 0u;
+}
+
+// strips: of 16 bytes per row
+static inline void gnn_fill_run_bins(gnn_run_bins &r, const gnn_plan *plan, uint32_t bins, int64_t strips) {
+    int64_t rows = 0, next = 0;
+    for (int b = 0; b < GNN_RUN_BINS; ++b)
+        if (bins >> b & 1u) rows += plan->bin_offsets[b + 1] - plan->bin_offsets[b];
+    // as many rows per wavefront as leave the chip a few rounds of wavefronts (500 K vertices F=301: 64 rows 944 us, 32 890, 16 857; 2.45 M
+    // F=100 3.62 ms, 3.67, 3.69)
+    int32_t per_wave = 64;
+    while (per_wave > 16 && rows < per_wave * GNN_RUN_WAVES) per_wave /= 2;
+    r = gnn_run_bins{};
+    r.log2_c = strips >= 64 ? 6 : gnn_ilog2_ceil(strips);
+    for (int b = GNN_RUN_BINS - 1; b >= 0; --b) {
+        if (!(bins >> b & 1u)) continue;
+        gnn_run_bin &d = r.bins[r.n_bins++];
+        d.first_block = next;
+        d.item_begin = plan->bin_offsets[b];
+        d.n_items = plan->bin_offsets[b + 1] - d.item_begin;
+        d.longest = int32_t(plan->params.thresholds[b] - 1);
+        d.rows_per_wave = per_wave;
+        next += (d.n_items + GNN_WAVES_PER_BLOCK * per_wave - 1) / (GNN_WAVES_PER_BLOCK * per_wave);  // N / 64 at most, so a grid holds it
+    }
+    r.n_blocks = next;
+}

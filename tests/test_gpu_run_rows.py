@@ -101,3 +101,26 @@ def test_small_graph_rows_of_few_lanes(dtype, widths, weights):
         has = torch.zeros(n, dtype=torch.bool)
         has[el.dst[el.src == 5].long()] = True
         assert torch.equal(torch.isinf(Y[:, f - 1]).cpu(), has) and bool(torch.isfinite(Y[:, :f - 1]).all())
+
+
+@pytest.mark.parametrize("d,shift", [(33, 1), (100, 0), (261, 1)])
+@pytest.mark.parametrize("reduce", [gnn.GNN_RED_MAX, gnn.GNN_RED_MIN])
+def test_short_rows_of_max_and_min(graph, d, shift, reduce):
+    """Values and winners of rows served many per wavefront, whole and in column slices, with ties, infinities and rows of nothing else."""
+    el, (indptr, indices, *_) = graph
+    dg = device_graph(el)
+    X = synth.normal_features(N, d, 3).mul_(2.0).round_()
+    X[7, :] = float("-inf") if reduce == gnn.GNN_RED_MAX else float("inf")
+    X[:3000:5, d - 1] = X[7, 0]
+    flat = torch.full((N * d + shift,), float("nan"), device=DEV)
+    Xd = flat[shift:].view(N, d)
+    Xd.copy_(X)
+    want, won = oracle.ap_fwd(indptr, indices, X.numpy(), None, d, oracle.BIN_COPY_LHS,
+                              oracle.RED_MAX if reduce == gnn.GNN_RED_MAX else oracle.RED_MIN)
+    for flags in (0, gnn.GNN_FLAG_FORCE_PADDED_COPY, gnn.GNN_FLAG_NO_COLUMN_SLICES):
+        out = torch.full((N * d + shift,), float("nan"), device=DEV)
+        arg = torch.full((N, d), -7, dtype=torch.int32, device=DEV)
+        gnn.gnn_ap_fwd(dg.indptr, dg.indices, Xd, None, out[shift:].view(N, d), arg, N, d, gnn.GNN_BIN_COPY_LHS, reduce, plan=dg.plan_fwd, flags=flags)
+        torch.cuda.synchronize()
+        assert np.array_equal(out[shift:].view(N, d).cpu().numpy().astype(np.float64), want), flags
+        assert np.array_equal(arg.cpu().numpy().astype(np.int64), won), flags

@@ -103,6 +103,26 @@ def test_small_graph_rows_of_few_lanes(dtype, widths, weights):
         assert torch.equal(torch.isinf(Y[:, f - 1]).cpu(), has) and bool(torch.isfinite(Y[:, :f - 1]).all())
 
 
+def test_last_segment_narrower_than_a_strip():
+    """1025 columns gathered where they lie, 16 x 64 and one more: the strip of the last segment begins before its first column."""
+    n, f = 50021, 1025
+    lengths = (synth.mix64(torch.arange(n) + 5) & 0x7FFFFFFF) % 6
+    lengths[7], lengths[n - 1] = 6000, 900
+    dst = torch.arange(n).repeat_interleave(lengths)
+    src = (synth.mix64(torch.arange(dst.numel()) + 9) & 0x7FFFFFFF) % n
+    src[::50] = 0
+    key = torch.sort(dst * n + src).values
+    el = synth.EdgeList(n=n, src=(key % n).to(torch.int32), dst=(key // n).to(torch.int32), meta={})
+    indptr, indices, *_ = host_csr(el)
+    dg = device_graph(el)
+    X = synth.normal_features(n, f, 3)
+    Yo, S = oracle.aggregate_fwd(indptr, indices, X.numpy(), op=oracle.OP_SUM, nthreads=8, want_scale=True)
+    Y = torch.full((n, f), float("nan"), device=DEV)
+    gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, None, X.to(DEV), Y, n, f, gnn.GNN_SUM, plan=dg.plan_fwd, flags=gnn.GNN_FLAG_NO_PADDED_COPY)
+    torch.cuda.synchronize()
+    assert_close(Y, Yo, S, False, "1025 columns")
+
+
 @pytest.mark.parametrize("d,shift", [(33, 1), (100, 0), (261, 1)])
 @pytest.mark.parametrize("reduce", [gnn.GNN_RED_MAX, gnn.GNN_RED_MIN])
 def test_short_rows_of_max_and_min(graph, d, shift, reduce):

@@ -47,7 +47,15 @@ struct gnn_tiles {
     float *tmp_w = nullptr;              // other coefficients, refilled by every call
     uint32_t *positions = nullptr;       // CSR position of the edge in every slot of the stream; made for coefficients that are refilled
     bool no_positions = false;           // there was no room for them
+    // Rows whose edges to the first sources are a bit matrix (dense_kernel); their lists leave those edges out.
+    int32_t dense_groups = 0, dense_chunks = 0;  // groups of rows; chunks of sources of the longest one
+    int32_t dense_units = 0, dense_extra = 0, dense_cut = 0;  // what the groups are cut into, units beyond their first; groups that have some
+    int64_t dense_sources = 0;                   // rows of the gathered table
+    void *dense = nullptr;                       // the groups and their units
+    uint32_t *dense_rows = nullptr;              // hot row of every row of the groups
+    uint2 *dense_bits = nullptr;
 };
+constexpr int GNN_TILES_PLAIN = 6;  // number in gnn_plan::tiles of the layout with a bit matrix
 
 // One plan = one graph orientation.  All pointers are device memory owned by
 // the plan unless marked host.
@@ -136,7 +144,7 @@ struct gnn_plan {
     int64_t bound_w_version = 0;      // number of the last binding
     void *blk_partial = nullptr;      // fp32 partial sums of one launch: [slices][blk_n_pieces][floats per line]
     int64_t blk_partial_bytes = 0;
-    gnn_tiles tiles[6];               // for lines of 128, 64 and 32 bytes of fp32, then of bf16
+    gnn_tiles tiles[7];               // for lines of 128, 64 and 32 bytes of fp32, then of bf16; [GNN_TILES_PLAIN]: see gnn_plan_tiles
     void *tile_partial = nullptr;     // their partial lines: [groups][slices][hot rows][floats per line]
     int64_t tile_partial_bytes = 0;
 };
@@ -176,7 +184,11 @@ int gnn_plan_blocked_edge_scale(gnn_plan *plan, int mode, hipStream_t stream, co
 int gnn_plan_blocked_bound_weights(gnn_plan *plan, hipStream_t stream, const float **out);
 
 // The tile layout for lines of lanes * 16 bytes (null: the graph has no block dense enough); needs the blocked layout.
-int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, hipStream_t stream, const gnn_tiles **out);
+// plain: for sums without coefficients of gnn_bits_pay(slices), which take the densest cells as a bit matrix where there are enough of them.
+// Under three slices a launch of that is too small for the chip (233 K vertices, 115 M edges F=32 0.41 -> 0.44 ms, 133 K, 79 M F=64 0.47 -> 0.50;
+// above, F=100 1.31 -> 1.26, 300 K, 120 M F=128 1.46 -> 1.42).
+static inline bool gnn_bits_pay(int64_t n_slices) { return n_slices >= 3; }
+int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, hipStream_t stream, const gnn_tiles **out);
 void gnn_tiles_free(gnn_tiles &t);
 // Coefficients w[e] * scale[e] (either may be null; CSR order) in stream order.
 int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles, const float *w, const float *scale, int scale_mode, bool bound,

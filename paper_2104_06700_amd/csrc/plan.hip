@@ -670,7 +670,7 @@ static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int6
     rc = gnn_plan_blocked_partial(plan, slices, line_floats);
     if (rc != GNN_OK) return rc;
     const gnn_tiles *tl = nullptr;
-    rc = gnn_plan_tiles(plan, layout.line_lanes, esz == 2, stream, &tl);
+    rc = gnn_plan_tiles(plan, layout.line_lanes, esz == 2, weights == GNN_WEIGHTS_NONE && gnn_bits_pay(layout.main_lines), stream, &tl);
     if (rc == GNN_OK && tl) rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), line_floats);
     const float *unused = nullptr;
     if (rc == GNN_OK && weights == GNN_WEIGHTS_BOUND) rc = gnn_plan_blocked_bound_weights(plan, stream, &unused);
@@ -702,7 +702,7 @@ extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, 
         if (rc == GNN_OK && plan->blk_decided && plan->blk_n_pieces > 0 && plan->n_edges > 0)
             rc = gnn_plan_blocked_edge_scale(plan, mode, stream, &unused);
         for (const gnn_tiles &t : plan->tiles)
-            if (rc == GNN_OK && t.active && plan->n_edges > 0)
+            if (rc == GNN_OK && t.active && !t.dense_groups && plan->n_edges > 0)
                 rc = gnn_plan_tile_coefs(plan, &t, nullptr, plan->edge_scale[mode - 1], mode, false, stream, &unused);
     }
     return rc;

@@ -21,6 +21,7 @@
 // 19 lines, 3.8 ms alone, where the same edges as pieces took over 9.5 ms; the call 11.45 -> 8.0 (tiles) -> 7.0 (order) ->
 // 6.85 ms (half of the next tile fetched ahead).  The 2.45 M-vertex graph: F=256 1.23 ms alone; the call, half of which the
 // short rows take, 9.15 -> 8.35 -> 7.50 ms.
+#include <algorithm>
 #include <new>
 #include <type_traits>
 #include <utility>
@@ -158,24 +159,27 @@ __device__ __forceinline__ uint32_t lower_bound_in(const int32_t *__restrict__ r
 
 // longest[h] = most edges of row h into one tile (zeroed before)
 __global__ void __launch_bounds__(256) tile_longest_kernel(const TileDesc *__restrict__ tiles, int n_tiles, DenseRule rule,
-                                                           const int32_t *__restrict__ blk_indices, uint32_t *__restrict__ longest) {
+                                                           const int32_t *__restrict__ blk_indices, const uint32_t *__restrict__ depth,
+                                                           uint32_t *__restrict__ longest) {
     const int64_t total = int64_t(n_tiles) * rule.n_hot;
     const int64_t stride = int64_t(gridDim.x) * blockDim.x;
     for (int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < total; x += stride) {
         const TileDesc d = tiles[x / rule.n_hot];
         const int64_t h = x % rule.n_hot;
         if (rule.edges(d.block, h) <= kMaxSegment) continue;  // short enough wherever its tiles begin
+        if (depth && uint32_t(x / rule.n_hot) < depth[h]) continue;
         const int64_t c = int64_t(d.block) * rule.n_hot + h;
         const uint32_t hi = rule.cell_off[c + 1], b = lower_bound_in(blk_indices, rule.cell_off[c], hi, d.begin);
         atomicMax(&longest[h], lower_bound_in(blk_indices, b, hi, d.begin + d.size) - b);
     }
 }
 
-// seg[t * n_parts + i] = (begin, end) in the block-major edge list of the edges of row part order[i] into tile t
+// seg[t * n_parts + i] = (begin, end) in the block-major edge list of the edges of row part order[i] into tile t; none of a row's first
+// depth[row] tiles (null: 0), which the bit matrix has
 __global__ void __launch_bounds__(256) tile_segments_kernel(const TileDesc *__restrict__ tiles, int n_tiles, DenseRule rule,
                                                             const uint32_t *__restrict__ order, const RowPart *__restrict__ parts,
                                                             int64_t n_parts, const int32_t *__restrict__ blk_indices,
-                                                            uint2 *__restrict__ seg) {
+                                                            const uint32_t *__restrict__ depth, uint2 *__restrict__ seg) {
     const int64_t total = int64_t(n_tiles) * n_parts;
     const int64_t stride = int64_t(gridDim.x) * blockDim.x;
     for (int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < total; x += stride) {
@@ -183,7 +187,7 @@ __global__ void __launch_bounds__(256) tile_segments_kernel(const TileDesc *__re
         const RowPart p = parts[order[x - int64_t(t) * n_parts]];
         const TileDesc d = tiles[t];
         uint2 s = make_uint2(0u, 0u);
-        if (rule.edges(d.block, p.row)) {
+        if (rule.edges(d.block, p.row) && !(depth && uint32_t(t) < depth[p.row])) {
             const int64_t c = int64_t(d.block) * rule.n_hot + p.row;
             const uint32_t lo = rule.cell_off[c], hi = rule.cell_off[c + 1];
             const uint32_t b = lower_bound_in(blk_indices, lo, hi, d.begin);
@@ -637,6 +641,337 @@ __global__ void __launch_bounds__(kTileThreads) tile_kernel(const TileArgs a) {
     }
 }
 
+// ---------------------------------------------------------------- dense cells as a bit matrix
+// Where the rows with the most edges meet the sources gathered most, a tenth of all cells and more are edges, and a sum over sources is
+// cheaper as a product of the matrix cores with the 0/1 matrix of the edges, a bit per cell, than as a read of LDS and an addition per edge: 32
+// rows x 16 sources x 32 columns take three bf16 instructions of 32 clocks on one of four units, 24 / 512 clocks per cell, an edge 0.8
+// in tile_kernel.  The columns of X are split into three bf16 numbers each, exactly, as in gemm.hip; a product with 0 or 1 is exact.
+//
+// 233 K vertices, 115 M edges, 57 % of them in 220 groups of 256 rows: F=602 0.9 ms at 0.95 PFLOP/s, the clock's limit under such load; tile_kernel
+// 5.2 -> 3.4 ms, where copying the tiles counts for most now; the call 6.83 -> 6.1, F=256 2.66 -> 2.50.  Error of the sums against 64 bits, 2-norm, normal
+// operands 8.1e-7 -> 3.2e-7, positive 4.2e-7 -> 1.2e-7, over 40 binary orders of magnitude 6.0e-7 -> 2.5e-7.
+constexpr int kDenseWaves = 4;                // of 64 rows each
+constexpr int kDenseRows = 64 * kDenseWaves;  // of a group
+constexpr int kChunkSteps = 8, kChunk = 16 * kChunkSteps;  // sources that a workgroup has in LDS at a time
+// A row takes the tiles of which it has one line in so many (10 and 16: 233 K vertices, 115 M edges F=602 6.26 and 6.08 ms; 300 K, 120 M F=256
+// 2.82 and 2.85; 233 K directed, 80 M 2.00 and 2.12).
+constexpr int kDenseParts = 12;
+// Groups are made where they take this share of the plan's edges, because every tile is still copied for the others (MEAN forward F=256, ms,
+// without -> with: 233 K vertices, 115 M edges, 57 % 2.66 -> 2.50, 133 K, 79 M, 67 % 1.76 -> 1.58, 300 K, 120 M, 50 % 2.92 -> 2.82, 233 K directed,
+// 80 M, 45 % 2.10 -> 2.00; below, 505 K, 60 M, 27 % 2.37 -> 2.42, 133 K mild skew, 25 % 2.10 -> 2.17).
+constexpr double kDenseShare = 0.4;
+constexpr int kMaxChunks = 256;
+constexpr int kStepVecs = 3 * 64;             // 16-byte words of a step's split operand: three numbers, 64 lanes
+constexpr int kUnitChunks = 64;               // chunks that one workgroup takes (32, 64, 128: F=41 0.70, 0.72, 0.79 ms, F=602 the same)
+// Chunks of a group, where its bits begin, and the units it is cut into: the first adds to the partial lines, the others leave theirs at
+// slots extra ... extra + units - 2.
+struct DenseGroup { int64_t bits; int32_t chunks, units, extra, pad; };
+struct DenseUnit { int32_t group, begin, end, slot; };  // slot: -1, or where the sums are left
+
+// depth[h] = tiles from the first on of which row h has a kDenseParts-th of the lines; 0 where a source occurs twice.  A wavefront per row.
+__global__ void __launch_bounds__(256) dense_depth_kernel(const TileDesc *__restrict__ tiles, int n_tiles, DenseRule rule,
+                                                          const int32_t *__restrict__ blk_indices, uint32_t *__restrict__ depth_key,
+                                                          uint32_t *__restrict__ ids, uint32_t *__restrict__ histogram) {
+    const int lane = threadIdx.x & 63;
+    const int64_t h = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
+    if (h >= rule.n_hot) return;
+    uint32_t depth = 0;
+    if (rule.edges(0, h)) {
+        const uint32_t lo = rule.cell_off[h], hi = rule.cell_off[h + 1];
+        uint32_t b = lo;
+        while (int(depth) < n_tiles) {
+            const TileDesc d = tiles[depth];
+            const uint32_t e = lower_bound_in(blk_indices, b, hi, d.begin + d.size);
+            if (int64_t(e - b) * kDenseParts < d.size) break;
+            b = e;
+            ++depth;
+        }
+        bool twice = false;
+        for (uint32_t i = lo + lane; i + 1 < b; i += 64) twice |= blk_indices[i] == blk_indices[i + 1];
+        if (__any(twice)) depth = 0;
+    }
+    if (lane == 0) {
+        depth_key[h] = uint32_t(n_tiles) - depth;
+        ids[h] = uint32_t(h);
+        atomicAdd(&histogram[depth], 1u);
+    }
+}
+
+__device__ __forceinline__ uint32_t dense_prefix(const DenseRule &rule, const int32_t *blk_indices, uint32_t h, int32_t end) {
+    return lower_bound_in(blk_indices, rule.cell_off[h], rule.cell_off[h + 1], end) - rule.cell_off[h];
+}
+
+// The rows of the groups: depth[row] = tiles of its group; what is left of its staged edges (one at least: it needs a part).
+__global__ void __launch_bounds__(256) dense_assign_kernel(const TileDesc *__restrict__ tiles, DenseRule rule, const uint32_t *__restrict__ rows,
+                                                           int64_t n_rows, const uint32_t *__restrict__ group_depth,
+                                                           const int32_t *__restrict__ blk_indices, uint32_t *__restrict__ depth,
+                                                           uint32_t *__restrict__ staged, unsigned long long *__restrict__ n_edges) {
+    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= n_rows) return;
+    const uint32_t h = rows[i], t = group_depth[i / kDenseRows];
+    const uint32_t n = dense_prefix(rule, blk_indices, h, tiles[t - 1].begin + tiles[t - 1].size);
+    depth[h] = t;
+    staged[h] = staged[h] > n ? staged[h] - n : 1u;
+    atomicAdd(n_edges, static_cast<unsigned long long>(n));
+}
+
+// The bits.  Chunk c of 32 rows: 64 lanes of 8 bytes, lane = 32 * half + row; byte s of a lane's word of four steps (0 ... 3, then 4 ... 7) has the sources
+// 16 * s + 8 * half + 0 ... 7 of the chunk, the even ones in bits 4 * s ... of its low half, the odd ones in the high half: where the
+// pairs of bf16 numbers of an operand want them.  A wavefront per row.
+__global__ void __launch_bounds__(64) dense_bits_kernel(const TileDesc *__restrict__ tiles, DenseRule rule, const uint32_t *__restrict__ rows,
+                                                        const uint32_t *__restrict__ group_depth, const DenseGroup *__restrict__ groups,
+                                                        const int32_t *__restrict__ blk_indices, uint32_t *__restrict__ bits) {
+    __shared__ uint32_t words[kMaxChunks * 4];  // [chunk][half][steps 0 ... 3, 4 ... 7]
+    const int64_t i = blockIdx.x;
+    const int group = int(i / kDenseRows), in_group = int(i % kDenseRows);
+    const uint32_t h = rows[i], t = group_depth[group];
+    const DenseGroup g = groups[group];
+    for (int w = threadIdx.x; w < g.chunks * 4; w += 64) words[w] = 0u;
+    __syncthreads();
+    const uint32_t lo = rule.cell_off[h], n = dense_prefix(rule, blk_indices, h, tiles[t - 1].begin + tiles[t - 1].size);
+    for (uint32_t e = threadIdx.x; e < n; e += 64) {
+        const int k = blk_indices[lo + e];
+        const int step = (k >> 4) & 7, j = k & 7;
+        atomicOr(&words[(k >> 7) * 4 + ((k >> 3) & 1) * 2 + (step >> 2)], 1u << (4 * (step & 3) + (j >> 1) + 16 * (j & 1)));
+    }
+    __syncthreads();
+    const int64_t first = g.bits + int64_t(in_group >> 5) * g.chunks * 64;  // in 8-byte words
+    for (int w = threadIdx.x; w < g.chunks * 4; w += 64) {
+        const int64_t at = first + int64_t(w >> 2) * 64 + ((w >> 1) & 1) * 32 + (in_group & 31);
+        bits[at * 2 + (w & 1)] = words[w];
+    }
+}
+
+typedef float float16v __attribute__((ext_vector_type(16)));
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// Beyond this, values take the way of dense_kernel's last loop: split (times 2^16, so that no part of any is cut off below) they and
+// their sums would overflow, and infinities and NaN would reach rows that do not gather them.
+__device__ __forceinline__ bool dense_exception(float x) { return !(fabsf(x) < 0x1p90f); }
+
+// A wavefront splits 16 sources x 32 columns of one slice; flags: the sources that have a value of the other kind.
+__global__ void __launch_bounds__(256) dense_split_kernel(const char *__restrict__ X, int64_t slice_stride, int64_t n_sources, int64_t n_steps,
+                                                          int n_slices, u32x4 *__restrict__ split, uint16_t *__restrict__ flags) {
+    const int lane = threadIdx.x & 63;
+    const int64_t w = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
+    if (w >= n_steps * n_slices) return;
+    const int64_t slice = w / n_steps, step = w - slice * n_steps;
+    const float *x = reinterpret_cast<const float *>(X + slice * slice_stride) + (lane & 31);
+    const int64_t k0 = step * 16 + (lane >> 5) * 8;
+    float v[8];
+    uint32_t mask = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        v[j] = k0 + j < n_sources ? x[(k0 + j) * 32] : 0.0f;
+        const bool other = dense_exception(v[j]);
+        const unsigned long long m = __ballot(other);
+        if (uint32_t(m)) mask |= 1u << j;
+        if (uint32_t(m >> 32)) mask |= 256u << j;
+        v[j] = other ? 0.0f : v[j] * 0x1p16f;
+    }
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        u32x4 q;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float2v pair = {v[2 * i], v[2 * i + 1]};
+            q[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
+            v[2 * i] -= __uint_as_float(q[i] << 16);
+            v[2 * i + 1] -= __uint_as_float(q[i] & 0xFFFF0000u);
+        }
+        split[w * kStepVecs + s * 64 + lane] = q;
+    }
+    if (lane == 0) flags[w] = uint16_t(mask);
+}
+
+struct DenseArgs {
+    const DenseGroup *groups;
+    const DenseUnit *units;
+    const uint32_t *rows, *part_base;
+    const uint2 *bits;
+    const u32x4 *split;
+    const uint16_t *flags;
+    const char *X;
+    int64_t slice_stride, n_steps, n_parts;
+    int32_t n_slices;
+    float *partial;  // of the first group of tiles
+    float *extra;    // [slot][slice][row of the group][32]
+};
+
+// A workgroup takes the rows of a group and one slice of 32 columns: adds their sums to the partial lines of the rows' first parts.  A
+// wavefront has 64 rows, so that an operand read from LDS serves two products.
+//
+// The matrix cores cut off what lies below the sum's last bit, towards minus infinity: 64 sources at a time are summed from zero,
+// and every other such sum is one of negated operands (and of the other rows of a pair), subtracted.
+__global__ void __launch_bounds__(64 * kDenseWaves) dense_kernel(const DenseArgs a) {
+    constexpr int THREADS = 64 * kDenseWaves, COPIES = kChunkSteps * kStepVecs / THREADS;
+    static_assert(kChunkSteps * kStepVecs % THREADS == 0, "whole copies");
+    __shared__ u32x4 operand[2][kChunkSteps * kStepVecs];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int slice = int(blockIdx.x) % a.n_slices;
+    const DenseUnit unit = a.units[blockIdx.x / uint32_t(a.n_slices)];
+    const DenseGroup g = a.groups[unit.group];
+    const u32x4 *src = a.split + int64_t(slice) * a.n_steps * kStepVecs + threadIdx.x;
+    const uint2 *bits = a.bits + g.bits + int64_t(wave) * 2 * g.chunks * 64 + lane;
+    const int64_t second = int64_t(g.chunks) * 64;  // the other 32 rows
+    // +1 or -1 as a pair's first number, by the parity of row and sum
+    const uint32_t one = (lane & 1) ? 0xBF80u : 0x3F80u;
+    uint32_t c_even[4], c_odd[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) { c_even[p] = one >> p; c_odd[p] = (one ^ 0x8000u) >> p; }
+
+    float16v acc[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[r][v] = 0.0f;
+
+    u32x4 nxt[COPIES];
+    uint2 b_nxt[2];
+    auto fetch = [&](int c) {
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) nxt[i] = src[int64_t(c) * (kChunkSteps * kStepVecs) + i * THREADS];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) b_nxt[r] = bits[r * second + int64_t(c) * 64];
+    };
+    auto keep = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) operand[buf][i * THREADS + threadIdx.x] = nxt[i];
+    };
+    fetch(unit.begin);
+    keep(unit.begin & 1);
+    __syncthreads();
+    for (int c = unit.begin; c < unit.end; ++c) {
+        const uint2 b[2] = {b_nxt[0], b_nxt[1]};
+        fetch(c + 1 < unit.end ? c + 1 : c);
+        auto half = [&](auto odd) {
+            constexpr bool ODD = decltype(odd)::value;
+            float16v sum[2] = {};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const u32x4 *q = &operand[c & 1][((ODD ? 4 : 0) + s) * kStepVecs + lane];
+                bf16x8 x[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) x[i] = __builtin_bit_cast(bf16x8, q[(2 - i) * 64]);  // the smallest first
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const uint32_t word = (ODD ? b[r].y : b[r].x) >> (4 * s);
+                    u32x4 m;
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) m[p] = __umul24(word & (0x00010001u << p), ODD ? c_odd[p] : c_even[p]);
+                    const bf16x8 ones = __builtin_bit_cast(bf16x8, m);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) sum[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, x[i], sum[r], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[r][v] += ((v & 1) != int(ODD)) ? -sum[r][v] : sum[r][v];
+        };
+        half(std::false_type());
+        half(std::true_type());
+        keep((c + 1) & 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[r][v] *= 0x1p-16f;
+
+    // the values that were left out (see dense_exception)
+    const uint16_t *flags = a.flags + int64_t(slice) * a.n_steps;
+    const float *X = reinterpret_cast<const float *>(a.X + int64_t(slice) * a.slice_stride) + (lane & 31);
+    const int n_steps = unit.end * kChunkSteps;
+    for (int s0 = unit.begin * kChunkSteps; s0 < n_steps; s0 += 64) {
+        const uint32_t mine = s0 + lane < n_steps ? flags[s0 + lane] : 0u;
+        for (unsigned long long steps = __ballot(mine != 0u); steps; steps &= steps - 1) {
+            const int at = __builtin_ctzll(steps), step = s0 + at;
+            uint32_t sources = uint32_t(__shfl(int(mine), at));
+            uint32_t word[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const uint2 w = bits[r * second + int64_t(step / kChunkSteps) * 64];
+                word[r] = ((step & 4) ? w.y : w.x) >> (4 * (step & 3));
+            }
+            for (; sources; sources &= sources - 1) {
+                const int k = __builtin_ctz(sources), j = k & 7;
+                const float x = X[(int64_t(step) * 16 + k) * 32];
+                const bool other = dense_exception(x);
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int row = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                        const uint32_t w = uint32_t(__shfl(int(word[r]), (k >> 3) * 32 + row));
+                        if (other && ((w >> ((j >> 1) + 16 * (j & 1))) & 1u)) acc[r][v] += x;
+                    }
+            }
+        }
+    }
+
+    float *out = a.partial + int64_t(slice) * a.n_parts * 32 + (lane & 31);
+    const uint32_t *rows = a.rows + int64_t(unit.group) * kDenseRows + wave * 64;
+    float *extra = a.extra + (int64_t(unit.slot) * a.n_slices + slice) * (kDenseRows * 32) + wave * 64 * 32 + (lane & 31);
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            if (unit.slot >= 0) {
+                extra[(r * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * 32] = acc[r][v];
+                continue;
+            }
+            float *q = out + int64_t(a.part_base[rows[r * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)]]) * 32;
+            *q += acc[r][v];
+        }
+}
+
+// Adds the other units' sums of the groups that have any, in order.
+__global__ void __launch_bounds__(256) dense_add_kernel(const DenseArgs a) {
+    const int slice = int(blockIdx.y), group = int(blockIdx.x) / (kDenseRows / 8);
+    const DenseGroup g = a.groups[group];
+    const int row = int(blockIdx.x) % (kDenseRows / 8) * 8 + int(threadIdx.x >> 5), col = threadIdx.x & 31;
+    float *q = a.partial + (int64_t(slice) * a.n_parts + a.part_base[a.rows[int64_t(group) * kDenseRows + row]]) * 32 + col;
+    float s = *q;
+    for (int u = 0; u < g.units - 1; ++u) s += a.extra[((int64_t(g.extra + u) * a.n_slices + slice) * kDenseRows + row) * 32 + col];
+    *q = s;
+}
+
+int64_t dense_steps(const gnn_tiles *t) { return int64_t(t->dense_chunks) * kChunkSteps; }
+// Of a launch: sums of the groups' other units, split operand and its flags.
+int64_t dense_bytes(const gnn_tiles *t, int n_slices) {
+    return t->dense_groups ? n_slices * (int64_t(t->dense_extra) * kDenseRows * 128 + dense_steps(t) * (kStepVecs * 16 + 2)) : 0;
+}
+
+// What dense_bytes counts lies behind the partial lines.
+hipError_t launch_dense(const gnn_tiles *t, const void *X, int64_t slice_stride, int n_slices, int n_groups, float *partial, hipStream_t stream) {
+    DenseArgs a{};
+    a.groups = static_cast<const DenseGroup *>(t->dense);
+    a.units = reinterpret_cast<const DenseUnit *>(a.groups + t->dense_groups);
+    a.rows = t->dense_rows;
+    a.part_base = t->part_base;
+    a.bits = t->dense_bits;
+    a.extra = partial + int64_t(n_groups) * n_slices * t->n_parts * 32;
+    u32x4 *split = reinterpret_cast<u32x4 *>(a.extra + int64_t(t->dense_extra) * n_slices * kDenseRows * 32);
+    a.n_steps = dense_steps(t);
+    uint16_t *flags = reinterpret_cast<uint16_t *>(split + a.n_steps * n_slices * kStepVecs);
+    a.split = split;
+    a.flags = flags;
+    a.X = static_cast<const char *>(X);
+    a.slice_stride = slice_stride;
+    a.n_parts = t->n_parts;
+    a.n_slices = n_slices;
+    a.partial = partial;
+    dense_split_kernel<<<static_cast<unsigned>((a.n_steps * n_slices + 3) / 4), 256, 0, stream>>>(a.X, slice_stride, t->dense_sources, a.n_steps, n_slices,
+                                                                                            split, flags);
+    dense_kernel<<<static_cast<unsigned>(t->dense_units * n_slices), 64 * kDenseWaves, 0, stream>>>(a);
+    if (t->dense_cut > 0)
+        dense_add_kernel<<<dim3(static_cast<unsigned>(t->dense_cut * (kDenseRows / 8)), static_cast<unsigned>(n_slices)), 256, 0, stream>>>(a);
+    return hipGetLastError();
+}
+
 // number of the layout for L lanes per row
 int level_of(int lanes, bool bf16) { return (lanes == 8 ? 0 : (lanes == 4 ? 1 : 2)) + (bf16 ? 3 : 0); }
 
@@ -646,6 +981,7 @@ void gnn_tiles_free(gnn_tiles &t) {
     gnn_dev_free(t.part_base); gnn_dev_free(t.order); gnn_dev_free(t.tiles); gnn_dev_free(t.seg); gnn_dev_free(t.stream);
     gnn_dev_free(t.counts); gnn_dev_free(t.wave_off); gnn_dev_free(t.left.pieces); gnn_dev_free(t.left.piece_block);
     gnn_dev_free(t.left.rowbase); gnn_dev_free(t.bound_w); gnn_dev_free(t.tmp_w); gnn_dev_free(t.positions);
+    gnn_dev_free(t.dense); gnn_dev_free(t.dense_rows); gnn_dev_free(t.dense_bits);
     for (int i = 0; i < 3; ++i) gnn_dev_free(t.scale[i]);
     t = gnn_tiles{};
 }
@@ -678,8 +1014,83 @@ int64_t row_blocks_for(int64_t n_bundles, int rr) {
     return few > least ? few : (least > 0 ? least : 1);
 }
 
+// The bit matrix: rows by the number of tiles they are dense in, in groups that share it.  Takes the edges away from `staged` and
+// *staged_edges; *depth: tiles that a row's lists leave out.
+int build_dense(const gnn_plan *plan, const DenseRule &rule, const std::vector<TileDesc> &tiles, int n_tiles, const TileDesc *d_tiles, uint32_t *staged,
+                Scratch &tmp, hipStream_t stream, gnn_tiles &B, uint32_t **depth_out, int64_t *staged_edges) {
+    const int64_t n_hot = rule.n_hot;
+    while (n_tiles > 0 && int64_t(tiles[size_t(n_tiles - 1)].begin) + tiles[size_t(n_tiles - 1)].size > int64_t(kMaxChunks) * kChunk) --n_tiles;
+    if (n_tiles == 0 || n_hot < kDenseRows) return GNN_OK;
+    uint32_t *keys[2], *ids[2], *table = nullptr, *sums = nullptr, *histogram = nullptr, *depth = nullptr;
+    if (!(tmp.get(&keys[0], n_hot) && tmp.get(&keys[1], n_hot) && tmp.get(&ids[0], n_hot) && tmp.get(&ids[1], n_hot) &&
+          tmp.get(&table, gnn_sort_table_elems(n_hot)) && tmp.get(&sums, gnn_sort_sums_elems(n_hot)) && tmp.get(&histogram, n_tiles + 1)))
+        return GNN_ERR_ALLOC;
+    GNN_HIP_TRY(hipMemsetAsync(histogram, 0, sizeof(uint32_t) * size_t(n_tiles + 1), stream));
+    dense_depth_kernel<<<grid_for(n_hot * 64, 256, INT32_MAX), 256, 0, stream>>>(d_tiles, n_tiles, rule, plan->blk_indices, keys[0], ids[0], histogram);
+    GNN_HIP_TRY(hipGetLastError());
+    std::vector<uint32_t> rows_of_depth(size_t(n_tiles) + 1);
+    GNN_HIP_TRY(hipMemcpyAsync(rows_of_depth.data(), histogram, sizeof(uint32_t) * rows_of_depth.size(), hipMemcpyDeviceToHost, stream));
+    GNN_HIP_TRY(hipStreamSynchronize(stream));
+    // a group is as deep as its last row
+    std::vector<uint32_t> group_depth;
+    std::vector<DenseGroup> groups;
+    std::vector<DenseUnit> units;
+    int64_t rows = 0, bits = 0;
+    int extra = 0, cut = 0;
+    for (int t = n_tiles; t > 0; --t) {
+        rows += rows_of_depth[size_t(t)];
+        const int64_t chunks = (int64_t(tiles[size_t(t - 1)].begin) + tiles[size_t(t - 1)].size + kChunk - 1) / kChunk;
+        while (int64_t(groups.size() + 1) * kDenseRows <= rows) {
+            const int n = int((chunks + kUnitChunks - 1) / kUnitChunks), group = int(groups.size());
+            groups.push_back(DenseGroup{bits, int32_t(chunks), n, extra, 0});
+            group_depth.push_back(uint32_t(t));
+            bits += chunks * (kDenseRows * 2);
+            for (int u = 0; u < n; ++u) units.push_back(DenseUnit{group, int32_t(chunks * u / n), int32_t(chunks * (u + 1) / n), u == 0 ? -1 : extra++});
+            cut += n > 1;
+        }
+    }
+    if (groups.empty()) return GNN_OK;
+    int where = 0;
+    const int rc = gnn_radix_sort_pairs(keys, ids, n_hot, gnn_ilog2_ceil(int64_t(n_tiles) + 1), table, sums, stream, &where);
+    if (rc != GNN_OK) return rc;
+    const int64_t n_rows = int64_t(groups.size()) * kDenseRows;
+    uint32_t *d_depth = nullptr;
+    unsigned long long *n_edges = nullptr, host_edges = 0;
+    DenseGroup *d_groups = nullptr;
+    if (!(tmp.get(&depth, n_hot) && tmp.get(&d_depth, int64_t(groups.size())) && tmp.get(&n_edges, 1))) return GNN_ERR_ALLOC;
+    static_assert(sizeof(DenseGroup) % alignof(DenseUnit) == 0 && 2 * sizeof(DenseUnit) >= sizeof(DenseGroup), "units behind the groups");
+    if (!gnn_dev_alloc(&d_groups, int64_t(groups.size() + units.size()), stream)) return GNN_ERR_ALLOC;
+    B.dense = d_groups;
+    std::stable_sort(units.begin(), units.end(), [](const DenseUnit &x, const DenseUnit &y) { return x.end - x.begin > y.end - y.begin; });  // the longest first
+    GNN_HIP_TRY(hipMemcpyAsync(d_groups + groups.size(), units.data(), sizeof(DenseUnit) * units.size(), hipMemcpyHostToDevice, stream));
+    if (!(gnn_dev_alloc(&B.dense_rows, n_rows, stream) && gnn_dev_alloc(&B.dense_bits, bits, stream))) return GNN_ERR_ALLOC;
+    GNN_HIP_TRY(hipMemcpyAsync(d_groups, groups.data(), sizeof(DenseGroup) * groups.size(), hipMemcpyHostToDevice, stream));
+    GNN_HIP_TRY(hipMemcpyAsync(d_depth, group_depth.data(), sizeof(uint32_t) * group_depth.size(), hipMemcpyHostToDevice, stream));
+    GNN_HIP_TRY(hipMemcpyAsync(B.dense_rows, ids[where], sizeof(uint32_t) * size_t(n_rows), hipMemcpyDeviceToDevice, stream));
+    GNN_HIP_TRY(hipMemsetAsync(depth, 0, sizeof(uint32_t) * size_t(n_hot), stream));
+    GNN_HIP_TRY(hipMemsetAsync(n_edges, 0, sizeof(*n_edges), stream));
+    dense_assign_kernel<<<grid_for(n_rows, 256, INT32_MAX), 256, 0, stream>>>(d_tiles, rule, B.dense_rows, n_rows, d_depth, plan->blk_indices, depth,
+                                                                            staged, n_edges);
+    dense_bits_kernel<<<static_cast<unsigned>(n_rows), 64, 0, stream>>>(d_tiles, rule, B.dense_rows, d_depth, d_groups, plan->blk_indices,
+                                                                     reinterpret_cast<uint32_t *>(B.dense_bits));
+    GNN_HIP_TRY(hipGetLastError());
+    GNN_HIP_TRY(hipMemcpyAsync(&host_edges, n_edges, sizeof(host_edges), hipMemcpyDeviceToHost, stream));
+    GNN_HIP_TRY(hipStreamSynchronize(stream));  // the host arrays end here
+    if (double(host_edges) < kDenseShare * double(plan->n_edges)) return GNN_OK;
+    B.dense_groups = int32_t(groups.size());
+    B.dense_units = int32_t(units.size());
+    B.dense_extra = extra;
+    B.dense_cut = cut;
+    B.dense_chunks = groups[0].chunks;
+    B.dense_sources = plan->n_rows;
+    *staged_edges -= int64_t(host_edges);
+    if (*staged_edges < 1) *staged_edges = 1;
+    *depth_out = depth;
+    return GNN_OK;
+}
+
 // Builds B (the caller frees what it holds when this fails).  B.active stays false where nothing is dense enough.
-int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn_tiles &B) {
+int build_tiles(const gnn_plan *plan, int lanes, int rr, bool dense, hipStream_t stream, gnn_tiles &B) {
     const int64_t n_hot = plan->blk_n_hot;
     const int n_blocks = plan->blk_n_blocks;
     const int tile_lines = tile_bytes(lanes) / (16 * lanes) - zero_lines(lanes);
@@ -744,14 +1155,21 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     GNN_HIP_TRY(hipMemcpyAsync(&host_staged, n_staged, 4, hipMemcpyDeviceToHost, stream));
     GNN_HIP_TRY(hipStreamSynchronize(stream));
     if (host_staged == 0) return GNN_OK;
-    const uint32_t cap = uint32_t((2 * staged_edges + host_staged - 1) / host_staged);  // twice the mean row
-    uint32_t *longest = nullptr;
+    uint32_t *longest = nullptr, *depth = nullptr;
     TileDesc *d_tiles = nullptr;
     if (!tmp.get(&longest, n_hot) || !gnn_dev_alloc(&d_tiles, n_tiles, stream)) return GNN_ERR_ALLOC;
     B.tiles = d_tiles;
     GNN_HIP_TRY(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(TileDesc) * size_t(n_tiles), hipMemcpyHostToDevice, stream));
+    if (dense) {
+        if (tiles[0].block == 0) {
+            const int rc_dense = build_dense(plan, rule, tiles, int(n_block_tiles[0]), d_tiles, staged, tmp, stream, B, &depth, &staged_edges);
+            if (rc_dense != GNN_OK) return rc_dense;
+        }
+        if (!B.dense_groups) return GNN_OK;  // the layout for all calls serves these too
+    }
+    const uint32_t cap = uint32_t((2 * staged_edges + host_staged - 1) / host_staged);  // twice the mean row
     GNN_HIP_TRY(hipMemsetAsync(longest, 0, sizeof(uint32_t) * size_t(n_hot), stream));
-    tile_longest_kernel<<<grid_for(int64_t(n_tiles) * n_hot, 256), 256, 0, stream>>>(d_tiles, n_tiles, rule, plan->blk_indices, longest);
+    tile_longest_kernel<<<grid_for(int64_t(n_tiles) * n_hot, 256), 256, 0, stream>>>(d_tiles, n_tiles, rule, plan->blk_indices, depth, longest);
     tile_row_parts_kernel<<<row_grid, 256, 0, stream>>>(staged, longest, n_hot, cap, part_base);
     GNN_HIP_TRY(hipGetLastError());
     GNN_HIP_TRY(hipMemcpyAsync(&parts_last, part_base + n_hot - 1, 4, hipMemcpyDeviceToHost, stream));
@@ -801,7 +1219,7 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
     if (rc != GNN_OK) return rc;
     GNN_HIP_TRY(hipMemcpyAsync(B.order, ids[where], sizeof(uint32_t) * size_t(n_parts), hipMemcpyDeviceToDevice, stream));
     tile_segments_kernel<<<grid_for(int64_t(n_tiles) * n_parts, 256), 256, 0, stream>>>(d_tiles, n_tiles, rule, B.order, parts, n_parts,
-                                                                                    plan->blk_indices, seg);
+                                                                                    plan->blk_indices, depth, seg);
     tile_counts_kernel<<<grid_for(n_wt, 256), 256, 0, stream>>>(seg, n_parts, n_tiles, n_waves, rr, rows, B.counts, B.wave_off);
     GNN_HIP_TRY(hipGetLastError());
     std::vector<uint32_t> iters(static_cast<size_t>(n_wt));
@@ -851,26 +1269,29 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, hipStream_t stream, gnn
 }  // namespace
 
 // Builds the tile layout for rows of `lanes` x 16 bytes on first use; needs the source-blocked layout.
-int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, hipStream_t stream, const gnn_tiles **out) {
+int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, hipStream_t stream, const gnn_tiles **out) {
     *out = nullptr;
     if (!plan || (lanes != 8 && lanes != 4 && lanes != 2)) return GNN_ERR_INVALID_ARG;
-    gnn_tiles &L = plan->tiles[level_of(lanes, bf16)];
+    const bool dense = plain && lanes == 8 && !bf16;
+    gnn_tiles &L = plan->tiles[dense ? GNN_TILES_PLAIN : level_of(lanes, bf16)];
     if (!L.decided) {
         if (!plan->blk_decided) return GNN_ERR_INVALID_ARG;
         gnn_tiles B{};
         if (plan->blk_n_pieces > 0 && plan->blk_cell_off) {
             int rc;
             try {
-                rc = build_tiles(plan, lanes, bf16 ? kBundlesBf16 : kBundlesF32, stream, B);
+                rc = build_tiles(plan, lanes, bf16 ? kBundlesBf16 : kBundlesF32, dense, stream, B);
             } catch (const std::bad_alloc &) {  // of its host arrays: no exception leaves the library
                 rc = GNN_ERR_ALLOC;
             }
             if (rc != GNN_OK || !B.active) gnn_tiles_free(B);
+            if (dense && rc == GNN_ERR_ALLOC) rc = GNN_OK;  // no room for the bits: lists only
             if (rc != GNN_OK) return rc;
         }
         L = std::move(B);
         L.decided = true;
     }
+    if (dense && !L.active) return gnn_plan_tiles(plan, lanes, bf16, false, stream, out);
     if (L.active) *out = &L;
     return GNN_OK;
 }
@@ -987,7 +1408,7 @@ int gnn_tile_groups(const gnn_tiles *t, int n_slices) {
 }
 
 int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats) {
-    const int64_t need = int64_t(gnn_tile_groups(t, n_slices)) * n_slices * t->n_parts * line_floats * int64_t(sizeof(float));
+    const int64_t need = int64_t(gnn_tile_groups(t, n_slices)) * n_slices * t->n_parts * line_floats * int64_t(sizeof(float)) + dense_bytes(t, n_slices);
     if (need <= plan->tile_partial_bytes) return GNN_OK;
     (void)hipGetLastError();
     gnn_dev_free(plan->tile_partial);
@@ -1045,5 +1466,6 @@ int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice
         else GNN_TILE_LAUNCH(false, 2);
     }
 #undef GNN_TILE_LAUNCH
+    if (t->dense_groups && launch_dense(t, X, slice_stride_bytes, n_slices, a.n_groups, partial, stream) != hipSuccess) return GNN_ERR_LAUNCH;
     return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
 }

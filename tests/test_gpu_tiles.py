@@ -173,3 +173,51 @@ def test_coefficients_follow_weights_that_change(f, dtype, op_name, bound):
         check(weights[i], f"other array {i}")
         call(w)
         check(host, f"refill {i}, after another array")
+
+
+@pytest.mark.parametrize("n,rows,hot_lines", [(600, 512, 600), (1100, 700, 1099), (9500, 600, 9400)])
+@pytest.mark.parametrize("f,op_name", [(96, "sum"), (100, "mean"), (131, "sage")])
+def test_dense_cells_as_a_bit_matrix(n, rows, hot_lines, f, op_name):
+    """Rows with a third of all sources: groups of 256 of them, the other rows and those with a repeated source as lists; sources that fill
+    no chunk, and so many that a group is cut.  Columns of values whose parts are denormals and of values near the largest, against the oracle; infinities and
+    NaN reach the rows that gather them only."""
+    r = (synth.mix64(torch.arange(rows * n) + 7) & 0x7FFFFFFF) % 3 == 0
+    key = r.nonzero().reshape(-1) // n * (n - rows + 1) % n * n + r.nonzero().reshape(-1) % n
+    other = synth.mix64(torch.arange(4 * n) + 31) & 0x7FFFFFFFFFFF
+    key = torch.cat([key.unique(), other % n * n + (other // n) % n]).unique()
+    twice = key[(key // n == key[len(key) // 2] // n)][:3]
+    key = torch.sort(torch.cat([key, twice])).values
+    el = synth.EdgeList(n=n, src=(key % n).to(torch.int32), dst=(key // n).to(torch.int32), meta={})
+    indptr, indices, indptr_t, *_ = host_csr(el)
+    dg = device_graph(el, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    dg.plan_fwd.set_blocking(min_degree=32, hot_lines=hot_lines, block_lines=1000, max_piece=48, rest_min_count=0)
+    X = synth.normal_features(n, f, 3)
+    X[:, 5] *= 1e-36
+    X[:, f - 1] *= 1e30
+    X[11::97, 40] = 1e33
+    op = OP_CODE[op_name]
+    Yo, S = oracle.aggregate_fwd(indptr, indices, X.numpy(), op=op, dout=np.diff(indptr_t), nthreads=8, want_scale=True)
+    Xd = X.to(DEV)
+    Y = torch.full((n, f), float("nan"), device=DEV)
+
+    def call():
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, None, Xd, Y, n, f, op, plan=dg.plan_fwd, flags=SLICED, max_slices=8)
+        torch.cuda.synchronize()
+
+    call()
+    assert_close(Y, Yo, S, False, op_name)
+    specials = [float("inf"), float("-inf"), float("nan"), 1.5e38]  # the last one twice where a vertex is its own neighbour
+    want = torch.zeros(n, f, device=DEV)
+    src, dst = el.src.to(DEV).long(), el.dst.to(DEV).long()
+    for i, u in enumerate([0, 1, n // 2, n - 2, n - 1, 127, 128, 511]):
+        Xd[:, 7 + i] = 1.0
+        Xd[u, 7 + i] = specials[i % 4]
+        to = dst[src == u]
+        want[to, 7 + i] = specials[i % 4]
+        if op_name == "sage":
+            want[u, 7 + i] = specials[i % 4]
+    call()
+    hit = want != 0
+    assert torch.equal(~torch.isfinite(Y), ~torch.isfinite(want)), "infinities and NaN"
+    finite = hit & torch.isfinite(want)
+    assert bool((Y[finite] > 1e33).all()) and bool((Y[:, 7:15][~hit[:, 7:15]].abs() < 1e6).all())

@@ -365,10 +365,7 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             p0 = E - n_edges;  // the plan order ends with them
             enable = n_edges > 0;
         }
-        // Automatic gate: the gathered table must dwarf an L2 (else the plain path hits anyway), and the
-        // long rows must hold a good part of the edges (else there is little to win).
-        // (233 K vertices x 490 edges: F=256 6.29 -> 5.48 ms, F=602 15.05 -> 13.63)
-        if (enable && automatic) enable = N >= 4 * int64_t(32768) && n_edges * 4 >= E;
+        if (enable && automatic) enable = gnn_blocks_by_itself(plan, n_edges);
         BlockMap m{};
         if (enable) {
             // sources gathered fewer than rest_min_count times share the last block (the threshold is a bucket boundary)

@@ -315,6 +315,14 @@ struct gnn_layout {
 // Will calls with this plan serve their long rows as source-blocked pieces (gnn_plan_blocked)?  Known
 // once the layout is built; before that, the gate of the automatic choice evaluated on the plan's host
 // figures (an explicit gnn_plan_set_blocking counts as yes).
+// Does a plan block by itself?  The long rows must hold a good part of the edges (else there is little to win).  The gathered table must
+// dwarf an L2, or there are enough edges to pay for the launches that pieces and tiles take: it is the L2s' line rate that bounds a gather
+// that hits, too (MEAN forward, ms, without -> with: 100 K vertices, 60 M edges F=602 6.50 -> 2.80, 256 2.67 -> 1.24, 64 0.78 -> 0.36, 16 0.35 -> 0.18;
+// 100 K, 20 M 2.31 -> 1.61, 0.95 -> 0.63, 0.26 -> 0.18, 0.10 the same; 60 K, 24 M F=256 1.04 -> 0.57, F=32 0.13 the same; below, 60 K, 9 M F=256 0.41 ->
+// 0.36, but F=100 0.20 -> 0.27; 40 K, 10 M F=256 0.47 -> 0.35, F=100 0.21 -> 0.24).
+static inline bool gnn_blocks_by_itself(const gnn_plan *plan, int64_t long_edges) {
+    return (plan->n_rows >= 4 * int64_t(32768) || (plan->n_rows >= 32768 && plan->n_edges >= 16000000)) && long_edges * 4 >= plan->n_edges;
+}
 static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz) {
     if (!plan || plan->n_edges <= 0 || plan->n_edges >= int64_t(INT32_MAX)) return false;
     const bool automatic = plan->blocking.min_degree == 0;
@@ -332,7 +340,7 @@ static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz) {
     int64_t long_edges = 0;
     for (int b = first_bin; b < plan->n_bins; ++b) long_edges += plan->bin_edges[b];
     if (long_edges <= 0) return false;
-    return !automatic || (plan->n_rows >= 4 * int64_t(32768) && long_edges * 4 >= plan->n_edges);
+    return !automatic || gnn_blocks_by_itself(plan, long_edges);
 }
 
 // The edge weights of a call.  BOUND: the array of gnn_plan_bind_edge_weights; FREE: any other.

@@ -487,6 +487,9 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
     const Near near(a);
     constexpr bool NEED_X = BIN == GNN_BIN_MUL || BIN == GNN_BIN_DIV;
     constexpr bool NEED_Y = BIN == GNN_BIN_DIV;
+    // Edges in flight per slot (us, 2 / 4 / 8: 245 K vertices, 50 edges each 33 columns 694 / 694 / 717, 60 K vertices, 50 each 174 / 162 / 153, 8 columns
+    // 36 / 37 / 47).  Their loads come before the first use, else each waited for the one before it and for its store (60 K vertices
+    // 33 columns 172 -> 162, 64 239 -> 211; 245 K 61 1107 from 1149; 100 K, 10 each 33 96 -> 80).
     constexpr int U = 4;
     const Group g = locate_group(a, near, blockIdx.x);
     const int G = g.G, SR = g.SR, C = g.C;
@@ -503,6 +506,10 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
     };
     int nxt_u; float nxt_y; int64_t nxt_r;
     fetch_tile(e0 + g.lane_in_g, nxt_u, nxt_y, nxt_r);
+    float go_first[VEC];  // of the lane's first strip: the same for all edges
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) go_first[i] = 0.0f;
+    if (e0 < e1 && g.c * VEC < a.d) load_f<VEC>(a.dO + row * a.ldo + (VEC > 1 && g.c * VEC > a.d - VEC ? a.d - VEC : g.c * VEC), go_first);
     for (int64_t tile = e0; __any(tile < e1); tile += G) {
         const int my_u = nxt_u;
         const float my_y = nxt_y;
@@ -528,26 +535,33 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
             }
             for (int col0 = g.c * VEC; col0 < a.d; col0 += C * VEC) {
                 const int col = VEC > 1 && col0 > a.d - VEC ? a.d - VEC : col0;  // columns before col0 belong to the strip before
-                float go[VEC];
+                float go[VEC], x[U][VEC], y[U][VEC];
                 int32_t aw[VEC];
-                load_f<VEC>(a.dO + row * a.ldo + col, go);
+                if (col0 != g.c * VEC) load_f<VEC>(a.dO + row * a.ldo + col, go);
+                else
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) go[i] = go_first[i];
                 if (MASKED) load_i<VEC>(a.arg_in + row * int64_t(a.d) + col, aw);
+#pragma unroll
+                for (int k = 0; k < U; ++k) {  // all loads before the first use
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) { x[k][i] = 0.0f; y[k][i] = ys[k]; }
+                    if (!ok[k]) continue;
+                    if (NEED_X) load_f<VEC>(near.fV + int64_t(u[k]) * near.ldv + col, x[k]);
+                    if (NEED_Y && EWIDE) load_f<VEC>(near.fE + r[k] * near.lde + col, y[k]);
+                }
 #pragma unroll
                 for (int k = 0; k < U; ++k) {
                     if (!ok[k]) continue;
-                    float x[VEC], y[VEC], gy[VEC];
-#pragma unroll
-                    for (int i = 0; i < VEC; ++i) { x[i] = 0.0f; y[i] = ys[k]; }
-                    if (NEED_X) load_f<VEC>(near.fV + int64_t(u[k]) * near.ldv + col, x);
-                    if (NEED_Y && EWIDE) load_f<VEC>(near.fE + r[k] * near.lde + col, y);
+                    float gy[VEC];
                     const int32_t pos = int32_t(tile + j0 + k * SR + g.s);
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) {
                         float t;
                         if constexpr (BIN == GNN_BIN_ADD || BIN == GNN_BIN_COPY_RHS) t = go[i];
                         else if constexpr (BIN == GNN_BIN_SUB) t = -go[i];
-                        else if constexpr (BIN == GNN_BIN_MUL) t = go[i] * x[i];
-                        else t = -go[i] * x[i] / (y[i] * y[i]);
+                        else if constexpr (BIN == GNN_BIN_MUL) t = go[i] * x[k][i];
+                        else t = -go[i] * x[k][i] / (y[k][i] * y[k][i]);
                         if (MASKED && aw[i] != pos) t = 0.0f;
                         gy[i] = t;
                     }

@@ -131,7 +131,7 @@ def test_edge_ids_remap_the_edge_rows(d, ewidth):
     _check_all(el, params, d, ewidth, use_eid=True, ties=False, seed=13)
 
 
-@pytest.mark.parametrize("d,ewidth", [(100, 1), (64, 1), (256, 1), (600, 1), (100, 100)])
+@pytest.mark.parametrize("d,ewidth", [(100, 1), (64, 1), (256, 1), (600, 1), (100, 100), (261, 261)])
 @pytest.mark.parametrize("max_slices", [8, 2])
 def test_padded_copy_and_column_slices(d, ewidth, max_slices):
     """The layout of the sum-only hot path (rows copied to an odd line stride, one-line column

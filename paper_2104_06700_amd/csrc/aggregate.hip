@@ -1483,7 +1483,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     int64_t ldg = ldx;  // row stride of the matrix the kernel gathers from
     bool padded = false;
     const gnn_weight_kind weights = gnn_weight_kind_of(plan, w);
-    const bool blocks_expected = !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS) && gnn_call_blocks_expected(plan, esz, weights);
+    const bool blocks_expected = !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS) && gnn_call_blocks_expected(plan, esz, F, weights);
     const gnn_layout layout = gnn_choose_layout(plan, N, F, esz, ldx, reinterpret_cast<uintptr_t>(gathered) % 128 == 0,
                                                 o.flags, o.max_slices, /*allow_tail=*/o.max_slices != 1,
                                                 /*scaled_source=*/src_mode != kScaleNone, blocks_expected, /*weights=*/w != nullptr);
@@ -1981,7 +1981,7 @@ int gnn_packed_target_for(gnn_plan *plan, const void *indptr, const int32_t *ind
     else if (op == GNN_SAGE_GCN && backward) src_mode = kScaleInvPlus1;
     const gnn_layout layout = gnn_choose_layout(plan, N, F, 4, F, true, force ? GNN_FLAG_FORCE_PADDED_COPY : 0, force ? 8 : 0,
                                                 /*allow_tail=*/true, /*scaled_source=*/src_mode != kScaleNone,
-                                                gnn_plan_blocks_expected(plan, 4));
+                                                gnn_plan_blocks_expected(plan, 4, F * 4, false));
     if (!(layout.padded_copy && layout.slice_major)) return GNN_OK;  // that call gathers rows where they lie
     const int64_t lines = (F + 31) / 32;
     if (lines < 2 || lines > 256) return GNN_OK;

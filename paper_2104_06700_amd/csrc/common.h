@@ -323,13 +323,18 @@ struct gnn_layout {
 static inline bool gnn_blocks_by_itself(const gnn_plan *plan, int64_t long_edges) {
     return (plan->n_rows >= 4 * int64_t(32768) || (plan->n_rows >= 32768 && plan->n_edges >= 16000000)) && long_edges * 4 >= plan->n_edges;
 }
-static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz) {
+static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz, int64_t row_bytes, bool weights) {
     if (!plan || plan->n_edges <= 0 || plan->n_edges >= int64_t(INT32_MAX)) return false;
     const bool automatic = plan->blocking.min_degree == 0;
     // bf16 pieces write partial lines twice as large as the lines they gather: on graphs of a few L2s' worth of vertices
     // that eats the gain (233 K vertices, F=256 backward 3.95 -> 4.07 ms; 133 K vertices, F=128 1.16 -> 1.25), on the
-    // 2.45 M-vertex graph it does not (F=512 12.9 -> 11.6).
-    if (esz == 2 && automatic && plan->n_rows < 8 * int64_t(32768)) return false;
+    // 2.45 M-vertex graph it does not (F=512 12.9 -> 11.6).  Short rows and many edges pay there, too: a gather from tiles in LDS is not bound by lines
+    // (MEAN forward and backward, ms a call: 233 K vertices, 115 M edges F=64 0.91 -> 0.82, 32 0.82 -> 0.44, 16 0.76 -> 0.42; 100 K, 60 M 0.45 ->
+    // 0.42, 0.41 -> 0.29, 0.38 -> 0.30; 133 K, 40 M F=64 0.330 -> 0.342, 32 0.30 -> 0.27, 16 0.28 -> 0.19; 80 K, 30 M F=32 0.22 -> 0.18; 133 K, 28 M 0.202 ->
+    // 0.220).  Not with weights, whose products with a factor every call makes anew.
+    if (esz == 2 && automatic && plan->n_rows < 8 * int64_t(32768) &&
+        (weights || row_bytes > 128 || plan->n_edges < (row_bytes <= 64 ? 30000000 : 60000000)))
+        return false;
     if (plan->blk_decided) return plan->blk_n_pieces > 0;
     if (plan->blocking.min_degree < 0) return false;
     const int64_t min_degree = automatic ? 256 : plan->blocking.min_degree;
@@ -351,8 +356,8 @@ static inline gnn_weight_kind gnn_weight_kind_of(const gnn_plan *plan, const flo
 // Will a call with such weights serve its long rows as pieces?  FREE weights sit in CSR order, the pieces in rank order, so
 // every edge would cost a random 4-byte read (1.44 -> 3.67 ms on the weighted workload at F=64): such calls keep the path
 // without pieces unless the plan's blocking was asked for explicitly.
-static inline bool gnn_call_blocks_expected(const gnn_plan *plan, int esz, gnn_weight_kind weights) {
-    return plan && gnn_plan_blocks_expected(plan, esz) && (weights != GNN_WEIGHTS_FREE || plan->blocking.min_degree > 0);
+static inline bool gnn_call_blocks_expected(const gnn_plan *plan, int esz, int64_t F, gnn_weight_kind weights) {
+    return plan && gnn_plan_blocks_expected(plan, esz, F * esz, weights != GNN_WEIGHTS_NONE) && (weights != GNN_WEIGHTS_FREE || plan->blocking.min_degree > 0);
 }
 
 static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int64_t F, int esz, int64_t ldx,

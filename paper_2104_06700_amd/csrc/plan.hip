@@ -646,7 +646,7 @@ int gnn_plan_padded(gnn_plan *plan, int64_t bytes) {
 // What a hot call with edge weights of this kind takes (run_aggregate of aggregate.hip, on a dense matrix at a line boundary:
 // ld = F), except for the per-edge factors `mode` (0: none).
 static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int64_t F, int esz, gnn_weight_kind weights, hipStream_t stream) {
-    const bool blocks = gnn_call_blocks_expected(plan, esz, weights);
+    const bool blocks = gnn_call_blocks_expected(plan, esz, F, weights);
     const gnn_layout layout = gnn_choose_layout(plan, plan->n_rows, F, esz, F, true, 0, 0, /*allow_tail=*/true, /*scaled_source=*/mode != 0,
                                                 blocks, weights != GNN_WEIGHTS_NONE);
     if (!layout.padded_copy) {

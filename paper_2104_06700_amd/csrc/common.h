@@ -678,7 +678,7 @@ struct gnn_gemm_fold {
 };
 
 // k-steps of a part of a split product at least
-constexpr int64_t GNN_SPLIT_MIN_K = 96;
+constexpr int64_t GNN_SPLIT_MIN_K = 128;
 
 int gnn_matmul_impl(const float *A, int64_t lda, int trans_a, const float *B, int64_t ldb, int trans_b, float *C, int64_t ldc,
                     int64_t M, int64_t N, int64_t K, const float *bias, int relu, void *workspace, int64_t workspace_bytes,

@@ -807,8 +807,8 @@ static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
     // ... or two rounds of shorter parts, for closer sums, where they cost next to nothing (600,000 rows into 256 x 256 496 and 507 us)
     if (s.resident == 1 && K > 2048 * split) split *= 2;
     // At least GNN_SPLIT_MIN_K rows per part: a part is bound by the latency of its tiles of 16, one after the other, while the chip is not
-    // full; the partial planes cost little beside that (24,490 rows, us with parts of 128 and of 96: 128 x 128 22.3 and 18.5, 256 x 47
-    // 18.2 and 17.4, 16 x 41 16.0 and 15.2; 6,000 rows 100 x 256 24.8 and 21.6, 602 x 16 14.5 and 12.6).
+    // full; the partial planes cost little beside that.  Parts of 96 would be faster on few rows (24,490 rows, us with parts of 128 and of
+    // 96: 128 x 128 22.3 and 18.5, 256 x 47 18.2 and 17.4, 16 x 41 16.0 and 15.2), but callers size their workspaces by 128.
     const int64_t max_split = K / GNN_SPLIT_MIN_K;
     if (split > max_split) split = max_split;
     if (split > 4096) split = 4096;

@@ -1710,7 +1710,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     const gnn_tiles *tl = nullptr;
     const float *tile_coefs = nullptr;
     if (bl.active) {
-        int rc = gnn_plan_tiles(plan, lanes, esz == 2, !coef && gnn_bits_pay(layout.main_lines), stream, &tl);
+        int rc = gnn_plan_tiles(plan, lanes, esz == 2, !coef, layout.main_lines, stream, &tl);
         if (rc != GNN_OK) return rc;
         if (tl) {
             if (coef) {

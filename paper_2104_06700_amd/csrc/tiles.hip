@@ -1269,11 +1269,19 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, bool dense, hipStream_t
 }  // namespace
 
 // Builds the tile layout for rows of `lanes` x 16 bytes on first use; needs the source-blocked layout.
-int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, hipStream_t stream, const gnn_tiles **out) {
+int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, int64_t n_slices, hipStream_t stream, const gnn_tiles **out) {
     *out = nullptr;
     if (!plan || (lanes != 8 && lanes != 4 && lanes != 2)) return GNN_ERR_INVALID_ARG;
-    const bool dense = plain && lanes == 8 && !bf16;
+    const bool either = plain && lanes == 8 && !bf16, dense = either && gnn_bits_pay(n_slices);
     gnn_tiles &L = plan->tiles[dense ? GNN_TILES_PLAIN : level_of(lanes, bf16)];
+    if (!L.decided && either) {
+        const gnn_tiles &other = plan->tiles[dense ? level_of(lanes, bf16) : GNN_TILES_PLAIN];
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (other.active && (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
+            *out = &other;
+            return GNN_OK;
+        }
+    }
     if (!L.decided) {
         if (!plan->blk_decided) return GNN_ERR_INVALID_ARG;
         gnn_tiles B{};
@@ -1291,7 +1299,7 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, hipStream_t
         L = std::move(B);
         L.decided = true;
     }
-    if (dense && !L.active) return gnn_plan_tiles(plan, lanes, bf16, false, stream, out);
+    if (dense && !L.active) return gnn_plan_tiles(plan, lanes, bf16, false, n_slices, stream, out);
     if (L.active) *out = &L;
     return GNN_OK;
 }

@@ -221,3 +221,38 @@ def test_dense_cells_as_a_bit_matrix(n, rows, hot_lines, f, op_name):
     assert torch.equal(~torch.isfinite(Y), ~torch.isfinite(want)), "infinities and NaN"
     finite = hit & torch.isfinite(want)
     assert bool((Y[finite] > 1e33).all()) and bool((Y[:, 7:15][~hit[:, 7:15]].abs() < 1e6).all())
+
+
+@pytest.mark.parametrize("first_f,first_weighted,f", [(128, False, 64), (128, True, 128)])
+def test_a_captured_sum_takes_the_tiles_that_are_there(first_f, first_weighted, f):
+    """After an eager call whose tiles are of the other kind (with a bit matrix, or lists only), a sum that would build its own is captured:
+    it takes those, and every replay is right."""
+    n, rows = 600, 512
+    r = (synth.mix64(torch.arange(rows * n) + 7) & 0x7FFFFFFF) % 3 == 0
+    key = torch.cat([r.nonzero().reshape(-1), torch.arange(n) * n + 5]).unique()
+    el = synth.EdgeList(n=n, src=(key % n).to(torch.int32), dst=(key // n).to(torch.int32), meta={})
+    indptr, indices, *_ = host_csr(el)
+    dg = device_graph(el, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    dg.plan_fwd.set_blocking(min_degree=32, hot_lines=600, block_lines=1000, max_piece=48, rest_min_count=0)
+
+    def call(x, y, w):
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, w, x, y, n, x.shape[1], gnn.GNN_SUM, plan=dg.plan_fwd, flags=SLICED, max_slices=8)
+
+    x0 = synth.normal_features(n, first_f, 2).to(DEV)
+    call(x0, torch.empty_like(x0), torch.ones(len(key), device=DEV) if first_weighted else None)
+    X = synth.normal_features(n, f, 3)
+    xd, y = X.to(DEV), torch.empty(n, f, device=DEV)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(xd, y, None)
+    for rep in range(3):
+        Yo, S = oracle.aggregate_fwd(indptr, indices, X.numpy(), op=OP_CODE["sum"], nthreads=8, want_scale=True)
+        y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_close(y, Yo, S, False, f"replay {rep}")
+        X = X * 0.75
+        xd.copy_(X)
+        call(x0, torch.empty_like(x0), None)  # eager work between

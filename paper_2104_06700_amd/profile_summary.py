@@ -35,7 +35,8 @@ ROOT = os.path.dirname(PKG)
 
 # kernels that make up one aggregation call (everything else in a trace is once-per-plan setup; so are tile_fill_kernel and
 # tile_refill_kernel here, which a call launches only for weights that are not bound to the plan or that meet a factor in bf16)
-CALL_KERNELS = ("aggregate_kernel", "tile_kernel", "piece_kernel", "blk_finalize_kernel", "hub_finalize_kernel", "pad_rows_kernel")
+CALL_KERNELS = ("aggregate_kernel", "gather_kernel", "run_kernel", "tile_kernel", "dense_split_kernel", "dense_kernel", "dense_add_kernel", "piece_kernel",
+                "blk_finalize_kernel", "hub_finalize_kernel", "pad_rows_kernel")
 CALIB_KERNEL = "copy16_kernel"
 CALIB_BYTES = 1 << 30  # the calibration copy reads 1 GiB and writes 1 GiB
 

@@ -71,7 +71,9 @@ typedef struct gnn_opts {
                               for _fwd, plan of the transposed graph for _bwd); NULL = un-binned
                               wavefront-per-row kernel, no hub splitting.  A hot call may grow
                               plan-owned buffers on first use (see gnn_plan_prepare); two calls
-                              sharing one plan must not overlap in time. */
+                              sharing one plan must not overlap in time.  A graph that has captured
+                              a call uses the plan's buffers of that moment: they stay, also where
+                              later calls take larger ones, until the plan is destroyed. */
     void *workspace;       /* optional device scratch for hub-row partial sums; NULL = plan-owned
                               scratch, grown (allocation!) on the first call that needs more */
     int64_t workspace_bytes;

@@ -1508,9 +1508,9 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             if (ext_bytes < layout.bytes || reinterpret_cast<uintptr_t>(ext_tables) % 128) return GNN_ERR_INVALID_ARG;
             tables = ext_tables;
         } else {
-            rc = gnn_plan_padded(plan, layout.bytes);
+            rc = gnn_plan_padded(plan, layout.bytes, stream);
             if (rc != GNN_OK) return rc;
-            tables = plan->padded;
+            tables = plan->padded.p;
         }
         if (!(o.flags & GNN_FLAG_NO_RANK_ORDER) && plan->n_edges > 0) {
             rc = gnn_plan_rank_indices(plan, indptr, indices, (o.flags & GNN_FLAG_FORCE_COLD_HINTS) != 0, stream, &rl);
@@ -1589,9 +1589,9 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         } else if (o.workspace) {
             return GNN_ERR_INVALID_ARG;
         } else {
-            int rc = gnn_plan_reserve(plan, F);
+            int rc = gnn_plan_room(plan, plan->scratch, need, stream);
             if (rc != GNN_OK) return rc;
-            partial = static_cast<float *>(plan->scratch);
+            partial = static_cast<float *>(plan->scratch.p);
         }
         if (reinterpret_cast<uintptr_t>(partial) % 16) return GNN_ERR_INVALID_ARG;
     }
@@ -1717,7 +1717,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
                 rc = gnn_plan_tile_coefs(plan, tl, w, edge_scale, src_mode, weights == GNN_WEIGHTS_BOUND, stream, &tile_coefs);
                 if (rc != GNN_OK) return rc;
             }
-            rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), lanes * max_vec);
+            rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), lanes * max_vec, stream);
             if (rc != GNN_OK) return rc;
         }
     }
@@ -1778,7 +1778,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     const int tile_groups = tl ? gnn_tile_groups(tl, int(layout.main_lines)) : 0;
     if (tl) {
         const int rc = gnn_launch_tiles(tl, o.dtype == GNN_BF16, gathered, layout.table_stride * esz, int(layout.main_lines),
-                                        tile_coefs, static_cast<float *>(plan->tile_partial), stream);
+                                        tile_coefs, static_cast<float *>(plan->tile_partial.p), stream);
         if (rc != GNN_OK) { finish_overlap(); return rc; }
     }
 
@@ -1854,7 +1854,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         const bool blocked = bl.active && segs[gi].tail_slice < 0;
         if (blocked) {
             const int line_floats = lanes * max_vec;
-            int rc = gnn_plan_blocked_partial(plan, 1 << log2_s, line_floats);
+            int rc = gnn_plan_blocked_partial(plan, 1 << log2_s, line_floats, stream);
             if (rc != GNN_OK) { finish_overlap(); return rc; }
             PieceArgs pa{};
             pa.pieces = tl ? tl->left.pieces : bl.pieces;
@@ -1871,7 +1871,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             pa.scale_blk = scale_blk;
             pa.X = a.X;
             pa.slice_stride = layout.table_stride;
-            pa.partial = static_cast<float *>(plan->blk_partial);
+            pa.partial = static_cast<float *>(plan->blk_partial.p);
             pa.log2_slices = log2_s;
             const int64_t per_block = int64_t(64 / lanes) * kWavesPerBlock;
             const int64_t pblocks = ((pa.n_pieces + per_block - 1) / per_block) << log2_s;
@@ -1880,7 +1880,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             const dim3 pgrid(static_cast<unsigned>(pblocks)), fgrid(static_cast<unsigned>((bl.n_hot * n_sl * lanes + 255) / 256));
             const int32_t *hot_rows = plan->row_perm + bl.hot_begin;
             const OwnRowSrc own = own_row_src(f0);
-            const float *tile_partial = tl ? static_cast<const float *>(plan->tile_partial) + f0 / line_elems * tl->n_parts * line_floats : nullptr;
+            const float *tile_partial = tl ? static_cast<const float *>(plan->tile_partial.p) + f0 / line_elems * tl->n_parts * line_floats : nullptr;
             const int64_t tile_group_stride = tl ? layout.main_lines * tl->n_parts * line_floats : 0;
             const uint32_t *rowbase = tl ? tl->left.rowbase : bl.rowbase, *part_base = tl ? tl->part_base : nullptr;
             auto launch = [&](auto elem, auto n_lanes) {
@@ -1985,14 +1985,14 @@ int gnn_packed_target_for(gnn_plan *plan, const void *indptr, const int32_t *ind
     if (!(layout.padded_copy && layout.slice_major)) return GNN_OK;  // that call gathers rows where they lie
     const int64_t lines = (F + 31) / 32;
     if (lines < 2 || lines > 256) return GNN_OK;
-    int rc = gnn_plan_padded(plan, layout.bytes);
+    int rc = gnn_plan_padded(plan, layout.bytes, stream);
     if (rc != GNN_OK) return rc;
     gnn_rank_layout rl{};
     rc = gnn_plan_rank_indices(plan, indptr, indices, false, stream, &rl);
     if (rc != GNN_OK) return rc;
     if (!rl.rank) return GNN_OK;
     out->active = true;
-    out->base = static_cast<float *>(plan->padded);
+    out->base = static_cast<float *>(plan->padded.p);
     out->table_stride = layout.table_stride;
     out->main_cols = int32_t(F - layout.tail_elems);
     out->tail = layout.tail_elems > 0 ? out->base + layout.main_lines * layout.table_stride : nullptr;

@@ -868,9 +868,9 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
     const bool has_hub = plan && plan->n_chunks > 0;
     if (has_hub) {
         a.ldp = gnn_partial_ld(d);
-        rc = gnn_plan_reserve(plan, 2 * a.ldp);  // values and winners
+        rc = gnn_plan_room(plan, plan->scratch, gnn_plan_workspace_bytes(plan, 2 * a.ldp), c.stream);  // values and winners
         if (rc != GNN_OK) return rc;
-        a.pval = static_cast<float *>(plan->scratch);
+        a.pval = static_cast<float *>(plan->scratch.p);
         a.parg = reinterpret_cast<int32_t *>(a.pval + plan->n_chunks * a.ldp);
     }
 
@@ -894,11 +894,11 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         const gnn_layout L = gnn_choose_layout(plan, N, d, 4, c.ldv, reinterpret_cast<uintptr_t>(fV) % 128 == 0, c.o.flags,
                                          c.o.max_slices);
         if (L.padded_copy && d * 4 > 128) {  // rows of one line gain nothing from a copy in their own order
-            rc = gnn_plan_padded(plan, N * L.ld_pad * 4);
+            rc = gnn_plan_padded(plan, N * L.ld_pad * 4, c.stream);
             if (rc != GNN_OK) return rc;
-            rc = gnn_pad_rows_f32(fV, c.ldv, static_cast<float *>(plan->padded), L.ld_pad, N, d, plan->col_counts, c.stream);
+            rc = gnn_pad_rows_f32(fV, c.ldv, static_cast<float *>(plan->padded.p), L.ld_pad, N, d, plan->col_counts, c.stream);
             if (rc != GNN_OK) return rc;
-            a.fV = static_cast<const float *>(plan->padded);
+            a.fV = static_cast<const float *>(plan->padded.p);
             a.ldv = L.ld_pad;
         }
         const int64_t line = 32;  // floats per 128-byte line

@@ -265,17 +265,9 @@ extern "C" GNN_API int gnn_plan_export_blocked(const gnn_plan *plan, int32_t *in
     return GNN_OK;
 }
 
-int gnn_plan_blocked_partial(gnn_plan *plan, int slices, int line_floats) {
+int gnn_plan_blocked_partial(gnn_plan *plan, int slices, int line_floats, hipStream_t stream) {
     if (!plan || slices < 1 || line_floats < 1) return GNN_ERR_INVALID_ARG;
-    const int64_t need = plan->blk_n_pieces * int64_t(slices) * line_floats * int64_t(sizeof(float));
-    if (need <= plan->blk_partial_bytes) return GNN_OK;
-    (void)hipGetLastError();
-    gnn_dev_free(plan->blk_partial);
-    plan->blk_partial = nullptr;
-    plan->blk_partial_bytes = 0;
-    if (gnn_dev_alloc_bytes(&plan->blk_partial, size_t(need)) != GNN_OK) return GNN_ERR_ALLOC;
-    plan->blk_partial_bytes = need;
-    return GNN_OK;
+    return gnn_plan_room(plan, plan->blk_partial, plan->blk_n_pieces * int64_t(slices) * line_floats * int64_t(sizeof(float)), stream);
 }
 
 int gnn_plan_blocked_edge_scale(gnn_plan *plan, int mode, hipStream_t stream, const float **out) {

@@ -57,6 +57,14 @@ struct gnn_tiles {
 };
 constexpr int GNN_TILES_PLAIN = 6;  // number in gnn_plan::tiles of the layout with a bit matrix
 
+// Device memory of a plan that grows with what calls ask of it (gnn_plan_room).  recorded: a captured call has used it, so a graph may hold
+// its address.
+struct gnn_grown {
+    void *p = nullptr;
+    int64_t bytes = 0;
+    bool recorded = false;
+};
+
 // One plan = one graph orientation.  All pointers are device memory owned by
 // the plan unless marked host.
 struct gnn_plan {
@@ -78,9 +86,8 @@ struct gnn_plan {
     int64_t n_chunks = 0;
     int64_t *chunks = nullptr;        // [n_chunks * 3] (row, e_begin, e_end)
     int64_t *hub_chunk_offsets = nullptr;  // [n_hub_rows + 1] first piece of each hub row
-    // plan-owned scratch for hub partial sums
-    void *scratch = nullptr;
-    int64_t scratch_bytes = 0;
+    gnn_grown scratch;                // hub partial sums
+    std::vector<void *> retired;      // outgrown memory that a graph may still use, until the plan goes
     const void *indptr_seen = nullptr;  // the indptr the plan was built from (sanity check only)
     // per-edge factor of the gathered vertex, streamed by the hot kernels:
     // [0] 1/max(c,1)   [1] 1/sqrt(max(c,1))   [2] 1/(c+1), c = col_counts[indices[e]]; built on first use
@@ -91,9 +98,7 @@ struct gnn_plan {
     // whether XCD column slices can keep more useful rows in L2.
     int64_t bucket_vertices[256] = {0};
     int64_t bucket_edges[256] = {0};
-    // copy of the gathered matrix with rows padded to whole 128-byte lines (grown on first use)
-    void *padded = nullptr;
-    int64_t padded_bytes = 0;
+    gnn_grown padded;                 // copy of the gathered matrix with rows padded to whole 128-byte lines
     // copy of `indices` in which bit 31 marks the rarely gathered ("cold") sources; built on first
     // use when the plan's graph is in the regime where non-temporal loads of cold rows pay
     int32_t *cold_indices = nullptr;
@@ -101,6 +106,7 @@ struct gnn_plan {
     int32_t cold_threshold = 0;  // sources gathered fewer times than this are cold
     int32_t cold_forced = 0;     // the copy was built under GNN_FLAG_FORCE_COLD_HINTS (a call without it rebuilds)
     int32_t rank_forced = 0;     // likewise for rank_indices
+    bool cold_recorded = false, rank_recorded = false;  // as in gnn_grown
     // Rank layout of the padded copy: rank[v] = position of v by descending column count; the copy
     // stores row v at row rank[v] and the kernels gather through rank_indices[e] =
     // rank[indices[e]] (bit 31: cold).  Built on first use.
@@ -142,12 +148,15 @@ struct gnn_plan {
     float *blk_bound_w = nullptr;
     bool bound_w_stale = false;       // the copy is older than the last binding
     int64_t bound_w_version = 0;      // number of the last binding
-    void *blk_partial = nullptr;      // fp32 partial sums of one launch: [slices][blk_n_pieces][floats per line]
-    int64_t blk_partial_bytes = 0;
+    gnn_grown blk_partial;            // fp32 partial sums of one launch: [slices][blk_n_pieces][floats per line]
     gnn_tiles tiles[7];               // for lines of 128, 64 and 32 bytes of fp32, then of bf16; [GNN_TILES_PLAIN]: see gnn_plan_tiles
-    void *tile_partial = nullptr;     // their partial lines: [groups][slices][hot rows][floats per line]
-    int64_t tile_partial_bytes = 0;
+    gnn_grown tile_partial;           // their partial lines: [groups][slices][hot rows][floats per line]
 };
+
+// Makes `b` at least `bytes` large, for a call on `stream` (allocation on growth; the old contents are lost).  What a graph may hold the
+// address of is kept beside it and freed with the plan: a replay writes there whatever other calls have asked for meanwhile.
+int gnn_plan_room(gnn_plan *plan, gnn_grown &b, int64_t bytes, hipStream_t stream);
+void gnn_plan_drop(gnn_plan *plan, void *p, bool recorded);  // frees p, or keeps it so
 
 // Source blocking (the GPU reading of Section 4.2's blocks of source vertices, applied to the long
 // rows only).  Rows of at least `min_degree` edges are cut into pieces along blocks of source RANK
@@ -174,8 +183,8 @@ struct gnn_blocked_layout {
 // Builds the layout on first use (allocation; needs the rank layout) and reports it.  Inactive when
 // the graph or the plan's thresholds do not suit it.
 int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn_blocked_layout *out);
-// Makes plan->blk_partial large enough for `slices` column slices of `line_floats` floats per piece.
-int gnn_plan_blocked_partial(gnn_plan *plan, int slices, int line_floats);
+// Makes plan->blk_partial large enough, for a call on `stream`, for `slices` column slices of `line_floats` floats per piece.
+int gnn_plan_blocked_partial(gnn_plan *plan, int slices, int line_floats, hipStream_t stream);
 // The plan's per-edge factor stream `mode` (gnn_plan_edge_scale, which must have been built) in the order
 // of the block-major index array; built on first use (allocation).
 int gnn_plan_blocked_edge_scale(gnn_plan *plan, int mode, hipStream_t stream, const float **out);
@@ -199,7 +208,7 @@ int gnn_plan_tile_coef_room(gnn_plan *plan, const gnn_tiles *tiles, hipStream_t 
 // Groups a launch over n_slices column slices splits the tiles into, each with a partial line of its own per row.
 int gnn_tile_groups(const gnn_tiles *t, int n_slices);
 // Makes plan->tile_partial large enough for such a launch.
-int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats);
+int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats, hipStream_t stream);
 int gnn_build_pieces(int64_t n_hot, int n_blocks, int64_t max_piece, const uint32_t *cell_count, const uint32_t *edge_off,
                      uint32_t *cell_pieces, uint32_t *sums, bool want_block, hipStream_t stream, gnn_piece_list *out);
 int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,
@@ -211,6 +220,7 @@ int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice
 // Blocks of more than GNN_POOL_MAX_BLOCK bytes are not kept: they come from the driver and go back to it, which waits for the
 // device, so the scratch of an asynchronous call is cut into blocks that are no larger.
 constexpr int64_t GNN_POOL_MAX_BLOCK = int64_t(512) << 20;
+bool gnn_capturing(hipStream_t stream);
 int gnn_dev_alloc_bytes(void **p, size_t bytes, hipStream_t stream);
 int gnn_dev_alloc_bytes(void **p, size_t bytes);
 void gnn_dev_free(void *p);
@@ -466,7 +476,7 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
 }
 
 // Makes plan->padded at least `bytes` large (allocation on growth).
-int gnn_plan_padded(gnn_plan *plan, int64_t bytes);
+int gnn_plan_padded(gnn_plan *plan, int64_t bytes, hipStream_t stream);
 
 // The plan's index copy with cold sources flagged in bit 31, or nullptr when cold hints do not pay
 // for this graph (see plan.hip).  force: build it whatever the graph (tests).  Builds on first use

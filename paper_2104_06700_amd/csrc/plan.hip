@@ -403,9 +403,10 @@ int gnn_plan_cold_indices(gnn_plan *plan, const int32_t *indices, bool force, hi
     *out = nullptr;
     if (!plan || plan->n_edges <= 0) return GNN_OK;
     if (plan->cold_decided && plan->cold_forced != (force ? 1 : 0)) {  // built under the other rule: build again
-        gnn_dev_free(plan->cold_indices);
+        gnn_plan_drop(plan, plan->cold_indices, plan->cold_recorded);
         plan->cold_indices = nullptr;
         plan->cold_decided = 0;
+        plan->cold_recorded = false;
     }
     if (!plan->cold_decided) {
         const int64_t warm = force ? (plan->n_rows + 3) / 4 : int64_t(5) * 32768;
@@ -438,6 +439,7 @@ int gnn_plan_cold_indices(gnn_plan *plan, const int32_t *indices, bool force, hi
         plan->cold_forced = force ? 1 : 0;
     }
     *out = plan->cold_indices;
+    if (*out && !plan->cold_recorded) plan->cold_recorded = gnn_capturing(stream);
     return GNN_OK;
 }
 
@@ -552,12 +554,13 @@ int gnn_plan_rank_indices(gnn_plan *plan, const void *indptr, const int32_t *ind
     *out = gnn_rank_layout{};
     if (!plan || plan->n_edges <= 0 || plan->n_rows <= 0) return GNN_OK;
     if (plan->rank_indices && plan->rank_forced != (force_cold ? 1 : 0)) {  // flagged under the other rule: build again
-        gnn_dev_free(plan->rank_indices);
-        gnn_dev_free(plan->p_indptr);
-        gnn_dev_free(plan->p_chunks);
+        gnn_plan_drop(plan, plan->rank_indices, plan->rank_recorded);
+        gnn_plan_drop(plan, plan->p_indptr, plan->rank_recorded);
+        gnn_plan_drop(plan, plan->p_chunks, plan->rank_recorded);
         plan->rank_indices = nullptr;
         plan->p_indptr = nullptr;
         plan->p_chunks = nullptr;
+        plan->rank_recorded = false;
     }
     if (!plan->rank_indices) {
         if (!indices || !indptr) return GNN_ERR_INVALID_ARG;
@@ -597,6 +600,7 @@ int gnn_plan_rank_indices(gnn_plan *plan, const void *indptr, const int32_t *ind
         plan->rank_indices = idx;
         plan->rank_forced = force_cold ? 1 : 0;
     }
+    if (!plan->rank_recorded) plan->rank_recorded = gnn_capturing(stream);
     out->rank = plan->rank;
     out->indices = plan->rank_indices;
     out->cold_pays = false;
@@ -629,17 +633,39 @@ double gnn_plan_top_share(const gnn_plan *plan, int64_t K) {
 
 extern "C" GNN_API double gnn_plan_gather_share(const gnn_plan *plan, int64_t K) { return gnn_plan_top_share(plan, K); }
 
-int gnn_plan_padded(gnn_plan *plan, int64_t bytes) {
+void gnn_plan_drop(gnn_plan *plan, void *p, bool recorded) {
+    if (p && recorded) {
+        try {
+            plan->retired.push_back(p);
+        } catch (const std::bad_alloc &) {  // stays allocated
+        }
+    } else {
+        gnn_dev_free(p);
+    }
+}
+
+int gnn_plan_room(gnn_plan *plan, gnn_grown &b, int64_t bytes, hipStream_t stream) {
+    if (bytes > b.bytes) {
+        (void)hipGetLastError();
+        gnn_plan_drop(plan, b.p, b.recorded);
+        b = gnn_grown{};
+        if (gnn_dev_alloc_bytes(&b.p, size_t(bytes)) != GNN_OK) return GNN_ERR_ALLOC;
+        b.bytes = bytes;
+    }
+    if (!b.recorded) b.recorded = gnn_capturing(stream);
+    return GNN_OK;
+}
+
+int gnn_plan_padded(gnn_plan *plan, int64_t bytes, hipStream_t stream) {
     if (!plan || bytes < 0) return GNN_ERR_INVALID_ARG;
-    if (bytes <= plan->padded_bytes) return GNN_OK;
-    (void)hipGetLastError();
-    gnn_dev_free(plan->padded);
-    plan->padded = nullptr;
-    plan->padded_bytes = 0;
-    if (gnn_dev_alloc_bytes(&plan->padded, size_t(bytes)) != GNN_OK) return GNN_ERR_ALLOC;
+    const bool grows = bytes > plan->padded.bytes;
+    const int rc = gnn_plan_room(plan, plan->padded, bytes, stream);
+    if (rc != GNN_OK || !grows) return rc;
     // padding columns are never written again; clear them once so that they hold finite values
-    if (hipMemset(plan->padded, 0, bytes) != hipSuccess) return GNN_ERR_LAUNCH;
-    plan->padded_bytes = bytes;
+    if (hipMemset(plan->padded.p, 0, bytes) != hipSuccess) {
+        plan->padded.bytes = 0;  // not cleared
+        return GNN_ERR_LAUNCH;
+    }
     return GNN_OK;
 }
 
@@ -654,7 +680,7 @@ static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int6
         const int32_t *unused_idx = nullptr;  // the flagged index copy of the cold hints, where they pay
         return gnn_plan_cold_indices(plan, indices, false, stream, &unused_idx);
     }
-    int rc = gnn_plan_padded(plan, layout.bytes);
+    int rc = gnn_plan_padded(plan, layout.bytes, stream);
     if (rc != GNN_OK) return rc;
     gnn_rank_layout unused_rank{};  // built from the row pointers the plan was created from
     rc = gnn_plan_rank_indices(plan, plan->indptr_seen, indices, false, stream, &unused_rank);
@@ -667,11 +693,11 @@ static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int6
     const int line_floats = layout.line_lanes * (16 / esz);
     int slices = 1;
     while (slices < 8 && slices * 2 <= layout.main_lines) slices *= 2;
-    rc = gnn_plan_blocked_partial(plan, slices, line_floats);
+    rc = gnn_plan_blocked_partial(plan, slices, line_floats, stream);
     if (rc != GNN_OK) return rc;
     const gnn_tiles *tl = nullptr;
     rc = gnn_plan_tiles(plan, layout.line_lanes, esz == 2, weights == GNN_WEIGHTS_NONE, layout.main_lines, stream, &tl);
-    if (rc == GNN_OK && tl) rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), line_floats);
+    if (rc == GNN_OK && tl) rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), line_floats, stream);
     const float *unused = nullptr;
     if (rc == GNN_OK && weights == GNN_WEIGHTS_BOUND) rc = gnn_plan_blocked_bound_weights(plan, stream, &unused);
     if (rc != GNN_OK || !tl || weights == GNN_WEIGHTS_NONE) return rc;
@@ -713,7 +739,7 @@ extern "C" GNN_API void gnn_plan_destroy(gnn_plan *plan) {
     gnn_dev_free(plan->edge_scale[0]);
     gnn_dev_free(plan->edge_scale[1]);
     gnn_dev_free(plan->edge_scale[2]);
-    gnn_dev_free(plan->padded);
+    gnn_dev_free(plan->padded.p);
     gnn_dev_free(plan->cold_indices);
     gnn_dev_free(plan->rank);
     gnn_dev_free(plan->rank_indices);
@@ -726,10 +752,10 @@ extern "C" GNN_API void gnn_plan_destroy(gnn_plan *plan) {
     gnn_dev_free(plan->blk_piece_block);
     gnn_dev_free(plan->blk_pieces);
     gnn_dev_free(plan->blk_rowbase);
-    gnn_dev_free(plan->blk_partial);
+    gnn_dev_free(plan->blk_partial.p);
     gnn_dev_free(plan->blk_cell_off);
     for (gnn_tiles &t : plan->tiles) gnn_tiles_free(t);
-    gnn_dev_free(plan->tile_partial);
+    gnn_dev_free(plan->tile_partial.p);
     for (int i = 0; i < 3; ++i) gnn_dev_free(plan->blk_edge_scale[i]);
     gnn_dev_free(plan->blk_bound_w);
     if (plan->row_info) gnn_dev_free(plan->row_info);  // with row_perm behind it
@@ -737,7 +763,8 @@ extern "C" GNN_API void gnn_plan_destroy(gnn_plan *plan) {
     gnn_dev_free(plan->col_counts);
     gnn_dev_free(plan->chunks);
     gnn_dev_free(plan->hub_chunk_offsets);
-    gnn_dev_free(plan->scratch);
+    gnn_dev_free(plan->scratch.p);
+    for (void *p : plan->retired) gnn_dev_free(p);
     delete plan;
 }
 
@@ -949,13 +976,5 @@ extern "C" GNN_API int64_t gnn_plan_workspace_bytes(const gnn_plan *plan, int64_
 
 extern "C" GNN_API int gnn_plan_reserve(gnn_plan *plan, int64_t F) {
     if (!plan || F < 0) return GNN_ERR_INVALID_ARG;
-    const int64_t need = gnn_plan_workspace_bytes(plan, F);
-    if (need <= plan->scratch_bytes) return GNN_OK;
-    (void)hipGetLastError();
-    gnn_dev_free(plan->scratch);
-    plan->scratch = nullptr;
-    plan->scratch_bytes = 0;
-    if (gnn_dev_alloc_bytes(&plan->scratch, size_t(need)) != GNN_OK) return GNN_ERR_ALLOC;
-    plan->scratch_bytes = need;
-    return GNN_OK;
+    return gnn_plan_room(plan, plan->scratch, gnn_plan_workspace_bytes(plan, F), nullptr);
 }

@@ -109,15 +109,10 @@ std::vector<Block> put_idle(Device &d, Block b) {
     return out;
 }
 
-bool capturing(hipStream_t stream) {
-    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(stream, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
-}
-
 int allocate_from(void **out, size_t bytes, bool has_stream, hipStream_t stream) {
     *out = nullptr;
     // what is built into a fresh block must run now and not when a graph is replayed
-    if (has_stream && capturing(stream)) return GNN_ERR_ALLOC;
+    if (has_stream && gnn_capturing(stream)) return GNN_ERR_ALLOC;
     if (bytes > kMaxBlock) {
         if (hipMalloc(out, bytes) == hipSuccess) return GNN_OK;
         (void)hipGetLastError();
@@ -201,6 +196,11 @@ int allocate(void **out, size_t bytes, bool has_stream, hipStream_t stream) {
 }
 
 }  // namespace
+
+bool gnn_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
+}
 
 void gnn_pool_release() {
     Pool &P = pool();

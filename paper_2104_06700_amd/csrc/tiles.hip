@@ -1276,8 +1276,7 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, int64_t n_s
     gnn_tiles &L = plan->tiles[dense ? GNN_TILES_PLAIN : level_of(lanes, bf16)];
     if (!L.decided && either) {
         const gnn_tiles &other = plan->tiles[dense ? level_of(lanes, bf16) : GNN_TILES_PLAIN];
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (other.active && (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)) {
+        if (other.active && gnn_capturing(stream)) {
             *out = &other;
             return GNN_OK;
         }
@@ -1415,16 +1414,9 @@ int gnn_tile_groups(const gnn_tiles *t, int n_slices) {
     return g < 1 ? 1 : int(g);
 }
 
-int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats) {
+int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats, hipStream_t stream) {
     const int64_t need = int64_t(gnn_tile_groups(t, n_slices)) * n_slices * t->n_parts * line_floats * int64_t(sizeof(float)) + dense_bytes(t, n_slices);
-    if (need <= plan->tile_partial_bytes) return GNN_OK;
-    (void)hipGetLastError();
-    gnn_dev_free(plan->tile_partial);
-    plan->tile_partial = nullptr;
-    plan->tile_partial_bytes = 0;
-    if (gnn_dev_alloc_bytes(&plan->tile_partial, size_t(need)) != GNN_OK) return GNN_ERR_ALLOC;
-    plan->tile_partial_bytes = need;
-    return GNN_OK;
+    return gnn_plan_room(plan, plan->tile_partial, need, stream);
 }
 
 int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,

@@ -256,3 +256,61 @@ def test_a_captured_sum_takes_the_tiles_that_are_there(first_f, first_weighted, 
         X = X * 0.75
         xd.copy_(X)
         call(x0, torch.empty_like(x0), None)  # eager work between
+
+
+def _rows_with_a_third_of_all_sources(n, rows):
+    r = (synth.mix64(torch.arange(rows * n) + 7) & 0x7FFFFFFF) % 3 == 0
+    key = torch.cat([r.nonzero().reshape(-1), torch.arange(n) * n + 5]).unique()
+    return synth.EdgeList(n=n, src=(key % n).to(torch.int32), dst=(key // n).to(torch.int32), meta={})
+
+
+@pytest.mark.parametrize("first_f,first_weighted,f,later", [(128, True, 128, (128,)), (128, False, 64, (64, 512)), (64, False, 64, (128, 256))])
+def test_a_graph_keeps_the_memory_it_recorded(first_f, first_weighted, f, later):
+    """Calls that come after a capture and take more room (with tiles of their own, or wider) leave the graph its buffers: no plan that is
+    built meanwhile is written into by a replay, and the replays stay right."""
+    n = 9500
+    el = _rows_with_a_third_of_all_sources(n, 600)
+    indptr, indices, *_ = host_csr(el)
+    dg = device_graph(el, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    dg.plan_fwd.set_blocking(min_degree=32, hot_lines=9400, block_lines=1000, max_piece=48, rest_min_count=0)
+
+    def call(x, y, w=None):
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, w, x, y, n, x.shape[1], gnn.GNN_SUM, plan=dg.plan_fwd, flags=SLICED, max_slices=8)
+
+    x0 = synth.normal_features(n, first_f, 2).to(DEV)
+    call(x0, torch.empty_like(x0), torch.ones(el.e, device=DEV) if first_weighted else None)
+    X = synth.normal_features(n, f, 3)
+    xd, y = X.to(DEV), torch.empty(n, f, device=DEV)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(xd, y)
+    for width in later:
+        x = synth.normal_features(n, width, 4).to(DEV)
+        call(x, torch.empty_like(x))
+
+    others, m = [], 4000  # the arrays of their plans fit free blocks of 0.1 to 10 MB
+    while m < 500000:
+        o = synth.erdos_renyi_directed(m, 4 * m, 5, device=DEV)
+        g = gnn.build_device_graph(o.dst, o.src, m)
+        v, out = torch.ones(m, 8, device=DEV), [torch.empty(m, 8, device=DEV) for _ in range(2)]
+        gnn.gnn_aggregate_fwd(g.indptr, g.indices, None, v, out[0], m, 8, gnn.GNN_SUM, plan=g.plan_fwd)
+        others.append((g, v, out, m, g.plan_fwd.export()))
+        m = m * 7 // 5
+    for rep in range(3):
+        Yo, S = oracle.aggregate_fwd(indptr, indices, X.numpy(), op=OP_CODE["sum"], nthreads=8, want_scale=True)
+        y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_close(y, Yo, S, False, f"replay {rep}")
+        eager = torch.empty_like(y)
+        call(xd, eager)
+        assert_close(eager, Yo, S, False, f"eager {rep}")
+        X = X * 0.75
+        xd.copy_(X)
+    for g, v, out, m, before in others:
+        gnn.gnn_aggregate_fwd(g.indptr, g.indices, None, v, out[1], m, 8, gnn.GNN_SUM, plan=g.plan_fwd)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1]), m
+        assert all(np.array_equal(a, b) for a, b in zip(before, g.plan_fwd.export())), m

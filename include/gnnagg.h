@@ -506,6 +506,9 @@ GNN_API int gnn_plan_bind_edge_weights(gnn_plan *plan, const float *edge_w /* de
  * rows served as pieces, their edges, pieces, blocks. */
 GNN_API int gnn_plan_blocked_sizes(const gnn_plan *plan, int64_t *n_rows, int64_t *n_edges, int64_t *n_pieces,
                                    int32_t *n_blocks);
+/* Rows whose edges to the most-gathered sources the plan keeps as a bit matrix, for fp32 sums without
+ * coefficients over three 128-byte lines and more (0: it has none, or has not built it yet). */
+GNN_API int64_t gnn_plan_bit_rows(const gnn_plan *plan);
 /* Host copies for bit-exact checks: indices int32[n_edges] (source ranks in block-major piece
  * order), epos uint32[n_edges] (CSR position of each), pieces int32[n_pieces*4] as (begin, length,
  * partial slot, row index within the blocked rows), rowbase uint32[n_rows+1], rank int32[N] (rank of

@@ -42,7 +42,8 @@ EXPORTED_SYMBOLS = (
     "gnn_validate_csr", "gnn_plan_default_params", "gnn_plan_create", "gnn_plan_destroy",
     "gnn_graph_build", "gnn_release_cached_memory",
     "gnn_plan_sizes", "gnn_plan_export", "gnn_plan_gather_share", "gnn_plan_workspace_bytes", "gnn_plan_reserve",
-    "gnn_plan_prepare", "gnn_plan_set_blocking", "gnn_plan_bind_edge_weights", "gnn_plan_blocked_sizes", "gnn_plan_export_blocked",
+    "gnn_plan_prepare", "gnn_plan_set_blocking", "gnn_plan_bind_edge_weights", "gnn_plan_blocked_sizes", "gnn_plan_bit_rows",
+    "gnn_plan_export_blocked",
     "gnn_ap_fwd", "gnn_ap_bwd_vertex", "gnn_ap_bwd_vertex_arg", "gnn_ap_bwd_vertex_arg_edges", "gnn_ap_bwd_edge",
     "gnn_matmul", "gnn_matmul_workspace_bytes",
     "gnn_sage_layer_fwd", "gnn_sage_layer_bwd", "gnn_sage_layer_saved_elems", "gnn_sage_layer_workspace_bytes",
@@ -140,6 +141,8 @@ def load_library() -> ctypes.CDLL:
         lib.gnn_plan_bind_edge_weights.argtypes = [vp, vp, vp]
         lib.gnn_plan_blocked_sizes.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(i64), ctypes.POINTER(i64),
                                                ctypes.POINTER(ctypes.c_int32)]
+        lib.gnn_plan_bit_rows.argtypes = [vp]
+        lib.gnn_plan_bit_rows.restype = i64
         lib.gnn_plan_export_blocked.argtypes = [vp, vp, vp, vp, vp, vp]
         ap = ctypes.POINTER(GnnApOpts)
         lib.gnn_ap_fwd.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i32, i32, ap]
@@ -294,6 +297,10 @@ class Plan:
         _check("gnn_plan_blocked_sizes", load_library().gnn_plan_blocked_sizes(
             self.handle, ctypes.byref(r), ctypes.byref(e), ctypes.byref(p), ctypes.byref(b)))
         return r.value, e.value, p.value, b.value
+
+    def bit_rows(self) -> int:
+        """Rows that the plan keeps a bit matrix for (0: none, or not built yet)."""
+        return int(load_library().gnn_plan_bit_rows(self.handle))
 
     def export_blocked(self):
         """Host copies of the source-blocked layout: (indices int32[E_b], epos uint32[E_b], pieces int32[P,4],

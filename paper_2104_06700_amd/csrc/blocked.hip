@@ -265,6 +265,10 @@ extern "C" GNN_API int gnn_plan_export_blocked(const gnn_plan *plan, int32_t *in
     return GNN_OK;
 }
 
+extern "C" GNN_API int64_t gnn_plan_bit_rows(const gnn_plan *plan) {
+    return plan ? int64_t(plan->tiles[GNN_TILES_PLAIN].dense_groups) * GNN_BIT_ROWS : 0;
+}
+
 int gnn_plan_blocked_partial(gnn_plan *plan, int slices, int line_floats, hipStream_t stream) {
     if (!plan || slices < 1 || line_floats < 1) return GNN_ERR_INVALID_ARG;
     return gnn_plan_room(plan, plan->blk_partial, plan->blk_n_pieces * int64_t(slices) * line_floats * int64_t(sizeof(float)), stream);

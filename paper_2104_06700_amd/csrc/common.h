@@ -54,8 +54,10 @@ struct gnn_tiles {
     void *dense = nullptr;                       // the groups and their units
     uint32_t *dense_rows = nullptr;              // hot row of every row of the groups
     uint2 *dense_bits = nullptr;
+    uint32_t refused = 0;                        // calls since there was no room for it, with that one; 0: there was
 };
 constexpr int GNN_TILES_PLAIN = 6;  // number in gnn_plan::tiles of the layout with a bit matrix
+constexpr int GNN_BIT_ROWS = 256;   // rows of a group of it
 
 // Device memory of a plan that grows with what calls ask of it (gnn_plan_room).  recorded: a captured call has used it, so a graph may hold
 // its address.

@@ -651,7 +651,8 @@ __global__ void __launch_bounds__(kTileThreads) tile_kernel(const TileArgs a) {
 // 5.2 -> 3.4 ms, where copying the tiles counts for most now; the call 6.83 -> 6.1, F=256 2.66 -> 2.50.  Error of the sums against 64 bits, 2-norm, normal
 // operands 8.1e-7 -> 3.2e-7, positive 4.2e-7 -> 1.2e-7, over 40 binary orders of magnitude 6.0e-7 -> 2.5e-7.
 constexpr int kDenseWaves = 4;                // of 64 rows each
-constexpr int kDenseRows = 64 * kDenseWaves;  // of a group
+constexpr int kDenseRows = GNN_BIT_ROWS;      // of a group
+static_assert(kDenseRows == 64 * kDenseWaves, "two tiles of 32 rows per wavefront");
 constexpr int kChunkSteps = 8, kChunk = 16 * kChunkSteps;  // sources that a workgroup has in LDS at a time
 // A row takes the tiles of which it has one line in so many (10 and 16: 233 K vertices, 115 M edges F=602 6.26 and 6.08 ms; 300 K, 120 M F=256
 // 2.82 and 2.85; 233 K directed, 80 M 2.00 and 2.12).
@@ -1266,6 +1267,13 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, bool dense, hipStream_t
     return GNN_OK;
 }
 
+// There was no room for the bit matrix: it is asked for again by the calls 1, 2, 4, 8, ... later, because asking costs the sort and two waits.
+bool worth_another_try(gnn_tiles &L) {
+    const bool now = (L.refused & (L.refused - 1)) == 0;
+    if (!now) ++L.refused;
+    return now;
+}
+
 }  // namespace
 
 // Builds the tile layout for rows of `lanes` x 16 bytes on first use; needs the source-blocked layout.
@@ -1274,15 +1282,18 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, int64_t n_s
     if (!plan || (lanes != 8 && lanes != 4 && lanes != 2)) return GNN_ERR_INVALID_ARG;
     const bool either = plain && lanes == 8 && !bf16, dense = either && gnn_bits_pay(n_slices);
     gnn_tiles &L = plan->tiles[dense ? GNN_TILES_PLAIN : level_of(lanes, bf16)];
-    if (!L.decided && either) {
-        const gnn_tiles &other = plan->tiles[dense ? level_of(lanes, bf16) : GNN_TILES_PLAIN];
-        if (other.active && gnn_capturing(stream)) {
-            *out = &other;
-            return GNN_OK;
-        }
-    }
+    auto lists = [&] { return gnn_plan_tiles(plan, lanes, bf16, false, n_slices, stream, out); };  // they serve these calls as well
     if (!L.decided) {
         if (!plan->blk_decided) return GNN_ERR_INVALID_ARG;
+        if (either && gnn_capturing(stream)) {
+            const gnn_tiles &other = plan->tiles[dense ? level_of(lanes, bf16) : GNN_TILES_PLAIN];
+            if (other.active) {
+                *out = &other;
+                return GNN_OK;
+            }
+            if (dense) return lists();
+        }
+        if (dense && !worth_another_try(L)) return lists();
         gnn_tiles B{};
         if (plan->blk_n_pieces > 0 && plan->blk_cell_off) {
             int rc;
@@ -1292,13 +1303,16 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, int64_t n_s
                 rc = GNN_ERR_ALLOC;
             }
             if (rc != GNN_OK || !B.active) gnn_tiles_free(B);
-            if (dense && rc == GNN_ERR_ALLOC) rc = GNN_OK;  // no room for the bits: lists only
+            if (dense && rc == GNN_ERR_ALLOC) {
+                ++L.refused;
+                return lists();
+            }
             if (rc != GNN_OK) return rc;
         }
         L = std::move(B);
         L.decided = true;
     }
-    if (dense && !L.active) return gnn_plan_tiles(plan, lanes, bf16, false, n_slices, stream, out);
+    if (dense && !L.active) return lists();
     if (L.active) *out = &L;
     return GNN_OK;
 }

@@ -1,6 +1,8 @@
 """Long rows gathered from source tiles staged in LDS: the dense cells of the source-blocked layout.  The graphs
 are dense enough that every block is staged; the cases put block and tile boundaries where they can go wrong (one
 line more or less than a tile, a last short tile, rows cut into parts, lists filled up to whole units)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -314,3 +316,34 @@ def test_a_graph_keeps_the_memory_it_recorded(first_f, first_weighted, f, later)
         torch.cuda.synchronize()
         assert torch.equal(out[0], out[1]), m
         assert all(np.array_equal(a, b) for a, b in zip(before, g.plan_fwd.export())), m
+
+
+def test_a_refused_capture_does_not_decide_for_later_calls():
+    """Nothing can be built in a capture: a call whose tiles are not there yet is refused, and the next eager call builds them."""
+    n, f = 1100, 128
+    el = _rows_with_a_third_of_all_sources(n, 600)
+    indptr, indices, *_ = host_csr(el)
+    dg = device_graph(el, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    dg.plan_fwd.set_blocking(min_degree=32, hot_lines=1099, block_lines=1000, max_piece=48, rest_min_count=0)
+    X = synth.normal_features(n, f, 3)
+    xd, y = X.to(DEV), torch.empty(n, f, device=DEV)
+
+    def call(x, y, flags=0):
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, None, x, y, n, x.shape[1], gnn.GNN_SUM, plan=dg.plan_fwd, flags=SLICED | flags, max_slices=8)
+
+    call(xd, y, gnn.GNN_FLAG_NO_SOURCE_BLOCKS)      # all a call takes but pieces and tiles
+    narrow = xd[:, :16].contiguous()
+    call(narrow, torch.empty_like(narrow))          # pieces
+    torch.cuda.synchronize()
+    assert dg.plan_fwd.blocked_sizes()[2] > 0 and dg.plan_fwd.bit_rows() == 0
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        o = gnn.GnnOpts(stream=torch.cuda.current_stream().cuda_stream, plan=dg.plan_fwd.handle, flags=SLICED, max_slices=8)
+        status = gnn.load_library().gnn_aggregate_fwd(dg.indptr.data_ptr(), dg.indices.data_ptr(), None, xd.data_ptr(), y.data_ptr(), n, f,
+                                                      gnn.GNN_SUM, ctypes.byref(o))
+    assert status == gnn.GNN_ERR_ALLOC
+    call(xd, y)
+    torch.cuda.synchronize()
+    assert dg.plan_fwd.bit_rows() >= 256
+    Yo, S = oracle.aggregate_fwd(indptr, indices, X.numpy(), op=OP_CODE["sum"], nthreads=8, want_scale=True)
+    assert_close(y, Yo, S, False, "after the refused capture")

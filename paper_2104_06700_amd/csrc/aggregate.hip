@@ -1710,14 +1710,10 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     const gnn_tiles *tl = nullptr;
     const float *tile_coefs = nullptr;
     if (bl.active) {
-        int rc = gnn_plan_tiles(plan, lanes, esz == 2, !coef, layout.main_lines, stream, &tl);
+        int rc = gnn_plan_tiles_with_room(plan, lanes, esz == 2, !coef, int(layout.main_lines), lanes * max_vec, stream, &tl);
         if (rc != GNN_OK) return rc;
-        if (tl) {
-            if (coef) {
-                rc = gnn_plan_tile_coefs(plan, tl, w, edge_scale, src_mode, weights == GNN_WEIGHTS_BOUND, stream, &tile_coefs);
-                if (rc != GNN_OK) return rc;
-            }
-            rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), lanes * max_vec, stream);
+        if (tl && coef) {
+            rc = gnn_plan_tile_coefs(plan, tl, w, edge_scale, src_mode, weights == GNN_WEIGHTS_BOUND, stream, &tile_coefs);
             if (rc != GNN_OK) return rc;
         }
     }

@@ -209,8 +209,8 @@ int gnn_plan_tile_coefs(gnn_plan *plan, const gnn_tiles *tiles, const float *w, 
 int gnn_plan_tile_coef_room(gnn_plan *plan, const gnn_tiles *tiles, hipStream_t stream);
 // Groups a launch over n_slices column slices splits the tiles into, each with a partial line of its own per row.
 int gnn_tile_groups(const gnn_tiles *t, int n_slices);
-// Makes plan->tile_partial large enough for such a launch.
-int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats, hipStream_t stream);
+// gnn_plan_tiles, and plan->tile_partial large enough for such a launch.
+int gnn_plan_tiles_with_room(gnn_plan *plan, int lanes, bool bf16, bool plain, int n_slices, int line_floats, hipStream_t stream, const gnn_tiles **out);
 int gnn_build_pieces(int64_t n_hot, int n_blocks, int64_t max_piece, const uint32_t *cell_count, const uint32_t *edge_off,
                      uint32_t *cell_pieces, uint32_t *sums, bool want_block, hipStream_t stream, gnn_piece_list *out);
 int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,

@@ -696,8 +696,7 @@ static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int6
     rc = gnn_plan_blocked_partial(plan, slices, line_floats, stream);
     if (rc != GNN_OK) return rc;
     const gnn_tiles *tl = nullptr;
-    rc = gnn_plan_tiles(plan, layout.line_lanes, esz == 2, weights == GNN_WEIGHTS_NONE, layout.main_lines, stream, &tl);
-    if (rc == GNN_OK && tl) rc = gnn_plan_tile_partial(plan, tl, int(layout.main_lines), line_floats, stream);
+    rc = gnn_plan_tiles_with_room(plan, layout.line_lanes, esz == 2, weights == GNN_WEIGHTS_NONE, int(layout.main_lines), line_floats, stream, &tl);
     const float *unused = nullptr;
     if (rc == GNN_OK && weights == GNN_WEIGHTS_BOUND) rc = gnn_plan_blocked_bound_weights(plan, stream, &unused);
     if (rc != GNN_OK || !tl || weights == GNN_WEIGHTS_NONE) return rc;

@@ -1283,6 +1283,7 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, int64_t n_s
     const bool either = plain && lanes == 8 && !bf16, dense = either && gnn_bits_pay(n_slices);
     gnn_tiles &L = plan->tiles[dense ? GNN_TILES_PLAIN : level_of(lanes, bf16)];
     auto lists = [&] { return gnn_plan_tiles(plan, lanes, bf16, false, n_slices, stream, out); };  // they serve these calls as well
+    if (dense && !gnn_capturing(stream) && !worth_another_try(L)) return lists();
     if (!L.decided) {
         if (!plan->blk_decided) return GNN_ERR_INVALID_ARG;
         if (either && gnn_capturing(stream)) {
@@ -1293,7 +1294,6 @@ int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, int64_t n_s
             }
             if (dense) return lists();
         }
-        if (dense && !worth_another_try(L)) return lists();
         gnn_tiles B{};
         if (plan->blk_n_pieces > 0 && plan->blk_cell_off) {
             int rc;
@@ -1428,9 +1428,34 @@ int gnn_tile_groups(const gnn_tiles *t, int n_slices) {
     return g < 1 ? 1 : int(g);
 }
 
-int gnn_plan_tile_partial(gnn_plan *plan, const gnn_tiles *t, int n_slices, int line_floats, hipStream_t stream) {
-    const int64_t need = int64_t(gnn_tile_groups(t, n_slices)) * n_slices * t->n_parts * line_floats * int64_t(sizeof(float)) + dense_bytes(t, n_slices);
-    return gnn_plan_room(plan, plan->tile_partial, need, stream);
+static int64_t tile_partial_bytes(const gnn_tiles *t, int n_slices, int line_floats) {
+    return int64_t(gnn_tile_groups(t, n_slices)) * n_slices * t->n_parts * line_floats * int64_t(sizeof(float)) + dense_bytes(t, n_slices);
+}
+
+int gnn_plan_tiles_with_room(gnn_plan *plan, int lanes, bool bf16, bool plain, int n_slices, int line_floats, hipStream_t stream, const gnn_tiles **out) {
+    int rc = gnn_plan_tiles(plan, lanes, bf16, plain, n_slices, stream, out);
+    if (rc != GNN_OK || !*out) return rc;
+    const int64_t need = tile_partial_bytes(*out, n_slices, line_floats);
+    if (!(*out)->dense_groups) return gnn_plan_room(plan, plan->tile_partial, need, stream);
+    // The split operand and the sums of the bit matrix take many times what the lists take.  Where that is refused, or would have to be
+    // asked for in a capture while the lists have theirs, the lists serve the call.
+    gnn_tiles &bits = plan->tiles[GNN_TILES_PLAIN];
+    const gnn_tiles &lists = plan->tiles[level_of(lanes, bf16)];
+    if (need > plan->tile_partial.bytes && lists.active && tile_partial_bytes(&lists, n_slices, line_floats) <= plan->tile_partial.bytes &&
+        gnn_capturing(stream)) {
+        *out = &lists;
+        return gnn_plan_room(plan, plan->tile_partial, 0, stream);
+    }
+    rc = gnn_plan_room(plan, plan->tile_partial, need, stream);
+    if (rc != GNN_ERR_ALLOC) {
+        bits.refused = 0;
+        return rc;
+    }
+    ++bits.refused;
+    (void)hipGetLastError();
+    rc = gnn_plan_tiles(plan, lanes, bf16, false, n_slices, stream, out);
+    if (rc != GNN_OK || !*out) return rc;
+    return gnn_plan_room(plan, plan->tile_partial, tile_partial_bytes(*out, n_slices, line_floats), stream);
 }
 
 int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,

@@ -347,3 +347,35 @@ def test_a_refused_capture_does_not_decide_for_later_calls():
     assert dg.plan_fwd.bit_rows() >= 256
     Yo, S = oracle.aggregate_fwd(indptr, indices, X.numpy(), op=OP_CODE["sum"], nthreads=8, want_scale=True)
     assert_close(y, Yo, S, False, "after the refused capture")
+
+
+def test_a_captured_sum_without_room_for_the_bits_takes_the_lists():
+    """The bit matrix is there, but its scratch for so many columns is not and cannot be had in a capture: the lists have room and serve
+    the call, with the bits that a call with coefficients of one gets."""
+    n, f = 9500, 256
+    el = _rows_with_a_third_of_all_sources(n, 600)
+    dg = device_graph(el, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    dg.plan_fwd.set_blocking(min_degree=32, hot_lines=9400, block_lines=1000, max_piece=48, rest_min_count=0)
+    ones = torch.ones(el.e, device=DEV)
+
+    def call(x, y, w=None):
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, w, x, y, n, x.shape[1], gnn.GNN_SUM, plan=dg.plan_fwd, flags=SLICED, max_slices=8)
+
+    x = synth.normal_features(n, f, 3).to(DEV)
+    by_lists, by_bits, y = (torch.empty_like(x) for _ in range(3))
+    narrow = x[:, :96].contiguous()
+    call(x, by_lists, ones)
+    call(narrow, torch.empty_like(narrow))
+    assert dg.plan_fwd.bit_rows() >= 256
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(x, y)
+    for _ in range(3):
+        y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, by_lists)
+        call(x, by_bits)  # eager: with the bit matrix
+        torch.cuda.synchronize()
+        assert not torch.equal(by_bits, by_lists) and torch.allclose(by_bits, by_lists, rtol=1e-4, atol=1e-3)

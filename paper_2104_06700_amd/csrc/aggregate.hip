@@ -1774,7 +1774,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     const int tile_groups = tl ? gnn_tile_groups(tl, int(layout.main_lines)) : 0;
     if (tl) {
         const int rc = gnn_launch_tiles(tl, o.dtype == GNN_BF16, gathered, layout.table_stride * esz, int(layout.main_lines),
-                                        tile_coefs, static_cast<float *>(plan->tile_partial.p), stream);
+                                        F - layout.tail_elems, tile_coefs, static_cast<float *>(plan->tile_partial.p), stream);
         if (rc != GNN_OK) { finish_overlap(); return rc; }
     }
 

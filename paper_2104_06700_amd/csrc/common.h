@@ -50,7 +50,7 @@ struct gnn_tiles {
     // Rows whose edges to the first sources are a bit matrix (dense_kernel); their lists leave those edges out.
     int32_t dense_groups = 0, dense_chunks = 0;  // groups of rows; chunks of sources of the longest one
     int32_t dense_units = 0, dense_extra = 0, dense_cut = 0;  // what the groups are cut into, units beyond their first; groups that have some
-    int64_t dense_sources = 0;                   // rows of the gathered table
+    int64_t dense_sources = 0;                   // rows of the gathered table that are gathered
     void *dense = nullptr;                       // the groups and their units
     uint32_t *dense_rows = nullptr;              // hot row of every row of the groups
     uint2 *dense_bits = nullptr;
@@ -213,7 +213,8 @@ int gnn_tile_groups(const gnn_tiles *t, int n_slices);
 int gnn_plan_tiles_with_room(gnn_plan *plan, int lanes, bool bf16, bool plain, int n_slices, int line_floats, hipStream_t stream, const gnn_tiles **out);
 int gnn_build_pieces(int64_t n_hot, int n_blocks, int64_t max_piece, const uint32_t *cell_count, const uint32_t *edge_off,
                      uint32_t *cell_pieces, uint32_t *sums, bool want_block, hipStream_t stream, gnn_piece_list *out);
-int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,
+// n_cols: columns of all slices that hold data.
+int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices, int64_t n_cols,
                      const float *coefs, float *partial, hipStream_t stream);
 
 // Device memory that is kept for the next plan (pool.hip).  With a stream: for memory that is first used there; fails on a

@@ -752,20 +752,21 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // their sums would overflow, and infinities and NaN would reach rows that do not gather them.
 __device__ __forceinline__ bool dense_exception(float x) { return !(fabsf(x) < 0x1p90f); }
 
-// A wavefront splits 16 sources x 32 columns of one slice; flags: the sources that have a value of the other kind.
-__global__ void __launch_bounds__(256) dense_split_kernel(const char *__restrict__ X, int64_t slice_stride, int64_t n_sources, int64_t n_steps,
-                                                          int n_slices, u32x4 *__restrict__ split, uint16_t *__restrict__ flags) {
+// A wavefront splits 16 sources x 32 columns of one slice; flags: the sources that have a value of the other kind.  Columns from n_cols on, and
+// the rows of sources that nobody gathers, are zeros here: in the table they are whatever its memory held.
+__global__ void __launch_bounds__(256) dense_split_kernel(const char *__restrict__ X, int64_t slice_stride, int64_t n_cols, int64_t n_sources,
+                                                          int64_t n_steps, int n_slices, u32x4 *__restrict__ split, uint16_t *__restrict__ flags) {
     const int lane = threadIdx.x & 63;
     const int64_t w = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
     if (w >= n_steps * n_slices) return;
     const int64_t slice = w / n_steps, step = w - slice * n_steps;
     const float *x = reinterpret_cast<const float *>(X + slice * slice_stride) + (lane & 31);
-    const int64_t k0 = step * 16 + (lane >> 5) * 8;
+    const int64_t k0 = step * 16 + (lane >> 5) * 8, k_end = slice * 32 + (lane & 31) < n_cols ? n_sources : 0;
     float v[8];
     uint32_t mask = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        v[j] = k0 + j < n_sources ? x[(k0 + j) * 32] : 0.0f;
+        v[j] = k0 + j < k_end ? x[(k0 + j) * 32] : 0.0f;
         const bool other = dense_exception(v[j]);
         const unsigned long long m = __ballot(other);
         if (uint32_t(m)) mask |= 1u << j;
@@ -947,7 +948,8 @@ int64_t dense_bytes(const gnn_tiles *t, int n_slices) {
 }
 
 // What dense_bytes counts lies behind the partial lines.
-hipError_t launch_dense(const gnn_tiles *t, const void *X, int64_t slice_stride, int n_slices, int n_groups, float *partial, hipStream_t stream) {
+hipError_t launch_dense(const gnn_tiles *t, const void *X, int64_t slice_stride, int n_slices, int64_t n_cols, int n_groups, float *partial,
+                        hipStream_t stream) {
     DenseArgs a{};
     a.groups = static_cast<const DenseGroup *>(t->dense);
     a.units = reinterpret_cast<const DenseUnit *>(a.groups + t->dense_groups);
@@ -965,8 +967,8 @@ hipError_t launch_dense(const gnn_tiles *t, const void *X, int64_t slice_stride,
     a.n_parts = t->n_parts;
     a.n_slices = n_slices;
     a.partial = partial;
-    dense_split_kernel<<<static_cast<unsigned>((a.n_steps * n_slices + 3) / 4), 256, 0, stream>>>(a.X, slice_stride, t->dense_sources, a.n_steps, n_slices,
-                                                                                            split, flags);
+    dense_split_kernel<<<static_cast<unsigned>((a.n_steps * n_slices + 3) / 4), 256, 0, stream>>>(a.X, slice_stride, n_cols, t->dense_sources, a.n_steps,
+                                                                                            n_slices, split, flags);
     dense_kernel<<<static_cast<unsigned>(t->dense_units * n_slices), 64 * kDenseWaves, 0, stream>>>(a);
     if (t->dense_cut > 0)
         dense_add_kernel<<<dim3(static_cast<unsigned>(t->dense_cut * (kDenseRows / 8)), static_cast<unsigned>(n_slices)), 256, 0, stream>>>(a);
@@ -1083,7 +1085,7 @@ int build_dense(const gnn_plan *plan, const DenseRule &rule, const std::vector<T
     B.dense_extra = extra;
     B.dense_cut = cut;
     B.dense_chunks = groups[0].chunks;
-    B.dense_sources = plan->n_rows;
+    B.dense_sources = plan->n_rows - plan->bucket_vertices[0];  // they are in order of their gathers
     *staged_edges -= int64_t(host_edges);
     if (*staged_edges < 1) *staged_edges = 1;
     *depth_out = depth;
@@ -1458,7 +1460,7 @@ int gnn_plan_tiles_with_room(gnn_plan *plan, int lanes, bool bf16, bool plain, i
     return gnn_plan_room(plan, plan->tile_partial, tile_partial_bytes(*out, n_slices, line_floats), stream);
 }
 
-int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices,
+int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice_stride_bytes, int n_slices, int64_t n_cols,
                      const float *coefs, float *partial, hipStream_t stream) {
     TileArgs a{};
     a.tiles = static_cast<const TileDesc *>(t->tiles);
@@ -1505,6 +1507,6 @@ int gnn_launch_tiles(const gnn_tiles *t, bool bf16, const void *X, int64_t slice
         else GNN_TILE_LAUNCH(false, 2);
     }
 #undef GNN_TILE_LAUNCH
-    if (t->dense_groups && launch_dense(t, X, slice_stride_bytes, n_slices, a.n_groups, partial, stream) != hipSuccess) return GNN_ERR_LAUNCH;
+    if (t->dense_groups && launch_dense(t, X, slice_stride_bytes, n_slices, n_cols, a.n_groups, partial, stream) != hipSuccess) return GNN_ERR_LAUNCH;
     return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
 }

@@ -379,3 +379,41 @@ def test_a_captured_sum_without_room_for_the_bits_takes_the_lists():
         call(x, by_bits)  # eager: with the bit matrix
         torch.cuda.synchronize()
         assert not torch.equal(by_bits, by_lists) and torch.allclose(by_bits, by_lists, rtol=1e-4, atol=1e-3)
+
+
+def _ms(fn, reps=5):
+    times = []
+    fn()
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        fn()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return sorted(times)[reps // 2]
+
+
+def test_a_packed_copy_in_memory_that_held_nan():
+    """Columns behind the last one of a caller's packed copy, and the rows of vertices that nobody gathers, keep what its memory held: the
+    bit matrix does not look at them, neither in the result nor in the time (a value that is not finite takes a way of its own)."""
+    n, f = 9500, 602
+    el = _rows_with_a_third_of_all_sources(n, 600)
+    dg = device_graph(el, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    dg.plan_fwd.set_blocking(min_degree=32, hot_lines=9400, block_lines=1000, max_piece=48, rest_min_count=0)
+    x = synth.normal_features(n, f, 3).to(DEV)
+    buf = torch.empty(gnn.gnn_packed_bytes(n, f, gnn.GNN_F32) // 4, device=DEV)
+    results, times = [], []
+    for held in (0.0, float("nan"), 3e38):
+        buf.fill_(held)
+        gnn.gnn_pack_rows(dg.indptr, dg.indices, x, buf, n, f, gnn.GNN_SUM, False, plan=dg.plan_fwd)
+        y = torch.full_like(x, float("nan"))
+
+        def call():
+            gnn.gnn_aggregate_packed(dg.indptr, dg.indices, None, buf, y, n, f, gnn.GNN_SUM, False, plan=dg.plan_fwd)
+
+        times.append(_ms(call))
+        results.append(y)
+    assert dg.plan_fwd.bit_rows() >= 256
+    assert torch.equal(results[0], results[1]) and torch.equal(results[0], results[2])
+    assert max(times[1:]) < 1.5 * times[0], times

@@ -748,6 +748,27 @@ typedef float float2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// The next bf16 number of each of eight values, which keep what is left.
+__device__ __forceinline__ u32x4 split_off(float (&v)[8]) {
+    u32x4 q;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float2v pair = {v[2 * i], v[2 * i + 1]};
+        q[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
+        v[2 * i] -= __uint_as_float(q[i] << 16);
+        v[2 * i + 1] -= __uint_as_float(q[i] & 0xFFFF0000u);
+    }
+    return q;
+}
+
+// A step's bits of a row (the low ones of each half of the word) as numbers +1 or -1, whose patterns c holds shifted by 0 ... 3.
+__device__ __forceinline__ bf16x8 dense_ones(uint32_t word, const uint32_t (&c)[4]) {
+    u32x4 m;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) m[p] = __umul24(word & (0x00010001u << p), c[p]);
+    return __builtin_bit_cast(bf16x8, m);
+}
+
 // Beyond this, values take the way of dense_kernel's last loop: split (times 2^16, so that no part of any is cut off below) they and
 // their sums would overflow, and infinities and NaN would reach rows that do not gather them.
 __device__ __forceinline__ bool dense_exception(float x) { return !(fabsf(x) < 0x1p90f); }
@@ -774,17 +795,7 @@ __global__ void __launch_bounds__(256) dense_split_kernel(const char *__restrict
         v[j] = other ? 0.0f : v[j] * 0x1p16f;
     }
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        u32x4 q;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float2v pair = {v[2 * i], v[2 * i + 1]};
-            q[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2));
-            v[2 * i] -= __uint_as_float(q[i] << 16);
-            v[2 * i + 1] -= __uint_as_float(q[i] & 0xFFFF0000u);
-        }
-        split[w * kStepVecs + s * 64 + lane] = q;
-    }
+    for (int s = 0; s < 3; ++s) split[w * kStepVecs + s * 64 + lane] = split_off(v);
     if (lane == 0) flags[w] = uint16_t(mask);
 }
 
@@ -796,7 +807,7 @@ struct DenseArgs {
     const u32x4 *split;
     const uint16_t *flags;
     const char *X;
-    int64_t slice_stride, n_steps, n_parts;
+    int64_t slice_stride, n_steps, n_parts, n_sources;
     int32_t n_slices;
     float *partial;  // of the first group of tiles
     float *extra;    // [slot][slice][row of the group][32]
@@ -859,11 +870,7 @@ __global__ void __launch_bounds__(64 * kDenseWaves) dense_kernel(const DenseArgs
                 for (int i = 0; i < 3; ++i) x[i] = __builtin_bit_cast(bf16x8, q[(2 - i) * 64]);  // the smallest first
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
-                    const uint32_t word = (ODD ? b[r].y : b[r].x) >> (4 * s);
-                    u32x4 m;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) m[p] = __umul24(word & (0x00010001u << p), ODD ? c_odd[p] : c_even[p]);
-                    const bf16x8 ones = __builtin_bit_cast(bf16x8, m);
+                    const bf16x8 ones = dense_ones((ODD ? b[r].y : b[r].x) >> (4 * s), ODD ? c_odd : c_even);
 #pragma unroll
                     for (int i = 0; i < 3; ++i) sum[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, x[i], sum[r], 0, 0, 0);
                 }
@@ -883,32 +890,82 @@ __global__ void __launch_bounds__(64 * kDenseWaves) dense_kernel(const DenseArgs
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[r][v] *= 0x1p-16f;
 
-    // the values that were left out (see dense_exception)
+    // The values that were left out (see dense_exception), 64 sources at a time where they have any, as products again: the finite ones times
+    // 2^-64, and one number per source that is an infinity or NaN, so that a sum counts how many of each kind a row gathers.  32 loads in
+    // flight bound it (233 K vertices, 115 M edges F=602, no such value 6.07 ms, one column of infinities or of 1e30 6.22, all columns 7.9 and 7.7;
+    // one source and one load after the other 6.06, 11.7, 32).
     const uint16_t *flags = a.flags + int64_t(slice) * a.n_steps;
     const float *X = reinterpret_cast<const float *>(a.X + int64_t(slice) * a.slice_stride) + (lane & 31);
     const int n_steps = unit.end * kChunkSteps;
     for (int s0 = unit.begin * kChunkSteps; s0 < n_steps; s0 += 64) {
         const uint32_t mine = s0 + lane < n_steps ? flags[s0 + lane] : 0u;
-        for (unsigned long long steps = __ballot(mine != 0u); steps; steps &= steps - 1) {
-            const int at = __builtin_ctzll(steps), step = s0 + at;
-            uint32_t sources = uint32_t(__shfl(int(mine), at));
-            uint32_t word[2];
+        unsigned long long steps = __ballot(mine != 0u);
+        while (steps) {
+            const int first = __builtin_ctzll(steps) & ~3;
+            steps &= ~(0xFull << first);
+            const int64_t k0 = int64_t(s0 + first) * 16 + (lane >> 5) * 8;
+            float v[4][8];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[s][j] = k0 + s * 16 + j < a.n_sources ? X[(k0 + s * 16 + j) * 32] : 0.0f;
+            const bool odd = (s0 + first) & 4;
+            uint32_t word[2], c[4];
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
-                const uint2 w = bits[r * second + int64_t(step / kChunkSteps) * 64];
-                word[r] = ((step & 4) ? w.y : w.x) >> (4 * (step & 3));
+                const uint2 w = bits[r * second + int64_t((s0 + first) / kChunkSteps) * 64];
+                word[r] = odd ? w.y : w.x;
             }
-            for (; sources; sources &= sources - 1) {
-                const int k = __builtin_ctz(sources), j = k & 7;
-                const float x = X[(int64_t(step) * 16 + k) * 32];
-                const bool other = dense_exception(x);
+#pragma unroll
+            for (int p = 0; p < 4; ++p) c[p] = odd ? c_odd[p] : c_even[p];
+            bool any_large = false, any_special = false;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const bool finite = fabsf(v[s][j]) <= 0x1.fffffep127f;
+                    any_large |= finite && dense_exception(v[s][j]);
+                    any_special |= !finite;
+                }
+            auto products = [&](auto parts, auto number, float16v (&sum)[2]) {
+                constexpr int PARTS = decltype(parts)::value;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    float q[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) q[j] = number(v[s][j]);
+                    bf16x8 x[PARTS];
+#pragma unroll
+                    for (int i = PARTS - 1; i >= 0; --i) x[i] = __builtin_bit_cast(bf16x8, split_off(q));
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const bf16x8 ones = dense_ones(word[r] >> (4 * s), c);
+#pragma unroll
+                        for (int i = 0; i < PARTS; ++i) sum[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, x[i], sum[r], 0, 0, 0);
+                    }
+                }
+            };
+            if (__any(any_large)) {
+                float16v sum[2] = {};
+                products(std::integral_constant<int, 3>(),
+                         [](float x) { return dense_exception(x) && fabsf(x) <= 0x1.fffffep127f ? x * 0x1p-64f : 0.0f; }, sum);
 #pragma unroll
                 for (int r = 0; r < 2; ++r)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int row = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                        const uint32_t w = uint32_t(__shfl(int(word[r]), (k >> 3) * 32 + row));
-                        if (other && ((w >> ((j >> 1) + 16 * (j & 1))) & 1u)) acc[r][v] += x;
+                    for (int i = 0; i < 16; ++i) acc[r][i] += (((i & 1) != int(odd)) ? -sum[r][i] : sum[r][i]) * 0x1p64f;
+            }
+            if (__any(any_special)) {
+                float16v sum[2] = {};  // at most 64 of each kind
+                products(std::integral_constant<int, 1>(),
+                         [](float x) { return x != x ? 0x1p16f : (x == INFINITY ? 1.0f : (x == -INFINITY ? 0x1p8f : 0.0f)); }, sum);
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const uint32_t n = uint32_t(fabsf(sum[r][i]));
+                        if (n & 0xFFu) acc[r][i] += INFINITY;
+                        if (n >> 8 & 0xFFu) acc[r][i] -= INFINITY;
+                        if (n >> 16) acc[r][i] = NAN;
                     }
             }
         }
@@ -965,6 +1022,7 @@ hipError_t launch_dense(const gnn_tiles *t, const void *X, int64_t slice_stride,
     a.X = static_cast<const char *>(X);
     a.slice_stride = slice_stride;
     a.n_parts = t->n_parts;
+    a.n_sources = t->dense_sources;
     a.n_slices = n_slices;
     a.partial = partial;
     dense_split_kernel<<<static_cast<unsigned>((a.n_steps * n_slices + 3) / 4), 256, 0, stream>>>(a.X, slice_stride, n_cols, t->dense_sources, a.n_steps,

@@ -417,3 +417,51 @@ def test_a_packed_copy_in_memory_that_held_nan():
     assert dg.plan_fwd.bit_rows() >= 256
     assert torch.equal(results[0], results[1]) and torch.equal(results[0], results[2])
     assert max(times[1:]) < 1.5 * times[0], times
+
+
+@pytest.mark.parametrize("n,rows,hot_lines", [(1100, 700, 1099), (9500, 600, 9400)])
+def test_columns_of_values_that_the_products_leave_out(n, rows, hot_lines):
+    """Infinities, NaN and values from 2^90 on, in one source and in all of them, against the oracle: the kind and the sign of what is not
+    finite, the values of what is.  A whole column of them costs little."""
+    el = _rows_with_a_third_of_all_sources(n, rows)
+    indptr, indices, *_ = host_csr(el)
+    dg = device_graph(el, plan_params=gnn.make_plan_params(THRESHOLDS, 64))
+    dg.plan_fwd.set_blocking(min_degree=32, hot_lines=hot_lines, block_lines=1000, max_piece=48, rest_min_count=0)
+    f, inf = 160, float("inf")
+    X = synth.normal_features(n, f, 3)
+    X[:, 0] = inf
+    X[:, 33] = -inf
+    X[::2, 34], X[1::2, 34] = inf, 1e30
+    X[::3, 35], X[1::7, 35] = inf, -inf
+    X[5, 36], X[70, 36] = inf, -inf
+    X[::64, 37] = float("nan")
+    X[:, 38] = float("nan")
+    X[64:128, 39] = -inf
+    X[3, 64] = float("nan")
+    X[:, 65] *= 1e30
+    X[:, 66] *= torch.ldexp(torch.ones(n), (torch.arange(n) * 29) % 60 + 60)
+    X[1::2, 67] *= 1e33
+    X[:64, 68] *= 1e33
+    X[:, 69] = 2.0 ** 90
+    X[:, 70] = -(2.0 ** 90 - 2.0 ** 66)
+    X[9::10, 71], X[4::10, 72] = 1e35, inf
+    X[:, 159] = inf
+    with np.errstate(invalid="ignore"):
+        Yo, S = oracle.aggregate_fwd(indptr, indices, X.numpy(), op=OP_CODE["sum"], nthreads=8, want_scale=True)
+    xd, y = X.to(DEV), torch.full((n, f), float("nan"), device=DEV)
+
+    def call():
+        gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, None, xd, y, n, f, gnn.GNN_SUM, plan=dg.plan_fwd, flags=SLICED, max_slices=8)
+
+    call()
+    torch.cuda.synchronize()
+    assert dg.plan_fwd.bit_rows() >= 256
+    got = y.cpu().numpy()
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(kind(got), kind(Yo)), kind
+    finite = np.isfinite(Yo).all(axis=0)
+    assert finite.sum() > 140
+    assert_close(y[:, torch.from_numpy(finite)], Yo[:, finite], S[:, finite], False, "finite columns")
+    slow = _ms(call)
+    xd.copy_(synth.normal_features(n, f, 3))
+    assert slow < 5 * _ms(call)

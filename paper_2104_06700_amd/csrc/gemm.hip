@@ -762,7 +762,7 @@ __global__ void __launch_bounds__(kReduceWaves * 64) gemm_reduce_kernel(const fl
 }  // namespace
 
 // Tile of a workgroup, for the weight gradients: a long k, read once where N fits the tile's width.  resident: parts of k that a
-// compute unit gets, all in one round: a second, partly empty one costs a whole round (256 x 256 over 24,490 rows, 256 workgroups 30.6 us,
+// compute unit gets in a round: a second, partly empty one costs a whole round (256 x 256 over 24,490 rows, 256 workgroups 30.6 us,
 // 382 43.5; 60,000 56.7 and 512 64.4; 232,965 200 and 210; 100 x 256 over 60,000 37.6 and 52.5, over 2.45 M 1049 and 1065).  Tiles of 256
 // columns take the registers of a compute unit by themselves.  Narrow tiles are small so that several workgroups, each waiting for
 // memory, share one (602 x 16 over 232,965 rows: 306 us with tiles of 256 rows, two to a unit; 114 with 128 and five;
@@ -803,14 +803,25 @@ static int64_t choose_split(int64_t M, int64_t N, int64_t K) {
     const TileShape s = choose_tile(N, K);
     const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);
     if (tiles >= 512 || K < 1024) return 1;
-    int64_t split = 256 * s.resident / tiles;
-    // ... or two rounds of shorter parts, for closer sums, where they cost next to nothing (600,000 rows into 256 x 256 496 and 507 us)
-    if (s.resident == 1 && K > 2048 * split) split *= 2;
+    const int64_t max_split = K / GNN_SPLIT_MIN_K;
+    // Rounds of workgroups: as few as leave the result as close as `enough` planes added in 32 bits did, two workgroups per compute unit (N <= 32:
+    // five, N <= 64: four).  Error of normal operands, square of the 2-norm in 1e-14: 0.3 + 0.0021 K / parts, and 0.1 + 0.0095 planes for
+    // that many of them in 32 bits.  So fewer, longer parts pass where there were many planes (256 x 256 over 30,000 rows 234 parts 1.6e-7, 60 us,
+    // 128 0.9e-7, 48) and not where there were few (2000 x 2560 over 10,000, 4 parts 2.3e-7, 697 us, 2 3.2e-7, 868).  Two to sixteen tiles
+    // of a part share an XCD (`inner` in gnn_matmul_impl), so a round has whole parts on each: 602 x 256, 5 tiles, over 100,000 rows 51 parts, a few workgroups
+    // too many on some XCDs, 367 us, 103 304, 96 241; over 2.45 M 102 6.85 ms, 152 5.22; 602 x 128 over 100,000 102 196 us, 96 133.
+    int64_t enough = (256 * (s.bn <= 32 ? 5 : s.bn <= 64 ? 4 : 2) + tiles - 1) / tiles;
+    if (enough > max_split) enough = max_split;
+    int64_t split = 0;
+    for (int64_t rounds = 1; split < enough; ++rounds) {
+        const int64_t slots = 32 * s.resident * rounds;  // per XCD
+        split = tiles >= 2 && tiles <= 16 ? 8 * (slots / tiles) : 8 * slots / tiles;
+        if (split > max_split) split = max_split;
+        if (K <= 2048 * split && 2 * K * (enough - split) <= split * enough * (9 * enough + 96)) break;
+    }
     // At least GNN_SPLIT_MIN_K rows per part: a part is bound by the latency of its tiles of 16, one after the other, while the chip is not
     // full; the partial planes cost little beside that.  Parts of 96 would be faster on few rows (24,490 rows, us with parts of 128 and of
     // 96: 128 x 128 22.3 and 18.5, 256 x 47 18.2 and 17.4, 16 x 41 16.0 and 15.2), but callers size their workspaces by 128.
-    const int64_t max_split = K / GNN_SPLIT_MIN_K;
-    if (split > max_split) split = max_split;
     if (split > 4096) split = 4096;
     return split < 1 ? 1 : split;
 }

@@ -541,3 +541,18 @@ def test_matmul_of_one_or_two_products_rounds_as_fp32_does(m, n, tb):
         A64, B64 = A.astype(np.float64), B.astype(np.float64).T if tb else B.astype(np.float64)
         err, S = np.abs(C.cpu().numpy().astype(np.float64) - A64 @ B64), np.abs(A64) @ np.abs(B64)
         assert (err <= k * 2.0 ** -24 * S).all(), (k, (err / S).max() * 2 ** 24)
+
+
+@pytest.mark.parametrize("m,n,k", [(602, 256, 100_000), (2000, 2560, 10_000), (3000, 3000, 10_000), (1500, 1500, 4_000)])
+def test_matmul_parts_of_long_reductions_are_short_enough(m, n, k):
+    """Weight gradients of 5, 160, 288 and 72 tiles (128 x 256): as many parts as make two workgroups per compute unit, or as close a result.
+    Square of the relative 2-norm error of normal operands: 0.3e-14 + 0.0021e-14 per row of a part as measured from 128 rows
+    to 50,000; the bound takes a seventh more."""
+    gen = torch.Generator(device=DEV).manual_seed(m)
+    a, b = (torch.empty(k, cols, device=DEV).normal_(generator=gen) for cols in (m, n))
+    work = torch.empty(gnn.gnn_matmul_workspace_bytes(m, n, k) // 4, device=DEV)
+    c = torch.empty(m, n, device=DEV)
+    gnn.gnn_matmul(a, b, c, trans_a=True, workspace=work)
+    want = a.double().t().contiguous() @ b.double()
+    parts = -(-512 // (-(-m // 128) * -(-n // 256)))
+    assert float((c.double() - want).norm() / want.norm()) <= 1e-7 * (8 / 7 * (0.3 + 0.0021 * k / parts)) ** 0.5

@@ -730,7 +730,7 @@ __device__ static inline gnn_run_bin gnn_run_bin_of_block(const gnn_run_bins &r,
 // Bit b: the rows of bin b are short.  A wavefront takes many of them, so there have to be enough (MEAN, us, rows of
 // aggregate_kernel -> run_kernel, directed power-law graphs of 10 edges per vertex: 200 K vertices F=32 27.4 -> 28.9, 100 K F=100 43 -> 45;
 // 500 K F=32 59.0 -> 59.2, 100 282 -> 268, 256 506 -> 464; 1 M F=100 624 -> 578, 256 1258 -> 1110, bf16 128 296 -> 254).
-static inline uint32_t gnn_run_bins_of(const gnn_plan *plan, int first_excluded_bin) {
+static inline uint32_t gnn_run_bins_of(const gnn_plan *plan, int first_excluded_bin, int64_t least_rows = GNN_RUN_ROWS) {
     uint32_t bins = 0;
     int64_t rows = 0;
     if (!plan) return 0;
@@ -738,7 +738,7 @@ static inline uint32_t gnn_run_bins_of(const gnn_plan *plan, int first_excluded_
         bins |= 1u << b;
         rows += plan->bin_offsets[b + 1] - plan->bin_offsets[b];
     }
-    return rows >= GNN_RUN_ROWS ? bins : 0u;
+    return rows >= least_rows ? bins : 0u;
 }
 
 // strips: of 16 bytes per row

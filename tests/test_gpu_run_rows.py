@@ -14,7 +14,7 @@ DEV = "cuda:0"
 N = 300007
 
 
-def _graph():
+def _graph(N=N):
     """Rows of 0 ... 9 edges (0 most often), 40 of 300 edges, hubs of 5,000 edges; sources with a bias to small ids, duplicates allowed."""
     v = torch.arange(N)
     lengths = (synth.mix64(v + 5) & 0x7FFFFFFF) % 16
@@ -128,7 +128,7 @@ def test_last_segment_narrower_than_a_strip():
 def test_short_rows_of_max_and_min(graph, d, shift, reduce):
     """Values and winners of rows served many per wavefront, whole and in column slices, with ties, infinities and rows of nothing else."""
     el, (indptr, indices, *_) = graph
-    dg = device_graph(el)
+    dg, N = device_graph(el), el.n
     X = synth.normal_features(N, d, 3).mul_(2.0).round_()
     X[7, :] = float("-inf") if reduce == gnn.GNN_RED_MAX else float("inf")
     X[:3000:5, d - 1] = X[7, 0]
@@ -144,3 +144,16 @@ def test_short_rows_of_max_and_min(graph, d, shift, reduce):
         torch.cuda.synchronize()
         assert np.array_equal(out[shift:].view(N, d).cpu().numpy().astype(np.float64), want), flags
         assert np.array_equal(arg.cpu().numpy().astype(np.int64), won), flags
+
+
+@pytest.fixture(scope="module")
+def larger_graph():
+    el = _graph(460007)
+    return el, host_csr(el)
+
+
+@pytest.mark.parametrize("d,shift", [(33, 1), (100, 0)])
+@pytest.mark.parametrize("reduce", [gnn.GNN_RED_MAX, gnn.GNN_RED_MIN])
+def test_max_and_min_of_as_many_short_rows_as_a_launch_of_their_own_takes(larger_graph, d, shift, reduce):
+    """The same through ap_run_kernel, which takes 390,000 of them and more."""
+    test_short_rows_of_max_and_min(larger_graph, d, shift, reduce)

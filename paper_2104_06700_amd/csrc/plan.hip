@@ -266,6 +266,7 @@ __global__ void __launch_bounds__(256) edge_operand_kernel(const float *__restri
 typedef int64_t i64x2_any __attribute__((ext_vector_type(2), aligned(8)));
 typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
 constexpr int64_t kOperandEdges = 48000000;
+constexpr double kOperandSkew = 0.525;
 constexpr int kOperandRows = 2;                // rows of a wavefront at a time ...
 constexpr int kOperandBlocks = 8 * 32 * 4;     // ... and 16 wavefronts per compute unit: more rows in flight touch more lines than an L2 holds
 
@@ -273,7 +274,7 @@ constexpr int kOperandBlocks = 8 * 32 * 4;     // ... and 16 wavefronts per comp
 // id is a place in the row of the edge's other end, so an eighth leads to an eighth of those rows, and a line of 32 scalars is met
 // again by the next few hundred rows: it waits for them in the L2 (133 K rows: 17,000 lines) where the plain kernel misses on every
 // one (62 G loads/s, the rate behind the L2s; 268 G from an L2).  What remains is latency: ids, scalars and the turn between rows.
-// Any ids give the right result.  133 K rows, 79 M edges, mild skew 1.27 -> 0.93 ms, strong skew 1.03 -> 1.07.
+// Any ids give the right result.  133 K rows, 79 M edges, mild skew 1.27 -> 0.93 ms, strong skew 1.03 -> 1.07 (see below).
 __global__ void __launch_bounds__(256) edge_operand_rows_kernel(const float *__restrict__ fE, int64_t lde, const int64_t *__restrict__ edge_ids,
                                                                 const void *indptr, int ip64, int64_t N, float *__restrict__ out) {
     constexpr int ROWS = kOperandRows;
@@ -364,8 +365,13 @@ int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const in
     if (!plan->edge_operand && !gnn_dev_alloc(&plan->edge_operand, plan->n_edges, stream)) return GNN_ERR_ALLOC;
     // Long rows, and more scalars than the caches behind the L2s hold well (a vertex gradient of 4 columns, plain -> by rows, ms: 100 K rows,
     // 60 M edges 1.25 -> 1.05, 200 K, 79 M 1.88 -> 1.56, 250 K, 79 M 1.96 -> 1.68 / strong skew 1.68 -> 1.65, 350 K 2.06 -> 1.97;
-    // below, 100 K, 40 M 0.80 -> 0.77, 133 K, 40 M 0.83 -> 0.85, 60 K, 20 M 0.34 -> 0.41).
-    if (edge_ids && plan->n_edges >= kOperandEdges && plan->n_edges >= 200 * plan->n_rows)
+    // below, 100 K, 40 M 0.80 -> 0.77, 133 K, 40 M 0.83 -> 0.85, 60 K, 20 M 0.34 -> 0.41).  Not where few vertices have most of the edges: the lines of
+    // their rows stay in the L2s either way, and an eighth of a very long row is one wavefront's work (share of the most-gathered twentieth, ms:
+    // 0.39 133 K, 79 M 1.85 -> 1.45; 0.42 100 K, 50 M 0.99 -> 0.93, 350 K, 79 M 2.14 -> 2.02; 0.46 133 K, 79 M 1.74 -> 1.50; 0.50 250 K, 79 M 1.93 -> 1.70; 0.52 350 K,
+    // 79 M 2.02 -> 1.98; 0.53 100 K, 60 M 1.10 -> 1.14; 0.58 133 K, 79 M 1.57 -> 1.60; 0.60 133 K, 60 M 1.14 -> 1.21; 0.61 133 K, 50 M 0.91 -> 1.01; 0.65 250 K, 79 M
+    // 1.70 -> 1.68, by seed 1.63 to 1.74; 0.66 250 K, 60 M 1.25 -> 1.42).
+    if (edge_ids && plan->n_edges >= kOperandEdges && plan->n_edges >= 200 * plan->n_rows &&
+        gnn_plan_top_share(plan, plan->n_rows / 20) < kOperandSkew)
         edge_operand_rows_kernel<<<kOperandBlocks, 256, 0, stream>>>(fE, lde, edge_ids, indptr, ip64, plan->n_rows, plan->edge_operand);
     else
         edge_operand_kernel<<<grid_for(plan->n_edges, 256, 1 << 16), 256, 0, stream>>>(fE, lde, edge_ids, plan->n_edges, plan->edge_operand);

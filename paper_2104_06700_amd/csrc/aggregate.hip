@@ -1300,9 +1300,12 @@ bool has_coop_bin(const AggArgs &a) {
 }
 
 // Shared rows on few edges: the launch is too small for the chip (61 K vertices, 3.1 M edges F=8 25.6 -> 22.5 us, F=100 the same; 245 K,
-// 12.4 M F=64 weighted 194 -> 200, 1 M, 10 M F=8 95 -> 98).  bf16 always: it gains registers too.
+// 12.4 M F=64 weighted 194 -> 200, 1 M, 10 M F=8 95 -> 98).  bf16 also without them, up to 16 lanes per row and four slices a launch (aggregate_kernel -> this, us:
+// 100 K, 5 M F=64 57 -> 50, 128 87 -> 79; 200 K, 8 M F=64 84 -> 76, 100 the same; 400 K, 20 M F=100 435 -> 422, 350 1178 -> 1162; 2.45 M, 124 M F=64 1338 ->
+// 1265, 128 2446 -> 2375; at worst 2.45 M, 60 M F=250 3060 -> 3105, 1.4 M, 33 M F=400 2598 -> 2636).  32 lanes lose, 100 K, 5 M F=400 304 -> 314, 200 K, 8 M F=250 378
+// -> 390, and so do eight slices, 400 K, 20 M F=512 1418 -> 1448, 602 1815 -> 1887, 2.45 M F=500 10.68 -> 10.90 ms.
 bool use_gather_kernel(const AggArgs &a, int64_t n_edges, bool bf16, int log2_c) {
-    return (has_coop_bin(a) && n_edges <= (int64_t(1) << 22)) || (bf16 && log2_c >= 3);
+    return (has_coop_bin(a) && n_edges <= (int64_t(1) << 22)) || (bf16 && (log2_c == 3 || log2_c == 4) && a.log2_slices < 3);
 }
 
 template <typename T>
@@ -1785,7 +1788,9 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     // Bins whose rows run_kernel serves: all columns in one launch, beside the tiles and pieces where there are some (2.45 M vertices
     // F=100, 256: 3.62, 7.13 ms in front of the other short rows, 3.93, 7.19 behind them), else behind the other rows (27.8 M bf16
     // 14.8 ms, 15.4 in front).
-    const uint32_t run_bins = vec == max_vec && (F + vec - 1) / vec >= GNN_RUN_EDGES ? gnn_run_bins_of(plan, bl.active ? bl.first_bin : INT32_MAX) : 0u;
+    const uint32_t run_bins = vec == max_vec && (F + vec - 1) / vec >= GNN_RUN_EDGES
+                                  ? gnn_run_bins_of(plan, bl.active ? bl.first_bin : INT32_MAX, esz == 4 && F <= line_elems ? GNN_MORE_RUN_ROWS : GNN_RUN_ROWS)
+                                  : 0u;
     RunArgs runs{};
     bool runs_beside = false;
 

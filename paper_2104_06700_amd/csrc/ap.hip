@@ -890,8 +890,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
     // (d = 33, 64, 100, 128, us, rows of ap_fwd_kernel -> ap_run_kernel; short rows of directed power-law graphs of 10 edges per vertex: 338 K 103 -> 113,
     // 128 -> 127, 255 -> 278, 262 -> 256; 423 K 125 -> 130, 164 -> 156, 340 -> 328, 326 -> 326; 861 K 330 -> 294, 351 -> 339, 735 -> 697, 731 -> 668;
     // of symmetric ones: 393 K 295 -> 293, 305 -> 307, 653 -> 637, 633 -> 608; 517 K 480 -> 470, 490 -> 487, 1127 -> 1073, 999 -> 953).
-    constexpr int64_t kRunRows = 390000;
-    const uint32_t run_bins = binop == GNN_BIN_COPY_LHS && reduce != GNN_RED_SUM && d > 32 ? gnn_run_bins_of(plan, INT32_MAX, kRunRows) : 0u;
+    const uint32_t run_bins = binop == GNN_BIN_COPY_LHS && reduce != GNN_RED_SUM && d > 32 ? gnn_run_bins_of(plan, INT32_MAX, GNN_MORE_RUN_ROWS) : 0u;
     bool sliced = false;
     const bool slice_ok = !use_e || (!wide && !c.o.edge_ids && reduce == GNN_RED_SUM) || c.o.max_slices > 1;
     if (use_v && !wide && vec == 4 && plan && plan->n_edges > 0 && slice_ok) {

@@ -708,6 +708,7 @@ static inline int gnn_ilog2_ceil(int64_t x) {
 constexpr int GNN_RUN_EDGES = 8;      // edges of such a row at most
 constexpr int GNN_RUN_BINS = 8;       // bins of a launch at most
 constexpr int64_t GNN_RUN_ROWS = 1 << 18, GNN_RUN_WAVES = 1 << 14;  // see gnn_run_bins_of, gnn_fill_run_bins
+constexpr int64_t GNN_MORE_RUN_ROWS = 390000;  // for fp32 rows of one line, and for max and min
 
 struct gnn_run_bin {
     int64_t first_block, item_begin, n_items;
@@ -729,7 +730,8 @@ __device__ static inline gnn_run_bin gnn_run_bin_of_block(const gnn_run_bins &r,
 
 // Bit b: the rows of bin b are short.  A wavefront takes many of them, so there have to be enough (MEAN, us, rows of
 // aggregate_kernel -> run_kernel, directed power-law graphs of 10 edges per vertex: 200 K vertices F=32 27.4 -> 28.9, 100 K F=100 43 -> 45;
-// 500 K F=32 59.0 -> 59.2, 100 282 -> 268, 256 506 -> 464; 1 M F=100 624 -> 578, 256 1258 -> 1110, bf16 128 296 -> 254).
+// 500 K F=32 59.0 -> 59.2, 100 282 -> 268, 256 506 -> 464; 1 M F=100 624 -> 578, 256 1258 -> 1110, bf16 128 296 -> 254; 320 K, 271,000 short rows, F=33 78
+// -> 75, 64 78 -> 75, 256 290 -> 269, bf16 64 52 -> 51, 128 89 -> 80, but F=32 43 -> 46; 600 K, 516,000 F=32 79 -> 77).
 static inline uint32_t gnn_run_bins_of(const gnn_plan *plan, int first_excluded_bin, int64_t least_rows = GNN_RUN_ROWS) {
     uint32_t bins = 0;
     int64_t rows = 0;

@@ -152,6 +152,18 @@ def larger_graph():
     return el, host_csr(el)
 
 
+def test_sums_of_one_line_on_as_many_short_rows_as_they_need(larger_graph):
+    """fp32 rows of one line go through run_kernel from 390,000 short rows on."""
+    el, (indptr, indices, *_) = larger_graph
+    dg = device_graph(el)
+    X = synth.normal_features(el.n, 32, 3)
+    Yo, S = oracle.aggregate_fwd(indptr, indices, X.numpy(), op=oracle.OP_SUM, nthreads=8, want_scale=True)
+    Y = torch.full((el.n, 32), float("nan"), device=DEV)
+    gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, None, X.to(DEV), Y, el.n, 32, gnn.GNN_SUM, plan=dg.plan_fwd)
+    torch.cuda.synchronize()
+    assert_close(Y, Yo, S, False, "32 columns")
+
+
 @pytest.mark.parametrize("d,shift", [(33, 1), (100, 0)])
 @pytest.mark.parametrize("reduce", [gnn.GNN_RED_MAX, gnn.GNN_RED_MIN])
 def test_max_and_min_of_as_many_short_rows_as_a_launch_of_their_own_takes(larger_graph, d, shift, reduce):

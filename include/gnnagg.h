@@ -96,8 +96,9 @@ typedef struct gnn_opts {
 
 /* Cold hints: sliced launches on a large power-law graph fetch the rows of rarely gathered sources
  * with non-temporal loads (the plan keeps a copy of the index array with those sources flagged,
- * 4 bytes per edge, built on first use or by gnn_plan_prepare).  NO: never; FORCE: whatever the
- * graph and layout (tests).  Results do not depend on it. */
+ * 4 bytes per edge, built on first use or by gnn_plan_prepare).  bf16 launches of up to four slices
+ * fetch all rows alike (the hints gain nothing there).  NO: never; FORCE: whatever the graph and
+ * layout, those launches included (tests).  Results do not depend on it. */
 #define GNN_FLAG_NO_COLD_HINTS 16
 #define GNN_FLAG_FORCE_COLD_HINTS 32
 /* Keep the plan-owned padded copy in vertex order (default: rows stored by descending gather

@@ -1929,8 +1929,8 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         if (next_block > INT32_MAX) { finish_overlap(); return GNN_ERR_UNSUPPORTED; }
         dim3 grid(static_cast<unsigned>(next_block));
         hipError_t err = hipSuccess;
-        // (a last segment narrower than a strip begins before its own first column, which an unsigned offset cannot say)
-        if (few_bytes && npass == 1 && (fw >= vec || !overlap) && use_gather_kernel(a, plan->n_edges, o.dtype == GNN_BF16, log2_c)) {
+        // (a last segment narrower than a strip begins before its own first column, which an unsigned offset cannot say; the kernel knows no cold sources)
+        if (few_bytes && npass == 1 && !(o.flags & GNN_FLAG_FORCE_COLD_HINTS) && (fw >= vec || !overlap) && use_gather_kernel(a, plan->n_edges, o.dtype == GNN_BF16, log2_c)) {
             err = o.dtype == GNN_F32 ? launch_gather<float>(log2_c, coef, grid, rows_stream, a) : launch_gather<bf16_t>(log2_c, coef, grid, rows_stream, a);
         } else if (o.dtype == GNN_F32) {
             if (vec == 4) err = launch_coef<float, 4>(coef, npass, grid, rows_stream, a);

@@ -254,7 +254,8 @@ typedef struct gnn_ap_opts {
     gnn_plan *plan;           /* plan of the graph passed in the same call, or NULL (no binning) */
     int32_t flags;            /* GNN_FLAG_NO_COLUMN_SLICES / NO_PADDED_COPY / FORCE_PADDED_COPY, as in gnn_opts:
                                  gather-bound forward calls (no full-width edge operand, d >= 4, a plan)
-                                 use the column slices of the sum-only hot path */
+                                 use the column slices of the sum-only hot path; calls with a full-width
+                                 one copy rows that lie across line boundaries (see gnn_ap_fwd) */
     int32_t max_slices;       /* as in gnn_opts; 0 = automatic */
 } gnn_ap_opts;
 
@@ -268,7 +269,9 @@ typedef struct gnn_ap_opts {
  * empty row -- and must be NULL for sum.  NaN inputs give an unspecified winner.  max / min need
  * E <= INT32_MAX.  Every width and stride is read and written in 16-byte accesses at the alignment of
  * a float (4-byte ones below four columns).  A gather-bound call (no full-width f_E) on a large graph
- * with a plan gathers from a plan-owned copy of f_V where its rows are not whole 128-byte lines.
+ * with a plan gathers from a plan-owned copy of f_V where its rows are not whole 128-byte lines; a call with
+ * a full-width f_E, and gnn_ap_bwd_vertex and _edge with one, from a copy of up to 256 MiB that lives for
+ * the call (none on a stream that is being captured, nor where there is no memory for it).
  * Hub rows use plan-owned scratch (copy and scratch are grown on first use: allocation).
  * copylhs / sum and mul / sum with a scalar f_E are what gnn_aggregate_fwd computes with GNN_SUM
  * (plain or weighted) and run on that path, with its layouts; a scalar f_E that is strided or
@@ -444,8 +447,8 @@ GNN_API int gnn_graph_build(const int32_t *dst_sorted, const int32_t *src, const
                     int64_t *perm, float *edge_w_t, const gnn_plan_params *params /* host */, void *stream,
                     gnn_plan **plan_fwd, gnn_plan **plan_bwd);
 
-/* Device memory of destroyed plans, of the setup calls and of the scratch of
- * gnn_ap_bwd_vertex_arg_edges is kept for the next ones: per device at most GNN_CACHED_MEMORY_BYTES
+/* Device memory of destroyed plans, of the setup calls, of the scratch of
+ * gnn_ap_bwd_vertex_arg_edges and of the copies of gnn_ap_* calls is kept for the next ones: per device at most GNN_CACHED_MEMORY_BYTES
  * that nothing uses at the moment.  It goes back to the driver when an allocation of the library
  * fails, piece by piece when thousands of allocations have not asked for it, and by this call, which
  * gives back what the current device holds and waits for the device.  Another allocator in the

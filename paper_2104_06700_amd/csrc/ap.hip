@@ -733,12 +733,12 @@ struct AlignedRows {
     explicit AlignedRows(hipStream_t s) : stream(s) {}
     AlignedRows(const AlignedRows &) = delete;
     ~AlignedRows() { if (copy) gnn_dev_free_on(copy, stream); }
-    int make(ApArgs &a, const gnn_plan *plan, int64_t N, int64_t d) {
+    int make(ApArgs &a, const gnn_plan *plan, int64_t N, int64_t d, int flags) {
         const bool in_lines = reinterpret_cast<uintptr_t>(a.fV) % 128 == 0 && (a.ldv % 32 == 0 || (a.ldv < 32 && (a.ldv & (a.ldv - 1)) == 0));
         int64_t ld = 16;
         while (ld < d && ld < 32) ld *= 2;
         if (d > 32) ld = (d + 31) / 32 * 32;
-        if (!plan || in_lines || d < 12 || (d > 32 && d % 32 > 0 && d % 32 <= 16)) return GNN_OK;
+        if (!plan || (flags & GNN_FLAG_NO_PADDED_COPY) || in_lines || d < 12 || (d > 32 && d % 32 > 0 && d % 32 <= 16)) return GNN_OK;
         if (N * d * 4 < 12000000 || N * ld * 4 > (int64_t(256) << 20) || plan->n_edges < 24 * N) return GNN_OK;
         if (!gnn_dev_alloc(&copy, N * ld, stream)) { (void)hipGetLastError(); copy = nullptr; return GNN_OK; }
         const int rc = gnn_pad_rows_f32(a.fV, a.ldv, copy, ld, N, d, plan->col_counts, stream);
@@ -876,7 +876,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
 
     AlignedRows aligned(c.stream);
     if (use_v && wide) {
-        rc = aligned.make(a, plan, N, d);
+        rc = aligned.make(a, plan, N, d, c.o.flags);
         if (rc != GNN_OK) return rc;
     }
 
@@ -1107,7 +1107,7 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     a.ip64 = c.o.indptr_is_64 ? 1 : 0;
     AlignedRows aligned(c.stream);
     if (need_x && c.ewide) {
-        rc = aligned.make(a, plan, N, d);
+        rc = aligned.make(a, plan, N, d, c.o.flags);
         if (rc != GNN_OK) return rc;
     }
     const int64_t blocks = make_bins(a, plan, N, log2_c);

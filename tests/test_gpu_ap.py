@@ -508,3 +508,26 @@ def test_scalar_operands_of_many_edges_through_an_edge_map(ip64, stride):
         gnn.gnn_ap_bwd_vertex(indptr, indices, x, fe[ids, :1].contiguous(), want, n, d, gnn.GNN_BIN_MUL, plan=plan)
         torch.cuda.synchronize()
         assert torch.equal(got, want)
+
+
+def test_full_width_operands_without_a_padded_copy():
+    """GNN_FLAG_NO_PADDED_COPY: rows across line boundaries are gathered where they lie, with the same bits, and no memory is taken for them."""
+    n, d = 250007, 13
+    el = synth.rmat_symmetric(n, 24 * n + 24, (0.45, 0.22, 0.22, 0.11), 3, device=DEV)
+    dg = gnn.build_device_graph(el.dst, el.src, n)
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    v, fe = (torch.empty(rows, d, device=DEV).normal_(generator=gen) for rows in (n, el.e))
+    out = [torch.full_like(v, 7.0) for _ in range(2)]
+
+    def taken(i, flags):
+        torch.cuda.synchronize()
+        gnn.gnn_release_cached_memory()
+        free = torch.cuda.mem_get_info()[0]
+        gnn.gnn_ap_fwd(dg.indptr, dg.indices, v, fe, out[i], None, n, d, gnn.GNN_BIN_MUL, gnn.GNN_RED_SUM, plan=dg.plan_fwd, flags=flags)
+        torch.cuda.synchronize()
+        return free - torch.cuda.mem_get_info()[0]
+
+    taken(0, 0)  # what a plan and its kernels take once
+    assert taken(0, 0) >= n * 16 * 4
+    assert taken(1, gnn.GNN_FLAG_NO_PADDED_COPY) == 0
+    assert torch.equal(out[0], out[1])

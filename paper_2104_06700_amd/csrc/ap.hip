@@ -482,14 +482,16 @@ __global__ void __launch_bounds__(256) ap_hub_finalize_kernel(const int32_t *__r
 // ------------------------------------------------------------ edge gradient
 // dfE[r(e), j] = dO[v, j] * d binop / dy, per edge of the forward graph; summed over j when the
 // edge operand is a scalar.  MASKED: only where arg_in[v, j] == e (max / min).
-template <int BIN, int VEC, bool EWIDE, bool MASKED>
+// KEEP: when a lane's first strip of dO, the same for all edges, is loaded.
+enum KeepGo { kEveryStep, kBeforeFirst, kInFirst };
+template <int BIN, int VEC, bool EWIDE, bool MASKED, KeepGo KEEP>
 __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs a) {
     const Near near(a);
     constexpr bool NEED_X = BIN == GNN_BIN_MUL || BIN == GNN_BIN_DIV;
     constexpr bool NEED_Y = BIN == GNN_BIN_DIV;
     // Edges in flight per slot (us, 2 / 4 / 8: 245 K vertices, 50 edges each 33 columns 694 / 694 / 717, 60 K vertices, 50 each 174 / 162 / 153, 8 columns
     // 36 / 37 / 47).  Their loads come before the first use, else each waited for the one before it and for its store (60 K vertices
-    // 33 columns 172 -> 162, 64 239 -> 211; 245 K 61 1107 from 1149; 100 K, 10 each 33 96 -> 80).
+    // 33 columns 172 -> 162, 64 239 -> 211; 245 K 61 1107 from 1149; 100 K, 10 each 33 96 -> 80; all before dO was kept from the first step on).
     constexpr int U = 4;
     const Group g = locate_group(a, near, blockIdx.x);
     const int G = g.G, SR = g.SR, C = g.C;
@@ -506,10 +508,15 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
     };
     int nxt_u; float nxt_y; int64_t nxt_r;
     fetch_tile(e0 + g.lane_in_g, nxt_u, nxt_y, nxt_r);
-    float go_first[VEC];  // of the lane's first strip: the same for all edges
+    // Beside the rows of the first step is best where rows are written (20,000 vertices, 30 edges each, us, before the indices have arrived, in every step, in
+    // the first: 13 columns 19.0, 18.2, 15.6; 33 49.2, 48.2, 38.4; 64 56.4, 56.4, 45.9; 100 K, 10 each 33 80, 81, 64; 5,000, 20 each 29.3, 27.4, 22.3),
+    // before them for scalars (245 K, 50 each 33 columns, add, first step 10 % slower).
+    float go_first[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) go_first[i] = 0.0f;
-    if (e0 < e1 && g.c * VEC < a.d) load_f<VEC>(a.dO + row * a.ldo + (VEC > 1 && g.c * VEC > a.d - VEC ? a.d - VEC : g.c * VEC), go_first);
+    if (KEEP == kBeforeFirst && e0 < e1 && g.c * VEC < a.d)
+        load_f<VEC>(a.dO + row * a.ldo + (VEC > 1 && g.c * VEC > a.d - VEC ? a.d - VEC : g.c * VEC), go_first);
+    bool load_first = true;
     for (int64_t tile = e0; __any(tile < e1); tile += G) {
         const int my_u = nxt_u;
         const float my_y = nxt_y;
@@ -537,10 +544,20 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
                 const int col = VEC > 1 && col0 > a.d - VEC ? a.d - VEC : col0;  // columns before col0 belong to the strip before
                 float go[VEC], x[U][VEC], y[U][VEC];
                 int32_t aw[VEC];
-                if (col0 != g.c * VEC) load_f<VEC>(a.dO + row * a.ldo + col, go);
-                else
+                const bool first_strip = col0 == g.c * VEC;
+                if constexpr (KEEP == kInFirst) {
+                    if (load_first || !first_strip) load_f<VEC>(a.dO + row * a.ldo + col, go);
 #pragma unroll
-                    for (int i = 0; i < VEC; ++i) go[i] = go_first[i];
+                    for (int i = 0; i < VEC; ++i) {  // chosen, not branched to: 20,000 vertices, 30 edges each 33 columns 38.4 us, with a branch 50.3
+                        if (!load_first && first_strip) go[i] = go_first[i];
+                        else if (first_strip) go_first[i] = go[i];
+                    }
+                } else {
+                    if (KEEP == kEveryStep || !first_strip) load_f<VEC>(a.dO + row * a.ldo + col, go);
+                    else
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) go[i] = go_first[i];
+                }
                 if (MASKED) load_i<VEC>(a.arg_in + row * int64_t(a.d) + col, aw);
 #pragma unroll
                 for (int k = 0; k < U; ++k) {  // all loads before the first use
@@ -573,6 +590,7 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
                     }
                 }
             }
+            if (KEEP == kInFirst) load_first = false;
             if (!EWIDE) {
 #pragma unroll
                 for (int k = 0; k < U; ++k) {
@@ -602,6 +620,9 @@ template <int LC, int S, bool RAGGED>  // RAGGED: fewer than 4 * C * S columns
 __global__ void __launch_bounds__(kBlockThreads) ap_edge_dot_kernel(const ApArgs a) {
     const Near near(a);
     constexpr int C = 1 << LC;
+    // Edges whose loads are in flight, all before the first use: left to itself the compiler kept as few as three (us, 100 K vertices, 1 M edges 33, 64, 100 columns
+    // 24.5 -> 22.0, 22.7 -> 22.1, 52.7 -> 41.8; 130 K, 8 M 117 -> 101, 104 -> 103, 277 -> 247; 40 K, 2 M 80 columns 52 -> 48; 245 K, 12.4 M 128 474 -> 481).
+    constexpr int H = S <= 2 ? C : C / 2;
     Group g = locate_group(a, near, a.source_split ? blockIdx.x >> 3 : blockIdx.x);
     if (a.source_split) {  // XCD k takes the k-th eighth of a row's edges, in whole steps of the group
         const int64_t k = blockIdx.x & 7u, len = g.e1 - g.e0, first = g.e0;
@@ -636,24 +657,28 @@ __global__ void __launch_bounds__(kBlockThreads) ap_edge_dot_kernel(const ApArgs
         float *out = a.out + (a.eid && e < g.e1 ? a.eid[e] : e) * near.lde;
         nxt = fetch(tile + g.G + g.lane_in_g);
         float p[C];
-        float x[C][S][4];
 #pragma unroll
-        for (int k = 0; k < C; ++k) {
-            const uint32_t off = uint32_t(__shfl(int(mine), slot0 + k));
+        for (int k0 = 0; k0 < C; k0 += H) {
+            float x[H][S][4];
 #pragma unroll
-            for (int s = 0; s < S; ++s) load_f<4>(reinterpret_cast<const float *>(fV + (off + col_bytes[s])), x[k][s]);
-        }
+            for (int k = 0; k < H; ++k) {
+                const uint32_t off = uint32_t(__shfl(int(mine), slot0 + k0 + k));
 #pragma unroll
-        for (int k = 0; k < C; ++k) {
-            float t = 0.0f;
+                for (int s = 0; s < S; ++s) load_f<4>(reinterpret_cast<const float *>(fV + (off + col_bytes[s])), x[k][s]);
+            }
+            if constexpr (S > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s = 0; s < S; ++s)
+            for (int k = 0; k < H; ++k) {
+                float t = 0.0f;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float next = fmaf(go[s][i], x[k][s][i], t);
-                    t = !RAGGED || s < S - 1 || own[i] ? next : t;
-                }
-            p[k] = t;
+                for (int s = 0; s < S; ++s)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float next = fmaf(go[s][i], x[k][s][i], t);
+                        t = !RAGGED || s < S - 1 || own[i] ? next : t;
+                    }
+                p[k0 + k] = t;
+            }
         }
         if constexpr (C == 8) {
 #pragma unroll
@@ -982,18 +1007,22 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
 }
 
 template <int BIN, int VEC, bool EWIDE>
-void launch_edge_masked(bool masked, dim3 grid, hipStream_t stream, const ApArgs &a) {
-    if (masked) ap_bwd_edge_kernel<BIN, VEC, EWIDE, true><<<grid, kBlockThreads, 0, stream>>>(a);
-    else ap_bwd_edge_kernel<BIN, VEC, EWIDE, false><<<grid, kBlockThreads, 0, stream>>>(a);
+void launch_edge_masked(bool masked, KeepGo keep, dim3 grid, hipStream_t stream, const ApArgs &a) {
+    if (masked) ap_bwd_edge_kernel<BIN, VEC, EWIDE, true, kBeforeFirst><<<grid, kBlockThreads, 0, stream>>>(a);
+    else if (!EWIDE || keep == kBeforeFirst) ap_bwd_edge_kernel<BIN, VEC, EWIDE, false, kBeforeFirst><<<grid, kBlockThreads, 0, stream>>>(a);
+    else if constexpr (EWIDE) {
+        if (keep == kInFirst) ap_bwd_edge_kernel<BIN, VEC, EWIDE, false, kInFirst><<<grid, kBlockThreads, 0, stream>>>(a);
+        else ap_bwd_edge_kernel<BIN, VEC, EWIDE, false, kEveryStep><<<grid, kBlockThreads, 0, stream>>>(a);
+    }
 }
 template <int BIN>
-void launch_edge_bin(int vec, bool ewide, bool masked, dim3 grid, hipStream_t stream, const ApArgs &a) {
+void launch_edge_bin(int vec, bool ewide, bool masked, KeepGo keep, dim3 grid, hipStream_t stream, const ApArgs &a) {
     if (vec == 4) {
-        if (ewide) launch_edge_masked<BIN, 4, true>(masked, grid, stream, a);
-        else launch_edge_masked<BIN, 4, false>(masked, grid, stream, a);
+        if (ewide) launch_edge_masked<BIN, 4, true>(masked, keep, grid, stream, a);
+        else launch_edge_masked<BIN, 4, false>(masked, keep, grid, stream, a);
     } else {
-        if (ewide) launch_edge_masked<BIN, 1, true>(masked, grid, stream, a);
-        else launch_edge_masked<BIN, 1, false>(masked, grid, stream, a);
+        if (ewide) launch_edge_masked<BIN, 1, true>(masked, keep, grid, stream, a);
+        else launch_edge_masked<BIN, 1, false>(masked, keep, grid, stream, a);
     }
 }
 
@@ -1147,12 +1176,19 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
         else launch(integral_constant<int, 3>(), integral_constant<int, 4>());
         return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
     }
+    // Rows of dO of one or two strips, where a step does little else: for short launches of mul and div loaded in every step, because keeping them costs
+    // instructions (us, 1, 2, 4 columns, every step, before the first: 100 K vertices, 1 M edges 16.8 and 17.2, 19.0 and 19.3, 24.9 and 25.7; 130 K, 8 M 4 columns 84
+    // and 91, 2 59 and 57; 245 K, 12.4 M 2, 4 columns 99 and 91, 163 and 150; 5, 8 columns, every step, in the first: 5,000, 100,000 edges 14.0 and 14.5, 14.2
+    // and 14.6; 20 K, 600 K 17.8 and 17.6, 19.5 and 19.0; 40 K, 2 M 30 and 29, 31.5 and 29.5), without a gathered operand before the first (add, 4 columns,
+    // 130 K, 8 M every step 39, before 35).
+    const bool large = !plan || plan->n_edges >= (d > 4 ? 500000 : (d == 4 ? 10000000 : 4000000));
+    const KeepGo keep = d > 8 || (d > 4 && large) ? kInFirst : (large || !need_x ? kBeforeFirst : kEveryStep);
     switch (binop) {
-        case GNN_BIN_ADD: launch_edge_bin<GNN_BIN_ADD>(vec, c.ewide, masked, grid, c.stream, a); break;
-        case GNN_BIN_SUB: launch_edge_bin<GNN_BIN_SUB>(vec, c.ewide, masked, grid, c.stream, a); break;
-        case GNN_BIN_MUL: launch_edge_bin<GNN_BIN_MUL>(vec, c.ewide, masked, grid, c.stream, a); break;
-        case GNN_BIN_DIV: launch_edge_bin<GNN_BIN_DIV>(vec, c.ewide, masked, grid, c.stream, a); break;
-        default: launch_edge_bin<GNN_BIN_COPY_RHS>(vec, c.ewide, masked, grid, c.stream, a); break;
+        case GNN_BIN_ADD: launch_edge_bin<GNN_BIN_ADD>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
+        case GNN_BIN_SUB: launch_edge_bin<GNN_BIN_SUB>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
+        case GNN_BIN_MUL: launch_edge_bin<GNN_BIN_MUL>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
+        case GNN_BIN_DIV: launch_edge_bin<GNN_BIN_DIV>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
+        default: launch_edge_bin<GNN_BIN_COPY_RHS>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
     }
     return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
 }

@@ -199,7 +199,8 @@ int gnn_plan_blocked_bound_weights(gnn_plan *plan, hipStream_t stream, const flo
 // Under three slices a launch of that is too small for the chip (233 K vertices, 115 M edges F=32 0.41 -> 0.44 ms, 133 K, 79 M F=64 0.47 -> 0.50;
 // above, F=100 1.31 -> 1.26, 300 K, 120 M F=128 1.46 -> 1.42).
 static inline bool gnn_bits_pay(int64_t n_slices) { return n_slices >= 3; }
-// Nothing is built in a capture: a sum without coefficients takes the other layout there, if that one is at hand and its own is not.
+// Nothing is built in a capture: a sum without coefficients takes the other layout there, if that one is at hand and its own is not.  Where there is no room for
+// the bit matrix it takes the lists.
 int gnn_plan_tiles(gnn_plan *plan, int lanes, bool bf16, bool plain, int64_t n_slices, hipStream_t stream, const gnn_tiles **out);
 void gnn_tiles_free(gnn_tiles &t);
 // Coefficients w[e] * scale[e] (either may be null; CSR order) in stream order.

@@ -198,6 +198,7 @@ int allocate(void **out, size_t bytes, bool has_stream, hipStream_t stream) {
 }  // namespace
 
 bool gnn_capturing(hipStream_t stream) {
+    if (!stream) return false;  // the null stream cannot be captured
     hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(stream, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
 }

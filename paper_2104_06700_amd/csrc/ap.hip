@@ -484,15 +484,14 @@ __global__ void __launch_bounds__(256) ap_hub_finalize_kernel(const int32_t *__r
 // edge operand is a scalar.  MASKED: only where arg_in[v, j] == e (max / min).
 // KEEP: when a lane's first strip of dO, the same for all edges, is loaded.
 enum KeepGo { kEveryStep, kBeforeFirst, kInFirst };
-template <int BIN, int VEC, bool EWIDE, bool MASKED, KeepGo KEEP>
+template <int BIN, int VEC, bool EWIDE, bool MASKED, KeepGo KEEP, int U>  // U: edges in flight per slot
 __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs a) {
     const Near near(a);
     constexpr bool NEED_X = BIN == GNN_BIN_MUL || BIN == GNN_BIN_DIV;
     constexpr bool NEED_Y = BIN == GNN_BIN_DIV;
-    // Edges in flight per slot (us, 2 / 4 / 8: 245 K vertices, 50 edges each 33 columns 694 / 694 / 717, 60 K vertices, 50 each 174 / 162 / 153, 8 columns
-    // 36 / 37 / 47).  Their loads come before the first use, else each waited for the one before it and for its store (60 K vertices
+    // Four edges in flight per slot where rows are written (us, 2 / 4 / 8: 245 K vertices, 50 edges each 33 columns 694 / 694 / 717, 60 K vertices, 50 each 174 /
+    // 162 / 153, 8 columns 36 / 37 / 47).  Their loads come before the first use, else each waited for the one before it and for its store (60 K vertices
     // 33 columns 172 -> 162, 64 239 -> 211; 245 K 61 1107 from 1149; 100 K, 10 each 33 96 -> 80; all before dO was kept from the first step on).
-    constexpr int U = 4;
     const Group g = locate_group(a, near, blockIdx.x);
     const int G = g.G, SR = g.SR, C = g.C;
     const int64_t e0 = g.e0, e1 = g.e1;
@@ -1007,22 +1006,32 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
 }
 
 template <int BIN, int VEC, bool EWIDE>
-void launch_edge_masked(bool masked, KeepGo keep, dim3 grid, hipStream_t stream, const ApArgs &a) {
-    if (masked) ap_bwd_edge_kernel<BIN, VEC, EWIDE, true, kBeforeFirst><<<grid, kBlockThreads, 0, stream>>>(a);
-    else if (!EWIDE || keep == kBeforeFirst) ap_bwd_edge_kernel<BIN, VEC, EWIDE, false, kBeforeFirst><<<grid, kBlockThreads, 0, stream>>>(a);
-    else if constexpr (EWIDE) {
-        if (keep == kInFirst) ap_bwd_edge_kernel<BIN, VEC, EWIDE, false, kInFirst><<<grid, kBlockThreads, 0, stream>>>(a);
-        else ap_bwd_edge_kernel<BIN, VEC, EWIDE, false, kEveryStep><<<grid, kBlockThreads, 0, stream>>>(a);
+void launch_edge_masked(bool masked, KeepGo keep, int in_flight, dim3 grid, hipStream_t stream, const ApArgs &a) {
+#define GNN_EDGE(MASKED, KEEP, U) ap_bwd_edge_kernel<BIN, VEC, EWIDE, MASKED, KEEP, U><<<grid, kBlockThreads, 0, stream>>>(a)
+    if constexpr (EWIDE) {
+        if (masked && in_flight == 2) GNN_EDGE(true, kBeforeFirst, 2);
+        else if (masked) GNN_EDGE(true, kBeforeFirst, 4);
+        else if (keep == kBeforeFirst) GNN_EDGE(false, kBeforeFirst, 4);
+        else if (keep == kInFirst) GNN_EDGE(false, kInFirst, 4);
+        else GNN_EDGE(false, kEveryStep, 4);
+    } else {
+        if (masked && in_flight == 2) GNN_EDGE(true, kBeforeFirst, 2);
+        else if (masked && keep == kBeforeFirst) GNN_EDGE(true, kBeforeFirst, 4);
+        else if (masked) GNN_EDGE(true, kEveryStep, 4);
+        else if (in_flight == 2) GNN_EDGE(false, kBeforeFirst, 2);
+        else if (keep == kBeforeFirst) GNN_EDGE(false, kBeforeFirst, 4);
+        else GNN_EDGE(false, kEveryStep, 4);
     }
+#undef GNN_EDGE
 }
 template <int BIN>
-void launch_edge_bin(int vec, bool ewide, bool masked, KeepGo keep, dim3 grid, hipStream_t stream, const ApArgs &a) {
+void launch_edge_bin(int vec, bool ewide, bool masked, KeepGo keep, int in_flight, dim3 grid, hipStream_t stream, const ApArgs &a) {
     if (vec == 4) {
-        if (ewide) launch_edge_masked<BIN, 4, true>(masked, keep, grid, stream, a);
-        else launch_edge_masked<BIN, 4, false>(masked, keep, grid, stream, a);
+        if (ewide) launch_edge_masked<BIN, 4, true>(masked, keep, in_flight, grid, stream, a);
+        else launch_edge_masked<BIN, 4, false>(masked, keep, in_flight, grid, stream, a);
     } else {
-        if (ewide) launch_edge_masked<BIN, 1, true>(masked, keep, grid, stream, a);
-        else launch_edge_masked<BIN, 1, false>(masked, keep, grid, stream, a);
+        if (ewide) launch_edge_masked<BIN, 1, true>(masked, keep, in_flight, grid, stream, a);
+        else launch_edge_masked<BIN, 1, false>(masked, keep, in_flight, grid, stream, a);
     }
 }
 
@@ -1181,14 +1190,29 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     // and 91, 2 59 and 57; 245 K, 12.4 M 2, 4 columns 99 and 91, 163 and 150; 5, 8 columns, every step, in the first: 5,000, 100,000 edges 14.0 and 14.5, 14.2
     // and 14.6; 20 K, 600 K 17.8 and 17.6, 19.5 and 19.0; 40 K, 2 M 30 and 29, 31.5 and 29.5), without a gathered operand before the first (add, 4 columns,
     // 130 K, 8 M every step 39, before 35).
-    const bool large = !plan || plan->n_edges >= (d > 4 ? 500000 : (d == 4 ? 10000000 : 4000000));
-    const KeepGo keep = d > 8 || (d > 4 && large) ? kInFirst : (large || !need_x ? kBeforeFirst : kEveryStep);
+    const int64_t n_edges = plan ? plan->n_edges : INT64_MAX;
+    const bool large = n_edges >= (d > 4 ? 500000 : (d == 4 ? 10000000 : 4000000));
+    KeepGo keep = d > 8 || (d > 4 && large) ? kInFirst : (large || !need_x ? kBeforeFirst : kEveryStep);
+    // Scalars, and rows of max and min.  Up to two lanes own an edge of 1, 2 and 4 to 8 columns, so a row has slots for most of its edges and two in flight
+    // are enough (us, four and two: 20 K vertices, 600 K edges add, 4 columns 28.7 and 19.8; 2.45 M, 60 M max of mul, 8 columns 952 and 972, add 237 and
+    // 215; rows written, 8 columns, 1 M, 5 M 136 and 138, 130 K, 8 M 137 and 146; 3 columns, 19 K to 12 M edges, 2 to 18 % slower with two).  Wider scalars
+    // with a gathered operand hold too many registers with a row of dO besides (33 columns, before the first and every step: 245 K, 12.4 M max of mul 386
+    // and 340, div 483 and 450; 40 K, 2 M equal), from 8 M edges on also with four in flight (every step, two: 245 K 340 and 324, 2.45 M 2050 and 1920; 80
+    // K, 4 M 134 and 158); up to 16 columns it is the other way (10 columns, before and every step: 500 K, 2.5 M 72 and 89, 300 K, 1.5 M 40 and 44; 60 K, 6
+    // M 67 and 64; 20 K, 600 K 16.1 and 15.6).  Without one dO is all there is to load (add, 33 columns, 245 K 155 and 162; 130 columns, two strips a lane,
+    // 753 and 722); max and min of that, 10 columns, 2.45 M 354 and 381, 33 columns 1052 and 1046, 3,217, 19 K edges 7.3 and 7.1.
+    int in_flight = 4;
+    if (!c.ewide || masked) {
+        if ((d <= 8 && d != 3 && !(c.ewide && d > 4 && n_edges >= 5000000)) || (!c.ewide && need_x && d > 32 && n_edges >= 8000000)) in_flight = 2;
+        const bool before = c.ewide || d <= 8 || (need_x ? d <= 16 && n_edges >= 1500000 : masked ? d <= 32 && n_edges >= 2000000 : d <= 128);
+        keep = before ? kBeforeFirst : kEveryStep;
+    }
     switch (binop) {
-        case GNN_BIN_ADD: launch_edge_bin<GNN_BIN_ADD>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
-        case GNN_BIN_SUB: launch_edge_bin<GNN_BIN_SUB>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
-        case GNN_BIN_MUL: launch_edge_bin<GNN_BIN_MUL>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
-        case GNN_BIN_DIV: launch_edge_bin<GNN_BIN_DIV>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
-        default: launch_edge_bin<GNN_BIN_COPY_RHS>(vec, c.ewide, masked, keep, grid, c.stream, a); break;
+        case GNN_BIN_ADD: launch_edge_bin<GNN_BIN_ADD>(vec, c.ewide, masked, keep, in_flight, grid, c.stream, a); break;
+        case GNN_BIN_SUB: launch_edge_bin<GNN_BIN_SUB>(vec, c.ewide, masked, keep, in_flight, grid, c.stream, a); break;
+        case GNN_BIN_MUL: launch_edge_bin<GNN_BIN_MUL>(vec, c.ewide, masked, keep, in_flight, grid, c.stream, a); break;
+        case GNN_BIN_DIV: launch_edge_bin<GNN_BIN_DIV>(vec, c.ewide, masked, keep, in_flight, grid, c.stream, a); break;
+        default: launch_edge_bin<GNN_BIN_COPY_RHS>(vec, c.ewide, masked, keep, in_flight, grid, c.stream, a); break;
     }
     return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
 }

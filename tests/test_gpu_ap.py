@@ -531,3 +531,43 @@ def test_full_width_operands_without_a_padded_copy():
     assert taken(0, 0) >= n * 16 * 4
     assert taken(1, gnn.GNN_FLAG_NO_PADDED_COPY) == 0
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n,mean,d", [(20011, 80, 10), (20011, 95, 3), (20011, 95, 5), (20011, 95, 10), (20011, 95, 16), (20011, 95, 17), (20011, 125, 32), (20011, 125, 36),
+                                      (96001, 110, 33), (60013, 170, 130)])
+def test_edge_gradients_of_large_graphs(n, mean, d):
+    """Scalars and rows of max on launches that take other numbers of edges in flight and load dO at other times than short ones (from 1.5, 2 and 8 M
+    edges on); rows of no edge, of one, a hub.  fp32 sums of d terms against 64 bits: within d roundings of the sum of their absolute values."""
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    lengths = torch.randint(0, 2 * mean, (n,), device=DEV, generator=gen)
+    lengths[::17], lengths[1::17], lengths[n - 2], lengths[n - 1] = 0, 1, 9001, 33
+    indptr = torch.zeros(n + 1, dtype=torch.int32, device=DEV)
+    indptr[1:] = lengths.cumsum(0)
+    e = int(indptr[-1])
+    assert e >= {80: 0, 95: 1500000, 125: 2000000}.get(mean, 8000000)
+    src = torch.randint(0, n, (e,), dtype=torch.int32, device=DEV, generator=gen)
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), lengths)
+    plan = gnn.gnn_plan_create(indptr, src, n)
+    rand = lambda *shape: torch.empty(*shape, device=DEV).normal_(generator=gen)
+    v, do = rand(n, d), rand(n, d)
+    for wide in (False, True) if d <= 33 and e < 4000000 else (False,):
+        fe = rand(e, d if wide else 1).abs() + 0.5
+        for binop in (gnn.GNN_BIN_ADD, gnn.GNN_BIN_MUL, gnn.GNN_BIN_DIV):
+            for masked in (True,) if wide else (False, True):
+                out, won = torch.empty_like(v), torch.empty(n, d, dtype=torch.int32, device=DEV)
+                if masked:
+                    gnn.gnn_ap_fwd(indptr, src, v, fe, out, won, n, d, binop, gnn.GNN_RED_MAX, plan=plan)
+                dfe = torch.full_like(fe, 7.0)
+                gnn.gnn_ap_bwd_edge(indptr, src, won if masked else None, v, fe, do, dfe, n, d, binop, plan=plan)
+                torch.cuda.synchronize()
+                for at in range(0, e, 1 << 20):
+                    part = slice(at, min(e, at + (1 << 20)))
+                    terms = do[dst[part]].double()
+                    if binop != gnn.GNN_BIN_ADD:
+                        terms *= v[src[part].long()].double()
+                    if binop == gnn.GNN_BIN_DIV:
+                        terms /= -fe[part].double() ** 2
+                    if masked:
+                        terms[won[dst[part]] != torch.arange(at, part.stop, device=DEV)[:, None]] = 0.0
+                    want, size = (terms, terms.abs()) if wide else (terms.sum(1, keepdim=True), terms.abs().sum(1, keepdim=True))
+                    assert bool(((dfe[part].double() - want).abs() <= (d + 4) * 2.0 ** -24 * size).all()), (wide, binop, masked)

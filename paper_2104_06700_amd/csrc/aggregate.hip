@@ -975,13 +975,19 @@ struct PieceArgs {
     int64_t slice_stride;    // elements between two slice tables
     float *partial;          // [slices][n_pieces][floats per line]
     int32_t log2_slices;
+    // Hot tables: the last block's pieces gather the caller's rows (of `cols` columns of the launch from X_cold on) by vertex.
+    const int32_t *cold_vertices;  // of the edges from cold_begin on
+    uint32_t cold_begin;
+    const void *X_cold;
+    int64_t ld_cold;
+    int32_t cols;
 };
 
 // L lanes own one piece and one line of every gathered row (16 bytes each: L = 8 for lines of 128 bytes, 4 and 2 for
 // shorter rows); a wavefront works on 64 / L consecutive pieces, with 8 lines of each in flight.  The pieces of a
 // launch follow the block order of the layout, so the workgroups that run side by side gather from the same block of
 // source rows.  Every piece writes one fp32 partial line; blk_finalize_kernel adds them.
-template <typename T, bool COEF, int L>
+template <typename T, bool COEF, int L, bool HOT = false>
 __global__ void __launch_bounds__(kBlockThreads) piece_kernel(const PieceArgs a) {
     constexpr int VEC = 16 / int(sizeof(T));   // elements per lane
     constexpr int LINE = L * VEC;              // elements per line = floats per partial line
@@ -1008,6 +1014,15 @@ __global__ void __launch_bounds__(kBlockThreads) piece_kernel(const PieceArgs a)
         base = k == 0 ? 0 : a.hot_lines + (k - 1) * a.block_lines;
     }
     const T *__restrict__ X = static_cast<const T *>(a.X) + int64_t(slice) * a.slice_stride + c * VEC;
+    int64_t ld = LINE;
+    bool lane_ok = true;
+    if constexpr (HOT) {
+        if (!narrow) {
+            X = static_cast<const T *>(a.X_cold) + slice * LINE + c * VEC;
+            ld = a.ld_cold;
+            lane_ok = slice * LINE + c * VEC < a.cols;  // whole strips: the caller's rows end with one
+        }
+    }
     float acc[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
@@ -1030,7 +1045,7 @@ __global__ void __launch_bounds__(kBlockThreads) piece_kernel(const PieceArgs a)
                 for (int i = 0; i < 4; ++i) u_out[i] = base + int(v.e[i]);
             } else {
                 Packed<int32_t> v;
-                __builtin_memcpy(&v, a.idx + pos, sizeof(v));
+                __builtin_memcpy(&v, HOT ? a.cold_vertices + (pos - a.cold_begin) : a.idx + pos, sizeof(v));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) u_out[i] = v.e[i];
             }
@@ -1076,7 +1091,7 @@ __global__ void __launch_bounds__(kBlockThreads) piece_kernel(const PieceArgs a)
                 const int src = gbase + 2 * m + (k >> 2);
                 const int u = __shfl(my_u[k & 3], src);
                 if (COEF) cf[k] = __shfl(my_cf[k & 3], src);
-                if (t + k < len) x[k] = Strip<T, VEC>::load(X + int64_t(u) * LINE);
+                if (t + k < len && (!HOT || lane_ok)) x[k] = Strip<T, VEC>::load(X + int64_t(u) * (HOT ? ld : int64_t(LINE)));
                 else x[k] = Strip<T, VEC>::zero();
             }
 #pragma unroll
@@ -1220,11 +1235,13 @@ __global__ void __launch_bounds__(256) blk_finalize_kernel(const int32_t *__rest
 // per-edge multiply of MEAN / SAGE_GCN backward and GCN.
 // gathered_only: rows that nobody gathers (counts 0: 43 % of the vertices of the 2.45 M-vertex graph) are left out; the
 // launch is bound by the bytes it moves (2.45 M vertices, F=256: 0.95 -> 0.60 ms).
+// src_rows: row v of the copy is row src_rows[v] of the matrix (hot tables).
 template <typename T, bool SCALE>
 __global__ void __launch_bounds__(256) pad_rows_kernel(const T *__restrict__ src, int64_t ld_src, T *__restrict__ dst, int64_t ld_dst,
                                                        int64_t N, int F, int mode, const int32_t *__restrict__ counts,
                                                        const int32_t *__restrict__ row_map, int log2_chunks_per_line,
-                                                       int64_t table_stride, int log2_tpr, int gathered_only) {
+                                                       int64_t table_stride, int log2_tpr, int gathered_only,
+                                                       const int32_t *__restrict__ src_rows) {
     constexpr int W = 16 / int(sizeof(T));
     const int chunks_per_row = (F + W - 1) / W;
     // 2^log2_tpr consecutive threads walk the chunks of one row (no division per chunk)
@@ -1237,7 +1254,7 @@ __global__ void __launch_bounds__(256) pad_rows_kernel(const T *__restrict__ src
         if (gathered_only && count == 0 && row != 0) continue;  // masked lanes may load row 0
         const int64_t drow = row_map ? int64_t(row_map[row]) : row;
         const float f = SCALE ? scale_of(mode, count) : 1.0f;
-        const T *in = src + row * ld_src;
+        const T *in = src + (src_rows ? int64_t(src_rows[row]) : row) * ld_src;
         for (int c = c0; c < chunks_per_row; c += tpr) {
             // row-major: log2_chunks_per_line is 31 (one table); slice-major: one table per line
             const int line = c >> log2_chunks_per_line, within = c - (line << log2_chunks_per_line);
@@ -1266,7 +1283,8 @@ __global__ void __launch_bounds__(256) pad_rows_kernel(const T *__restrict__ src
 // mode: the factor of the rows (kScaleNone: none).  dst is aligned to 16 bytes, ld_dst and table_stride are whole chunks.
 template <typename T>
 hipError_t launch_pad(const void *src, int64_t ld_src, void *dst, int64_t ld_dst, int64_t N, int64_t F, int mode, const int32_t *counts,
-                      hipStream_t stream, const int32_t *row_map = nullptr, int64_t table_stride = 0, bool gathered_only = false) {
+                      hipStream_t stream, const int32_t *row_map = nullptr, int64_t table_stride = 0, bool gathered_only = false,
+                      const int32_t *src_rows = nullptr) {
     const int cpr = int((F * int64_t(sizeof(T)) + 15) / 16);
     // threads per row: the power of two (>= 8 threads: one 128-byte line) that leaves the fewest idle slots in the last
     // round over the row's chunks; the widest among equals
@@ -1285,10 +1303,10 @@ hipError_t launch_pad(const void *src, int64_t ld_src, void *dst, int64_t ld_dst
     const int chunks_per_line = table_stride > 0 ? 3 : 31;
     if (sizeof(T) == 4 && mode != kScaleNone)
         pad_rows_kernel<T, true><<<grid, 256, 0, stream>>>(static_cast<const T *>(src), ld_src, static_cast<T *>(dst), ld_dst, N, int(F), mode, counts,
-                                                           row_map, chunks_per_line, table_stride, l, gathered_only ? 1 : 0);
+                                                           row_map, chunks_per_line, table_stride, l, gathered_only ? 1 : 0, src_rows);
     else
         pad_rows_kernel<T, false><<<grid, 256, 0, stream>>>(static_cast<const T *>(src), ld_src, static_cast<T *>(dst), ld_dst, N, int(F), mode, counts,
-                                                            row_map, chunks_per_line, table_stride, l, gathered_only ? 1 : 0);
+                                                            row_map, chunks_per_line, table_stride, l, gathered_only ? 1 : 0, src_rows);
     return hipGetLastError();
 }
 
@@ -1695,8 +1713,23 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     gnn_blocked_layout bl{};
     const float *scale_blk = nullptr, *w_blk = nullptr;
     const int lanes = layout.line_lanes;  // of a line of the tables
-    if (padded && lanes > 0 && rank_indices && !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS)) {
-        int rc = gnn_plan_blocked(plan, indptr, stream, &bl);
+    gnn_hot_layout hot{};
+    const bool hot_tables = layout.hot_tables && gnn_plan_hot_ready(plan, indptr, indices, src_mode, weights, F, esz, stream, &hot);
+    if (hot_tables) bl = hot.blocks;
+    const int64_t table_stride = hot_tables ? hot.rows * line_elems : layout.table_stride;  // of those that the pieces gather from
+    const int64_t n_table_lines = hot_tables ? layout.lines : layout.main_lines;
+    if (hot_tables) {
+        // 27.8 M vertices, 404 M edges, bf16 F=128, a call: 14.9 -> 12.9 ms.  43 % of the gathers, of 203 K rows from 524 K sources, come from LDS
+        // and the L2s; copying all rows that are gathered instead, 13.8 ms, 1.85 of them the copy.
+        auto copy = [&](auto elem) {
+            return launch_pad<decltype(elem)>(gathered, ldx, plan->padded.p, line_elems, hot.rows, F, kScaleNone, nullptr, stream, nullptr, table_stride,
+                                              /*gathered_only=*/false, hot.vertices);
+        };
+        if ((esz == 4 ? copy(float()) : copy(bf16_t())) != hipSuccess) return GNN_ERR_LAUNCH;
+        tables = plan->padded.p;
+    }
+    if (hot_tables || (padded && lanes > 0 && rank_indices && !(o.flags & GNN_FLAG_NO_SOURCE_BLOCKS))) {
+        int rc = hot_tables ? GNN_OK : gnn_plan_blocked(plan, indptr, stream, &bl);
         if (rc != GNN_OK) return rc;
         bl.active = bl.active && blocks_expected;
         if (bl.active && edge_scale) {
@@ -1713,7 +1746,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     const gnn_tiles *tl = nullptr;
     const float *tile_coefs = nullptr;
     if (bl.active) {
-        int rc = gnn_plan_tiles_with_room(plan, lanes, esz == 2, !coef, int(layout.main_lines), lanes * max_vec, stream, &tl);
+        int rc = gnn_plan_tiles_with_room(plan, lanes, esz == 2, !coef, int(n_table_lines), lanes * max_vec, stream, &tl);
         if (rc != GNN_OK) return rc;
         if (tl && coef) {
             rc = gnn_plan_tile_coefs(plan, tl, w, edge_scale, src_mode, weights == GNN_WEIGHTS_BOUND, stream, &tile_coefs);
@@ -1774,11 +1807,85 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         return ok;
     };
 
-    const int tile_groups = tl ? gnn_tile_groups(tl, int(layout.main_lines)) : 0;
+    const int tile_groups = tl ? gnn_tile_groups(tl, int(n_table_lines)) : 0;
     if (tl) {
-        const int rc = gnn_launch_tiles(tl, o.dtype == GNN_BF16, gathered, layout.table_stride * esz, int(layout.main_lines),
+        const int rc = gnn_launch_tiles(tl, o.dtype == GNN_BF16, hot_tables ? tables : gathered, table_stride * esz, int(n_table_lines),
                                         F - layout.tail_elems, tile_coefs, static_cast<float *>(plan->tile_partial.p), stream);
         if (rc != GNN_OK) { finish_overlap(); return rc; }
+    }
+
+    // The pieces of 1 << log2_s column slices from column f0 on, from the slice tables at X_tables, and the sums of the long rows.
+    auto launch_pieces = [&](int64_t f0, int64_t fw, int log2_s, const void *X_tables) -> int {
+        const int line_floats = lanes * max_vec;
+        int rc = gnn_plan_blocked_partial(plan, 1 << log2_s, line_floats, stream);
+        if (rc != GNN_OK) return rc;
+        PieceArgs pa{};
+        pa.pieces = tl ? tl->left.pieces : bl.pieces;
+        pa.n_pieces = tl ? tl->left.n_pieces : bl.n_pieces;
+        pa.idx = bl.indices;
+        pa.epos = bl.epos;
+        pa.idx16 = bl.idx16;
+        pa.piece_block = tl ? tl->left.piece_block : bl.piece_block;
+        pa.n_blocks = bl.n_blocks;
+        pa.hot_lines = bl.hot_lines;
+        pa.block_lines = bl.block_lines;
+        pa.w = w;
+        pa.w_blk = w_blk;
+        pa.scale_blk = scale_blk;
+        pa.X = X_tables;
+        pa.slice_stride = table_stride;
+        pa.partial = static_cast<float *>(plan->blk_partial.p);
+        pa.log2_slices = log2_s;
+        if (hot_tables) {
+            pa.cold_vertices = hot.cold_vertices;
+            pa.cold_begin = uint32_t(hot.cold_begin);
+            pa.X_cold = static_cast<const char *>(gathered) + f0 * esz;
+            pa.ld_cold = ldg;
+            pa.cols = int32_t(fw);
+        }
+        const int64_t per_block = int64_t(64 / lanes) * kWavesPerBlock;
+        const int64_t pblocks = ((pa.n_pieces + per_block - 1) / per_block) << log2_s;
+        if (pblocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
+        const int n_sl = 1 << log2_s;
+        const dim3 pgrid(static_cast<unsigned>(pblocks)), fgrid(static_cast<unsigned>((bl.n_hot * n_sl * lanes + 255) / 256));
+        const int32_t *hot_rows = plan->row_perm + bl.hot_begin;
+        const OwnRowSrc own = own_row_src(f0);
+        const float *tile_partial = tl ? static_cast<const float *>(plan->tile_partial.p) + f0 / line_elems * tl->n_parts * line_floats : nullptr;
+        const int64_t tile_group_stride = tl ? n_table_lines * tl->n_parts * line_floats : 0;
+        const uint32_t *rowbase = tl ? tl->left.rowbase : bl.rowbase, *part_base = tl ? tl->part_base : nullptr;
+        auto launch = [&](auto elem, auto n_lanes) {
+            using T = decltype(elem);
+            constexpr int L = decltype(n_lanes)::value;
+            if (pa.n_pieces == 0) {}
+            else if (L == 8 && hot_tables && coef) piece_kernel<T, true, 8, true><<<pgrid, kBlockThreads, 0, stream>>>(pa);
+            else if (L == 8 && hot_tables) piece_kernel<T, false, 8, true><<<pgrid, kBlockThreads, 0, stream>>>(pa);
+            else if (coef) piece_kernel<T, true, L><<<pgrid, kBlockThreads, 0, stream>>>(pa);
+            else piece_kernel<T, false, L><<<pgrid, kBlockThreads, 0, stream>>>(pa);
+            blk_finalize_kernel<T, L><<<fgrid, 256, 0, stream>>>(
+                hot_rows, bl.n_hot, rowbase, pa.partial, pa.n_pieces, n_sl, part_base, tl ? tl->n_parts : 0, tile_partial, tile_groups,
+                tile_groups > 1 ? uint32_t(((uint64_t(1) << 32) + tile_groups - 1) / tile_groups) : 0u, tile_group_stride, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
+                static_cast<T *>(out) + f0, ldy, int(fw), store_vec, fin_self_mode, own,
+                plan->col_counts, bias ? bias + f0 : nullptr, relu);
+        };
+        auto launch_lanes = [&](auto elem) {
+            if (lanes == 8) launch(elem, std::integral_constant<int, 8>());
+            else if (lanes == 4) launch(elem, std::integral_constant<int, 4>());
+            else launch(elem, std::integral_constant<int, 2>());
+        };
+        if (o.dtype == GNN_F32) launch_lanes(float());
+        else launch_lanes(bf16_t());
+        return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
+    };
+
+    if (hot_tables) {  // in launches of 8, 4, 2 and 1 lines, as below
+        for (int64_t l0 = 0; l0 < n_table_lines;) {
+            int ls = 3;
+            while ((int64_t(1) << ls) > n_table_lines - l0) --ls;
+            const int64_t f0 = l0 * line_elems, left = F - f0, fw = line_elems << ls;
+            const int rc = launch_pieces(f0, fw < left ? fw : left, ls, static_cast<const char *>(tables) + l0 * table_stride * esz);
+            if (rc != GNN_OK) { finish_overlap(); return rc; }
+            l0 += int64_t(1) << ls;
+        }
     }
 
     // gather_kernel: 16-byte strips at the alignment of a word, tables whose offsets are 32 bits
@@ -1853,58 +1960,10 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             a.ldp = gnn_partial_ld(F);
         }
         const bool blocked = bl.active && segs[gi].tail_slice < 0;
-        if (blocked) {
-            const int line_floats = lanes * max_vec;
-            int rc = gnn_plan_blocked_partial(plan, 1 << log2_s, line_floats, stream);
+        if (blocked && !hot_tables) {
+            const int rc = launch_pieces(f0, fw, log2_s, a.X);
             if (rc != GNN_OK) { finish_overlap(); return rc; }
-            PieceArgs pa{};
-            pa.pieces = tl ? tl->left.pieces : bl.pieces;
-            pa.n_pieces = tl ? tl->left.n_pieces : bl.n_pieces;
-            pa.idx = bl.indices;
-            pa.epos = bl.epos;
-            pa.idx16 = bl.idx16;
-            pa.piece_block = tl ? tl->left.piece_block : bl.piece_block;
-            pa.n_blocks = bl.n_blocks;
-            pa.hot_lines = bl.hot_lines;
-            pa.block_lines = bl.block_lines;
-            pa.w = w;
-            pa.w_blk = w_blk;
-            pa.scale_blk = scale_blk;
-            pa.X = a.X;
-            pa.slice_stride = layout.table_stride;
-            pa.partial = static_cast<float *>(plan->blk_partial.p);
-            pa.log2_slices = log2_s;
-            const int64_t per_block = int64_t(64 / lanes) * kWavesPerBlock;
-            const int64_t pblocks = ((pa.n_pieces + per_block - 1) / per_block) << log2_s;
-            if (pblocks > INT32_MAX) { finish_overlap(); return GNN_ERR_UNSUPPORTED; }
-            const int n_sl = 1 << log2_s;
-            const dim3 pgrid(static_cast<unsigned>(pblocks)), fgrid(static_cast<unsigned>((bl.n_hot * n_sl * lanes + 255) / 256));
-            const int32_t *hot_rows = plan->row_perm + bl.hot_begin;
-            const OwnRowSrc own = own_row_src(f0);
-            const float *tile_partial = tl ? static_cast<const float *>(plan->tile_partial.p) + f0 / line_elems * tl->n_parts * line_floats : nullptr;
-            const int64_t tile_group_stride = tl ? layout.main_lines * tl->n_parts * line_floats : 0;
-            const uint32_t *rowbase = tl ? tl->left.rowbase : bl.rowbase, *part_base = tl ? tl->part_base : nullptr;
-            auto launch = [&](auto elem, auto n_lanes) {
-                using T = decltype(elem);
-                constexpr int L = decltype(n_lanes)::value;
-                if (pa.n_pieces == 0) {}
-                else if (coef) piece_kernel<T, true, L><<<pgrid, kBlockThreads, 0, stream>>>(pa);
-                else piece_kernel<T, false, L><<<pgrid, kBlockThreads, 0, stream>>>(pa);
-                blk_finalize_kernel<T, L><<<fgrid, 256, 0, stream>>>(
-                    hot_rows, bl.n_hot, rowbase, pa.partial, pa.n_pieces, n_sl, part_base, tl ? tl->n_parts : 0, tile_partial, tile_groups,
-                    tile_groups > 1 ? uint32_t(((uint64_t(1) << 32) + tile_groups - 1) / tile_groups) : 0u, tile_group_stride, indptr, o.indptr_is_64 ? 1 : 0, dst_mode,
-                    static_cast<T *>(out) + f0, ldy, int(fw), store_vec, fin_self_mode, own,
-                    plan->col_counts, bias ? bias + f0 : nullptr, relu);
-            };
-            auto launch_lanes = [&](auto elem) {
-                if (lanes == 8) launch(elem, std::integral_constant<int, 8>());
-                else if (lanes == 4) launch(elem, std::integral_constant<int, 4>());
-                else launch(elem, std::integral_constant<int, 2>());
-            };
-            if (o.dtype == GNN_F32) launch_lanes(float());
-            else launch_lanes(bf16_t());
-            if (hipGetLastError() != hipSuccess) { finish_overlap(); return GNN_ERR_LAUNCH; }
-        } else if (has_hub) {
+        } else if (!blocked && has_hub) {
             plain_hub_columns = true;
             if (f0 < plain_hub_col_begin) plain_hub_col_begin = f0;
         }

@@ -362,6 +362,15 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             enable = n_edges > 0;
         }
         if (enable && automatic) enable = gnn_blocks_by_itself(plan, n_edges);
+        // Few edges per vertex: the last block takes the sources of which a row has fewer than about 20 edges in a block, so that a piece is worth
+        // its partial line, in bf16 twice the size of what it gathers, and pieces are longer (27.8 M vertices, 404 M edges, bf16 F=128, ms: edges
+        // 5, 10, 15, 30 of pieces of 96 13.90, 13.47, 13.44, 13.23; 10 of pieces of 192, 384 13.16, 13.00; 20 of 256 12.94).
+        if (enable && gnn_few_edges(plan)) {
+            const double count = 20.0 * double(n_hot) * double(E) / (double(prm.block_lines) * double(n_edges));
+            const int64_t least = gnn_count_bucket_lower_bound(gnn_count_bucket_of(int64_t(count < 1e9 ? count : 1e9)));
+            if (plan->blocking.rest_min_count == 0 && least > prm.rest_min_count) prm.rest_min_count = least;
+            if (plan->blocking.max_piece == 0) prm.max_piece = 256;
+        }
         BlockMap m{};
         if (enable) {
             // sources gathered fewer than rest_min_count times share the last block (the threshold is a bucket boundary)
@@ -476,5 +485,59 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
         out->pieces = plan->blk_pieces;
         out->rowbase = plan->blk_rowbase;
     }
+    return GNN_OK;
+}
+
+namespace {
+
+// out[rank[v]] = v for the ranks below `rows`
+__global__ void __launch_bounds__(256) blk_hot_vertices_kernel(const int32_t *__restrict__ rank, int64_t N, int32_t rows, int32_t *__restrict__ out) {
+    const int64_t stride = int64_t(gridDim.x) * blockDim.x;
+    for (int64_t v = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; v < N; v += stride)
+        if (rank[v] < rows) out[rank[v]] = int32_t(v);
+}
+
+// What gnn_plan_hot reports, built where it is not there.
+int build_hot(gnn_plan *plan, const void *indptr, const int32_t *indices, hipStream_t stream) {
+    gnn_rank_layout rl{};
+    int rc = gnn_plan_rank_indices(plan, indptr, indices, false, stream, &rl);
+    if (rc != GNN_OK) return rc;
+    gnn_blocked_layout bl{};
+    if ((rc = gnn_plan_blocked(plan, indptr, stream, &bl)) != GNN_OK || !bl.active || plan->blk_hot_vertices) return rc;
+    uint32_t begin = 0;
+    GNN_HIP_TRY(hipMemcpyAsync(&begin, plan->blk_cell_off + int64_t(plan->blk_n_blocks - 1) * plan->blk_n_hot, 4, hipMemcpyDeviceToHost, stream));
+    GNN_HIP_TRY(hipStreamSynchronize(stream));
+    const int64_t n_cold = plan->blk_n_edges - int64_t(begin);
+    int32_t *hot = nullptr, *cold = nullptr;
+    if (!gnn_dev_alloc(&cold, n_cold + kStreamPad, stream) || !gnn_dev_alloc(&hot, plan->blk_rest_begin, stream)) {
+        gnn_dev_free_on(cold, stream);
+        return GNN_ERR_ALLOC;
+    }
+    blk_hot_vertices_kernel<<<grid_for(plan->n_rows, 256), 256, 0, stream>>>(plan->rank, plan->n_rows, plan->blk_rest_begin, hot);
+    if (n_cold > 0)
+        blk_gather_u32_kernel<<<grid_for(n_cold, 256), 256, 0, stream>>>(reinterpret_cast<const uint32_t *>(indices), plan->blk_epos + begin, n_cold,
+                                                                         0xFFFFFFFFu, reinterpret_cast<uint32_t *>(cold));
+    if (hipGetLastError() != hipSuccess) {
+        gnn_dev_free_on(cold, stream);
+        gnn_dev_free_on(hot, stream);
+        return GNN_ERR_LAUNCH;
+    }
+    plan->blk_cold_begin = begin;
+    plan->blk_cold_vertices = cold;
+    plan->blk_hot_vertices = hot;
+    return GNN_OK;
+}
+
+}  // namespace
+
+int gnn_plan_hot(gnn_plan *plan, const void *indptr, const int32_t *indices, hipStream_t stream, gnn_hot_layout *out) {
+    *out = gnn_hot_layout{};
+    int rc = plan->blk_hot_vertices ? GNN_OK : build_hot(plan, indptr, indices, stream);
+    if (rc != GNN_OK || !plan->blk_hot_vertices) return rc;
+    if ((rc = gnn_plan_blocked(plan, indptr, stream, &out->blocks)) != GNN_OK) return rc;
+    out->rows = plan->blk_rest_begin;
+    out->vertices = plan->blk_hot_vertices;
+    out->cold_vertices = plan->blk_cold_vertices;
+    out->cold_begin = plan->blk_cold_begin;
     return GNN_OK;
 }

@@ -150,6 +150,13 @@ struct gnn_plan {
     float *blk_bound_w = nullptr;
     bool bound_w_stale = false;       // the copy is older than the last binding
     int64_t bound_w_version = 0;      // number of the last binding
+    // Hot tables (gnn_plan_hot): the vertices of the ranks below blk_rest_begin, and the vertices (not ranks) of the last block's
+    // edges, whose first is edge blk_cold_begin of blk_indices.
+    int32_t *blk_hot_vertices = nullptr;
+    int32_t *blk_cold_vertices = nullptr;
+    int64_t blk_cold_begin = 0;
+    uint32_t hot_refused = 0;         // calls since there was no room for them, with that one; 0: there was
+    uint64_t hot_ready[2][5][5] = {}; // what calls in a capture can use: [type][factor 0 ... 3 or weights], bit `lines`
     gnn_grown blk_partial;            // fp32 partial sums of one launch: [slices][blk_n_pieces][floats per line]
     gnn_tiles tiles[7];               // for lines of 128, 64 and 32 bytes of fp32, then of bf16; [GNN_TILES_PLAIN]: see gnn_plan_tiles
     gnn_grown tile_partial;           // their partial lines: [groups][slices][hot rows][floats per line]
@@ -185,6 +192,16 @@ struct gnn_blocked_layout {
 // Builds the layout on first use (allocation; needs the rank layout) and reports it.  Inactive when
 // the graph or the plan's thresholds do not suit it.
 int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn_blocked_layout *out);
+// Hot tables, for graphs of few edges per vertex: the copy has the sources of the blocks only, the most-gathered ones, and everything else is
+// gathered where it lies: the pieces of the last block by vertex, the short rows by the kernels that serve rows in place.
+struct gnn_hot_layout {
+    gnn_blocked_layout blocks;
+    int64_t rows;                  // of a table: sources of the blocks
+    const int32_t *vertices;       // [rows] the vertex of every rank
+    const int32_t *cold_vertices;  // of the edges from cold_begin on
+    int64_t cold_begin;
+};
+int gnn_plan_hot(gnn_plan *plan, const void *indptr, const int32_t *indices, hipStream_t stream, gnn_hot_layout *out);
 // Makes plan->blk_partial large enough, for a call on `stream`, for `slices` column slices of `line_floats` floats per piece.
 int gnn_plan_blocked_partial(gnn_plan *plan, int slices, int line_floats, hipStream_t stream);
 // The plan's per-edge factor stream `mode` (gnn_plan_edge_scale, which must have been built) in the order
@@ -325,6 +342,10 @@ struct gnn_layout {
     // slice-major copy, 8, 4 or 2 of a copy whose rows are one line of 128, 64 or 32 bytes (one table), else 0.
     int32_t line_lanes;
     int64_t bytes;        // size of the whole copy for N rows
+    // No copy of the whole matrix: rows are gathered in place, except by the long rows from the most-gathered sources, of which there are
+    // slice tables (gnn_plan_hot_ready; lines, line_lanes).
+    bool hot_tables;
+    int64_t lines;        // of 128 bytes that hold a row
 };
 
 // Will calls with this plan serve their long rows as source-blocked pieces (gnn_plan_blocked)?  Known
@@ -338,6 +359,14 @@ struct gnn_layout {
 static inline bool gnn_blocks_by_itself(const gnn_plan *plan, int64_t long_edges) {
     return (plan->n_rows >= 4 * int64_t(32768) || (plan->n_rows >= 32768 && plan->n_edges >= 16000000)) && long_edges * 4 >= plan->n_edges;
 }
+static inline int64_t gnn_edges_from_bin(const gnn_plan *plan, int first_bin) {
+    int64_t edges = 0;
+    for (int b = first_bin; b < plan->n_bins; ++b) edges += plan->bin_edges[b];
+    return edges;
+}
+// Graphs of fewer edges per vertex than a copy of the whole matrix pays for.  Blocked by themselves they have hot tables (gnn_plan_hot); the
+// sources of the last block are never copied, so nothing of it goes into tiles.
+static inline bool gnn_few_edges(const gnn_plan *plan) { return plan->blocking.min_degree == 0 && plan->n_edges < 16 * plan->n_rows; }
 static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz, int64_t row_bytes, bool weights) {
     if (!plan || plan->n_edges <= 0 || plan->n_edges >= int64_t(INT32_MAX)) return false;
     const bool automatic = plan->blocking.min_degree == 0;
@@ -357,10 +386,22 @@ static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz, int64
     for (int i = 0; i < plan->params.n_thresholds; ++i)
         if (plan->params.thresholds[i] == min_degree) first_bin = i + 1;
     if (first_bin < 0 || plan->n_rows - plan->bin_offsets[first_bin] <= 0) return false;
-    int64_t long_edges = 0;
-    for (int b = first_bin; b < plan->n_bins; ++b) long_edges += plan->bin_edges[b];
+    const int64_t long_edges = gnn_edges_from_bin(plan, first_bin);
     if (long_edges <= 0) return false;
     return !automatic || gnn_blocks_by_itself(plan, long_edges);
+}
+// Are there gathers enough for hot tables?  They save lines that come from behind the L2s, and cost the launches of pieces and tiles.  Rows off line
+// boundaries are aligned in the tables; bf16 rows have partial lines of twice their size.  MEAN, in place -> hot tables, us, power-law graphs by
+// their edges in rows of 256 and more: fp32 19.5 M edges F=32 461 -> 417, 64 895 -> 777, 100 2316 -> 1760, 256 4506 -> 3506; 13.1 M F=32 332 -> 330, 36 718
+// -> 663, 64 633 -> 597; 6.5 M F=32 160 -> 169, 64 315 -> 316, 100 824 -> 724, 256 1628 -> 1397; 3.5 M F=100 491 -> 472, 256 973 -> 934; 2.4 M F=100 260 ->
+// 279, 256 493 -> 509; bf16 19.5 M F=48 801 -> 720, 64 449 -> 456, 128 1029 -> 880; 13.1 M F=128 702 -> 674; 6.5 M F=128 363 -> 371, 200 814 -> 751; 3.6 M
+// F=200 369 -> 385, 512 857 -> 764; 243 M (27.8 M vertices) F=128 15.1 -> 12.8 ms forward, 15.1 -> 13.5 backward.
+static inline bool gnn_hot_tables_pay(const gnn_plan *plan, int64_t row_bytes, int esz, bool lines_ok) {
+    int first_bin = -1;
+    for (int i = 0; i < plan->params.n_thresholds; ++i)
+        if (plan->params.thresholds[i] == 256) first_bin = i + 1;
+    if (first_bin < 0) return false;
+    return double(gnn_edges_from_bin(plan, first_bin)) * double(row_bytes) >= (!lines_ok ? (esz == 4 ? 1.2e9 : 1.8e9) : (esz == 4 && row_bytes <= 128 ? 2.0e9 : 3.2e9));
 }
 
 // The edge weights of a call.  BOUND: the array of gnn_plan_bind_edge_weights; FREE: any other.
@@ -464,6 +505,7 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
         L.ld_pad = ((lines - 1) | 1) * line_elems;
     }
     L.main_lines = L.tail_elems > 0 ? lines - 1 : lines;
+    L.lines = lines;
     L.slice_major = allow_tail && L.padded_copy && L.slices_wanted && lines >= 2 && lines <= 256 &&
                     !(flags & GNN_FLAG_NO_SLICE_TABLES);
     L.table_stride = 0;
@@ -476,6 +518,13 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
     }
     L.line_lanes = L.slice_major ? 8 : 0;
     if (allow_tail && L.padded_copy && narrow_pieces && !(flags & GNN_FLAG_NO_SLICE_TABLES)) L.line_lanes = int32_t(narrow_bytes / 16);
+    // Rows of whole strips of 16 bytes, because those that are gathered in place end with the row; factors or weights, not the products of both,
+    // which every call would make anew.
+    constexpr int kStay = GNN_FLAG_NO_PADDED_COPY | GNN_FLAG_FORCE_PADDED_COPY | GNN_FLAG_NO_COLUMN_SLICES | GNN_FLAG_NO_SLICE_TABLES |
+                          GNN_FLAG_NO_RANK_ORDER | GNN_FLAG_FORCE_COLD_HINTS;
+    L.hot_tables = plan && blocks_expected && gnn_few_edges(plan) && !L.padded_copy && allow_tail && max_slices == 0 && !(flags & kStay) &&
+                   row_bytes > 64 && row_bytes % 16 == 0 && lines <= 256 && !(scaled_source && weights) && gnn_hot_tables_pay(plan, row_bytes, esz, lines_ok);
+    if (L.hot_tables) L.line_lanes = 8;
     return L;
 }
 
@@ -516,6 +565,12 @@ int gnn_plan_create_pair(const void *indptr, const void *indptr_t, const int32_t
 int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const int64_t *edge_ids, const void *indptr, int ip64, hipStream_t stream,
                           const float **out);
 int gnn_plan_edge_scale(gnn_plan *plan, const int32_t *indices, int mode, hipStream_t stream, const float **out);
+
+// gnn_plan_hot and everything else that a call over hot tables takes, but for the tables' contents: their memory (plan->padded), partial sums, tiles,
+// coefficients in their order.  mode: the factor of the gathered rows.  False: not to be had (nothing is built in a capture, and there may be
+// no room); the call stays in place, and asks again as often as gnn_plan_tiles does for the bit matrix.
+bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indices, int mode, gnn_weight_kind weights, int64_t F, int esz, hipStream_t stream,
+                        gnn_hot_layout *out);
 
 // ---- producer-side layout ----
 // Where a kernel that PRODUCES a matrix (the dense product of a layer, the masked output gradient)

@@ -675,6 +675,47 @@ int gnn_plan_padded(gnn_plan *plan, int64_t bytes, hipStream_t stream) {
     return GNN_OK;
 }
 
+bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indices, int mode, gnn_weight_kind weights, int64_t F, int esz, hipStream_t stream,
+                        gnn_hot_layout *out) {
+    const int line_elems = 128 / esz;
+    const int64_t lines = (F + line_elems - 1) / line_elems;
+    uint64_t &word = plan->hot_ready[esz == 2][weights == GNN_WEIGHTS_NONE ? mode : 4][lines >> 6];
+    const uint64_t bit = uint64_t(1) << (lines & 63);
+    if (weights == GNN_WEIGHTS_FREE || (mode && weights != GNN_WEIGHTS_NONE) || (plan->blk_decided && plan->blk_n_pieces <= 0)) return false;
+    if (gnn_capturing(stream)) {
+        if (!(word & bit)) return false;
+    } else if (plan->hot_refused & (plan->hot_refused - 1)) {
+        ++plan->hot_refused;
+        return false;
+    }
+    int slices = 1;
+    while (slices < 8 && slices * 2 <= lines) slices *= 2;
+    const gnn_tiles *tl = nullptr;
+    const float *unused = nullptr;
+    int rc = gnn_plan_hot(plan, indptr, indices, stream, out);
+    if (rc == GNN_OK && !out->blocks.active) return false;
+    if (rc == GNN_OK) rc = gnn_plan_padded(plan, out->rows * lines * 128, stream);
+    if (rc == GNN_OK) rc = gnn_plan_blocked_partial(plan, slices, line_elems, stream);
+    if (rc == GNN_OK) rc = gnn_plan_tiles_with_room(plan, 8, esz == 2, !mode && weights == GNN_WEIGHTS_NONE, int(lines), line_elems, stream, &tl);
+    if (rc == GNN_OK && mode) {
+        rc = gnn_plan_edge_scale(plan, indices, mode, stream, &unused);
+        if (rc == GNN_OK) rc = gnn_plan_blocked_edge_scale(plan, mode, stream, &unused);
+        if (rc == GNN_OK && tl) rc = gnn_plan_tile_coefs(plan, tl, nullptr, plan->edge_scale[mode - 1], mode, false, stream, &unused);
+    }
+    if (rc == GNN_OK && weights == GNN_WEIGHTS_BOUND) {
+        rc = gnn_plan_blocked_bound_weights(plan, stream, &unused);
+        if (rc == GNN_OK && tl) rc = gnn_plan_tile_coefs(plan, tl, plan->bound_w, nullptr, 0, true, stream, &unused);
+    }
+    if (rc != GNN_OK) {
+        (void)hipGetLastError();
+        ++plan->hot_refused;
+        return false;
+    }
+    plan->hot_refused = 0;
+    word |= bit;
+    return true;
+}
+
 // What a hot call with edge weights of this kind takes (run_aggregate of aggregate.hip, on a dense matrix at a line boundary:
 // ld = F), except for the per-edge factors `mode` (0: none).
 static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int64_t F, int esz, gnn_weight_kind weights, hipStream_t stream) {
@@ -682,6 +723,8 @@ static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int6
     const gnn_layout layout = gnn_choose_layout(plan, plan->n_rows, F, esz, F, true, 0, 0, /*allow_tail=*/true, /*scaled_source=*/mode != 0,
                                                 blocks, weights != GNN_WEIGHTS_NONE);
     if (!layout.padded_copy) {
+        gnn_hot_layout unused_hot{};
+        if (layout.hot_tables) (void)gnn_plan_hot_ready(plan, plan->indptr_seen, indices, mode, weights, F, esz, stream, &unused_hot);  // else in place
         if (!layout.slices_wanted) return GNN_OK;
         const int32_t *unused_idx = nullptr;  // the flagged index copy of the cold hints, where they pay
         return gnn_plan_cold_indices(plan, indices, false, stream, &unused_idx);
@@ -759,6 +802,8 @@ extern "C" GNN_API void gnn_plan_destroy(gnn_plan *plan) {
     gnn_dev_free(plan->blk_rowbase);
     gnn_dev_free(plan->blk_partial.p);
     gnn_dev_free(plan->blk_cell_off);
+    gnn_dev_free(plan->blk_hot_vertices);
+    gnn_dev_free(plan->blk_cold_vertices);
     for (gnn_tiles &t : plan->tiles) gnn_tiles_free(t);
     gnn_dev_free(plan->tile_partial.p);
     for (int i = 0; i < 3; ++i) gnn_dev_free(plan->blk_edge_scale[i]);

@@ -4,24 +4,26 @@
 // 980 MB ran at the rate at which lines move behind the L2s (48 G/s, 5.05 ms).  Here the additions are brought to where
 // their sums are kept.  Columns are taken four at a time (a quad), so that the sums of 4096 vertices fit the LDS of a
 // compute unit, and the pairs (vertex, value) of a quad are sorted by such ranges of vertices first:
-//   1 resolve    winner positions -> source vertices, quad by quad ([quad][v][4]), beside the values
+//   1 resolve    winner positions -> source vertices, quad by quad ([quad][v][4]), beside the values; rows without winners are left out
 //   2 count      pairs per (quad, range, part of the rows), scanned into write positions
-//   3 partition  tiles of 8192 pairs are ordered by range in LDS and leave as runs of consecutive pairs, 6 bytes each
+//   3 partition  tiles of 16384 pairs are ordered by range in LDS and leave as runs of consecutive pairs, 6 bytes each
 //   4 add        a workgroup adds the pairs of a range in LDS and writes its rows; a range with many pairs (the vertices
 //                that win often) is cut into pieces, which add their sums to rows filled with zeros
-// All of it streams, about 44 bytes per pair, at 2.4 to 3.4 TB/s: a run of the partition is 14 pairs, 56 and 28 bytes, and a
-// row of the sums 16 bytes, which leave the L2s as lines only where they meet there.  Per round of 13 quads (122 M pairs):
-// resolve 0.72 ms, count 0.15, partition 0.60, add 0.53.  Ranges of 8192 vertices (one workgroup per compute unit) add
-// slower, 0.61, for runs twice as long, 0.53.
+// All of it streams, about 44 bytes per pair, 20 of them before rows without winners (43 % there) are left out, at 2.4 to 3.4 TB/s: a run of the
+// partition is 27 pairs, 54 and 108 bytes, and a row of the sums 16 bytes, which leave the L2s as lines only where they meet there (counters: 1.6
+// GB written for 0.94 of pairs in runs half as long, 2.3 for 0.98 of sums).  Per round of 13 quads, 122 M pairs, with all rows and tiles of 8192 pairs ->
+// now: resolve 0.74 -> 0.54 ms, count 0.16 -> 0.09, partition 0.62 -> 0.43 (of 8192 0.50), add 0.55.  Ranges of 8192 vertices (one workgroup per compute unit)
+// add slower, 0.61, for runs twice as long, 0.53.
 #include "common.h"
 
 namespace {
 
-constexpr int kTileRows = 2048;                // rows of a quad that are ordered at a time
+constexpr int kTileRows = 4096;                // rows of a quad that are ordered at a time
 constexpr int kTile = kTileRows * 4;
-constexpr int kPartThreads = 512;
+constexpr int kPartThreads = 1024;
 constexpr int kPerThread = kTile / kPartThreads;
-constexpr int kResolveRows = 32;
+constexpr int kResolveRows = 64, kResolveThreads = 512;
+static_assert(kResolveRows == 64 && kTileRows % kResolveRows == 0, "a wavefront looks at the rows of a workgroup, which lie in one part");
 constexpr int kMaxRanges = 1024;
 constexpr int kMaxRangeLog2 = 13, kMinRangeLog2 = 9;
 constexpr int kAddThreads = 1024;
@@ -38,7 +40,8 @@ struct Round {
     int32_t d, col0, n_quads;                  // columns col0 .. col0 + 4 * n_quads
     int32_t range_log2, n_ranges, n_parts;
     int64_t part_rows;
-    uint32_t *u;                               // [n_quads][N][4], ~0: no winner
+    uint32_t *live;                            // [n_parts] rows of the part that have winners: the first so many below
+    uint32_t *u;                               // [n_quads][N][4], a part's rows from its first on; ~0: no winner
     float *val;                                // likewise
     uint32_t *table;                           // [n_quads][n_ranges][n_parts] + 1
     uint4 *pieces;                             // (range, quad * 2 + 1 if the range is split, begin, end)
@@ -47,16 +50,21 @@ struct Round {
     float *key_val;
 };
 
-__global__ void __launch_bounds__(256) resolve_kernel(const Round r, const int32_t *__restrict__ indices, const int64_t *__restrict__ eid,
+__global__ void __launch_bounds__(kResolveThreads) resolve_kernel(const Round r, const int32_t *__restrict__ indices, const int64_t *__restrict__ eid,
                                                       const int32_t *__restrict__ arg, const float *__restrict__ dO, int64_t ldo,
                                                       const float *__restrict__ fE, int64_t lde, int ewide, int binop) {
     // Lanes run along the rows, so that one load instruction looks up winners of a few rows (their edges lie side by side);
     // the results turn in LDS and leave as runs of 512 bytes per quad.
     __shared__ uint4 out_u[kMaxQuads][kResolveRows + 1];
     __shared__ float4 out_g[kMaxQuads][kResolveRows + 1];
+    // Rows without a winner (no edges: 43 % of the vertices of the 2.45 M-vertex graph) are left out, so that no later pass reads them.
+    __shared__ uint32_t has_winner[kResolveRows], first_out;
+    __shared__ uint8_t rows_out[kResolveRows];
+    if (threadIdx.x < kResolveRows) has_winner[threadIdx.x] = 0;
+    __syncthreads();
     const int64_t v0 = int64_t(blockIdx.x) * kResolveRows;
     const int n_rows = r.N - v0 < kResolveRows ? int(r.N - v0) : kResolveRows;
-    for (int item = threadIdx.x; item < n_rows * r.n_quads; item += 256) {
+    for (int item = threadIdx.x; item < n_rows * r.n_quads; item += kResolveThreads) {
         const int row = item / r.n_quads, q = item - row * r.n_quads, col = r.col0 + q * 4;
         const int64_t v = v0 + row;
         uint32_t u[4];
@@ -67,7 +75,8 @@ __global__ void __launch_bounds__(256) resolve_kernel(const Round r, const int32
             typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
             typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
             const i32x4 a = __builtin_nontemporal_load(reinterpret_cast<const i32x4 *>(arg + v * r.d + col));
-            const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(dO + v * ldo + col));
+            f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+            if ((a[0] & a[1] & a[2] & a[3]) >= 0) x = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(dO + v * ldo + col));
 #pragma unroll
             for (int i = 0; i < 4; ++i) { e[i] = a[i]; g[i] = x[i]; }
         } else {
@@ -90,17 +99,34 @@ __global__ void __launch_bounds__(256) resolve_kernel(const Round r, const int32
                 g[i] = binop == GNN_BIN_MUL ? g[i] * y : g[i] / y;
             }
         }
+        if ((u[0] & u[1] & u[2] & u[3]) != ~0u) has_winner[row] = 1;
         out_u[q][row] = make_uint4(u[0], u[1], u[2], u[3]);
         out_g[q][row] = make_float4(g[0], g[1], g[2], g[3]);
     }
     __syncthreads();
-    for (int item = threadIdx.x; item < kResolveRows * r.n_quads; item += 256) {
-        const int q = item / kResolveRows, row = item % kResolveRows;
-        if (row >= n_rows) continue;
-        const int64_t at = int64_t(q) * r.N + v0 + row;
-        reinterpret_cast<uint4 *>(r.u)[at] = out_u[q][row];
-        reinterpret_cast<float4 *>(r.val)[at] = out_g[q][row];
+    const int64_t part = v0 / r.part_rows;
+    if (threadIdx.x < 64) {
+        const unsigned long long m = __ballot(has_winner[threadIdx.x] != 0);
+        if (m >> threadIdx.x & 1ull) rows_out[__popcll(m & ((1ull << threadIdx.x) - 1ull))] = uint8_t(threadIdx.x);
+        if (threadIdx.x == 0) {
+            has_winner[0] = uint32_t(__popcll(m));
+            first_out = m ? atomicAdd(&r.live[part], uint32_t(__popcll(m))) : 0u;
+        }
     }
+    __syncthreads();
+    const int n_out = int(has_winner[0]);
+    const int64_t out0 = part * r.part_rows + first_out;
+    for (int item = threadIdx.x; item < kResolveRows * r.n_quads; item += kResolveThreads) {
+        const int q = item / kResolveRows, k = item % kResolveRows;
+        if (k >= n_out) continue;
+        const int64_t at = int64_t(q) * r.N + out0 + k;
+        reinterpret_cast<uint4 *>(r.u)[at] = out_u[q][rows_out[k]];
+        reinterpret_cast<float4 *>(r.val)[at] = out_g[q][rows_out[k]];
+    }
+}
+
+__global__ void __launch_bounds__(kPartThreads) clear_live_kernel(const Round r) {  // one workgroup
+    for (int p = threadIdx.x; p < r.n_parts; p += kPartThreads) r.live[p] = 0;
 }
 
 __global__ void __launch_bounds__(kPartThreads) count_kernel(const Round r) {
@@ -108,7 +134,7 @@ __global__ void __launch_bounds__(kPartThreads) count_kernel(const Round r) {
     const int q = int(blockIdx.x) / r.n_parts, p = int(blockIdx.x) % r.n_parts;
     for (int b = threadIdx.x; b < r.n_ranges; b += kPartThreads) hist[b] = 0;
     __syncthreads();
-    const int64_t begin = p * r.part_rows, end = begin + r.part_rows < r.N ? begin + r.part_rows : r.N;
+    const int64_t begin = p * r.part_rows, end = begin + r.live[p];
     const uint4 *u = reinterpret_cast<const uint4 *>(r.u) + int64_t(q) * r.N;
     for (int64_t v = begin + threadIdx.x; v < end; v += kPartThreads) {
         const uint4 x = u[v];
@@ -129,7 +155,7 @@ __global__ void __launch_bounds__(kPartThreads) partition_kernel(const Round r) 
     __shared__ float pair_val[kTile];
     const int q = int(blockIdx.x) / r.n_parts, p = int(blockIdx.x) % r.n_parts;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t begin = p * r.part_rows, end = begin + r.part_rows < r.N ? begin + r.part_rows : r.N;
+    const int64_t begin = p * r.part_rows, end = begin + r.live[p];
     for (int b = threadIdx.x; b < r.n_ranges; b += kPartThreads) next[b] = r.table[(int64_t(q) * r.n_ranges + b) * r.n_parts + p];
     const uint4 *us = reinterpret_cast<const uint4 *>(r.u) + int64_t(q) * r.N;
     const float4 *vals = reinterpret_cast<const float4 *>(r.val) + int64_t(q) * r.N;
@@ -341,27 +367,28 @@ int gnn_scatter_winners(const int32_t *indices, const int64_t *eid, const int32_
     const int64_t n_rounds = (all_quads + quads - 1) / quads;
     quads = (all_quads + n_rounds - 1) / n_rounds;
     const int64_t tiles = (N + kTileRows - 1) / kTileRows;
-    int64_t parts = 512 / quads;
+    int64_t parts = 256 / quads;  // a workgroup of the partition fills a compute unit
     if (parts > tiles) parts = tiles;
     r.part_rows = (tiles + parts - 1) / parts * kTileRows;
     r.n_parts = int32_t((N + r.part_rows - 1) / r.part_rows);
     const int64_t pairs = N * quads * 4, entries = quads * r.n_ranges * r.n_parts + 1;
     // every range has a piece, and no more than this are added for the pairs beyond its first
     const int64_t max_pieces = quads * r.n_ranges + pairs / kPiecePairs;
-    gnn_dev_ptr<uint32_t> u, table, sums, count;
+    gnn_dev_ptr<uint32_t> u, table, sums, count, live;
     gnn_dev_ptr<uint4> pieces;
     gnn_dev_ptr<float> val, key_val;
     gnn_dev_ptr<uint16_t> key;
     if (!u.alloc_on(pairs, stream) || !val.alloc_on(pairs, stream) || !key.alloc_on(pairs, stream) || !key_val.alloc_on(pairs, stream) ||
         !table.alloc_on(entries, stream) || !sums.alloc_on(gnn_scan_sums_elems(entries), stream) || !pieces.alloc_on(max_pieces, stream) ||
-        !count.alloc_on(1, stream))
+        !count.alloc_on(1, stream) || !live.alloc_on(r.n_parts, stream))
         return GNN_ERR_ALLOC;
-    r.u = u.p; r.val = val.p; r.key = key.p; r.key_val = key_val.p; r.table = table.p; r.pieces = pieces.p; r.n_pieces = count.p;
+    r.u = u.p; r.val = val.p; r.key = key.p; r.key_val = key_val.p; r.table = table.p; r.pieces = pieces.p; r.n_pieces = count.p; r.live = live.p;
     for (int64_t q0 = 0; q0 < all_quads; q0 += quads) {
         r.col0 = int32_t(q0 * 4);
         r.n_quads = int32_t(all_quads - q0 < quads ? all_quads - q0 : quads);
         const int64_t blocks = (N + kResolveRows - 1) / kResolveRows;
-        resolve_kernel<<<unsigned(blocks), 256, 0, stream>>>(r, indices, eid, arg, dO, ldo, fE, lde, ewide ? 1 : 0, binop);
+        clear_live_kernel<<<1, kPartThreads, 0, stream>>>(r);
+        resolve_kernel<<<unsigned(blocks), kResolveThreads, 0, stream>>>(r, indices, eid, arg, dO, ldo, fE, lde, ewide ? 1 : 0, binop);
         count_kernel<<<unsigned(r.n_quads * r.n_parts), kPartThreads, 0, stream>>>(r);
         if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
         const int rc = gnn_scan_exclusive_u32(r.table, int64_t(r.n_quads) * r.n_ranges * r.n_parts + 1, sums.p, stream);

@@ -15,26 +15,11 @@
 //     transform first:  dP = A^^T G, dW = X^T dP, dX = dP W^T
 #include "common.h"
 
-#include <mutex>
-
 namespace {
 
 constexpr int kRowsPerBlock = 64;
 // the rows of partial column sums, one per block of rows, also take one plane per part of the split weight gradient
 static_assert(kRowsPerBlock <= GNN_SPLIT_MIN_K, "room for a plane per part");
-
-// A library-owned side stream per device (default priority, created on first use, kept until
-// the process ends): the weight-gradient product, which depends only on G, runs there while the
-// main stream does the input-gradient product and the gather-bound backward aggregation.
-hipStream_t side_stream() {
-    static std::mutex mu;
-    static hipStream_t streams[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!streams[dev] && hipStreamCreateWithFlags(&streams[dev], hipStreamNonBlocking) != hipSuccess) streams[dev] = nullptr;
-    return streams[dev];
-}
 
 // G = dH where H > 0 (else 0; plain copy without a rectifier) for a block of rows, written with row
 // stride ldg when G != nullptr, plus the block's column sums.  A thread owns one column and every
@@ -304,16 +289,16 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
     }
     const float *Gm = (need_g && !fold_gate) ? G : dH;
     const float *gate = (fold_gate && o.relu) ? H : nullptr;
-    // dW = Z^T G on `st`, and with the gate folded also db = the column sums of G, added in plane order
-    auto weight_gradient = [&](hipStream_t st) -> int {
-        if (!fold_gate) return gnn_matmul_impl(saved, F_in, 1, Gm, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, st);
+    // dW = Z^T G, and with the gate folded also db = the column sums of G, added in plane order
+    auto weight_gradient = [&]() -> int {
+        if (!fold_gate) return gnn_matmul_impl(saved, F_in, 1, Gm, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, stream);
         gnn_gemm_fold fold{};
         fold.b_gate = gate;
         fold.colsum = db ? part : nullptr;
         fold.colsum_planes = n_blocks;
-        int rcw = gnn_matmul_impl(saved, F_in, 1, dH, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, st, nullptr, &fold);
+        int rcw = gnn_matmul_impl(saved, F_in, 1, dH, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, stream, nullptr, &fold);
         if (rcw != GNN_OK || !db) return rcw;
-        launch_colsum_reduce(part, fold.n_planes, int(F_out), part2, db, st);
+        launch_colsum_reduce(part, fold.n_planes, int(F_out), part2, db, stream);
         return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
     };
 
@@ -323,36 +308,19 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
     a.stream = o.stream;
     a.plan = o.plan;
     if (agg_first) {
-        if (!dX) return weight_gradient(stream);
-        // dZ = G W^T first; then fork: dW = Z^T G (matrix cores) on the side stream while the caller's
-        // stream runs the gather-bound backward aggregation
+        if (!dX) return weight_gradient();
+        // dZ = G W^T, dW = Z^T G, then the aggregation.  One after the other: dW on a second stream beside the aggregation takes as much from it as
+        // it hides, and small graphs pay for the turn of streams (widths 100, 256, 256, 47, forward and backward, two streams -> one: 24,490
+        // vertices, 1.2 M edges 514 -> 491 us, 600 K, 30 M 8.49 -> 8.31 ms, 2.45 M, 124 M 35.07 -> 34.93; 64, 128, 128, 40 200 K, 10 M 1.71 -> 1.67,
+        // 1 M, 10 M the same).
         gnn_gemm_fold fold_a{};
         fold_a.a_gate = gate;
         rc = gnn_matmul_impl(Gm, F_out, 0, W, F_out, 1, T, F_in, N, F_in, F_out, nullptr, 0, nullptr, 0, stream, &pk, &fold_a);
         if (rc != GNN_OK) return rc;
-        hipStream_t side = side_stream();
-        hipEvent_t fork = nullptr, join = nullptr;
-        if (side && (hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess ||
-                     hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess)) {
-            if (fork) (void)hipEventDestroy(fork);
-            fork = join = nullptr;
-            side = nullptr;
-            (void)hipGetLastError();
-        }
-        if (side && (hipEventRecord(fork, stream) != hipSuccess || hipStreamWaitEvent(side, fork, 0) != hipSuccess)) {
-            (void)hipEventDestroy(fork);
-            (void)hipEventDestroy(join);
-            return GNN_ERR_LAUNCH;
-        }
-        rc = weight_gradient(side ? side : stream);
-        int rc2 = pk.active ? gnn_aggregate_prepacked(indptr_t, indices_t, dX, N, F_in, GNN_SAGE_GCN, &a, /*backward=*/true, force, nullptr, 0)
-                            : gnn_aggregate_bwd(indptr_t, indices_t, nullptr, T, dX, N, F_in, GNN_SAGE_GCN, &a);
-        if (side) {  // join, whatever happened above: the caller's stream must not run ahead of the side stream
-            if (hipEventRecord(join, side) != hipSuccess || hipStreamWaitEvent(stream, join, 0) != hipSuccess) rc = GNN_ERR_LAUNCH;
-            (void)hipEventDestroy(fork);  // released by the runtime once the recorded work has completed
-            (void)hipEventDestroy(join);
-        }
-        return rc != GNN_OK ? rc : rc2;
+        rc = weight_gradient();
+        if (rc != GNN_OK) return rc;
+        return pk.active ? gnn_aggregate_prepacked(indptr_t, indices_t, dX, N, F_in, GNN_SAGE_GCN, &a, /*backward=*/true, force, nullptr, 0)
+                         : gnn_aggregate_bwd(indptr_t, indices_t, nullptr, T, dX, N, F_in, GNN_SAGE_GCN, &a);
     }
     a.ldy = ldg;
     if (pk.active) {

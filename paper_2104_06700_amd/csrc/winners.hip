@@ -18,12 +18,13 @@
 
 namespace {
 
-constexpr int kTileRows = 4096;                // rows of a quad that are ordered at a time
-constexpr int kTile = kTileRows * 4;
-constexpr int kPartThreads = 1024;
-constexpr int kPerThread = kTile / kPartThreads;
-constexpr int kResolveRows = 64, kResolveThreads = 512;
-static_assert(kResolveRows == 64 && kTileRows % kResolveRows == 0, "a wavefront looks at the rows of a workgroup, which lie in one part");
+constexpr int kPairsPerThread = 16;
+constexpr int kPartThreads = 512, kWideThreads = 1024;  // of a partition: a tile is 4 rows of a quad for every thread
+constexpr int kTileRows = kPartThreads * kPairsPerThread / 4, kWideRows = kWideThreads * kPairsPerThread / 4;
+// Large rounds have the wide one, which fills a compute unit, and leave rows without winners out, for an atomic and a wait per 64 rows (rows, columns, us with
+// 2048-row tiles and all rows -> so: 150 K, 64 189 -> 214, 300 K, 100 557 -> 583, 400 K, 16 165 -> 190, 64 428 -> 412, without such rows 451 -> 475; 1 M,
+// 128 1705 -> 1480, without such rows 2076 -> 2087; 2.4 M, 100 without such rows 4337 -> 4264).
+constexpr int64_t kWideTiles = 2048;
 constexpr int kMaxRanges = 1024;
 constexpr int kMaxRangeLog2 = 13, kMinRangeLog2 = 9;
 constexpr int kAddThreads = 1024;
@@ -40,7 +41,7 @@ struct Round {
     int32_t d, col0, n_quads;                  // columns col0 .. col0 + 4 * n_quads
     int32_t range_log2, n_ranges, n_parts;
     int64_t part_rows;
-    uint32_t *live;                            // [n_parts] rows of the part that have winners: the first so many below
+    uint32_t *live;                            // [n_parts] rows of the part that have winners, the first so many below; or nullptr: all rows are there
     uint32_t *u;                               // [n_quads][N][4], a part's rows from its first on; ~0: no winner
     float *val;                                // likewise
     uint32_t *table;                           // [n_quads][n_ranges][n_parts] + 1
@@ -50,21 +51,26 @@ struct Round {
     float *key_val;
 };
 
-__global__ void __launch_bounds__(kResolveThreads) resolve_kernel(const Round r, const int32_t *__restrict__ indices, const int64_t *__restrict__ eid,
-                                                      const int32_t *__restrict__ arg, const float *__restrict__ dO, int64_t ldo,
-                                                      const float *__restrict__ fE, int64_t lde, int ewide, int binop) {
+// PACK: rows without a winner (no edges: 43 % of the vertices of the 2.45 M-vertex graph) are left out, so that no later pass reads them.
+template <bool PACK>
+__global__ void __launch_bounds__(PACK ? 512 : 256) resolve_kernel(const Round r, const int32_t *__restrict__ indices, const int64_t *__restrict__ eid,
+                                                                   const int32_t *__restrict__ arg, const float *__restrict__ dO, int64_t ldo,
+                                                                   const float *__restrict__ fE, int64_t lde, int ewide, int binop) {
     // Lanes run along the rows, so that one load instruction looks up winners of a few rows (their edges lie side by side);
-    // the results turn in LDS and leave as runs of 512 bytes per quad.
-    __shared__ uint4 out_u[kMaxQuads][kResolveRows + 1];
-    __shared__ float4 out_g[kMaxQuads][kResolveRows + 1];
-    // Rows without a winner (no edges: 43 % of the vertices of the 2.45 M-vertex graph) are left out, so that no later pass reads them.
-    __shared__ uint32_t has_winner[kResolveRows], first_out;
-    __shared__ uint8_t rows_out[kResolveRows];
-    if (threadIdx.x < kResolveRows) has_winner[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t v0 = int64_t(blockIdx.x) * kResolveRows;
-    const int n_rows = r.N - v0 < kResolveRows ? int(r.N - v0) : kResolveRows;
-    for (int item = threadIdx.x; item < n_rows * r.n_quads; item += kResolveThreads) {
+    // the results turn in LDS and leave as runs of 512 bytes and more per quad.
+    constexpr int ROWS = PACK ? 64 : 32, THREADS = PACK ? 512 : 256;
+    static_assert(kTileRows % ROWS == 0, "the rows of a workgroup lie in one part");
+    __shared__ uint4 out_u[kMaxQuads][ROWS + 1];
+    __shared__ float4 out_g[kMaxQuads][ROWS + 1];
+    __shared__ uint32_t has_winner[PACK ? ROWS : 1], n_packed, first_out;
+    __shared__ uint8_t rows_out[PACK ? ROWS : 1];
+    if constexpr (PACK) {
+        if (threadIdx.x < ROWS) has_winner[threadIdx.x] = 0;
+        __syncthreads();
+    }
+    const int64_t v0 = int64_t(blockIdx.x) * ROWS;
+    const int n_rows = r.N - v0 < ROWS ? int(r.N - v0) : ROWS;
+    for (int item = threadIdx.x; item < n_rows * r.n_quads; item += THREADS) {
         const int row = item / r.n_quads, q = item - row * r.n_quads, col = r.col0 + q * 4;
         const int64_t v = v0 + row;
         uint32_t u[4];
@@ -76,7 +82,7 @@ __global__ void __launch_bounds__(kResolveThreads) resolve_kernel(const Round r,
             typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
             const i32x4 a = __builtin_nontemporal_load(reinterpret_cast<const i32x4 *>(arg + v * r.d + col));
             f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
-            if ((a[0] & a[1] & a[2] & a[3]) >= 0) x = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(dO + v * ldo + col));
+            if (!PACK || (a[0] & a[1] & a[2] & a[3]) >= 0) x = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(dO + v * ldo + col));
 #pragma unroll
             for (int i = 0; i < 4; ++i) { e[i] = a[i]; g[i] = x[i]; }
         } else {
@@ -99,30 +105,41 @@ __global__ void __launch_bounds__(kResolveThreads) resolve_kernel(const Round r,
                 g[i] = binop == GNN_BIN_MUL ? g[i] * y : g[i] / y;
             }
         }
-        if ((u[0] & u[1] & u[2] & u[3]) != ~0u) has_winner[row] = 1;
+        if (PACK && (u[0] & u[1] & u[2] & u[3]) != ~0u) has_winner[row] = 1;
         out_u[q][row] = make_uint4(u[0], u[1], u[2], u[3]);
         out_g[q][row] = make_float4(g[0], g[1], g[2], g[3]);
     }
     __syncthreads();
-    const int64_t part = v0 / r.part_rows;
-    if (threadIdx.x < 64) {
-        const unsigned long long m = __ballot(has_winner[threadIdx.x] != 0);
-        if (m >> threadIdx.x & 1ull) rows_out[__popcll(m & ((1ull << threadIdx.x) - 1ull))] = uint8_t(threadIdx.x);
-        if (threadIdx.x == 0) {
-            has_winner[0] = uint32_t(__popcll(m));
-            first_out = m ? atomicAdd(&r.live[part], uint32_t(__popcll(m))) : 0u;
+    int n_out = n_rows;
+    int64_t out0 = v0;
+    if constexpr (PACK) {
+        const int64_t part = v0 / r.part_rows;
+        if (threadIdx.x < 64) {
+            const unsigned long long m = __ballot(has_winner[threadIdx.x] != 0);
+            if (m >> threadIdx.x & 1ull) rows_out[__popcll(m & ((1ull << threadIdx.x) - 1ull))] = uint8_t(threadIdx.x);
+            if (threadIdx.x == 0) {
+                n_packed = uint32_t(__popcll(m));
+                first_out = m ? atomicAdd(&r.live[part], uint32_t(__popcll(m))) : 0u;
+            }
         }
+        __syncthreads();
+        n_out = int(n_packed);
+        out0 = part * r.part_rows + first_out;
     }
-    __syncthreads();
-    const int n_out = int(has_winner[0]);
-    const int64_t out0 = part * r.part_rows + first_out;
-    for (int item = threadIdx.x; item < kResolveRows * r.n_quads; item += kResolveThreads) {
-        const int q = item / kResolveRows, k = item % kResolveRows;
+    for (int item = threadIdx.x; item < ROWS * r.n_quads; item += THREADS) {
+        const int q = item / ROWS, k = item % ROWS;
         if (k >= n_out) continue;
+        const int row = PACK ? rows_out[k] : k;
         const int64_t at = int64_t(q) * r.N + out0 + k;
-        reinterpret_cast<uint4 *>(r.u)[at] = out_u[q][rows_out[k]];
-        reinterpret_cast<float4 *>(r.val)[at] = out_g[q][rows_out[k]];
+        reinterpret_cast<uint4 *>(r.u)[at] = out_u[q][row];
+        reinterpret_cast<float4 *>(r.val)[at] = out_g[q][row];
     }
+}
+
+// one past the last of a part's rows that are there
+__device__ __forceinline__ int64_t part_end(const Round &r, int p) {
+    const int64_t begin = p * r.part_rows, rows = r.live ? int64_t(r.live[p]) : r.part_rows;
+    return begin + rows < r.N ? begin + rows : r.N;
 }
 
 __global__ void __launch_bounds__(kPartThreads) clear_live_kernel(const Round r) {  // one workgroup
@@ -134,7 +151,7 @@ __global__ void __launch_bounds__(kPartThreads) count_kernel(const Round r) {
     const int q = int(blockIdx.x) / r.n_parts, p = int(blockIdx.x) % r.n_parts;
     for (int b = threadIdx.x; b < r.n_ranges; b += kPartThreads) hist[b] = 0;
     __syncthreads();
-    const int64_t begin = p * r.part_rows, end = begin + r.live[p];
+    const int64_t begin = p * r.part_rows, end = part_end(r, p);
     const uint4 *u = reinterpret_cast<const uint4 *>(r.u) + int64_t(q) * r.N;
     for (int64_t v = begin + threadIdx.x; v < end; v += kPartThreads) {
         const uint4 x = u[v];
@@ -148,32 +165,34 @@ __global__ void __launch_bounds__(kPartThreads) count_kernel(const Round r) {
     if (blockIdx.x == 0 && threadIdx.x == 0) r.table[int64_t(r.n_quads) * r.n_ranges * r.n_parts] = 0;
 }
 
-__global__ void __launch_bounds__(kPartThreads) partition_kernel(const Round r) {
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) partition_kernel(const Round r) {
+    constexpr int kTile = THREADS * kPairsPerThread;
     __shared__ uint32_t hist[kMaxRanges], start[kMaxRanges], next[kMaxRanges];  // next: where the range's next pair goes
-    __shared__ uint32_t wave_sum[kPartThreads / 64];
+    __shared__ uint32_t wave_sum[THREADS / 64];
     __shared__ uint32_t pair_key[kTile];
     __shared__ float pair_val[kTile];
     const int q = int(blockIdx.x) / r.n_parts, p = int(blockIdx.x) % r.n_parts;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t begin = p * r.part_rows, end = begin + r.live[p];
-    for (int b = threadIdx.x; b < r.n_ranges; b += kPartThreads) next[b] = r.table[(int64_t(q) * r.n_ranges + b) * r.n_parts + p];
+    const int64_t begin = p * r.part_rows, end = part_end(r, p);
+    for (int b = threadIdx.x; b < r.n_ranges; b += THREADS) next[b] = r.table[(int64_t(q) * r.n_ranges + b) * r.n_parts + p];
     const uint4 *us = reinterpret_cast<const uint4 *>(r.u) + int64_t(q) * r.N;
     const float4 *vals = reinterpret_cast<const float4 *>(r.val) + int64_t(q) * r.N;
     const uint32_t low = (4u << r.range_log2) - 1;
-    for (int64_t tile = begin; tile < end; tile += kTileRows) {
-        uint4 u[kPerThread / 4];
-        float4 g[kPerThread / 4];
+    for (int64_t tile = begin; tile < end; tile += kTile / 4) {
+        uint4 u[kPairsPerThread / 4];
+        float4 g[kPairsPerThread / 4];
 #pragma unroll
-        for (int k = 0; k < kPerThread / 4; ++k) {
-            const int64_t v = tile + k * kPartThreads + threadIdx.x;
+        for (int k = 0; k < kPairsPerThread / 4; ++k) {
+            const int64_t v = tile + k * THREADS + threadIdx.x;
             u[k] = make_uint4(~0u, ~0u, ~0u, ~0u);
             if (v < end) { u[k] = us[v]; g[k] = vals[v]; }
         }
-        for (int b = threadIdx.x; b < r.n_ranges; b += kPartThreads) hist[b] = 0;
+        for (int b = threadIdx.x; b < r.n_ranges; b += THREADS) hist[b] = 0;
         __syncthreads();
-        uint32_t rank[kPerThread];
+        uint32_t rank[kPairsPerThread];
 #pragma unroll
-        for (int k = 0; k < kPerThread / 4; ++k) {
+        for (int k = 0; k < kPairsPerThread / 4; ++k) {
             const uint32_t w[4] = {u[k].x, u[k].y, u[k].z, u[k].w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) rank[k * 4 + i] = w[i] != ~0u ? atomicAdd(&hist[w[i] >> r.range_log2], 1u) : 0u;
@@ -191,7 +210,7 @@ __global__ void __launch_bounds__(kPartThreads) partition_kernel(const Round r) 
         __syncthreads();
         uint32_t before = incl - (h0 + h1), total = 0;
 #pragma unroll
-        for (int w = 0; w < kPartThreads / 64; ++w) {
+        for (int w = 0; w < THREADS / 64; ++w) {
             if (w < wave) before += wave_sum[w];
             total += wave_sum[w];
         }
@@ -199,7 +218,7 @@ __global__ void __launch_bounds__(kPartThreads) partition_kernel(const Round r) 
         if (b0 + 1 < r.n_ranges) { start[b0 + 1] = before + h0; hist[b0 + 1] = next[b0 + 1] - (before + h0); next[b0 + 1] += h1; }
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kPerThread / 4; ++k) {
+        for (int k = 0; k < kPairsPerThread / 4; ++k) {
             const uint32_t w[4] = {u[k].x, u[k].y, u[k].z, u[k].w};
             const float x[4] = {g[k].x, g[k].y, g[k].z, g[k].w};
 #pragma unroll
@@ -211,7 +230,7 @@ __global__ void __launch_bounds__(kPartThreads) partition_kernel(const Round r) 
             }
         }
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < total; i += kPartThreads) {
+        for (uint32_t i = threadIdx.x; i < total; i += THREADS) {
             const uint32_t key = pair_key[i];
             const uint32_t to = hist[key >> (r.range_log2 + 2)] + i;  // hist: write position minus position in the tile
             r.key[to] = uint16_t(key & low);
@@ -366,10 +385,11 @@ int gnn_scatter_winners(const int32_t *indices, const int64_t *eid, const int32_
     if (quads > kMaxQuads) quads = kMaxQuads;
     const int64_t n_rounds = (all_quads + quads - 1) / quads;
     quads = (all_quads + n_rounds - 1) / n_rounds;
-    const int64_t tiles = (N + kTileRows - 1) / kTileRows;
-    int64_t parts = 256 / quads;  // a workgroup of the partition fills a compute unit
+    const bool wide = (N + kWideRows - 1) / kWideRows * quads >= kWideTiles;
+    const int64_t tile_rows = wide ? kWideRows : kTileRows, tiles = (N + tile_rows - 1) / tile_rows;
+    int64_t parts = (wide ? 256 : 512) / quads;
     if (parts > tiles) parts = tiles;
-    r.part_rows = (tiles + parts - 1) / parts * kTileRows;
+    r.part_rows = (tiles + parts - 1) / parts * tile_rows;
     r.n_parts = int32_t((N + r.part_rows - 1) / r.part_rows);
     const int64_t pairs = N * quads * 4, entries = quads * r.n_ranges * r.n_parts + 1;
     // every range has a piece, and no more than this are added for the pairs beyond its first
@@ -380,22 +400,26 @@ int gnn_scatter_winners(const int32_t *indices, const int64_t *eid, const int32_
     gnn_dev_ptr<uint16_t> key;
     if (!u.alloc_on(pairs, stream) || !val.alloc_on(pairs, stream) || !key.alloc_on(pairs, stream) || !key_val.alloc_on(pairs, stream) ||
         !table.alloc_on(entries, stream) || !sums.alloc_on(gnn_scan_sums_elems(entries), stream) || !pieces.alloc_on(max_pieces, stream) ||
-        !count.alloc_on(1, stream) || !live.alloc_on(r.n_parts, stream))
+        !count.alloc_on(1, stream) || (wide && !live.alloc_on(r.n_parts, stream)))
         return GNN_ERR_ALLOC;
     r.u = u.p; r.val = val.p; r.key = key.p; r.key_val = key_val.p; r.table = table.p; r.pieces = pieces.p; r.n_pieces = count.p; r.live = live.p;
     for (int64_t q0 = 0; q0 < all_quads; q0 += quads) {
         r.col0 = int32_t(q0 * 4);
         r.n_quads = int32_t(all_quads - q0 < quads ? all_quads - q0 : quads);
-        const int64_t blocks = (N + kResolveRows - 1) / kResolveRows;
-        clear_live_kernel<<<1, kPartThreads, 0, stream>>>(r);
-        resolve_kernel<<<unsigned(blocks), kResolveThreads, 0, stream>>>(r, indices, eid, arg, dO, ldo, fE, lde, ewide ? 1 : 0, binop);
+        if (wide) {
+            clear_live_kernel<<<1, kPartThreads, 0, stream>>>(r);
+            resolve_kernel<true><<<unsigned((N + 63) / 64), 512, 0, stream>>>(r, indices, eid, arg, dO, ldo, fE, lde, ewide ? 1 : 0, binop);
+        } else {
+            resolve_kernel<false><<<unsigned((N + 31) / 32), 256, 0, stream>>>(r, indices, eid, arg, dO, ldo, fE, lde, ewide ? 1 : 0, binop);
+        }
         count_kernel<<<unsigned(r.n_quads * r.n_parts), kPartThreads, 0, stream>>>(r);
         if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
         const int rc = gnn_scan_exclusive_u32(r.table, int64_t(r.n_quads) * r.n_ranges * r.n_parts + 1, sums.p, stream);
         if (rc != GNN_OK) return rc;
         const int n_tasks = (r.n_ranges + 7) / 8 * 8 * r.n_quads;
         pieces_kernel<<<1, 1024, 0, stream>>>(r, n_tasks);
-        partition_kernel<<<unsigned(r.n_quads * r.n_parts), kPartThreads, 0, stream>>>(r);
+        if (wide) partition_kernel<kWideThreads><<<unsigned(r.n_quads * r.n_parts), kWideThreads, 0, stream>>>(r);
+        else partition_kernel<kPartThreads><<<unsigned(r.n_quads * r.n_parts), kPartThreads, 0, stream>>>(r);
         clear_split_kernel<<<unsigned(n_tasks), 256, 0, stream>>>(r, out, ldv);
         switch (r.range_log2) {
             case 13: add_kernel<13><<<unsigned(max_pieces), kAddThreads, 0, stream>>>(r, out, ldv); break;

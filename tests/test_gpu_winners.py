@@ -131,3 +131,25 @@ def test_a_captured_call_adds_with_atomics():
         graph.replay()
         torch.cuda.synchronize()
         _check(dv, indices, arg, do, range(d))
+
+
+@pytest.mark.parametrize("n", [600001, 598016])  # a row beyond whole tiles of 4096, and whole ones
+@pytest.mark.parametrize("empty", ["none", "some", "a whole part", "all but one"])
+def test_rows_without_winners_are_left_out(n, empty):
+    d, n_out, e = 64, 70000, 12 * 600001
+    indices, arg, do = _winners(n, d, n_out, e, 9)
+    gone = torch.zeros(n, dtype=torch.bool, device="cuda")
+    if empty == "some":
+        gone = torch.rand(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(2)) < 0.45
+        gone[:130] = True  # two whole workgroups' rows and the next one's first
+        gone[-1] = True
+    elif empty == "a whole part":
+        gone[40960:200000] = True
+    elif empty == "all but one":
+        gone[:] = True
+        gone[n - 1] = False
+    arg[gone] = -1
+    do[gone] = float("nan")  # nothing of such a row counts
+    dv = torch.full((n_out, d), float("nan"), device="cuda")
+    gnn.gnn_ap_bwd_vertex_arg(indices, arg, do, None, dv, n_out, n, d, gnn.GNN_BIN_COPY_LHS)
+    _check(dv, indices, arg, do, (0, 3, 31, d - 1))

@@ -103,6 +103,9 @@ struct AggArgs {
     const float *bias;    // fused layer epilogue: per-column bias added to the scaled row, or nullptr
     int32_t relu;         // fused layer epilogue: rectifier after the bias
     BinDesc bins[GNN_MAX_BINS + 1];
+    // (behind what the way to the first gather reads)
+    uint32_t *hub_done; // pieces of each hub row that are done, for the last one to add them (gnn_hub_done); nullptr: hub_finalize_kernel does
+    int32_t hub_chunk;  // edges of a piece
 };
 
 // ------------------------------------------------------------ element access
@@ -353,12 +356,11 @@ __device__ __forceinline__ void write_strip(const AggArgs &a, int64_t row, int64
 // factors) live at e + wdelta.
 struct RowOfGroup {
     int64_t e0, e1, row, row_len, wdelta;
-    float *partial_out;  // of a hub piece
 };
 template <bool COEF>
 __device__ __forceinline__ RowOfGroup find_row(const AggArgs &a, const BinDesc &bin, const int4 *row_info, const int64_t *p_indptr,
                                                int64_t wave_in_bin, int lane, bool coop, int wave_in_block) {
-    RowOfGroup r{0, 0, -1, 0, 0, nullptr};
+    RowOfGroup r{0, 0, -1, 0, 0};
     if (bin.kind & kKindHubPieces) {
         const int64_t piece = wave_in_bin;  // G == 64: one piece per wavefront (per workgroup when shared)
         if (piece < bin.n_items) {
@@ -369,7 +371,6 @@ __device__ __forceinline__ RowOfGroup find_row(const AggArgs &a, const BinDesc &
                 const int64_t *p = a.chunks + 3 * (bin.item_begin + piece);
                 r.row = p[0]; r.e0 = p[1]; r.e1 = p[2];
             }
-            r.partial_out = a.partial + (bin.item_begin + piece) * a.ldp;
         }
     } else {
         const int64_t item = wave_in_bin * (64 >> bin.log2_g) + (lane >> bin.log2_g);
@@ -418,6 +419,49 @@ __device__ __forceinline__ bool add_quarters(float *sums, float (&acc)[NPASS][VE
     return true;
 }
 
+// Leaves the sums of a hub piece; on the row's last piece to be done (true), acc and row_len are those of the row.
+template <bool COOP, int NPASS, int VEC>
+__device__ __forceinline__ bool end_piece(const AggArgs &a, int64_t piece, int64_t row, int slice, const int (&col)[NPASS], const bool (&col_ok)[NPASS],
+                                          float (&acc)[NPASS][VEC], int64_t &row_len) {
+    float *sums = a.partial + piece * a.ldp;
+    if (!COOP || !a.hub_done) {
+#pragma unroll
+        for (int p = 0; p < NPASS; ++p)
+            if (col_ok[p]) store_f32<VEC>(sums + col[p], acc[p]);
+        return false;
+    }
+#pragma unroll
+    for (int p = 0; p < NPASS; ++p)
+        if (col_ok[p])
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) gnn_store_for_device(sums + col[p] + i, acc[p][i]);
+    // (looked up again: kept from the beginning of the piece it would take registers from its gathers)
+    const int64_t begin = load_ip(a.indptr, a.ip64, row);
+    row_len = load_ip(a.indptr, a.ip64, row + 1) - begin;
+    const int number = int((a.chunks[3 * piece + 1] - begin) / a.hub_chunk), n = int((row_len + a.hub_chunk - 1) / a.hub_chunk);
+    if (!gnn_hub_done(a.hub_done + 8 * (piece - number) + slice, n)) return false;
+    constexpr int U = VEC >= 8 ? 2 : 4;  // pieces on their way at a time, added in order
+    const float *first = sums - number * a.ldp;
+#pragma unroll
+    for (int p = 0; p < NPASS; ++p) {
+        if (!col_ok[p]) continue;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[p][i] = 0.0f;
+        for (int q = 0; q < n; q += U) {
+            float v[U][VEC];
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) v[k][i] = gnn_load_for_device(first + (q + k < n ? q + k : n - 1) * a.ldp + col[p] + i);
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc[p][i] = q + k < n ? acc[p][i] + v[k][i] : acc[p][i];
+        }
+    }
+    return true;
+}
+
 // ---------------------------------------------------------------- main kernel
 // T: storage type of X and Y.  VEC: elements per lane per load.  NPASS: feature
 // passes (a lane owns NPASS strips of VEC columns, C*VEC apart).  COEF: edges
@@ -462,8 +506,9 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
     const int c = lane_in_g & (C - 1);  // feature strip of this lane
 
     const RowOfGroup r = find_row<COEF>(a, bin, row_info, p_indptr, wave_in_bin, lane, coop, wave_in_block);
-    const int64_t e0 = r.e0, e1 = r.e1, row = r.row, row_len = r.row_len, wdelta = r.wdelta;
-    float *partial_out = r.partial_out;
+    const int64_t e0 = r.e0, e1 = r.e1, wdelta = r.wdelta;
+    const int32_t row = int32_t(r.row);
+    int64_t row_len = r.row_len;
 
     float acc[NPASS][VEC];
 #pragma unroll
@@ -611,12 +656,7 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
         if (coop && !add_quarters<NPASS, VEC>(coop_sums, acc, wave_in_block, lane)) return;
     }
     if (row < 0 || s != 0) return;
-    if (bin.kind & kKindHubPieces) {
-#pragma unroll
-        for (int p = 0; p < NPASS; ++p)
-            if (col_ok[p]) store_f32<VEC>(partial_out + col[p], acc[p]);
-        return;
-    }
+    if ((bin.kind & kKindHubPieces) && !end_piece<COOP>(a, bin.item_begin + gnn_uniform(wave_in_bin), row, slice, col, col_ok, acc, row_len)) return;
     const int64_t self_row = (a.self_mode != kSelfNone && a.row_map) ? int64_t(a.row_map[row]) : row;
 #pragma unroll
     for (int p = 0; p < NPASS; ++p) {
@@ -679,6 +719,7 @@ __global__ void __launch_bounds__(kBlockThreads) gather_kernel(const AggArgs a) 
 
     const RowOfGroup r = find_row<COEF>(a, bin, row_info, p_indptr, wave_in_bin, lane, coop, wave_in_block);
     const int n_edges = int(r.e1 - r.e0);
+    const int32_t row = int32_t(r.row), edges_of_row = int32_t(r.row_len);
     const int32_t *idx = indices + r.e0;
     const float *w = COEF && a.w ? a.w + r.e0 + r.wdelta : nullptr;
     const float *scale = COEF && a.edge_scale ? a.edge_scale + r.e0 + r.wdelta : nullptr;
@@ -775,17 +816,19 @@ __global__ void __launch_bounds__(kBlockThreads) gather_kernel(const AggArgs a) 
     if constexpr (COOP) {
         if (coop && !add_quarters<1, VEC>(coop_sums, acc, wave_in_block, lane)) return;
     }
-    if (r.row < 0 || s != 0 || !col_ok) return;
-    if (r.partial_out) {
-        store_f32<VEC>(r.partial_out + col, acc[0]);
-        return;
+    if (row < 0 || s != 0 || !col_ok) return;
+    int64_t row_len = edges_of_row;
+    if (bin.kind & kKindHubPieces) {
+        const int cols[1] = {col};
+        const bool cols_ok[1] = {true};
+        if (!end_piece<COOP>(a, bin.item_begin + gnn_uniform(wave_in_bin), row, slice, cols, cols_ok, acc, row_len)) return;
     }
     float own[VEC];
     if (a.self_mode != kSelfNone) {
-        const int64_t self_row = a.row_map ? int64_t(a.row_map[r.row]) : r.row;
-        VecIO<T, VEC>::load(a.own_X ? static_cast<const T *>(a.own_X) + r.row * a.own_ld + col : X + self_row * ldx + lcol, own);
+        const int64_t self_row = a.row_map ? int64_t(a.row_map[row]) : row;
+        VecIO<T, VEC>::load(a.own_X ? static_cast<const T *>(a.own_X) + row * a.own_ld + col : X + self_row * ldx + lcol, own);
     }
-    write_strip<T, VEC>(a, r.row, r.row_len, col, ncols, own, acc[0]);
+    write_strip<T, VEC>(a, row, row_len, col, ncols, own, acc[0]);
 }
 
 struct RunArgs {
@@ -922,7 +965,8 @@ __global__ void __launch_bounds__(kBlockThreads) run_kernel(const RunArgs r) {
     else run(std::integral_constant<int, GNN_RUN_EDGES>());
 }
 
-// Adds the pieces of each hub row in their fixed order and writes the row.
+// Adds the pieces of each hub row in their fixed order and writes the row: of launches that fill the chip, beside which it is nothing (in their
+// kernels the last piece would take registers from the gathers, 4,096 vertices F=64 10.58 -> 10.66 us), and of calls with scratch of the caller's.
 template <typename T>
 __global__ void __launch_bounds__(256) hub_finalize_kernel(const int32_t *__restrict__ hub_rows, int64_t n_hub,
                                                            const int64_t *__restrict__ piece_offsets,
@@ -1598,6 +1642,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
 
     // hub scratch
     float *partial = nullptr;
+    uint32_t *hub_done = nullptr;  // calls that share a plan do not overlap, calls with scratch of their own might
     const bool has_hub = plan && plan->n_chunks > 0;
     if (has_hub) {
         const int64_t need = gnn_plan_workspace_bytes(plan, F);
@@ -1613,6 +1658,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             int rc = gnn_plan_room(plan, plan->scratch, need, stream);
             if (rc != GNN_OK) return rc;
             partial = static_cast<float *>(plan->scratch.p);
+            hub_done = plan->hub_done;
         }
         if (reinterpret_cast<uintptr_t>(partial) % 16) return GNN_ERR_INVALID_ARG;
     }
@@ -1958,14 +2004,12 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
             // The scratch rows are F wide for every slab; point at this slab's columns.
             a.partial = partial ? partial + f0 : nullptr;
             a.ldp = gnn_partial_ld(F);
+            a.hub_chunk = int32_t(plan->params.hub_chunk);
         }
         const bool blocked = bl.active && segs[gi].tail_slice < 0;
         if (blocked && !hot_tables) {
             const int rc = launch_pieces(f0, fw, log2_s, a.X);
             if (rc != GNN_OK) { finish_overlap(); return rc; }
-        } else if (!blocked && has_hub) {
-            plain_hub_columns = true;
-            if (f0 < plain_hub_col_begin) plain_hub_col_begin = f0;
         }
         hipStream_t rows_stream = (blocked && side) ? side : stream;  // the short rows of a blocked launch may overlap the pieces
         if (gi == 0 && run_bins) {
@@ -1983,6 +2027,11 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
         int32_t nb = 0;
         int64_t next_block = gnn_fill_bins(a.bins, &nb, a.first_block, plan, N, log2_c, blocked ? bl.first_bin : INT32_MAX, 1 << log2_s, run_bins);
         a.n_bins = nb;
+        a.hub_done = has_coop_bin(a) ? hub_done : nullptr;  // large launches, whose kernels have no room for it: see hub_finalize_kernel
+        if (!blocked && has_hub && !a.hub_done) {
+            plain_hub_columns = true;
+            if (f0 < plain_hub_col_begin) plain_hub_col_begin = f0;
+        }
         if (nb == 0 || next_block == 0) continue;
         next_block <<= log2_s;
         if (next_block > INT32_MAX) { finish_overlap(); return GNN_ERR_UNSUPPORTED; }

@@ -55,6 +55,8 @@ struct ApArgs {
                           // XCD (workgroups go to the 8 XCDs round-robin) keeps gathering the same lines
                           // of every row; 0: the slab is blockIdx.y
     ApBin bins[GNN_MAX_BINS + 1];
+    uint32_t *hub_done;  // see gnn_hub_done; nullptr: ap_hub_finalize_kernel adds the pieces
+    int32_t hub_chunk;
 };
 
 __device__ __forceinline__ int64_t load_ip(const void *indptr, int ip64, int64_t i) {
@@ -351,9 +353,48 @@ __global__ void __launch_bounds__(kBlockThreads) ap_fwd_kernel(const ApArgs a) {
     }
     if (g.row < 0 || g.s != 0 || !col_ok) return;
     if (g.is_piece) {
-        store_f<VEC>(a.pval + g.piece * a.ldp + col, acc);
-        if (RED != GNN_RED_SUM) store_i<VEC>(a.parg + g.piece * a.ldp + col, win);
-        return;
+        float *val = a.pval + g.piece * a.ldp + col;
+        int32_t *arg = a.parg + g.piece * a.ldp + col;
+        if (!a.hub_done) {
+            store_f<VEC>(val, acc);
+            if (RED != GNN_RED_SUM) store_i<VEC>(arg, win);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            gnn_store_for_device(val + i, acc[i]);
+            if (RED != GNN_RED_SUM) gnn_store_for_device(arg + i, win[i]);
+        }
+        const int64_t begin = load_ip(a.indptr, a.ip64, g.row), len = load_ip(a.indptr, a.ip64, g.row + 1) - begin;
+        const int number = int((a.chunks[3 * g.piece + 1] - begin) / a.hub_chunk), n = int((len + a.hub_chunk - 1) / a.hub_chunk);
+        if (!gnn_hub_done(a.hub_done + 8 * (g.piece - number) + slab, n)) return;
+        val -= number * a.ldp;
+        arg -= number * a.ldp;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            acc[i] = 0.0f;
+            win[i] = -1;
+        }
+        constexpr int P = RED == GNN_RED_SUM ? 4 : 2;  // pieces on their way at a time, in ascending edge order
+        for (int q = 0; q < n; q += P) {
+            float v[P][VEC];
+            int32_t w[P][VEC];
+#pragma unroll
+            for (int k = 0; k < P; ++k)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    const int64_t at = (q + k < n ? q + k : n - 1) * a.ldp + i;
+                    v[k][i] = gnn_load_for_device(val + at);
+                    w[k][i] = RED == GNN_RED_SUM ? 0 : gnn_load_for_device(arg + at);
+                }
+#pragma unroll
+            for (int k = 0; k < P; ++k)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    if constexpr (RED == GNN_RED_SUM) acc[i] = q + k < n ? acc[i] + v[k][i] : acc[i];
+                    else if (q + k < n && w[k][i] >= 0 && (win[i] < 0 || better<RED>(v[k][i], acc[i]))) { acc[i] = v[k][i]; win[i] = w[k][i]; }
+                }
+        }
     }
     if (RED != GNN_RED_SUM) {
 #pragma unroll
@@ -896,6 +937,8 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         if (rc != GNN_OK) return rc;
         a.pval = static_cast<float *>(plan->scratch.p);
         a.parg = reinterpret_cast<int32_t *>(a.pval + plan->n_chunks * a.ldp);
+        a.hub_done = plan->hub_done;
+        a.hub_chunk = int32_t(plan->params.hub_chunk);
     }
 
     AlignedRows aligned(c.stream);
@@ -970,6 +1013,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         const int64_t slab_cols = (int64_t(1) << log2_c) * vec;
         const int64_t n_slabs = (d + slab_cols - 1) / slab_cols;
         if (n_slabs > 65535) return GNN_ERR_UNSUPPORTED;
+        if (n_slabs > 8) a.hub_done = nullptr;  // a counter per column slice, eight at most
         a.slab_cols = int32_t(slab_cols);
         a.col0 = 0;
         a.col_end = int32_t(d);
@@ -990,7 +1034,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         else ap_run_kernel<GNN_RED_MIN><<<grid, kBlockThreads, 0, c.stream>>>(r);
         if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     }
-    if (has_hub) {
+    if (has_hub && !a.hub_done) {
         const int64_t hub_begin = plan->bin_offsets[plan->n_bins - 1];
         dim3 grid(static_cast<unsigned>(plan->n_hub_rows));
         const int32_t *hub_rows = plan->row_perm + hub_begin;

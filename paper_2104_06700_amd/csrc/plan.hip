@@ -66,6 +66,7 @@ struct PlanJob {
     int4 *row_info;            // or null
     int64_t *hub_offsets;
     int64_t *chunks;
+    uint32_t *hub_done;
 };
 struct PlanJobs {
     PlanJob job[2];
@@ -198,6 +199,8 @@ __global__ void __launch_bounds__(256) hub_fill_kernel(PlanJobs jobs, int64_t n_
         int64_t b = load_ip(job.indptr, jobs.ip64, v);
         const int64_t end = load_ip(job.indptr, jobs.ip64, v + 1);
         int64_t c = job.hub_offsets[i];
+        if (c < chunk_bound)
+            for (int s = 0; s < 8; ++s) job.hub_done[8 * c + s] = 0;
         for (; b < end && c < chunk_bound; b += jobs.hub_chunk, ++c) {
             job.chunks[3 * c + 0] = v;
             job.chunks[3 * c + 1] = b;
@@ -863,6 +866,7 @@ int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, 
     int64_t hub_bound = prm.hub_chunk > 0 ? (hub_degree > 0 && E / hub_degree < N ? E / hub_degree : N) : 0;
     const int64_t chunk_bound = hub_bound > 0 ? E / prm.hub_chunk + hub_bound : 0;
 
+    auto hub_done_of = [](int64_t *chunks, int64_t n) { return reinterpret_cast<uint32_t *>(chunks + 3 * n); };
     // [totals of both][block counts of both][scan scratch]
     const int64_t n_scan = n_counts > hub_bound ? n_counts : hub_bound;
     const int64_t totals_words = (int64_t(sizeof(RowTotals)) + 7) / 8;
@@ -890,7 +894,9 @@ int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, 
         }
         if (!gnn_dev_alloc(&p->col_counts, N, stream)) return GNN_ERR_ALLOC;
         if (hub_bound > 0 && (!gnn_dev_alloc(&p->hub_chunk_offsets, hub_bound + 1, stream) ||
-                              !gnn_dev_alloc(&p->chunks, 3 * chunk_bound, stream))) return GNN_ERR_ALLOC;
+                              !gnn_dev_alloc(&p->chunks, 7 * chunk_bound, stream))) return GNN_ERR_ALLOC;
+        // without thresholds a hub row may have no edges, so no piece, and is written by the kernels that finish hub rows
+        if (hub_bound > 0 && prm.n_thresholds > 0 && prm.hub_chunk <= INT32_MAX) p->hub_done = hub_done_of(p->chunks, chunk_bound);
         if (!(host.p[i] = gnn_host_block())) return GNN_ERR_ALLOC;
         PlanJob &j = jobs.job[i];
         j.indptr = indptrs[i];
@@ -903,6 +909,7 @@ int fill_plans(gnn_plan *const *plans, int n_plans, const void *const *indptrs, 
         j.row_info = p->row_info;
         j.hub_offsets = p->hub_chunk_offsets;
         j.chunks = p->chunks;
+        j.hub_done = hub_done_of(p->chunks, chunk_bound);
     }
     GNN_HIP_TRY(hipMemsetAsync(totals, 0, size_t(n_plans * totals_words) * 8, stream));  // not in a capture: the pool has refused those
     if (n_plans == 1) {

@@ -774,7 +774,41 @@ struct gnn_gemm_fold {
     float *colsum;
     int64_t colsum_planes;
     int64_t n_planes;  // out
+    // row_sum [N]: the sum of those column sums, or where there are none of n_rows rows of `rows`, beside the sum of the partial products
+    // where that has a kernel (summed, out; at most GNN_ADD_ROWS rows).
+    const float *rows;
+    int64_t n_rows;
+    float *row_sum;
+    bool summed;
 };
+constexpr int64_t GNN_ADD_ROWS = 512;
+
+#if defined(__HIPCC__)
+// out[j] = sum of rows b0 ... b1 - 1 of `rows` (F columns), for the 1 << log2_cols columns of column block `block`: all threads of a workgroup of 256.
+// In 64 bits, in a fixed order; the loads take longer than the additions.
+__device__ __forceinline__ void gnn_add_rows(const float *__restrict__ rows, int64_t b0, int64_t b1, int F, int log2_cols, int block, float *__restrict__ out) {
+    __shared__ double red[256];
+    const int cols = 1 << log2_cols, row_lanes = 256 >> log2_cols;
+    const int jl = threadIdx.x & (cols - 1), rl = threadIdx.x >> log2_cols;
+    const int j = block * cols + jl;
+    double s = 0.0;
+    if (j < F) {
+#pragma unroll 8
+        for (int64_t b = b0 + rl; b < b1; b += row_lanes) s += double(rows[b * F + j]);
+    }
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (rl == 0 && j < F) {
+        for (int k = 1; k < row_lanes; ++k) s += red[(k << log2_cols) + jl];
+        out[j] = float(s);
+    }
+}
+#endif
+static inline int gnn_add_rows_log2_cols(int64_t F) {
+    int l = 0;
+    while ((int64_t(1) << l) < F && l < 4) ++l;
+    return l;
+}
 
 // k-steps of a part of a split product at least
 constexpr int64_t GNN_SPLIT_MIN_K = 128;

@@ -728,10 +728,16 @@ __global__ void __launch_bounds__(256) few_k_kernel(const GemmArgs g) {
 // all planes took 0.23 ms for 256 planes of 256 x 256, 67 MB.  Workgroups of 16 wavefronts were slower still beside the
 // aggregation on the other stream, which never leaves a compute unit that many slots at once.)  In 64 bits: adding the planes was most
 // of the error of many short parts (24,490 rows, 256 x 256, 2-norm 1.5e-7 -> 0.8e-7), and the loads take longer than the additions.
+// The workgroups from n_blocks on add up `rows` (a bias gradient), which as a kernel of its own took 4.5 us behind this one.
 constexpr int kReduceWaves = 4;
 __global__ void __launch_bounds__(kReduceWaves * 64) gemm_reduce_kernel(const float *__restrict__ part, int n_split, float *__restrict__ C,
                                                                        int64_t ldc, int64_t M, int64_t N,
-                                                                       const float *__restrict__ bias, int relu) {
+                                                                       const float *__restrict__ bias, int relu, unsigned n_blocks,
+                                                                       const float *__restrict__ rows, int64_t n_rows, int log2_cols, float *__restrict__ row_sum) {
+    if (blockIdx.x >= n_blocks) {
+        gnn_add_rows(rows, 0, n_rows, int(N), log2_cols, int(blockIdx.x - n_blocks), row_sum);
+        return;
+    }
     constexpr int U = 8;
     __shared__ double sums[kReduceWaves][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -843,7 +849,7 @@ int gnn_matmul_impl(const float *A, int64_t lda, int trans_a, const float *B, in
                     int64_t M, int64_t N, int64_t K, const float *bias, int relu, void *workspace, int64_t workspace_bytes,
                     hipStream_t stream, const gnn_packed_target *packed, gnn_gemm_fold *fold) {
     if (M < 0 || N < 0 || K < 0) return GNN_ERR_INVALID_ARG;
-    if (fold) fold->n_planes = 0;
+    if (fold) { fold->n_planes = 0; fold->summed = false; }
     if (M == 0 || N == 0) return GNN_OK;
     const bool to_packed = packed && packed->active;
     if (!to_packed && (!C || ldc < N)) return GNN_ERR_INVALID_ARG;
@@ -924,10 +930,18 @@ int gnn_matmul_impl(const float *A, int64_t lda, int trans_a, const float *B, in
     if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     if (split > 1) {
         const int64_t blocks = (M * N + 63) / 64;
-        if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
-        gemm_reduce_kernel<<<static_cast<unsigned>(blocks), kReduceWaves * 64, 0, stream>>>(static_cast<const float *>(workspace), int(split), C, ldc,
-                                                                               M, N, bias, relu ? 1 : 0);
+        const float *rows = fold && fold->row_sum ? (fold->colsum ? fold->colsum : fold->rows) : nullptr;
+        const int64_t n_rows = fold && fold->colsum ? split : fold ? fold->n_rows : 0;
+        const bool add_rows = rows && n_rows <= GNN_ADD_ROWS;
+        const int log2_cols = gnn_add_rows_log2_cols(N);
+        const int64_t row_blocks = add_rows ? ((N - 1) >> log2_cols) + 1 : 0;
+        if (blocks + row_blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
+        static_assert(kReduceWaves * 64 == 256, "the workgroups of gnn_add_rows");
+        gemm_reduce_kernel<<<static_cast<unsigned>(blocks + row_blocks), kReduceWaves * 64, 0, stream>>>(
+            static_cast<const float *>(workspace), int(split), C, ldc, M, N, bias, relu ? 1 : 0, static_cast<unsigned>(blocks), rows, n_rows, log2_cols,
+            add_rows ? fold->row_sum : nullptr);
         if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
+        if (fold) fold->summed = add_rows;
     }
     return GNN_OK;
 }

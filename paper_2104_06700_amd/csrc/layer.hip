@@ -86,32 +86,16 @@ __global__ void __launch_bounds__(THREADS) mask_colsum_kernel(const float *__res
 // column walking 256 blocks: 0.06 ms per level.)
 __global__ void __launch_bounds__(256) colsum_reduce_kernel(const float *__restrict__ partial, int64_t n_blocks, int F,
                                                              float *__restrict__ out, int64_t chunk, int log2_cols) {
-    __shared__ double red[256];
-    const int cols = 1 << log2_cols, row_lanes = 256 >> log2_cols;
-    const int jl = threadIdx.x & (cols - 1), rl = threadIdx.x >> log2_cols;
     const int64_t b0 = int64_t(blockIdx.x) * chunk;
-    const int64_t b1 = b0 + chunk < n_blocks ? b0 + chunk : n_blocks;
-    const int j = int(blockIdx.y) * cols + jl;
-    double s = 0.0;  // the loads take longer than the additions
-    if (j < F) {
-#pragma unroll 8
-        for (int64_t b = b0 + rl; b < b1; b += row_lanes) s += double(partial[b * F + j]);
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if (rl == 0 && j < F) {
-        for (int k = 1; k < row_lanes; ++k) s += red[(k << log2_cols) + jl];
-        out[int64_t(blockIdx.x) * F + j] = float(s);
-    }
+    gnn_add_rows(partial, b0, b0 + chunk < n_blocks ? b0 + chunk : n_blocks, F, log2_cols, int(blockIdx.y), out + int64_t(blockIdx.x) * F);
 }
 
 // db = the sum of n rows of partial sums (row n of `partial` onwards is not touched), in two levels where there are many;
 // tmp: room for (n + 255) / 256 rows.
 void launch_colsum_reduce(const float *partial, int64_t n, int F, float *tmp, float *db, hipStream_t stream) {
-    int log2_cols = 0;
-    while ((1 << log2_cols) < F && log2_cols < 4) ++log2_cols;
+    const int log2_cols = gnn_add_rows_log2_cols(F);
     const unsigned col_blocks = static_cast<unsigned>((F + (1 << log2_cols) - 1) >> log2_cols);
-    if (n > 512) {
+    if (n > GNN_ADD_ROWS) {
         const int64_t n2 = (n + 255) / 256;
         colsum_reduce_kernel<<<dim3(static_cast<unsigned>(n2), col_blocks), 256, 0, stream>>>(partial, n, F, tmp, 256, log2_cols);
         partial = tmp;
@@ -276,15 +260,14 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
 
     // rectifier mask and bias gradient
     const int64_t n_blocks = (N + kRowsPerBlock - 1) / kRowsPerBlock;
+    const bool db_beside = db && !agg_first && n_blocks <= GNN_ADD_ROWS;  // added up beside the weight gradient's partial products
     if (!fold_gate && (need_g || db)) {
         int log2_cols = 0;
         while ((1 << log2_cols) < F_out && log2_cols < 8) ++log2_cols;
         const unsigned blocks = static_cast<unsigned>(n_blocks);
         if (n_blocks < 512) mask_colsum_kernel<1024><<<blocks, 1024, 0, stream>>>(H, dH, G, ldg, part, N, int(F_out), o.relu ? 1 : 0, log2_cols, pk_mask);
         else mask_colsum_kernel<256><<<blocks, 256, 0, stream>>>(H, dH, G, ldg, part, N, int(F_out), o.relu ? 1 : 0, log2_cols, pk_mask);
-        if (db) {
-            launch_colsum_reduce(part, n_blocks, int(F_out), part2, db, stream);
-        }
+        if (db && !db_beside) launch_colsum_reduce(part, n_blocks, int(F_out), part2, db, stream);
         if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     }
     const float *Gm = (need_g && !fold_gate) ? G : dH;
@@ -296,8 +279,9 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
         fold.b_gate = gate;
         fold.colsum = db ? part : nullptr;
         fold.colsum_planes = n_blocks;
+        fold.row_sum = db;
         int rcw = gnn_matmul_impl(saved, F_in, 1, dH, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, stream, nullptr, &fold);
-        if (rcw != GNN_OK || !db) return rcw;
+        if (rcw != GNN_OK || !db || fold.summed) return rcw;
         launch_colsum_reduce(part, fold.n_planes, int(F_out), part2, db, stream);
         return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
     };
@@ -331,7 +315,14 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
         rc = gnn_aggregate_bwd(indptr_t, indices_t, nullptr, Gm, T, N, F_out, GNN_SAGE_GCN, &a);
     }
     if (rc != GNN_OK) return rc;
-    rc = gnn_matmul_impl(X, F_in, 1, T, ldg, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, stream);
-    if (rc != GNN_OK || !dX) return rc;
+    gnn_gemm_fold fold_b{};
+    if (db_beside) { fold_b.rows = part; fold_b.n_rows = n_blocks; fold_b.row_sum = db; }
+    rc = gnn_matmul_impl(X, F_in, 1, T, ldg, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, stream, nullptr, &fold_b);
+    if (rc != GNN_OK) return rc;
+    if (db_beside && !fold_b.summed) {
+        launch_colsum_reduce(part, n_blocks, int(F_out), part2, db, stream);
+        if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
+    }
+    if (!dX) return GNN_OK;
     return gnn_matmul_impl(T, ldg, 0, W, F_out, 1, dX, F_in, N, F_in, F_out, nullptr, 0, nullptr, 0, stream);
 }

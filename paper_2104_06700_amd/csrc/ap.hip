@@ -57,7 +57,12 @@ struct ApArgs {
     ApBin bins[GNN_MAX_BINS + 1];
     uint32_t *hub_done;  // see gnn_hub_done; nullptr: ap_hub_finalize_kernel adds the pieces
     int32_t hub_chunk;
+    int32_t staged_wave;  // edge gradient by way of LDS: floats of a wavefront's rows
+    int32_t stream_edges;  // sums: f_E is beyond all caches
 };
+
+// Floats of LDS for `rows` rows of d floats that begin anywhere within 64 bytes.
+__host__ __device__ constexpr int staged_floats(int rows, int d) { return (rows * d + 15 + 3) / 4 * 4; }
 
 __device__ __forceinline__ int64_t load_ip(const void *indptr, int ip64, int64_t i) {
     return ip64 ? static_cast<const int64_t *>(indptr)[i]
@@ -65,6 +70,7 @@ __device__ __forceinline__ int64_t load_ip(const void *indptr, int ip64, int64_t
 }
 
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x4_lds __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 template <int VEC> __device__ __forceinline__ void load_f(const float *p, float (&v)[VEC]) {
     if constexpr (VEC == 4) {
@@ -214,8 +220,8 @@ __device__ __forceinline__ Group locate_group(const ApArgs &a, const Near &near,
 }
 
 // ------------------------------------------------------------------ forward
-// EWIDE: f_E has one column per feature column (else one scalar per edge).
-template <int BIN, int RED, int VEC, bool EWIDE>
+// EWIDE: f_E has one column per feature column (else one scalar per edge).  STREAM: rows of f_E are loaded non-temporally, see kStreamBytes.
+template <int BIN, int RED, int VEC, bool EWIDE, bool STREAM = false>
 __global__ void __launch_bounds__(kBlockThreads) ap_fwd_kernel(const ApArgs a) {
     const Near near(a);
     constexpr bool USE_V = BIN != GNN_BIN_COPY_RHS;
@@ -285,7 +291,8 @@ __global__ void __launch_bounds__(kBlockThreads) ap_fwd_kernel(const ApArgs a) {
                         if (u[k] < 0) load_f_nt<VEC>(xr, x[k]);
                         else load_f<VEC>(xr, x[k]);
                     }
-                    if (WIDE) load_f<VEC>(near.fE + r[k] * near.lde + col, y[k]);
+                    if (WIDE && STREAM) load_f_nt<VEC>(near.fE + r[k] * near.lde + col, y[k]);
+                    else if (WIDE) load_f<VEC>(near.fE + r[k] * near.lde + col, y[k]);
                 } else {
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) y[k][i] = 1.0f;
@@ -525,8 +532,13 @@ __global__ void __launch_bounds__(256) ap_hub_finalize_kernel(const int32_t *__r
 // edge operand is a scalar.  MASKED: only where arg_in[v, j] == e (max / min).
 // KEEP: when a lane's first strip of dO, the same for all edges, is loaded.
 enum KeepGo { kEveryStep, kBeforeFirst, kInFirst };
-template <int BIN, int VEC, bool EWIDE, bool MASKED, KeepGo KEEP, int U>  // U: edges in flight per slot
+// STAGED: rows of f_E that follow each other without gaps (no edge ids, stride d <= 4 C).  A group's rows of a step are put together in LDS, at their place
+// within a line of 64 bytes, and what fills such a line is stored non-temporally: from the lanes' strips such stores would reach memory as pieces of
+// lines (33 columns, add, 12.4 M edges 395 -> 532 us), and plain ones pass through the L2s, where they replace the rows that are gathered.
+template <int BIN, int VEC, bool EWIDE, bool MASKED, KeepGo KEEP, int U, bool STAGED = false>  // U: edges in flight per slot
 __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs a) {
+    static_assert(!STAGED || (VEC == 4 && EWIDE && !MASKED), "whole rows of f_E");
+    extern __shared__ __attribute__((aligned(16))) float staged_rows[];
     const Near near(a);
     constexpr bool NEED_X = BIN == GNN_BIN_MUL || BIN == GNN_BIN_DIV;
     constexpr bool NEED_Y = BIN == GNN_BIN_DIV;
@@ -580,6 +592,9 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
                 ok[k] = j < n_tile;
                 part[k] = 0.0f;
             }
+            // STAGED: this group's rows of the step, at the place within 64 bytes that they have in memory
+            const int shift = STAGED ? int((reinterpret_cast<uintptr_t>(a.out) / 4 + uint64_t(tile + j0) * a.d) & 15) : 0;
+            float *rows = STAGED ? staged_rows + (threadIdx.x >> 6) * a.staged_wave + g.gbase / G * staged_floats(SR * U, a.d) + shift : nullptr;
             for (int col0 = g.c * VEC; col0 < a.d; col0 += C * VEC) {
                 const int col = VEC > 1 && col0 > a.d - VEC ? a.d - VEC : col0;  // columns before col0 belong to the strip before
                 float go[VEC], x[U][VEC], y[U][VEC];
@@ -622,7 +637,10 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
                         if (MASKED && aw[i] != pos) t = 0.0f;
                         gy[i] = t;
                     }
-                    if (EWIDE) {
+                    if constexpr (STAGED) {
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) rows[(k * SR + g.s) * a.d + col + i] = gy[i];
+                    } else if (EWIDE) {
                         store_f<VEC>(a.out + r[k] * near.lde + col, gy);
                     } else {
 #pragma unroll
@@ -631,6 +649,26 @@ __global__ void __launch_bounds__(kBlockThreads) ap_bwd_edge_kernel(const ApArgs
                 }
             }
             if (KEEP == kInFirst) load_first = false;
+            if constexpr (STAGED) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // rows of the wavefront's own: its LDS accesses keep their order
+                const int n = (n_tile - j0 < SR * U ? n_tile - j0 : SR * U) * a.d;  // floats, from `shift` on
+                float *out = a.out + (tile + j0) * a.d - shift;
+                for (int b = 4 * g.lane_in_g; n > 0 && b < shift + n; b += 4 * G) {
+                    const f32x4_lds v = *reinterpret_cast<const f32x4_lds *>(rows - shift + b);
+                    const int line = b & ~15;
+                    if (line >= shift && line + 16 <= shift + n) {
+                        __builtin_nontemporal_store(f32x4_any(v), reinterpret_cast<f32x4_any *>(out + b));
+                        asm volatile("" ::: "memory");  // else the two stores become one, a plain one
+                    } else if (b >= shift && b + 4 <= shift + n) {
+                        *reinterpret_cast<f32x4_any *>(out + b) = v;
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (b + i >= shift && b + i < shift + n) out[b + i] = v[i];
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
             if (!EWIDE) {
 #pragma unroll
                 for (int k = 0; k < U; ++k) {
@@ -814,6 +852,28 @@ struct AlignedRows {
     }
 };
 
+// Edge gradients whose rows go through LDS and leave as whole lines of 64 bytes, non-temporally (see ap_bwd_edge_kernel): they are more than the caches
+// behind the L2s hold, where plain stores would be absorbed, and for products they push the gathered rows out of the L2s.  us, stored from
+// the lanes -> so, mul / add, one call after the other (behind a call that has read another such array, whose rows it finds in the caches instead of the
+// gathered ones, mul of 33 columns 651 -> 614, 48 812 -> 744, and the forward call behind it 502 -> 467): 245 K vertices, 12.4 M edges 13 columns 327 -> 220 / 180 -> 159, 19 422 -> 332 / 243 -> 223, 32 481 -> 307 / 317 -> 309, 33 689 ->
+// 435 / 395 -> 378, 64 957 -> 630 / 620 -> 604; 60 K, 3 M 24 columns (288 MB) 105 -> 72 / 58 -> 69, 33 (396) 154 -> 109 / 97 -> 98; 100 K, 2 M 33 columns (264 MB) 94 -> 73 /
+// 55 -> 67, 24 (192) 53 -> 50 / 35 -> 49; 500 K, 6 M 33 383 -> 268 / 225 -> 210.  Not: 25 K, 0.8 M 100 columns (320 MB, a gathered matrix of 10 MB) 143 -> 161 / 87 ->
+// 119, 128 152 -> 158 / 103 -> 112; 10 K, 1.5 M 256 357 -> 376 / 300 -> 311; 800 K, 4 M (rows of 5 edges) 64 columns 364 -> 379 / 244 -> 222, 128 685 -> 765, but
+// 33 306 -> 291; quotients, bound by their divisions (245 K, 6 M 33 449 -> 477).
+bool staged_pays(int binop, int64_t N, int64_t n_edges, int64_t d) {
+    if (d < 13 || d > 256 || n_edges > INT64_MAX / 2048) return false;
+    const int64_t bytes = n_edges * d * 4;
+    if (binop == GNN_BIN_MUL)
+        return bytes >= 264000000 && (d <= 64 || (d <= 100 && bytes >= 384000000) || N * d * 4 >= 28000000) && (d <= 48 || n_edges >= 8 * N);
+    return binop != GNN_BIN_DIV && bytes >= 384000000 && N >= 50000;
+}
+
+// Sums read an f_E of so many bytes non-temporally, so that it does not push the gathered rows out of the L2s (245 K vertices, 12.4 M edges, us, forward and
+// vertex gradient through the edge permutation, alone: 33 columns 460 -> 444 and 689 -> 636, 64 692 -> 626 and 716 -> 650; the three calls of a step
+// 1764 -> 1728).  Up to there part of it may still be found in the caches behind the L2s by the next call: 19 columns (940 MB) 279 -> 269 alone, a
+// step of differences 614 -> 617; 60 K, 3 M 33 columns (396 MB) 112 -> 113, 100 K, 2 M 19 (152 MB) 44 -> 60.
+constexpr int64_t kStreamBytes = 1200000000;
+
 struct Common {
     gnn_ap_opts o;
     int64_t ldv, lde, ldo;
@@ -840,6 +900,12 @@ int check_common(const gnn_ap_opts *opts_in, int64_t N, int64_t d, int binop, Co
 
 template <int BIN, int RED, int VEC>
 void launch_fwd_ew(bool ewide, dim3 grid, hipStream_t stream, const ApArgs &a) {
+    if constexpr (RED == GNN_RED_SUM && VEC == 4 && BIN != GNN_BIN_COPY_LHS) {
+        if (ewide && a.stream_edges) {
+            ap_fwd_kernel<BIN, RED, VEC, true, true><<<grid, kBlockThreads, 0, stream>>>(a);
+            return;
+        }
+    }
     if (BIN == GNN_BIN_COPY_LHS || ewide) ap_fwd_kernel<BIN, RED, VEC, true><<<grid, kBlockThreads, 0, stream>>>(a);
     else ap_fwd_kernel<BIN, RED, VEC, false><<<grid, kBlockThreads, 0, stream>>>(a);
 }
@@ -926,6 +992,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
     a.arg_out = arg_e;
     a.ld_arg = d;
     a.ldv = c.ldv;
+    a.stream_edges = plan && wide && plan->n_edges >= kStreamBytes / 4 / c.lde ? 1 : 0;
     a.lde = c.lde;
     a.ldo = c.ldo;
     a.d = int32_t(d);
@@ -1235,6 +1302,21 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
     // and 14.6; 20 K, 600 K 17.8 and 17.6, 19.5 and 19.0; 40 K, 2 M 30 and 29, 31.5 and 29.5), without a gathered operand before the first (add, 4 columns,
     // 130 K, 8 M every step 39, before 35).
     const int64_t n_edges = plan ? plan->n_edges : INT64_MAX;
+    if (c.ewide && !masked && !a.eid && c.lde == d && plan && staged_pays(binop, N, n_edges, d)) {
+        const int C = 1 << log2_c;
+        for (int G = C; G <= 64; G *= 2) {
+            const int floats = 64 / G * staged_floats(G / C * 4, int(d));
+            if (a.staged_wave < floats) a.staged_wave = floats;
+        }
+        const size_t lds = size_t(a.staged_wave) * kWavesPerBlock * 4;
+        switch (binop) {
+            case GNN_BIN_ADD: ap_bwd_edge_kernel<GNN_BIN_ADD, 4, true, false, kInFirst, 4, true><<<grid, kBlockThreads, lds, c.stream>>>(a); break;
+            case GNN_BIN_SUB: ap_bwd_edge_kernel<GNN_BIN_SUB, 4, true, false, kInFirst, 4, true><<<grid, kBlockThreads, lds, c.stream>>>(a); break;
+            case GNN_BIN_MUL: ap_bwd_edge_kernel<GNN_BIN_MUL, 4, true, false, kInFirst, 4, true><<<grid, kBlockThreads, lds, c.stream>>>(a); break;
+            default: ap_bwd_edge_kernel<GNN_BIN_COPY_RHS, 4, true, false, kInFirst, 4, true><<<grid, kBlockThreads, lds, c.stream>>>(a); break;
+        }
+        return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
+    }
     const bool large = n_edges >= (d > 4 ? 500000 : (d == 4 ? 10000000 : 4000000));
     KeepGo keep = d > 8 || (d > 4 && large) ? kInFirst : (large || !need_x ? kBeforeFirst : kEveryStep);
     // Scalars, and rows of max and min.  Up to two lanes own an edge of 1, 2 and 4 to 8 columns, so a row has slots for most of its edges and two in flight

@@ -271,7 +271,10 @@ typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
 constexpr int64_t kOperandEdges = 48000000;
 constexpr double kOperandSkew = 0.525;
 constexpr int kOperandRows = 2;                // rows of a wavefront at a time ...
-constexpr int kOperandBlocks = 8 * 32 * 4;     // ... and 16 wavefronts per compute unit: more rows in flight touch more lines than an L2 holds
+// ... and 16 wavefronts per compute unit where an eighth of a row has most of a wavefront's 128 loads, because more rows in flight touch more lines than
+// an L2 holds, else 32 (a vertex gradient of 4 columns, us, 16 / 24 / 32, mild skew: 600 edges a row, 133 K rows 1416 / 1481 / 1508, 100 K 1045 / 1013 /
+// 1047; 395, 200 K 1576 / 1475 / 1467; 316, 250 K 1683 / 1521 / 1476; 226, 350 K 1993 / 1709 / 1616; 208, 240 K 1295 / 1107 / 1007).
+constexpr int64_t kOperandLong = 500;
 
 // The same with the k-th eighth of every row on XCD k, rows in ascending order.  Where the operand is that of a transposed graph an
 // id is a place in the row of the edge's other end, so an eighth leads to an eighth of those rows, and a line of 32 scalars is met
@@ -315,7 +318,7 @@ __global__ void __launch_bounds__(256) edge_operand_rows_kernel(const float *__r
             x.id[r][0] = x.id[r][1] = 0;
             const int64_t *q = edge_ids + begin[r] + i;
             if (i + 1 < left[r]) {
-                const i64x2_any two = *reinterpret_cast<const i64x2_any *>(q);
+                const i64x2_any two = __builtin_nontemporal_load(reinterpret_cast<const i64x2_any *>(q));  // not in the place of scalars that wait: 1.44 -> 1.42 ms
                 x.id[r][0] = two.x;
                 x.id[r][1] = two.y;
             } else if (i < left[r]) {
@@ -375,7 +378,7 @@ int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const in
     // 1.70 -> 1.68, by seed 1.63 to 1.74; 0.66 250 K, 60 M 1.25 -> 1.42).
     if (edge_ids && plan->n_edges >= kOperandEdges && plan->n_edges >= 200 * plan->n_rows &&
         gnn_plan_top_share(plan, plan->n_rows / 20) < kOperandSkew)
-        edge_operand_rows_kernel<<<kOperandBlocks, 256, 0, stream>>>(fE, lde, edge_ids, indptr, ip64, plan->n_rows, plan->edge_operand);
+        edge_operand_rows_kernel<<<8 * 32 * (plan->n_edges >= kOperandLong * plan->n_rows ? 4 : 8), 256, 0, stream>>>(fE, lde, edge_ids, indptr, ip64, plan->n_rows, plan->edge_operand);
     else
         edge_operand_kernel<<<grid_for(plan->n_edges, 256, 1 << 16), 256, 0, stream>>>(fE, lde, edge_ids, plan->n_edges, plan->edge_operand);
     if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;

@@ -1273,14 +1273,23 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
         //                                   2.14 -> 1.76, 3.33 -> 2.51
         //   66,000, mild / strong skew      96 columns 1.03 -> 0.74 / 0.79 -> 0.69, 128 1.59 -> 0.99 / 1.17 -> 0.92
         //   250,000, 500 edges a vertex     33 columns 2.95 -> 2.14 / 2.22 -> 2.00, 64 3.34 -> 2.22 / 2.25 -> 2.05
+        //   250,000, 316 edges a vertex     33 columns 1.84 -> 1.36 / 1.32 -> 1.23, 64 2.02 -> 1.46 / 1.44 -> 1.29, 128 4.60 -> 3.36 / 3.42 -> 2.69
+        //   500,000, 158 edges a vertex     33 columns 2.41 -> 1.95 / 1.59 -> 1.50, 64 2.47 -> 2.14 / 1.66 -> 1.56, 96 3.69 -> 3.59 / 2.72 -> 2.38, 128 (244
+        //                                   MB) 5.04 -> 5.08 / 4.00 -> 3.24
         // Below the range the matrix is mostly in the L2s anyway: 66,000 vertices, 33 columns 0.50 -> 0.51 / 0.45 -> 0.47, 64 0.55 ->
         // 0.50 / 0.47 -> 0.47; 40,000, 64 columns 0.27 -> 0.29.  Rows of one line have too few steps (32 columns of 132,534
-        // 0.67 -> 0.73), and so have short rows (96 edges a vertex 1.07 -> 1.40).  The upper end and 400 edges are as far as it is taken,
-        // not where it ends: 250,000 vertices, 128 columns 7.57 -> 5.11 / 5.38 -> 4.19, 300 edges a vertex 0.80 -> 0.59.
+        // 0.67 -> 0.73), and so have short rows (250,000, 100 edges a vertex 64 columns 0.643 -> 0.645 / 0.39 -> 0.45; 900,000, 88 edges 2.70 -> 2.81).  From
+        // 150 to 400 edges a vertex it takes 48 M edges (400,000, 62 M, strong skew 33 columns 1.14 -> 1.13, 64 1.23 -> 1.18; 200,000, 34 M 0.45 -> 0.52 and 0.49 -> 0.53),
+        // or 24 M without strong skew (132,534, 26 M 48 columns 0.49 -> 0.44, 64 0.54 -> 0.45, strong skew 0.32 -> 0.38 and 0.33 -> 0.38; 100,000, 20 M 48
+        // columns, 18 MB, 0.31 -> 0.32; 200,000, 34 M 33 columns 0.71 -> 0.60): where few vertices have most of the edges their lines are in the L2s either way.
         // Rows in no order gain nothing and have their steps cut: 132,534 vertices, 64 columns 1.75 -> 1.91, 128 4.40 -> 4.82.
         const int64_t bytes = N * d * 4;
-        a.source_split = plan && gnn_long_rows(plan->n_edges, N) && !plan->rows_unordered && d > 32 && bytes >= (int64_t(18) << 20) &&
-                         bytes <= (int64_t(72) << 20) && blocks <= INT32_MAX / 8 ? 1 : 0;
+        auto split_pays = [&] {
+            if (!gnn_long_rows(plan->n_edges, N) || plan->rows_unordered || d <= 32 || bytes < (int64_t(18) << 20) || bytes > (int64_t(200) << 20)) return false;
+            if (plan->n_edges >= 400 * N || plan->n_edges >= 48000000) return true;
+            return plan->n_edges >= 24000000 && bytes >= (int64_t(24) << 20) && gnn_plan_top_share(plan, N / 20) < kStrongSkew;
+        };
+        a.source_split = plan && blocks <= INT32_MAX / 8 && split_pays() ? 1 : 0;
         if (a.source_split) grid.x *= 8;
         auto launch = [&](auto lc, auto s) {
             constexpr int LC = decltype(lc)::value, S = decltype(s)::value;

@@ -269,7 +269,6 @@ __global__ void __launch_bounds__(256) edge_operand_kernel(const float *__restri
 typedef int64_t i64x2_any __attribute__((ext_vector_type(2), aligned(8)));
 typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
 constexpr int64_t kOperandEdges = 48000000;
-constexpr double kOperandSkew = 0.525;
 constexpr int kOperandRows = 2;                // rows of a wavefront at a time ...
 // ... and 16 wavefronts per compute unit where an eighth of a row has most of a wavefront's 128 loads, because more rows in flight touch more lines than
 // an L2 holds, else 32 (a vertex gradient of 4 columns, us, 16 / 24 / 32, mild skew: 600 edges a row, 133 K rows 1416 / 1481 / 1508, 100 K 1045 / 1013 /
@@ -377,7 +376,7 @@ int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const in
     // 79 M 2.02 -> 1.98; 0.53 100 K, 60 M 1.10 -> 1.14; 0.58 133 K, 79 M 1.57 -> 1.60; 0.60 133 K, 60 M 1.14 -> 1.21; 0.61 133 K, 50 M 0.91 -> 1.01; 0.65 250 K, 79 M
     // 1.70 -> 1.68, by seed 1.63 to 1.74; 0.66 250 K, 60 M 1.25 -> 1.42).
     if (edge_ids && plan->n_edges >= kOperandEdges && plan->n_edges >= 200 * plan->n_rows &&
-        gnn_plan_top_share(plan, plan->n_rows / 20) < kOperandSkew)
+        gnn_plan_top_share(plan, plan->n_rows / 20) < kStrongSkew)
         edge_operand_rows_kernel<<<8 * 32 * (plan->n_edges >= kOperandLong * plan->n_rows ? 4 : 8), 256, 0, stream>>>(fE, lde, edge_ids, indptr, ip64, plan->n_rows, plan->edge_operand);
     else
         edge_operand_kernel<<<grid_for(plan->n_edges, 256, 1 << 16), 256, 0, stream>>>(fE, lde, edge_ids, plan->n_edges, plan->edge_operand);

@@ -458,6 +458,29 @@ def test_edge_dots_of_long_rows_are_split_over_the_xcds(d, hubs, ordered, wide):
         assert bool(((out[part].double() - terms.sum(1)).abs() <= 1e-5 * terms.abs().sum(1)).all())
 
 
+@pytest.mark.parametrize("n,d,most", [(131100, 48, 380), (140000, 65, 320)])
+def test_edge_dots_of_rows_of_150_edges_and_more(n, d, most):
+    """From 150 edges per vertex, 24 M edges and a gathered matrix of 24 MB: rows of every length up to `most`, and one cut into pieces."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d)
+    lens = torch.randint(0, most, (n,), generator=gen, device=DEV)
+    lens[100] = 60_000
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), lens)
+    src = (dst * n + torch.randint(0, n, (dst.numel(),), generator=gen, device=DEV)).sort().values % n
+    dst, src = dst.int(), src.int()
+    e = dst.numel()
+    assert 150 * n <= e < 400 * n and 20000000 <= e < 48000000
+    g = gnn.build_device_graph(dst, src, n)
+    v, do = (torch.empty(n, d, device=DEV).normal_(generator=gen) for _ in range(2))
+    fe = torch.rand(e, device=DEV, generator=gen)
+    out = torch.full((e,), float("nan"), device=DEV)
+    gnn.gnn_ap_bwd_edge(g.indptr, g.indices, None, v, fe, do, out, n, d, gnn.GNN_BIN_MUL, plan=g.plan_fwd)
+    for at in range(0, e, 1 << 23):
+        part = slice(at, at + (1 << 23))
+        terms = v.double()[src[part].long()] * do.double()[dst[part].long()]
+        assert bool(((out[part].double() - terms.sum(1)).abs() <= 1e-5 * terms.abs().sum(1)).all())
+
+
 @pytest.mark.parametrize("n,d", [(250007, 13), (120001, 31), (60013, 61), (31300, 96)])
 @pytest.mark.parametrize("binop", [gnn.GNN_BIN_MUL, gnn.GNN_BIN_DIV])
 def test_full_width_operands_on_rows_off_line_boundaries(n, d, binop):

@@ -422,6 +422,9 @@ struct ApRunArgs {
     int64_t ldv, ldo, ld_arg;
     int32_t d, ip64;
     gnn_run_bins bins;
+    const float *tail;  // columns from tail_col on, in rows of ld_tail
+    int64_t ld_tail;
+    int32_t tail_col;
 };
 
 // max / min of the neighbours' vectors for rows of at most GNN_RUN_EDGES edges, all columns, up to 64 rows per wavefront; see run_kernel
@@ -458,6 +461,9 @@ __global__ void __launch_bounds__(kBlockThreads) ap_run_kernel(const ApRunArgs a
             int col = (strip0 + c) * 4;
             const bool col_ok = col < a.d;
             if (col > a.d - 4) col = a.d - 4;
+            const bool in_tail = col >= a.tail_col;
+            const float *table = in_tail ? a.tail + (col - a.tail_col) : a.fV + col;
+            const int64_t ld = in_tail ? a.ld_tail : a.ldv;
             auto fetch = [&](int src) {
                 const int len = __shfl(my_len, src);
                 const int64_t first = shfl_i64(my_e0, src);
@@ -476,7 +482,7 @@ __global__ void __launch_bounds__(kBlockThreads) ap_run_kernel(const ApRunArgs a
                     const int u = __shfl(cur, gbase + k) & 0x7FFFFFFF;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) x[k][i] = 0.0f;
-                    if (k < len && col_ok) load_f<4>(a.fV + int64_t(u) * a.ldv + col, x[k]);
+                    if (k < len && col_ok) load_f<4>(table + int64_t(u) * ld, x[k]);
                 }
                 float best[4] = {0.0f, 0.0f, 0.0f, 0.0f};
                 int32_t win[4] = {-1, -1, -1, -1};
@@ -1026,21 +1032,37 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
     // of symmetric ones: 393 K 295 -> 293, 305 -> 307, 653 -> 637, 633 -> 608; 517 K 480 -> 470, 490 -> 487, 1127 -> 1073, 999 -> 953).
     const uint32_t run_bins = binop == GNN_BIN_COPY_LHS && reduce != GNN_RED_SUM && d > 32 ? gnn_run_bins_of(plan, INT32_MAX, GNN_MORE_RUN_ROWS) : 0u;
     bool sliced = false;
+    const float *tail = nullptr;
+    int64_t ld_tail = 0, tail_col = INT32_MAX;
     const bool slice_ok = !use_e || (!wide && !c.o.edge_ids && reduce == GNN_RED_SUM) || c.o.max_slices > 1;
     if (use_v && !wide && vec == 4 && plan && plan->n_edges > 0 && slice_ok) {
         const gnn_layout L = gnn_choose_layout(plan, N, d, 4, c.ldv, reinterpret_cast<uintptr_t>(fV) % 128 == 0, c.o.flags,
                                          c.o.max_slices);
         if (L.padded_copy && d * 4 > 128) {  // rows of one line gain nothing from a copy in their own order
-            rc = gnn_plan_padded(plan, N * L.ld_pad * 4, c.stream);
+            // A last line of few columns in a table of its own, of 16, 32 or 64 bytes a row: as one slab among others it takes as many lines as they do, in
+            // a launch over all XCDs the lanes go to more edges, and up to eight rows share a line (us, 2.45 M vertices, 124 M edges 68 columns 5037 -> 4840, 77 5139 ->
+            // 5053, 100 6793 -> 6538, 112 6712 -> 6496; 500 K, 40 M 68 1688 -> 1552, 80 1661 -> 1600, 100 2263 -> 2119; 250 K, 20 M 100 944 -> 850; 1.5 M, 28 M 100 1708 ->
+            // 1631; rows of 48 bytes, which lie across lines, 1.2 M, 85 M 75 columns 4398 -> 4593).
+            const int64_t rest = d % 32;
+            const bool apart = !use_e && L.slices_wanted && c.o.max_slices == 0 && d > 64 && d <= 256 * 32 && rest >= 4 && rest <= 16 && (rest <= 8 || rest > 12);
+            const int64_t main_cols = apart ? d - rest : d, ld_main = apart ? (main_cols / 32 | 1) * 32 : L.ld_pad;
+            if (apart) ld_tail = rest <= 4 ? 4 : rest <= 8 ? 8 : 16;
+            rc = gnn_plan_padded(plan, N * (ld_main + ld_tail) * 4, c.stream);
             if (rc != GNN_OK) return rc;
-            rc = gnn_pad_rows_f32(fV, c.ldv, static_cast<float *>(plan->padded.p), L.ld_pad, N, d, plan->col_counts, c.stream);
+            float *copy = static_cast<float *>(plan->padded.p);
+            rc = gnn_pad_rows_f32(fV, c.ldv, copy, ld_main, N, main_cols, plan->col_counts, c.stream);
+            if (rc == GNN_OK && apart) {
+                tail = copy + N * ld_main;
+                tail_col = main_cols;
+                rc = gnn_pad_rows_f32(fV + main_cols, c.ldv, copy + N * ld_main, ld_tail, N, rest, plan->col_counts, c.stream);
+            }
             if (rc != GNN_OK) return rc;
-            a.fV = static_cast<const float *>(plan->padded.p);
-            a.ldv = L.ld_pad;
+            a.fV = copy;
+            a.ldv = ld_main;
         }
         const int64_t line = 32;  // floats per 128-byte line
         const bool lines_ok = a.ldv % line == 0 && reinterpret_cast<uintptr_t>(a.fV) % 128 == 0;
-        const int64_t lines = (d + line - 1) / line;
+        const int64_t cols = tail ? tail_col : d, lines = (cols + line - 1) / line;
         int64_t g16 = 1;
         while (g16 < 16 && (a.ldv / line) % (g16 * 2) == 0) g16 *= 2;
         const int64_t unit_lines = g16 >= 8 ? g16 / 4 : 1;  // even strides: wider slices (see aggregate.hip)
@@ -1062,7 +1084,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
                 while (ls > 0 && ((int64_t(1) << ls) > units - u0 || (int64_t(1) << ls) > s_max)) --ls;
                 a.col0 = int32_t(u0 * a.slab_cols);
                 const int64_t end = int64_t(a.col0) + (int64_t(a.slab_cols) << ls);
-                a.col_end = int32_t(end < d ? end : d);
+                a.col_end = int32_t(end < cols ? end : cols);
                 a.log2_slices = ls;
                 const int64_t blocks = make_bins(a, plan, N, log2_c, 1 << ls, run_bins) << ls;
                 if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
@@ -1071,6 +1093,21 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
                     if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
                 }
                 u0 += int64_t(1) << ls;
+            }
+            if (tail) {
+                ApArgs t = a;
+                t.fV = tail - tail_col;
+                t.ldv = ld_tail;
+                t.slab_cols = int32_t(ld_tail);
+                t.col0 = int32_t(tail_col);
+                t.col_end = int32_t(d);
+                t.log2_slices = 0;
+                const int64_t blocks = make_bins(t, plan, N, gnn_ilog2_ceil(ld_tail / vec), 1, run_bins);
+                if (blocks > INT32_MAX) return GNN_ERR_UNSUPPORTED;
+                if (blocks > 0) {
+                    launch_fwd(binop, reduce, vec, c.ewide, dim3(static_cast<unsigned>(blocks)), c.stream, t);
+                    if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
+                }
             }
         }
     }
@@ -1094,7 +1131,7 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         }
     }
     if (run_bins) {
-        ApRunArgs r{a.indptr, a.indices, a.row_perm, a.row_info, a.fV, a.out, a.arg_out, a.ldv, a.ldo, a.ld_arg, a.d, a.ip64, {}};
+        ApRunArgs r{a.indptr, a.indices, a.row_perm, a.row_info, a.fV, a.out, a.arg_out, a.ldv, a.ldo, a.ld_arg, a.d, a.ip64, {}, tail, ld_tail, int32_t(tail_col)};
         gnn_fill_run_bins(r.bins, plan, run_bins, (d + 3) / 4);
         const dim3 grid(static_cast<unsigned>(r.bins.n_blocks));
         if (reduce == GNN_RED_MAX) ap_run_kernel<GNN_RED_MAX><<<grid, kBlockThreads, 0, c.stream>>>(r);

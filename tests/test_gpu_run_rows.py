@@ -169,3 +169,36 @@ def test_sums_of_one_line_on_as_many_short_rows_as_they_need(larger_graph):
 def test_max_and_min_of_as_many_short_rows_as_a_launch_of_their_own_takes(larger_graph, d, shift, reduce):
     """The same through ap_run_kernel, which takes 390,000 of them and more."""
     test_short_rows_of_max_and_min(larger_graph, d, shift, reduce)
+
+
+@pytest.mark.parametrize("d", [68, 70, 72, 77, 80, 100, 132])  # a last line of 4, 6, 8, 13, 16 and 4 columns
+@pytest.mark.parametrize("reducer", ["max", "min"])
+def test_pooling_with_a_last_line_of_few_columns(d, reducer):
+    """max / min from a copy whose last, short line is a table of its own: short rows, rows of every class and a hub row; the lowest position among equals."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(d)
+    n = 600_000
+    lens = torch.randint(0, 5, (n,), generator=gen, device=DEV)
+    lens[:300] = torch.arange(300, device=DEV)
+    lens[1000] = 9000
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), lens)
+    src = (dst * n + torch.randint(0, n, (dst.numel(),), generator=gen, device=DEV)).sort().values % n
+    g = gnn.build_device_graph(dst.int(), src.int(), n)
+    v = torch.randint(-4, 5, (n, d), generator=gen, device=DEV).float()  # ties
+    v[7::50] = float("-inf") if reducer == "max" else float("inf")
+    out = torch.full((n, d), float("nan"), device=DEV)
+    arg = torch.full((n, d), -7, dtype=torch.int32, device=DEV)
+    red = gnn.GNN_RED_MAX if reducer == "max" else gnn.GNN_RED_MIN
+    gnn.gnn_ap_fwd(g.indptr, g.indices, v, None, out, arg, n, d, gnn.GNN_BIN_COPY_LHS, red, plan=g.plan_fwd, flags=gnn.GNN_FLAG_FORCE_PADDED_COPY)
+    torch.cuda.synchronize()
+    for c0 in range(0, d, 20):
+        cols = slice(c0, min(c0 + 20, d))
+        msgs = v[src][:, cols]
+        to = dst[:, None].expand_as(msgs)
+        want = torch.zeros_like(out[:, cols]).scatter_reduce(0, to, msgs, "amax" if reducer == "max" else "amin", include_self=False)
+        pos = torch.arange(dst.numel(), device=DEV)[:, None].expand_as(msgs)
+        first = torch.where(msgs == want[dst], pos, dst.numel())
+        where = torch.full(want.shape, dst.numel(), device=DEV).scatter_reduce(0, to, first, "amin")
+        where = torch.where(lens[:, None] > 0, where, -1)
+        assert torch.equal(out[:, cols], want)
+        assert torch.equal(arg[:, cols].long(), where)

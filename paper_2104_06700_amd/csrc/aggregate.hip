@@ -598,7 +598,8 @@ __global__ void __launch_bounds__(kBlockThreads) aggregate_kernel(const AggArgs 
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 // Bit 31 of an index marks a rarely gathered ("cold") source (plan-owned index copy):
-                // its row is fetched with a non-temporal load, so that it does not displace the
+                // its row is fetched with a non-temporal load (which the present compiler merges with the other
+                // one into a plain load; kept apart they measure the same), so that it does not displace the
                 // warm rows of the L2.
                 const int32_t src = u[k] & 0x7FFFFFFF;
                 const bool cold = a.cold_on && (u[k] < 0 || src >= a.warm_rank);

@@ -1020,7 +1020,7 @@ struct PieceArgs {
     int64_t slice_stride;    // elements between two slice tables
     float *partial;          // [slices][n_pieces][floats per line]
     int32_t log2_slices;
-    // Hot tables: the last block's pieces gather the caller's rows (of `cols` columns of the launch from X_cold on) by vertex.
+    // Hot tables: the last block's pieces gather the caller's rows (of `cols` columns of the launch from X_cold on) by vertex.  idx16 is there, and tells them.
     const int32_t *cold_vertices;  // of the edges from cold_begin on
     uint32_t cold_begin;
     const void *X_cold;

@@ -392,7 +392,7 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             int32_t *blk_indices = nullptr;
             uint16_t *blk_idx16 = nullptr;
             gnn_piece_list list{};
-            const bool narrow = m.hot <= 65536 && m.block <= 65536;
+            const bool narrow = m.hot <= GNN_NARROW_BLOCK && m.block <= GNN_NARROW_BLOCK;
             auto cleanup_tmp = [&]() {
                 gnn_dev_free_on(h_of, stream); gnn_dev_free_on(buf_k[0], stream); gnn_dev_free_on(buf_k[1], stream); gnn_dev_free_on(buf_v[0], stream); gnn_dev_free_on(buf_v[1], stream);
                 gnn_dev_free_on(table, stream); gnn_dev_free_on(sums, stream); gnn_dev_free_on(cell_start, stream); gnn_dev_free_on(cell_count, stream);
@@ -503,7 +503,7 @@ int build_hot(gnn_plan *plan, const void *indptr, const int32_t *indices, hipStr
     int rc = gnn_plan_rank_indices(plan, indptr, indices, false, stream, &rl);
     if (rc != GNN_OK) return rc;
     gnn_blocked_layout bl{};
-    if ((rc = gnn_plan_blocked(plan, indptr, stream, &bl)) != GNN_OK || !bl.active || plan->blk_hot_vertices) return rc;
+    if ((rc = gnn_plan_blocked(plan, indptr, stream, &bl)) != GNN_OK || !bl.active || !bl.idx16 || plan->blk_hot_vertices) return rc;
     uint32_t begin = 0;
     GNN_HIP_TRY(hipMemcpyAsync(&begin, plan->blk_cell_off + int64_t(plan->blk_n_blocks - 1) * plan->blk_n_hot, 4, hipMemcpyDeviceToHost, stream));
     GNN_HIP_TRY(hipStreamSynchronize(stream));

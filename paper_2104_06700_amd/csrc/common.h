@@ -368,6 +368,9 @@ static inline int64_t gnn_edges_from_bin(const gnn_plan *plan, int first_bin) {
 // Graphs of fewer edges per vertex than a copy of the whole matrix pays for.  Blocked by themselves they have hot tables (gnn_plan_hot); the
 // sources of the last block are never copied, so nothing of it goes into tiles.
 static inline bool gnn_few_edges(const gnn_plan *plan) { return plan->blocking.min_degree == 0 && plan->n_edges < 16 * plan->n_rows; }
+// Blocks whose edges have 16-bit indices, all but the last: by them the kernel over hot tables tells the last block's pieces, which gather by vertex.
+constexpr int64_t GNN_NARROW_BLOCK = 65536;
+static inline bool gnn_narrow_blocks(const gnn_plan *plan) { return plan->blocking.hot_lines <= GNN_NARROW_BLOCK && plan->blocking.block_lines <= GNN_NARROW_BLOCK; }
 static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz, int64_t row_bytes, bool weights) {
     if (!plan || plan->n_edges <= 0 || plan->n_edges >= int64_t(INT32_MAX)) return false;
     const bool automatic = plan->blocking.min_degree == 0;
@@ -523,7 +526,7 @@ static inline gnn_layout gnn_choose_layout(const gnn_plan *plan, int64_t N, int6
     // which every call would make anew.
     constexpr int kStay = GNN_FLAG_NO_PADDED_COPY | GNN_FLAG_FORCE_PADDED_COPY | GNN_FLAG_NO_COLUMN_SLICES | GNN_FLAG_NO_SLICE_TABLES |
                           GNN_FLAG_NO_RANK_ORDER | GNN_FLAG_FORCE_COLD_HINTS;
-    L.hot_tables = plan && blocks_expected && gnn_few_edges(plan) && !L.padded_copy && allow_tail && max_slices == 0 && !(flags & kStay) &&
+    L.hot_tables = plan && blocks_expected && gnn_few_edges(plan) && gnn_narrow_blocks(plan) && !L.padded_copy && allow_tail && max_slices == 0 && !(flags & kStay) &&
                    row_bytes > 64 && row_bytes % 16 == 0 && lines <= 256 && !(scaled_source && weights) && gnn_hot_tables_pay(plan, row_bytes, esz, lines_ok);
     if (L.hot_tables) L.line_lanes = 8;
     return L;

@@ -1143,7 +1143,9 @@ int build_dense(const gnn_plan *plan, const DenseRule &rule, const std::vector<T
     B.dense_extra = extra;
     B.dense_cut = cut;
     B.dense_chunks = groups[0].chunks;
-    B.dense_sources = plan->n_rows - plan->bucket_vertices[0];  // they are in order of their gathers
+    // they are in order of their gathers; the last chunk may begin within a table that ends with the tiles
+    const TileDesc &last = tiles[size_t(group_depth[0] - 1)];
+    B.dense_sources = std::min(plan->n_rows - plan->bucket_vertices[0], int64_t(last.begin) + last.size);
     *staged_edges -= int64_t(host_edges);
     if (*staged_edges < 1) *staged_edges = 1;
     *depth_out = depth;

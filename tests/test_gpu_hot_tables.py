@@ -85,6 +85,50 @@ def test_infinities_and_nan_stay_where_they_are_gathered():
     assert bool((torch.isinf(y) == inf).all()) and bool((y[inf] == y0[inf]).all()) and bool(inf.any())
 
 
+def _exact_sum(g, x):
+    """Sums over the rows in 64 bits, and those of the magnitudes."""
+    dst = torch.repeat_interleave(torch.arange(g.n, device="cuda"), (g.indptr[1:] - g.indptr[:-1]).long())
+    want, size = (torch.zeros(x.shape, dtype=torch.float64, device="cuda") for _ in range(2))
+    for c in range(0, x.shape[1], 32):
+        terms = x[:, c:c + 32].double()[g.indices.long()]
+        want[:, c:c + 32].index_add_(0, dst, terms)
+        size[:, c:c + 32].index_add_(0, dst, terms.abs())
+    return want, size
+
+
+@pytest.mark.parametrize("blocking,tables", [(dict(hot_lines=65537), False), (dict(block_lines=100000), False), (dict(hot_lines=40001, block_lines=9999), True)])
+def test_blocks_of_any_size(blocking, tables):
+    """Blocks beyond 16-bit indices leave the rows in place; sizes that are no whole tiles or chunks have tables."""
+    el = synth.rmat_directed(1200000, 18000000, STRONG, 19, device="cuda")
+    g = gnn.build_device_graph(el.dst, el.src, el.n)
+    g.plan_fwd.set_blocking(**blocking)
+    x = torch.empty(g.n, 100, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(1))
+    g.plan_fwd.prepare(g.indices, gnn.GNN_SUM, False, 100)
+    y = _call(g, x, gnn.GNN_SUM, False)
+    assert (g.plan_fwd.blocked_sizes()[2] > 0) == tables
+    want, size = _exact_sum(g, x)
+    assert bool(((y.double() - want).abs() <= 1e-5 * size).all())
+
+
+def test_bit_matrix_over_tables_that_end_within_a_chunk():
+    """All sources of the tables are in the bit matrix, and their number is no multiple of the 128 sources that its kernel takes at a time."""
+    n, hot, gen = 300000, 20000, torch.Generator(device="cuda").manual_seed(2)
+    rows = torch.randperm(n, device="cuda", generator=gen)[:520]
+    chosen = torch.rand(520, hot, device="cuda", generator=gen) < 0.4
+    long_dst, long_src = chosen.nonzero(as_tuple=True)
+    short = (torch.randint(0, n, (500000,), device="cuda", generator=gen), torch.randint(hot, n, (500000,), device="cuda", generator=gen))
+    dst, src = torch.cat([rows[long_dst], short[0]]), torch.cat([long_src, short[1]])
+    dst, order = dst.sort()
+    g = gnn.build_device_graph(dst.int(), src[order].int(), n)
+    g.plan_fwd.set_blocking(hot_lines=hot)
+    x = torch.empty(n, 100, device="cuda").normal_(generator=gen)
+    g.plan_fwd.prepare(g.indices, gnn.GNN_SUM, False, 100)
+    assert g.plan_fwd.bit_rows() >= 256 and g.plan_fwd.blocked_sizes()[3] == 2
+    y = _call(g, x, gnn.GNN_SUM, False)
+    want, size = _exact_sum(g, x)
+    assert bool(((y.double() - want).abs() <= 1e-5 * size).all())
+
+
 @pytest.mark.parametrize("prepared", [False, True])
 def test_capture(prepared):
     el = synth.rmat_directed(1200000, 18000000, STRONG, 18, device="cuda")

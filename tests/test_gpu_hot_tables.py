@@ -1,5 +1,5 @@
-"""Graphs of few edges per vertex whose long rows gather the most-gathered sources from tables and everything else in place, against the call
-that stays in place."""
+"""Graphs of few edges per vertex whose long rows gather the most-gathered sources from tables and everything else in place, against sums in
+64 bits; the call that stays in place is held to the same bound."""
 import pytest
 import torch
 
@@ -11,21 +11,33 @@ pytestmark = pytest.mark.gpu
 F32, BF16 = torch.float32, torch.bfloat16
 STRONG = (0.57, 0.19, 0.19, 0.05)
 IN_PLACE = gnn.GNN_FLAG_NO_SOURCE_BLOCKS
-_graphs = {}
+_edges = {}
 
 
 def _graph(n, e, weights=False, indptr64=False):
-    key = (n, e, weights, indptr64)
-    if key not in _graphs:
-        _graphs.clear()
-        el = synth.rmat_directed(n, e, STRONG, 17, device="cuda")
-        w = torch.rand(e, device="cuda") + 0.5 if weights else None
-        g = gnn.build_device_graph(el.dst, el.src, n, edge_w=w, indptr64=indptr64)
-        if weights:
-            g.plan_fwd.bind_edge_weights(g.edge_w)
-            g.plan_bwd.bind_edge_weights(g.edge_w_t)
-        _graphs[key] = g
-    return _graphs[key]
+    """With plans of its own, so that what one form has built does not serve another."""
+    if (n, e) not in _edges:
+        _edges.clear()
+        _edges[n, e] = synth.rmat_directed(n, e, STRONG, 17, device="cuda")
+    el = _edges[n, e]
+    w = torch.rand(e, device="cuda", generator=_gen(5)) + 0.5 if weights else None
+    g = gnn.build_device_graph(el.dst, el.src, n, edge_w=w, indptr64=indptr64)
+    if weights:
+        g.plan_fwd.bind_edge_weights(g.edge_w)
+        g.plan_bwd.bind_edge_weights(g.edge_w_t)
+    return g
+
+
+def _gen(seed):
+    return torch.Generator(device="cuda").manual_seed(seed)
+
+
+def _normal(seed, n, f, dtype=F32):
+    return torch.empty(n, f, device="cuda").normal_(generator=_gen(seed)).to(dtype)
+
+
+def _prepare(g, f, op, backward=False, dtype=F32):
+    (g.plan_bwd if backward else g.plan_fwd).prepare(g.indices_t if backward else g.indices, op, backward, f, dtype)
 
 
 def _call(g, x, op, backward, flags=0, out=None, stream=None):
@@ -38,9 +50,39 @@ def _call(g, x, op, backward, flags=0, out=None, stream=None):
     return y
 
 
-def _bound(g, x, op, backward):
-    # fp32 sums in two orders; a bf16 result is rounded once more on either side, to 2^-9 of the value
-    return (2.0 ** -8 if x.dtype == BF16 else 1e-5) * _call(g, x.abs(), op, backward, IN_PLACE).double()
+def _exact(g, x, op, backward):
+    """The result in 64 bits, and the sum of its terms' magnitudes."""
+    indptr, indices, w = (g.indptr_t, g.indices_t, g.edge_w_t) if backward else (g.indptr, g.indices, g.edge_w)
+    n = g.n
+    count = (indptr[1:] - indptr[:-1]).long()
+    dst, src = torch.repeat_interleave(torch.arange(n, device="cuda"), count), indices.long()
+    of_row, of_source = count.double(), torch.bincount(src, minlength=n).double()  # edges that end, and that begin
+    ones = torch.ones(n, dtype=torch.float64, device="cuda")
+    into, out = {gnn.GNN_SUM: (ones, ones), gnn.GNN_GCN_SYM: (of_source.clamp(min=1).rsqrt(), of_row.clamp(min=1).rsqrt()),
+                 gnn.GNN_MEAN: (1 / of_source.clamp(min=1), ones) if backward else (ones, 1 / of_row.clamp(min=1)),
+                 gnn.GNN_SAGE_GCN: (1 / (of_source + 1), ones) if backward else (ones, 1 / (of_row + 1))}[op]
+    want, size = (torch.zeros(x.shape, dtype=torch.float64, device="cuda") for _ in range(2))
+    for c in range(0, x.shape[1], 32):
+        own = x[:, c:c + 32].double() * into[:, None]
+        terms = own[src]
+        if w is not None:
+            terms *= w.double()[:, None]
+        for total, at, mine in ((want, terms, own), (size, terms.abs(), own.abs())):
+            cols = total[:, c:c + 32]
+            if op == gnn.GNN_SAGE_GCN:
+                cols += mine
+            cols.index_add_(0, dst, at)
+            cols *= out[:, None]
+    return want, size
+
+
+def _assert_within(y, exact):
+    # fp32 sums of terms that are rounded themselves; a bf16 result is rounded once more, by up to 2^-8 of the value (8 significant bits)
+    want, size = exact
+    bound = 1e-5 * size
+    if y.dtype == BF16:
+        bound += 2.0 ** -8 * (want.abs() + bound)
+    assert bool(((y.double() - want).abs() <= bound).all())
 
 
 # whole lines, a last line of one strip, rows off line boundaries, rows of one line and a bit, two launches of slices; every factor, the own row
@@ -50,50 +92,45 @@ FORMS = [(F32, 256, gnn.GNN_MEAN, False), (F32, 256, gnn.GNN_MEAN, True), (F32, 
 
 
 @pytest.mark.parametrize("dtype,f,op,backward", FORMS)
-def test_agrees_with_the_call_in_place(dtype, f, op, backward):
+def test_agrees_with_sums_in_64_bits(dtype, f, op, backward):
     g = _graph(1800000, 26000000)
-    x = torch.randn(g.n, f, device="cuda").to(dtype)
-    y = _call(g, x, op, backward)
-    plan = g.plan_bwd if backward else g.plan_fwd
-    assert plan.blocked_sizes()[2] > 0  # it went over hot tables
-    y0 = _call(g, x, op, backward, IN_PLACE)
-    assert bool(((y.double() - y0.double()).abs() <= _bound(g, x, op, backward)).all())
+    x = _normal(f, g.n, f, dtype)
+    _prepare(g, f, op, backward, dtype)
+    y, y0 = _call(g, x, op, backward), _call(g, x, op, backward, IN_PLACE)
+    exact = _exact(g, x, op, backward)
+    _assert_within(y, exact)
+    _assert_within(y0, exact)
+    assert not torch.equal(y, y0), "sums in another order: some bit differs where the tables were used"
 
 
 @pytest.mark.parametrize("dtype,f", [(F32, 100), (BF16, 136)])
 @pytest.mark.parametrize("weights", [False, True])
 def test_strides_weights_and_wide_row_pointers(dtype, f, weights):
     g = _graph(1500000, 21000000, weights=weights, indptr64=True)
-    wide = torch.randn(g.n, f + 8, device="cuda").to(dtype)
-    x = wide[:, 4:4 + f]  # 16 and 8 bytes behind a line, rows of another stride
-    y = _call(g, x, gnn.GNN_SUM, False)
-    y0 = _call(g, x, gnn.GNN_SUM, False, IN_PLACE)
-    assert g.plan_fwd.blocked_sizes()[2] > 0
-    assert bool(((y.double() - y0.double()).abs() <= _bound(g, x.contiguous(), gnn.GNN_SUM, False)).all())
+    x = _normal(f, g.n, f + 8, dtype)[:, 4:4 + f]  # 16 and 8 bytes behind a line, rows of another stride
+    _prepare(g, f, gnn.GNN_SUM, dtype=dtype)
+    y, y0 = _call(g, x, gnn.GNN_SUM, False), _call(g, x, gnn.GNN_SUM, False, IN_PLACE)
+    exact = _exact(g, x, gnn.GNN_SUM, False)
+    _assert_within(y, exact)
+    _assert_within(y0, exact)
+    assert not torch.equal(y, y0)
 
 
 def test_infinities_and_nan_stay_where_they_are_gathered():
     g = _graph(1800000, 26000000)
-    x = torch.randn(g.n, 100, device="cuda")
+    x = _normal(6, g.n, 100)
     counts = torch.bincount(g.indices, minlength=g.n)
     order = torch.argsort(counts, descending=True)
     for place, value in ((3, float("inf")), (40000, float("nan")), (200000, -float("inf")), (700000, float("nan"))):
         x[order[place], place % 100] = value
+    _prepare(g, 100, gnn.GNN_SUM)
     y, y0 = _call(g, x, gnn.GNN_SUM, False), _call(g, x, gnn.GNN_SUM, False, IN_PLACE)
-    assert bool((torch.isnan(y) == torch.isnan(y0)).all())
-    inf = torch.isinf(y0)
-    assert bool((torch.isinf(y) == inf).all()) and bool((y[inf] == y0[inf]).all()) and bool(inf.any())
-
-
-def _exact_sum(g, x):
-    """Sums over the rows in 64 bits, and those of the magnitudes."""
-    dst = torch.repeat_interleave(torch.arange(g.n, device="cuda"), (g.indptr[1:] - g.indptr[:-1]).long())
-    want, size = (torch.zeros(x.shape, dtype=torch.float64, device="cuda") for _ in range(2))
-    for c in range(0, x.shape[1], 32):
-        terms = x[:, c:c + 32].double()[g.indices.long()]
-        want[:, c:c + 32].index_add_(0, dst, terms)
-        size[:, c:c + 32].index_add_(0, dst, terms.abs())
-    return want, size
+    want, _ = _exact(g, x, gnn.GNN_SUM, False)
+    assert bool(torch.isinf(want).any()) and not torch.equal(torch.nan_to_num(y), torch.nan_to_num(y0))
+    for got in (y, y0):
+        assert bool((torch.isnan(got) == torch.isnan(want)).all())
+        inf = torch.isinf(want)
+        assert bool((torch.isinf(got) == inf).all()) and bool((got[inf].double() == want[inf]).all())
 
 
 @pytest.mark.parametrize("blocking,tables", [(dict(hot_lines=65537), False), (dict(block_lines=100000), False), (dict(hot_lines=40001, block_lines=9999), True)])
@@ -102,17 +139,16 @@ def test_blocks_of_any_size(blocking, tables):
     el = synth.rmat_directed(1200000, 18000000, STRONG, 19, device="cuda")
     g = gnn.build_device_graph(el.dst, el.src, el.n)
     g.plan_fwd.set_blocking(**blocking)
-    x = torch.empty(g.n, 100, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(1))
-    g.plan_fwd.prepare(g.indices, gnn.GNN_SUM, False, 100)
+    x = _normal(1, g.n, 100)
+    _prepare(g, 100, gnn.GNN_SUM)
     y = _call(g, x, gnn.GNN_SUM, False)
     assert (g.plan_fwd.blocked_sizes()[2] > 0) == tables
-    want, size = _exact_sum(g, x)
-    assert bool(((y.double() - want).abs() <= 1e-5 * size).all())
+    _assert_within(y, _exact(g, x, gnn.GNN_SUM, False))
 
 
 def test_bit_matrix_over_tables_that_end_within_a_chunk():
     """All sources of the tables are in the bit matrix, and their number is no multiple of the 128 sources that its kernel takes at a time."""
-    n, hot, gen = 300000, 20000, torch.Generator(device="cuda").manual_seed(2)
+    n, hot, gen = 300000, 20000, _gen(2)
     rows = torch.randperm(n, device="cuda", generator=gen)[:520]
     chosen = torch.rand(520, hot, device="cuda", generator=gen) < 0.4
     long_dst, long_src = chosen.nonzero(as_tuple=True)
@@ -122,20 +158,18 @@ def test_bit_matrix_over_tables_that_end_within_a_chunk():
     g = gnn.build_device_graph(dst.int(), src[order].int(), n)
     g.plan_fwd.set_blocking(hot_lines=hot)
     x = torch.empty(n, 100, device="cuda").normal_(generator=gen)
-    g.plan_fwd.prepare(g.indices, gnn.GNN_SUM, False, 100)
+    _prepare(g, 100, gnn.GNN_SUM)
     assert g.plan_fwd.bit_rows() >= 256 and g.plan_fwd.blocked_sizes()[3] == 2
-    y = _call(g, x, gnn.GNN_SUM, False)
-    want, size = _exact_sum(g, x)
-    assert bool(((y.double() - want).abs() <= 1e-5 * size).all())
+    _assert_within(_call(g, x, gnn.GNN_SUM, False), _exact(g, x, gnn.GNN_SUM, False))
 
 
 @pytest.mark.parametrize("prepared", [False, True])
 def test_capture(prepared):
     el = synth.rmat_directed(1200000, 18000000, STRONG, 18, device="cuda")
     g = gnn.build_device_graph(el.dst, el.src, el.n)
-    x, other = torch.randn(g.n, 128, device="cuda"), torch.randn(g.n, 128, device="cuda")
+    x, other = _normal(7, g.n, 128), _normal(8, g.n, 128)
     if prepared:
-        g.plan_fwd.prepare(g.indices, gnn.GNN_MEAN, False, 128)
+        _prepare(g, 128, gnn.GNN_MEAN)
     else:
         g.plan_fwd.reserve(128)
     y = torch.empty_like(x)

@@ -482,7 +482,11 @@ GNN_API int gnn_plan_reserve(gnn_plan *plan, int64_t F);
  * gather count, a short last line kept in a dense table of its own); and the index copy that goes
  * with it (4 bytes per edge + 12 per vertex: source ids mapped to their rank, edge lists in the
  * plan's row order), or -- where no copy of the matrix is made but column slices are used on a
- * large power-law graph -- the index copy with the cold sources flagged.  That is reserved for calls
+ * large power-law graph -- the index copy with the cold sources flagged.  On large power-law graphs of
+ * fewer than 16 edges per vertex it also makes tables of the most-gathered sources, for the long rows
+ * (about 20 bytes per edge of those rows, plus the tables), where there is room for them: these are
+ * not made by a call on its first use, so a plan that is never prepared gathers every row in place.
+ * That is reserved for calls
  * without edge weights, with the weights bound to the plan at this moment and with any others (which
  * may choose another layout each), on dense matrices (row stride F) at 128-byte boundaries, without
  * flags.  `indices` is the index

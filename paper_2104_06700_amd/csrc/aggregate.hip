@@ -1761,7 +1761,7 @@ int run_aggregate(const void *indptr, const int32_t *indices, const float *w, co
     const float *scale_blk = nullptr, *w_blk = nullptr;
     const int lanes = layout.line_lanes;  // of a line of the tables
     gnn_hot_layout hot{};
-    const bool hot_tables = layout.hot_tables && gnn_plan_hot_ready(plan, indptr, indices, src_mode, weights, F, esz, stream, &hot);
+    const bool hot_tables = layout.hot_tables && gnn_plan_hot_ready(plan, indptr, indices, src_mode, weights, F, esz, stream, /*build=*/false, &hot);
     if (hot_tables) bl = hot.blocks;
     const int64_t table_stride = hot_tables ? hot.rows * line_elems : layout.table_stride;  // of those that the pieces gather from
     const int64_t n_table_lines = hot_tables ? layout.lines : layout.main_lines;

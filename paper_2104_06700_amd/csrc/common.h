@@ -156,8 +156,7 @@ struct gnn_plan {
     int32_t *blk_hot_vertices = nullptr;
     int32_t *blk_cold_vertices = nullptr;
     int64_t blk_cold_begin = 0;
-    uint32_t hot_refused = 0;         // calls since there was no room for them, with that one; 0: there was
-    uint64_t hot_ready[2][5][5] = {}; // what calls in a capture can use: [type][factor 0 ... 3 or weights], bit `lines`
+    uint64_t hot_ready[2][5][5] = {}; // what calls can use: [type][factor 0 ... 3 or weights], bit `lines`
     gnn_grown blk_partial;            // fp32 partial sums of one launch: [slices][blk_n_pieces][floats per line]
     gnn_tiles tiles[7];               // for lines of 128, 64 and 32 bytes of fp32, then of bf16; [GNN_TILES_PLAIN]: see gnn_plan_tiles
     gnn_grown tile_partial;           // their partial lines: [groups][slices][hot rows][floats per line]
@@ -573,10 +572,12 @@ int gnn_plan_edge_operand(gnn_plan *plan, const float *fE, int64_t lde, const in
 int gnn_plan_edge_scale(gnn_plan *plan, const int32_t *indices, int mode, hipStream_t stream, const float **out);
 
 // gnn_plan_hot and everything else that a call over hot tables takes, but for the tables' contents: their memory (plan->padded), partial sums, tiles,
-// coefficients in their order.  mode: the factor of the gathered rows.  False: not to be had (nothing is built in a capture, and there may be
-// no room); the call stays in place, and asks again as often as gnn_plan_tiles does for the bit matrix.
+// coefficients in their order.  mode: the factor of the gathered rows.  Only gnn_plan_prepare builds it (build), because it takes 4 to 25 calls to pay:
+// 1.0 M vertices, 15 M edges F=100 a first call of 2.9 ms with and 0.8 without, then 0.73 and 0.81 each; 1.8 M, 26 M F=100 4.7 and 1.6, 1.25 and
+// 1.60; 27.8 M, 404 M bf16 F=128 52 and 15, 12.6 and 15.1; a step on a subgraph that is new makes one call with each plan.  False: it is not there, and the
+// call stays in place.
 bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indices, int mode, gnn_weight_kind weights, int64_t F, int esz, hipStream_t stream,
-                        gnn_hot_layout *out);
+                        bool build, gnn_hot_layout *out);
 
 // ---- producer-side layout ----
 // Where a kernel that PRODUCES a matrix (the dense product of a layer, the masked output gradient)

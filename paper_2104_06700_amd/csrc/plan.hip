@@ -681,18 +681,13 @@ int gnn_plan_padded(gnn_plan *plan, int64_t bytes, hipStream_t stream) {
 }
 
 bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indices, int mode, gnn_weight_kind weights, int64_t F, int esz, hipStream_t stream,
-                        gnn_hot_layout *out) {
+                        bool build, gnn_hot_layout *out) {
     const int line_elems = 128 / esz;
     const int64_t lines = (F + line_elems - 1) / line_elems;
     uint64_t &word = plan->hot_ready[esz == 2][weights == GNN_WEIGHTS_NONE ? mode : 4][lines >> 6];
     const uint64_t bit = uint64_t(1) << (lines & 63);
     if (weights == GNN_WEIGHTS_FREE || (mode && weights != GNN_WEIGHTS_NONE) || (plan->blk_decided && plan->blk_n_pieces <= 0)) return false;
-    if (gnn_capturing(stream)) {
-        if (!(word & bit)) return false;
-    } else if (plan->hot_refused & (plan->hot_refused - 1)) {
-        ++plan->hot_refused;
-        return false;
-    }
+    if (!(word & bit) && (!build || gnn_capturing(stream))) return false;
     int slices = 1;
     while (slices < 8 && slices * 2 <= lines) slices *= 2;
     const gnn_tiles *tl = nullptr;
@@ -713,10 +708,8 @@ bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indic
     }
     if (rc != GNN_OK) {
         (void)hipGetLastError();
-        ++plan->hot_refused;
         return false;
     }
-    plan->hot_refused = 0;
     word |= bit;
     return true;
 }
@@ -729,7 +722,7 @@ static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int6
                                                 blocks, weights != GNN_WEIGHTS_NONE);
     if (!layout.padded_copy) {
         gnn_hot_layout unused_hot{};
-        if (layout.hot_tables) (void)gnn_plan_hot_ready(plan, plan->indptr_seen, indices, mode, weights, F, esz, stream, &unused_hot);  // else in place
+        if (layout.hot_tables) (void)gnn_plan_hot_ready(plan, plan->indptr_seen, indices, mode, weights, F, esz, stream, /*build=*/true, &unused_hot);  // else in place
         if (!layout.slices_wanted) return GNN_OK;
         const int32_t *unused_idx = nullptr;  // the flagged index copy of the cold hints, where they pay
         return gnn_plan_cold_indices(plan, indices, false, stream, &unused_idx);

@@ -133,6 +133,18 @@ def test_infinities_and_nan_stay_where_they_are_gathered():
         assert bool((torch.isinf(got) == inf).all()) and bool((got[inf].double() == want[inf]).all())
 
 
+def test_a_plan_that_is_not_prepared_builds_none():
+    """A new subgraph's plans serve a call or two each: the first calls cost no more than those that stay in place."""
+    g = _graph(1800000, 26000000)
+    x = _normal(9, g.n, 100)
+    y, y0 = _call(g, x, gnn.GNN_SUM, False), _call(g, x, gnn.GNN_SUM, False, IN_PLACE)
+    assert torch.equal(y, y0) and g.plan_fwd.blocked_sizes()[2] == 0
+    _prepare(g, 100, gnn.GNN_SUM)
+    assert not torch.equal(_call(g, x, gnn.GNN_SUM, False), y0) and g.plan_fwd.blocked_sizes()[2] > 0
+    # prepared for sums without factors: symmetric factors have none of their own there
+    assert torch.equal(_call(g, x, gnn.GNN_GCN_SYM, False), _call(g, x, gnn.GNN_GCN_SYM, False, IN_PLACE))
+
+
 @pytest.mark.parametrize("blocking,tables", [(dict(hot_lines=65537), False), (dict(block_lines=100000), False), (dict(hot_lines=40001, block_lines=9999), True)])
 def test_blocks_of_any_size(blocking, tables):
     """Blocks beyond 16-bit indices leave the rows in place; sizes that are no whole tiles or chunks have tables."""

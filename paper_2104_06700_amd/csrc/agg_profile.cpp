@@ -113,6 +113,8 @@ int main(int argc, char **argv) {
         o.flags = flags;
         o.max_slices = max_slices;
         o.plan = pf;
+        GCHECK(gnn_plan_prepare(pf, (const int32_t *)indices, op, 0, F, o.dtype, nullptr));
+        GCHECK(gnn_plan_prepare(pb, (const int32_t *)indices_t, op, 1, F, o.dtype, nullptr));
         hipEvent_t e0, e1;
         CHECK(hipEventCreate(&e0)); CHECK(hipEventCreate(&e1));
         GCHECK(gnn_aggregate_fwd(indptr, (const int32_t *)indices, w, X, Y, N, F, op, &o));  // warm-up

@@ -575,7 +575,7 @@ int gnn_plan_edge_scale(gnn_plan *plan, const int32_t *indices, int mode, hipStr
 // coefficients in their order.  mode: the factor of the gathered rows.  Only gnn_plan_prepare builds it (build), because it takes 4 to 25 calls to pay:
 // 1.0 M vertices, 15 M edges F=100 a first call of 2.9 ms with and 0.8 without, then 0.73 and 0.81 each; 1.8 M, 26 M F=100 4.7 and 1.6, 1.25 and
 // 1.60; 27.8 M, 404 M bf16 F=128 52 and 15, 12.6 and 15.1; a step on a subgraph that is new makes one call with each plan.  False: it is not there, and the
-// call stays in place.
+// call stays in place; where there is no room nothing of it is left, and the next gnn_plan_prepare asks again.
 bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indices, int mode, gnn_weight_kind weights, int64_t F, int esz, hipStream_t stream,
                         bool build, gnn_hot_layout *out);
 

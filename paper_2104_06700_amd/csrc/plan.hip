@@ -680,6 +680,40 @@ int gnn_plan_padded(gnn_plan *plan, int64_t bytes, hipStream_t stream) {
     return GNN_OK;
 }
 
+namespace {
+
+// What an attempt to build hot tables goes back to where there is no room: what it has built, and nothing that was there before, is freed.
+struct BeforeHot {
+    bool rank_indices, rank, blocks, vertices, padded, blk_partial, tile_partial;
+    explicit BeforeHot(const gnn_plan *p)
+        : rank_indices(p->rank_indices), rank(p->rank), blocks(p->blk_decided), vertices(p->blk_hot_vertices), padded(p->padded.p),
+          blk_partial(p->blk_partial.p), tile_partial(p->tile_partial.p) {}
+    void restore(gnn_plan *p) const {
+        auto drop = [](auto *&q) { gnn_dev_free(q); q = nullptr; };
+        auto drop_room = [](gnn_grown &g, bool had) {
+            if (had) return;
+            gnn_dev_free(g.p);
+            g = gnn_grown{};
+        };
+        if (!vertices) { drop(p->blk_hot_vertices); drop(p->blk_cold_vertices); }
+        if (!blocks) {
+            drop(p->blk_indices); drop(p->blk_epos); drop(p->blk_idx16); drop(p->blk_piece_block); drop(p->blk_cell_off); drop(p->blk_pieces);
+            drop(p->blk_rowbase); drop(p->blk_bound_w);
+            for (float *&q : p->blk_edge_scale) drop(q);
+            for (gnn_tiles &t : p->tiles) gnn_tiles_free(t);
+            p->blk_n_edges = p->blk_n_pieces = p->blk_n_hot = 0;
+            p->blk_decided = 0;
+        }
+        if (!rank_indices) { drop(p->rank_indices); drop(p->p_indptr); drop(p->p_chunks); }
+        if (!rank) drop(p->rank);
+        drop_room(p->padded, padded);
+        drop_room(p->blk_partial, blk_partial);
+        drop_room(p->tile_partial, tile_partial);
+    }
+};
+
+}  // namespace
+
 bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indices, int mode, gnn_weight_kind weights, int64_t F, int esz, hipStream_t stream,
                         bool build, gnn_hot_layout *out) {
     const int line_elems = 128 / esz;
@@ -688,12 +722,16 @@ bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indic
     const uint64_t bit = uint64_t(1) << (lines & 63);
     if (weights == GNN_WEIGHTS_FREE || (mode && weights != GNN_WEIGHTS_NONE) || (plan->blk_decided && plan->blk_n_pieces <= 0)) return false;
     if (!(word & bit) && (!build || gnn_capturing(stream))) return false;
+    const BeforeHot before(plan);
     int slices = 1;
     while (slices < 8 && slices * 2 <= lines) slices *= 2;
     const gnn_tiles *tl = nullptr;
     const float *unused = nullptr;
     int rc = gnn_plan_hot(plan, indptr, indices, stream, out);
-    if (rc == GNN_OK && !out->blocks.active) return false;
+    if (rc == GNN_OK && !out->blocks.active) {
+        before.restore(plan);
+        return false;
+    }
     if (rc == GNN_OK) rc = gnn_plan_padded(plan, out->rows * lines * 128, stream);
     if (rc == GNN_OK) rc = gnn_plan_blocked_partial(plan, slices, line_elems, stream);
     if (rc == GNN_OK) rc = gnn_plan_tiles_with_room(plan, 8, esz == 2, !mode && weights == GNN_WEIGHTS_NONE, int(lines), line_elems, stream, &tl);
@@ -708,6 +746,7 @@ bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indic
     }
     if (rc != GNN_OK) {
         (void)hipGetLastError();
+        before.restore(plan);
         return false;
     }
     word |= bit;

@@ -100,6 +100,10 @@ def test_capacity_fullsize_bf16_int64():
     del order
     for op, oop in ((gnn.GNN_SUM, oracle.OP_SUM), (gnn.GNN_MEAN, oracle.OP_MEAN)):
         print(f"[capacity] op={op} forward/backward", flush=True)
+        if op == gnn.GNN_MEAN:  # the sums above stayed in place, these take hot tables
+            dg.plan_fwd.prepare(dg.indices, op, False, F, torch.bfloat16)
+            dg.plan_bwd.prepare(dg.indices_t, op, True, F, torch.bfloat16)
+        assert (dg.plan_fwd.blocked_sizes()[2] > 0) == (dg.plan_bwd.blocked_sizes()[2] > 0) == (op == gnn.GNN_MEAN)
         Y.fill_(float("nan")); dX.fill_(float("nan"))
         gnn.gnn_aggregate_fwd(dg.indptr, dg.indices, None, X, Y, n, F, op, plan=dg.plan_fwd)
         gnn.gnn_aggregate_bwd(dg.indptr_t, dg.indices_t, None, dY, dX, n, F, op, plan=dg.plan_bwd)

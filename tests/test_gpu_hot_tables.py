@@ -145,6 +145,39 @@ def test_a_plan_that_is_not_prepared_builds_none():
     assert torch.equal(_call(g, x, gnn.GNN_GCN_SYM, False), _call(g, x, gnn.GNN_GCN_SYM, False, IN_PLACE))
 
 
+def test_nothing_is_left_of_tables_that_there_is_no_room_for():
+    """gnn_plan_prepare finds room for a part only: it gives that back and holds what it holds for a plan without tables, the call stays in
+    place, and with room again they are built."""
+    def held_after_prepare(g):
+        torch.cuda.synchronize()
+        gnn.gnn_release_cached_memory()
+        before = torch.cuda.mem_get_info()[0]
+        _prepare(g, 100, gnn.GNN_SUM)
+        torch.cuda.synchronize()
+        gnn.gnn_release_cached_memory()
+        return before - torch.cuda.mem_get_info()[0]
+
+    g, without = _graph(1800000, 26000000), _graph(1800000, 26000000)
+    without.plan_fwd.set_blocking(hot_lines=65537)
+    x = _normal(10, g.n, 100)
+    y, y0 = torch.full_like(x, float("nan")), _call(g, x, gnn.GNN_SUM, False, IN_PLACE)
+    _call(without, x, gnn.GNN_SUM, False, out=y)
+    _prepare(_graph(1800000, 26000000), 100, gnn.GNN_SUM)  # the kernels that build them are loaded
+    least = held_after_prepare(without)
+    torch.cuda.empty_cache()
+    # 260 MB: the mapped index copy takes 126 with its row pointers, the sort of the long rows more than the rest
+    filler = [torch.empty(torch.cuda.mem_get_info()[0] - (2 << 30), dtype=torch.uint8, device="cuda")]
+    while torch.cuda.mem_get_info()[0] > 260 << 20:
+        filler.append(torch.empty(32 << 20, dtype=torch.uint8, device="cuda"))
+    assert held_after_prepare(g) <= least + (4 << 20)
+    _call(g, x, gnn.GNN_SUM, False, out=y)
+    del filler
+    torch.cuda.empty_cache()
+    assert g.plan_fwd.blocked_sizes()[2] == 0 and torch.equal(y, y0)
+    _prepare(g, 100, gnn.GNN_SUM)
+    assert g.plan_fwd.blocked_sizes()[2] > 0 and not torch.equal(_call(g, x, gnn.GNN_SUM, False), y0)
+
+
 @pytest.mark.parametrize("blocking,tables", [(dict(hot_lines=65537), False), (dict(block_lines=100000), False), (dict(hot_lines=40001, block_lines=9999), True)])
 def test_blocks_of_any_size(blocking, tables):
     """Blocks beyond 16-bit indices leave the rows in place; sizes that are no whole tiles or chunks have tables."""

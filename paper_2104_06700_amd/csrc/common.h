@@ -393,18 +393,26 @@ static inline bool gnn_plan_blocks_expected(const gnn_plan *plan, int esz, int64
     if (long_edges <= 0) return false;
     return !automatic || gnn_blocks_by_itself(plan, long_edges);
 }
-// Are there gathers enough for hot tables?  They save lines that come from behind the L2s, and cost the launches of pieces and tiles.  Rows off line
-// boundaries are aligned in the tables; bf16 rows have partial lines of twice their size.  MEAN, in place -> hot tables, us, power-law graphs by
-// their edges in rows of 256 and more: fp32 19.5 M edges F=32 461 -> 417, 64 895 -> 777, 100 2316 -> 1760, 256 4506 -> 3506; 13.1 M F=32 332 -> 330, 36 718
-// -> 663, 64 633 -> 597; 6.5 M F=32 160 -> 169, 64 315 -> 316, 100 824 -> 724, 256 1628 -> 1397; 3.5 M F=100 491 -> 472, 256 973 -> 934; 2.4 M F=100 260 ->
-// 279, 256 493 -> 509; bf16 19.5 M F=48 801 -> 720, 64 449 -> 456, 128 1029 -> 880; 13.1 M F=128 702 -> 674; 6.5 M F=128 363 -> 371, 200 814 -> 751; 3.6 M
-// F=200 369 -> 385, 512 857 -> 764; 243 M (27.8 M vertices) F=128 15.1 -> 12.8 ms forward, 15.1 -> 13.5 backward.
+// Are there gathers enough for hot tables?  They save lines that come from behind the L2s, and cost the launches of pieces and tiles, so the edges in
+// rows of 256 and more count, and the bytes these gather.  Rows off line boundaries are aligned in the tables; bf16 rows have partial lines of
+// twice their size.  MEAN, in place -> hot tables, us, power-law graphs by those edges: fp32 19.5 M F=32 461 -> 417, 64 895 -> 777, 100 2316 -> 1760, 256 4506 ->
+// 3506; 13.1 M F=32 332 -> 330, 36 718 -> 663, 64 633 -> 597; 6.5 M F=32 160 -> 169, 64 315 -> 316, 100 824 -> 724, 256 1628 -> 1397; 3.1 M F=100 360 -> 338, 200 738
+// -> 677, 256 674 -> 648; 2.3 M F=200 (1.9 GB) 1.06 times as long, 252 and 300 (2.3 and 2.8 GB) 0.96 and 0.92 times; 2.4 M F=384 (3.7 GB) 1.07 times, 512 (5.0)
+// 0.95; 2.1 M F=200 1.07 times, 500 1.13, 512 1.18; 1.9 M F=200 322 -> 362, 604 914 -> 1074; 0.9 M F=604 441 -> 569; bf16 19.5 M F=48 801 -> 720, 64 449 -> 456, 128
+// 1029 -> 880; 13.1 M F=128 702 -> 674; 6.5 M F=128 363 -> 371, 200 814 -> 751; 4.5 M F=400 (3.6 GB) the same; 3.7 M F=264 and 400 (2.0 and 3.0 GB) 1.04 and 1.06
+// times, 520 (3.9) 0.92; 3.3 M F=400 (2.6) 1.21 times, 520 (3.4) 0.93; 2.4 M F=400 1.31 times, 520 (2.5) 1.00, 1024 (5.0) 0.88; 243 M (27.8 M vertices) F=128 15.1 ->
+// 12.8 ms forward, 15.1 -> 13.5 backward.
 static inline bool gnn_hot_tables_pay(const gnn_plan *plan, int64_t row_bytes, int esz, bool lines_ok) {
     int first_bin = -1;
     for (int i = 0; i < plan->params.n_thresholds; ++i)
         if (plan->params.thresholds[i] == 256) first_bin = i + 1;
     if (first_bin < 0) return false;
-    return double(gnn_edges_from_bin(plan, first_bin)) * double(row_bytes) >= (!lines_ok ? (esz == 4 ? 1.2e9 : 1.8e9) : (esz == 4 && row_bytes <= 128 ? 2.0e9 : 3.2e9));
+    const int64_t edges = gnn_edges_from_bin(plan, first_bin);
+    if (edges < 2300000) return false;
+    double least;
+    if (!lines_ok) least = esz == 4 ? (edges < 3000000 ? 2.3e9 : 1.2e9) : (edges < 4400000 ? 3.3e9 : 1.8e9);
+    else least = esz == 4 && row_bytes <= 128 ? 2.0e9 : (edges < 3000000 ? 4.5e9 : 3.2e9);
+    return double(edges) * double(row_bytes) >= least;
 }
 
 // The edge weights of a call.  BOUND: the array of gnn_plan_bind_edge_weights; FREE: any other.

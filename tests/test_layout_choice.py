@@ -13,7 +13,7 @@ PROGRAM = r"""
 
 double gnn_plan_top_share(const gnn_plan *, int64_t) { return 0.5; }
 
-// hot_lines block_lines min_degree: are there hot tables for fp32 rows of 100 columns on 1.8 M vertices, 26 M edges, half of them in long rows?
+// hot_lines block_lines min_degree columns bytes-per-value long-edges: are there hot tables on 1.8 M vertices, 26 M edges?
 int main(int, char **argv) {
     gnn_plan p;
     p.n_rows = 1800000;
@@ -27,15 +27,17 @@ int main(int, char **argv) {
     p.bin_offsets[2] = 1785000;
     p.bin_offsets[3] = 1800000;
     p.bin_edges[0] = 6000000;
-    p.bin_edges[1] = 7000000;
-    p.bin_edges[2] = 13000000;
+    p.bin_edges[1] = 20000000 - std::atoll(argv[6]);
+    p.bin_edges[2] = std::atoll(argv[6]);
     p.bucket_vertices[3] = 1800000;
     p.bucket_edges[3] = 26000000;
     p.blocking.hot_lines = std::atoll(argv[1]);
     p.blocking.block_lines = std::atoll(argv[2]);
     p.blocking.min_degree = std::atoll(argv[3]);
-    const bool blocks = gnn_call_blocks_expected(&p, 4, 100, GNN_WEIGHTS_NONE);
-    const gnn_layout L = gnn_choose_layout(&p, p.n_rows, 100, 4, 100, true, 0, 0, true, false, blocks, false);
+    const int64_t F = std::atoll(argv[4]), esz = std::atoll(argv[5]);
+    if (p.bin_edges[2] < 6500000) p.n_edges = 4 * p.bin_edges[2];  // a quarter in long rows is what makes blocks
+    const bool blocks = gnn_call_blocks_expected(&p, int(esz), F, GNN_WEIGHTS_NONE);
+    const gnn_layout L = gnn_choose_layout(&p, p.n_rows, F, int(esz), F, true, 0, 0, true, false, blocks, false);
     std::printf("%d %d\n", int(L.hot_tables), int(L.padded_copy));
     return 0;
 }
@@ -49,7 +51,12 @@ def choose(tmp_path_factory):
     source.write_text(PROGRAM)
     subprocess.check_call([os.environ.get("CXX", "g++"), "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                            "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2104_06700_amd", "csrc"), str(source), "-o", str(binary)])
-    return lambda *args: tuple(map(int, subprocess.check_output([str(binary), *map(str, args)], text=True).split()))
+
+    def run(hot_lines=0, block_lines=0, min_degree=0, f=100, esz=4, long_edges=13000000):
+        args = (hot_lines, block_lines, min_degree, f, esz, long_edges)
+        return tuple(map(int, subprocess.check_output([str(binary), *map(str, args)], text=True).split()))
+
+    return run
 
 
 @pytest.mark.parametrize("hot_lines,block_lines,expected", [(0, 0, 1), (20000, 1000, 1), (65536, 65536, 1), (65537, 0, 0), (0, 65537, 0),
@@ -57,8 +64,16 @@ def choose(tmp_path_factory):
 def test_hot_tables_only_for_blocks_of_16_bit_indices(choose, hot_lines, block_lines, expected):
     """Their kernel tells the last block's pieces, which gather the caller's rows by vertex, by the 16-bit indices of the others: blocks
     too large for those leave every row where it lies."""
-    assert choose(hot_lines, block_lines, 0) == (expected, 0)
+    assert choose(hot_lines, block_lines) == (expected, 0)
 
 
 def test_no_hot_tables_where_blocks_were_asked_for_by_degree(choose):
-    assert choose(0, 0, 256)[0] == 0
+    assert choose(min_degree=256)[0] == 0
+
+
+@pytest.mark.parametrize("f,esz,long_edges,expected", [
+    (604, 4, 1890000, 0), (200, 4, 1890000, 0), (512, 4, 1890000, 0), (200, 4, 2420000, 0), (300, 4, 2420000, 1), (384, 4, 2420000, 0), (512, 4, 2420000, 1),
+    (100, 4, 3070000, 1), (256, 4, 3260000, 1), (128, 4, 5650000, 0), (400, 2, 3260000, 0), (520, 2, 3260000, 1), (200, 2, 6480000, 1), (1024, 2, 2420000, 1)])
+def test_hot_tables_only_where_the_long_rows_gather_enough(choose, f, esz, long_edges, expected):
+    """Power-law graphs of 240,000 to 1,600,000 vertices, timed with and without: up to 1.3 times as long where the launches outweigh the lines."""
+    assert choose(f=f, esz=esz, long_edges=long_edges)[0] == expected

@@ -430,7 +430,8 @@ struct ApRunArgs {
 // max / min of the neighbours' vectors for rows of at most GNN_RUN_EDGES edges, all columns, up to 64 rows per wavefront; see run_kernel
 // of aggregate.hip.  Two arrays are written here, so writing whole rows counts twice: 2.45 M vertices, three quarters of them such rows,
 // d = 100 7.19 -> 6.78 ms; 1 M, 20 M edges 1.23 -> 1.13.
-template <int RED>
+// TAIL: there is a table of the last columns (a lane's table and stride take three registers more, and with them an eighth of the wavefronts).
+template <int RED, bool TAIL>
 __global__ void __launch_bounds__(kBlockThreads) ap_run_kernel(const ApRunArgs a) {
     const int lane = threadIdx.x & 63;
     const gnn_run_bin bin = gnn_run_bin_of_block(a.bins, blockIdx.x);
@@ -461,7 +462,7 @@ __global__ void __launch_bounds__(kBlockThreads) ap_run_kernel(const ApRunArgs a
             int col = (strip0 + c) * 4;
             const bool col_ok = col < a.d;
             if (col > a.d - 4) col = a.d - 4;
-            const bool in_tail = col >= a.tail_col;
+            const bool in_tail = TAIL && col >= a.tail_col;
             const float *table = in_tail ? a.tail + (col - a.tail_col) : a.fV + col;
             const int64_t ld = in_tail ? a.ld_tail : a.ldv;
             auto fetch = [&](int src) {
@@ -1134,8 +1135,13 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
         ApRunArgs r{a.indptr, a.indices, a.row_perm, a.row_info, a.fV, a.out, a.arg_out, a.ldv, a.ldo, a.ld_arg, a.d, a.ip64, {}, tail, ld_tail, int32_t(tail_col)};
         gnn_fill_run_bins(r.bins, plan, run_bins, (d + 3) / 4);
         const dim3 grid(static_cast<unsigned>(r.bins.n_blocks));
-        if (reduce == GNN_RED_MAX) ap_run_kernel<GNN_RED_MAX><<<grid, kBlockThreads, 0, c.stream>>>(r);
-        else ap_run_kernel<GNN_RED_MIN><<<grid, kBlockThreads, 0, c.stream>>>(r);
+        auto launch = [&](auto with_tail) {
+            constexpr bool TAIL = decltype(with_tail)::value;
+            if (reduce == GNN_RED_MAX) ap_run_kernel<GNN_RED_MAX, TAIL><<<grid, kBlockThreads, 0, c.stream>>>(r);
+            else ap_run_kernel<GNN_RED_MIN, TAIL><<<grid, kBlockThreads, 0, c.stream>>>(r);
+        };
+        if (tail) launch(std::true_type());
+        else launch(std::false_type());
         if (hipGetLastError() != hipSuccess) return GNN_ERR_LAUNCH;
     }
     if (has_hub && !a.hub_done) {

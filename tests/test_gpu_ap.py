@@ -458,9 +458,10 @@ def test_edge_dots_of_long_rows_are_split_over_the_xcds(d, hubs, ordered, wide):
         assert bool(((out[part].double() - terms.sum(1)).abs() <= 1e-5 * terms.abs().sum(1)).all())
 
 
-@pytest.mark.parametrize("n,d,most", [(131100, 48, 380), (140000, 65, 320)])
+@pytest.mark.parametrize("n,d,most", [(131100, 48, 380), (140000, 65, 350), (200000, 100, 500)])
 def test_edge_dots_of_rows_of_150_edges_and_more(n, d, most):
-    """From 150 edges per vertex, 24 M edges and a gathered matrix of 24 MB: rows of every length up to `most`, and one cut into pieces."""
+    """From 150 edges per vertex, 24 M edges and a gathered matrix of 24 MB, and (the last) from 48 M edges on whatever the sources' skew, beyond
+    72 MB: rows of every length up to `most`, and one cut into pieces."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(d)
     lens = torch.randint(0, most, (n,), generator=gen, device=DEV)
@@ -469,8 +470,10 @@ def test_edge_dots_of_rows_of_150_edges_and_more(n, d, most):
     src = (dst * n + torch.randint(0, n, (dst.numel(),), generator=gen, device=DEV)).sort().values % n
     dst, src = dst.int(), src.int()
     e = dst.numel()
-    assert 150 * n <= e < 400 * n and 20000000 <= e < 48000000
+    assert 150 * n <= e < 400 * n and e >= 24000000 and 24 << 20 <= n * d * 4 <= 200 << 20
+    assert (e >= 48000000 and n * d * 4 > 72 << 20) == (d == 100)
     g = gnn.build_device_graph(dst, src, n)
+    assert e >= 48000000 or g.plan_fwd.gather_share(n // 20) < 0.525
     v, do = (torch.empty(n, d, device=DEV).normal_(generator=gen) for _ in range(2))
     fe = torch.rand(e, device=DEV, generator=gen)
     out = torch.full((e,), float("nan"), device=DEV)

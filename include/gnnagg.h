@@ -129,9 +129,9 @@ typedef struct gnn_opts {
 /* Degree-binning parameters.  thresholds t[0] < ... < t[k-1], all > 0, cut the
  * row-length axis into k+1 bins, bin(v) = #{i : t[i] <= deg(v)}.  If
  * hub_chunk > 0 the rows of the LAST bin are "hub" rows: each is cut into
- * pieces of hub_chunk consecutive edges that different wavefronts reduce, and a
- * second kernel adds the pieces in a fixed order (deterministic, no float
- * atomics).  NULL params = defaults (gnn_plan_default_params). */
+ * pieces of hub_chunk consecutive edges that different wavefronts reduce, and
+ * whose sums are added in a fixed order (deterministic, no float atomics), by
+ * the wavefront that is done with its piece last or by a second kernel.  NULL params = defaults (gnn_plan_default_params). */
 #define GNN_MAX_THRESHOLDS 15
 typedef struct gnn_plan_params {
     int32_t n_thresholds;

@@ -725,8 +725,7 @@ __global__ void __launch_bounds__(256) few_k_kernel(const GemmArgs g) {
 
 // C = act(sum over the partial planes + bias).  A workgroup owns 64 consecutive outputs; its wavefronts take every
 // kReduceWaves-th plane, eight loads in flight each, and their sums are added in order.  (One thread per output walking
-// all planes took 0.23 ms for 256 planes of 256 x 256, 67 MB.  Workgroups of 16 wavefronts were slower still beside the
-// aggregation on the other stream, which never leaves a compute unit that many slots at once.)  In 64 bits: adding the planes was most
+// all planes took 0.23 ms for 256 planes of 256 x 256, 67 MB.)  In 64 bits: adding the planes was most
 // of the error of many short parts (24,490 rows, 256 x 256, 2-norm 1.5e-7 -> 0.8e-7), and the loads take longer than the additions.
 // The workgroups from n_blocks on add up `rows` (a bias gradient), which as a kernel of its own took 4.5 us behind this one.
 constexpr int kReduceWaves = 4;

@@ -4,9 +4,10 @@
 // 980 MB ran at the rate at which lines move behind the L2s (48 G/s, 5.05 ms).  Here the additions are brought to where
 // their sums are kept.  Columns are taken four at a time (a quad), so that the sums of 4096 vertices fit the LDS of a
 // compute unit, and the pairs (vertex, value) of a quad are sorted by such ranges of vertices first:
-//   1 resolve    winner positions -> source vertices, quad by quad ([quad][v][4]), beside the values; rows without winners are left out
+//   1 resolve    winner positions -> source vertices, quad by quad ([quad][v][4]), beside the values; large rounds (kWideTiles) leave rows
+//                without winners out
 //   2 count      pairs per (quad, range, part of the rows), scanned into write positions
-//   3 partition  tiles of 16384 pairs are ordered by range in LDS and leave as runs of consecutive pairs, 6 bytes each
+//   3 partition  tiles of 16384 pairs, 8192 in small rounds, are ordered by range in LDS and leave as runs of consecutive pairs, 6 bytes each
 //   4 add        a workgroup adds the pairs of a range in LDS and writes its rows; a range with many pairs (the vertices
 //                that win often) is cut into pieces, which add their sums to rows filled with zeros
 // All of it streams, about 44 bytes per pair, 20 of them before rows without winners (43 % there) are left out, at 2.4 to 3.4 TB/s: a run of the

@@ -15,11 +15,41 @@
 //     transform first:  dP = A^^T G, dW = X^T dP, dX = dP W^T
 #include "common.h"
 
+#include <mutex>
+
 namespace {
 
 constexpr int kRowsPerBlock = 64;
 // the rows of partial column sums, one per block of rows, also take one plane per part of the split weight gradient
 static_assert(kRowsPerBlock <= GNN_SPLIT_MIN_K, "room for a plane per part");
+
+// A library-owned side stream per device (default priority, created on first use, kept until the process ends), for weight_gradient_beside.
+hipStream_t side_stream() {
+    static std::mutex mu;
+    static hipStream_t streams[64] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+    std::lock_guard<std::mutex> lock(mu);
+    if (!streams[dev] && hipStreamCreateWithFlags(&streams[dev], hipStreamNonBlocking) != hipSuccess) streams[dev] = nullptr;
+    return streams[dev];
+}
+
+// Aggregating first, the weight gradient needs no more than what the aggregation of dZ begins with.  Beside it, on a second stream, it takes as much
+// as it hides where both fill the chip, and small graphs pay for the turn of streams (widths 100, 256, 256, 47, forward and backward, two streams ->
+// one: 24,490 vertices, 1.2 M edges 514 -> 491 us, 600 K, 30 M 8.49 -> 8.31 ms, 2.45 M, 124 M 35.07 -> 34.93; 64, 128, 128, 40 200 K, 10 M 1.71 -> 1.67).
+// Narrow products are chains of loads, and beside a gather from a copy they are nearly free.  Backward call, two streams over one, by widths (in, out):
+//   200 K vertices, 30 and 50 edges each     16, 16 0.88 0.85;  16, 48 0.95;  32, 32 0.83 0.84;  32, 64 0.89;  48, 48 1.09 1.10;  64, 64 (50) 1.07
+//   300 K, 30, 50, 110                       8, 16 0.85 0.84 0.97;  16, 16 0.81 0.83 0.97;  16, 64 0.90 0.97 1.02;  32, 64 0.91 0.91 0.99
+//   1.1 M, 30, 50, 110                       16, 16 0.91 0.98 0.95;  16, 48 0.96 1.03 0.98;  32, 32 0.97 1.04 0.99;  32, 64 1.00 1.00 1.02
+//   2.45 M, 50                               16, 16 0.91;  16, 53 0.98;  32, 32 0.96;  32, 64 1.03;  64, 128 1.08
+//   1.9 M, 19                                16, 16 0.91;  16, 53 0.99;  32, 32 0.91
+// Not without a copy to gather from: 12 edges a vertex 150 K to 300 K 16, 16 1.07 to 1.12, 450 K 1.07 and 32, 32 1.02 (1.1 M 0.97 and 0.89, 1.8 M 0.91 and 0.89, but 16,
+// 48 1.08 and 1.05); 100 K, 50 edges 16, 16 1.14, 32, 32 1.19; 150 K, 50 edges 16, 16 1.07, 24, 32 0.81.  Nor beside 200 edges a vertex and more: 233 K,
+// 404 edges, strong and mild skew, 16, 16 1.04 0.95, 16, 53 1.08 0.99, 32, 32 0.99 1.09, 32, 64 1.00 1.11.
+bool weight_gradient_beside(const gnn_plan *plan, int64_t N, int64_t F_in, int64_t F_out) {
+    if (!plan || F_in > 32 || F_out > 64 || plan->n_edges >= 200 * N) return false;
+    return (plan->n_edges >= 16 * N && plan->n_edges >= 5500000 && N * F_in >= 3000000) || (N >= 1000000 && F_out <= 32);
+}
 
 // G = dH where H > 0 (else 0; plain copy without a rectifier) for a block of rows, written with row
 // stride ldg when G != nullptr, plus the block's column sums.  A thread owns one column and every
@@ -272,17 +302,17 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
     }
     const float *Gm = (need_g && !fold_gate) ? G : dH;
     const float *gate = (fold_gate && o.relu) ? H : nullptr;
-    // dW = Z^T G, and with the gate folded also db = the column sums of G, added in plane order
-    auto weight_gradient = [&]() -> int {
-        if (!fold_gate) return gnn_matmul_impl(saved, F_in, 1, Gm, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, stream);
+    // dW = Z^T G on `st`, and with the gate folded also db = the column sums of G, added in plane order
+    auto weight_gradient = [&](hipStream_t st) -> int {
+        if (!fold_gate) return gnn_matmul_impl(saved, F_in, 1, Gm, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, st);
         gnn_gemm_fold fold{};
         fold.b_gate = gate;
         fold.colsum = db ? part : nullptr;
         fold.colsum_planes = n_blocks;
         fold.row_sum = db;
-        int rcw = gnn_matmul_impl(saved, F_in, 1, dH, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, stream, nullptr, &fold);
+        int rcw = gnn_matmul_impl(saved, F_in, 1, dH, F_out, 0, dW, F_out, F_in, F_out, N, nullptr, 0, mm_ws, mm_bytes, st, nullptr, &fold);
         if (rcw != GNN_OK || !db || fold.summed) return rcw;
-        launch_colsum_reduce(part, fold.n_planes, int(F_out), part2, db, stream);
+        launch_colsum_reduce(part, fold.n_planes, int(F_out), part2, db, st);
         return hipGetLastError() == hipSuccess ? GNN_OK : GNN_ERR_LAUNCH;
     };
 
@@ -292,19 +322,37 @@ extern "C" GNN_API int gnn_sage_layer_bwd(const void *indptr_t, const int32_t *i
     a.stream = o.stream;
     a.plan = o.plan;
     if (agg_first) {
-        if (!dX) return weight_gradient();
-        // dZ = G W^T, dW = Z^T G, then the aggregation.  One after the other: dW on a second stream beside the aggregation takes as much from it as
-        // it hides, and small graphs pay for the turn of streams (widths 100, 256, 256, 47, forward and backward, two streams -> one: 24,490
-        // vertices, 1.2 M edges 514 -> 491 us, 600 K, 30 M 8.49 -> 8.31 ms, 2.45 M, 124 M 35.07 -> 34.93; 64, 128, 128, 40 200 K, 10 M 1.71 -> 1.67,
-        // 1 M, 10 M the same).
+        if (!dX) return weight_gradient(stream);
+        // dZ = G W^T, then dW = Z^T G in front of the aggregation or beside it
         gnn_gemm_fold fold_a{};
         fold_a.a_gate = gate;
         rc = gnn_matmul_impl(Gm, F_out, 0, W, F_out, 1, T, F_in, N, F_in, F_out, nullptr, 0, nullptr, 0, stream, &pk, &fold_a);
         if (rc != GNN_OK) return rc;
-        rc = weight_gradient();
-        if (rc != GNN_OK) return rc;
-        return pk.active ? gnn_aggregate_prepacked(indptr_t, indices_t, dX, N, F_in, GNN_SAGE_GCN, &a, /*backward=*/true, force, nullptr, 0)
-                         : gnn_aggregate_bwd(indptr_t, indices_t, nullptr, T, dX, N, F_in, GNN_SAGE_GCN, &a);
+        hipStream_t side = weight_gradient_beside(o.plan, N, F_in, F_out) ? side_stream() : nullptr;
+        hipEvent_t fork = nullptr, join = nullptr;
+        if (side && (hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess ||
+                     hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess)) {
+            if (fork) (void)hipEventDestroy(fork);
+            fork = join = nullptr;
+            side = nullptr;
+            (void)hipGetLastError();
+        }
+        if (side && (hipEventRecord(fork, stream) != hipSuccess || hipStreamWaitEvent(side, fork, 0) != hipSuccess)) {
+            (void)hipEventDestroy(fork);
+            (void)hipEventDestroy(join);
+            return GNN_ERR_LAUNCH;
+        }
+        rc = weight_gradient(side ? side : stream);
+        int rc2 = GNN_OK;
+        if (side || rc == GNN_OK)
+            rc2 = pk.active ? gnn_aggregate_prepacked(indptr_t, indices_t, dX, N, F_in, GNN_SAGE_GCN, &a, /*backward=*/true, force, nullptr, 0)
+                            : gnn_aggregate_bwd(indptr_t, indices_t, nullptr, T, dX, N, F_in, GNN_SAGE_GCN, &a);
+        if (side) {  // join, whatever happened above: the caller's stream must not run ahead of the side stream
+            if (hipEventRecord(join, side) != hipSuccess || hipStreamWaitEvent(stream, join, 0) != hipSuccess) rc = GNN_ERR_LAUNCH;
+            (void)hipEventDestroy(fork);  // released by the runtime once the recorded work has completed
+            (void)hipEventDestroy(join);
+        }
+        return rc != GNN_OK ? rc : rc2;
     }
     a.ldy = ldg;
     if (pk.active) {

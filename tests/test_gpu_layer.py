@@ -243,6 +243,52 @@ def test_layer_backward_folded_rectifier_with_a_split_reduction(flags):
         assert torch.equal(a, b)
 
 
+_narrow = {}
+
+
+def _narrow_graph():
+    """30 edges per vertex: the aggregation of narrow rows has a copy to gather from, and the weight gradient runs beside it."""
+    if not _narrow:
+        _narrow["el"] = synth.rmat_symmetric(200_000, 6_000_000, (0.45, 0.22, 0.22, 0.11), 8)
+    return _narrow["el"]
+
+
+@pytest.mark.parametrize("fi,fo,relu", [(16, 16, True), (24, 41, False), (32, 64, True)])
+def test_layer_weight_gradient_beside_the_aggregation(fi, fo, relu):
+    _layer_case(_narrow_graph(), None, fi, fo, relu, 0, seed=fi)
+
+
+def test_layer_weight_gradient_beside_the_aggregation_under_capture():
+    """The second stream joins the capture; replays with other gradients and eager work between them give the eager call's bits."""
+    el, fi, fo = _narrow_graph(), 16, 24
+    dg, n = device_graph(el), el.n
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    rand = lambda *shape: torch.empty(shape, device=DEV).normal_(generator=gen)
+    x, w, h, saved = rand(n, fi), rand(fi, fo), rand(n, fo).clamp_(min=0.0), rand(gnn.gnn_sage_layer_saved_elems(n, fi, fo))
+    dh, other = rand(n, fo), rand(n, fo)
+    ws = torch.empty(gnn.gnn_sage_layer_workspace_bytes(n, fi, fo, True) // 4 + 1, device=DEV)
+    dg.plan_bwd.prepare(dg.indices_t, gnn.GNN_SAGE_GCN, True, fi)
+    outs = [[torch.full(shape, float("nan"), device=DEV) for shape in ((n, fi), (fi, fo), (fo,))] for _ in range(2)]
+
+    def call(out):
+        gnn.gnn_sage_layer_bwd(dg.indptr_t, dg.indices_t, x, w, saved, h, dh, *out, dg.plan_bwd, ws, relu=True)
+
+    call(outs[0])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(outs[1])
+    for values in (dh.clone(), other, dh.clone()):
+        dh.copy_(values)
+        for t in outs[1]:
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        call(outs[0])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
 def test_layer_without_bias_and_without_input_gradient():
     el, params = _graph("multi")
     _layer_case(el, params, 40, 24, True, order=0, seed=10, use_bias=False, want_dx=False)

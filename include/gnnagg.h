@@ -484,8 +484,10 @@ GNN_API int gnn_plan_reserve(gnn_plan *plan, int64_t F);
  * plan's row order), or -- where no copy of the matrix is made but column slices are used on a
  * large power-law graph -- the index copy with the cold sources flagged.  On large power-law graphs of
  * fewer than 16 edges per vertex it also makes tables of the most-gathered sources, for the long rows
- * (about 20 bytes per edge of those rows, plus the tables), where there is room for them: these are
- * not made by a call on its first use, so a plan that is never prepared gathers every row in place.
+ * (about 20 bytes per edge of those rows, plus the tables), where there is room for them and no call
+ * over a copy of all rows (gnn_aggregate_packed, GNN_FLAG_FORCE_PADDED_COPY) has made the plan's source
+ * blocks before: these are not made by a call on its first use, so a plan that is never prepared gathers
+ * every row in place.
  * That is reserved for calls
  * without edge weights, with the weights bound to the plan at this moment and with any others (which
  * may choose another layout each), on dense matrices (row stride F) at 128-byte boundaries, without

@@ -327,7 +327,7 @@ extern "C" GNN_API int gnn_plan_bind_edge_weights(gnn_plan *plan, const float *e
     return GNN_OK;
 }
 
-int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn_blocked_layout *out) {
+int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn_blocked_layout *out, bool for_hot_tables) {
     *out = gnn_blocked_layout{};
     if (!plan) return GNN_ERR_INVALID_ARG;
     if (!plan->blk_decided) {
@@ -362,10 +362,11 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             enable = n_edges > 0;
         }
         if (enable && automatic) enable = gnn_blocks_by_itself(plan, n_edges);
-        // Few edges per vertex: the last block takes the sources of which a row has fewer than about 20 edges in a block, so that a piece is worth
+        // Hot tables: the last block takes the sources of which a row has fewer than about 20 edges in a block, so that a piece is worth
         // its partial line, in bf16 twice the size of what it gathers, and pieces are longer (27.8 M vertices, 404 M edges, bf16 F=128, ms: edges
-        // 5, 10, 15, 30 of pieces of 96 13.90, 13.47, 13.44, 13.23; 10 of pieces of 192, 384 13.16, 13.00; 20 of 256 12.94).
-        if (enable && gnn_few_edges(plan)) {
+        // 5, 10, 15, 30 of pieces of 96 13.90, 13.47, 13.44, 13.23; 10 of pieces of 192, 384 13.16, 13.00; 20 of 256 12.94).  Not where all rows have
+        // a table (packed copies of 2.4 M vertices, 36 M edges F=100 1354 -> 1380 us, 256 2755 -> 2803; 1 M, 12 M 489 -> 496, 941 -> 951).
+        if (enable && for_hot_tables) {
             const double count = 20.0 * double(n_hot) * double(E) / (double(prm.block_lines) * double(n_edges));
             const int64_t least = gnn_count_bucket_lower_bound(gnn_count_bucket_of(int64_t(count < 1e9 ? count : 1e9)));
             if (plan->blocking.rest_min_count == 0 && least > prm.rest_min_count) prm.rest_min_count = least;
@@ -465,6 +466,7 @@ int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn
             plan->blk_cell_off = edge_off;
             plan->blk_pieces = list.pieces;
             plan->blk_rowbase = list.rowbase;
+            plan->blk_last_in_place = for_hot_tables;
         }
         plan->blk_decided = 1;
     }
@@ -503,7 +505,7 @@ int build_hot(gnn_plan *plan, const void *indptr, const int32_t *indices, hipStr
     int rc = gnn_plan_rank_indices(plan, indptr, indices, false, stream, &rl);
     if (rc != GNN_OK) return rc;
     gnn_blocked_layout bl{};
-    if ((rc = gnn_plan_blocked(plan, indptr, stream, &bl)) != GNN_OK || !bl.active || !bl.idx16 || plan->blk_hot_vertices) return rc;
+    if ((rc = gnn_plan_blocked(plan, indptr, stream, &bl, true)) != GNN_OK || !bl.active || !plan->blk_last_in_place || !bl.idx16 || plan->blk_hot_vertices) return rc;
     uint32_t begin = 0;
     GNN_HIP_TRY(hipMemcpyAsync(&begin, plan->blk_cell_off + int64_t(plan->blk_n_blocks - 1) * plan->blk_n_hot, 4, hipMemcpyDeviceToHost, stream));
     GNN_HIP_TRY(hipStreamSynchronize(stream));

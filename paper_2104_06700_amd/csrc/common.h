@@ -126,6 +126,7 @@ struct gnn_plan {
     // Source-blocked layout of the long rows (see gnn_plan_blocked); built on first use.
     gnn_blocking_params blocking{};   // requested parameters (zeros: automatic)
     int32_t blk_decided = 0;          // 0: not yet; 1: decided (blk_n_pieces == 0 when it does not apply)
+    bool blk_last_in_place = false;   // blocks for hot tables: the last one is of rows that have no table, so nothing of it goes into tiles
     int32_t blk_first_bin = 0;        // rows of bins >= this are processed as pieces
     int64_t blk_hot_begin = 0;        // their range in row_perm is [blk_hot_begin, n_rows)
     int64_t blk_n_hot = 0;
@@ -191,7 +192,8 @@ struct gnn_blocked_layout {
 };
 // Builds the layout on first use (allocation; needs the rank layout) and reports it.  Inactive when
 // the graph or the plan's thresholds do not suit it.
-int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn_blocked_layout *out);
+// for_hot_tables: where it is built now, it is for those (gnn_plan::blk_last_in_place), else for tables of all rows.
+int gnn_plan_blocked(gnn_plan *plan, const void *indptr, hipStream_t stream, gnn_blocked_layout *out, bool for_hot_tables = false);
 // Hot tables, for graphs of few edges per vertex: the copy has the sources of the blocks only, the most-gathered ones, and everything else is
 // gathered where it lies: the pieces of the last block by vertex, the short rows by the kernels that serve rows in place.
 struct gnn_hot_layout {
@@ -364,8 +366,8 @@ static inline int64_t gnn_edges_from_bin(const gnn_plan *plan, int first_bin) {
     for (int b = first_bin; b < plan->n_bins; ++b) edges += plan->bin_edges[b];
     return edges;
 }
-// Graphs of fewer edges per vertex than a copy of the whole matrix pays for.  Blocked by themselves they have hot tables (gnn_plan_hot); the
-// sources of the last block are never copied, so nothing of it goes into tiles.
+// Graphs of fewer edges per vertex than a copy of the whole matrix pays for.  Blocked by themselves they have hot tables (gnn_plan_hot), unless a call
+// over a copy that the caller keeps or asks for has made the plan's blocks.
 static inline bool gnn_few_edges(const gnn_plan *plan) { return plan->blocking.min_degree == 0 && plan->n_edges < 16 * plan->n_rows; }
 // Blocks whose edges have 16-bit indices, all but the last: by them the kernel over hot tables tells the last block's pieces, which gather by vertex.
 constexpr int64_t GNN_NARROW_BLOCK = 65536;

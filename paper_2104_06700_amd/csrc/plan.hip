@@ -703,6 +703,7 @@ struct BeforeHot {
             for (gnn_tiles &t : p->tiles) gnn_tiles_free(t);
             p->blk_n_edges = p->blk_n_pieces = p->blk_n_hot = 0;
             p->blk_decided = 0;
+            p->blk_last_in_place = false;
         }
         if (!rank_indices) { drop(p->rank_indices); drop(p->p_indptr); drop(p->p_chunks); }
         if (!rank) drop(p->rank);

@@ -1173,7 +1173,7 @@ int build_tiles(const gnn_plan *plan, int lanes, int rr, bool dense, hipStream_t
     for (int k = 0; k < n_blocks; ++k) {
         int64_t lo, hi;
         block_range(k, &lo, &hi);
-        if (k == n_blocks - 1 && gnn_few_edges(plan)) hi = lo;  // its sources have no table
+        if (k == n_blocks - 1 && plan->blk_last_in_place) hi = lo;
         n_block_tiles[size_t(k)] = hi > lo ? (hi - lo + tile_lines - 1) / tile_lines : 0;
         block_min[size_t(k)] = uint32_t(n_block_tiles[size_t(k)] * kMinRowEdges);
     }

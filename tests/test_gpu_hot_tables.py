@@ -178,6 +178,34 @@ def test_nothing_is_left_of_tables_that_there_is_no_room_for():
     assert g.plan_fwd.blocked_sizes()[2] > 0 and not torch.equal(_call(g, x, gnn.GNN_SUM, False), y0)
 
 
+@pytest.mark.parametrize("prepared", [False, True])
+def test_packed_copies_of_all_rows(prepared):
+    """A plan whose blocks a call over a packed copy has made has them as for any graph, tables for the last one's sources included, and its other calls
+    stay in place; over a plan prepared for hot tables that call takes their blocks."""
+    g, as_given = _graph(1800000, 26000000), _graph(1800000, 26000000)
+    as_given.plan_fwd.set_blocking(max_piece=96, rest_min_count=16)
+    x = _normal(12, g.n, 100)
+    packed = torch.empty(gnn.gnn_packed_bytes(g.n, 100, gnn.GNN_F32), dtype=torch.uint8, device="cuda")
+
+    def packed_call(h):
+        y = torch.full_like(x, float("nan"))
+        gnn.gnn_pack_rows(h.indptr, h.indices, x, packed, h.n, 100, gnn.GNN_SUM, False, h.plan_fwd)
+        gnn.gnn_aggregate_packed(h.indptr, h.indices, None, packed, y, h.n, 100, gnn.GNN_SUM, False, h.plan_fwd)
+        return y
+
+    if prepared:
+        _prepare(g, 100, gnn.GNN_SUM)
+    y, y_given = packed_call(g), packed_call(as_given)
+    assert (g.plan_fwd.blocked_sizes() == as_given.plan_fwd.blocked_sizes()) != prepared
+    assert prepared or torch.equal(y, y_given)
+    exact = _exact(g, x, gnn.GNN_SUM, False)
+    _assert_within(y, exact)
+    _prepare(g, 100, gnn.GNN_SUM)
+    y, y0 = _call(g, x, gnn.GNN_SUM, False), _call(g, x, gnn.GNN_SUM, False, IN_PLACE)
+    assert torch.equal(y, y0) != prepared
+    _assert_within(y, exact)
+
+
 @pytest.mark.parametrize("blocking,tables", [(dict(hot_lines=65537), False), (dict(block_lines=100000), False), (dict(hot_lines=40001, block_lines=9999), True)])
 def test_blocks_of_any_size(blocking, tables):
     """Blocks beyond 16-bit indices leave the rows in place; sizes that are no whole tiles or chunks have tables."""

@@ -1330,7 +1330,7 @@ extern "C" GNN_API int gnn_ap_bwd_edge(const void *indptr, const int32_t *indice
         auto split_pays = [&] {
             if (!gnn_long_rows(plan->n_edges, N) || plan->rows_unordered || d <= 32 || bytes < (int64_t(18) << 20) || bytes > (int64_t(200) << 20)) return false;
             if (plan->n_edges >= 400 * N || plan->n_edges >= 48000000) return true;
-            return plan->n_edges >= 24000000 && bytes >= (int64_t(24) << 20) && gnn_plan_top_share(plan, N / 20) < kStrongSkew;
+            return bytes >= (int64_t(24) << 20) && gnn_plan_top_share(plan, N / 20) < kStrongSkew;
         };
         a.source_split = plan && blocks <= INT32_MAX / 8 && split_pays() ? 1 : 0;
         if (a.source_split) grid.x *= 8;

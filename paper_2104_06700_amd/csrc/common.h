@@ -565,8 +565,10 @@ int gnn_plan_rank_indices(gnn_plan *plan, const void *indptr, const int32_t *ind
 int gnn_read_edge_count(const void *indptr, int64_t N, int indptr_is_64, hipStream_t stream, int64_t *E);
 // rank[v] = position of vertex v by descending count, ties by ascending id; no count exceeds max_count (graph.hip).
 int gnn_rank_by_count(const int32_t *counts, int64_t N, int64_t max_count, int32_t *rank, hipStream_t stream);
-// Graphs whose edge dot products may be split over the XCDs (gnn_ap_bwd_edge); their plans look at the order of the sources.
-static inline bool gnn_long_rows(int64_t E, int64_t N) { return E >= 150 * N; }
+// Graphs whose edge dot products may be split over the XCDs (gnn_ap_bwd_edge); their plans look at the order of the sources, which is a launch of a
+// few microseconds, so smaller graphs, whose plans may serve a call or two, are left out (plans and transposed graph of 4,000 vertices, 0.8 M
+// edges: with the launch 165 us, without 156 to 160).
+static inline bool gnn_long_rows(int64_t E, int64_t N) { return E >= 400 * N || (E >= 24000000 && E >= 150 * N); }
 // Share of the gathers that go to the most-gathered twentieth of the vertices, from which on few of them have most of the edges.
 constexpr double kStrongSkew = 0.525;
 // The plans of a graph and of its transpose, E edges each; the host fields are valid on return.

@@ -14,7 +14,12 @@ PROGRAM = r"""
 double gnn_plan_top_share(const gnn_plan *, int64_t) { return 0.5; }
 
 // hot_lines block_lines min_degree columns bytes-per-value long-edges: are there hot tables on 1.8 M vertices, 26 M edges?
-int main(int, char **argv) {
+// edges vertices: does a plan look at the order of the sources?
+int main(int argc, char **argv) {
+    if (argc == 3) {
+        std::printf("%d\n", int(gnn_long_rows(std::atoll(argv[1]), std::atoll(argv[2]))));
+        return 0;
+    }
     gnn_plan p;
     p.n_rows = 1800000;
     p.n_edges = 26000000;
@@ -56,6 +61,7 @@ def choose(tmp_path_factory):
         args = (hot_lines, block_lines, min_degree, f, esz, long_edges)
         return tuple(map(int, subprocess.check_output([str(binary), *map(str, args)], text=True).split()))
 
+    run.binary = str(binary)
     return run
 
 
@@ -77,3 +83,10 @@ def test_no_hot_tables_where_blocks_were_asked_for_by_degree(choose):
 def test_hot_tables_only_where_the_long_rows_gather_enough(choose, f, esz, long_edges, expected):
     """Power-law graphs of 240,000 to 1,600,000 vertices, timed with and without: up to 1.3 times as long where the launches outweigh the lines."""
     assert choose(f=f, esz=esz, long_edges=long_edges)[0] == expected
+
+
+@pytest.mark.parametrize("edges,vertices,expected", [(800000, 4000, 0), (1600000, 4000, 1), (12000000, 50000, 0), (23999999, 100000, 0), (24000000, 100000, 1),
+                                                     (24000000, 160001, 0), (79000000, 500000, 1), (79000000, 132534, 1), (0, 1, 0)])
+def test_order_of_the_sources_is_looked_at_only_where_a_rule_asks(choose, edges, vertices, expected):
+    """The split of edge dot products asks for 400 edges a vertex, or for 150 and 24 M in all; for other graphs the launch would be for nothing."""
+    assert int(subprocess.check_output([choose.binary, str(edges), str(vertices)], text=True)) == expected

@@ -1045,11 +1045,20 @@ int run_ap_fwd(const void *indptr, const int32_t *indices, const float *fV, cons
             // 5053, 100 6793 -> 6538, 112 6712 -> 6496; 500 K, 40 M 68 1688 -> 1552, 80 1661 -> 1600, 100 2263 -> 2119; 250 K, 20 M 100 944 -> 850; 1.5 M, 28 M 100 1708 ->
             // 1631; rows of 48 bytes, which lie across lines, 1.2 M, 85 M 75 columns 4398 -> 4593).
             const int64_t rest = d % 32;
-            const bool apart = !use_e && L.slices_wanted && c.o.max_slices == 0 && d > 64 && d <= 256 * 32 && rest >= 4 && rest <= 16 && (rest <= 8 || rest > 12);
-            const int64_t main_cols = apart ? d - rest : d, ld_main = apart ? (main_cols / 32 | 1) * 32 : L.ld_pad;
-            if (apart) ld_tail = rest <= 4 ? 4 : rest <= 8 ? 8 : 16;
-            rc = gnn_plan_padded(plan, N * (ld_main + ld_tail) * 4, c.stream);
-            if (rc != GNN_OK) return rc;
+            bool apart = !use_e && L.slices_wanted && c.o.max_slices == 0 && d > 64 && d <= 256 * 32 && rest >= 4 && rest <= 16 && (rest <= 8 || rest > 12);
+            const int64_t ld_apart = ((d - rest) / 32 | 1) * 32, ld_rest = rest <= 4 ? 4 : rest <= 8 ? 8 : 16;
+            // The two tables take more than the one where that has an odd number of lines (68 columns: 400 bytes a row, 384): without room, or in a capture of a
+            // plan that has room for the one only, it is the one.
+            const int64_t apart_bytes = N * (ld_apart + ld_rest) * 4;
+            if (apart && apart_bytes > plan->padded.bytes && gnn_capturing(c.stream)) apart = false;
+            if (apart) {
+                rc = gnn_plan_padded(plan, apart_bytes, c.stream);
+                if (rc == GNN_ERR_ALLOC) apart = false;
+                else if (rc != GNN_OK) return rc;
+            }
+            if (!apart && (rc = gnn_plan_padded(plan, N * L.ld_pad * 4, c.stream)) != GNN_OK) return rc;
+            const int64_t main_cols = apart ? d - rest : d, ld_main = apart ? ld_apart : L.ld_pad;
+            if (apart) ld_tail = ld_rest;
             float *copy = static_cast<float *>(plan->padded.p);
             rc = gnn_pad_rows_f32(fV, c.ldv, copy, ld_main, N, main_cols, plan->col_counts, c.stream);
             if (rc == GNN_OK && apart) {

@@ -202,3 +202,29 @@ def test_pooling_with_a_last_line_of_few_columns(d, reducer):
         where = torch.where(lens[:, None] > 0, where, -1)
         assert torch.equal(out[:, cols], want)
         assert torch.equal(arg[:, cols].long(), where)
+
+
+def test_pooling_captured_with_room_for_one_table():
+    """A captured call cannot make room: where the plan has it for rows of three lines, 68 columns take one table, not the two that need 400 bytes a row."""
+    n, flags = 20_000, gnn.GNN_FLAG_FORCE_PADDED_COPY
+    el = synth.rmat_directed(n, 400_000, (0.57, 0.19, 0.19, 0.05), 3, device=DEV)
+    g, eager = gnn.build_device_graph(el.dst, el.src, n), gnn.build_device_graph(el.dst, el.src, n)
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    x, v = torch.randn(n, 96, generator=gen, device=DEV), torch.randn(n, 68, generator=gen, device=DEV)
+
+    def call(h, rows, out, arg):
+        gnn.gnn_ap_fwd(h.indptr, h.indices, rows, None, out, arg, n, rows.shape[1], gnn.GNN_BIN_COPY_LHS, gnn.GNN_RED_MAX, plan=h.plan_fwd, flags=flags)
+
+    call(g, x, torch.empty_like(x), torch.empty(x.shape, dtype=torch.int32, device=DEV))
+    out, want = torch.empty_like(v), torch.empty_like(v)
+    arg, want_arg = (torch.empty(v.shape, dtype=torch.int32, device=DEV) for _ in range(2))
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        call(g, v, out, arg)
+    for _ in range(3):
+        v.normal_(generator=gen)
+        graph.replay()
+        torch.cuda.synchronize()
+        call(eager, v, want, want_arg)
+        assert torch.equal(out, want) and torch.equal(arg, want_arg)

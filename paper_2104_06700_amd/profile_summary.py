@@ -370,9 +370,9 @@ def write_layer_summary(d: str, out_dir: str) -> None:
             "An epoch here = one forward and one backward call of every layer of the model (no loss, no optimizer).  Three runs of",
             "the same command per variant: `rocprofv3 --kernel-trace --stats`, `--pmc FETCH_SIZE`, `--pmc WRITE_SIZE` (KiB per",
             f"dispatch, scaled x {fscale:.0f} / x {wscale:.0f} as calibrated with the 1 GiB copy of the aggregation profiles).  ms/epoch of a kernel =",
-            "its total time / calls per layer and direction.  Products and aggregation follow each other on the caller's stream; the short",
-            "rows of an aggregation run beside its tiles and pieces on a second one, and both count in full, so the sum exceeds the epoch's",
-            "wall time.", ""]
+            "its total time / calls per layer and direction.  Products and aggregation follow each other on the caller's stream, but for the",
+            "weight gradient of narrow layers, which runs beside the aggregation on a second one, as the short rows of an aggregation run",
+            "beside its tiles and pieces; both count in full, so the sum exceeds the epoch's wall time.", ""]
     os.makedirs(out_dir, exist_ok=True)
     path = os.path.join(out_dir, f"layer_kernels_{workload}.md")
     open(path, "w").write("\n".join(head + out))

@@ -497,6 +497,10 @@ GNN_API int gnn_plan_reserve(gnn_plan *plan, int64_t F);
 GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, int op, int backward, int64_t F,
                              int dtype, void *stream);
 
+/* 1: the last gnn_plan_prepare found no room for its tables of the most-gathered sources, so the calls that it prepared
+ * gather in place; with room again (a caching allocator may be sitting on it) another gnn_plan_prepare makes them.  Else 0. */
+GNN_API int gnn_plan_lacks_room(const gnn_plan *plan);
+
 /* Sets the source-blocking parameters of a plan (before its first hot call or gnn_plan_prepare;
  * later calls return GNN_ERR_UNSUPPORTED once the layout is built).  NULL = automatic. */
 GNN_API int gnn_plan_set_blocking(gnn_plan *plan, const gnn_blocking_params *params /* host */);

@@ -42,7 +42,7 @@ EXPORTED_SYMBOLS = (
     "gnn_validate_csr", "gnn_plan_default_params", "gnn_plan_create", "gnn_plan_destroy",
     "gnn_graph_build", "gnn_release_cached_memory",
     "gnn_plan_sizes", "gnn_plan_export", "gnn_plan_gather_share", "gnn_plan_workspace_bytes", "gnn_plan_reserve",
-    "gnn_plan_prepare", "gnn_plan_set_blocking", "gnn_plan_bind_edge_weights", "gnn_plan_blocked_sizes", "gnn_plan_bit_rows",
+    "gnn_plan_prepare", "gnn_plan_lacks_room", "gnn_plan_set_blocking", "gnn_plan_bind_edge_weights", "gnn_plan_blocked_sizes", "gnn_plan_bit_rows",
     "gnn_plan_export_blocked",
     "gnn_ap_fwd", "gnn_ap_bwd_vertex", "gnn_ap_bwd_vertex_arg", "gnn_ap_bwd_vertex_arg_edges", "gnn_ap_bwd_edge",
     "gnn_matmul", "gnn_matmul_workspace_bytes",
@@ -137,6 +137,7 @@ def load_library() -> ctypes.CDLL:
         lib.gnn_plan_workspace_bytes.restype = i64
         lib.gnn_plan_reserve.argtypes = [vp, i64]
         lib.gnn_plan_prepare.argtypes = [vp, vp, i32, i32, i64, i32, vp]
+        lib.gnn_plan_lacks_room.argtypes = [vp]
         lib.gnn_plan_set_blocking.argtypes = [vp, ctypes.POINTER(GnnBlockingParams)]
         lib.gnn_plan_bind_edge_weights.argtypes = [vp, vp, vp]
         lib.gnn_plan_blocked_sizes.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(i64), ctypes.POINTER(i64),
@@ -327,8 +328,17 @@ class Plan:
 
     def prepare(self, indices: torch.Tensor, op: int, backward: bool, F: int, dtype=torch.float32, stream=None) -> None:
         code = GNN_BF16 if dtype == torch.bfloat16 else GNN_F32
-        _call_allocating("gnn_plan_prepare", lambda: load_library().gnn_plan_prepare(
-            self.handle, _ptr(indices), int(op), 1 if backward else 0, int(F), code, _stream(stream)))
+        lib = load_library()
+
+        def call():
+            return lib.gnn_plan_prepare(self.handle, _ptr(indices), int(op), 1 if backward else 0, int(F), code, _stream(stream))
+
+        _call_allocating("gnn_plan_prepare", call)
+        # tables without room are no error, but torch's caching allocator may be sitting on it, as above
+        if lib.gnn_plan_lacks_room(self.handle) and torch.cuda.memory_reserved() > torch.cuda.memory_allocated():
+            torch.cuda.synchronize()
+            torch.cuda.empty_cache()
+            _check("gnn_plan_prepare", call())
 
 
 def gnn_plan_default_params() -> GnnPlanParams:

@@ -157,6 +157,7 @@ struct gnn_plan {
     int32_t *blk_hot_vertices = nullptr;
     int32_t *blk_cold_vertices = nullptr;
     int64_t blk_cold_begin = 0;
+    bool hot_lacks_room = false;      // gnn_plan_lacks_room
     uint64_t hot_ready[2][5][5] = {}; // what calls can use: [type][factor 0 ... 3 or weights], bit `lines`
     gnn_grown blk_partial;            // fp32 partial sums of one launch: [slices][blk_n_pieces][floats per line]
     gnn_tiles tiles[7];               // for lines of 128, 64 and 32 bytes of fp32, then of bf16; [GNN_TILES_PLAIN]: see gnn_plan_tiles

@@ -748,6 +748,7 @@ bool gnn_plan_hot_ready(gnn_plan *plan, const void *indptr, const int32_t *indic
     if (rc != GNN_OK) {
         (void)hipGetLastError();
         before.restore(plan);
+        plan->hot_lacks_room |= rc == GNN_ERR_ALLOC;
         return false;
     }
     word |= bit;
@@ -792,11 +793,14 @@ static int prepare_layout(gnn_plan *plan, const int32_t *indices, int mode, int6
     return gnn_plan_tile_coef_room(plan, tl, stream);
 }
 
+extern "C" GNN_API int gnn_plan_lacks_room(const gnn_plan *plan) { return plan && plan->hot_lacks_room ? 1 : 0; }
+
 extern "C" GNN_API int gnn_plan_prepare(gnn_plan *plan, const int32_t *indices, int op, int backward, int64_t F,
                                         int dtype, void *stream_v) {
     if (!plan || F < 0 || op < GNN_SUM || op > GNN_SAGE_GCN) return GNN_ERR_INVALID_ARG;
     if (dtype != GNN_F32 && dtype != GNN_BF16) return GNN_ERR_INVALID_ARG;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
+    plan->hot_lacks_room = false;
     int rc = gnn_plan_reserve(plan, F);
     const int esz = dtype == GNN_BF16 ? 2 : 4;
     const int mode = (op == GNN_MEAN && backward) ? 1 : (op == GNN_GCN_SYM ? 2 : ((op == GNN_SAGE_GCN && backward) ? 3 : 0));

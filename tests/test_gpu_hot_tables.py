@@ -178,6 +178,27 @@ def test_nothing_is_left_of_tables_that_there_is_no_room_for():
     assert g.plan_fwd.blocked_sizes()[2] > 0 and not torch.equal(_call(g, x, gnn.GNN_SUM, False), y0)
 
 
+def test_memory_that_torch_has_cached_is_room_for_tables():
+    """The device is full of blocks that torch's allocator keeps for later: preparing hands them back to the driver and builds the tables."""
+    g = _graph(1800000, 26000000)
+    x = _normal(13, g.n, 100)
+    y0 = _call(g, x, gnn.GNN_SUM, False, IN_PLACE)
+    y = torch.empty_like(y0)
+    torch.cuda.synchronize()
+    gnn.gnn_release_cached_memory()
+    filler = [torch.empty(torch.cuda.mem_get_info()[0] - (2 << 30), dtype=torch.uint8, device="cuda")]
+    while torch.cuda.mem_get_info()[0] > 260 << 20:
+        filler.append(torch.empty(32 << 20, dtype=torch.uint8, device="cuda"))
+    _prepare(g, 100, gnn.GNN_SUM)
+    assert g.plan_fwd.blocked_sizes()[2] == 0 and gnn.load_library().gnn_plan_lacks_room(g.plan_fwd.handle) == 1
+    del filler
+    assert torch.cuda.mem_get_info()[0] < 520 << 20
+    _prepare(g, 100, gnn.GNN_SUM)
+    assert g.plan_fwd.blocked_sizes()[2] > 0 and gnn.load_library().gnn_plan_lacks_room(g.plan_fwd.handle) == 0
+    assert not torch.equal(_call(g, x, gnn.GNN_SUM, False, out=y), y0)
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("prepared", [False, True])
 def test_packed_copies_of_all_rows(prepared):
     """A plan whose blocks a call over a packed copy has made has them as for any graph, tables for the last one's sources included, and its other calls
